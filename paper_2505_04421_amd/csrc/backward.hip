@@ -30,8 +30,7 @@
 //     (two-feature dot products, fp32 sums): inside a group of K tokens (InnerTrans: K x K scores
 //     per head), and over a user's own rows under the mask of Eq. 8 (reduced stack).
 // Padded token rows are never read and cost only the zeros written for them.
-#include "../../include/longer.h"
-#include "device.h"
+#include "bw_grads.h"
 
 #include <cstdio>
 
@@ -44,11 +43,10 @@ int inner_chain_f32(const longer_config* cfg, const longer_block* inner, int lay
 namespace bw {
 
 constexpr int kMaxGroup = 32;   // K <= 32
-constexpr int kComputeUnits = 256;
 
 // ------------------------------------------------------------------------------------
 // GEMM  C[M, N] = A[M, Kc] B[Kc, N]  (bf16 operands, fp32 accumulation)
-//   A_KC: A is stored [M][Kc] (contraction contiguous), else [Kc][M];
+//   A is stored [M][Kc] (contraction contiguous);
 //   B_KC: B is stored [N][Kc] (contraction contiguous), else [Kc][N].
 // Workgroup tile 128 x 128, contraction step 32, four waves in 2 x 2, each 64 x 64 (2 x 2 MFMA
 // tiles of 32 x 32).  Requirements checked by the host: strides multiples of 8 elements,
@@ -61,44 +59,19 @@ enum Epilogue {
   EPI_ACT = 2,       // out[m][n] = bf16(v), out2[m][n] = bf16(act(v)), v = acc + bias[n]
   EPI_DACT = 3,      // out[m][n] = bf16(acc * act'(pre[m][n]))
   EPI_F32 = 5,       // outf[m][n] = acc + bias[n]
-  EPI_FFN_MID = 6,   // two products in one launch, v = A B + bias and g = A2 B2 (same shapes):
+  EPI_FFN_MID = 6    // two products in one launch, v = A B + bias and g = A2 B2 (same shapes):
                      // out[m][n] = bf16(g * act'(v)), out2[m][n] = bf16(act(v)); v itself is not stored
-  EPI_PARTIAL = 4    // parameter gradients: the contraction (over the tokens) is dealt to slices, one workgroup per
-                     // tile and slice; outf[slice][m][n] = acc, summed afterwards by bw_reduce_kernel (out2, if
-                     // given: [slice][n] column sums of B, the bias gradient's partials)
 };
 
-// Padded token rows (row r = u L + pos with pos >= the user's length) carry no gradient.  With the
-// batch's geometry at hand a kernel leaves them out: row GEMMs skip tiles without a valid row, the
-// gradient GEMMs read them as zeros and pass over steps that hold nothing else, the LayerNorm kernels
-// write zeros for them.  L = 0: every row counts (the reduced stack's rows).
-struct RowsValid { const int32_t* lens; int L; };
-__device__ __forceinline__ bool row_valid(const RowsValid& v, int r) {
-  if (v.L == 0 || v.lens == nullptr) return true;
-  const int u = r / v.L;
-  return r - u * v.L < v.lens[u];
-}
-// any valid row in [r0, r1)?
-__device__ __forceinline__ bool rows_any_valid(const RowsValid& v, int r0, int r1) {
-  if (v.L == 0 || v.lens == nullptr) return true;
-  for (int u = r0 / v.L; u * v.L < r1; ++u) {
-    const int first = max(r0, u * v.L) - u * v.L;
-    if (first < v.lens[u]) return true;
-  }
-  return false;
-}
-
 struct GemmArgs {
-  RowsValid rows;             // of the token dimension (M of a row GEMM, the contraction of a gradient GEMM)
+  RowsValid rows;             // of the token dimension M
   const __bf16* A; const __bf16* B;
   int lda, ldb;
   int M, N, Kc;
-  int nsplit;                 // gradient GEMM: number of slices the contraction steps are dealt to
   int epi, act;
   void* out; void* out2; int ldo;
   const __bf16* bias; const float* res; const __bf16* pre;
   const __bf16* A2; const __bf16* B2; int lda2, ldb2;   // the second product of a two-product launch (EPI_FFN_MID)
-  int pstride, pstride2;      // EPI_PARTIAL: floats from one slice's partial result to the next (matrix, bias)
 };
 
 // Phi(v) = (1 + erf(v / sqrt 2)) / 2 and exp(-v^2 / 2) from one exponential: for z >= 0,
@@ -149,11 +122,12 @@ constexpr int kStagePitch = 68;         // floats per row of the epilogue's stag
 // KS: contraction elements per step.  Every launch uses 32: steps of 64 and 128 (one LDS buffer per operand
 // at 128) were measured for the two-product launch, whose contraction is only the model width, and
 // changed nothing (6.49 - 6.56 ms per merge backward at the headline shape for the three widths).
-template <bool A_KC, bool B_KC, bool DUAL = false, int KS = 32>
-__global__ __launch_bounds__(256, DUAL ? 2 : (A_KC ? 4 : 3)) void bw_gemm_kernel(GemmArgs g) {
-  static_assert(KS == 32 || (A_KC && B_KC), "wide steps: contraction-contiguous operands only");
+template <bool B_KC, bool DUAL = false, int KS = 32>
+__global__ __launch_bounds__(256, DUAL ? 2 : 4) void bw_gemm_kernel(GemmArgs g) {
+  static_assert(KS == 32 || B_KC, "wide steps: contraction-contiguous operands only");
   constexpr int kPitchKC = KS + 8;            // elements per row of a contraction-contiguous LDS tile (8 pad)
-  constexpr int kTileElems = 128 * kPitchKC;  // >= KS * 128 of the strided form
+  constexpr int kPitchT = 144;                // the strided form's row pitch (see bw_wgrad_kernel)
+  constexpr int kTileElems = 128 * kPitchKC;  // >= KS * kPitchT of the strided form
   constexpr int CPR = KS / 8;                 // 16-byte chunks per tile row (contraction-contiguous form)
   constexpr int NCH = KS / 16;                // chunks per thread and operand tile
   constexpr int NBUF = KS >= 128 ? 1 : 2;
@@ -163,24 +137,14 @@ __global__ __launch_bounds__(256, DUAL ? 2 : (A_KC ? 4 : 3)) void bw_gemm_kernel
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wm = w & 1, wn = w >> 1, hi = lane >> 5, l32 = lane & 31;
   // Tile order.  Workgroups go to the 8 accelerator dies round-robin by index, each die with an L2 of
-  // its own.  Row GEMMs: the N tiles of one M tile (which share the A rows) get consecutive slots
-  // on one die.  Split GEMMs (parameter gradients): all tiles of one slice of the contraction
-  // (which share both operands' rows) do, and the slices are spread over the dies.
+  // its own: the N tiles of one M tile (which share the A rows) get consecutive slots on one die.
   const int ntn = (g.N + 127) / 128, ntm = (g.M + 127) / 128;
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const bool split = g.epi == EPI_PARTIAL;
-  const int inner = split ? ntm * ntn : ntn;
-  const int outer = (slot / inner) * 8 + xcd, in = slot % inner;
-  if (outer >= (split ? g.nsplit : ntm)) return;
-  const int mt = split ? in / ntn : outer, nt_ = in % ntn;
+  const int mt = (slot / ntn) * 8 + xcd, nt_ = slot % ntn;
+  if (mt >= ntm) return;
   const int m0 = mt * 128, n0 = nt_ * 128;
-  // contraction steps of 32: a row GEMM takes them all; slice `outer` of a gradient GEMM takes every
-  // nsplit-th step, so that every slice samples the whole batch (long and short users alike)
-  const int kstride = split ? g.nsplit : 1, kfirst = split ? outer : 0;
-  const int ksteps = (g.Kc + KS - 1) / KS;
-  const int kend = g.Kc;
-  if (!split && !rows_any_valid(g.rows, m0, min(g.M, m0 + 128))) return;   // a tile of padded rows: nobody reads its result
-  const int nk = ksteps > kfirst ? (ksteps - kfirst + kstride - 1) / kstride : 0;
+  const int nk = (g.Kc + KS - 1) / KS, kend = g.Kc;
+  if (!rows_any_valid(g.rows, m0, min(g.M, m0 + 128))) return;   // a tile of padded rows: nobody reads its result
 
   constexpr int NPH = DUAL ? 2 : 1;     // products of the launch
   f32x16 accs[NPH][2][2];
@@ -195,25 +159,12 @@ __global__ __launch_bounds__(256, DUAL ? 2 : (A_KC ? 4 : 3)) void bw_gemm_kernel
   const __bf16* opA = g.A; const __bf16* opB = g.B;
   int ldA = g.lda, ldB = g.ldb;
 
-  // Split GEMM with a bias gradient asked for (out2): the column sums of B over the slice are one more
-  // product, ones[32, Kc] B, taken by the waves that hold the first 32 rows of the first M tile;
-  // every row of its result is the column sum.
-  const bool bias_sum = split && g.out2 != nullptr && mt == 0 && wm == 0;
-  f32x16 accb[2];
-  bf16x8 ones;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.f;
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) accb[b][r] = 0.f;
-
   // Operand tiles travel global -> registers -> LDS.  One tile = 512 chunks of 16 bytes, two per
   // thread.  (Keeping the loads of four steps in flight was measured: 188 registers, two waves per
   // SIMD instead of four, every GEMM slower.)
   bf16x8 ra[1][NCH], rb[1][NCH];
   auto gload = [&](int kt, bf16x8* pa, bf16x8* pb) {
-    const int k0 = (kfirst + kt * kstride) * KS;
+    const int k0 = kt * KS;
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
       const int c = tid + 256 * i;
@@ -221,14 +172,10 @@ __global__ __launch_bounds__(256, DUAL ? 2 : (A_KC ? 4 : 3)) void bw_gemm_kernel
 #pragma unroll
       for (int e = 0; e < 8; ++e) z[e] = (__bf16)0.f;
       pa[i] = z; pb[i] = z;
-      if (A_KC) {
+      {
         const int row = c / CPR, kc = c % CPR;
         const int gr = m0 + row, gk = k0 + 8 * kc;
         if (gr < g.M && gk < kend) pa[i] = *(const bf16x8*)(opA + (size_t)gr * ldA + gk);
-      } else {
-        const int kr = c >> 4, xc = c & 15;
-        const int gk = k0 + kr, gx = m0 + 8 * xc;
-        if (gk < kend && gx < g.M && (!split || row_valid(g.rows, gk))) pa[i] = *(const bf16x8*)(opA + (size_t)gk * ldA + gx);
       }
       if (B_KC) {
         const int row = c / CPR, kc = c % CPR;
@@ -237,7 +184,7 @@ __global__ __launch_bounds__(256, DUAL ? 2 : (A_KC ? 4 : 3)) void bw_gemm_kernel
       } else {
         const int kr = c >> 4, xc = c & 15;
         const int gk = k0 + kr, gx = n0 + 8 * xc;
-        if (gk < kend && gx < g.N && (!split || row_valid(g.rows, gk))) pb[i] = *(const bf16x8*)(opB + (size_t)gk * ldB + gx);
+        if (gk < kend && gx < g.N) pb[i] = *(const bf16x8*)(opB + (size_t)gk * ldB + gx);
       }
     }
   };
@@ -245,43 +192,32 @@ __global__ __launch_bounds__(256, DUAL ? 2 : (A_KC ? 4 : 3)) void bw_gemm_kernel
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
       const int c = tid + 256 * i;
-      if (A_KC) *(bf16x8*)&sA(buf)[(c / CPR) * kPitchKC + 8 * (c % CPR)] = pa[i];
-      else      *(bf16x8*)&sA(buf)[(c >> 4) * 128 + 8 * (c & 15)] = pa[i];
+      *(bf16x8*)&sA(buf)[(c / CPR) * kPitchKC + 8 * (c % CPR)] = pa[i];
       if (B_KC) *(bf16x8*)&sB(buf)[(c / CPR) * kPitchKC + 8 * (c % CPR)] = pb[i];
-      else      *(bf16x8*)&sB(buf)[(c >> 4) * 128 + 8 * (c & 15)] = pb[i];
+      else      *(bf16x8*)&sB(buf)[(c >> 4) * kPitchT + 8 * (c & 15)] = pb[i];
     }
   };
   // fragment of the 32 x 16 operand slice: lane (x = l32, hi) holds contraction slots 8 hi .. 8 hi + 7
-  auto frag = [&](const __bf16* s, bool kc, int x, int ks) -> bf16x8 {
-    bf16x8 f;
-    if (kc) {
-      f = *(const bf16x8*)&s[x * kPitchKC + 16 * ks + 8 * hi];
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) f[e] = s[(16 * ks + 8 * hi + e) * 128 + x];
-    }
-    return f;
+  const int foff = frag_t_offset<kPitchT>(lane);
+  auto frag = [&](const __bf16* s, int x, int ks) -> bf16x8 { return *(const bf16x8*)&s[(x + l32) * kPitchKC + 16 * ks + 8 * hi]; };
+  auto fragB = [&](const __bf16* s, int x, int ks) -> bf16x8 {
+    if constexpr (B_KC) return frag(s, x, ks);
+    else return frag_t<kPitchT>(s + foff + 16 * ks * kPitchT + x);
   };
 
   // Contraction steps, two LDS buffers: step's tile goes to LDS (the buffer was last read two steps ago,
   // which every thread left before the previous step's barrier), the registers are refilled with the
-  // next step's tile, barrier, MFMAs.  A gradient GEMM passes over steps whose 32 token rows are all
-  // padding (the test is the same for the whole workgroup).
-  auto next_step = [&](int kt) {
-    if (split)
-      while (kt < nk && !rows_any_valid(g.rows, (kfirst + kt * kstride) * KS, min(kend, (kfirst + kt * kstride) * KS + KS))) ++kt;
-    return kt;
-  };
+  // next step's tile, barrier, MFMAs.
   int buf = 0;
 #pragma unroll
   for (int ph = 0; ph < NPH; ++ph) {
   f32x16 (&acc)[2][2] = accs[ph];
-  int kt = next_step(0);
+  int kt = 0;
   if (kt < nk && !(DUAL && ph == 1)) gload(kt, ra[0], rb[0]);   // (the second product's first tile is on its way already)
   while (kt < nk) {
     if (NBUF == 1) __syncthreads();          // the one buffer is still being read by the step before
     sstore(buf, ra[0], rb[0]);
-    const int kn = next_step(kt + 1);
+    const int kn = kt + 1;
     if (kn < nk) {
       gload(kn, ra[0], rb[0]);
     } else if (DUAL && ph == 0) {            // last step of the first product: request the second product's first tile
@@ -294,18 +230,14 @@ __global__ __launch_bounds__(256, DUAL ? 2 : (A_KC ? 4 : 3)) void bw_gemm_kernel
       bf16x8 fa[2], fb[2];
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        fa[t] = frag(sA(buf), A_KC, 64 * wm + 32 * t + l32, ks);
-        fb[t] = frag(sB(buf), B_KC, 64 * wn + 32 * t + l32, ks);
+        fa[t] = frag(sA(buf), 64 * wm + 32 * t, ks);
+        fb[t] = fragB(sB(buf), 64 * wn + 32 * t, ks);
       }
 #pragma unroll
       for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b)
           acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
-      if (!A_KC && !B_KC && bias_sum) {
-#pragma unroll
-        for (int b = 0; b < 2; ++b) accb[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, fb[b], accb[b], 0, 0, 0);
-      }
     }
     buf ^= NBUF - 1;
     kt = kn;
@@ -313,13 +245,6 @@ __global__ __launch_bounds__(256, DUAL ? 2 : (A_KC ? 4 : 3)) void bw_gemm_kernel
   }
   f32x16 (&acc)[2][2] = accs[0];
 
-  if (!A_KC && !B_KC && bias_sum && hi == 0) {
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int n = n0 + 64 * wn + 32 * b + l32;
-      if (n < g.N) ((float*)g.out2)[(size_t)outer * g.pstride2 + n] = accb[b][0];     // row 0 of the ones product
-    }
-  }
   float* stage = (float*)smem + w * (32 * kStagePitch);
   static_assert(4 * 32 * kStagePitch * 4 <= 2 * NBUF * kTileElems * 2, "staging area fits the operand buffers");
   // Loads and stores leave one in-order queue: a load that follows a store is not back before the store
@@ -415,13 +340,9 @@ __global__ __launch_bounds__(256, DUAL ? 2 : (A_KC ? 4 : 3)) void bw_gemm_kernel
         }
         *(bf16x8*)((__bf16*)g.out + o) = ob;
         *(bf16x8*)((__bf16*)g.out2 + o) = oa;
-      } else if (g.epi == EPI_F32) {
+      } else {
         *(f32x4*)((float*)g.out + o) = *(const f32x4*)&v[0];
         *(f32x4*)((float*)g.out + o + 4) = *(const f32x4*)&v[4];
-      } else {
-        float* po = (float*)g.out + (size_t)outer * g.pstride + o;
-        *(f32x4*)po = *(const f32x4*)&v[0];
-        *(f32x4*)(po + 4) = *(const f32x4*)&v[4];
       }
     }
   }
@@ -690,7 +611,7 @@ __global__ __launch_bounds__(256) void bw_ln_fwd_kernel(const float* __restrict_
 // LayerNorm backward for y = LN(x) g + b with upstream dn = dL/dy (bf16) and the gradient dres that
 // reaches x through the residual connection (NULL: none): dx_out = dres + dLN, also stored as bf16 (dxb, may be
 // NULL); the block's share of dg[e] = sum_r dn xhat and db[e] = sum_r dn goes to part[block][2][D]
-// (bw_reduce_kernel sums the blocks).
+// (bw_reduce_jobs_kernel sums the blocks).
 template <int LPR>
 __global__ __launch_bounds__(256) void bw_ln_bwd_kernel(const __bf16* __restrict__ dn, const float* __restrict__ x,
                                                         const __bf16* __restrict__ gam, const float* __restrict__ dres,
@@ -1095,36 +1016,6 @@ __global__ __launch_bounds__(256) void bw_concat_qkv_kernel(const __bf16* wq, co
       const int j = col / d, c = col - j * d;
       const __bf16* b = j == 0 ? bq : (j == 1 ? bk : bv);
       bcat[col] = b[c];
-    }
-  }
-}
-
-// out[i] += sum over the slices s of part[s][i], i < count (count a multiple of 4; out starts at zero).
-// Thread (x, y) of a 64 x 4 block sums every fourth slice of four adjacent outputs inside the block's
-// share of the slices (blockIdx.y of gridDim.y shares), the four partial sums meet in LDS, and the
-// block adds its sum with one atomic per output (a plain store when there is one share and the result
-// is not to be added to what out holds).
-__global__ __launch_bounds__(256) void bw_reduce_kernel(const float* __restrict__ part, int nsplit, int count, float* out,
-                                                        int accumulate) {
-  __shared__ f32x4 red[4][64];
-  const int x = threadIdx.x & 63, y = threadIdx.x >> 6;
-  const int i = (blockIdx.x * 64 + x) * 4;
-  const int per = (nsplit + gridDim.y - 1) / gridDim.y;
-  const int s0 = blockIdx.y * per, s1 = min(nsplit, s0 + per);
-  f32x4 s = {0.f, 0.f, 0.f, 0.f};
-  if (i < count) {
-#pragma unroll 4
-    for (int sl = s0 + y; sl < s1; sl += 4) s += *(const f32x4*)(part + (size_t)sl * count + i);
-  }
-  red[y][x] = s;
-  __syncthreads();
-  if (y == 0 && i < count) {
-    const f32x4 t = red[0][x] + red[1][x] + red[2][x] + red[3][x];
-    if (gridDim.y == 1 && !accumulate) {
-      *(f32x4*)(out + i) = t;
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) unsafeAtomicAdd(out + i + e, t[e]);
     }
   }
 }
@@ -1762,12 +1653,12 @@ static GradLayout grad_layout(int d, int f) {
   g.w1 = take((size_t)d * f); g.b1 = take(f);
   g.w2 = take((size_t)f * d); g.b2 = take(d);
   g.total = o;
-  return g;      // ln*_b follows ln*_g directly: ln_bwd writes the two as one vector
+  return g;      // ln*_b follows ln*_g directly: their partial sums are one vector
 }
 
-// tiles x slices of a split GEMM <= kMaxPartials, each a 128 x 128 fp32 tile
-constexpr int kMaxPartials = 512;
-constexpr size_t kPartialBytes = (size_t)kMaxPartials * 128 * 128 * 4;
+// most workgroups of a LayerNorm backward launch, each with a partial [2][d] of the gain / shift gradients
+constexpr int kMaxLnBlocks = 2048;
+static unsigned ln_blocks(size_t rows) { return (unsigned)((rows + 3) / 4 > kMaxLnBlocks ? kMaxLnBlocks : (rows + 3) / 4); }
 
 struct Workspace {
   size_t wcat, bcat;                       // per layer: [d][3d] bf16, [3d] bf16
@@ -1775,10 +1666,33 @@ struct Workspace {
   size_t w1t, wcatt, wot;                  // per layer, transposed: W1 [f][d], [wq | wk | wv] [3d][d], W_O [d][d] (bf16)
   size_t n1, qkv, o, xmid, n2, a;          // one block's recomputed intermediates
   size_t dy, dyb, dh, dn, dxm, dxmb, dob, dqkv, stat;
-  size_t part, bpart;                      // partial parameter gradients of one split GEMM (matrix, bias)
+  size_t part, lnpart;                     // partial parameter gradients of one block: matrices, LayerNorms (ln1, ln2)
   size_t fwd, fwd_bytes, ztmp;             // the fused forward kernel's scratch and output when it recomputes block inputs
   size_t total;
 };
+// The gradients of an InnerTrans block's four products (Q / K / V side by side), all over the raw token rows
+static WgradBatch block_wgrads(int d, int f, size_t ntok, RowsValid rv, const __bf16* n1, const __bf16* dqkv, const __bf16* o,
+                               const __bf16* dxmb, const __bf16* n2, const __bf16* dh, const __bf16* a, const __bf16* dyb, float* g) {
+  const GradLayout gl = grad_layout(d, f);
+  WgradBatch w(d, ntok);
+  w.add(a, f, f, dyb, d, d, d, ntok, rv, g + gl.w2);
+  w.add(n2, d, d, dh, f, f, f, ntok, rv, g + gl.w1);
+  w.add(o, d, d, dxmb, d, d, d, ntok, rv, g + gl.wo);
+  w.add(n1, d, d, dqkv, 3 * d, 3 * d, d, ntok, rv, g + gl.wq);
+  return w;
+}
+static int launch(WgradBatch& w, float* part, hipStream_t st) {
+  w.place(part);
+  const unsigned grid = (unsigned)((w.a.nslices + 7) / 8 * 8 * w.a.tiles);
+  if (w.tb == 128) bw_wgrad_kernel<128><<<grid, 256, 0, st>>>(w.a);
+  else bw_wgrad_kernel<64><<<grid, 256, 0, st>>>(w.a);
+  return hipGetLastError() == hipSuccess ? 0 : api_error(LONGER_ERR_HIP, "parameter gradient launch failed");
+}
+static int launch(const ReduceBatch& r, hipStream_t st) {
+  bw_reduce_jobs_kernel<<<(unsigned)r.blocks, 256, 0, st>>>(r.a);
+  return hipGetLastError() == hipSuccess ? 0 : api_error(LONGER_ERR_HIP, "gradient reduction launch failed");
+}
+
 static Workspace workspace(int layers, size_t ntok, int d, int f, int heads, size_t fwd_bytes, size_t ztmp_bytes) {
   Workspace w;
   size_t o = 0;
@@ -1804,8 +1718,8 @@ static Workspace workspace(int layers, size_t ntok, int d, int f, int heads, siz
   w.dob = take(ntok * d * 2);
   w.dqkv = take(ntok * 3 * d * 2);
   w.stat = take(ntok * heads * 8);
-  w.part = take(kPartialBytes);
-  w.bpart = take((size_t)kMaxPartials * 2048 * 4);
+  w.part = take(block_wgrads(d, f, ntok, RowsValid{}, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr).place(nullptr) * 4);
+  w.lnpart = take((size_t)2 * kMaxLnBlocks * 2 * d * 4);
   w.fwd = take(fwd_bytes);
   w.fwd_bytes = fwd_bytes;
   w.ztmp = take(ztmp_bytes);
@@ -1861,20 +1775,11 @@ static int launched(const char* what) {
   return hipGetLastError() == hipSuccess ? 0 : api_error(LONGER_ERR_HIP, "%s launch failed", what);
 }
 
-static int reduce(hipStream_t st, const float* part, int nsplit, int count, float* out, bool accumulate = false) {
-  int shares = nsplit / 32;                 // at least 32 slices per block
-  shares = shares < 1 ? 1 : (shares > 64 ? 64 : shares);
-  bw_reduce_kernel<<<dim3((count / 4 + 63) / 64, shares), 256, 0, st>>>(part, nsplit, count, out, accumulate ? 1 : 0);
-  return launched("gradient reduction");
-}
-
-static int gemm(hipStream_t st, bool a_kc, bool b_kc, GemmArgs g, int splits) {
+static int gemm(hipStream_t st, bool b_kc, GemmArgs g) {
   if (!aligned16(g.A) || !aligned16(g.B) || g.lda % 8 || g.ldb % 8) return api_error(LONGER_ERR_ARG, "backward GEMM operand misaligned");
   const int ntm = (g.M + 127) / 128, ntn = (g.N + 127) / 128;
-  g.nsplit = splits;
-  const int outer = g.epi == EPI_PARTIAL ? splits : ntm, inner = g.epi == EPI_PARTIAL ? ntm * ntn : ntn;
-  dim3 grid((unsigned)(((outer + 7) / 8) * 8 * inner));            // see the tile order in the kernel
-  if (a_kc && b_kc && splits == 1 && (g.Kc == 32 || g.Kc == 64 || g.Kc == 128) &&
+  dim3 grid((unsigned)(((ntm + 7) / 8) * 8 * ntn));            // see the tile order in the kernel
+  if (b_kc && (g.Kc == 32 || g.Kc == 64 || g.Kc == 128) &&
       (g.epi == EPI_FFN_MID || g.epi == EPI_BF16 || g.epi == EPI_RES_F32 || g.epi == EPI_F32)) {
     if (g.epi == EPI_FFN_MID && (!aligned16(g.A2) || !aligned16(g.B2) || g.lda2 % 8 || g.ldb2 % 8))
       return api_error(LONGER_ERR_ARG, "backward GEMM operand misaligned");
@@ -1890,13 +1795,11 @@ static int gemm(hipStream_t st, bool a_kc, bool b_kc, GemmArgs g, int splits) {
     return launched("backward row GEMM");
   }
   if (g.epi == EPI_FFN_MID) {
-    if (!(a_kc && b_kc) || !aligned16(g.A2) || !aligned16(g.B2) || g.lda2 % 8 || g.ldb2 % 8)
+    if (!b_kc || !aligned16(g.A2) || !aligned16(g.B2) || g.lda2 % 8 || g.ldb2 % 8)
       return api_error(LONGER_ERR_ARG, "backward GEMM operand misaligned");
-    bw_gemm_kernel<true, true, true><<<grid, 256, 0, st>>>(g);
-  } else if (a_kc && b_kc) bw_gemm_kernel<true, true><<<grid, 256, 0, st>>>(g);
-  else if (a_kc && !b_kc) bw_gemm_kernel<true, false><<<grid, 256, 0, st>>>(g);
-  else if (!a_kc && !b_kc) bw_gemm_kernel<false, false><<<grid, 256, 0, st>>>(g);
-  else return api_error(LONGER_ERR_ARG, "backward GEMM form not built");
+    bw_gemm_kernel<true, true><<<grid, 256, 0, st>>>(g);
+  } else if (b_kc) bw_gemm_kernel<true><<<grid, 256, 0, st>>>(g);
+  else bw_gemm_kernel<false><<<grid, 256, 0, st>>>(g);
   return launched("backward GEMM");
 }
 
@@ -1909,7 +1812,7 @@ static int gemm_rows(hipStream_t st, const __bf16* x, int kc, const __bf16* W, i
   g.rows = rows;
   g.A = x; g.lda = kc; g.B = W; g.ldb = ldb ? ldb : n; g.M = (int)ntok; g.N = n; g.Kc = kc;
   g.epi = epi; g.act = act; g.out = out; g.out2 = out2; g.ldo = n; g.bias = bias; g.res = res; g.pre = pre;
-  return gemm(st, true, false, g, 1);
+  return gemm(st, false, g);
 }
 // y = x W (+ epilogue) with W handed over transposed, wt [n][kc]: both operands contraction-contiguous
 static int gemm_rows_wt(hipStream_t st, const __bf16* x, int kc, const __bf16* wt, int n, size_t ntok, int epi,
@@ -1918,7 +1821,7 @@ static int gemm_rows_wt(hipStream_t st, const __bf16* x, int kc, const __bf16* w
   g.rows = rows;
   g.A = x; g.lda = kc; g.B = wt; g.ldb = kc; g.M = (int)ntok; g.N = n; g.Kc = kc;
   g.epi = epi; g.out = out; g.ldo = n; g.bias = bias; g.res = res;
-  return gemm(st, true, true, g, 1);
+  return gemm(st, true, g);
 }
 // dx = dy W^T: dy [ntok][kc], W [n][.. kc columns, pitch ldb] row-major (the forward's [in = n][out = kc])
 static int gemm_rows_t(hipStream_t st, const __bf16* dy, int kc, const __bf16* W, int n, size_t ntok, int epi, int act,
@@ -1927,7 +1830,7 @@ static int gemm_rows_t(hipStream_t st, const __bf16* dy, int kc, const __bf16* W
   g.rows = rows;
   g.A = dy; g.lda = kc; g.B = W; g.ldb = ldb ? ldb : kc; g.M = (int)ntok; g.N = n; g.Kc = kc;
   g.epi = epi; g.act = act; g.out = out; g.ldo = n; g.pre = pre;
-  return gemm(st, true, true, g, 1);
+  return gemm(st, true, g);
 }
 // The middle of the FFN's backward in one launch: v = x W1 + b1 (recomputed, not stored), g = dy W2^T,
 // a_out = bf16(act(v)), dh_out = bf16(g act'(v)).  x, dy [ntok][d]; w1t = W1 transposed, [f][d]; w2 [f][d].
@@ -1938,42 +1841,12 @@ static int gemm_ffn_mid(hipStream_t st, const __bf16* x, const __bf16* dy, int d
   g.A = x; g.lda = d; g.B = w1t; g.ldb = d; g.A2 = dy; g.lda2 = d; g.B2 = w2; g.ldb2 = d;
   g.M = (int)ntok; g.N = f; g.Kc = d;
   g.epi = EPI_FFN_MID; g.act = act; g.out = dh_out; g.out2 = a_out; g.ldo = f; g.bias = b1;
-  return gemm(st, true, true, g, 1);
+  return gemm(st, true, g);
 }
 static int transpose(hipStream_t st, const __bf16* in, __bf16* out, int rows, int cols) {
   bw_transpose_kernel<<<dim3((cols + 31) / 32, (rows + 31) / 32), 256, 0, st>>>(in, out, rows, cols);
   return launched("transpose");
 }
-// dW [m][n] = x^T dy: x [ntok][.. m columns, pitch lda], dy [ntok][.. n columns, pitch ldb]
-// and db [n] = column sums of dy
-static int gemm_wgrad(hipStream_t st, const __bf16* x, int lda, int m, const __bf16* dy, int ldb, int n, size_t ntok,
-                      float* part, float* bpart, float* dW, float* db, RowsValid rows = RowsValid{nullptr, 0}) {
-  GemmArgs g = {};
-  g.rows = rows;
-  g.A = x; g.lda = lda; g.B = dy; g.ldb = ldb; g.M = m; g.N = n; g.Kc = (int)ntok;
-  const int tiles = ((m + 127) / 128) * ((n + 127) / 128);
-  if (tiles > kMaxPartials) return api_error(LONGER_ERR_ARG, "parameter matrix %d x %d too large for the backward pass", m, n);
-  int splits = kMaxPartials / tiles;
-  const int most = (int)((ntok + 255) / 256);
-  if (splits > most) splits = most;
-  const int steps = (int)((ntok + 31) / 32);
-  if (splits > steps) splits = steps;
-  g.epi = EPI_PARTIAL; g.out = part; g.ldo = n;
-  // The bias gradient follows its matrix in every gradient buffer, and `bpart` follows `part` in every
-  // workspace: a slice's bias partial then goes right behind its matrix partial, and one reduction
-  // launch sums both.
-  const bool together = db == dW + (size_t)m * n && bpart == part + kPartialBytes / 4;
-  g.pstride = together ? m * n + n : m * n;
-  g.pstride2 = together ? m * n + n : n;
-  g.out2 = together ? part + (size_t)m * n : bpart;
-  int rc = gemm(st, false, false, g, splits);
-  if (rc) return rc;
-  if (together) return reduce(st, part, splits, m * n + n, dW);
-  rc = reduce(st, part, splits, m * n, dW);
-  if (rc) return rc;
-  return reduce(st, bpart, splits, n, db);
-}
-
 static void ln_fwd(hipStream_t st, unsigned grid, int d, const float* x, const __bf16* g, const __bf16* b, __bf16* out,
                    int ntok, float eps, RowsValid rows = RowsValid{nullptr, 0}) {
   switch (d) {
@@ -1983,18 +1856,16 @@ static void ln_fwd(hipStream_t st, unsigned grid, int d, const float* x, const _
     default: bw_ln_fwd_kernel<64><<<grid, 256, 0, st>>>(x, g, b, out, ntok, eps, rows); break;
   }
 }
-// dgb: the gain gradient [d] followed directly by the shift gradient [d]
+// part: the launch's partial gain / shift gradients, [grid][2 d]
 static int ln_bwd(hipStream_t st, unsigned grid, int d, const __bf16* dn, const float* x, const __bf16* g, const float* dres,
-                  float* dx, __bf16* dxb, float* part, float* dgb, int ntok, float eps, bool accumulate = false,
-                  RowsValid rows = RowsValid{nullptr, 0}) {
+                  float* dx, __bf16* dxb, float* part, int ntok, float eps, RowsValid rows = RowsValid{nullptr, 0}) {
   switch (d) {
     case 32: bw_ln_bwd_kernel<8><<<grid, 256, 0, st>>>(dn, x, g, dres, dx, dxb, part, ntok, eps, rows); break;
     case 64: bw_ln_bwd_kernel<16><<<grid, 256, 0, st>>>(dn, x, g, dres, dx, dxb, part, ntok, eps, rows); break;
     case 128: bw_ln_bwd_kernel<32><<<grid, 256, 0, st>>>(dn, x, g, dres, dx, dxb, part, ntok, eps, rows); break;
     default: bw_ln_bwd_kernel<64><<<grid, 256, 0, st>>>(dn, x, g, dres, dx, dxb, part, ntok, eps, rows); break;
   }
-  if (hipGetLastError() != hipSuccess) return api_error(LONGER_ERR_HIP, "LayerNorm backward launch failed");
-  return reduce(st, part, (int)grid, 2 * d, dgb, accumulate);
+  return launched("LayerNorm backward");
 }
 
 static unsigned flat_grid(size_t n) {
@@ -2025,12 +1896,10 @@ static int run(const longer_config* c, const longer_block* inner, const void* H,
   __bf16* dxmb = (__bf16*)(ws + w.dxmb); __bf16* dob = (__bf16*)(ws + w.dob); __bf16* dqkv = (__bf16*)(ws + w.dqkv);
   float2* stat = (float2*)(ws + w.stat);
   float* part = (float*)(ws + w.part);
-  float* bpart = (float*)(ws + w.bpart);
-  const unsigned ln_grid = (unsigned)((nt + 3) / 4 > 4096 ? 4096 : (nt + 3) / 4);   // 4096 x 2 x 256 floats fit `part`
+  float* lnpart[2] = {(float*)(ws + w.lnpart), (float*)(ws + w.lnpart) + (size_t)kMaxLnBlocks * 2 * d};
+  const unsigned ln_grid = ln_blocks(nt);
   const unsigned ah_grid = (unsigned)((nt * s.heads + 255) / 256);
 
-  bw_zero_kernel<<<flat_grid(gl.total * s.layers), 256, 0, st>>>(grads, gl.total * s.layers);
-  BW_TRY(launched("zero fill"));
   for (int l = 0; l < s.layers; ++l) {
     const longer_block& b = inner[l];
     bw_concat_qkv_kernel<<<64, 256, 0, st>>>((const __bf16*)b.wq, (const __bf16*)b.wk, (const __bf16*)b.wv, (const __bf16*)b.bq,
@@ -2079,12 +1948,9 @@ static int run(const longer_config* c, const longer_block* inner, const void* H,
     // FFN: y = xmid + act(n2 W1 + b1) W2 + b2; the hidden pre-activation is formed inside the launch
     // that takes its gradient, and only the activated values and the hidden gradient reach memory
     BW_TRY(gemm_ffn_mid(st, n2, dyb, d, w1t(l), (const __bf16*)b.w2, f, (const __bf16*)b.b1, nt, c->act, dh, a, rv));
-    BW_TRY(gemm_wgrad(st, a, f, f, dyb, d, d, nt, part, bpart, g + gl.w2, g + gl.b2, rv));
-    BW_TRY(gemm_wgrad(st, n2, d, d, dh, f, f, nt, part, bpart, g + gl.w1, g + gl.b1, rv));
     BW_TRY(gemm_rows_t(st, dh, f, (const __bf16*)b.w1, d, nt, EPI_BF16, 0, dn, nullptr, 0, rv));
-    BW_TRY(ln_bwd(st, ln_grid, d, dn, xmid, (const __bf16*)b.ln2_g, dy, dxm, dxmb, part, g + gl.ln2_g, (int)nt, c->ln_eps, false, rv));
+    BW_TRY(ln_bwd(st, ln_grid, d, dn, xmid, (const __bf16*)b.ln2_g, dy, dxm, dxmb, lnpart[1], (int)nt, c->ln_eps, rv));
     // attention: xmid = x + att W_O + b_O
-    BW_TRY(gemm_wgrad(st, o, d, d, dxmb, d, d, nt, part, bpart, g + gl.wo, g + gl.bo, rv));
     BW_TRY(gemm_rows_t(st, dxmb, d, (const __bf16*)b.wo, d, nt, EPI_BF16, 0, dob, nullptr, 0, rv));
     if (L % s.K == 0 && 256 % s.heads == 0 && (256 / s.heads) % s.K == 0) {     // every group inside one workgroup's rows
       group_attn(3, s.dh, s.K, ah_grid, st, qkv, dob, dqkv, stat, q, d, s.heads);
@@ -2093,15 +1959,19 @@ static int run(const longer_config* c, const longer_block* inner, const void* H,
       group_attn(2, s.dh, s.K, ah_grid, st, qkv, dob, dqkv, stat, q, d, s.heads);
     }
     BW_TRY(launched("group attention backward"));
-    const size_t wofs[3] = {gl.wq, gl.wk, gl.wv}, bofs[3] = {gl.bq, gl.bk, gl.bv};
-    for (int j = 0; j < 3; ++j) {
-      BW_TRY(gemm_wgrad(st, n1, d, d, dqkv + (size_t)j * d, 3 * d, d, nt, part, bpart, g + wofs[j], g + bofs[j], rv));
-    }
+    // every matrix of the block at once, now that all operands are there (dyb goes to the next block's below)
+    WgradBatch wg = block_wgrads(d, f, nt, rv, n1, dqkv, o, dxmb, n2, dh, a, dyb, g);
+    BW_TRY(launch(wg, part, st));
     BW_TRY(gemm_rows_t(st, dqkv, 3 * d, wcat(l), d, nt, EPI_BF16, 0, dn, nullptr, 0, rv));
     // the gradient of this block's input is the upstream gradient of the block before it
     float* dx = l ? dy : dH;
-    BW_TRY(ln_bwd(st, ln_grid, d, dn, xin(l), (const __bf16*)b.ln1_g, dxm, dx, l ? dyb : nullptr, part, g + gl.ln1_g,
-                  (int)nt, c->ln_eps, false, rv));
+    BW_TRY(ln_bwd(st, ln_grid, d, dn, xin(l), (const __bf16*)b.ln1_g, dxm, dx, l ? dyb : nullptr, lnpart[0],
+                  (int)nt, c->ln_eps, rv));
+    ReduceBatch rb;
+    rb.add(wg);
+    rb.add_ln(lnpart[0], (int)ln_grid, d, g + gl.ln1_g);
+    rb.add_ln(lnpart[1], (int)ln_grid, d, g + gl.ln2_g);
+    BW_TRY(launch(rb, st));
   }
   return 0;
 }
@@ -2116,10 +1986,36 @@ struct StackWs {
   size_t qdesc, kdesc, wcat, bcat;
   size_t Rx, xs;                          // cross-layer key rows; the layers' input rows ([layers + 1][rq][d], [0] = O)
   size_t n1q, n1k, qkv, kv, o, xmid, n2, h, a, stat;    // every layer's intermediates are kept (per_layer bytes apart):
-  size_t per_layer;                                     // the reduced stack is small, only the merge is recomputed
-  size_t dy, dyb, dh, dnq, dnk, dxm, dxmb, dob, dqkv, dkv, dR, part, bpart;
+  size_t dyb, dh, dxmb, dqkv;                           // the reduced stack is small, only the merge is recomputed; so
+  size_t per_layer;                                     // are the gradients that its parameter gradients contract
+  size_t dy, dnq, dnk, dxm, dob, dkv, dR, part, lnpart;
   size_t total;
 };
+// The gradients of every matrix of the stack in one batch: the self layers' (per_layer bytes and `per_main` floats
+// apart), then the cross layer's, whose keys and values contract over the key rows
+static WgradBatch stack_wgrads(const StackDims& s, const StackWs& w, const char* ws, float* grads, size_t cross, size_t self0, size_t per_main) {
+  const int d = s.d, f = s.f;
+  const GradLayout gl = grad_layout(d, f);
+  const RowsValid all = {nullptr, 0};
+  WgradBatch b(d, s.rq);
+  const long long ls = (long long)(w.per_layer / 2), os = (long long)per_main;
+  auto at = [&](size_t ofs, int l) { return (const __bf16*)(ws + ofs + (size_t)l * w.per_layer); };
+  auto side = [&](int l, int n, float* g) {
+    b.add(at(w.a, l), f, f, at(w.dyb, l), d, d, d, s.rq, all, g + gl.w2, n, ls, ls, os);
+    b.add(at(w.n2, l), d, d, at(w.dh, l), f, f, f, s.rq, all, g + gl.w1, n, ls, ls, os);
+    b.add(at(w.o, l), d, d, at(w.dxmb, l), d, d, d, s.rq, all, g + gl.wo, n, ls, ls, os);
+  };
+  if (s.layers > 1) {
+    float* g = grads + self0;
+    side(1, s.layers - 1, g);
+    b.add(at(w.n1q, 1), d, d, at(w.dqkv, 1), 3 * d, 3 * d, d, s.rq, all, g + gl.wq, s.layers - 1, ls, ls, os);
+  }
+  float* g = grads + cross;
+  side(0, 1, g);
+  b.add(at(w.n1q, 0), d, d, at(w.dqkv, 0), d, d, d, s.rq, all, g + gl.wq);
+  b.add(at(w.n1k, 0), d, d, (const __bf16*)(ws + w.dkv), 2 * d, 2 * d, d, s.rk, all, g + gl.wk);
+  return b;
+}
 static StackWs stack_ws(const StackDims& s, size_t fwd_bytes) {
   StackWs w;
   size_t o = 0;
@@ -2145,21 +2041,21 @@ static StackWs stack_ws(const StackDims& s, size_t fwd_bytes) {
   w.h = take(rq * f * 2);
   w.a = take(rq * f * 2);
   w.stat = take(rq * s.heads * 8);
+  w.dyb = take(rq * d * 2);
+  w.dh = take(rq * f * 2);
+  w.dxmb = take(rq * d * 2);
+  w.dqkv = take(rq * 3 * d * 2);
   w.per_layer = o - layer0;
   o += (size_t)(s.layers - 1) * w.per_layer;
   w.dy = take(rq * d * 4);
-  w.dyb = take(rq * d * 2);
-  w.dh = take(rq * f * 2);
   w.dnq = take(rq * d * 2);
   w.dnk = take(rk * d * 2);
   w.dxm = take(rq * d * 4);
-  w.dxmb = take(rq * d * 2);
   w.dob = take(rq * d * 2);
-  w.dqkv = take(rq * 3 * d * 2);
   w.dkv = take(rk * 2 * d * 2);
   w.dR = take(rk * d * 4);
-  w.part = take(kPartialBytes);
-  w.bpart = take((size_t)kMaxPartials * 2048 * 4);
+  w.part = take(stack_wgrads(s, w, nullptr, nullptr, 0, 0, 0).place(nullptr) * 4);
+  w.lnpart = take((size_t)(2 * s.layers + 1) * kMaxLnBlocks * 2 * d * 4);
   w.total = o;
   return w;
 }
@@ -2237,7 +2133,7 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
   auto wcat = [&](int l) { return (__bf16*)(ws + w.wcat) + (size_t)l * d * 3 * d; };
   auto bcat = [&](int l) { return (__bf16*)(ws + w.bcat + (size_t)l * up256((size_t)3 * d * 2)); };
   auto blk = [&](int l) -> const longer_block& { return l == 0 ? wts->cross[0] : wts->self[l - 1]; };
-  __bf16 *n1q, *n1k, *qkv, *kv, *o, *n2, *h, *a;      // the current layer's intermediates
+  __bf16 *n1q, *n1k, *qkv, *kv, *o, *n2, *h, *a, *dyb, *dh, *dxmb, *dqkv;      // the current layer's intermediates
   float* xmid;
   float2* stat;
   auto use_layer = [&](int l) {
@@ -2245,15 +2141,19 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
     n1q = (__bf16*)(base + w.n1q); n1k = (__bf16*)(base + w.n1k); qkv = (__bf16*)(base + w.qkv); kv = (__bf16*)(base + w.kv);
     o = (__bf16*)(base + w.o); xmid = (float*)(base + w.xmid); n2 = (__bf16*)(base + w.n2); h = (__bf16*)(base + w.h);
     a = (__bf16*)(base + w.a); stat = (float2*)(base + w.stat);
+    dyb = (__bf16*)(base + w.dyb); dh = (__bf16*)(base + w.dh); dxmb = (__bf16*)(base + w.dxmb); dqkv = (__bf16*)(base + w.dqkv);
   };
-  float* dy = (float*)(ws + w.dy);     __bf16* dyb = (__bf16*)(ws + w.dyb); __bf16* dh = (__bf16*)(ws + w.dh);
+  float* dy = (float*)(ws + w.dy);
   __bf16* dnq = (__bf16*)(ws + w.dnq); __bf16* dnk = (__bf16*)(ws + w.dnk); float* dxm = (float*)(ws + w.dxm);
-  __bf16* dxmb = (__bf16*)(ws + w.dxmb); __bf16* dob = (__bf16*)(ws + w.dob); __bf16* dqkv = (__bf16*)(ws + w.dqkv);
-  __bf16* dkv = (__bf16*)(ws + w.dkv); float* dR = (float*)(ws + w.dR);
-  float* part = (float*)(ws + w.part); float* bpart = (float*)(ws + w.bpart);
-  auto ln_grid = [&](size_t rows) { return (unsigned)((rows + 3) / 4 > 4096 ? 4096 : (rows + 3) / 4); };
+  __bf16* dob = (__bf16*)(ws + w.dob); __bf16* dkv = (__bf16*)(ws + w.dkv); float* dR = (float*)(ws + w.dR);
+  // LayerNorm partials: ln2 of every layer, ln1 of the self layers, then the cross layer's ln1 (query rows, key rows)
+  const unsigned lnq = ln_blocks(rq), lnk = ln_blocks(rk);
+  const size_t ln_stride = (size_t)kMaxLnBlocks * 2 * d;
+  auto ln2part = [&](int l) { return (float*)(ws + w.lnpart) + (size_t)l * ln_stride; };
+  auto ln1part = [&](int l) { return (float*)(ws + w.lnpart) + (size_t)(s.layers + (l ? l - 1 : s.layers - 1)) * ln_stride; };
 
-  bw_zero_kernel<<<flat_grid(mg.total + 1), 256, 0, st>>>(grads, mg.total);
+  // what is added to with atomics: the head's gradients, the learnable query tokens', the loss
+  bw_zero_kernel<<<flat_grid(mg.total - mg.head_w), 256, 0, st>>>(grads + mg.head_w, mg.total - mg.head_w);
   bw_zero_kernel<<<1, 256, 0, st>>>(loss, 1);
   BW_TRY(launched("zero fill"));
 
@@ -2284,9 +2184,9 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
     const longer_block& b = blk(l);
     const float* x = xs(l);
     use_layer(l);
-    ln_fwd(st, ln_grid(rq), d, x, (const __bf16*)b.ln1_g, (const __bf16*)b.ln1_b, n1q, (int)rq, c->ln_eps);
+    ln_fwd(st, lnq, d, x, (const __bf16*)b.ln1_g, (const __bf16*)b.ln1_b, n1q, (int)rq, c->ln_eps);
     if (l == 0) {
-      ln_fwd(st, ln_grid(rk), d, Rx, (const __bf16*)b.ln1_g, (const __bf16*)b.ln1_b, n1k, (int)rk, c->ln_eps);
+      ln_fwd(st, lnk, d, Rx, (const __bf16*)b.ln1_g, (const __bf16*)b.ln1_b, n1k, (int)rk, c->ln_eps);
       BW_TRY(launched("LayerNorm"));
       BW_TRY(gemm_rows(st, n1q, d, wcat(l), d, rq, EPI_BF16, 0, qkv, nullptr, bcat(l), nullptr, nullptr, 3 * d));
       BW_TRY(gemm_rows(st, n1k, d, wcat(l) + d, 2 * d, rk, EPI_BF16, 0, kv, nullptr, bcat(l) + d, nullptr, nullptr, 3 * d));
@@ -2299,7 +2199,7 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
     else set_attn_launch<32>(st, 0, t, nullptr, d, o, 0, nullptr, nullptr, stat);
     BW_TRY(launched("attention"));
     BW_TRY(gemm_rows(st, o, d, (const __bf16*)b.wo, d, rq, EPI_RES_F32, 0, xmid, nullptr, (const __bf16*)b.bo, x, nullptr));
-    ln_fwd(st, ln_grid(rq), d, xmid, (const __bf16*)b.ln2_g, (const __bf16*)b.ln2_b, n2, (int)rq, c->ln_eps);
+    ln_fwd(st, lnq, d, xmid, (const __bf16*)b.ln2_g, (const __bf16*)b.ln2_b, n2, (int)rq, c->ln_eps);
     BW_TRY(launched("LayerNorm"));
     BW_TRY(gemm_rows(st, n2, d, (const __bf16*)b.w1, f, rq, EPI_ACT, c->act, h, a, (const __bf16*)b.b1, nullptr, nullptr));
     if (y_out) {
@@ -2312,6 +2212,7 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
   for (int l = 0; l < s.layers; ++l) BW_TRY(forward(l, xs(l + 1)));
 
   // ---- head and loss (Eq. 1-2), and the gradient of the stack's output
+  use_layer(s.layers - 1);
   bw_head_kernel<<<B, 256, 0, st>>>(xs(s.layers), (const __bf16*)wts->head_w, (const __bf16*)wts->head_b, labels, B, s.n, s.m, d,
                                     logits, loss, dy, dyb, grads + mg.head_w, grads + mg.head_b);
   BW_TRY(launched("head"));
@@ -2319,17 +2220,13 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
   // ---- back through the layers
   for (int l = s.layers - 1; l >= 0; --l) {
     const longer_block& b = blk(l);
-    float* g = grads + (l == 0 ? mg.cross : mg.self0 + (size_t)(l - 1) * mg.per_main);
+    use_layer(l);                                  // kept by the forward pass above
     // rows that were written as zeros pass no gradient
     bw_mask_rows_kernel<<<flat_grid(rq * d / 4), 256, 0, st>>>(dy, dyb, qdesc, rq, d);
     BW_TRY(launched("row mask"));
-    use_layer(l);                                  // kept by the forward pass above
-    BW_TRY(gemm_wgrad(st, a, f, f, dyb, d, d, rq, part, bpart, g + gl.w2, g + gl.b2));
     BW_TRY(gemm_rows_t(st, dyb, d, (const __bf16*)b.w2, f, rq, EPI_DACT, c->act, dh, h));
-    BW_TRY(gemm_wgrad(st, n2, d, d, dh, f, f, rq, part, bpart, g + gl.w1, g + gl.b1));
     BW_TRY(gemm_rows_t(st, dh, f, (const __bf16*)b.w1, d, rq, EPI_BF16, 0, dnq, nullptr));
-    BW_TRY(ln_bwd(st, ln_grid(rq), d, dnq, xmid, (const __bf16*)b.ln2_g, dy, dxm, dxmb, part, g + gl.ln2_g, (int)rq, c->ln_eps));
-    BW_TRY(gemm_wgrad(st, o, d, d, dxmb, d, d, rq, part, bpart, g + gl.wo, g + gl.bo));
+    BW_TRY(ln_bwd(st, lnq, d, dnq, xmid, (const __bf16*)b.ln2_g, dy, dxm, dxmb, ln2part(l), (int)rq, c->ln_eps));
     BW_TRY(gemm_rows_t(st, dxmb, d, (const __bf16*)b.wo, d, rq, EPI_BF16, 0, dob, nullptr));
     const SetAttn t = attn(l);
     if (l == 0) {
@@ -2341,15 +2238,12 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
         set_attn_launch<32>(st, 2, t, dob, d, nullptr, 2 * d, dkv, dkv + d, stat);
       }
       BW_TRY(launched("attention backward"));
-      BW_TRY(gemm_wgrad(st, n1q, d, d, dqkv, d, d, rq, part, bpart, g + gl.wq, g + gl.bq));
-      BW_TRY(gemm_wgrad(st, n1k, d, d, dkv, 2 * d, d, rk, part, bpart, g + gl.wk, g + gl.bk));
-      BW_TRY(gemm_wgrad(st, n1k, d, d, dkv + d, 2 * d, d, rk, part, bpart, g + gl.wv, g + gl.bv));
       BW_TRY(gemm_rows_t(st, dqkv, d, wcat(l), d, rq, EPI_BF16, 0, dnq, nullptr, 3 * d));
       BW_TRY(gemm_rows_t(st, dkv, 2 * d, wcat(l) + d, d, rk, EPI_BF16, 0, dnk, nullptr, 3 * d));
       // LN1 normalises the query rows and the key rows: its gain / shift gradient is the sum of both;
       // dO goes to dy (the query rows' gradient), dR to its own buffer
-      BW_TRY(ln_bwd(st, ln_grid(rq), d, dnq, xs(0), (const __bf16*)b.ln1_g, dxm, dy, nullptr, part, g + gl.ln1_g, (int)rq, c->ln_eps, true));
-      BW_TRY(ln_bwd(st, ln_grid(rk), d, dnk, Rx, (const __bf16*)b.ln1_g, nullptr, dR, nullptr, part, g + gl.ln1_g, (int)rk, c->ln_eps, true));
+      BW_TRY(ln_bwd(st, lnq, d, dnq, xs(0), (const __bf16*)b.ln1_g, dxm, dy, nullptr, ln1part(0), (int)rq, c->ln_eps));
+      BW_TRY(ln_bwd(st, lnk, d, dnk, Rx, (const __bf16*)b.ln1_g, nullptr, dR, nullptr, ln1part(0) + (size_t)lnq * 2 * d, (int)rk, c->ln_eps));
     } else {
       if (s.dh == 16) {
         set_attn_launch<16>(st, 1, t, dob, d, dqkv, 3 * d, nullptr, nullptr, stat);
@@ -2359,13 +2253,22 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
         set_attn_launch<32>(st, 2, t, dob, d, nullptr, 3 * d, dqkv + d, dqkv + 2 * d, stat);
       }
       BW_TRY(launched("attention backward"));
-      const size_t wofs[3] = {gl.wq, gl.wk, gl.wv}, bofs[3] = {gl.bq, gl.bk, gl.bv};
-      for (int j = 0; j < 3; ++j)
-        BW_TRY(gemm_wgrad(st, n1q, d, d, dqkv + (size_t)j * d, 3 * d, d, rq, part, bpart, g + wofs[j], g + bofs[j]));
       BW_TRY(gemm_rows_t(st, dqkv, 3 * d, wcat(l), d, rq, EPI_BF16, 0, dnq, nullptr));
-      BW_TRY(ln_bwd(st, ln_grid(rq), d, dnq, xs(l), (const __bf16*)b.ln1_g, dxm, dy, dyb, part, g + gl.ln1_g, (int)rq, c->ln_eps));
+      BW_TRY(ln_bwd(st, lnq, d, dnq, xs(l), (const __bf16*)b.ln1_g, dxm, dy, nullptr, ln1part(l), (int)rq, c->ln_eps));
     }
   }
+  // ---- parameter gradients of all layers: one launch, one for the sums of its partial results and the LayerNorms'
+  WgradBatch wg = stack_wgrads(s, w, ws, grads, mg.cross, mg.self0, mg.per_main);
+  BW_TRY(launch(wg, (float*)(ws + w.part), st));
+  ReduceBatch rb;
+  rb.add(wg);
+  if (s.layers > 1) {
+    rb.add_ln(ln1part(1), (int)lnq, d, grads + mg.self0 + gl.ln1_g, s.layers - 1, (long long)ln_stride, (long long)mg.per_main);
+    rb.add_ln(ln2part(1), (int)lnq, d, grads + mg.self0 + gl.ln2_g, s.layers - 1, (long long)ln_stride, (long long)mg.per_main);
+  }
+  rb.add_ln(ln1part(0), (int)(lnq + lnk), d, grads + mg.cross + gl.ln1_g);
+  rb.add_ln(ln2part(0), (int)lnq, d, grads + mg.cross + gl.ln2_g);
+  BW_TRY(launch(rb, st));
   // ---- gradients of the stack's inputs: global tokens (query rows and key rows), merged tokens (key
   // rows, plus the query slots that hold them)
   bw_split_grad_kernel<<<flat_grid(rk * d / 4), 256, 0, st>>>(geo, d, dy, dR, dG, dM);
@@ -2377,7 +2280,14 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
 
 // ------------------------------------------------------------------------------------
 // Input generation backward (longer_input_generation_backward)
-struct InputWs { size_t w1t, x, a, dyb, dh, dx, part, bpart, total; };
+struct InputWs { size_t w1t, x, a, dyb, dh, dx, part, total; };
+static WgradBatch input_wgrads(int d, int f, size_t ntok, RowsValid rv, const __bf16* x, const __bf16* dh, const __bf16* a,
+                               const __bf16* dyb, float* gw1, float* gw2) {
+  WgradBatch w(d, ntok);
+  w.add(a, f, f, dyb, d, d, d, ntok, rv, gw2);          // H = a w2 + b2
+  w.add(x, d, d, dh, f, f, f, ntok, rv, gw1);
+  return w;
+}
 static InputWs input_ws(size_t ntok, int d, int f) {
   InputWs w;
   size_t o = 0;
@@ -2388,8 +2298,7 @@ static InputWs input_ws(size_t ntok, int d, int f) {
   w.dyb = take(ntok * d * 2);
   w.dh = take(ntok * f * 2);
   w.dx = take(ntok * d * 4);
-  w.part = take(kPartialBytes);
-  w.bpart = take((size_t)kMaxPartials * 2048 * 4);
+  w.part = take(input_wgrads(d, f, ntok, RowsValid{}, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr).place(nullptr) * 4);
   w.total = o;
   return w;
 }
@@ -2538,20 +2447,20 @@ int longer_input_generation_backward(const longer_config* cfg, const longer_inpu
   char* w8 = (char*)ws;
   __bf16* x = (__bf16*)(w8 + l.x);   __bf16* w1t = (__bf16*)(w8 + l.w1t); __bf16* a = (__bf16*)(w8 + l.a);
   __bf16* dyb = (__bf16*)(w8 + l.dyb); __bf16* dh = (__bf16*)(w8 + l.dh); float* dx = (float*)(w8 + l.dx);
-  float* part = (float*)(w8 + l.part); float* bpart = (float*)(w8 + l.bpart);
   const bw::RowGeom q = {lens, L, 1, (int)nt};
   const bw::RowsValid rv = {lens, L};
   const unsigned eg = bw::flat_grid(nt * d / 4);
-  bw::bw_zero_kernel<<<bw::flat_grid(gl.total), 256, 0, st>>>(grads_out, gl.total);
   bw::bw_input_rows_kernel<<<eg, 256, 0, st>>>((const __bf16*)E, (const __bf16*)w->pos, (const __bf16*)tdiff, x, q, d, d_e);
   bw::bw_cast_rows_kernel<<<eg, 256, 0, st>>>(dH, dyb, q, d);
   if ((rc = bw::launched("input rows"))) return rc;
   // the hidden pre-activation is formed again inside the launch that takes its gradient (as in the merge's FFN)
   if ((rc = bw::transpose(st, (const __bf16*)w->w1, w1t, d, f))) return rc;
   if ((rc = bw::gemm_ffn_mid(st, x, dyb, d, w1t, (const __bf16*)w->w2, f, (const __bf16*)w->b1, nt, cfg->act, dh, a, rv))) return rc;
-  // H = a w2 + b2
-  if ((rc = bw::gemm_wgrad(st, a, f, f, dyb, d, d, nt, part, bpart, grads_out + gl.w2, grads_out + gl.b2, rv))) return rc;
-  if ((rc = bw::gemm_wgrad(st, x, d, d, dh, f, f, nt, part, bpart, grads_out + gl.w1, grads_out + gl.b1, rv))) return rc;
+  bw::WgradBatch wg = bw::input_wgrads(d, f, nt, rv, x, dh, a, dyb, grads_out + gl.w1, grads_out + gl.w2);
+  bw::ReduceBatch rb;
+  if ((rc = bw::launch(wg, (float*)(w8 + l.part), st))) return rc;
+  rb.add(wg);
+  if ((rc = bw::launch(rb, st))) return rc;
   if ((rc = bw::gemm_rows_t(st, dh, f, (const __bf16*)w->w1, d, nt, bw::EPI_F32, 0, dx, nullptr, 0, rv))) return rc;
   bw::bw_split_input_grad_kernel<<<eg, 256, 0, st>>>(dx, dE_out, dtdiff_out, q, d, d_e);
   bw::bw_pos_grad_kernel<<<bw::flat_grid((size_t)L * d_e / 4), 256, 0, st>>>(dx, grads_out + gl.pos, q, B, d, d_e);

@@ -1,0 +1,52 @@
+// Shared by the backward pass's kernels: valid rows, the transposing LDS fragment read.
+#pragma once
+#include "../../include/longer.h"
+#include "device.h"
+
+namespace longer {
+namespace bw {
+
+constexpr int kComputeUnits = 256;
+
+// Padded token rows (row r = u L + pos with pos >= the user's length) carry no gradient.  With the
+// batch's geometry at hand a kernel leaves them out: row GEMMs skip tiles without a valid row, the
+// gradient GEMMs read them as zeros and pass over steps that hold nothing else, the LayerNorm kernels
+// write zeros for them.  L = 0: every row counts (the reduced stack's rows).
+struct RowsValid { const int32_t* lens; int L; };
+__device__ __forceinline__ bool row_valid(const RowsValid& v, int r) {
+  if (v.L == 0 || v.lens == nullptr) return true;
+  const int u = r / v.L;
+  return r - u * v.L < v.lens[u];
+}
+// any valid row in [r0, r1)?
+__device__ __forceinline__ bool rows_any_valid(const RowsValid& v, int r0, int r1) {
+  if (v.L == 0 || v.lens == nullptr) return true;
+  for (int u = r0 / v.L; u * v.L < r1; ++u) {
+    const int first = max(r0, u * v.L) - u * v.L;
+    if (first < v.lens[u]) return true;
+  }
+  return false;
+}
+
+// Matrix-core operand fragment of a row-major LDS tile whose rows are the contraction index: lane (x = l % 32,
+// hi = l / 32) gets rows 8 hi .. 8 hi + 7 of column x.  The transposing read works on groups of 16 lanes: lane i
+// of a group points at four consecutive columns (4 (i % 4) ..) of row i / 4 and receives column i of the
+// group's four rows.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+template <int PITCH>
+__device__ __forceinline__ int frag_t_offset(int lane) {
+  return (8 * (lane >> 5) + ((lane & 15) >> 2)) * PITCH + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+}
+// s: the tile's element (first row, first column) plus frag_t_offset
+template <int PITCH>
+__device__ __forceinline__ bf16x8 frag_t(const __bf16* s) {
+  typedef __attribute__((address_space(3))) s16x4 lds4;
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4*)s);
+  const s16x4 up = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4*)(s + 4 * PITCH));
+  const s16x8 v = __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7);
+  return __builtin_bit_cast(bf16x8, v);
+}
+
+}  // namespace bw
+}  // namespace longer

@@ -1,0 +1,274 @@
+// Parameter gradients of the backward pass: dW = x^T dy for every matrix of a launch at once, and the
+// sums of the partial results.
+//
+// A parameter gradient is a contraction over the token rows, so its parallelism comes from cutting the
+// rows into slices.  One launch takes all matrices (of all layers) whose operands are ready: the reduced
+// stack's gradients, 24-48 tiles of 128 x 128 with 100-1000 row steps each, were 24 launches of 12-16 us and
+// as many reductions before (512 us of a 1091 us step of the small model: B = 128, L = 512, d = 64), each too
+// small for the chip; see the figures at bw_wgrad_kernel.
+#pragma once
+#include "bw_common.h"
+
+namespace longer {
+namespace bw {
+
+// One matrix (or one per layer): dW [m][n] = X^T Y over `rows` token rows, and db [n] = column sums of Y.
+struct WgradJob {
+  RowsValid rv;                       // padded rows read as zeros; row steps that hold nothing else are passed over
+  const __bf16* X; const __bf16* Y;   // [rows][..], pitches ldx, ldy
+  long long xstride, ystride;         // elements from one layer's operand to the next layer's
+  float* part;                        // partial results: [layer][slice][m n + n]
+  int ldx, ldy, m, n, rows;
+  int tiles_m, tiles_n, layers;
+  int nsub;                           // slices of this job per slice of the launch (a job with more rows than the others)
+  int first;                          // its first tile inside a slice's tiles
+};
+constexpr int kMaxWgradJobs = 10;
+struct WgradArgs { WgradJob job[kMaxWgradJobs]; int njobs, tiles, nslices; };
+
+// TB: output tile TB x TB, four waves in 2 x 2.  Both operands are stored with the contraction (token) index
+// strided: a step's 32 rows go to LDS as they are, and the fragments (lane = column, eight tokens per lane)
+// come back through the transposing LDS read, two per fragment.  The six launches that this one replaces, with
+// eight 2-byte LDS reads per fragment, took 595 us for a block of the headline batch (512 000 rows, width 128), this
+// one 392 us (5.3 TB/s of the 4.1 KB per row below); at 4608 rows of width 64 and three layers (the small model's
+// reduced stack) 18 launches of 12-16 us became one of 13 us.  The row pitch of 2 TB + 32 bytes puts the four rows
+// that 16 lanes read together into different banks.
+// Memory bound at scale: at the headline batch one block's gradients read 4.1 KB per token, 2.1 GB.  Slices take
+// every nslices-th step, so that each samples long and short users alike; the tiles of a slice, which share
+// their operands' rows, run on one accelerator die (one L2).
+template <int TB>
+__global__ __launch_bounds__(256, 3) void bw_wgrad_kernel(const WgradArgs a) {
+  constexpr int PITCH = TB + 16, TT = TB / 64, NCH = TB / 64;     // NCH: 16-byte chunks per thread, operand and step
+  constexpr int CPR = TB / 8;                                     // chunks per row
+  __shared__ __attribute__((aligned(16))) __bf16 sm[4 * 32 * PITCH];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int wm = w & 1, wn = w >> 1, hi = lane >> 5, l32 = lane & 31;
+  const int slot = blockIdx.x >> 3, slice = (slot / a.tiles) * 8 + (blockIdx.x & 7);
+  if (slice >= a.nslices) return;
+  int t = slot % a.tiles;
+  // (static offsets into the kernel arguments and scalar selects: no run-time index into a by-value argument)
+  WgradJob jb = a.job[0];
+#pragma unroll
+  for (int i = 1; i < kMaxWgradJobs; ++i)
+    if (i < a.njobs && t >= a.job[i].first) jb = a.job[i];
+  t -= jb.first;
+  const int sub = t % jb.nsub; t /= jb.nsub;
+  const int tn = t % jb.tiles_n; t /= jb.tiles_n;
+  const int tm = t % jb.tiles_m, layer = t / jb.tiles_m;
+  const __bf16* X = jb.X + layer * jb.xstride;
+  const __bf16* Y = jb.Y + layer * jb.ystride;
+  const int m0 = tm * TB, n0 = tn * TB;
+  const int kfirst = slice * jb.nsub + sub, kstride = a.nslices * jb.nsub;
+  const int steps = (jb.rows + 31) / 32;
+  const int nk = steps > kfirst ? (steps - kfirst + kstride - 1) / kstride : 0;
+
+  f32x16 acc[TT][TT], accb[TT];
+#pragma unroll
+  for (int i = 0; i < TT; ++i) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) accb[i][r] = 0.f;
+#pragma unroll
+    for (int j = 0; j < TT; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  }
+  // column sums of Y: one more product, ones [32, rows] Y, by the waves of the first row half of the first row tile
+  const bool bias_sum = tm == 0 && wm == 0;
+  bf16x8 ones;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.f;
+
+  bf16x8 rx[NCH], ry[NCH];
+  auto gload = [&](int kt) {
+    const int k0 = (kfirst + kt * kstride) * 32;
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+      const int c = tid + 256 * i, row = k0 + c / CPR, col = 8 * (c % CPR);
+      bf16x8 z;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) z[e] = (__bf16)0.f;
+      rx[i] = z; ry[i] = z;
+      if (row < jb.rows && row_valid(jb.rv, row)) {
+        if (m0 + col < jb.m) rx[i] = *(const bf16x8*)(X + (size_t)row * jb.ldx + m0 + col);
+        if (n0 + col < jb.n) ry[i] = *(const bf16x8*)(Y + (size_t)row * jb.ldy + n0 + col);
+      }
+    }
+  };
+  auto next_step = [&](int kt) {
+    while (kt < nk) {
+      const int k0 = (kfirst + kt * kstride) * 32;
+      if (rows_any_valid(jb.rv, k0, min(jb.rows, k0 + 32))) break;
+      ++kt;
+    }
+    return kt;
+  };
+  const int foff = frag_t_offset<PITCH>(lane);
+  int buf = 0, kt = next_step(0);
+  if (kt < nk) gload(kt);
+  while (kt < nk) {
+    __bf16* sx = sm + buf * (2 * 32 * PITCH);
+    __bf16* sy = sx + 32 * PITCH;
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+      const int c = tid + 256 * i, o = (c / CPR) * PITCH + 8 * (c % CPR);
+      *(bf16x8*)&sx[o] = rx[i];
+      *(bf16x8*)&sy[o] = ry[i];
+    }
+    const int kn = next_step(kt + 1);
+    if (kn < nk) gload(kn);
+    __syncthreads();       // (the other buffer was last read two steps ago, ahead of the previous barrier)
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      bf16x8 fx[TT], fy[TT];
+#pragma unroll
+      for (int i = 0; i < TT; ++i) {
+        fx[i] = frag_t<PITCH>(sx + foff + 16 * ks * PITCH + (TB / 2) * wm + 32 * i);
+        fy[i] = frag_t<PITCH>(sy + foff + 16 * ks * PITCH + (TB / 2) * wn + 32 * i);
+      }
+#pragma unroll
+      for (int i = 0; i < TT; ++i)
+#pragma unroll
+        for (int j = 0; j < TT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[i], fy[j], acc[i][j], 0, 0, 0);
+      if (bias_sum) {
+#pragma unroll
+        for (int j = 0; j < TT; ++j) accb[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, fy[j], accb[j], 0, 0, 0);
+      }
+    }
+    buf ^= 1;
+    kt = kn;
+  }
+  float* out = jb.part + ((size_t)layer * kstride + kfirst) * ((size_t)jb.m * jb.n + jb.n);
+#pragma unroll
+  for (int i = 0; i < TT; ++i)
+#pragma unroll
+    for (int j = 0; j < TT; ++j) {
+      const int n = n0 + (TB / 2) * wn + 32 * j + l32, mb = m0 + (TB / 2) * wm + 32 * i;
+      if (n >= jb.n || mb >= jb.m) continue;               // (m and n are multiples of 32)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) out[(size_t)(mb + tile_row(r, hi)) * jb.n + n] = acc[i][j][r];
+    }
+  if (bias_sum && hi == 0) {
+#pragma unroll
+    for (int j = 0; j < TT; ++j) {
+      const int n = n0 + (TB / 2) * wn + 32 * j + l32;
+      if (n < jb.n) out[(size_t)jb.m * jb.n + n] = accb[j][0];
+    }
+  }
+}
+
+// Sums of partial results: out = sum over the slices of part[slice][m n + n], for every job (and layer) of a
+// launch.  Columns come in blocks of nb (the three matrices of [W_Q | W_K | W_V] are one job): column block j, its
+// m rows and then its n-vector, goes to out + j (m nb + nb).  m = 0: a plain vector of n (the LayerNorms' [gain | shift]).
+// A workgroup sums 4 CX adjacent outputs, its 256 / CX rows of threads each every (256 / CX)-th slice: CX = 16 for the
+// matrices (tens of slices), 4 for the vectors (hundreds).  Every sum is taken in a fixed order.
+struct ReduceJob {
+  const float* part; float* out;
+  long long sstride, plstride, olstride;    // floats from slice to slice, from layer to layer (partial, output)
+  int nslices, m, n, nb, layers, cxlog, blocks, first;   // blocks: workgroups per layer; first: its first workgroup
+};
+constexpr int kMaxReduceJobs = 16;
+struct ReduceArgs { ReduceJob job[kMaxReduceJobs]; int njobs; };
+
+__global__ __launch_bounds__(256) void bw_reduce_jobs_kernel(const ReduceArgs a) {
+  __shared__ f32x4 red[256];
+  int b = blockIdx.x;
+  ReduceJob jb = a.job[0];
+#pragma unroll
+  for (int i = 1; i < kMaxReduceJobs; ++i)
+    if (i < a.njobs && b >= a.job[i].first) jb = a.job[i];
+  b -= jb.first;
+  const int layer = b / jb.blocks, blk = b - layer * jb.blocks;
+  const int cx = 1 << jb.cxlog, ny = 256 >> jb.cxlog;
+  const int x = threadIdx.x & (cx - 1), y = threadIdx.x >> jb.cxlog;
+  const long long i4 = 4ll * ((long long)blk * cx + x), count = (long long)jb.m * jb.n + jb.n;
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};
+  if (i4 < count) {
+    const float* p = jb.part + layer * jb.plstride + i4;
+#pragma unroll 4
+    for (int sl = y; sl < jb.nslices; sl += ny) s += *(const f32x4*)(p + sl * jb.sstride);
+  }
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int h = ny >> 1; h > 0; h >>= 1) {
+    if (y < h) red[threadIdx.x] += red[threadIdx.x + (h << jb.cxlog)];
+    __syncthreads();
+  }
+  if (y == 0 && i4 < count) {
+    const int row = (int)(i4 / jb.n), col = (int)(i4 - (long long)row * jb.n);
+    const int cb = col / jb.nb, cc = col - cb * jb.nb;
+    float* o = jb.out + layer * jb.olstride + (size_t)cb * ((size_t)jb.m * jb.nb + jb.nb) + (size_t)row * jb.nb + cc;
+    *(f32x4*)o = red[x];
+  }
+}
+
+// ------------------------------------------------------------------------------------ host side
+// Slices of a launch with `tiles` output tiles over `rows` rows: enough workgroups to fill the chip three deep
+// (what fits a compute unit), but at least four row steps (128 rows) each.
+static inline int wgrad_slices(int tiles, size_t rows) {
+  const int steps = (int)((rows + 31) / 32);
+  int s = 3 * kComputeUnits / (tiles > 0 ? tiles : 1);
+  if (s > steps / 4) s = steps / 4;
+  if (s > 8) s = s / 8 * 8;                 // (slices are dealt to the 8 dies)
+  return s < 1 ? 1 : s;
+}
+static inline int wgrad_tile(int d) { return d >= 128 ? 128 : 64; }
+
+// The matrices of a launch, then their reductions.  Used twice with the same calls: without a base pointer
+// to learn how many floats of partial results the launch needs, and with one to launch it.
+struct WgradBatch {
+  WgradArgs a = {};
+  int tb; size_t rows;                      // rows: of the jobs with nsub = 1 (sets the number of slices)
+  struct Out { float* out; long long olstride; int nb; } outs[kMaxWgradJobs];
+  WgradBatch(int d, size_t rows_) : tb(wgrad_tile(d)), rows(rows_) {}
+  void add(const __bf16* X, int ldx, int m, const __bf16* Y, int ldy, int n, int nb, size_t nrows, RowsValid rv, float* out,
+           int layers = 1, long long xstride = 0, long long ystride = 0, long long olstride = 0) {
+    WgradJob& j = a.job[a.njobs];
+    j.X = X; j.Y = Y; j.ldx = ldx; j.ldy = ldy; j.m = m; j.n = n; j.rows = (int)nrows; j.rv = rv;
+    j.tiles_m = (m + tb - 1) / tb; j.tiles_n = (n + tb - 1) / tb; j.layers = layers;
+    j.nsub = nrows > rows ? (int)((nrows + rows - 1) / rows) : 1;
+    j.xstride = xstride; j.ystride = ystride; j.first = a.tiles;
+    a.tiles += j.tiles_m * j.tiles_n * layers * j.nsub;
+    outs[a.njobs] = Out{out, olstride, nb};
+    ++a.njobs;
+  }
+  // floats of partial results, and where each job's start
+  size_t place(float* base) {
+    a.nslices = wgrad_slices(a.tiles, rows);
+    size_t o = 0;
+    for (int i = 0; i < a.njobs; ++i) {
+      WgradJob& j = a.job[i];
+      j.part = base ? base + o : nullptr;
+      o += (size_t)j.layers * a.nslices * j.nsub * ((size_t)j.m * j.n + j.n);
+    }
+    return o;
+  }
+};
+
+struct ReduceBatch {
+  ReduceArgs a = {};
+  int blocks = 0;
+  void add(const float* part, long long sstride, int nslices, int m, int n, int nb, float* out, int layers, long long plstride,
+           long long olstride) {
+    ReduceJob& j = a.job[a.njobs++];
+    j.part = part; j.out = out; j.sstride = sstride; j.nslices = nslices; j.m = m; j.n = n; j.nb = nb; j.layers = layers;
+    j.plstride = plstride; j.olstride = olstride; j.cxlog = m ? 4 : 2;
+    const long long groups = ((long long)m * n + n) / 4;
+    j.blocks = (int)((groups + (1 << j.cxlog) - 1) >> j.cxlog);
+    j.first = blocks;
+    blocks += j.blocks * layers;
+  }
+  // the LayerNorm partials [nslices][2 d] of a launch (per layer plstride floats apart)
+  void add_ln(const float* part, int nslices, int d, float* out, int layers = 1, long long plstride = 0, long long olstride = 0) {
+    add(part, 2 * d, nslices, 0, 2 * d, 2 * d, out, layers, plstride, olstride);
+  }
+  void add(const WgradBatch& w) {
+    for (int i = 0; i < w.a.njobs; ++i) {
+      const WgradJob& j = w.a.job[i];
+      const long long per = (long long)j.m * j.n + j.n;
+      add(j.part, per, w.a.nslices * j.nsub, j.m, j.n, w.outs[i].nb, w.outs[i].out, j.layers, per * w.a.nslices * j.nsub, w.outs[i].olstride);
+    }
+  }
+};
+
+}  // namespace bw
+}  // namespace longer

@@ -1,0 +1,34 @@
+"""GPU parity of the backward pass at the sizes where its kernels can go wrong: fewer rows than a tile or a
+contraction step, remainders of both, more key rows than query rows by a factor, every width.  Oracle, tolerances
+and their derivation as in test_gpu_backward."""
+import pytest
+
+import longer_synth as synth
+from test_gpu_backward import _compare, _compare_model, _say
+
+pytestmark = pytest.mark.gpu
+
+
+# (width, heads, users, raw length, ragged): 1 row; 31 / 33 rows (a 32-row step and its neighbours); 129 rows and
+# 3 x 257 (a 128-row tile and one more); a step that is all padding
+@pytest.mark.parametrize("d,heads,B,L,ragged", [(32, 2, 1, 1, False), (64, 4, 1, 31, False), (128, 8, 1, 33, False),
+                                                (128, 4, 1, 129, False), (64, 2, 3, 257, True), (256, 8, 2, 65, True)])
+def test_parameter_gradients_at_row_remainders(d, heads, B, L, ragged):
+    cfg = synth.CONFIGS["C2"].replace(d=d, heads=heads, inner_heads=heads, B=B, L=L, k_recent=5, n_self=1, ragged=ragged,
+                                      len_lo=0, len_hi=L, index=61)
+    case = synth.make_case(cfg)
+    if ragged:
+        case["lens"][:2] = [L, 3]
+    _compare("width %d, %d rows" % (d, B * L), case, synth.draw_merge_gradient(cfg))
+    _compare_model("width %d, %d rows" % (d, B * L), case)
+
+
+@pytest.mark.parametrize("n_self", [1, 3])
+def test_parameter_gradients_many_more_key_rows_than_query_rows(n_self):
+    """The cross layer's key and value gradients contract over m + T rows a user, the others over m + k: here 20 times
+    as many, so their slices are cut finer than the launch's.  (Not with n_self = 0: b_2 then gets its gradient from
+    the global rows alone, sum over the users of (sigmoid(logit) - label) / B times a fixed vector, and these three
+    users' terms, -0.0129 - 0.1356 + 0.1473, cancel to -0.0012; a logit error of 3e-3 moves a term by up to
+    3e-3 / 4 / 3 = 2.5e-4, a fifth of what is left.)"""
+    cfg = synth.CONFIGS["C2"].replace(B=3, L=1000, K=4, m=2, k_recent=10, n_self=n_self, ragged=True, len_lo=300, len_hi=1000, index=62)
+    _compare_model("T = 250, k = 10, n_self = %d" % n_self, synth.make_case(cfg))
