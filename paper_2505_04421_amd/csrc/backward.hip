@@ -31,6 +31,7 @@
 //     per head), and over a user's own rows under the mask of Eq. 8 (reduced stack).
 // Padded token rows are never read and cost only the zeros written for them.
 #include "bw_grads.h"
+#include "bw_set_attn.h"
 
 #include <cstdio>
 
@@ -759,26 +760,6 @@ __device__ __forceinline__ void axpy(float* acc, float w, const HeadVec<DH>& v) 
     for (int e = 0; e < 8; ++e) acc[8 * c + e] = fmaf(w, (float)v.c[c][e], acc[8 * c + e]);
 }
 
-// The same with the weight rounded to bf16: acc[2i] and acc[2i + 1] each take one two-feature product
-// against (w, 0) or (0, w), so the packed features need no widening (half the instructions of axpy).
-// For the long loops of the reduced stack's attention, where the weight is a probability or a
-// score gradient that multiplies bf16 values anyway.
-template <int DH>
-__device__ __forceinline__ void axpy_packed(float* acc, float w, const HeadVec<DH>& v) {
-  const __bf16 wb = (__bf16)w;
-  const bf16x2 w0 = {wb, (__bf16)0.f}, w1 = {(__bf16)0.f, wb};
-#pragma unroll
-  for (int c = 0; c < DH / 8; ++c) {
-    const bf16x2 pr[4] = {__builtin_shufflevector(v.c[c], v.c[c], 0, 1), __builtin_shufflevector(v.c[c], v.c[c], 2, 3),
-                          __builtin_shufflevector(v.c[c], v.c[c], 4, 5), __builtin_shufflevector(v.c[c], v.c[c], 6, 7)};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      acc[8 * c + 2 * e] = __builtin_amdgcn_fdot2_f32_bf16(pr[e], w0, acc[8 * c + 2 * e], false);
-      acc[8 * c + 2 * e + 1] = __builtin_amdgcn_fdot2_f32_bf16(pr[e], w1, acc[8 * c + 2 * e + 1], false);
-    }
-  }
-}
-
 // KG: the loops over a group's tokens are unrolled KG times (K <= KG) so that the per-token values
 // stay in registers; tokens past the group's valid count are predicated off.
 template <int DH, int KG>
@@ -1037,17 +1018,7 @@ __global__ __launch_bounds__(256) void bw_zero_kernel(float* p, size_t n) {
 
 // ------------------------------------------------------------------------------------
 // The reduced stack (Section 3.5): cross-causal layer over R = [G; M] with the query set O of Eq. 5,
-// self-causal layers over O's rows.  Every row carries a descriptor of its token: -1 invalid, a for
-// global token a, kSeq + t for the sequence token with merged index t; visibility is the rule of
-// Eq. 8 on those descriptors.
-constexpr int kSeq = 1 << 24;
-
-__device__ __forceinline__ bool visible(int qd, int kd, int gmask) {
-  if (qd < 0 || kd < 0) return false;
-  if (qd >= kSeq) return kd >= kSeq && kd <= qd;          // a sequence query: sequence keys not newer than itself
-  if (kd >= kSeq) return true;                            // a global query: every valid sequence key
-  return gmask == LONGER_GMASK_FULL || kd >= qd;          // and the global keys of its set
-}
+// self-causal layers over O's rows (descriptors and attention: bw_set_attn.h).
 
 // merged index held by query slot i of a user with tu merged tokens (Section 3.5.1): the last
 // k - k_uniform slots the most recent tokens, the first k_uniform spread evenly over the older ones
@@ -1128,361 +1099,6 @@ __global__ __launch_bounds__(256) void bw_mask_rows_kernel(float* __restrict__ x
     if (desc[row] >= 0) v = *(const f32x4*)(x + i * 4);
     *(f32x4*)(x + i * 4) = v;
     if (xb) store_bf16x4(xb + i * 4, v);
-  }
-}
-
-struct SetAttn {
-  const __bf16* q; int qpitch;          // [B nq][..]
-  const __bf16* k; const __bf16* v; int kvpitch;   // [B nk][..]
-  const int* qdesc; const int* kdesc;
-  int nq, nk, B, heads, gmask;
-  int m, self;                          // global rows come first in both sets; self: the key rows are the query rows
-};
-
-// Keys a query row can see at all lie in [lo, hi) of its user's key rows: a sequence query sees no global
-// row and nothing newer than itself (its own row in a self layer, its merged token's row in the cross
-// layer); the visibility test inside the loops still decides each pair.
-__device__ __forceinline__ void key_range(const SetAttn& a, int qd, int i, int* lo, int* hi) {
-  *lo = 0; *hi = a.nk;
-  if (qd >= kSeq) {
-    *lo = a.m;
-    *hi = min(a.nk, a.self ? i + 1 : a.m + (qd - kSeq) + 1);
-  }
-}
-
-// Row-per-thread set-attention kernels, reading keys (queries) from global memory: the ones that run when a
-// user's rows do not fit the LDS-staged kernels further down.  They give a (row, head) pair to kSplit adjacent
-// lanes, each taking every kSplit-th key (query) of the loop, and combine the lanes' partial results with
-// cross-lane shuffles.
-constexpr int kSplit = 1;   // measured at the headline batch: with the keys in global memory 8 lanes per pair were no
-                            // faster, and slower in the two backward kernels
-__device__ __forceinline__ float split_sum(float v) {
-#pragma unroll
-  for (int o = 1; o < kSplit; o <<= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-__device__ __forceinline__ float split_max(float v) {
-#pragma unroll
-  for (int o = 1; o < kSplit; o <<= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-
-// o[row][h] = softmax over the visible keys of the row's user (q . k / sqrt(dh)) v; stat[row][h].x = the
-// log-sum-exp of the scaled scores.  One pass with a running maximum per lane.
-template <int DH>
-__global__ __launch_bounds__(256) void bw_set_attn_fwd_kernel(SetAttn a, __bf16* __restrict__ o, int d, float2* __restrict__ stat) {
-  const long long idx = ((long long)blockIdx.x * 256 + threadIdx.x) / kSplit;
-  const int sub = threadIdx.x % kSplit;
-  if (idx >= (long long)a.B * a.nq * a.heads) return;
-  const int row = (int)(idx / a.heads), h = (int)(idx - (long long)row * a.heads);
-  const int u = row / a.nq, qd = a.qdesc[row];
-  float acc[DH];
-#pragma unroll
-  for (int c = 0; c < DH; ++c) acc[c] = 0.f;
-  float mx = -3.0e38f, l = 0.f;
-  if (qd >= 0) {
-    const float scale = rsqrtf((float)DH);
-    const HeadVec<DH> qv = load_head<DH>(a.q + (size_t)row * a.qpitch + h * DH);
-    int lo, hi;
-    key_range(a, qd, row - u * a.nq, &lo, &hi);
-    // every row of the range is loaded, a hidden key weighs nothing: no branch in the loop, so that the
-    // loads of several keys are in flight at once
-#pragma unroll(DH == 16 ? 4 : 2)
-    for (int j = lo + sub; j < hi; j += kSplit) {
-      const size_t kr = (size_t)u * a.nk + j;
-      const bool vis = visible(qd, a.kdesc[kr], a.gmask);
-      const HeadVec<DH> kv = load_head<DH>(a.k + kr * a.kvpitch + h * DH);
-      const HeadVec<DH> vv = load_head<DH>(a.v + kr * a.kvpitch + h * DH);
-      const float sc = vis ? scale * dot<DH>(qv, kv) : -3.0e38f;
-      const float mn = fmaxf(mx, sc);
-      const float corr = __expf(mx - mn), p = vis ? __expf(sc - mn) : 0.f;
-      l = l * corr + p;
-#pragma unroll
-      for (int c = 0; c < DH; ++c) acc[c] *= corr;
-      axpy<DH>(acc, p, vv);
-      mx = mn;
-    }
-  }
-  const float mall = split_max(mx);
-  const float corr = __expf(mx - mall);          // a lane without a visible key: l = 0, acc = 0
-  l = split_sum(l * corr);
-  const float inv = l > 0.f ? 1.f / l : 0.f;
-#pragma unroll
-  for (int c = 0; c < DH; ++c) acc[c] = split_sum(acc[c] * corr) * inv;
-  if (sub == 0) {
-    store_head<DH>(o + (size_t)row * d + h * DH, acc);
-    stat[(size_t)row * a.heads + h] = make_float2(l > 0.f ? mall + __logf(l) : 0.f, 0.f);
-  }
-}
-
-// Query side of the backward: with P_ij = exp(s_ij - lse_i) and dP_ij = do_i . v_j,
-// D_i = sum_j P_ij dP_ij and dq_i = scale (sum_j P_ij dP_ij k_j - D_i sum_j P_ij k_j), one pass.
-template <int DH>
-__global__ __launch_bounds__(256) void bw_set_attn_bwd_q_kernel(SetAttn a, const __bf16* __restrict__ dob, int d,
-                                                                __bf16* __restrict__ dq, int dqpitch, float2* __restrict__ stat) {
-  const long long idx = ((long long)blockIdx.x * 256 + threadIdx.x) / kSplit;
-  const int sub = threadIdx.x % kSplit;
-  if (idx >= (long long)a.B * a.nq * a.heads) return;
-  const int row = (int)(idx / a.heads), h = (int)(idx - (long long)row * a.heads);
-  const int u = row / a.nq, qd = a.qdesc[row];
-  float A[DH], Bv[DH];
-#pragma unroll
-  for (int c = 0; c < DH; ++c) { A[c] = 0.f; Bv[c] = 0.f; }
-  float D = 0.f;
-  const float scale = rsqrtf((float)DH);
-  const float lse = stat[(size_t)row * a.heads + h].x;
-  if (qd >= 0) {
-    const HeadVec<DH> qv = load_head<DH>(a.q + (size_t)row * a.qpitch + h * DH);
-    const HeadVec<DH> dov = load_head<DH>(dob + (size_t)row * d + h * DH);
-    int lo, hi;
-    key_range(a, qd, row - u * a.nq, &lo, &hi);
-    // (branch-free, unrolled loops as in the forward kernel were slower here: more live registers)
-    for (int j = lo + sub; j < hi; j += kSplit) {
-      const size_t kr = (size_t)u * a.nk + j;
-      if (!visible(qd, a.kdesc[kr], a.gmask)) continue;
-      const HeadVec<DH> kv = load_head<DH>(a.k + kr * a.kvpitch + h * DH);
-      const HeadVec<DH> vv = load_head<DH>(a.v + kr * a.kvpitch + h * DH);
-      const float p = __expf(scale * dot<DH>(qv, kv) - lse);
-      const float pd = p * dot<DH>(dov, vv);
-      D += pd;
-      axpy<DH>(A, pd, kv);
-      axpy<DH>(Bv, p, kv);
-    }
-  }
-  D = split_sum(D);
-#pragma unroll
-  for (int c = 0; c < DH; ++c) A[c] = scale * (split_sum(A[c]) - D * split_sum(Bv[c]));
-  if (sub == 0) {
-    store_head<DH>(dq + (size_t)row * dqpitch + h * DH, A);
-    stat[(size_t)row * a.heads + h].y = D;
-  }
-}
-
-// Key side: dv_j = sum_i P_ij do_i, dk_j = scale sum_i P_ij (do_i . v_j - D_i) q_i over the user's query
-// rows that see key j.
-template <int DH>
-__global__ __launch_bounds__(256) void bw_set_attn_bwd_kv_kernel(SetAttn a, const __bf16* __restrict__ dob, int d,
-                                                                 __bf16* __restrict__ dk, __bf16* __restrict__ dv, int dkvpitch,
-                                                                 const float2* __restrict__ stat) {
-  const long long idx = ((long long)blockIdx.x * 256 + threadIdx.x) / kSplit;
-  const int sub = threadIdx.x % kSplit;
-  if (idx >= (long long)a.B * a.nk * a.heads) return;
-  const int kr = (int)(idx / a.heads), h = (int)(idx - (long long)kr * a.heads);
-  const int u = kr / a.nk, kd = a.kdesc[kr];
-  float gk[DH], gv[DH];
-#pragma unroll
-  for (int c = 0; c < DH; ++c) { gk[c] = 0.f; gv[c] = 0.f; }
-  if (kd >= 0) {
-    const float scale = rsqrtf((float)DH);
-    const HeadVec<DH> kv = load_head<DH>(a.k + (size_t)kr * a.kvpitch + h * DH);
-    const HeadVec<DH> vv = load_head<DH>(a.v + (size_t)kr * a.kvpitch + h * DH);
-    // a sequence key of a self layer is seen by the global rows and by the slots from its own on
-    const int own = kr - u * a.nk;
-    const int skip_lo = a.m, skip_hi = (a.self && kd >= kSeq) ? max(a.m, own) : a.m;
-    for (int i0 = sub; i0 < a.nq - (skip_hi - skip_lo); i0 += kSplit) {
-      const int i = i0 < skip_lo ? i0 : i0 + (skip_hi - skip_lo);      // the rows outside [skip_lo, skip_hi)
-      const size_t qr = (size_t)u * a.nq + i;
-      if (!visible(a.qdesc[qr], kd, a.gmask)) continue;
-      const HeadVec<DH> qi = load_head<DH>(a.q + qr * a.qpitch + h * DH);
-      const HeadVec<DH> doi = load_head<DH>(dob + qr * d + h * DH);
-      const float2 st = stat[qr * a.heads + h];
-      const float p = __expf(scale * dot<DH>(qi, kv) - st.x);
-      const float ds = scale * p * (dot<DH>(doi, vv) - st.y);
-      axpy<DH>(gv, p, doi);
-      axpy<DH>(gk, ds, qi);
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < DH; ++c) { gk[c] = split_sum(gk[c]); gv[c] = split_sum(gv[c]); }
-  if (sub == 0) {
-    store_head<DH>(dk + (size_t)kr * dkvpitch + h * DH, gk);
-    store_head<DH>(dv + (size_t)kr * dkvpitch + h * DH, gv);
-  }
-}
-
-// The same three kernels with one workgroup per (user, head): the rows every thread of the loop reads
-// (the user's keys and values; for the key side its queries, output gradients and their statistics)
-// are copied to LDS once, together with their descriptors, and the loops read them from there (all
-// lanes the same address: a broadcast).  One thread per query row (key row), strided by the workgroup.
-// Dynamic LDS: n rows x (2 DH bf16 + extras), see set_attn_lds_bytes.
-template <int DH>
-__device__ __forceinline__ HeadVec<DH> lds_head(const uint4* s, int row) {
-  HeadVec<DH> v;
-#pragma unroll
-  for (int c = 0; c < DH / 8; ++c) v.c[c] = __builtin_bit_cast(bf16x8, s[row * (DH / 8) + c]);
-  return v;
-}
-template <int DH>
-__device__ __forceinline__ void stage_heads(uint4* dst, const __bf16* src, size_t pitch, int n, int h) {
-  constexpr int CP = DH / 8;
-  for (int c = threadIdx.x; c < n * CP; c += blockDim.x)
-    dst[c] = *(const uint4*)(src + (size_t)(c / CP) * pitch + h * DH + 8 * (c % CP));
-}
-
-// S adjacent lanes share a row: lane s of them takes every S-th key (query) of the loop, and the partial
-// results meet through cross-lane shuffles.  The loops are chains of dependent LDS reads and arithmetic,
-// and a workgroup has only as many rows as a user has queries (keys): more lanes per row hide the latency.
-template <int S>
-__device__ __forceinline__ float lanes_sum(float v) {
-#pragma unroll
-  for (int o = 1; o < S; o <<= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-template <int S>
-__device__ __forceinline__ float lanes_max(float v) {
-#pragma unroll
-  for (int o = 1; o < S; o <<= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-
-template <int DH, int S>
-__global__ __launch_bounds__(512) void bw_set_attn_fwd_lds_kernel(SetAttn a, __bf16* __restrict__ o, int d, float2* __restrict__ stat) {
-  extern __shared__ uint4 sm[];
-  uint4* sK = sm; uint4* sV = sm + (size_t)a.nk * (DH / 8);
-  int* sD = (int*)(sV + (size_t)a.nk * (DH / 8));
-  const int u = blockIdx.x / a.heads, h = blockIdx.x - u * a.heads;
-  stage_heads<DH>(sK, a.k + (size_t)u * a.nk * a.kvpitch, a.kvpitch, a.nk, h);
-  stage_heads<DH>(sV, a.v + (size_t)u * a.nk * a.kvpitch, a.kvpitch, a.nk, h);
-  for (int j = threadIdx.x; j < a.nk; j += blockDim.x) sD[j] = a.kdesc[(size_t)u * a.nk + j];
-  __syncthreads();
-  const float scale = rsqrtf((float)DH);
-  const int sub = threadIdx.x % S;
-  for (int base = 0; base < a.nq * S; base += blockDim.x) {        // (blockDim.x is a multiple of 64: a row's lanes share a wave)
-    const int i = (base + threadIdx.x) / S;
-    const bool live = i < a.nq;
-    const size_t row = (size_t)u * a.nq + (live ? i : 0);
-    const int qd = live ? a.qdesc[row] : -1;
-    float acc[DH];
-#pragma unroll
-    for (int c = 0; c < DH; ++c) acc[c] = 0.f;
-    float mx = -3.0e38f, l = 0.f;
-    if (qd >= 0) {
-      const HeadVec<DH> qv = load_head<DH>(a.q + row * a.qpitch + h * DH);
-      int lo, hi;
-      key_range(a, qd, i, &lo, &hi);
-#pragma unroll 2
-      for (int j = lo + sub; j < hi; j += S) {
-        const bool vis = visible(qd, sD[j], a.gmask);
-        const float sc = vis ? scale * dot<DH>(qv, lds_head<DH>(sK, j)) : -3.0e38f;
-        const float mn = fmaxf(mx, sc);
-        const float corr = __expf(mx - mn), p = vis ? __expf(sc - mn) : 0.f;
-        l = l * corr + p;
-#pragma unroll
-        for (int c = 0; c < DH; ++c) acc[c] *= corr;
-        axpy_packed<DH>(acc, p, lds_head<DH>(sV, j));
-        mx = mn;
-      }
-    }
-    const float mall = lanes_max<S>(mx);
-    const float corr = __expf(mx - mall);          // a lane without a visible key: l = 0, acc = 0
-    l = lanes_sum<S>(l * corr);
-    const float inv = l > 0.f ? 1.f / l : 0.f;
-#pragma unroll
-    for (int c = 0; c < DH; ++c) acc[c] = lanes_sum<S>(acc[c] * corr) * inv;
-    if (live && sub == 0) {
-      store_head<DH>(o + row * d + h * DH, acc);
-      stat[row * a.heads + h] = make_float2(l > 0.f ? mall + __logf(l) : 0.f, 0.f);
-    }
-  }
-}
-
-template <int DH, int S>
-__global__ __launch_bounds__(512) void bw_set_attn_bwd_q_lds_kernel(SetAttn a, const __bf16* __restrict__ dob, int d,
-                                                                   __bf16* __restrict__ dq, int dqpitch, float2* __restrict__ stat) {
-  extern __shared__ uint4 sm[];
-  uint4* sK = sm; uint4* sV = sm + (size_t)a.nk * (DH / 8);
-  int* sD = (int*)(sV + (size_t)a.nk * (DH / 8));
-  const int u = blockIdx.x / a.heads, h = blockIdx.x - u * a.heads;
-  stage_heads<DH>(sK, a.k + (size_t)u * a.nk * a.kvpitch, a.kvpitch, a.nk, h);
-  stage_heads<DH>(sV, a.v + (size_t)u * a.nk * a.kvpitch, a.kvpitch, a.nk, h);
-  for (int j = threadIdx.x; j < a.nk; j += blockDim.x) sD[j] = a.kdesc[(size_t)u * a.nk + j];
-  __syncthreads();
-  const float scale = rsqrtf((float)DH);
-  const int sub = threadIdx.x % S;
-  for (int base = 0; base < a.nq * S; base += blockDim.x) {
-    const int i = (base + threadIdx.x) / S;
-    const bool live = i < a.nq;
-    const size_t row = (size_t)u * a.nq + (live ? i : 0);
-    const int qd = live ? a.qdesc[row] : -1;
-    float A[DH], Bv[DH];
-#pragma unroll
-    for (int c = 0; c < DH; ++c) { A[c] = 0.f; Bv[c] = 0.f; }
-    float D = 0.f;
-    if (qd >= 0) {
-      const float lse = stat[row * a.heads + h].x;
-      const HeadVec<DH> qv = load_head<DH>(a.q + row * a.qpitch + h * DH);
-      const HeadVec<DH> dov = load_head<DH>(dob + row * d + h * DH);
-      int lo, hi;
-      key_range(a, qd, i, &lo, &hi);
-      for (int j = lo + sub; j < hi; j += S) {
-        if (!visible(qd, sD[j], a.gmask)) continue;
-        const HeadVec<DH> kv = lds_head<DH>(sK, j);
-        const float p = __expf(scale * dot<DH>(qv, kv) - lse);
-        const float pd = p * dot<DH>(dov, lds_head<DH>(sV, j));
-        D += pd;
-        axpy_packed<DH>(A, pd, kv);
-        axpy_packed<DH>(Bv, p, kv);
-      }
-    }
-    D = lanes_sum<S>(D);
-#pragma unroll
-    for (int c = 0; c < DH; ++c) A[c] = scale * (lanes_sum<S>(A[c]) - D * lanes_sum<S>(Bv[c]));
-    if (live && sub == 0) {
-      store_head<DH>(dq + row * dqpitch + h * DH, A);
-      stat[row * a.heads + h].y = D;
-    }
-  }
-}
-
-template <int DH, int S>
-__global__ __launch_bounds__(512) void bw_set_attn_bwd_kv_lds_kernel(SetAttn a, const __bf16* __restrict__ dob, int d,
-                                                                    __bf16* __restrict__ dk, __bf16* __restrict__ dv, int dkvpitch,
-                                                                    const float2* __restrict__ stat) {
-  extern __shared__ uint4 sm[];
-  uint4* sQ = sm; uint4* sO = sm + (size_t)a.nq * (DH / 8);
-  float2* sS = (float2*)(sO + (size_t)a.nq * (DH / 8));
-  int* sD = (int*)(sS + a.nq);
-  const int u = blockIdx.x / a.heads, h = blockIdx.x - u * a.heads;
-  stage_heads<DH>(sQ, a.q + (size_t)u * a.nq * a.qpitch, a.qpitch, a.nq, h);
-  stage_heads<DH>(sO, dob + (size_t)u * a.nq * d, d, a.nq, h);
-  for (int i = threadIdx.x; i < a.nq; i += blockDim.x) {
-    sS[i] = stat[((size_t)u * a.nq + i) * a.heads + h];
-    sD[i] = a.qdesc[(size_t)u * a.nq + i];
-  }
-  __syncthreads();
-  const float scale = rsqrtf((float)DH);
-  const int sub = threadIdx.x % S;
-  for (int base = 0; base < a.nk * S; base += blockDim.x) {
-    const int own = (base + threadIdx.x) / S;
-    const bool live = own < a.nk;
-    const size_t kr = (size_t)u * a.nk + (live ? own : 0);
-    const int kd = live ? a.kdesc[kr] : -1;
-    float gk[DH], gv[DH];
-#pragma unroll
-    for (int c = 0; c < DH; ++c) { gk[c] = 0.f; gv[c] = 0.f; }
-    if (kd >= 0) {
-      const HeadVec<DH> kv = load_head<DH>(a.k + kr * a.kvpitch + h * DH);
-      const HeadVec<DH> vv = load_head<DH>(a.v + kr * a.kvpitch + h * DH);
-      // a sequence key of a self layer is seen by the global rows and by the slots from its own on
-      const int skip_lo = a.m, skip_hi = (a.self && kd >= kSeq) ? max(a.m, own) : a.m;
-      for (int i0 = sub; i0 < a.nq - (skip_hi - skip_lo); i0 += S) {
-        const int i = i0 < skip_lo ? i0 : i0 + (skip_hi - skip_lo);      // the rows outside [skip_lo, skip_hi)
-        if (!visible(sD[i], kd, a.gmask)) continue;
-        const HeadVec<DH> qi = lds_head<DH>(sQ, i);
-        const HeadVec<DH> doi = lds_head<DH>(sO, i);
-        const float2 st = sS[i];
-        const float p = __expf(scale * dot<DH>(qi, kv) - st.x);
-        const float ds = scale * p * (dot<DH>(doi, vv) - st.y);
-        axpy_packed<DH>(gv, p, doi);
-        axpy_packed<DH>(gk, ds, qi);
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < DH; ++c) { gk[c] = lanes_sum<S>(gk[c]); gv[c] = lanes_sum<S>(gv[c]); }
-    if (live && sub == 0) {
-      store_head<DH>(dk + kr * dkvpitch + h * DH, gk);
-      store_head<DH>(dv + kr * dkvpitch + h * DH, gv);
-    }
   }
 }
 
@@ -2073,7 +1689,7 @@ static int check_stack(const longer_config* c, int B, int L, StackDims* s) {
   s->d = d; s->f = c->ffn_mult * d; s->heads = c->heads; s->dh = d / c->heads; s->m = c->m; s->k = c->k_recent;
   s->n = c->m + c->k_recent; s->T = (L + c->K - 1) / c->K; s->B = B; s->layers = 1 + c->n_self;
   s->rq = (size_t)B * s->n; s->rk = (size_t)B * (c->m + s->T);
-  if (s->rk * (size_t)s->heads * kSplit >= ((size_t)1 << 31) - 256) return api_error(LONGER_ERR_ARG, "too many key rows for one call; split the batch");
+  if (s->rk * (size_t)s->heads >= ((size_t)1 << 31) - 256) return api_error(LONGER_ERR_ARG, "too many key rows for one call; split the batch");
   return 0;
 }
 
@@ -2091,31 +1707,6 @@ static ModelGrads model_grads(const Dims& mi, const StackDims& s, bool learn) {
   g.q_learn = (g.head_b + 1 + 3) & ~(size_t)3;
   g.total = g.q_learn + (learn ? (size_t)s.k * s.d : 0);
   return g;
-}
-
-// bytes of LDS the staged kernels need for n rows (two head vectors per row, its descriptor, and on the
-// key side the query's two statistics)
-static size_t set_attn_lds_bytes(int n, int dh, bool key_side) { return (size_t)n * (2 * dh * 2 + 4 + (key_side ? 8 : 0)); }
-constexpr size_t kSetAttnLdsMax = 64 * 1024;     // what a workgroup may take without an opt-in
-
-template <int DH>
-static void set_attn_launch(hipStream_t st, int which, const SetAttn& a, const __bf16* dob, int d, __bf16* o_or_dq, int pitch,
-                            __bf16* dk, __bf16* dv, float2* stat) {
-  const unsigned gq = (unsigned)(((size_t)a.B * a.nq * a.heads * kSplit + 255) / 256);
-  const unsigned gk = (unsigned)(((size_t)a.B * a.nk * a.heads * kSplit + 255) / 256);
-  const size_t lq = set_attn_lds_bytes(a.nk, DH, false), lk = set_attn_lds_bytes(a.nq, DH, true);
-  auto threads = [](int n) { int t = (n + 63) / 64 * 64; return t > 512 ? 512 : t; };
-  const unsigned wgs = (unsigned)a.B * a.heads;
-  // lanes per row: 1 / 2 / 4 / 8 measured at the headline batch (forward, query side, key side, four layers each):
-  // 429 + 511 + 399, 324 + 367 + 336, 276 + 322 + 336, 274 + 324 + 380 us
-  constexpr int kLanes = 4;
-  if ((which == 2 ? lk : lq) <= kSetAttnLdsMax) {
-    if (which == 0) bw_set_attn_fwd_lds_kernel<DH, kLanes><<<wgs, threads(a.nq * kLanes), lq, st>>>(a, o_or_dq, d, stat);
-    else if (which == 1) bw_set_attn_bwd_q_lds_kernel<DH, kLanes><<<wgs, threads(a.nq * kLanes), lq, st>>>(a, dob, d, o_or_dq, pitch, stat);
-    else bw_set_attn_bwd_kv_lds_kernel<DH, kLanes><<<wgs, threads(a.nk * kLanes), lk, st>>>(a, dob, d, dk, dv, pitch, stat);
-  } else if (which == 0) bw_set_attn_fwd_kernel<DH><<<gq, 256, 0, st>>>(a, o_or_dq, d, stat);
-  else if (which == 1) bw_set_attn_bwd_q_kernel<DH><<<gq, 256, 0, st>>>(a, dob, d, o_or_dq, pitch, stat);
-  else bw_set_attn_bwd_kv_kernel<DH><<<gk, 256, 0, st>>>(a, dob, d, dk, dv, pitch, stat);
 }
 
 static int run_model(const longer_config* c, const longer_weights* wts, const void* H, const void* G, const int32_t* lens,
@@ -2173,7 +1764,7 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
 
   auto attn = [&](int l) {
     SetAttn t;
-    t.qdesc = qdesc; t.nq = s.n; t.B = B; t.heads = s.heads; t.gmask = c->gmask; t.m = s.m; t.self = l != 0;
+    t.qdesc = qdesc; t.nq = s.n; t.B = B; t.heads = s.heads; t.gmask = c->gmask;
     if (l == 0) { t.q = qkv; t.qpitch = d; t.k = kv; t.v = kv + d; t.kvpitch = 2 * d; t.kdesc = kdesc; t.nk = s.m + s.T; }
     else { t.q = qkv; t.qpitch = 3 * d; t.k = qkv + d; t.v = qkv + 2 * d; t.kvpitch = 3 * d; t.kdesc = qdesc; t.nk = s.n; }
     return t;
