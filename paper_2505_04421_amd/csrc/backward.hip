@@ -100,24 +100,6 @@ __device__ __forceinline__ float act_grad(float v, int act) {
   return c + v * 0.39894228040143268f * e;
 }
 
-// The activation and its derivative at once, for the launch that rounds both to bf16 right away.
-// GELU: Phi(v) - 1/2 as v times an even polynomial of degree 8 (minimax fit on [-3.5, 3.5] that reaches 1/2
-// at the interval's end, clamped to [0, 1] beyond it; absolute error below 1.3e-3, under the bf16
-// rounding step of the values it produces) and the density from one exponential.
-__device__ __forceinline__ void act_both(float v, int act, float* a, float* da) {
-  if (act == LONGER_ACT_RELU) { *a = v > 0.f ? v : 0.f; *da = v > 0.f ? 1.f : 0.f; return; }
-  const float u = v * v;
-  float pl = 9.366767568843253e-06f;
-  pl = fmaf(pl, u, -0.0003847714538096606f);
-  pl = fmaf(pl, u, 0.0064495445928312006f);
-  pl = fmaf(pl, u, -0.05893596715178192f);
-  pl = fmaf(pl, u, 0.3934098519357524f);
-  const float c = __builtin_amdgcn_fmed3f(fmaf(v, pl, 0.5f), 0.f, 1.f);
-  const float e = __expf(-0.5f * u);
-  *a = v * c;
-  *da = fmaf(v * e, 0.39894228040143268f, c);
-}
-
 constexpr int kStagePitch = 68;         // floats per row of the epilogue's staging area (64 + 4 pad)
 
 // KS: contraction elements per step.  Every launch uses 32: steps of 64 and 128 (one LDS buffer per operand
@@ -1251,6 +1233,79 @@ __global__ __launch_bounds__(256) void bw_transpose_kernel(const __bf16* __restr
     if (c0 + i < cols && r0 + x < rows) out[(size_t)(c0 + i) * rows + r0 + x] = t[x][i];
 }
 
+// ------------------------------------------------------------------------------------
+// Weights of InnerTrans blocks for the block kernel (bw_block.h): the segments in the order it consumes them, each
+// D / 16 fragments of 64 lanes x 16 bytes.  Fragment = 32 rows of the product's result (lane % 32) x 16 contracted
+// features in the order the lanes hold them (element e of lane half hi: 8 (e / 4) + 4 hi + e % 4).
+constexpr int kPackBlocks = 8;            // blocks per launch
+struct PackBlocks { struct { const __bf16 *wq, *wk, *wv, *wo, *w1, *w2; } b[kPackBlocks]; __bf16* out; size_t stride; };   // stride: elements
+__global__ __launch_bounds__(256) void bw_pack_block_kernel(const PackBlocks a, int d, int f) {
+  const int NT = d / 32, NG = d / 16, NC = f / 32, segs = bw_block_segs(d, f), padded = bw_block_segs_padded(d, f);
+  const auto& b = a.b[blockIdx.y];
+  __bf16* out = a.out + blockIdx.y * a.stride;
+  const int total = padded * NG * 64;
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
+    const int lane = i & 63, fr = i >> 6, s = fr % NG;
+    int seg = fr / NG;
+    const int m = lane & 31, hi = lane >> 5;
+    // element (k, m) of the fragment sits at src[k ks + m ms], k the contracted feature
+    const __bf16* src = nullptr;
+    int ks = 1;
+    if (seg < 3 * NT) {                                  // Q, K, V of 32 features
+      const __bf16* w = seg % 3 == 0 ? b.wq : seg % 3 == 1 ? b.wk : b.wv;
+      src = w + (size_t)(16 * s) * d + 32 * (seg / 3) + m; ks = d;
+    } else if (seg < 4 * NT) {                           // output projection
+      src = b.wo + (size_t)(16 * s) * d + 32 * (seg - 3 * NT) + m; ks = d;
+    } else if (seg < 4 * NT + 3 * NC) {
+      seg -= 4 * NT;
+      const int c = seg / 3;
+      if (seg % 3 == 0) { src = b.w1 + (size_t)(16 * s) * f + 32 * c + m; ks = f; }                   // hidden values
+      else if (seg % 3 == 1) src = b.w2 + (size_t)(32 * c + m) * d + 16 * s;                          // their gradient
+      else src = b.w1 + (size_t)(32 * (s / 2) + m) * f + 32 * c + 16 * (s % 2);                       // back through W1
+    } else if (seg < segs) {
+      seg -= 4 * NT + 3 * NC;
+      const int ft = seg / 4;
+      if (seg % 4 == 0) src = b.wo + (size_t)(32 * ft + m) * d + 16 * s;                              // back through W_O
+      else {
+        const __bf16* w = seg % 4 == 1 ? b.wq : seg % 4 == 2 ? b.wk : b.wv;
+        src = w + (size_t)(32 * (s / 2) + m) * d + 32 * ft + 16 * (s % 2);                            // through W_Q, W_K, W_V
+      }
+    }
+    bf16x8 v;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = src ? src[(size_t)(8 * (e / 4) + 4 * hi + e % 4) * ks] : (__bf16)0.f;
+    *(bf16x8*)(out + (size_t)i * 8) = v;
+  }
+}
+
+// The parameter gradients that the block kernel leaves in terms of the normalised rows xh (y = xh g + s in front
+// of the products W): with X = xh^T dY and c = column sums of dY (bias gradients) both summed by now,
+//   dW = diag(g) X + s c^T,   dg[e] = sum_c W[e][c] X[e][c],   ds[e] = sum_c W[e][c] c[c],
+// so the LayerNorm gradients need no pass over the tokens.  One workgroup per row e and LayerNorm.
+struct NormGrads { struct { const __bf16 *w[3], *gain, *shift; float *dw, *dgain; } n[2 * kPackBlocks]; };
+__global__ __launch_bounds__(256) void bw_norm_grads_kernel(const NormGrads a, int d, int f) {
+  const int which = blockIdx.y & 1, e = blockIdx.x, n = which ? f : d, mats = which ? 1 : 3;     // ln1: Q, K, V; ln2: W1
+  const auto& q = a.n[blockIdx.y];
+  const float gain = (float)q.gain[e], shift = (float)q.shift[e];
+  float sg = 0.f, ss = 0.f;
+  for (int i = threadIdx.x; i < mats * n; i += 256) {
+    const int j = i / n, c = i - j * n;
+    float* m = q.dw + (size_t)j * ((size_t)d * n + n);
+    const float w = (float)q.w[j][(size_t)e * n + c], bias = m[(size_t)d * n + c], X = m[(size_t)e * n + c];
+    sg = fmaf(w, X, sg);
+    ss = fmaf(w, bias, ss);
+    m[(size_t)e * n + c] = fmaf(gain, X, shift * bias);
+  }
+  __shared__ float red[2][4];
+  sg = wave_sum(sg); ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) { red[0][threadIdx.x >> 6] = sg; red[1][threadIdx.x >> 6] = ss; }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    const float* r = red[threadIdx.x];
+    q.dgain[threadIdx.x * d + e] = r[0] + r[1] + r[2] + r[3];
+  }
+}
+
 // ------------------------------------------------------------------------------------ host side
 static inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 
@@ -1284,6 +1339,7 @@ struct Workspace {
   size_t dy, dyb, dh, dn, dxm, dxmb, dob, dqkv, stat;
   size_t part, lnpart;                     // partial parameter gradients of one block: matrices, LayerNorms (ln1, ln2)
   size_t fwd, fwd_bytes, ztmp;             // the fused forward kernel's scratch and output when it recomputes block inputs
+  size_t stream;                           // block kernel: packed weights per layer (n1, n2 hold the normalised rows, qkv also dqkv)
   size_t total;
 };
 // The gradients of an InnerTrans block's four products (Q / K / V side by side), all over the raw token rows
@@ -1297,11 +1353,25 @@ static WgradBatch block_wgrads(int d, int f, size_t ntok, RowsValid rv, const __
   w.add(n1, d, d, dqkv, 3 * d, 3 * d, d, ntok, rv, g + gl.wq);
   return w;
 }
+// the same on the block kernel's tile blocks
+static WgradBatch block_wgrads_tiles(int d, int f, size_t slots, RowsValid rv, const __bf16* xh1, const __bf16* dqkv, const __bf16* o,
+                                     const __bf16* dxmb, const __bf16* xh2, const __bf16* dh, const __bf16* a, const __bf16* dyb, float* g) {
+  const GradLayout gl = grad_layout(d, f);
+  WgradBatch w(d, slots, true);
+  w.add(a, f / 16, f, dyb, d / 16, d, d, slots, rv, g + gl.w2);
+  w.add(xh2, d / 16, d, dh, f / 16, f, f, slots, rv, g + gl.w1);
+  w.add(o, d / 16, d, dxmb, d / 16, d, d, slots, rv, g + gl.wo);
+  w.add(xh1, d / 16, d, dqkv, 3 * d / 16, 3 * d, d, slots, rv, g + gl.wq);
+  return w;
+}
 static int launch(WgradBatch& w, float* part, hipStream_t st) {
   w.place(part);
   const unsigned grid = (unsigned)((w.a.nslices + 7) / 8 * 8 * w.a.tiles);
-  if (w.tb == 128) bw_wgrad_kernel<128><<<grid, 256, 0, st>>>(w.a);
-  else bw_wgrad_kernel<64><<<grid, 256, 0, st>>>(w.a);
+  if (w.tiled) {
+    if (w.tb == 128) bw_wgrad_kernel<128, true><<<grid, 256, 0, st>>>(w.a);
+    else bw_wgrad_kernel<64, true><<<grid, 256, 0, st>>>(w.a);
+  } else if (w.tb == 128) bw_wgrad_kernel<128, false><<<grid, 256, 0, st>>>(w.a);
+  else bw_wgrad_kernel<64, false><<<grid, 256, 0, st>>>(w.a);
   return hipGetLastError() == hipSuccess ? 0 : api_error(LONGER_ERR_HIP, "parameter gradient launch failed");
 }
 static int launch(const ReduceBatch& r, hipStream_t st) {
@@ -1343,13 +1413,39 @@ static Workspace workspace(int layers, size_t ntok, int d, int f, int heads, siz
   return w;
 }
 
-struct Dims { int d, f, heads, dh, layers, K, T; size_t ntok; };
+// tiled: a block is one launch of the block kernel (bw_block.h); slots: B T K, padded: in whole workgroups of it
+struct Dims { int d, f, heads, dh, layers, K, T; size_t ntok, slots, padded; bool tiled; };
+
+// Workspace of the block kernel's form: tile blocks over the slots, block inputs [B][T K][d]
+static Workspace tiled_workspace(const Dims& s, size_t fwd_bytes) {
+  Workspace w = {};
+  size_t o = 0;
+  auto take = [&](size_t bytes) { size_t at = o; o += up256(bytes); return at; };
+  const size_t n = s.padded, d = s.d, f = s.f;
+  w.stream = take((size_t)s.layers * bw_block_segs_padded(s.d, s.f) * packed_seg_bytes(s.d, 2));
+  w.xin = take((size_t)(s.layers - 1) * n * d * 4);
+  w.n1 = take(n * d * 2);
+  w.qkv = take(n * 3 * d * 2);
+  w.o = take(n * d * 2);
+  w.n2 = take(n * d * 2);
+  w.a = take(n * f * 2);
+  w.dh = take(n * f * 2);
+  w.dyb = take(n * d * 2);
+  w.dxmb = take(n * d * 2);
+  w.dy = take(n * d * 4);
+  w.part = take(block_wgrads_tiles(s.d, s.f, s.slots, RowsValid{}, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr).place(nullptr) * 4);
+  w.fwd = take(fwd_bytes);
+  w.fwd_bytes = fwd_bytes;
+  w.total = o;
+  return w;
+}
 
 // the merge backward's workspace for a batch: with more than one block the fused forward kernel
 // recomputes the block inputs (its scratch; a staging copy when L is not a multiple of K, whose rows
 // then sit at [B, T K] instead of [B, L])
 static Workspace merge_workspace(const longer_config* c, const Dims& s, int B, int L) {
   size_t fwd = 0, zt = 0;
+  if (s.tiled) return tiled_workspace(s, s.layers > 1 ? longer_workspace_bytes(c, B, L) : 0);
   if (s.layers > 1) {
     fwd = longer_workspace_bytes(c, B, L);
     if (L % s.K) zt = (size_t)B * s.T * s.K * s.d * 4;
@@ -1382,6 +1478,11 @@ static int check(const longer_config* c, int B, int L, Dims* s) {
     return api_error(LONGER_ERR_ARG, "B * L = %lld token rows are too many for one call; split the batch", ntok);
   s->d = d; s->f = c->ffn_mult * d; s->heads = c->inner_heads; s->dh = dh; s->layers = c->inner_layers;
   s->K = c->K; s->T = (L + c->K - 1) / c->K; s->ntok = (size_t)ntok;
+  // The block kernel holds a tile's rows and two gradients of them in registers: 192 fp32 values per lane at width
+  // 128, more than there are at 256.  It counts slots in 32 bits.
+  s->slots = (size_t)B * s->T * s->K;
+  s->padded = (s->slots + 32 * kBlkWaves - 1) / (32 * kBlkWaves) * (32 * kBlkWaves);
+  s->tiled = d <= 128 && s->slots < ((size_t)1 << 31) - 256;
   return 0;
 }
 
@@ -1491,8 +1592,71 @@ static unsigned flat_grid(size_t n) {
 
 #define BW_TRY(x) do { int rc_ = (x); if (rc_) return rc_; } while (0)
 
+static int run_tiled(const longer_config* c, const longer_block* inner, const void* H, const int32_t* lens, int B, int L,
+                     const float* dM, float* dH, float* grads, char* ws, hipStream_t st, const Dims& s) {
+  const int d = s.d, f = s.f;
+  const Workspace w = merge_workspace(c, s, B, L);
+  const GradLayout gl = grad_layout(d, f);
+  const RowsValid rv = {lens, s.T * s.K};
+  const size_t stream_elems = (size_t)bw_block_segs_padded(d, f) * packed_seg_bytes(d, 2) / 2;
+  auto at = [&](size_t o) { return (__bf16*)(ws + o); };
+  for (int l0 = 0; l0 < s.layers; l0 += kPackBlocks) {
+    PackBlocks pk = {};
+    const int n = s.layers - l0 < kPackBlocks ? s.layers - l0 : kPackBlocks;
+    for (int i = 0; i < n; ++i) {
+      const longer_block& b = inner[l0 + i];
+      pk.b[i] = {(const __bf16*)b.wq, (const __bf16*)b.wk, (const __bf16*)b.wv, (const __bf16*)b.wo, (const __bf16*)b.w1, (const __bf16*)b.w2};
+    }
+    pk.out = at(w.stream) + l0 * stream_elems; pk.stride = stream_elems;
+    bw_pack_block_kernel<<<dim3((unsigned)((stream_elems / 8 + 255) / 256), n), 256, 0, st>>>(pk, d, f);
+    BW_TRY(launched("weight packing"));
+  }
+  // block inputs, by the fused forward kernel (its fp32 residual stream after l blocks is block l's input)
+  auto xin = [&](int l) { return (float*)(ws + w.xin) + (size_t)(l - 1) * s.padded * d; };
+  for (int l = 1; l < s.layers; ++l) BW_TRY(inner_chain_f32(c, inner, l, H, lens, B, L, xin(l), ws + w.fwd, w.fwd_bytes, st));
+
+  for (int l = s.layers - 1; l >= 0; --l) {
+    const longer_block& b = inner[l];
+    float* g = grads + (size_t)l * gl.total;
+    BlockBwParams p = {};
+    p.wstream = ws + w.stream + (size_t)l * stream_elems * 2;
+    p.ln1_g = (const __bf16*)b.ln1_g; p.ln1_b = (const __bf16*)b.ln1_b; p.bq = (const __bf16*)b.bq; p.bv = (const __bf16*)b.bv;
+    p.bo = (const __bf16*)b.bo; p.ln2_g = (const __bf16*)b.ln2_g; p.ln2_b = (const __bf16*)b.ln2_b; p.b1 = (const __bf16*)b.b1;
+    p.lens = lens; p.B = B; p.L = L; p.K = s.K; p.T = s.T; p.f = f; p.act = c->act; p.eps = c->ln_eps;
+    p.x = l ? (const void*)xin(l) : H; p.x_f32 = l != 0;
+    p.dM = l == s.layers - 1 ? dM : nullptr; p.concat = c->merge == LONGER_MERGE_CONCAT;
+    p.dy = (const float*)(ws + w.dy);
+    p.qkv = at(w.qkv); p.xh1 = at(w.n1); p.o = at(w.o); p.xh2 = at(w.n2); p.a = at(w.a); p.dh = at(w.dh); p.dyb = at(w.dyb);
+    p.dxmb = at(w.dxmb); p.dqkv = at(w.qkv);
+    p.dx = l ? (float*)(ws + w.dy) : dH; p.dx_rows = l == 0;      // (dy in place: a tile's values are read before they are replaced)
+    if (d == 32) bw_block_launch_32(s.dh, p, st);
+    else if (d == 64) bw_block_launch_64(s.dh, p, st);
+    else bw_block_launch_128(s.dh, p, st);
+    BW_TRY(launched("block backward"));
+    WgradBatch wg = block_wgrads_tiles(d, f, s.slots, rv, p.xh1, p.dqkv, p.o, p.dxmb, p.xh2, p.dh, p.a, p.dyb, g);
+    BW_TRY(launch(wg, (float*)(ws + w.part), st));
+    ReduceBatch rb;
+    rb.add(wg);
+    BW_TRY(launch(rb, st));
+  }
+  for (int l0 = 0; l0 < s.layers; l0 += kPackBlocks) {
+    NormGrads ng = {};
+    const int n = s.layers - l0 < kPackBlocks ? s.layers - l0 : kPackBlocks;
+    for (int i = 0; i < n; ++i) {
+      const longer_block& b = inner[l0 + i];
+      float* g = grads + (size_t)(l0 + i) * gl.total;
+      ng.n[2 * i] = {{(const __bf16*)b.wq, (const __bf16*)b.wk, (const __bf16*)b.wv}, (const __bf16*)b.ln1_g, (const __bf16*)b.ln1_b, g + gl.wq, g + gl.ln1_g};
+      ng.n[2 * i + 1] = {{(const __bf16*)b.w1, nullptr, nullptr}, (const __bf16*)b.ln2_g, (const __bf16*)b.ln2_b, g + gl.w1, g + gl.ln2_g};
+    }
+    bw_norm_grads_kernel<<<dim3(d, 2 * n), 256, 0, st>>>(ng, d, f);
+    BW_TRY(launched("LayerNorm gradients"));
+  }
+  return 0;
+}
+
 static int run(const longer_config* c, const longer_block* inner, const void* H, const int32_t* lens, int B, int L,
                const float* dM, float* dH, float* grads, char* ws, hipStream_t st, const Dims& s) {
+  if (s.tiled) return run_tiled(c, inner, H, lens, B, L, dM, dH, grads, ws, st, s);
   const int d = s.d, f = s.f;
   const size_t nt = s.ntok;
   const Workspace w = merge_workspace(c, s, B, L);

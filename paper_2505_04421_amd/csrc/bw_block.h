@@ -1,0 +1,538 @@
+// One InnerTrans block's recomputation and backward pass in one launch, a tile of 32 tokens per wave.
+//
+// Everything between the block's input rows and the operands of its parameter gradients stays in the wave's
+// registers, in the layout of the forward kernels (device.h: lane = token, registers = features; an accumulator
+// tile rounded to bf16 is the next product's operand): LayerNorm, Q / K / V, the attention inside the groups,
+// output projection, LayerNorm, the FFN's hidden values and their gradient chunk by chunk, and back through all
+// of them.  What reaches memory is what the parameter gradients contract over the whole batch, and q, k, v, which
+// wait there for the way back.
+//
+// What bounds it: as thirteen launches over [token, feature] tensors (two LayerNorms, three products, attention,
+// the FFN's middle, three products back, attention back, two LayerNorms back) a block of the headline batch
+// (512 000 rows of width 128) moved 18.8 KB per token beside its parameter gradients; here it is 7.4 KB.
+//
+// Tile blocks.  A tensor of F features that the parameter gradients read is stored as [tile][F / 16][1 KiB]: 16
+// features of 32 tokens, 32 bytes per token, as the lanes hold them (lane half hi: features 4 hi .. + 3 and
+// 8 + 4 hi .. + 3 of the sixteen), so a store or load of a wave is 1 KiB without gaps and the transposing LDS
+// read finds four consecutive features in every 8 bytes.  In odd sixteens the tokens' 128-byte quarters are
+// swapped pairwise, so that the two sixteens of a fragment lie in different LDS banks.
+// Tiles count slots [B][T K] (a user's groups, the last one filled up), so a group never spans two tiles.
+#pragma once
+#include "block_kernel.h"
+#include "bw_common.h"
+
+namespace longer {
+namespace bw {
+
+struct BlockBwParams {
+  const char* wstream;                      // packed weights of the block (bw_pack_block_kernel)
+  const __bf16 *ln1_g, *ln1_b, *bq, *bv, *bo, *ln2_g, *ln2_b, *b1;
+  const int32_t* lens;
+  int B, L, K, T, f, act;
+  float eps;
+  const void* x; int x_f32;                 // the block's input rows: raw tokens [B][L][D] bf16, or [B][T K][D] fp32
+  const float* dM; int concat;              // gradient of the block's output: from the merged tokens' gradient,
+  const float* dy;                          // or (dM NULL) the fp32 tile blocks the block after this one wrote
+  __bf16 *qkv, *xh1, *o, *xh2, *a, *dh, *dyb, *dxmb, *dqkv;    // tile blocks (xh: normalised rows before gain and shift)
+  float* dx; int dx_rows;                   // gradient of the input: fp32 tile blocks, or [B][L][D] (zeros for padded tokens)
+};
+
+constexpr int kBlkWaves = 4;
+__host__ __device__ inline int bw_block_segs(int d, int f) { return 8 * (d / 32) + 3 * (f / 32); }
+constexpr int kBlkPanel = 2;                // segments per panel of the weight stream (4 below width 128)
+// segments that are readable: the stream is read in whole panels
+__host__ __device__ inline int bw_block_segs_padded(int d, int f) { return (bw_block_segs(d, f) + 3) / 4 * 4; }
+// floats of the block's vectors in LDS: ln1 gain and shift, b_Q, b_V, b_O, ln2 gain and shift, b_1
+__host__ __device__ inline int bw_block_vec_floats(int d, int f) { return 7 * d + f; }
+
+void bw_block_launch_32(int dh, const BlockBwParams& p, hipStream_t st);
+void bw_block_launch_64(int dh, const BlockBwParams& p, hipStream_t st);
+void bw_block_launch_128(int dh, const BlockBwParams& p, hipStream_t st);
+
+__device__ __forceinline__ size_t tile_block_offset(int tile, int groups, int g, int lane) {     // in bytes
+  const int j = lane & 31, hi = lane >> 5;
+  return ((size_t)tile * groups + g) * 1024 + ((j ^ (4 * (g & 1))) * 32 + hi * 16);
+}
+__device__ __forceinline__ void tile_store(__bf16* base, int tile, int groups, int g, int lane, bf16x8 v) {
+  *(bf16x8*)((char*)base + tile_block_offset(tile, groups, g, lane)) = v;
+}
+__device__ __forceinline__ bf16x8 tile_load(const __bf16* base, int tile, int groups, int g, int lane) {
+  return *(const bf16x8*)((const char*)base + tile_block_offset(tile, groups, g, lane));
+}
+
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+__device__ __forceinline__ bf16x8 join_tr(s16x4 lo, s16x4 up) {
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
+  const s16x8 v = __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7);
+  return __builtin_bit_cast(bf16x8, v);
+}
+// byte offset, inside a 2 KiB piece (32 features = two sixteens) of a tile block, that this lane hands to the
+// transposing read: 16 lanes cover four tokens from `token` on and sixteen features
+__device__ __forceinline__ int tile_tr_offset(int lane, int token) {
+  const int i = lane & 15, c = i & 3, fg = (lane >> 4) & 1;
+  return fg * 1024 + (((token + (i >> 2)) ^ (4 * fg)) * 32) + (c & 1) * 16 + (c >> 1) * 8;
+}
+
+// The W registers of a score tile that a lane's group can occupy, and probabilities back into an operand
+// (block_kernel.h, softmax_window, explains the windows).
+template <int W>
+__device__ __forceinline__ void pick_window(const f32x16& S, int widx, float (&x)[W]) {
+  const bool b0 = widx & 1, b1 = widx & 2;
+  float sv[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) { float t = S[r]; asm("" : "+v"(t)); sv[r] = t; }
+#pragma unroll
+  for (int c = 0; c < W; ++c) {
+    const float a0 = sv[c], a1 = sv[(16 / W > 2 ? 4 : 8) % 16 + c % 8];      // (values, not elements: no indexed register)
+    if (W == 16) x[c] = a0;
+    else if (W == 8) x[c] = b0 ? a1 : a0;
+    else {
+      const float a2 = sv[8 + c % 4], a3 = sv[12 + c % 4];
+      const float lo = b0 ? a1 : a0, up = b0 ? a3 : a2;
+      x[c] = b1 ? up : lo;
+    }
+  }
+}
+template <int W>
+__device__ __forceinline__ void place_window(const float (&x)[W], const uint32_t (&wmask)[16 / W], bf16x8 (&op)[2]) {
+  uint32_t pk[W / 2];
+#pragma unroll
+  for (int c = 0; c < W / 2; ++c) {
+    const longer::bf16x2 t2 = {(__bf16)x[2 * c], (__bf16)x[2 * c + 1]};
+    pk[c] = __builtin_bit_cast(uint32_t, t2);
+  }
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    u32x4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int ps = 4 * g + i;
+      v[i] = W == 16 ? pk[ps % (W / 2)] : pk[ps % (W / 2)] & wmask[ps / (W / 2)];
+    }
+    op[g] = __builtin_bit_cast(bf16x8, v);
+  }
+}
+
+// A matrix product's result may be read by a vector instruction 11 wait states after it at the earliest.  The
+// compiler keeps that distance along the longest way between the two, and the weight stream's advance() has a short
+// one (no new panel): with nothing in between, the first eight features of a tile were read too early.
+__device__ __forceinline__ void settle(f32x16& acc) { asm volatile("s_nop 10" : "+v"(acc)); }
+
+template <int NT>
+__device__ __forceinline__ void row_stats(const f32x16 (&x)[NT], float eps, float& mean, float& rstd) {
+  float s = 0.f, v = 0.f;
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s += x[t][r];
+  mean = sum_halves(s) * (1.f / (32 * NT));
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { const float q = x[t][r] - mean; v = fmaf(q, q, v); }
+  rstd = 1.f / sqrtf(sum_halves(v) * (1.f / (32 * NT)) + eps);
+}
+
+// dx = res + LayerNorm backward of dn at the rows x; result in x
+template <int NT>
+__device__ __forceinline__ void norm_backward(f32x16 (&x)[NT], f32x16 (&dn)[NT], const float* gain, float mean, float rstd, int hi) {
+  float c1 = 0.f, c2 = 0.f;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    dn[t] *= bias_tile(gain, t, hi);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      x[t][r] = (x[t][r] - mean) * rstd;
+      c1 += dn[t][r];
+      c2 = fmaf(dn[t][r], x[t][r], c2);
+    }
+  }
+  c1 = sum_halves(c1) * (1.f / (32 * NT));
+  c2 = sum_halves(c2) * (1.f / (32 * NT));
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x[t][r] = rstd * (dn[t][r] - c1 - x[t][r] * c2);
+}
+
+// W: registers of a score tile that one group can occupy (K <= 2 W)
+template <int D, int DH, int W>
+__global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const BlockBwParams p) {
+  constexpr int NT = D / 32, NG = D / 16, SEGV = NG * 64, HPT = 32 / DH, GPH = DH / 16;
+  constexpr int PSEG = D >= 128 ? kBlkPanel : 4, NB = 3;
+  using E = ET<__bf16>;
+  __shared__ uint4 ring[NB * PSEG * SEGV];
+  __shared__ uint4 turn[kBlkWaves][3][128];        // a wave's K, Q and dO (V on the way forward) pieces of 32 features
+  __shared__ f32x4 stat[kBlkWaves][2][8];          // its queries' log-sum-exp and sum of P dP
+  extern __shared__ f32x4 vec4[];
+  float* vec = (float*)vec4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 31, hi = lane >> 5;
+  const int NC = p.f / 32, FG = p.f / 16;
+
+  // ---- the lane's token
+  const int tile = blockIdx.x * kBlkWaves + wave;
+  const uint32_t slot = (uint32_t)tile * 32u + (uint32_t)j;
+  const uint32_t gidx = slot >> __builtin_ctz(p.K);
+  const int jj = (int)(slot & (uint32_t)(p.K - 1));
+  const int u = (int)(gidx / (uint32_t)p.T), tg = (int)(gidx - (uint32_t)u * (uint32_t)p.T);
+  const bool inside = u < p.B;
+  int len = 0;
+  if (inside) { len = p.lens ? p.lens[u] : p.L; len = min(max(len, 0), p.L); }
+  const int pos = tg * p.K + jj;
+  const bool valid = inside && pos < len;
+  const bool stored = inside && pos < p.L;         // the token has a row in the [B][L] tensors
+  const long long row = (long long)u * p.L + pos;
+  if (!__syncthreads_or(valid ? 1 : 0)) {
+    if (p.dx_rows && stored) {
+      const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *(f32x4*)(p.dx + row * D + 32 * t + 8 * q + 4 * hi) = z;
+    }
+    return;
+  }
+  const int widx = W == 16 ? 0 : j / (2 * W);
+  uint32_t wmask[16 / W];
+#pragma unroll
+  for (int w = 0; w < 16 / W; ++w) { wmask[w] = widx == w ? 0xffffffffu : 0u; asm("" : "+v"(wmask[w])); }
+  const uint32_t vb = (uint32_t)__ballot(valid);
+  const uint32_t gb = (p.K >= 32 ? 0xffffffffu : ((1u << p.K) - 1u)) << (p.K * (j / p.K));
+  const uint32_t seen = ((gb & vb) >> (4 * hi)) >> (2 * W * widx);     // window bits: the group's valid tokens
+
+  // ---- vectors to LDS, weight stream
+  const int oG1 = 0, oB1n = D, oBq = 2 * D, oBv = 3 * D, oBo = 4 * D, oG2 = 5 * D, oB2n = 6 * D, oBf = 7 * D;
+  for (int i = tid; i < D; i += 64 * kBlkWaves) {
+    vec[oG1 + i] = (float)p.ln1_g[i]; vec[oB1n + i] = (float)p.ln1_b[i];
+    vec[oBq + i] = (float)p.bq[i];    vec[oBv + i] = (float)p.bv[i];   vec[oBo + i] = (float)p.bo[i];
+    vec[oG2 + i] = (float)p.ln2_g[i]; vec[oB2n + i] = (float)p.ln2_b[i];
+  }
+  for (int i = tid; i < p.f; i += 64 * kBlkWaves) vec[oBf + i] = (float)p.b1[i];
+
+  f32x16 x[NT];
+  const long long xoff = (p.x_f32 ? (long long)slot : row) * D;
+  load_rows<__bf16, NT>(x, p.x, p.x_f32, xoff, valid, hi);
+  WStream<SEGV, PSEG, NB, false, 64 * kBlkWaves> ws;
+  ws.init(ring, p.wstream, bw_block_segs(D, p.f));
+  auto product = [&](f32x16& acc, const bf16x8 (&b)[NG]) {      // acc += (this segment's 32 output features) b
+#pragma unroll
+    for (int s = 0; s < NG; ++s) acc = E::mma(ws.template frag<bf16x8>(s), b[s], acc);
+    ws.advance();
+    settle(acc);
+  };
+  auto spread = [&](f32x16 (&acc)[NT], const bf16x8 (&b)[2]) {  // acc += (all output features of 32 contracted ones) b
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int g = 0; g < 2; ++g) acc[t] = E::mma(ws.template frag<bf16x8>(2 * t + g), b[g], acc[t]);
+    ws.advance();
+  };
+  // pieces of 32 features through LDS: in as the lanes hold them, out with lane = feature (tokens 16 g ..)
+  const int put = j * 32 + hi * 16, put1 = 1024 + (j ^ 4) * 32 + hi * 16, get = tile_tr_offset(lane, 4 * hi);
+  auto turn_in = [&](int which, const bf16x8 (&v)[2]) {
+    char* s = (char*)turn[wave][which];
+    *(bf16x8*)(s + put) = v[0];
+    *(bf16x8*)(s + put1) = v[1];
+  };
+  auto turn_out = [&](int which, int g) -> bf16x8 {
+    const char* s = (const char*)turn[wave][which] + get + 16 * g * 32;
+    return join_tr(__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)s),
+                   __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(s + 8 * 32)));
+  };
+
+  // ---- first LayerNorm
+  float mean1, rstd1;
+  row_stats<NT>(x, p.eps, mean1, rstd1);
+  bf16x8 nop[NG];
+  auto normalise = [&](float mean, float rstd, int og, int ob, __bf16* dump) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const f32x16 g = bias_tile(vec + og, t, hi), b = bias_tile(vec + ob, t, hi);
+      f32x16 h, y;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { h[r] = (x[t][r] - mean) * rstd; y[r] = fmaf(h[r], g[r], b[r]); }
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        tile_store(dump, tile, NG, 2 * t + q, lane, E::pack(h, q));
+        nop[2 * t + q] = E::pack(y, q);
+      }
+    }
+  };
+  normalise(mean1, rstd1, oG1, oB1n, p.xh1);
+
+  // ---- attention inside the groups.  Q carries log2(e) / sqrt(head width): scores come out ready for exp2.  The
+  // key bias adds a constant to a query's scores and is left out.
+  const float scale = 1.f / sqrtf((float)DH), qscale = scale * 1.44269504088896341f;
+  auto probabilities = [&](const f32x16& S, float (&x_)[W], float& m, float& l) {   // lane = query; unnormalised
+    pick_window<W>(S, widx, x_);
+    m = kNegBig;
+#pragma unroll
+    for (int c = 0; c < W; ++c) {
+      x_[c] = ((seen >> (8 * (c / 4) + (c % 4))) & 1u) ? x_[c] : -__builtin_inff();
+      m = fmaxf(m, x_[c]);
+    }
+    m = max_halves(m);
+    l = 0.f;
+#pragma unroll
+    for (int c = 0; c < W; ++c) { x_[c] = __builtin_amdgcn_exp2f(x_[c] - m); l += x_[c]; }
+    l = sum_halves(l);
+  };
+  {
+    bf16x8 oop[NG];
+#pragma unroll
+    for (int ft = 0; ft < NT; ++ft) {
+      bf16x8 qop[2], kop[2];
+      {
+        f32x16 q = bias_tile(vec + oBq, ft, hi);
+        product(q, nop);
+        q *= qscale;
+#pragma unroll
+        for (int g = 0; g < 2; ++g) { qop[g] = E::pack(q, g); tile_store(p.qkv, tile, 3 * NG, 2 * ft + g, lane, qop[g]); }
+      }
+      {
+        f32x16 k = splat16(0.f);
+        product(k, nop);
+#pragma unroll
+        for (int g = 0; g < 2; ++g) { kop[g] = E::pack(k, g); tile_store(p.qkv, tile, 3 * NG, NG + 2 * ft + g, lane, kop[g]); }
+      }
+      {
+        f32x16 v = bias_tile(vec + oBv, ft, hi);
+        product(v, nop);
+        bf16x8 vop[2];
+#pragma unroll
+        for (int g = 0; g < 2; ++g) { vop[g] = E::pack(v, g); tile_store(p.qkv, tile, 3 * NG, 2 * NG + 2 * ft + g, lane, vop[g]); }
+        turn_in(2, vop);
+      }
+      __builtin_amdgcn_wave_barrier();
+      f32x16 o;
+#pragma unroll
+      for (int hh = 0; hh < HPT; ++hh) {
+        f32x16 S = splat16(0.f);
+#pragma unroll
+        for (int g = 0; g < GPH; ++g) S = E::mma(kop[hh * GPH + g], qop[hh * GPH + g], S);
+        float pr[W], m, l;
+        probabilities(S, pr, m, l);
+        const float inv = l > 0.f ? 1.f / l : 0.f;
+        bf16x8 pop[2];
+        place_window<W>(pr, wmask, pop);
+        f32x16 acc = splat16(0.f);
+#pragma unroll
+        for (int g = 0; g < 2; ++g) acc = E::mma(turn_out(2, g), pop[g], acc);
+#pragma unroll
+        for (int r = 0; r < 16 / HPT; ++r) o[16 / HPT * hh + r] = acc[16 / HPT * hh + r] * inv;
+      }
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int g = 0; g < 2; ++g) { oop[2 * ft + g] = E::pack(o, g); tile_store(p.o, tile, NG, 2 * ft + g, lane, oop[2 * ft + g]); }
+    }
+    // output projection + residual, second LayerNorm
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      x[t] += bias_tile(vec + oBo, t, hi);
+      product(x[t], oop);
+    }
+  }
+  float mean2, rstd2;
+  row_stats<NT>(x, p.eps, mean2, rstd2);
+  normalise(mean2, rstd2, oG2, oB2n, p.xh2);
+
+  // ---- gradient of the block's output
+  float share = 0.f;
+  const float* up = nullptr;
+  if (p.dM && valid) {
+    up = p.dM + ((size_t)u * p.T + tg) * (size_t)(p.concat ? p.K * D : D) + (p.concat ? jj * D : 0);
+    share = p.concat ? 1.f : 1.f / (float)min(p.K, len - tg * p.K);
+  }
+  auto upstream = [&](int t) -> f32x16 {
+    f32x16 v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      f32x4 w = {0.f, 0.f, 0.f, 0.f};
+      if (!p.dM) w = *(const f32x4*)(p.dy + ((size_t)tile * (D / 8) + 4 * t + q) * 256 + 4 * lane);
+      else if (up) w = *(const f32x4*)(up + 32 * t + 8 * q + 4 * hi) * share;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[4 * q + e] = w[e];
+    }
+    return v;
+  };
+  f32x16 dn[NT];
+  {
+    bf16x8 dyop[NG];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const f32x16 v = upstream(t);
+#pragma unroll
+      for (int g = 0; g < 2; ++g) { dyop[2 * t + g] = E::pack(v, g); tile_store(p.dyb, tile, NG, 2 * t + g, lane, dyop[2 * t + g]); }
+      dn[t] = splat16(0.f);
+    }
+    // FFN, 32 hidden features at a time: values and gradient formed, used and written out
+    for (int c = 0; c < NC; ++c) {
+      f32x16 v = bias_tile(vec + oBf, c, hi), g = splat16(0.f);
+      product(v, nop);
+      product(g, dyop);
+      if (p.act == LONGER_ACT_RELU) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { float a_, d_; act_both(v[r], LONGER_ACT_RELU, &a_, &d_, g[r]); v[r] = a_; g[r] = d_; }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { float a_, d_; act_both(v[r], LONGER_ACT_GELU_ERF, &a_, &d_, g[r]); v[r] = a_; g[r] = d_; }
+      }
+      bf16x8 hop[2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        hop[q] = E::pack(g, q);
+        tile_store(p.dh, tile, FG, 2 * c + q, lane, hop[q]);
+        tile_store(p.a, tile, FG, 2 * c + q, lane, E::pack(v, q));
+      }
+      spread(dn, hop);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < NT; ++t) settle(dn[t]);
+  norm_backward<NT>(x, dn, vec + oG2, mean2, rstd2, hi);
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    x[t] += upstream(t);                           // gradient of the rows between attention and FFN
+#pragma unroll
+    for (int g = 0; g < 2; ++g) { nop[2 * t + g] = E::pack(x[t], g); tile_store(p.dxmb, tile, NG, 2 * t + g, lane, nop[2 * t + g]); }
+    dn[t] = splat16(0.f);
+  }
+
+  // ---- back through the attention, 32 features (one or two heads) at a time
+  const uint32_t keyseen = valid ? seen : 0u;
+#pragma unroll
+  for (int ft = 0; ft < NT; ++ft) {
+    bf16x8 qop[2], kop[2], vop[2], dop[2];
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      qop[g] = tile_load(p.qkv, tile, 3 * NG, 2 * ft + g, lane);
+      kop[g] = tile_load(p.qkv, tile, 3 * NG, NG + 2 * ft + g, lane);
+      vop[g] = tile_load(p.qkv, tile, 3 * NG, 2 * NG + 2 * ft + g, lane);
+    }
+    {
+      f32x16 d = splat16(0.f);
+      product(d, nop);
+#pragma unroll
+      for (int g = 0; g < 2; ++g) dop[g] = E::pack(d, g);
+    }
+    turn_in(0, kop);
+    turn_in(1, qop);
+    turn_in(2, dop);
+    __builtin_amdgcn_wave_barrier();
+    f32x16 dq, dk, dv;
+#pragma unroll
+    for (int hh = 0; hh < HPT; ++hh) {
+      constexpr int RH = 16 / HPT;
+      {   // lane = query: probabilities, dP, D = sum P dP, dS = P (dP - D); dq^T = K^T dS^T
+        f32x16 S = splat16(0.f), dP = splat16(0.f);
+#pragma unroll
+        for (int g = 0; g < GPH; ++g) {
+          S = E::mma(kop[hh * GPH + g], qop[hh * GPH + g], S);
+          dP = E::mma(vop[hh * GPH + g], dop[hh * GPH + g], dP);
+        }
+        float pr[W], dp[W], m, l;
+        probabilities(S, pr, m, l);
+        pick_window<W>(dP, widx, dp);
+        const float inv = l > 0.f ? 1.f / l : 0.f;
+        float dsum = 0.f;
+#pragma unroll
+        for (int c = 0; c < W; ++c) { pr[c] *= inv; dsum = fmaf(pr[c], dp[c], dsum); }
+        dsum = sum_halves(dsum);
+        if (hi == 0) {
+          ((float*)stat[wave][0])[j] = m + __builtin_amdgcn_logf(l);
+          ((float*)stat[wave][1])[j] = dsum;
+        }
+#pragma unroll
+        for (int c = 0; c < W; ++c) pr[c] *= dp[c] - dsum;
+        bf16x8 sop[2];
+        place_window<W>(pr, wmask, sop);
+        f32x16 acc = splat16(0.f);
+#pragma unroll
+        for (int g = 0; g < 2; ++g) acc = E::mma(turn_out(0, g), sop[g], acc);
+#pragma unroll
+        for (int r = 0; r < RH; ++r) dq[RH * hh + r] = acc[RH * hh + r] * scale;
+      }
+      __builtin_amdgcn_wave_barrier();
+      {   // lane = key: the same with queries in the registers; dv^T = dO^T P, dk^T = Q^T dS
+        f32x16 S = splat16(0.f), dP = splat16(0.f);
+#pragma unroll
+        for (int g = 0; g < GPH; ++g) {
+          S = E::mma(qop[hh * GPH + g], kop[hh * GPH + g], S);
+          dP = E::mma(dop[hh * GPH + g], vop[hh * GPH + g], dP);
+        }
+        float pr[W], dp[W];
+        pick_window<W>(S, widx, pr);
+        pick_window<W>(dP, widx, dp);
+#pragma unroll
+        for (int q = 0; q < W / 4; ++q) {
+          const f32x4 lse = stat[wave][0][(W / 2) * widx + 2 * q + hi], ds = stat[wave][1][(W / 2) * widx + 2 * q + hi];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int c = 4 * q + e;
+            const float s = ((keyseen >> (8 * q + e)) & 1u) ? pr[c] - lse[e] : -__builtin_inff();
+            pr[c] = __builtin_amdgcn_exp2f(s);
+            dp[c] = pr[c] * (dp[c] - ds[e]);
+          }
+        }
+        bf16x8 pop[2], sop[2];
+        place_window<W>(pr, wmask, pop);
+        place_window<W>(dp, wmask, sop);
+        f32x16 accv = splat16(0.f), acck = splat16(0.f);
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+          accv = E::mma(turn_out(2, g), pop[g], accv);
+          acck = E::mma(turn_out(1, g), sop[g], acck);
+        }
+#pragma unroll
+        for (int r = 0; r < RH; ++r) {
+          dv[RH * hh + r] = accv[RH * hh + r];
+          dk[RH * hh + r] = acck[RH * hh + r] * 0.69314718055994531f;       // (Q carries scale log2 e)
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+      bf16x8 op[2];
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        op[g] = E::pack(m == 0 ? dq : m == 1 ? dk : dv, g);
+        tile_store(p.dqkv, tile, 3 * NG, m * NG + 2 * ft + g, lane, op[g]);
+      }
+      spread(dn, op);
+    }
+  }
+
+  // ---- first LayerNorm's backward: x holds the gradient that reaches the input through the residual connection
+  f32x16 xin[NT];
+  load_rows<__bf16, NT>(xin, p.x, p.x_f32, xoff, valid, hi);
+#pragma unroll
+  for (int t = 0; t < NT; ++t) settle(dn[t]);
+  norm_backward<NT>(xin, dn, vec + oG1, mean1, rstd1, hi);
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    x[t] += xin[t];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      f32x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = valid ? x[t][4 * q + e] : 0.f;
+      if (!p.dx_rows) *(f32x4*)(p.dx + ((size_t)tile * (D / 8) + 4 * t + q) * 256 + 4 * lane) = v;
+      else if (stored) *(f32x4*)(p.dx + row * D + 32 * t + 8 * q + 4 * hi) = v;
+    }
+  }
+}
+
+template <int D>
+inline void bw_block_launch_d(int dh, const BlockBwParams& p, hipStream_t st) {
+  const size_t tiles = ((size_t)p.B * p.T * p.K + 31) / 32;
+  const unsigned grid = (unsigned)((tiles + kBlkWaves - 1) / kBlkWaves);
+  const size_t lds = (size_t)bw_block_vec_floats(D, p.f) * 4;
+#define LONGER_BW_BLOCK(DH, W) bw_block_kernel<D, DH, W><<<grid, 64 * kBlkWaves, lds, st>>>(p)
+  if (dh == 16) { if (p.K <= 8) LONGER_BW_BLOCK(16, 4); else if (p.K == 16) LONGER_BW_BLOCK(16, 8); else LONGER_BW_BLOCK(16, 16); }
+  else { if (p.K <= 8) LONGER_BW_BLOCK(32, 4); else if (p.K == 16) LONGER_BW_BLOCK(32, 8); else LONGER_BW_BLOCK(32, 16); }
+#undef LONGER_BW_BLOCK
+}
+
+}  // namespace bw
+}  // namespace longer

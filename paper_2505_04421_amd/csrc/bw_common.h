@@ -28,6 +28,30 @@ __device__ __forceinline__ bool rows_any_valid(const RowsValid& v, int r0, int r
   return false;
 }
 
+// The activation and its derivative at once, for the launch that rounds both to bf16 right away.
+// GELU: Phi(v) - 1/2 as v times an even polynomial of degree 8 (minimax fit on [-3.5, 3.5] that reaches 1/2
+// at the interval's end, clamped to [0, 1] beyond it; absolute error below 1.3e-3, under the bf16
+// rounding step of the values it produces) and the density from one exponential.
+__device__ __forceinline__ void act_both(float v, int act, float* a, float* da) {
+  if (act == LONGER_ACT_RELU) { *a = v > 0.f ? v : 0.f; *da = v > 0.f ? 1.f : 0.f; return; }
+  const float u = v * v;
+  float pl = 9.366767568843253e-06f;
+  pl = fmaf(pl, u, -0.0003847714538096606f);
+  pl = fmaf(pl, u, 0.0064495445928312006f);
+  pl = fmaf(pl, u, -0.05893596715178192f);
+  pl = fmaf(pl, u, 0.3934098519357524f);
+  const float c = __builtin_amdgcn_fmed3f(fmaf(v, pl, 0.5f), 0.f, 1.f);
+  const float e = __expf(-0.5f * u);
+  *a = v * c;
+  *da = fmaf(v * e, 0.39894228040143268f, c);
+}
+// the activation, and a gradient g times its derivative
+__device__ __forceinline__ void act_both(float v, int act, float* a, float* dg, float g) {
+  float da;
+  act_both(v, act, a, &da);
+  *dg = g * da;
+}
+
 // Matrix-core operand fragment of a row-major LDS tile whose rows are the contraction index: lane (x = l % 32,
 // hi = l / 32) gets rows 8 hi .. 8 hi + 7 of column x.  The transposing read works on groups of 16 lanes: lane i
 // of a group points at four consecutive columns (4 (i % 4) ..) of row i / 4 and receives column i of the

@@ -7,7 +7,7 @@
 // as many reductions before (512 us of a 1091 us step of the small model: B = 128, L = 512, d = 64), each too
 // small for the chip; see the figures at bw_wgrad_kernel.
 #pragma once
-#include "bw_common.h"
+#include "bw_block.h"
 
 namespace longer {
 namespace bw {
@@ -36,7 +36,9 @@ struct WgradArgs { WgradJob job[kMaxWgradJobs]; int njobs, tiles, nslices; };
 // Memory bound at scale: at the headline batch one block's gradients read 4.1 KB per token, 2.1 GB.  Slices take
 // every nslices-th step, so that each samples long and short users alike; the tiles of a slice, which share
 // their operands' rows, run on one accelerator die (one L2).
-template <int TB>
+// TILES: the operands are tile blocks (bw_block.h: rows are slots, ldx / ldy count sixteens of features).  A step's
+// tile is then contiguous in memory and goes to LDS as it is.
+template <int TB, bool TILES>
 __global__ __launch_bounds__(256, 3) void bw_wgrad_kernel(const WgradArgs a) {
   constexpr int PITCH = TB + 16, TT = TB / 64, NCH = TB / 64;     // NCH: 16-byte chunks per thread, operand and step
   constexpr int CPR = TB / 8;                                     // chunks per row
@@ -88,7 +90,12 @@ __global__ __launch_bounds__(256, 3) void bw_wgrad_kernel(const WgradArgs a) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) z[e] = (__bf16)0.f;
       rx[i] = z; ry[i] = z;
-      if (row < jb.rows && row_valid(jb.rv, row)) {
+      if constexpr (TILES) {
+        const size_t tile = (size_t)(k0 >> 5);
+        const int gx = m0 / 16 + (c >> 6), gy = n0 / 16 + (c >> 6);
+        if (gx < jb.m / 16) rx[i] = *(const bf16x8*)(X + (tile * jb.ldx + gx) * 512 + 8 * (c & 63));
+        if (gy < jb.n / 16) ry[i] = *(const bf16x8*)(Y + (tile * jb.ldy + gy) * 512 + 8 * (c & 63));
+      } else if (row < jb.rows && row_valid(jb.rv, row)) {
         if (m0 + col < jb.m) rx[i] = *(const bf16x8*)(X + (size_t)row * jb.ldx + m0 + col);
         if (n0 + col < jb.n) ry[i] = *(const bf16x8*)(Y + (size_t)row * jb.ldy + n0 + col);
       }
@@ -102,7 +109,17 @@ __global__ __launch_bounds__(256, 3) void bw_wgrad_kernel(const WgradArgs a) {
     }
     return kt;
   };
-  const int foff = frag_t_offset<PITCH>(lane);
+  const int foff = TILES ? tile_tr_offset(lane, 8 * hi) : frag_t_offset<PITCH>(lane);
+  // 32 columns from x on, contraction rows 16 ks ..: eight rows per lane half
+  auto frag = [&](const __bf16* s, int x, int ks) -> bf16x8 {
+    if constexpr (TILES) {
+      const char* q = (const char*)s + x * 64 + 512 * ks;
+      return join_tr(__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(q + foff)),
+                     __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(q + (foff ^ 128))));
+    } else {
+      return frag_t<PITCH>(s + foff + 16 * ks * PITCH + x);
+    }
+  };
   int buf = 0, kt = next_step(0);
   if (kt < nk) gload(kt);
   while (kt < nk) {
@@ -110,7 +127,7 @@ __global__ __launch_bounds__(256, 3) void bw_wgrad_kernel(const WgradArgs a) {
     __bf16* sy = sx + 32 * PITCH;
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
-      const int c = tid + 256 * i, o = (c / CPR) * PITCH + 8 * (c % CPR);
+      const int c = tid + 256 * i, o = TILES ? 8 * c : (c / CPR) * PITCH + 8 * (c % CPR);
       *(bf16x8*)&sx[o] = rx[i];
       *(bf16x8*)&sy[o] = ry[i];
     }
@@ -122,8 +139,8 @@ __global__ __launch_bounds__(256, 3) void bw_wgrad_kernel(const WgradArgs a) {
       bf16x8 fx[TT], fy[TT];
 #pragma unroll
       for (int i = 0; i < TT; ++i) {
-        fx[i] = frag_t<PITCH>(sx + foff + 16 * ks * PITCH + (TB / 2) * wm + 32 * i);
-        fy[i] = frag_t<PITCH>(sy + foff + 16 * ks * PITCH + (TB / 2) * wn + 32 * i);
+        fx[i] = frag(sx, (TB / 2) * wm + 32 * i, ks);
+        fy[i] = frag(sy, (TB / 2) * wn + 32 * i, ks);
       }
 #pragma unroll
       for (int i = 0; i < TT; ++i)
@@ -217,9 +234,10 @@ static inline int wgrad_tile(int d) { return d >= 128 ? 128 : 64; }
 // to learn how many floats of partial results the launch needs, and with one to launch it.
 struct WgradBatch {
   WgradArgs a = {};
+  bool tiled;                               // the operands are tile blocks
   int tb; size_t rows;                      // rows: of the jobs with nsub = 1 (sets the number of slices)
   struct Out { float* out; long long olstride; int nb; } outs[kMaxWgradJobs];
-  WgradBatch(int d, size_t rows_) : tb(wgrad_tile(d)), rows(rows_) {}
+  WgradBatch(int d, size_t rows_, bool tiled_ = false) : tiled(tiled_), tb(wgrad_tile(d)), rows(rows_) {}
   void add(const __bf16* X, int ldx, int m, const __bf16* Y, int ldy, int n, int nb, size_t nrows, RowsValid rv, float* out,
            int layers = 1, long long xstride = 0, long long ystride = 0, long long olstride = 0) {
     WgradJob& j = a.job[a.njobs];

@@ -32,3 +32,26 @@ def test_parameter_gradients_many_more_key_rows_than_query_rows(n_self):
     3e-3 / 4 / 3 = 2.5e-4, a fifth of what is left.)"""
     cfg = synth.CONFIGS["C2"].replace(B=3, L=1000, K=4, m=2, k_recent=10, n_self=n_self, ragged=True, len_lo=300, len_hi=1000, index=62)
     _compare_model("T = 250, k = 10, n_self = %d" % n_self, synth.make_case(cfg))
+
+
+# Token merge alone, two blocks, at every register window of the block kernel (K <= 8, 16, 32) and both head widths:
+# lengths that are no multiple of K, tiles that hold several users or end inside one, users without a token, the
+# last workgroup's empty tiles; both merges; the widest hidden layer (2048)
+@pytest.mark.parametrize("d,dh,K,B,L,merge,ffn", [(32, 16, 4, 7, 9, "mean", 4), (32, 16, 32, 5, 70, "mean", 4), (64, 32, 16, 9, 50, "mean", 4),
+                                                  (64, 16, 8, 33, 1, "mean", 4), (128, 16, 16, 6, 45, "mean", 4), (128, 32, 32, 3, 130, "mean", 4),
+                                                  (128, 16, 1, 2, 77, "mean", 4), (64, 32, 2, 3, 65, "concat", 4), (32, 16, 8, 4, 131, "concat", 7)])
+def test_block_kernel_windows_and_tile_remainders(d, dh, K, B, L, merge, ffn):
+    w = d * K if merge == "concat" else d
+    cfg = synth.CONFIGS["C2"].replace(d=w, heads=w // 16, inner_heads=d // dh, inner_layers=2, K=K, B=B, L=L, ragged=True, len_lo=0,
+                                      len_hi=L, merge=merge, ffn_mult=ffn, m=2, k_recent=4, n_self=1, index=63)
+    case = synth.make_case(cfg)
+    case["lens"][0] = L
+    if B > 1:
+        case["lens"][1] = 0
+    _compare("width %d, head width %d, K = %d, %d x %d, %s" % (d, dh, K, B, L, merge), case, synth.draw_merge_gradient(cfg))
+
+
+def test_block_kernel_widest_hidden_layer():
+    """One block with 2048 hidden features: its vectors and the weight ring no longer let two workgroups share a compute unit."""
+    cfg = synth.CONFIGS["C2"].replace(d=128, heads=8, inner_heads=8, inner_layers=1, K=8, B=2, L=70, ffn_mult=16, index=64)
+    _compare("2048 hidden features", synth.make_case(cfg), synth.draw_merge_gradient(cfg))
