@@ -1339,7 +1339,7 @@ struct Workspace {
   size_t dy, dyb, dh, dn, dxm, dxmb, dob, dqkv, stat;
   size_t part, lnpart;                     // partial parameter gradients of one block: matrices, LayerNorms (ln1, ln2)
   size_t fwd, fwd_bytes, ztmp;             // the fused forward kernel's scratch and output when it recomputes block inputs
-  size_t stream;                           // block kernel: packed weights per layer (n1, n2 hold the normalised rows, qkv also dqkv)
+  size_t stream, rec;                      // block kernel: packed weights per layer, tile records
   size_t total;
 };
 // The gradients of an InnerTrans block's four products (Q / K / V side by side), all over the raw token rows
@@ -1353,15 +1353,16 @@ static WgradBatch block_wgrads(int d, int f, size_t ntok, RowsValid rv, const __
   w.add(n1, d, d, dqkv, 3 * d, 3 * d, d, ntok, rv, g + gl.wq);
   return w;
 }
-// the same on the block kernel's tile blocks
-static WgradBatch block_wgrads_tiles(int d, int f, size_t slots, RowsValid rv, const __bf16* xh1, const __bf16* dqkv, const __bf16* o,
-                                     const __bf16* dxmb, const __bf16* xh2, const __bf16* dh, const __bf16* a, const __bf16* dyb, float* g) {
+// the same from the block kernel's tile records
+static WgradBatch block_wgrads_tiles(int d, int f, size_t slots, RowsValid rv, const __bf16* rec, float* g) {
   const GradLayout gl = grad_layout(d, f);
+  const BlockRecord r(d, f);
+  auto at = [&](int o) { return rec + (size_t)o * 512; };
   WgradBatch w(d, slots, true);
-  w.add(a, f / 16, f, dyb, d / 16, d, d, slots, rv, g + gl.w2);
-  w.add(xh2, d / 16, d, dh, f / 16, f, f, slots, rv, g + gl.w1);
-  w.add(o, d / 16, d, dxmb, d / 16, d, d, slots, rv, g + gl.wo);
-  w.add(xh1, d / 16, d, dqkv, 3 * d / 16, 3 * d, d, slots, rv, g + gl.wq);
+  w.add(at(r.a), r.size, f, at(r.dyb), r.size, d, d, slots, rv, g + gl.w2);
+  w.add(at(r.xh2), r.size, d, at(r.dh), r.size, f, f, slots, rv, g + gl.w1);
+  w.add(at(r.o), r.size, d, at(r.dxmb), r.size, d, d, slots, rv, g + gl.wo);
+  w.add(at(r.xh1), r.size, d, at(r.qkv), r.size, 3 * d, d, slots, rv, g + gl.wq);
   return w;
 }
 static int launch(WgradBatch& w, float* part, hipStream_t st) {
@@ -1424,16 +1425,9 @@ static Workspace tiled_workspace(const Dims& s, size_t fwd_bytes) {
   const size_t n = s.padded, d = s.d, f = s.f;
   w.stream = take((size_t)s.layers * bw_block_segs_padded(s.d, s.f) * packed_seg_bytes(s.d, 2));
   w.xin = take((size_t)(s.layers - 1) * n * d * 4);
-  w.n1 = take(n * d * 2);
-  w.qkv = take(n * 3 * d * 2);
-  w.o = take(n * d * 2);
-  w.n2 = take(n * d * 2);
-  w.a = take(n * f * 2);
-  w.dh = take(n * f * 2);
-  w.dyb = take(n * d * 2);
-  w.dxmb = take(n * d * 2);
+  w.rec = take(n / 32 * BlockRecord(s.d, s.f).size * 1024);
   w.dy = take(n * d * 4);
-  w.part = take(block_wgrads_tiles(s.d, s.f, s.slots, RowsValid{}, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr).place(nullptr) * 4);
+  w.part = take(block_wgrads_tiles(s.d, s.f, s.slots, RowsValid{}, nullptr, nullptr).place(nullptr) * 4);
   w.fwd = take(fwd_bytes);
   w.fwd_bytes = fwd_bytes;
   w.total = o;
@@ -1626,14 +1620,13 @@ static int run_tiled(const longer_config* c, const longer_block* inner, const vo
     p.x = l ? (const void*)xin(l) : H; p.x_f32 = l != 0;
     p.dM = l == s.layers - 1 ? dM : nullptr; p.concat = c->merge == LONGER_MERGE_CONCAT;
     p.dy = (const float*)(ws + w.dy);
-    p.qkv = at(w.qkv); p.xh1 = at(w.n1); p.o = at(w.o); p.xh2 = at(w.n2); p.a = at(w.a); p.dh = at(w.dh); p.dyb = at(w.dyb);
-    p.dxmb = at(w.dxmb); p.dqkv = at(w.qkv);
+    p.rec = at(w.rec);
     p.dx = l ? (float*)(ws + w.dy) : dH; p.dx_rows = l == 0;      // (dy in place: a tile's values are read before they are replaced)
     if (d == 32) bw_block_launch_32(s.dh, p, st);
     else if (d == 64) bw_block_launch_64(s.dh, p, st);
     else bw_block_launch_128(s.dh, p, st);
     BW_TRY(launched("block backward"));
-    WgradBatch wg = block_wgrads_tiles(d, f, s.slots, rv, p.xh1, p.dqkv, p.o, p.dxmb, p.xh2, p.dh, p.a, p.dyb, g);
+    WgradBatch wg = block_wgrads_tiles(d, f, s.slots, rv, p.rec, g);
     BW_TRY(launch(wg, (float*)(ws + w.part), st));
     ReduceBatch rb;
     rb.add(wg);

@@ -11,7 +11,7 @@
 // the FFN's middle, three products back, attention back, two LayerNorms back) a block of the headline batch
 // (512 000 rows of width 128) moved 18.8 KB per token beside its parameter gradients; here it is 7.4 KB.
 //
-// Tile blocks.  A tensor of F features that the parameter gradients read is stored as [tile][F / 16][1 KiB]: 16
+// Tile blocks.  A tensor of F features that the parameter gradients read is stored as [F / 16][1 KiB] per tile: 16
 // features of 32 tokens, 32 bytes per token, as the lanes hold them (lane half hi: features 4 hi .. + 3 and
 // 8 + 4 hi .. + 3 of the sixteen), so a store or load of a wave is 1 KiB without gaps and the transposing LDS
 // read finds four consecutive features in every 8 bytes.  In odd sixteens the tokens' 128-byte quarters are
@@ -33,8 +33,16 @@ struct BlockBwParams {
   const void* x; int x_f32;                 // the block's input rows: raw tokens [B][L][D] bf16, or [B][T K][D] fp32
   const float* dM; int concat;              // gradient of the block's output: from the merged tokens' gradient,
   const float* dy;                          // or (dM NULL) the fp32 tile blocks the block after this one wrote
-  __bf16 *qkv, *xh1, *o, *xh2, *a, *dh, *dyb, *dxmb, *dqkv;    // tile blocks (xh: normalised rows before gain and shift)
+  __bf16* rec;                              // tile records (BlockRecord)
   float* dx; int dx_rows;                   // gradient of the input: fp32 tile blocks, or [B][L][D] (zeros for padded tokens)
+};
+
+// A tile's record: all of its tile blocks side by side (xh: normalised rows before gain and shift; the gradients of q, k,
+// v take the place of q, k, v).  Offsets and size in sixteens of features (1 KiB).
+struct BlockRecord {
+  int qkv, xh1, o, xh2, dyb, dxmb, a, dh, size;
+  __host__ __device__ BlockRecord(int d, int f)
+      : qkv(0), xh1(3 * d / 16), o(4 * d / 16), xh2(5 * d / 16), dyb(6 * d / 16), dxmb(7 * d / 16), a(8 * d / 16), dh(a + f / 16), size(dh + f / 16) {}
 };
 
 constexpr int kBlkWaves = 4;
@@ -49,16 +57,8 @@ void bw_block_launch_32(int dh, const BlockBwParams& p, hipStream_t st);
 void bw_block_launch_64(int dh, const BlockBwParams& p, hipStream_t st);
 void bw_block_launch_128(int dh, const BlockBwParams& p, hipStream_t st);
 
-__device__ __forceinline__ size_t tile_block_offset(int tile, int groups, int g, int lane) {     // in bytes
-  const int j = lane & 31, hi = lane >> 5;
-  return ((size_t)tile * groups + g) * 1024 + ((j ^ (4 * (g & 1))) * 32 + hi * 16);
-}
-__device__ __forceinline__ void tile_store(__bf16* base, int tile, int groups, int g, int lane, bf16x8 v) {
-  *(bf16x8*)((char*)base + tile_block_offset(tile, groups, g, lane)) = v;
-}
-__device__ __forceinline__ bf16x8 tile_load(const __bf16* base, int tile, int groups, int g, int lane) {
-  return *(const bf16x8*)((const char*)base + tile_block_offset(tile, groups, g, lane));
-}
+// the lane's 16 bytes of a sixteen whose index has parity `odd`
+__device__ __forceinline__ int tile_lane_offset(int lane, int odd) { return ((lane & 31) ^ (4 * odd)) * 32 + (lane >> 5) * 16; }
 
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 __device__ __forceinline__ bf16x8 join_tr(s16x4 lo, s16x4 up) {
@@ -167,10 +167,15 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   extern __shared__ f32x4 vec4[];
   float* vec = (float*)vec4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 31, hi = lane >> 5;
-  const int NC = p.f / 32, FG = p.f / 16;
+  const int NC = p.f / 32;
+  const BlockRecord rc(D, p.f);
 
   // ---- the lane's token
   const int tile = blockIdx.x * kBlkWaves + wave;
+  char* rec = (char*)p.rec + (size_t)tile * rc.size * 1024 + tile_lane_offset(lane, 0);
+  const int odd = tile_lane_offset(lane, 1) - tile_lane_offset(lane, 0);
+  auto put_rec = [&](int base, int g, bf16x8 v) { *(bf16x8*)(rec + (base + g) * 1024 + (g & 1 ? odd : 0)) = v; };   // (base is even)
+  auto get_rec = [&](int base, int g) -> bf16x8 { return *(const bf16x8*)(rec + (base + g) * 1024 + (g & 1 ? odd : 0)); };
   const uint32_t slot = (uint32_t)tile * 32u + (uint32_t)j;
   const uint32_t gidx = slot >> __builtin_ctz(p.K);
   const int jj = (int)(slot & (uint32_t)(p.K - 1));
@@ -244,7 +249,7 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   float mean1, rstd1;
   row_stats<NT>(x, p.eps, mean1, rstd1);
   bf16x8 nop[NG];
-  auto normalise = [&](float mean, float rstd, int og, int ob, __bf16* dump) {
+  auto normalise = [&](float mean, float rstd, int og, int ob, int dump) {
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const f32x16 g = bias_tile(vec + og, t, hi), b = bias_tile(vec + ob, t, hi);
@@ -253,12 +258,12 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
       for (int r = 0; r < 16; ++r) { h[r] = (x[t][r] - mean) * rstd; y[r] = fmaf(h[r], g[r], b[r]); }
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
-        tile_store(dump, tile, NG, 2 * t + q, lane, E::pack(h, q));
+        put_rec(dump, 2 * t + q, E::pack(h, q));
         nop[2 * t + q] = E::pack(y, q);
       }
     }
   };
-  normalise(mean1, rstd1, oG1, oB1n, p.xh1);
+  normalise(mean1, rstd1, oG1, oB1n, rc.xh1);
 
   // ---- attention inside the groups.  Q carries log2(e) / sqrt(head width): scores come out ready for exp2.  The
   // key bias adds a constant to a query's scores and is left out.
@@ -287,20 +292,20 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
         product(q, nop);
         q *= qscale;
 #pragma unroll
-        for (int g = 0; g < 2; ++g) { qop[g] = E::pack(q, g); tile_store(p.qkv, tile, 3 * NG, 2 * ft + g, lane, qop[g]); }
+        for (int g = 0; g < 2; ++g) { qop[g] = E::pack(q, g); put_rec(rc.qkv, 2 * ft + g, qop[g]); }
       }
       {
         f32x16 k = splat16(0.f);
         product(k, nop);
 #pragma unroll
-        for (int g = 0; g < 2; ++g) { kop[g] = E::pack(k, g); tile_store(p.qkv, tile, 3 * NG, NG + 2 * ft + g, lane, kop[g]); }
+        for (int g = 0; g < 2; ++g) { kop[g] = E::pack(k, g); put_rec(rc.qkv, NG + 2 * ft + g, kop[g]); }
       }
       {
         f32x16 v = bias_tile(vec + oBv, ft, hi);
         product(v, nop);
         bf16x8 vop[2];
 #pragma unroll
-        for (int g = 0; g < 2; ++g) { vop[g] = E::pack(v, g); tile_store(p.qkv, tile, 3 * NG, 2 * NG + 2 * ft + g, lane, vop[g]); }
+        for (int g = 0; g < 2; ++g) { vop[g] = E::pack(v, g); put_rec(rc.qkv, 2 * NG + 2 * ft + g, vop[g]); }
         turn_in(2, vop);
       }
       __builtin_amdgcn_wave_barrier();
@@ -323,7 +328,7 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
       }
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int g = 0; g < 2; ++g) { oop[2 * ft + g] = E::pack(o, g); tile_store(p.o, tile, NG, 2 * ft + g, lane, oop[2 * ft + g]); }
+      for (int g = 0; g < 2; ++g) { oop[2 * ft + g] = E::pack(o, g); put_rec(rc.o, 2 * ft + g, oop[2 * ft + g]); }
     }
     // output projection + residual, second LayerNorm
 #pragma unroll
@@ -334,7 +339,7 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   }
   float mean2, rstd2;
   row_stats<NT>(x, p.eps, mean2, rstd2);
-  normalise(mean2, rstd2, oG2, oB2n, p.xh2);
+  normalise(mean2, rstd2, oG2, oB2n, rc.xh2);
 
   // ---- gradient of the block's output
   float share = 0.f;
@@ -362,7 +367,7 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
     for (int t = 0; t < NT; ++t) {
       const f32x16 v = upstream(t);
 #pragma unroll
-      for (int g = 0; g < 2; ++g) { dyop[2 * t + g] = E::pack(v, g); tile_store(p.dyb, tile, NG, 2 * t + g, lane, dyop[2 * t + g]); }
+      for (int g = 0; g < 2; ++g) { dyop[2 * t + g] = E::pack(v, g); put_rec(rc.dyb, 2 * t + g, dyop[2 * t + g]); }
       dn[t] = splat16(0.f);
     }
     // FFN, 32 hidden features at a time: values and gradient formed, used and written out
@@ -381,8 +386,8 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         hop[q] = E::pack(g, q);
-        tile_store(p.dh, tile, FG, 2 * c + q, lane, hop[q]);
-        tile_store(p.a, tile, FG, 2 * c + q, lane, E::pack(v, q));
+        put_rec(rc.dh, 2 * c + q, hop[q]);
+        put_rec(rc.a, 2 * c + q, E::pack(v, q));
       }
       spread(dn, hop);
     }
@@ -394,7 +399,7 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   for (int t = 0; t < NT; ++t) {
     x[t] += upstream(t);                           // gradient of the rows between attention and FFN
 #pragma unroll
-    for (int g = 0; g < 2; ++g) { nop[2 * t + g] = E::pack(x[t], g); tile_store(p.dxmb, tile, NG, 2 * t + g, lane, nop[2 * t + g]); }
+    for (int g = 0; g < 2; ++g) { nop[2 * t + g] = E::pack(x[t], g); put_rec(rc.dxmb, 2 * t + g, nop[2 * t + g]); }
     dn[t] = splat16(0.f);
   }
 
@@ -405,9 +410,9 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
     bf16x8 qop[2], kop[2], vop[2], dop[2];
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
-      qop[g] = tile_load(p.qkv, tile, 3 * NG, 2 * ft + g, lane);
-      kop[g] = tile_load(p.qkv, tile, 3 * NG, NG + 2 * ft + g, lane);
-      vop[g] = tile_load(p.qkv, tile, 3 * NG, 2 * NG + 2 * ft + g, lane);
+      qop[g] = get_rec(rc.qkv, 2 * ft + g);
+      kop[g] = get_rec(rc.qkv, NG + 2 * ft + g);
+      vop[g] = get_rec(rc.qkv, 2 * NG + 2 * ft + g);
     }
     {
       f32x16 d = splat16(0.f);
@@ -497,7 +502,7 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
 #pragma unroll
       for (int g = 0; g < 2; ++g) {
         op[g] = E::pack(m == 0 ? dq : m == 1 ? dk : dv, g);
-        tile_store(p.dqkv, tile, 3 * NG, m * NG + 2 * ft + g, lane, op[g]);
+        put_rec(rc.qkv, m * NG + 2 * ft + g, op[g]);
       }
       spread(dn, op);
     }

@@ -36,7 +36,7 @@ struct WgradArgs { WgradJob job[kMaxWgradJobs]; int njobs, tiles, nslices; };
 // Memory bound at scale: at the headline batch one block's gradients read 4.1 KB per token, 2.1 GB.  Slices take
 // every nslices-th step, so that each samples long and short users alike; the tiles of a slice, which share
 // their operands' rows, run on one accelerator die (one L2).
-// TILES: the operands are tile blocks (bw_block.h: rows are slots, ldx / ldy count sixteens of features).  A step's
+// TILES: the operands are tile blocks in records (bw_block.h: rows are slots; ldx, ldy: sixteens of features from one tile to the next).  A step's
 // tile is then contiguous in memory and goes to LDS as it is.
 template <int TB, bool TILES>
 __global__ __launch_bounds__(256, 3) void bw_wgrad_kernel(const WgradArgs a) {
