@@ -166,34 +166,53 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   __shared__ f32x4 stat[kBlkWaves][2][8];          // its queries' log-sum-exp and sum of P dP
   extern __shared__ f32x4 vec4[];
   float* vec = (float*)vec4;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 31, hi = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 31, hi = lane >> 5;
   const int NC = p.f / 32;
   const BlockRecord rc(D, p.f);
 
   // ---- the lane's token
   const int tile = blockIdx.x * kBlkWaves + wave;
-  char* rec = (char*)p.rec + (size_t)tile * rc.size * 1024 + tile_lane_offset(lane, 0);
-  const int odd = tile_lane_offset(lane, 1) - tile_lane_offset(lane, 0);
-  auto put_rec = [&](int base, int g, bf16x8 v) { *(bf16x8*)(rec + (base + g) * 1024 + (g & 1 ? odd : 0)) = v; };   // (base is even)
-  auto get_rec = [&](int base, int g) -> bf16x8 { return *(const bf16x8*)(rec + (base + g) * 1024 + (g & 1 ? odd : 0)); };
-  const uint32_t slot = (uint32_t)tile * 32u + (uint32_t)j;
-  const uint32_t gidx = slot >> __builtin_ctz(p.K);
-  const int jj = (int)(slot & (uint32_t)(p.K - 1));
-  const int u = (int)(gidx / (uint32_t)p.T), tg = (int)(gidx - (uint32_t)u * (uint32_t)p.T);
-  const bool inside = u < p.B;
-  int len = 0;
-  if (inside) { len = p.lens ? p.lens[u] : p.L; len = min(max(len, 0), p.L); }
-  const int pos = tg * p.K + jj;
-  const bool valid = inside && pos < len;
-  const bool stored = inside && pos < p.L;         // the token has a row in the [B][L] tensors
-  const long long row = (long long)u * p.L + pos;
+  char* rec = (char*)p.rec + (size_t)tile * rc.size * 1024;       // (wave-uniform: a scalar base, the lane's part an offset)
+  const unsigned lane0 = tile_lane_offset(lane, 0), lane1 = tile_lane_offset(lane, 1);
+  typedef __attribute__((address_space(1))) char gchar;
+  typedef __attribute__((address_space(1))) bf16x8 gbf16x8;
+  typedef __attribute__((address_space(1))) f32x4 gf32x4;
+  auto at_rec = [&](int base, int g) -> gbf16x8* {                    // (base is even)
+    gchar* q = (gchar*)(rec + (size_t)((base + g) * 1024));
+    asm("" : "+s"(q));
+    return (gbf16x8*)(q + (g & 1 ? lane1 : lane0));
+  };
+  auto put_rec = [&](int base, int g, bf16x8 v) { *at_rec(base, g) = v; };
+  auto get_rec = [&](int base, int g) -> bf16x8 { return *at_rec(base, g); };
+  auto at_dy = [&](const float* base, int q) -> gf32x4* {             // 1 KiB per 8 features: 4 per lane
+    gchar* b = (gchar*)(base + ((size_t)tile * (D / 8) + q) * 256);
+    asm("" : "+s"(b));
+    return (gf32x4*)(b + 16u * (unsigned)lane);
+  };
+  struct Token { uint32_t slot; int u, tg, jj, len; bool valid, stored; long long row; };
+  auto locate = [&](uint32_t first) {
+    Token k;
+    k.slot = first + (uint32_t)j;
+    const uint32_t gidx = k.slot >> __builtin_ctz(p.K);
+    k.jj = (int)(k.slot & (uint32_t)(p.K - 1));
+    k.u = (int)(gidx / (uint32_t)p.T); k.tg = (int)(gidx - (uint32_t)k.u * (uint32_t)p.T);
+    k.len = 0;
+    if (k.u < p.B) { k.len = p.lens ? p.lens[k.u] : p.L; k.len = min(max(k.len, 0), p.L); }
+    const int pos = k.tg * p.K + k.jj;
+    k.valid = pos < k.len;
+    k.stored = k.u < p.B && pos < p.L;             // the token has a row in the [B][L] tensors
+    k.row = (long long)k.u * p.L + pos;
+    return k;
+  };
+  const Token tk = locate((uint32_t)tile * 32u);
+  const bool valid = tk.valid;
   if (!__syncthreads_or(valid ? 1 : 0)) {
-    if (p.dx_rows && stored) {
+    if (p.dx_rows && tk.stored) {
       const f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) *(f32x4*)(p.dx + row * D + 32 * t + 8 * q + 4 * hi) = z;
+        for (int q = 0; q < 4; ++q) *(f32x4*)(p.dx + tk.row * D + 32 * t + 8 * q + 4 * hi) = z;
     }
     return;
   }
@@ -201,9 +220,9 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   uint32_t wmask[16 / W];
 #pragma unroll
   for (int w = 0; w < 16 / W; ++w) { wmask[w] = widx == w ? 0xffffffffu : 0u; asm("" : "+v"(wmask[w])); }
-  const uint32_t vb = (uint32_t)__ballot(valid);
+  uint32_t vb = (uint32_t)__ballot(valid);
   const uint32_t gb = (p.K >= 32 ? 0xffffffffu : ((1u << p.K) - 1u)) << (p.K * (j / p.K));
-  const uint32_t seen = ((gb & vb) >> (4 * hi)) >> (2 * W * widx);     // window bits: the group's valid tokens
+  uint32_t seen = ((gb & vb) >> (4 * hi)) >> (2 * W * widx);     // window bits: the group's valid tokens
 
   // ---- vectors to LDS, weight stream
   const int oG1 = 0, oB1n = D, oBq = 2 * D, oBv = 3 * D, oBo = 4 * D, oG2 = 5 * D, oB2n = 6 * D, oBf = 7 * D;
@@ -215,8 +234,7 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   for (int i = tid; i < p.f; i += 64 * kBlkWaves) vec[oBf + i] = (float)p.b1[i];
 
   f32x16 x[NT];
-  const long long xoff = (p.x_f32 ? (long long)slot : row) * D;
-  load_rows<__bf16, NT>(x, p.x, p.x_f32, xoff, valid, hi);
+  load_rows<__bf16, NT>(x, p.x, p.x_f32, (p.x_f32 ? (long long)tk.slot : tk.row) * D, valid, hi);
   WStream<SEGV, PSEG, NB, false, 64 * kBlkWaves> ws;
   ws.init(ring, p.wstream, bw_block_segs(D, p.f));
   auto product = [&](f32x16& acc, const bf16x8 (&b)[NG]) {      // acc += (this segment's 32 output features) b
@@ -342,19 +360,15 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   normalise(mean2, rstd2, oG2, oB2n, rc.xh2);
 
   // ---- gradient of the block's output
-  float share = 0.f;
-  const float* up = nullptr;
-  if (p.dM && valid) {
-    up = p.dM + ((size_t)u * p.T + tg) * (size_t)(p.concat ? p.K * D : D) + (p.concat ? jj * D : 0);
-    share = p.concat ? 1.f : 1.f / (float)min(p.K, len - tg * p.K);
-  }
-  auto upstream = [&](int t) -> f32x16 {
+  auto upstream = [&](const Token& k, int t) -> f32x16 {
     f32x16 v;
+    const float share = p.concat ? 1.f : 1.f / (float)min(p.K, k.len - k.tg * p.K);
+    const float* up = p.dM + ((size_t)k.u * p.T + k.tg) * (size_t)(p.concat ? p.K * D : D) + (p.concat ? k.jj * D : 0);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       f32x4 w = {0.f, 0.f, 0.f, 0.f};
-      if (!p.dM) w = *(const f32x4*)(p.dy + ((size_t)tile * (D / 8) + 4 * t + q) * 256 + 4 * lane);
-      else if (up) w = *(const f32x4*)(up + 32 * t + 8 * q + 4 * hi) * share;
+      if (!p.dM) w = *at_dy(p.dy, 4 * t + q);
+      else if (k.valid) w = *(const f32x4*)(up + 32 * t + 8 * q + 4 * hi) * share;
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[4 * q + e] = w[e];
     }
@@ -362,19 +376,28 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   };
   f32x16 dn[NT];
   {
+    // (at width 128 the LDS pieces of the attention, idle here, hold six of the operand's eight groups)
+    constexpr int PARK = NG == 8 ? 6 : 0;
     bf16x8 dyop[NG];
+    char* park = (char*)turn[wave] + lane * 16;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      const f32x16 v = upstream(t);
+      const f32x16 v = upstream(tk, t);
 #pragma unroll
       for (int g = 0; g < 2; ++g) { dyop[2 * t + g] = E::pack(v, g); put_rec(rc.dyb, 2 * t + g, dyop[2 * t + g]); }
       dn[t] = splat16(0.f);
     }
+#pragma unroll
+    for (int g = 0; g < PARK; ++g) *(bf16x8*)(park + g * 1024) = dyop[g];
     // FFN, 32 hidden features at a time: values and gradient formed, used and written out
     for (int c = 0; c < NC; ++c) {
       f32x16 v = bias_tile(vec + oBf, c, hi), g = splat16(0.f);
       product(v, nop);
-      product(g, dyop);
+#pragma unroll
+      for (int s = 0; s < NG; ++s)
+        g = E::mma(ws.template frag<bf16x8>(s), s < PARK ? *(const bf16x8*)(park + s * 1024) : dyop[s], g);
+      ws.advance();
+      settle(g);
       if (p.act == LONGER_ACT_RELU) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) { float a_, d_; act_both(v[r], LONGER_ACT_RELU, &a_, &d_, g[r]); v[r] = a_; g[r] = d_; }
@@ -395,16 +418,22 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
 #pragma unroll
   for (int t = 0; t < NT; ++t) settle(dn[t]);
   norm_backward<NT>(x, dn, vec + oG2, mean2, rstd2, hi);
+  // (where the lane's token sits is worked out again, so that nothing of it is kept through the FFN)
+  uint32_t again = (uint32_t)tile * 32u;
+  asm volatile("" : "+s"(again));
+  const Token tk2 = locate(again);
+  vb = (uint32_t)__ballot(tk2.valid);
+  seen = ((gb & vb) >> (4 * hi)) >> (2 * W * widx);
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    x[t] += upstream(t);                           // gradient of the rows between attention and FFN
+    x[t] += upstream(tk2, t);                          // gradient of the rows between attention and FFN
 #pragma unroll
     for (int g = 0; g < 2; ++g) { nop[2 * t + g] = E::pack(x[t], g); put_rec(rc.dxmb, 2 * t + g, nop[2 * t + g]); }
     dn[t] = splat16(0.f);
   }
 
   // ---- back through the attention, 32 features (one or two heads) at a time
-  const uint32_t keyseen = valid ? seen : 0u;
+  const uint32_t keyseen = tk2.valid ? seen : 0u;
 #pragma unroll
   for (int ft = 0; ft < NT; ++ft) {
     bf16x8 qop[2], kop[2], vop[2], dop[2];
@@ -510,7 +539,10 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
 
   // ---- first LayerNorm's backward: x holds the gradient that reaches the input through the residual connection
   f32x16 xin[NT];
-  load_rows<__bf16, NT>(xin, p.x, p.x_f32, xoff, valid, hi);
+  asm volatile("" : "+s"(again));
+  const Token tk3 = locate(again);
+  load_rows<__bf16, NT>(xin, p.x, p.x_f32, (p.x_f32 ? (long long)tk3.slot : tk3.row) * D, tk3.valid, hi);
+  row_stats<NT>(xin, p.eps, mean1, rstd1);
 #pragma unroll
   for (int t = 0; t < NT; ++t) settle(dn[t]);
   norm_backward<NT>(xin, dn, vec + oG1, mean1, rstd1, hi);
@@ -521,9 +553,9 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
     for (int q = 0; q < 4; ++q) {
       f32x4 v;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = valid ? x[t][4 * q + e] : 0.f;
-      if (!p.dx_rows) *(f32x4*)(p.dx + ((size_t)tile * (D / 8) + 4 * t + q) * 256 + 4 * lane) = v;
-      else if (stored) *(f32x4*)(p.dx + row * D + 32 * t + 8 * q + 4 * hi) = v;
+      for (int e = 0; e < 4; ++e) v[e] = tk3.valid ? x[t][4 * q + e] : 0.f;
+      if (!p.dx_rows) *at_dy(p.dx, 4 * t + q) = v;
+      else if (tk3.stored) *(f32x4*)(p.dx + tk3.row * D + 32 * t + 8 * q + 4 * hi) = v;
     }
   }
 }
