@@ -32,6 +32,7 @@
 // Padded token rows are never read and cost only the zeros written for them.
 #include "bw_grads.h"
 #include "bw_set_attn.h"
+#include "bw_stack.h"
 
 #include <cstdio>
 
@@ -75,18 +76,6 @@ struct GemmArgs {
   const __bf16* A2; const __bf16* B2; int lda2, ldb2;   // the second product of a two-product launch (EPI_FFN_MID)
 };
 
-// Phi(v) = (1 + erf(v / sqrt 2)) / 2 and exp(-v^2 / 2) from one exponential: for z >= 0,
-// erf(z) = 1 - (a1 t + a2 t^2 + a3 t^3 + a4 t^4 + a5 t^5) exp(-z^2), t = 1 / (1 + p z), absolute error
-// below 1.5e-7 (the classic five-term approximation; odd extension for z < 0).
-__device__ __forceinline__ void gauss_cdf(float v, float* cdf, float* ex) {
-  const float z = fabsf(v) * 0.70710678118654752f;
-  const float e = __expf(-z * z);
-  const float t = __frcp_rn(1.f + 0.3275911f * z);
-  const float poly = ((((1.061405429f * t - 1.453152027f) * t + 1.421413741f) * t - 0.284496736f) * t + 0.254829592f) * t;
-  const float half_erfc = 0.5f * poly * e;                 // (1 - erf(|z|)) / 2
-  *cdf = v >= 0.f ? 1.f - half_erfc : half_erfc;
-  *ex = e;
-}
 __device__ __forceinline__ float act_fwd(float v, int act) {
   if (act == LONGER_ACT_RELU) return v > 0.f ? v : 0.f;
   float c, e;
@@ -1070,28 +1059,13 @@ __global__ __launch_bounds__(256) void bw_build_rows_kernel(StackGeom g, int d, 
   }
 }
 
-// x[row][:] = valid(row) ? x[row][:] : 0, and its bf16 copy (xb may be NULL)
-__global__ __launch_bounds__(256) void bw_mask_rows_kernel(float* __restrict__ x, __bf16* __restrict__ xb,
-                                                           const int* __restrict__ desc, size_t rows, int d) {
-  const int d4 = d / 4;
-  const size_t total = rows * d4;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
-    const size_t row = i / d4;
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (desc[row] >= 0) v = *(const f32x4*)(x + i * 4);
-    *(f32x4*)(x + i * 4) = v;
-    if (xb) store_bf16x4(xb + i * 4, v);
-  }
-}
-
 // Head and loss (Eq. 1-2) for one user per block: logit = <head_w, the m global rows of Y> + head_b,
 // loss += (softplus form of the cross-entropy) / B, dlogit = (sigmoid(logit) - label) / B, and the
-// gradients that follow: dY (global rows dlogit head_w, the other rows zero; fp32 and bf16), head_w, head_b.
+// gradients that follow: dY (global rows dlogit head_w, the other rows zero), head_w, head_b.
 __global__ __launch_bounds__(256) void bw_head_kernel(const float* __restrict__ Y, const __bf16* __restrict__ hw,
                                                       const __bf16* __restrict__ hb, const float* __restrict__ labels,
                                                       int B, int n, int m, int d, float* __restrict__ logits,
-                                                      float* loss, float* __restrict__ dY, __bf16* __restrict__ dYb,
-                                                      float* dhw, float* dhb) {
+                                                      float* loss, float* __restrict__ dY, float* dhw, float* dhb) {
   __shared__ float red[4];
   __shared__ float dl_s;
   const int u = blockIdx.x;
@@ -1117,7 +1091,6 @@ __global__ __launch_bounds__(256) void bw_head_kernel(const float* __restrict__ 
   for (int j = threadIdx.x; j < n * d; j += 256) {
     const float g = j < m * d ? dl * (float)hw[j] : 0.f;
     dY[(size_t)u * n * d + j] = g;
-    dYb[(size_t)u * n * d + j] = (__bf16)g;
     if (j < m * d) unsafeAtomicAdd(dhw + j, dl * y[j]);
   }
 }
@@ -1234,55 +1207,36 @@ __global__ __launch_bounds__(256) void bw_transpose_kernel(const __bf16* __restr
 }
 
 // ------------------------------------------------------------------------------------
-// Weights of InnerTrans blocks for the block kernel (bw_block.h): the segments in the order it consumes them, each
-// D / 16 fragments of 64 lanes x 16 bytes.  Fragment = 32 rows of the product's result (lane % 32) x 16 contracted
-// features in the order the lanes hold them (element e of lane half hi: 8 (e / 4) + 4 hi + e % 4).
-constexpr int kPackBlocks = 8;            // blocks per launch
-struct PackBlocks { struct { const __bf16 *wq, *wk, *wv, *wo, *w1, *w2; } b[kPackBlocks]; __bf16* out; size_t stride; };   // stride: elements
-__global__ __launch_bounds__(256) void bw_pack_block_kernel(const PackBlocks a, int d, int f) {
-  const int NT = d / 32, NG = d / 16, NC = f / 32, segs = bw_block_segs(d, f), padded = bw_block_segs_padded(d, f);
-  const auto& b = a.b[blockIdx.y];
-  __bf16* out = a.out + blockIdx.y * a.stride;
-  const int total = padded * NG * 64;
+// Weights for the tile kernels (bw_block.h, bw_stack.h), in the order a launch consumes them: segments of d / 16
+// fragments of 64 lanes x 16 bytes.  Fragment = 32 rows of the product's result (lane % 32) x 16 contracted features in
+// the order the lanes hold them (element e of lane half hi: 8 (e / 4) + 4 hi + e % 4).  A segment is either 32 result
+// features over the whole width, or (spread) all result features over 32 contracted ones.
+struct PackJob {
+  const __bf16* w; int sk, sm;            // element (contracted k, result m) at w[k sk + m sm]
+  int spread, n, pos, stride;             // n segments, the i-th at place pos + i stride of the stream
+};
+constexpr int kPackJobs = 64;
+struct PackJobs { PackJob job[kPackJobs]; __bf16* out; };
+__global__ __launch_bounds__(256) void bw_pack_kernel(const PackJobs a, int d) {
+  const PackJob& b = a.job[blockIdx.y];
+  const int NG = d / 16, total = b.n * NG * 64;
   for (int i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
-    const int lane = i & 63, fr = i >> 6, s = fr % NG;
-    int seg = fr / NG;
-    const int m = lane & 31, hi = lane >> 5;
-    // element (k, m) of the fragment sits at src[k ks + m ms], k the contracted feature
-    const __bf16* src = nullptr;
-    int ks = 1;
-    if (seg < 3 * NT) {                                  // Q, K, V of 32 features
-      const __bf16* w = seg % 3 == 0 ? b.wq : seg % 3 == 1 ? b.wk : b.wv;
-      src = w + (size_t)(16 * s) * d + 32 * (seg / 3) + m; ks = d;
-    } else if (seg < 4 * NT) {                           // output projection
-      src = b.wo + (size_t)(16 * s) * d + 32 * (seg - 3 * NT) + m; ks = d;
-    } else if (seg < 4 * NT + 3 * NC) {
-      seg -= 4 * NT;
-      const int c = seg / 3;
-      if (seg % 3 == 0) { src = b.w1 + (size_t)(16 * s) * f + 32 * c + m; ks = f; }                   // hidden values
-      else if (seg % 3 == 1) src = b.w2 + (size_t)(32 * c + m) * d + 16 * s;                          // their gradient
-      else src = b.w1 + (size_t)(32 * (s / 2) + m) * f + 32 * c + 16 * (s % 2);                       // back through W1
-    } else if (seg < segs) {
-      seg -= 4 * NT + 3 * NC;
-      const int ft = seg / 4;
-      if (seg % 4 == 0) src = b.wo + (size_t)(32 * ft + m) * d + 16 * s;                              // back through W_O
-      else {
-        const __bf16* w = seg % 4 == 1 ? b.wq : seg % 4 == 2 ? b.wk : b.wv;
-        src = w + (size_t)(32 * (s / 2) + m) * d + 32 * ft + 16 * (s % 2);                            // through W_Q, W_K, W_V
-      }
-    }
+    const int lane = i & 63, s = (i >> 6) % NG, seg = (i >> 6) / NG, m = lane & 31, hi = lane >> 5;
+    const __bf16* src = b.w + (b.spread ? (size_t)(32 * seg + 16 * (s % 2)) * b.sk + (size_t)(32 * (s / 2) + m) * b.sm
+                                        : (size_t)(16 * s) * b.sk + (size_t)(32 * seg + m) * b.sm);
     bf16x8 v;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = src ? src[(size_t)(8 * (e / 4) + 4 * hi + e % 4) * ks] : (__bf16)0.f;
-    *(bf16x8*)(out + (size_t)i * 8) = v;
+    for (int e = 0; e < 8; ++e) v[e] = src[(size_t)(8 * (e / 4) + 4 * hi + e % 4) * b.sk];
+    *(bf16x8*)(a.out + (((size_t)(b.pos + seg * b.stride) * NG + s) * 64 + lane) * 8) = v;
   }
 }
 
-// The parameter gradients that the block kernel leaves in terms of the normalised rows xh (y = xh g + s in front
+// The parameter gradients that the tile kernels leave in terms of the normalised rows xh (y = xh g + s in front
 // of the products W): with X = xh^T dY and c = column sums of dY (bias gradients) both summed by now,
 //   dW = diag(g) X + s c^T,   dg[e] = sum_c W[e][c] X[e][c],   ds[e] = sum_c W[e][c] c[c],
 // so the LayerNorm gradients need no pass over the tokens.  One workgroup per row e and LayerNorm.
-struct NormGrads { struct { const __bf16 *w[3], *gain, *shift; float *dw, *dgain; } n[2 * kPackBlocks]; };
+constexpr int kNormBlocks = 8;            // blocks per launch
+struct NormGrads { struct { const __bf16 *w[3], *gain, *shift; float *dw, *dgain; } n[2 * kNormBlocks]; };
 __global__ __launch_bounds__(256) void bw_norm_grads_kernel(const NormGrads a, int d, int f) {
   const int which = blockIdx.y & 1, e = blockIdx.x, n = which ? f : d, mats = which ? 1 : 3;     // ln1: Q, K, V; ln2: W1
   const auto& q = a.n[blockIdx.y];
@@ -1378,6 +1332,42 @@ static int launch(WgradBatch& w, float* part, hipStream_t st) {
 static int launch(const ReduceBatch& r, hipStream_t st) {
   bw_reduce_jobs_kernel<<<(unsigned)r.blocks, 256, 0, st>>>(r.a);
   return hipGetLastError() == hipSuccess ? 0 : api_error(LONGER_ERR_HIP, "gradient reduction launch failed");
+}
+
+// Weights of one or several streams, packed in as few launches as their number allows
+struct PackBatch {
+  PackJobs a = {};
+  int n = 0, d; hipStream_t st; int rc = 0;
+  PackBatch(int d_, __bf16* out, hipStream_t st_) : d(d_), st(st_) { a.out = out; }
+  void add(const void* w, int sk, int sm, bool spread, int segs, int pos, int stride) {
+    if (n == kPackJobs) flush();
+    a.job[n++] = PackJob{(const __bf16*)w, sk, sm, spread, segs, pos, stride};
+  }
+  int flush() {
+    if (n && !rc) {
+      bw_pack_kernel<<<dim3(64, n), 256, 0, st>>>(a, d);
+      if (hipGetLastError() != hipSuccess) rc = api_error(LONGER_ERR_HIP, "weight packing launch failed");
+    }
+    n = 0;
+    return rc;
+  }
+};
+// LayerNorm gradients and dW = diag(g) X + s c^T of whole blocks (bw_norm_grads_kernel); grads of block i at g0 + i stride
+static int norm_grads(int d, int f, const longer_block* blocks, int count, float* g0, size_t stride, hipStream_t st) {
+  const GradLayout gl = grad_layout(d, f);
+  for (int l0 = 0; l0 < count; l0 += kNormBlocks) {
+    NormGrads ng = {};
+    const int n = count - l0 < kNormBlocks ? count - l0 : kNormBlocks;
+    for (int i = 0; i < n; ++i) {
+      const longer_block& b = blocks[l0 + i];
+      float* g = g0 + (size_t)(l0 + i) * stride;
+      ng.n[2 * i] = {{(const __bf16*)b.wq, (const __bf16*)b.wk, (const __bf16*)b.wv}, (const __bf16*)b.ln1_g, (const __bf16*)b.ln1_b, g + gl.wq, g + gl.ln1_g};
+      ng.n[2 * i + 1] = {{(const __bf16*)b.w1, nullptr, nullptr}, (const __bf16*)b.ln2_g, (const __bf16*)b.ln2_b, g + gl.w1, g + gl.ln2_g};
+    }
+    bw_norm_grads_kernel<<<dim3(d, 2 * n), 256, 0, st>>>(ng, d, f);
+    if (hipGetLastError() != hipSuccess) return api_error(LONGER_ERR_HIP, "LayerNorm gradient launch failed");
+  }
+  return 0;
 }
 
 static Workspace workspace(int layers, size_t ntok, int d, int f, int heads, size_t fwd_bytes, size_t ztmp_bytes) {
@@ -1594,17 +1584,20 @@ static int run_tiled(const longer_config* c, const longer_block* inner, const vo
   const RowsValid rv = {lens, s.T * s.K};
   const size_t stream_elems = (size_t)bw_block_segs_padded(d, f) * packed_seg_bytes(d, 2) / 2;
   auto at = [&](size_t o) { return (__bf16*)(ws + o); };
-  for (int l0 = 0; l0 < s.layers; l0 += kPackBlocks) {
-    PackBlocks pk = {};
-    const int n = s.layers - l0 < kPackBlocks ? s.layers - l0 : kPackBlocks;
-    for (int i = 0; i < n; ++i) {
-      const longer_block& b = inner[l0 + i];
-      pk.b[i] = {(const __bf16*)b.wq, (const __bf16*)b.wk, (const __bf16*)b.wv, (const __bf16*)b.wo, (const __bf16*)b.w1, (const __bf16*)b.w2};
-    }
-    pk.out = at(w.stream) + l0 * stream_elems; pk.stride = stream_elems;
-    bw_pack_block_kernel<<<dim3((unsigned)((stream_elems / 8 + 255) / 256), n), 256, 0, st>>>(pk, d, f);
-    BW_TRY(launched("weight packing"));
+  PackBatch pk(d, at(w.stream), st);
+  for (int l = 0; l < s.layers; ++l) {
+    const longer_block& b = inner[l];
+    const int NT = d / 32, NC = f / 32, o = l * bw_block_segs_padded(d, f), c = o + 4 * NT, k = c + 3 * NC;
+    const void* qkv[3] = {b.wq, b.wk, b.wv};
+    for (int i = 0; i < 3; ++i) pk.add(qkv[i], d, 1, false, NT, o + i, 3);
+    pk.add(b.wo, d, 1, false, NT, o + 3 * NT, 1);
+    pk.add(b.w1, f, 1, false, NC, c, 3);              // hidden values, their gradient, back through W1
+    pk.add(b.w2, 1, d, false, NC, c + 1, 3);
+    pk.add(b.w1, 1, f, true, NC, c + 2, 3);
+    pk.add(b.wo, 1, d, false, NT, k, 4);              // back through W_O and, 32 features at a time, W_Q, W_K, W_V
+    for (int i = 0; i < 3; ++i) pk.add(qkv[i], 1, d, true, NT, k + 1 + i, 4);
   }
+  BW_TRY(pk.flush());
   // block inputs, by the fused forward kernel (its fp32 residual stream after l blocks is block l's input)
   auto xin = [&](int l) { return (float*)(ws + w.xin) + (size_t)(l - 1) * s.padded * d; };
   for (int l = 1; l < s.layers; ++l) BW_TRY(inner_chain_f32(c, inner, l, H, lens, B, L, xin(l), ws + w.fwd, w.fwd_bytes, st));
@@ -1632,18 +1625,7 @@ static int run_tiled(const longer_config* c, const longer_block* inner, const vo
     rb.add(wg);
     BW_TRY(launch(rb, st));
   }
-  for (int l0 = 0; l0 < s.layers; l0 += kPackBlocks) {
-    NormGrads ng = {};
-    const int n = s.layers - l0 < kPackBlocks ? s.layers - l0 : kPackBlocks;
-    for (int i = 0; i < n; ++i) {
-      const longer_block& b = inner[l0 + i];
-      float* g = grads + (size_t)(l0 + i) * gl.total;
-      ng.n[2 * i] = {{(const __bf16*)b.wq, (const __bf16*)b.wk, (const __bf16*)b.wv}, (const __bf16*)b.ln1_g, (const __bf16*)b.ln1_b, g + gl.wq, g + gl.ln1_g};
-      ng.n[2 * i + 1] = {{(const __bf16*)b.w1, nullptr, nullptr}, (const __bf16*)b.ln2_g, (const __bf16*)b.ln2_b, g + gl.w1, g + gl.ln2_g};
-    }
-    bw_norm_grads_kernel<<<dim3(d, 2 * n), 256, 0, st>>>(ng, d, f);
-    BW_TRY(launched("LayerNorm gradients"));
-  }
+  BW_TRY(norm_grads(d, f, inner, s.layers, grads, gl.total, st));
   return 0;
 }
 
@@ -1756,79 +1738,88 @@ struct StackDims { int d, f, heads, dh, m, k, n, T, B, layers; size_t rq, rk; };
 
 struct StackWs {
   size_t fwd_ws, Mb, dM;                  // forward token merge: its scratch, M (bf16), and the gradient handed to the merge
-  size_t qdesc, kdesc, wcat, bcat;
+  size_t qdesc, kdesc, stream;
   size_t Rx, xs;                          // cross-layer key rows; the layers' input rows ([layers + 1][rq][d], [0] = O)
-  size_t n1q, n1k, qkv, kv, o, xmid, n2, h, a, stat;    // every layer's intermediates are kept (per_layer bytes apart):
-  size_t dyb, dh, dxmb, dqkv;                           // the reduced stack is small, only the merge is recomputed; so
-  size_t per_layer;                                     // are the gradients that its parameter gradients contract
-  size_t dy, dnq, dnk, dxm, dob, dkv, dR, part, lnpart;
+  size_t qkv, stat, xmid, rec, per_layer; // every layer's intermediates are kept (per_layer bytes apart): the reduced stack is
+                                          // small, only the merge is recomputed
+  size_t kv, krec, o, dy, dxm, dob, dqkv, dkv, dR, part;
+  size_t rqp, rkp;                        // rows in whole workgroups of the tile kernels
   size_t total;
+};
+// records of the cross layer's key rows: normalised rows, gradients of K and V
+static int key_record(int d) { return 3 * d / 16; }
+// Where each launch's weights start (segments).  Forward: [Q of the cross layer] | [tail of 0, head of 1] | ... | [tail of the
+// last]; backward: [head of the last] | [tail of it, head of the one before] | ... | [Q]; then K / V of the cross layer, both ways.
+struct StackStreams {
+  int NT, NC, layers, kv_f, kv_b, total;
+  StackStreams(int d, int f, int n) : NT(d / 32), NC(f / 32), layers(n) {
+    kv_f = bwd_tail(0) + NT; kv_b = kv_f + 2 * NT; total = kv_b + 2 * NT + 4;      // (streams are read in whole panels)
+  }
+  int fwd_head(int l) const { return l == 0 ? 0 : fwd_tail(l) - 3 * NT; }
+  int fwd_tail(int l) const { return NT + l * (NT + 2 * NC + 3 * NT); }
+  int fwd_end() const { return fwd_tail(layers - 1) + NT + 2 * NC; }
+  int bwd_head(int l) const { return fwd_end() + (layers - 1 - l) * (3 * NC + NT + 3 * NT); }
+  int bwd_tail(int l) const { return bwd_head(l) + 3 * NC + NT; }
 };
 // The gradients of every matrix of the stack in one batch: the self layers' (per_layer bytes and `per_main` floats
 // apart), then the cross layer's, whose keys and values contract over the key rows
 static WgradBatch stack_wgrads(const StackDims& s, const StackWs& w, const char* ws, float* grads, size_t cross, size_t self0, size_t per_main) {
   const int d = s.d, f = s.f;
   const GradLayout gl = grad_layout(d, f);
+  const BlockRecord r(d, f);
   const RowsValid all = {nullptr, 0};
-  WgradBatch b(d, s.rq);
+  WgradBatch b(d, s.rq, true);
   const long long ls = (long long)(w.per_layer / 2), os = (long long)per_main;
-  auto at = [&](size_t ofs, int l) { return (const __bf16*)(ws + ofs + (size_t)l * w.per_layer); };
+  auto at = [&](int o, int l) { return (const __bf16*)(ws + w.rec + (size_t)l * w.per_layer) + (size_t)o * 512; };
   auto side = [&](int l, int n, float* g) {
-    b.add(at(w.a, l), f, f, at(w.dyb, l), d, d, d, s.rq, all, g + gl.w2, n, ls, ls, os);
-    b.add(at(w.n2, l), d, d, at(w.dh, l), f, f, f, s.rq, all, g + gl.w1, n, ls, ls, os);
-    b.add(at(w.o, l), d, d, at(w.dxmb, l), d, d, d, s.rq, all, g + gl.wo, n, ls, ls, os);
+    b.add(at(r.a, l), r.size, f, at(r.dyb, l), r.size, d, d, s.rq, all, g + gl.w2, n, ls, ls, os);
+    b.add(at(r.xh2, l), r.size, d, at(r.dh, l), r.size, f, f, s.rq, all, g + gl.w1, n, ls, ls, os);
+    b.add(at(r.o, l), r.size, d, at(r.dxmb, l), r.size, d, d, s.rq, all, g + gl.wo, n, ls, ls, os);
   };
   if (s.layers > 1) {
     float* g = grads + self0;
     side(1, s.layers - 1, g);
-    b.add(at(w.n1q, 1), d, d, at(w.dqkv, 1), 3 * d, 3 * d, d, s.rq, all, g + gl.wq, s.layers - 1, ls, ls, os);
+    b.add(at(r.xh1, 1), r.size, d, at(r.qkv, 1), r.size, 3 * d, d, s.rq, all, g + gl.wq, s.layers - 1, ls, ls, os);
   }
   float* g = grads + cross;
   side(0, 1, g);
-  b.add(at(w.n1q, 0), d, d, at(w.dqkv, 0), d, d, d, s.rq, all, g + gl.wq);
-  b.add(at(w.n1k, 0), d, d, (const __bf16*)(ws + w.dkv), 2 * d, 2 * d, d, s.rk, all, g + gl.wk);
+  b.add(at(r.xh1, 0), r.size, d, at(r.qkv, 0), r.size, d, d, s.rq, all, g + gl.wq);
+  const __bf16* kr = (const __bf16*)(ws + w.krec);
+  b.add(kr, key_record(d), d, kr + (size_t)(d / 16) * 512, key_record(d), 2 * d, d, s.rk, all, g + gl.wk);
   return b;
 }
 static StackWs stack_ws(const StackDims& s, size_t fwd_bytes) {
   StackWs w;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += up256(bytes); return at; };
-  const size_t rq = s.rq, rk = s.rk, d = s.d, f = s.f;
+  const size_t rq = s.rq, rk = s.rk, d = s.d, f = s.f, whole = 32 * kStackWaves;
+  w.rqp = (rq + whole - 1) / whole * whole;
+  w.rkp = (rk + whole - 1) / whole * whole;
   w.fwd_ws = take(fwd_bytes);
   w.Mb = take((size_t)s.B * s.T * d * 2);
   w.dM = take((size_t)s.B * s.T * d * 4);
   w.qdesc = take(rq * 4);
   w.kdesc = take(rk * 4);
-  w.wcat = take((size_t)s.layers * d * 3 * d * 2);
-  w.bcat = take((size_t)s.layers * up256(3 * d * 2));
+  w.stream = take((size_t)StackStreams(s.d, s.f, s.layers).total * packed_seg_bytes(s.d, 2));
   w.Rx = take(rk * d * 4);
   w.xs = take((size_t)(s.layers + 1) * rq * d * 4);
   const size_t layer0 = o;
-  w.n1q = take(rq * d * 2);
-  w.n1k = take(rk * d * 2);
   w.qkv = take(rq * 3 * d * 2);
-  w.kv = take(rk * 2 * d * 2);
-  w.o = take(rq * d * 2);
-  w.xmid = take(rq * d * 4);
-  w.n2 = take(rq * d * 2);
-  w.h = take(rq * f * 2);
-  w.a = take(rq * f * 2);
   w.stat = take(rq * s.heads * 8);
-  w.dyb = take(rq * d * 2);
-  w.dh = take(rq * f * 2);
-  w.dxmb = take(rq * d * 2);
-  w.dqkv = take(rq * 3 * d * 2);
+  w.xmid = take(w.rqp * d * 4);
+  w.rec = take(w.rqp / 32 * BlockRecord(s.d, s.f).size * 1024);
   w.per_layer = o - layer0;
   o += (size_t)(s.layers - 1) * w.per_layer;
+  w.kv = take(rk * 2 * d * 2);
+  w.krec = take(w.rkp / 32 * key_record(s.d) * 1024);
+  w.o = take(rq * d * 2);
   w.dy = take(rq * d * 4);
-  w.dnq = take(rq * d * 2);
-  w.dnk = take(rk * d * 2);
-  w.dxm = take(rq * d * 4);
+  w.dxm = take(w.rqp * d * 4);
   w.dob = take(rq * d * 2);
+  w.dqkv = take(rq * 3 * d * 2);
   w.dkv = take(rk * 2 * d * 2);
   w.dR = take(rk * d * 4);
   w.part = take(stack_wgrads(s, w, nullptr, nullptr, 0, 0, 0).place(nullptr) * 4);
-  w.lnpart = take((size_t)(2 * s.layers + 1) * kMaxLnBlocks * 2 * d * 4);
   w.total = o;
   return w;
 }
@@ -1878,27 +1869,16 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
   int* qdesc = (int*)(ws + w.qdesc);   int* kdesc = (int*)(ws + w.kdesc);
   __bf16* Mb = (__bf16*)(ws + w.Mb);   float* dM = (float*)(ws + w.dM);     float* Rx = (float*)(ws + w.Rx);
   auto xs = [&](int l) { return (float*)(ws + w.xs) + (size_t)l * rq * d; };
-  auto wcat = [&](int l) { return (__bf16*)(ws + w.wcat) + (size_t)l * d * 3 * d; };
-  auto bcat = [&](int l) { return (__bf16*)(ws + w.bcat + (size_t)l * up256((size_t)3 * d * 2)); };
   auto blk = [&](int l) -> const longer_block& { return l == 0 ? wts->cross[0] : wts->self[l - 1]; };
-  __bf16 *n1q, *n1k, *qkv, *kv, *o, *n2, *h, *a, *dyb, *dh, *dxmb, *dqkv;      // the current layer's intermediates
-  float* xmid;
-  float2* stat;
-  auto use_layer = [&](int l) {
-    char* base = ws + (size_t)l * w.per_layer;
-    n1q = (__bf16*)(base + w.n1q); n1k = (__bf16*)(base + w.n1k); qkv = (__bf16*)(base + w.qkv); kv = (__bf16*)(base + w.kv);
-    o = (__bf16*)(base + w.o); xmid = (float*)(base + w.xmid); n2 = (__bf16*)(base + w.n2); h = (__bf16*)(base + w.h);
-    a = (__bf16*)(base + w.a); stat = (float2*)(base + w.stat);
-    dyb = (__bf16*)(base + w.dyb); dh = (__bf16*)(base + w.dh); dxmb = (__bf16*)(base + w.dxmb); dqkv = (__bf16*)(base + w.dqkv);
-  };
-  float* dy = (float*)(ws + w.dy);
-  __bf16* dnq = (__bf16*)(ws + w.dnq); __bf16* dnk = (__bf16*)(ws + w.dnk); float* dxm = (float*)(ws + w.dxm);
-  __bf16* dob = (__bf16*)(ws + w.dob); __bf16* dkv = (__bf16*)(ws + w.dkv); float* dR = (float*)(ws + w.dR);
-  // LayerNorm partials: ln2 of every layer, ln1 of the self layers, then the cross layer's ln1 (query rows, key rows)
-  const unsigned lnq = ln_blocks(rq), lnk = ln_blocks(rk);
-  const size_t ln_stride = (size_t)kMaxLnBlocks * 2 * d;
-  auto ln2part = [&](int l) { return (float*)(ws + w.lnpart) + (size_t)l * ln_stride; };
-  auto ln1part = [&](int l) { return (float*)(ws + w.lnpart) + (size_t)(s.layers + (l ? l - 1 : s.layers - 1)) * ln_stride; };
+  auto of = [&](size_t o, int l) { return ws + o + (size_t)l * w.per_layer; };      // a layer's own buffers
+  auto bf = [](const void* q) { return (const __bf16*)q; };
+  __bf16* kv = (__bf16*)(ws + w.kv);   __bf16* krec = (__bf16*)(ws + w.krec); __bf16* o = (__bf16*)(ws + w.o);
+  float* dy = (float*)(ws + w.dy);     float* dxm = (float*)(ws + w.dxm);     __bf16* dob = (__bf16*)(ws + w.dob);
+  __bf16* dqkv = (__bf16*)(ws + w.dqkv); __bf16* dkv = (__bf16*)(ws + w.dkv); float* dR = (float*)(ws + w.dR);
+  const BlockRecord r(d, f);
+  const StackStreams sg(d, f, s.layers);
+  const int NT = d / 32, NC = f / 32, last = s.layers - 1;
+  auto stream_at = [&](int seg) { return ws + w.stream + (size_t)seg * packed_seg_bytes(d, 2); };
 
   // what is added to with atomics: the head's gradients, the learnable query tokens', the loss
   bw_zero_kernel<<<flat_grid(mg.total - mg.head_w), 256, 0, st>>>(grads + mg.head_w, mg.total - mg.head_w);
@@ -1912,111 +1892,125 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
   bw_desc_kernel<<<flat_grid(rq + rk), 256, 0, st>>>(geo, qdesc, kdesc);
   bw_build_rows_kernel<<<flat_grid((rq + rk) * d / 4), 256, 0, st>>>(geo, d, (const __bf16*)G, Mb, (const __bf16*)c->q_learn, qdesc, kdesc, xs(0), Rx);
   BW_TRY(launched("row build"));
+  PackBatch pk(d, (__bf16*)(ws + w.stream), st);
   for (int l = 0; l < s.layers; ++l) {
     const longer_block& b = blk(l);
-    bw_concat_qkv_kernel<<<64, 256, 0, st>>>((const __bf16*)b.wq, (const __bf16*)b.wk, (const __bf16*)b.wv, (const __bf16*)b.bq,
-                                             (const __bf16*)b.bk, (const __bf16*)b.bv, wcat(l), bcat(l), d);
-    BW_TRY(launched("weight concatenation"));
+    const void* qkv[3] = {b.wq, b.wk, b.wv};
+    const int mats = l ? 3 : 1, t = sg.fwd_tail(l) + NT, h = sg.bwd_head(l);
+    for (int i = 0; i < mats; ++i) {
+      pk.add(qkv[i], d, 1, false, NT, sg.fwd_head(l) + i, mats);
+      pk.add(qkv[i], 1, d, true, NT, sg.bwd_tail(l) + i, mats);
+    }
+    for (int i = mats; i < 3; ++i) {
+      pk.add(qkv[i], d, 1, false, NT, sg.kv_f + i - 1, 2);
+      pk.add(qkv[i], 1, d, true, NT, sg.kv_b + i - 1, 2);
+    }
+    pk.add(b.wo, d, 1, false, NT, sg.fwd_tail(l), 1);
+    pk.add(b.w1, f, 1, false, NC, t, 2);
+    pk.add(b.w2, d, 1, true, NC, t + 1, 2);
+    pk.add(b.w1, f, 1, false, NC, h, 3);              // hidden values, their gradient, back through W1
+    pk.add(b.w2, 1, d, false, NC, h + 1, 3);
+    pk.add(b.w1, 1, f, true, NC, h + 2, 3);
+    pk.add(b.wo, 1, d, false, NT, h + 3 * NC, 1);
   }
+  BW_TRY(pk.flush());
 
   auto attn = [&](int l) {
     SetAttn t;
+    const __bf16* qkv = (const __bf16*)of(w.qkv, l);
     t.qdesc = qdesc; t.nq = s.n; t.B = B; t.heads = s.heads; t.gmask = c->gmask;
     if (l == 0) { t.q = qkv; t.qpitch = d; t.k = kv; t.v = kv + d; t.kvpitch = 2 * d; t.kdesc = kdesc; t.nk = s.m + s.T; }
     else { t.q = qkv; t.qpitch = 3 * d; t.k = qkv + d; t.v = qkv + 2 * d; t.kvpitch = 3 * d; t.kdesc = qdesc; t.nk = s.n; }
     return t;
   };
-  // layer l forward from its input rows xs(l) (layer 0: and the key rows Rx), intermediates into the
-  // layer's own buffers; output into y_out (masked to the valid rows)
-  auto forward = [&](int l, float* y_out) -> int {
-    const longer_block& b = blk(l);
-    const float* x = xs(l);
-    use_layer(l);
-    ln_fwd(st, lnq, d, x, (const __bf16*)b.ln1_g, (const __bf16*)b.ln1_b, n1q, (int)rq, c->ln_eps);
-    if (l == 0) {
-      ln_fwd(st, lnk, d, Rx, (const __bf16*)b.ln1_g, (const __bf16*)b.ln1_b, n1k, (int)rk, c->ln_eps);
-      BW_TRY(launched("LayerNorm"));
-      BW_TRY(gemm_rows(st, n1q, d, wcat(l), d, rq, EPI_BF16, 0, qkv, nullptr, bcat(l), nullptr, nullptr, 3 * d));
-      BW_TRY(gemm_rows(st, n1k, d, wcat(l) + d, 2 * d, rk, EPI_BF16, 0, kv, nullptr, bcat(l) + d, nullptr, nullptr, 3 * d));
-    } else {
-      BW_TRY(launched("LayerNorm"));
-      BW_TRY(gemm_rows(st, n1q, d, wcat(l), 3 * d, rq, EPI_BF16, 0, qkv, nullptr, bcat(l), nullptr, nullptr));
-    }
-    const SetAttn t = attn(l);
-    if (s.dh == 16) set_attn_launch<16>(st, 0, t, nullptr, d, o, 0, nullptr, nullptr, stat);
-    else set_attn_launch<32>(st, 0, t, nullptr, d, o, 0, nullptr, nullptr, stat);
-    BW_TRY(launched("attention"));
-    BW_TRY(gemm_rows(st, o, d, (const __bf16*)b.wo, d, rq, EPI_RES_F32, 0, xmid, nullptr, (const __bf16*)b.bo, x, nullptr));
-    ln_fwd(st, lnq, d, xmid, (const __bf16*)b.ln2_g, (const __bf16*)b.ln2_b, n2, (int)rq, c->ln_eps);
-    BW_TRY(launched("LayerNorm"));
-    BW_TRY(gemm_rows(st, n2, d, (const __bf16*)b.w1, f, rq, EPI_ACT, c->act, h, a, (const __bf16*)b.b1, nullptr, nullptr));
-    if (y_out) {
-      BW_TRY(gemm_rows(st, a, f, (const __bf16*)b.w2, d, rq, EPI_RES_F32, 0, y_out, nullptr, (const __bf16*)b.b2, xmid, nullptr));
-      bw_mask_rows_kernel<<<flat_grid(rq * d / 4), 256, 0, st>>>(y_out, nullptr, qdesc, rq, d);
-      BW_TRY(launched("row mask"));
-    }
-    return 0;
+  auto set_attn = [&](int which, int l, __bf16* out, int pitch, __bf16* dk, __bf16* dv) -> int {
+    float2* stat = (float2*)of(w.stat, l);
+    if (s.dh == 16) set_attn_launch<16>(st, which, attn(l), dob, d, out, pitch, dk, dv, stat);
+    else set_attn_launch<32>(st, which, attn(l), dob, d, out, pitch, dk, dv, stat);
+    return launched(which ? "attention backward" : "attention");
   };
-  for (int l = 0; l < s.layers; ++l) BW_TRY(forward(l, xs(l + 1)));
-
-  // ---- head and loss (Eq. 1-2), and the gradient of the stack's output
-  use_layer(s.layers - 1);
-  bw_head_kernel<<<B, 256, 0, st>>>(xs(s.layers), (const __bf16*)wts->head_w, (const __bf16*)wts->head_b, labels, B, s.n, s.m, d,
-                                    logits, loss, dy, dyb, grads + mg.head_w, grads + mg.head_b);
-  BW_TRY(launched("head"));
-
-  // ---- back through the layers
-  for (int l = s.layers - 1; l >= 0; --l) {
-    const longer_block& b = blk(l);
-    use_layer(l);                                  // kept by the forward pass above
-    // rows that were written as zeros pass no gradient
-    bw_mask_rows_kernel<<<flat_grid(rq * d / 4), 256, 0, st>>>(dy, dyb, qdesc, rq, d);
-    BW_TRY(launched("row mask"));
-    BW_TRY(gemm_rows_t(st, dyb, d, (const __bf16*)b.w2, f, rq, EPI_DACT, c->act, dh, h));
-    BW_TRY(gemm_rows_t(st, dh, f, (const __bf16*)b.w1, d, rq, EPI_BF16, 0, dnq, nullptr));
-    BW_TRY(ln_bwd(st, lnq, d, dnq, xmid, (const __bf16*)b.ln2_g, dy, dxm, dxmb, ln2part(l), (int)rq, c->ln_eps));
-    BW_TRY(gemm_rows_t(st, dxmb, d, (const __bf16*)b.wo, d, rq, EPI_BF16, 0, dob, nullptr));
-    const SetAttn t = attn(l);
-    if (l == 0) {
-      if (s.dh == 16) {
-        set_attn_launch<16>(st, 1, t, dob, d, dqkv, d, nullptr, nullptr, stat);
-        set_attn_launch<16>(st, 2, t, dob, d, nullptr, 2 * d, dkv, dkv + d, stat);
-      } else {
-        set_attn_launch<32>(st, 1, t, dob, d, dqkv, d, nullptr, nullptr, stat);
-        set_attn_launch<32>(st, 2, t, dob, d, nullptr, 2 * d, dkv, dkv + d, stat);
-      }
-      BW_TRY(launched("attention backward"));
-      BW_TRY(gemm_rows_t(st, dqkv, d, wcat(l), d, rq, EPI_BF16, 0, dnq, nullptr, 3 * d));
-      BW_TRY(gemm_rows_t(st, dkv, 2 * d, wcat(l) + d, d, rk, EPI_BF16, 0, dnk, nullptr, 3 * d));
-      // LN1 normalises the query rows and the key rows: its gain / shift gradient is the sum of both;
-      // dO goes to dy (the query rows' gradient), dR to its own buffer
-      BW_TRY(ln_bwd(st, lnq, d, dnq, xs(0), (const __bf16*)b.ln1_g, dxm, dy, nullptr, ln1part(0), (int)rq, c->ln_eps));
-      BW_TRY(ln_bwd(st, lnk, d, dnk, Rx, (const __bf16*)b.ln1_g, nullptr, dR, nullptr, ln1part(0) + (size_t)lnq * 2 * d, (int)rk, c->ln_eps));
+  auto fwd = [&](const StackFwd& p) -> int {
+    if (d == 32) bw_stack_fwd_32(p, st); else if (d == 64) bw_stack_fwd_64(p, st);
+    else if (d == 128) bw_stack_fwd_128(p, st); else bw_stack_fwd_256(p, st);
+    return launched("stack forward");
+  };
+  auto bwd = [&](const StackBwd& p) -> int {
+    if (d == 32) bw_stack_bwd_32(p, st); else if (d == 64) bw_stack_bwd_64(p, st);
+    else if (d == 128) bw_stack_bwd_128(p, st); else bw_stack_bwd_256(p, st);
+    return launched("stack backward");
+  };
+  // forward: [head of 0 (and its keys)], attention, [tail of l, head of l + 1], ...
+  for (int l = -1; l <= last; ++l) {
+    StackFwd p = {};
+    p.rows = (int)rq; p.f = f; p.act = c->act; p.eps = c->ln_eps;
+    if (l >= 0) {
+      const longer_block& b = blk(l);
+      BW_TRY(set_attn(0, l, o, 0, nullptr, nullptr));
+      p.wstream = stream_at(sg.fwd_tail(l)); p.segs = NT + 2 * NC;
+      p.x = xs(l); p.o = o; p.bo = bf(b.bo); p.ln2_g = bf(b.ln2_g); p.ln2_b = bf(b.ln2_b); p.b1 = bf(b.b1); p.b2 = bf(b.b2);
+      p.desc = qdesc; p.xmid = (float*)of(w.xmid, l); p.y = xs(l + 1); p.rec = (__bf16*)of(w.rec, l);
     } else {
-      if (s.dh == 16) {
-        set_attn_launch<16>(st, 1, t, dob, d, dqkv, 3 * d, nullptr, nullptr, stat);
-        set_attn_launch<16>(st, 2, t, dob, d, nullptr, 3 * d, dqkv + d, dqkv + 2 * d, stat);
-      } else {
-        set_attn_launch<32>(st, 1, t, dob, d, dqkv, 3 * d, nullptr, nullptr, stat);
-        set_attn_launch<32>(st, 2, t, dob, d, nullptr, 3 * d, dqkv + d, dqkv + 2 * d, stat);
-      }
-      BW_TRY(launched("attention backward"));
-      BW_TRY(gemm_rows_t(st, dqkv, 3 * d, wcat(l), d, rq, EPI_BF16, 0, dnq, nullptr));
-      BW_TRY(ln_bwd(st, lnq, d, dnq, xs(l), (const __bf16*)b.ln1_g, dxm, dy, nullptr, ln1part(l), (int)rq, c->ln_eps));
+      p.wstream = stream_at(sg.fwd_head(0)); p.x = xs(0);
+    }
+    if (l < last) {
+      const longer_block& b = blk(l + 1);
+      p.mats = l < 0 ? 1 : 3; p.segs += p.mats * NT;
+      p.ln1_g = bf(b.ln1_g); p.ln1_b = bf(b.ln1_b); p.bias[0] = bf(b.bq); p.bias[1] = bf(b.bk); p.bias[2] = bf(b.bv);
+      p.out = (__bf16*)of(w.qkv, l + 1); p.ldo = p.mats * d; p.rec1 = (__bf16*)of(w.rec, l + 1); p.rec1_size = r.size; p.rec1_xh = r.xh1;
+    }
+    BW_TRY(fwd(p));
+    if (l < 0) {
+      const longer_block& b = blk(0);
+      StackFwd k = {};
+      k.rows = (int)rk; k.f = f; k.eps = c->ln_eps; k.wstream = stream_at(sg.kv_f); k.segs = 2 * NT; k.x = Rx;
+      k.ln1_g = bf(b.ln1_g); k.ln1_b = bf(b.ln1_b); k.bias[0] = bf(b.bk); k.bias[1] = bf(b.bv);
+      k.mats = 2; k.out = kv; k.ldo = 2 * d; k.rec1 = krec; k.rec1_size = key_record(d); k.rec1_xh = 0;
+      BW_TRY(fwd(k));
     }
   }
-  // ---- parameter gradients of all layers: one launch, one for the sums of its partial results and the LayerNorms'
+
+  // ---- head and loss (Eq. 1-2), and the gradient of the stack's output
+  bw_head_kernel<<<B, 256, 0, st>>>(xs(s.layers), bf(wts->head_w), bf(wts->head_b), labels, B, s.n, s.m, d,
+                                    logits, loss, dy, grads + mg.head_w, grads + mg.head_b);
+  BW_TRY(launched("head"));
+
+  // ---- back: [head of the last], attention backward, [tail of l, head of l - 1], ..., [tail of 0 (and its keys)]
+  for (int l = last + 1; l >= 0; --l) {
+    StackBwd p = {};
+    p.rows = (int)rq; p.f = f; p.act = c->act; p.eps = c->ln_eps;
+    if (l <= last) {
+      // (the cross layer's keys are rows of their own; a self layer's dq, dk, dv lie side by side)
+      BW_TRY(set_attn(1, l, dqkv, l ? 3 * d : d, nullptr, nullptr));
+      BW_TRY(l ? set_attn(2, l, nullptr, 3 * d, dqkv + d, dqkv + 2 * d) : set_attn(2, l, nullptr, 2 * d, dkv, dkv + d));
+      p.mats = l ? 3 : 1; p.wstream = stream_at(sg.bwd_tail(l)); p.segs = p.mats * NT;
+      p.dqkv = dqkv; p.ldq = p.mats * d; p.x = xs(l); p.ln1_g = bf(blk(l).ln1_g); p.dxm_in = dxm;
+      p.rec1 = (__bf16*)of(w.rec, l); p.rec1_size = r.size; p.rec1_dqkv = r.qkv; p.dx = dy;
+    } else {
+      p.wstream = stream_at(sg.bwd_head(last)); p.dy = dy;
+    }
+    if (l > 0) {
+      const longer_block& b = blk(l - 1);
+      p.segs += 3 * NC + NT;
+      p.desc = qdesc; p.xmid = (const float*)of(w.xmid, l - 1); p.ln2_g = bf(b.ln2_g); p.ln2_b = bf(b.ln2_b); p.b1 = bf(b.b1);
+      p.dxm = dxm; p.dob = dob; p.rec = (__bf16*)of(w.rec, l - 1);
+    }
+    BW_TRY(bwd(p));
+    if (l == 0) {
+      StackBwd k = {};
+      k.rows = (int)rk; k.f = f; k.eps = c->ln_eps; k.wstream = stream_at(sg.kv_b); k.segs = 2 * NT; k.mats = 2;
+      k.dqkv = dkv; k.ldq = 2 * d; k.x = Rx; k.ln1_g = bf(blk(0).ln1_g); k.rec1 = krec; k.rec1_size = key_record(d);
+      k.rec1_dqkv = d / 16; k.dx = dR;
+      BW_TRY(bwd(k));
+    }
+  }
+  // ---- parameter gradients of all layers: one launch, one for the sums of its partial results, the LayerNorms' from those
   WgradBatch wg = stack_wgrads(s, w, ws, grads, mg.cross, mg.self0, mg.per_main);
   BW_TRY(launch(wg, (float*)(ws + w.part), st));
   ReduceBatch rb;
   rb.add(wg);
-  if (s.layers > 1) {
-    rb.add_ln(ln1part(1), (int)lnq, d, grads + mg.self0 + gl.ln1_g, s.layers - 1, (long long)ln_stride, (long long)mg.per_main);
-    rb.add_ln(ln2part(1), (int)lnq, d, grads + mg.self0 + gl.ln2_g, s.layers - 1, (long long)ln_stride, (long long)mg.per_main);
-  }
-  rb.add_ln(ln1part(0), (int)(lnq + lnk), d, grads + mg.cross + gl.ln1_g);
-  rb.add_ln(ln2part(0), (int)lnq, d, grads + mg.cross + gl.ln2_g);
   BW_TRY(launch(rb, st));
+  BW_TRY(norm_grads(d, f, wts->cross, 1, grads + mg.cross, mg.per_main, st));
+  if (s.layers > 1) BW_TRY(norm_grads(d, f, wts->self, s.layers - 1, grads + mg.self0, mg.per_main, st));
   // ---- gradients of the stack's inputs: global tokens (query rows and key rows), merged tokens (key
   // rows, plus the query slots that hold them)
   bw_split_grad_kernel<<<flat_grid(rk * d / 4), 256, 0, st>>>(geo, d, dy, dR, dG, dM);

@@ -28,6 +28,19 @@ __device__ __forceinline__ bool rows_any_valid(const RowsValid& v, int r0, int r
   return false;
 }
 
+// Phi(v) = (1 + erf(v / sqrt 2)) / 2 and exp(-v^2 / 2) from one exponential: for z >= 0,
+// erf(z) = 1 - (a1 t + a2 t^2 + a3 t^3 + a4 t^4 + a5 t^5) exp(-z^2), t = 1 / (1 + p z), absolute error
+// below 1.5e-7 (the classic five-term approximation; odd extension for z < 0).
+__device__ __forceinline__ void gauss_cdf(float v, float* cdf, float* ex) {
+  const float z = fabsf(v) * 0.70710678118654752f;
+  const float e = __expf(-z * z);
+  const float t = __frcp_rn(1.f + 0.3275911f * z);
+  const float poly = ((((1.061405429f * t - 1.453152027f) * t + 1.421413741f) * t - 0.284496736f) * t + 0.254829592f) * t;
+  const float half_erfc = 0.5f * poly * e;                 // (1 - erf(|z|)) / 2
+  *cdf = v >= 0.f ? 1.f - half_erfc : half_erfc;
+  *ex = e;
+}
+
 // The activation and its derivative at once, for the launch that rounds both to bf16 right away.
 // GELU: Phi(v) - 1/2 as v times an even polynomial of degree 8 (minimax fit on [-3.5, 3.5] that reaches 1/2
 // at the interval's end, clamped to [0, 1] beyond it; absolute error below 1.3e-3, under the bf16
