@@ -132,17 +132,30 @@ struct StackStream {
   static constexpr int NT = D / 32, NG = D / 16, SEGV = NG * 64, PSEG = D >= 256 ? 1 : D >= 128 ? 2 : 4;
   typedef WStream<SEGV, PSEG, 3, false, 64 * NW> Stream;
   Stream ws;
-  __device__ __forceinline__ void product(f32x16& acc, const bf16x8 (&b)[NG]) {
+  // With a wave per SIMD every product would wait out the LDS latency of its own fragment (about four times its length), and
+  // scheduling hints are not followed: six reads are kept in flight by hand, the order pinned.
+  template <typename F>
+  __device__ __forceinline__ void fragments(F&& use) {
+    constexpr int AH = NG < 6 ? NG : 6;
+    bf16x8 w[AH];
 #pragma unroll
-    for (int s = 0; s < NG; ++s) acc = ET<__bf16>::mma(ws.template frag<bf16x8>(s), b[s], acc);
+    for (int i = 0; i < AH; ++i) w[i] = ws.template frag<bf16x8>(i);
+#pragma unroll
+    for (int i = 0; i < NG; ++i) {
+      __builtin_amdgcn_sched_barrier(0);
+      use(i, w[i % AH]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (i + AH < NG) w[i % AH] = ws.template frag<bf16x8>(i + AH);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  __device__ __forceinline__ void product(f32x16& acc, const bf16x8 (&b)[NG]) {
+    fragments([&](int s, const bf16x8 w) { acc = ET<__bf16>::mma(w, b[s], acc); });
     ws.advance();
     settle(acc);
   }
   __device__ __forceinline__ void spread(f32x16 (&acc)[NT], const bf16x8 (&b)[2]) {
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-      for (int g = 0; g < 2; ++g) acc[t] = ET<__bf16>::mma(ws.template frag<bf16x8>(2 * t + g), b[g], acc[t]);
+    fragments([&](int i, const bf16x8 w) { acc[i / 2] = ET<__bf16>::mma(w, b[i % 2], acc[i / 2]); });
     ws.advance();
   }
 };
