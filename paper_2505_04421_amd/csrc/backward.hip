@@ -1743,7 +1743,7 @@ struct StackWs {
   size_t qkv, stat, xmid, rec, per_layer; // every layer's intermediates are kept (per_layer bytes apart): the reduced stack is
                                           // small, only the merge is recomputed
   size_t kv, krec, o, dy, dxm, dob, dqkv, dkv, dR, part;
-  size_t rqp, rkp;                        // rows in whole workgroups of the tile kernels
+  size_t rqp, rkp;                        // rows in whole tiles
   size_t total;
 };
 // records of the cross layer's key rows: normalised rows, gradients of K and V
@@ -1753,7 +1753,7 @@ static int key_record(int d) { return 3 * d / 16; }
 struct StackStreams {
   int NT, NC, layers, kv_f, kv_b, total;
   StackStreams(int d, int f, int n) : NT(d / 32), NC(f / 32), layers(n) {
-    kv_f = bwd_tail(0) + NT; kv_b = kv_f + 2 * NT; total = kv_b + 2 * NT + 4;      // (streams are read in whole panels)
+    kv_f = bwd_tail(0) + NT; kv_b = kv_f + 2 * NT; total = kv_b + 2 * NT;
   }
   int fwd_head(int l) const { return l == 0 ? 0 : fwd_tail(l) - 3 * NT; }
   int fwd_tail(int l) const { return NT + l * (NT + 2 * NC + 3 * NT); }
@@ -1792,9 +1792,9 @@ static StackWs stack_ws(const StackDims& s, size_t fwd_bytes) {
   StackWs w;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += up256(bytes); return at; };
-  const size_t rq = s.rq, rk = s.rk, d = s.d, f = s.f, whole = 32 * kStackWaves;
-  w.rqp = (rq + whole - 1) / whole * whole;
-  w.rkp = (rk + whole - 1) / whole * whole;
+  const size_t rq = s.rq, rk = s.rk, d = s.d, f = s.f;
+  w.rqp = (rq + 31) / 32 * 32;
+  w.rkp = (rk + 31) / 32 * 32;
   w.fwd_ws = take(fwd_bytes);
   w.Mb = take((size_t)s.B * s.T * d * 2);
   w.dM = take((size_t)s.B * s.T * d * 4);
@@ -1946,7 +1946,7 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
     if (l >= 0) {
       const longer_block& b = blk(l);
       BW_TRY(set_attn(0, l, o, 0, nullptr, nullptr));
-      p.wstream = stream_at(sg.fwd_tail(l)); p.segs = NT + 2 * NC;
+      p.wstream = stream_at(sg.fwd_tail(l));
       p.x = xs(l); p.o = o; p.bo = bf(b.bo); p.ln2_g = bf(b.ln2_g); p.ln2_b = bf(b.ln2_b); p.b1 = bf(b.b1); p.b2 = bf(b.b2);
       p.desc = qdesc; p.xmid = (float*)of(w.xmid, l); p.y = xs(l + 1); p.rec = (__bf16*)of(w.rec, l);
     } else {
@@ -1954,7 +1954,7 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
     }
     if (l < last) {
       const longer_block& b = blk(l + 1);
-      p.mats = l < 0 ? 1 : 3; p.segs += p.mats * NT;
+      p.mats = l < 0 ? 1 : 3;
       p.ln1_g = bf(b.ln1_g); p.ln1_b = bf(b.ln1_b); p.bias[0] = bf(b.bq); p.bias[1] = bf(b.bk); p.bias[2] = bf(b.bv);
       p.out = (__bf16*)of(w.qkv, l + 1); p.ldo = p.mats * d; p.rec1 = (__bf16*)of(w.rec, l + 1); p.rec1_size = r.size; p.rec1_xh = r.xh1;
     }
@@ -1962,7 +1962,7 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
     if (l < 0) {
       const longer_block& b = blk(0);
       StackFwd k = {};
-      k.rows = (int)rk; k.f = f; k.eps = c->ln_eps; k.wstream = stream_at(sg.kv_f); k.segs = 2 * NT; k.x = Rx;
+      k.rows = (int)rk; k.f = f; k.eps = c->ln_eps; k.wstream = stream_at(sg.kv_f); k.x = Rx;
       k.ln1_g = bf(b.ln1_g); k.ln1_b = bf(b.ln1_b); k.bias[0] = bf(b.bk); k.bias[1] = bf(b.bv);
       k.mats = 2; k.out = kv; k.ldo = 2 * d; k.rec1 = krec; k.rec1_size = key_record(d); k.rec1_xh = 0;
       BW_TRY(fwd(k));
@@ -1982,7 +1982,7 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
       // (the cross layer's keys are rows of their own; a self layer's dq, dk, dv lie side by side)
       BW_TRY(set_attn(1, l, dqkv, l ? 3 * d : d, nullptr, nullptr));
       BW_TRY(l ? set_attn(2, l, nullptr, 3 * d, dqkv + d, dqkv + 2 * d) : set_attn(2, l, nullptr, 2 * d, dkv, dkv + d));
-      p.mats = l ? 3 : 1; p.wstream = stream_at(sg.bwd_tail(l)); p.segs = p.mats * NT;
+      p.mats = l ? 3 : 1; p.wstream = stream_at(sg.bwd_tail(l));
       p.dqkv = dqkv; p.ldq = p.mats * d; p.x = xs(l); p.ln1_g = bf(blk(l).ln1_g); p.dxm_in = dxm;
       p.rec1 = (__bf16*)of(w.rec, l); p.rec1_size = r.size; p.rec1_dqkv = r.qkv; p.dx = dy;
     } else {
@@ -1990,14 +1990,13 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
     }
     if (l > 0) {
       const longer_block& b = blk(l - 1);
-      p.segs += 3 * NC + NT;
       p.desc = qdesc; p.xmid = (const float*)of(w.xmid, l - 1); p.ln2_g = bf(b.ln2_g); p.ln2_b = bf(b.ln2_b); p.b1 = bf(b.b1);
       p.dxm = dxm; p.dob = dob; p.rec = (__bf16*)of(w.rec, l - 1);
     }
     BW_TRY(bwd(p));
     if (l == 0) {
       StackBwd k = {};
-      k.rows = (int)rk; k.f = f; k.eps = c->ln_eps; k.wstream = stream_at(sg.kv_b); k.segs = 2 * NT; k.mats = 2;
+      k.rows = (int)rk; k.f = f; k.eps = c->ln_eps; k.wstream = stream_at(sg.kv_b); k.mats = 2;
       k.dqkv = dkv; k.ldq = 2 * d; k.x = Rx; k.ln1_g = bf(blk(0).ln1_g); k.rec1 = krec; k.rec1_size = key_record(d);
       k.rec1_dqkv = d / 16; k.dx = dR;
       BW_TRY(bwd(k));
