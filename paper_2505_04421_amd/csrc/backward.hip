@@ -41,6 +41,8 @@ namespace longer {
 int api_error(int code, const char* fmt, ...);   // longer_api.hip
 int inner_chain_f32(const longer_config* cfg, const longer_block* inner, int layers, const void* H, const int32_t* lens,
                     int B, int L, float* Z_out, void* ws, size_t ws_bytes, void* stream);   // longer_api.hip
+int merge_keep_f32(const longer_config* cfg, const longer_block* inner, const void* H, const int32_t* lens, int B, int L, void* M_out,
+                   float* keep, size_t stride, void* ws, size_t ws_bytes, void* stream);   // longer_api.hip
 
 namespace bw {
 
@@ -1577,7 +1579,7 @@ static unsigned flat_grid(size_t n) {
 #define BW_TRY(x) do { int rc_ = (x); if (rc_) return rc_; } while (0)
 
 static int run_tiled(const longer_config* c, const longer_block* inner, const void* H, const int32_t* lens, int B, int L,
-                     const float* dM, float* dH, float* grads, char* ws, hipStream_t st, const Dims& s) {
+                     const float* dM, float* dH, float* grads, char* ws, hipStream_t st, const Dims& s, bool inputs_kept) {
   const int d = s.d, f = s.f;
   const Workspace w = merge_workspace(c, s, B, L);
   const GradLayout gl = grad_layout(d, f);
@@ -1600,7 +1602,8 @@ static int run_tiled(const longer_config* c, const longer_block* inner, const vo
   BW_TRY(pk.flush());
   // block inputs, by the fused forward kernel (its fp32 residual stream after l blocks is block l's input)
   auto xin = [&](int l) { return (float*)(ws + w.xin) + (size_t)(l - 1) * s.padded * d; };
-  for (int l = 1; l < s.layers; ++l) BW_TRY(inner_chain_f32(c, inner, l, H, lens, B, L, xin(l), ws + w.fwd, w.fwd_bytes, st));
+  // unless the forward merge of the same call left them there
+  for (int l = 1; l < s.layers && !inputs_kept; ++l) BW_TRY(inner_chain_f32(c, inner, l, H, lens, B, L, xin(l), ws + w.fwd, w.fwd_bytes, st));
 
   for (int l = s.layers - 1; l >= 0; --l) {
     const longer_block& b = inner[l];
@@ -1630,8 +1633,8 @@ static int run_tiled(const longer_config* c, const longer_block* inner, const vo
 }
 
 static int run(const longer_config* c, const longer_block* inner, const void* H, const int32_t* lens, int B, int L,
-               const float* dM, float* dH, float* grads, char* ws, hipStream_t st, const Dims& s) {
-  if (s.tiled) return run_tiled(c, inner, H, lens, B, L, dM, dH, grads, ws, st, s);
+               const float* dM, float* dH, float* grads, char* ws, hipStream_t st, const Dims& s, bool inputs_kept = false) {
+  if (s.tiled) return run_tiled(c, inner, H, lens, B, L, dM, dH, grads, ws, st, s, inputs_kept);
   const int d = s.d, f = s.f;
   const size_t nt = s.ntok;
   const Workspace w = merge_workspace(c, s, B, L);
@@ -1859,7 +1862,7 @@ static ModelGrads model_grads(const Dims& mi, const StackDims& s, bool learn) {
 
 static int run_model(const longer_config* c, const longer_weights* wts, const void* H, const void* G, const int32_t* lens,
                      int B, int L, const float* labels, float* loss, float* logits, float* dH, float* dG, float* grads,
-                     char* ws, size_t fwd_bytes, hipStream_t st, const Dims& mi, const StackDims& s) {
+                     char* ws, size_t fwd_bytes, hipStream_t st, const Dims& mi, const StackDims& s, float* block_inputs) {
   const int d = s.d, f = s.f;
   const size_t rq = s.rq, rk = s.rk;
   const StackWs w = stack_ws(s, fwd_bytes);
@@ -1887,7 +1890,8 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
 
   // ---- forward from the inputs: merged tokens (the fused forward kernel; the merge's intermediates are
   // recomputed later by its own backward pass), then the stack, keeping every layer's intermediates
-  int rc = longer_token_merge(c, wts->inner, H, lens, B, L, Mb, ws + w.fwd_ws, fwd_bytes, st);
+  int rc = block_inputs ? merge_keep_f32(c, wts->inner, H, lens, B, L, Mb, block_inputs, mi.padded * mi.d, ws + w.fwd_ws, fwd_bytes, st)
+                        : longer_token_merge(c, wts->inner, H, lens, B, L, Mb, ws + w.fwd_ws, fwd_bytes, st);
   if (rc) return rc;
   bw_desc_kernel<<<flat_grid(rq + rk), 256, 0, st>>>(geo, qdesc, kdesc);
   bw_build_rows_kernel<<<flat_grid((rq + rk) * d / 4), 256, 0, st>>>(geo, d, (const __bf16*)G, Mb, (const __bf16*)c->q_learn, qdesc, kdesc, xs(0), Rx);
@@ -2148,11 +2152,14 @@ int longer_forward_backward(const longer_config* cfg, const longer_weights* w, c
   const size_t need = stack_bytes + bw::merge_workspace(cfg, mi, B, L).total;
   if (ws_bytes < need) return api_error(LONGER_ERR_WS, "workspace too small: %zu < %zu bytes", ws_bytes, need);
   hipStream_t st = (hipStream_t)stream;
-  rc = bw::run_model(cfg, w, H, G, lens, B, L, labels, loss_out, logits_out, dH_out, dG_out, grads_out, (char*)ws, fwd, st, mi, s);
+  // with several blocks the forward merge writes the later ones' input rows where the merge's backward pass expects them
+  const bool keep = mi.tiled && mi.layers > 1;
+  float* block_inputs = keep ? (float*)((char*)ws + stack_bytes + bw::merge_workspace(cfg, mi, B, L).xin) : nullptr;
+  rc = bw::run_model(cfg, w, H, G, lens, B, L, labels, loss_out, logits_out, dH_out, dG_out, grads_out, (char*)ws, fwd, st, mi, s, block_inputs);
   if (rc) return rc;
   // the merge's gradients: dM was left in the stack's workspace; the InnerTrans blocks come first in grads_out
   const float* dM = (const float*)((char*)ws + bw::stack_ws(s, fwd).dM);
-  return bw::run(cfg, w->inner, H, lens, B, L, dM, dH_out, grads_out, (char*)ws + stack_bytes, st, mi);
+  return bw::run(cfg, w->inner, H, lens, B, L, dM, dH_out, grads_out, (char*)ws + stack_bytes, st, mi, keep);
 }
 
 size_t longer_input_backward_workspace_bytes(const longer_config* cfg, int B, int L, int d_e) {

@@ -20,7 +20,9 @@
 //                over rows built from item embedding + positional embedding and the
 //                time-difference features;
 //   MODE_MERGE_IN  MODE_INPUT and MODE_MERGE in one pass: the MLP's result stays in the
-//                registers as the rows the InnerTrans blocks start from.
+//                registers as the rows the InnerTrans blocks start from;
+//   MODE_MERGE_KEEP  MODE_MERGE that also writes every later block's input rows (a training step's merge: its
+//                backward pass starts each block from them).
 //
 // Every mode runs the same register-resident chain (see device.h); they differ in where
 // rows come from, which attention sources exist and what is written.
@@ -62,7 +64,7 @@ struct BlockParams {
   int kt_per_user;
   int KG;               // number of global keys in front of the sequence keys
   int key_self;         // 1: sequence keys are the k recent slots, 0: all T merged tokens
-  // MODE_ATTN / MODE_SCORE outputs
+  // MODE_ATTN / MODE_SCORE outputs; MODE_MERGE_KEEP: fp32 [block - 1][B T K][D], X_ustride floats from block to block
   void* X_out; int X_f32; long long X_ustride;
   float* logits; const float* head;   // head: fp32 [m*D] weights then the bias
   // MODE_INPUT / MODE_MERGE_IN: item embeddings [B, L, de], positional embedding [L, de],
@@ -435,7 +437,7 @@ __global__ void __launch_bounds__(64 * NW, (NW == kWaves && D <= 128 && TT == 1 
   constexpr int SEGV = NG * 64;
   constexpr int HPT = 32 / DH;        // heads per 32-feature tile
   constexpr int GPH = DH / E::GF;     // operand groups per head
-  constexpr bool MERGE = MODE == MODE_MERGE || MODE == MODE_MERGE_IN;
+  constexpr bool MERGE = MODE == MODE_MERGE || MODE == MODE_MERGE_IN || MODE == MODE_MERGE_KEEP;
   constexpr bool FUSED = (MERGE || MODE == MODE_SCORE);
   constexpr bool EXT = (MODE == MODE_ATTN || MODE == MODE_SCORE);
   constexpr bool STACK = MODE == MODE_STACK;
@@ -650,6 +652,10 @@ __global__ void __launch_bounds__(64 * NW, (NW == kWaves && D <= 128 && TT == 1 
     for (int i = 0; i < SEGV / kThreads; ++i) vecl[tid + kThreads * i] = ws.cur()[tid + kThreads * i];
     __syncthreads();
     ws.advance();
+    // (a store inside the loop can only make the stream's waits longer: they count what is outstanding)
+    if constexpr (MODE == MODE_MERGE_KEEP) {
+      if (layer > 0 && inrange[0]) store_rows<T, NT>(resid[0], reinterpret_cast<float*>(p.X_out) + (size_t)(layer - 1) * p.X_ustride, 1, out_off[0] * D, valid[0], hi);
+    }
     const float* vec = reinterpret_cast<const float*>(vecl);
     const VecLayout vl{D, p.FF};
     grp xn[TT][NG];
@@ -1225,6 +1231,19 @@ static int launch_stack_mode(const BlockParams& p, dim3 grid, hipStream_t stream
   }
 }
 
+// (training: bf16 up to width 128, what the block kernel of the backward pass covers)
+template <typename T, int D, int DH>
+static int launch_merge_keep(int win, const BlockParams& p, dim3 grid, hipStream_t stream) {
+  if constexpr (sizeof(T) == 2 && D <= 128) {
+    if (win == 4) LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE_KEEP, 4);
+    else if (win == 8) LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE_KEEP, 8);
+    else LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE_KEEP, 16);
+    return 0;
+  } else {
+    return -1;
+  }
+}
+
 #define LONGER_INSTANTIATE(T, D, DH)                                                                  \
   template <>                                                                                         \
   int launch_block<T, D, DH>(int mode, int tt, int win, const BlockParams& p, dim3 grid, hipStream_t stream) { \
@@ -1249,6 +1268,7 @@ static int launch_stack_mode(const BlockParams& p, dim3 grid, hipStream_t stream
         else if (win == 8) LONGER_LAUNCH(T, D, DH, 1, MODE_SCORE, 8);                                 \
         else LONGER_LAUNCH(T, D, DH, 1, MODE_SCORE, 16);                                              \
         break;                                                                                        \
+      case MODE_MERGE_KEEP: if (launch_merge_keep<T, D, DH>(win, p, grid, stream)) return -1; break;  \
       default: return -1;                                                                             \
     }                                                                                                 \
     return hipGetLastError() == hipSuccess ? 0 : -3;                                                  \

@@ -563,8 +563,9 @@ static int check_input(const longer_config* cfg, const longer_input_weights* w, 
 // followed directly by them, and the rows come from the raw inputs instead of H
 static int run_merge(const longer_config* c, const Shape& s, const char* packed, const void* H, const int32_t* lens,
                      int B, int L, void* M_out, int M_f32, void* Z_out, int Z_f32, hipStream_t st,
-                     const MergeInput* in = nullptr) {
+                     const MergeInput* in = nullptr, float* keep = nullptr, size_t keep_stride = 0) {
   BlockParams p = base_params(c, s, lens, B, L, s.DHi);
+  p.X_out = keep; p.X_ustride = (long long)keep_stride;
   p.wbase = packed; p.n_layers = c->inner_layers;
   p.H = H; p.M_out = M_out; p.M_f32 = M_f32; p.Z_out = Z_out; p.Z_f32 = Z_f32;
   if (in) {
@@ -577,7 +578,7 @@ static int run_merge(const longer_config* c, const Shape& s, const char* packed,
   if (slots + 32LL * tt * kWaves >= (1LL << 31)) return fail(LONGER_ERR_ARG, "B*ceil(L/K)*K = %lld token slots: at most 2^31 per call", slots);
   const int grid = cdiv(slots, 32LL * tt * kWaves);
   StageScope scope(ST_MERGE, st);
-  int rc = s.inner_fn(in ? MODE_MERGE_IN : MODE_MERGE, tt, win, p, dim3(grid), st);
+  int rc = s.inner_fn(in ? MODE_MERGE_IN : keep ? MODE_MERGE_KEEP : MODE_MERGE, tt, win, p, dim3(grid), st);
   return rc ? fail(LONGER_ERR_HIP, "merge kernel launch failed") : 0;
 }
 
@@ -768,7 +769,8 @@ int longer_pack_weights(const longer_config* cfg, const longer_weights* w, const
 }
 
 static int merge_entry(const longer_config* cfg, const longer_block* inner, const void* H, const int32_t* lens,
-                       int B, int L, void* M_out, void* Z_out, void* ws, size_t ws_bytes, void* stream, int z_f32 = 0) {
+                       int B, int L, void* M_out, void* Z_out, void* ws, size_t ws_bytes, void* stream, int z_f32 = 0,
+                       float* keep = nullptr, size_t keep_stride = 0) {
   Shape s;
   int rc = check_cfg(cfg, &s, true, false);
   if (rc) return rc;
@@ -785,7 +787,7 @@ static int merge_entry(const longer_config* cfg, const longer_block* inner, cons
   if ((rc = pk_batch.flush())) return rc;
   // a concat merge is the un-pooled output [B, T, K, d / K] read as [B, T, d]
   if (cfg->merge == LONGER_MERGE_CONCAT && M_out) { Z_out = M_out; M_out = nullptr; }
-  return run_merge(cfg, si, w8 + l.packed, H, lens, B, L, M_out, 0, Z_out, z_f32, st);
+  return run_merge(cfg, si, w8 + l.packed, H, lens, B, L, M_out, 0, Z_out, z_f32, st, nullptr, keep, keep_stride);
 }
 
 int longer_inner_transformer(const longer_config* cfg, const longer_block* inner, const void* H, const int32_t* lens,
@@ -1160,5 +1162,12 @@ __attribute__((visibility("hidden"))) int inner_chain_f32(const longer_config* c
   longer_config c = *cfg;
   c.inner_layers = layers;
   return merge_entry(&c, inner, H, lens, B, L, nullptr, Z_out, ws, ws_bytes, stream, 1);
+}
+// The token merge of a training step: merged tokens, and the input rows of every block after the first, fp32
+// [inner_layers - 1][B, T, K, w] with `stride` floats from block to block (rows of padded tokens zero or not written).
+__attribute__((visibility("hidden"))) int merge_keep_f32(const longer_config* cfg, const longer_block* inner, const void* H,
+                                                         const int32_t* lens, int B, int L, void* M_out, float* keep,
+                                                         size_t stride, void* ws, size_t ws_bytes, void* stream) {
+  return merge_entry(cfg, inner, H, lens, B, L, M_out, nullptr, ws, ws_bytes, stream, 0, keep, stride);
 }
 }  // namespace longer
