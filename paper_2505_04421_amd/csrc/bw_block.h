@@ -182,7 +182,7 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
     asm("" : "+s"(q));
     return (gbf16x8*)(q + (g & 1 ? lane1 : lane0));
   };
-  auto put_rec = [&](int base, int g, bf16x8 v) { *at_rec(base, g) = v; };
+  auto put_rec = [&](int base, int g, bf16x8 v) { __builtin_nontemporal_store(v, at_rec(base, g)); };
   auto get_rec = [&](int base, int g) -> bf16x8 { return *at_rec(base, g); };
   auto at_dy = [&](const float* base, int q) -> gf32x4* {             // 1 KiB per 8 features: 4 per lane
     gchar* b = (gchar*)(base + ((size_t)tile * (D / 8) + q) * 256);
@@ -226,17 +226,33 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
 
   // ---- vectors to LDS, weight stream
   const int oG1 = 0, oB1n = D, oBq = 2 * D, oBv = 3 * D, oBo = 4 * D, oG2 = 5 * D, oB2n = 6 * D, oBf = 7 * D;
-  for (int i = tid; i < D; i += 64 * kBlkWaves) {
-    vec[oG1 + i] = (float)p.ln1_g[i]; vec[oB1n + i] = (float)p.ln1_b[i];
-    vec[oBq + i] = (float)p.bq[i];    vec[oBv + i] = (float)p.bv[i];   vec[oBo + i] = (float)p.bo[i];
-    vec[oG2 + i] = (float)p.ln2_g[i]; vec[oB2n + i] = (float)p.ln2_b[i];
-  }
-  for (int i = tid; i < p.f; i += 64 * kBlkWaves) vec[oBf + i] = (float)p.b1[i];
-
+  // Everything that is read before the first product is requested at once (a trip to memory takes several thousand
+  // cycles under this kernel's stores): rows, vectors into registers, the stream's first panels.
   f32x16 x[NT];
   load_rows<__bf16, NT>(x, p.x, p.x_f32, (p.x_f32 ? (long long)tk.slot : tk.row) * D, valid, hi);
+  constexpr int VB = 2048 / (64 * kBlkWaves);
+  __bf16 vd[7], vf[VB];
+  {
+    const int i = tid < D ? tid : 0;
+    vd[0] = p.ln1_g[i]; vd[1] = p.ln1_b[i]; vd[2] = p.bq[i]; vd[3] = p.bv[i]; vd[4] = p.bo[i]; vd[5] = p.ln2_g[i]; vd[6] = p.ln2_b[i];
+#pragma unroll
+    for (int k = 0; k < VB; ++k) {
+      const int c = tid + 64 * kBlkWaves * k;
+      vf[k] = p.b1[c < p.f ? c : 0];
+    }
+  }
   WStream<SEGV, PSEG, NB, false, 64 * kBlkWaves> ws;
   ws.init(ring, p.wstream, bw_block_segs(D, p.f));
+  if (tid < D) {
+#pragma unroll
+    for (int k = 0; k < 7; ++k) vec[k * D + tid] = (float)vd[k];
+  }
+#pragma unroll
+  for (int k = 0; k < VB; ++k) {
+    const int c = tid + 64 * kBlkWaves * k;
+    if (c < p.f) vec[oBf + c] = (float)vf[k];
+  }
+  __syncthreads();
   auto product = [&](f32x16& acc, const bf16x8 (&b)[NG]) {      // acc += (this segment's 32 output features) b
 #pragma unroll
     for (int s = 0; s < NG; ++s) acc = E::mma(ws.template frag<bf16x8>(s), b[s], acc);
