@@ -113,11 +113,6 @@ __device__ __forceinline__ void place_window(const float (&x)[W], const uint32_t
   }
 }
 
-// A matrix product's result may be read by a vector instruction 11 wait states after it at the earliest.  The
-// compiler keeps that distance along the longest way between the two, and the weight stream's advance() has a short
-// one (no new panel): with nothing in between, the first eight features of a tile were read too early.
-__device__ __forceinline__ void settle(f32x16& acc) { asm volatile("s_nop 10" : "+v"(acc)); }
-
 template <int NT>
 __device__ __forceinline__ void row_stats(const f32x16 (&x)[NT], float eps, float& mean, float& rstd) {
   float s = 0.f, v = 0.f;

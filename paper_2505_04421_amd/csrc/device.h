@@ -103,6 +103,11 @@ __host__ __device__ __forceinline__ constexpr int tile_row(int r, int hi) {
   return 8 * (r / 4) + 4 * hi + (r % 4);
 }
 
+// A matrix product's result may be read by a vector instruction 11 wait states after it at the earliest.  The
+// compiler keeps that distance along the longest way between the two, and the weight stream's advance() has a short
+// one (no new panel): with nothing in between, the first eight features of a tile were read too early.
+__device__ __forceinline__ void settle(f32x16& acc) { asm volatile("s_nop 10" : "+v"(acc)); }
+
 // Lane l and lane l ^ 32 hold the two feature halves of one token.  Their values are
 // combined with the cross-half register swap (v_permlane32_swap: the upper 32 lanes of one
 // operand trade places with the lower 32 lanes of the other), no LDS round trip: with both

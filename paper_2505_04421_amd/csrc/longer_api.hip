@@ -2,6 +2,7 @@
 // layout, parameter packing and the launch sequence of each entry point.
 #include "../../include/longer.h"
 #include "pair_kernel.h"
+#include "quad_kernel.h"
 
 #include <cmath>
 #include <cstdarg>
@@ -30,19 +31,39 @@ template <> int launch_pair<128, 32>(int, int, const BlockParams&, dim3, hipStre
 template <> int launch_pair<256, 16>(int, int, const BlockParams&, dim3, hipStream_t);
 template <> int launch_pair<256, 32>(int, int, const BlockParams&, dim3, hipStream_t);
 
+template <> int launch_quad<64, 16>(int, int, bool, const BlockParams&, dim3, hipStream_t);
+template <> int launch_quad<64, 32>(int, int, bool, const BlockParams&, dim3, hipStream_t);
+template <> int launch_quad<128, 16>(int, int, bool, const BlockParams&, dim3, hipStream_t);
+template <> int launch_quad<128, 32>(int, int, bool, const BlockParams&, dim3, hipStream_t);
+template <> int launch_quad<256, 16>(int, int, bool, const BlockParams&, dim3, hipStream_t);
+template <> int launch_quad<256, 32>(int, int, bool, const BlockParams&, dim3, hipStream_t);
+
+typedef int (*quad_fn)(int, int, bool, const BlockParams&, dim3, hipStream_t);
 typedef int (*launch_fn)(int, int, int, const BlockParams&, dim3, hipStream_t);
 typedef int (*pair_fn)(int, int, const BlockParams&, dim3, hipStream_t);
 
 // The kernels that give a tile to a pair of waves (pair_kernel.h): bf16, d = 128 / 256.  The
 // environment variable LONGER_DISABLE_PAIR_KERNELS=1 (read once) keeps every launch on the
 // one-wave-per-tile kernels: a measurement aid for comparing the two.
-static pair_fn find_pair(int dtype, int D, int DH) {
+static bool one_wave_only() {
   static const bool off = [] { const char* e = getenv("LONGER_DISABLE_PAIR_KERNELS"); return e && e[0] == '1'; }();
-  if (off || dtype != LONGER_BF16) return nullptr;
+  return off;
+}
+static pair_fn find_pair(int dtype, int D, int DH) {
+  if (one_wave_only() || dtype != LONGER_BF16) return nullptr;
   if (D == 128 && DH == 16) return &launch_pair<128, 16>;
   if (D == 128 && DH == 32) return &launch_pair<128, 32>;
   if (D == 256 && DH == 16) return &launch_pair<256, 16>;
   if (D == 256 && DH == 32) return &launch_pair<256, 32>;
+  return nullptr;
+}
+
+// the kernels that give a tile to four waves (quad_kernel.h), for launches with few tiles: bf16, d = 64 / 128 / 256
+static quad_fn find_quad(int dtype, int D, int DH) {
+  if (one_wave_only() || dtype != LONGER_BF16) return nullptr;
+  if (D == 64) return DH == 16 ? &launch_quad<64, 16> : DH == 32 ? &launch_quad<64, 32> : nullptr;
+  if (D == 128) return DH == 16 ? &launch_quad<128, 16> : DH == 32 ? &launch_quad<128, 32> : nullptr;
+  if (D == 256) return DH == 16 ? &launch_quad<256, 16> : DH == 32 ? &launch_quad<256, 32> : nullptr;
   return nullptr;
 }
 
@@ -309,6 +330,7 @@ struct Shape {
   size_t seg;         // bytes of one stream segment
   launch_fn main_fn, inner_fn;
   pair_fn pair;       // the main stack's two-wave kernels, or NULL
+  quad_fn quad;       // its four-wave kernels, or NULL
 };
 
 static int check_cfg(const longer_config* c, Shape* s, bool need_inner, bool need_main) {
@@ -334,7 +356,7 @@ static int check_cfg(const longer_config* c, Shape* s, bool need_inner, bool nee
   s->seg = packed_seg_bytes(s->D, s->es);
   if ((size_t)(9 * s->D + s->FF) * 4 > s->seg) return fail(LONGER_ERR_ARG, "ffn_mult=%d too large for d=%d", c->ffn_mult, c->d);
   if (ffn_skewed(s->es, s->D) && s->FF < 64) return fail(LONGER_ERR_ARG, "ffn_mult * d = %d: the bf16 FFN needs a hidden width of at least 64", s->FF);
-  s->main_fn = s->inner_fn = nullptr; s->pair = nullptr; s->DH = s->DHi = 0;
+  s->main_fn = s->inner_fn = nullptr; s->pair = nullptr; s->quad = nullptr; s->DH = s->DHi = 0;
   s->Di = c->d;
   if (c->merge == LONGER_MERGE_CONCAT) {
     if (c->d % c->K || (c->d / c->K) % 32)
@@ -347,6 +369,7 @@ static int check_cfg(const longer_config* c, Shape* s, bool need_inner, bool nee
     s->main_fn = find_launch(c->dtype, c->d, s->DH);
     if (!s->main_fn) return fail(LONGER_ERR_ARG, "unsupported shape: dtype=%d d=%d head width=%d", c->dtype, c->d, s->DH);
     s->pair = find_pair(c->dtype, c->d, s->DH);
+    s->quad = find_quad(c->dtype, c->d, s->DH);
   }
   if (need_inner) {
     if (c->inner_layers < 1) return fail(LONGER_ERR_ARG, "inner_layers=%d", c->inner_layers);
@@ -593,6 +616,15 @@ struct AttnIO {
   float* logits; const float* head;
 };
 
+// Launches with few tiles: a tile's chain of products is all that counts, so four or eight waves share it (quad_kernel.h).
+// The line is where every compute unit has its workgroups (two of four waves, or one of eight at width 256) at once.
+// Four layers of scoring, microseconds with it / without: width 64 at 50, 250, 512 tiles 24 / 38, 26 / 39, 34 / 41;
+// width 128 at 25, 256, 512 tiles 53 / 107, 59 / 110, 81 / 115 (1008 tiles without it: 131); cold weights and caches, width 128,
+// 25 tiles 59 / 107.  Width 256, cold, 128 tiles: 45 less in a cache build and first list of 772.  A cache build (two layers of
+// attention), width 128 at 32, 256, 512 tiles 106 / 135, 117 / 148, 160 / 174; width 256 at 64, 256, 512 tiles 202 / 279,
+// 278 / 351, 531 / 480.
+static bool quad_pays(const Shape& s, long long tiles) { return s.quad && tiles <= (s.D >= 256 ? 256 : 512); }
+
 static int run_layer(const longer_config* c, const Shape& s, const char* packed_blk, const int32_t* lens, int B, int L,
                      const AttnIO& io, bool do_attn, hipStream_t st) {
   {
@@ -616,8 +648,14 @@ static int run_layer(const longer_config* c, const Shape& s, const char* packed_
   p.KG = io.KG; p.key_self = io.key_self;
   p.X_out = io.X_out; p.X_f32 = io.X_f32; p.X_ustride = io.X_ustride;
   p.logits = io.logits; p.head = io.head;
-  const int grid = cdiv((long long)B * p.tiles_per_user, kWaves);
+  const long long tiles = (long long)B * p.tiles_per_user;
+  const int grid = cdiv(tiles, kWaves);
   StageScope scope(ST_ATTN, st);
+  if (quad_pays(s, tiles) && !p.logits) {
+    p.n_layers = 1;
+    if (s.quad(MODE_ATTN, 16, false, p, dim3((unsigned)tiles), st)) return fail(LONGER_ERR_HIP, "attention launch failed");
+    return 0;
+  }
   if (s.main_fn(MODE_ATTN, 1, 16, p, dim3(grid), st)) return fail(LONGER_ERR_HIP, "attention launch failed");
   return 0;
 }
@@ -1041,10 +1079,18 @@ static int run_score(const longer_config* cfg, const Shape& s, const char* strea
   p.X_out = Yg_out; p.X_f32 = 0;
   p.logits = logits_out; p.head = head;
   const int tiles = cdiv((long long)C * cfg->m, 32);
-  p.xcds = kXcds; p.wg_per_user = cdiv(tiles, kWaves);
-  dim3 grid((unsigned)(kXcds * cdiv(U, kXcds) * p.wg_per_user));
+  // (all of a user's tiles on one die only where that loads the dies evenly: one user's 2000 candidates at d = 256 on one
+  // die of eight took 908 us)
+  p.xcds = U % kXcds ? 1 : kXcds; p.wg_per_user = cdiv(tiles, kWaves);
+  dim3 grid((unsigned)((long long)U * p.wg_per_user));
   StageScope scope(ST_SCORE, st);
   const int win = cfg->m <= 8 ? 4 : (cfg->m <= 16 ? 8 : 16);
+  if (quad_pays(s, (long long)U * tiles)) {
+    p.wg_per_user = tiles;
+    grid = dim3((unsigned)((long long)U * tiles));
+    if (s.quad(MODE_SCORE, win, pair_score(s), p, grid, st)) return fail(LONGER_ERR_HIP, "score kernel launch failed");
+    return 0;
+  }
   if (pair_score(s) ? s.pair(MODE_SCORE, win, p, grid, st) : s.main_fn(MODE_SCORE, 1, win, p, grid, st))
     return fail(LONGER_ERR_HIP, "score kernel launch failed");
   return 0;

@@ -24,3 +24,50 @@ def test_parity_with_the_pair_kernels_switched_off():
     tail = "\n".join(r.stdout.splitlines()[-25:])
     assert r.returncode == 0, tail
     assert " passed" in tail and "failed" not in tail, tail
+
+
+# Scoring more candidates than the few-tiles kernels take (512 tiles, 256 at d = 256) runs the same rows through the
+# two-wave (d = 128 / 256) or one-wave (d = 64) kernels: both against the oracle for the candidates at the ends of the
+# list, and against each other, a call of 40 candidates at a time, for all of them.  Users dealt to the dies (8) and not (3);
+# one row more than whole tiles, rows that end inside a tile, m = 32 (one candidate fills a tile).
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,heads,m,U,C", [(64, 4, 4, 3, 1367), (64, 2, 2, 8, 1025), (128, 8, 8, 1, 2049), (128, 4, 32, 8, 65),
+                                           (256, 8, 8, 3, 343), (256, 16, 16, 8, 65)])
+def test_many_candidates_equal_the_same_candidates_in_short_lists(d, heads, m, U, C):
+    import numpy as np
+    import torch
+    import longer_synth as synth
+    import paper_2505_04421_amd as lg
+    from oracle import longer_oracle as orc
+    cfg = synth.CONFIGS["C2"].replace(B=U, L=150, d=d, heads=heads, inner_heads=heads, m=m, k_recent=9, n_self=2, C=C, ragged=True,
+                                      len_lo=1, len_hi=150, index=71)
+    case = synth.make_case(cfg)
+    model = lg.DeviceModel(cfg, case["weights"])
+    H, lens = model.upload(case["H"]), torch.from_numpy(case["lens"].astype(np.int32)).to(model.device)
+    g = np.random.default_rng(5).standard_normal((U, C, m, d)).astype(np.float32)
+    G = model.upload(g)
+    ws, cache = model.workspace(U, cfg.L), model.kv_cache(U, cfg.L)
+    lg.longer_kv_cache_build(model.ccfg, model.weights, H, lens, U, cfg.L, cache, ws)
+
+    def score(Gc):
+        n = Gc.shape[1]
+        Y, lo = model.empty(U, n, m, d), model.empty(U, n, dtype=torch.float32)
+        lg.longer_score_candidates(model.ccfg, model.weights, cache, lens, U, cfg.L, Gc.contiguous(), n, Y, lo, ws)
+        return Y.float().cpu().numpy().astype(np.float64), lo.cpu().numpy().astype(np.float64)
+    Y, lo = score(G)
+    step = 40 if m * U * 40 < 32 * 256 else 4
+    parts = [score(G[:, i:i + step]) for i in range(0, C, step)]
+    Y2, lo2 = np.concatenate([a for a, _ in parts], 1), np.concatenate([b for _, b in parts], 1)
+    rel = lambda a, b: np.linalg.norm(a - b) / np.linalg.norm(b)
+    # two bf16 evaluations, each within 1e-2 of the exact result (the parity tests' bar)
+    assert rel(Y, Y2) < 1e-2 and rel(lo, lo2) < 2e-2, (rel(Y, Y2), rel(lo, lo2))
+    ends = [0, 1, C - 2, C - 1]
+    Gr = G[:, ends].float().cpu().numpy()
+    for i, c in enumerate(ends):
+        Yr, lr = orc.forward(cfg, case["weights"], case["H"], Gr[:, i], case["lens"])
+        for got in (Y, Y2):
+            assert rel(got[:, c], Yr[:, :m]) < 1e-2, (c, rel(got[:, c], Yr[:, :m]))
+        # (a logit is a sum of m d products of either sign: its error goes with the logits' spread over the list, not with how
+        # near to zero one of them happens to come; 3e-2 of it is the parity tests' bar for a batch of logits)
+        for got in (lo, lo2):
+            assert np.abs(got[:, c] - lr).max() < 3e-2 * np.sqrt(np.mean(lo ** 2)), (c, got[:, c], lr)
