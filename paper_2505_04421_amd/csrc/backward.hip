@@ -14,21 +14,18 @@
 // parameter gradient are fp32; activations and activation gradients between two GEMMs are
 // stored as bf16.
 //
-// Unlike the forward kernels this pass is not fused per tile: a parameter gradient is a sum
-// over every token of the batch, i.e. a GEMM whose contraction runs over the tokens, so the
-// activations it contracts have to exist for the whole batch.  They are row-major
-// [token, feature] tensors in the workspace, and three kinds of kernels work on them:
-//   * one bf16 MFMA GEMM (bw_gemm_kernel) whose operands may each be stored with the
-//     contraction index contiguous or strided, which covers y = x W (+ epilogues),
-//     dx = dy W^T and dW = x^T dy (the tokens dealt to slices whose partial results a second
-//     kernel sums; the bias gradient, a column sum, rides along as one more product with ones),
-//     and the middle of the merge's FFN backward as two products under one epilogue (the hidden
-//     pre-activation is formed again there and never stored);
-//   * row kernels: LayerNorm forward / backward (+ gain / shift gradients), the merge's
-//     backward, the reduced stack's row build, masks, head and loss, gradient routing;
-//   * attention, forward and backward, one thread per (row, head), heads kept as packed bf16
-//     (two-feature dot products, fp32 sums): inside a group of K tokens (InnerTrans: K x K scores
-//     per head), and over a user's own rows under the mask of Eq. 8 (reduced stack).
+// A parameter gradient is a sum over every token of the batch, i.e. a product whose contraction runs over the tokens
+// (bw_grads.h), so what it contracts has to exist for the whole batch.  Everything else is fused per tile of 32 rows:
+//   * InnerTrans blocks up to width 128: one launch per block (bw_block.h);
+//   * the reduced stack: one launch between two attention launches (bw_stack.h, bw_set_attn.h).
+// InnerTrans blocks of width 256, whose tile does not fit a wave's registers, and the input generation run as kernels over
+// row-major [token, feature] tensors in the workspace, below:
+//   * bf16 MFMA GEMMs, operands with the contraction index contiguous: y = x W (+ epilogues), dx = dy W^T, and the middle
+//     of the FFN backward as two products under one epilogue (the hidden pre-activation is formed again there and
+//     never stored);
+//   * row kernels: LayerNorm forward / backward (+ gain / shift gradients), the merge's backward;
+//   * attention inside a group of K tokens, forward and backward, one thread per (row, head), heads kept as packed
+//     bf16 (two-feature dot products, fp32 sums).
 // Padded token rows are never read and cost only the zeros written for them.
 #include "bw_grads.h"
 #include "bw_set_attn.h"
@@ -51,17 +48,14 @@ constexpr int kMaxGroup = 32;   // K <= 32
 // ------------------------------------------------------------------------------------
 // GEMM  C[M, N] = A[M, Kc] B[Kc, N]  (bf16 operands, fp32 accumulation)
 //   A is stored [M][Kc] (contraction contiguous);
-//   B_KC: B is stored [N][Kc] (contraction contiguous), else [Kc][N].
+//   B is stored [N][Kc] (contraction contiguous).
 // Workgroup tile 128 x 128, contraction step 32, four waves in 2 x 2, each 64 x 64 (2 x 2 MFMA
 // tiles of 32 x 32).  Requirements checked by the host: strides multiples of 8 elements,
-// 16-byte aligned bases; a contiguous contraction dimension is a multiple of 32; the
-// non-contracted extent of a strided operand is a multiple of 8.  Rows / columns / contraction
+// 16-byte aligned bases; the contraction dimension is a multiple of 32.  Rows / columns / contraction
 // slices past the extents read as zeros.
 enum Epilogue {
   EPI_BF16 = 0,      // out[m][n] = bf16(acc + bias[n])
   EPI_RES_F32 = 1,   // outf[m][n] = res[m][n] + acc + bias[n]
-  EPI_ACT = 2,       // out[m][n] = bf16(v), out2[m][n] = bf16(act(v)), v = acc + bias[n]
-  EPI_DACT = 3,      // out[m][n] = bf16(acc * act'(pre[m][n]))
   EPI_F32 = 5,       // outf[m][n] = acc + bias[n]
   EPI_FFN_MID = 6    // two products in one launch, v = A B + bias and g = A2 B2 (same shapes):
                      // out[m][n] = bf16(g * act'(v)), out2[m][n] = bf16(act(v)); v itself is not stored
@@ -74,34 +68,19 @@ struct GemmArgs {
   int M, N, Kc;
   int epi, act;
   void* out; void* out2; int ldo;
-  const __bf16* bias; const float* res; const __bf16* pre;
+  const __bf16* bias; const float* res;
   const __bf16* A2; const __bf16* B2; int lda2, ldb2;   // the second product of a two-product launch (EPI_FFN_MID)
 };
-
-__device__ __forceinline__ float act_fwd(float v, int act) {
-  if (act == LONGER_ACT_RELU) return v > 0.f ? v : 0.f;
-  float c, e;
-  gauss_cdf(v, &c, &e);
-  return v * c;
-}
-__device__ __forceinline__ float act_grad(float v, int act) {
-  if (act == LONGER_ACT_RELU) return v > 0.f ? 1.f : 0.f;
-  float c, e;
-  gauss_cdf(v, &c, &e);
-  return c + v * 0.39894228040143268f * e;
-}
 
 constexpr int kStagePitch = 68;         // floats per row of the epilogue's staging area (64 + 4 pad)
 
 // KS: contraction elements per step.  Every launch uses 32: steps of 64 and 128 (one LDS buffer per operand
 // at 128) were measured for the two-product launch, whose contraction is only the model width, and
 // changed nothing (6.49 - 6.56 ms per merge backward at the headline shape for the three widths).
-template <bool B_KC, bool DUAL = false, int KS = 32>
+template <bool DUAL, int KS = 32>
 __global__ __launch_bounds__(256, DUAL ? 2 : 4) void bw_gemm_kernel(GemmArgs g) {
-  static_assert(KS == 32 || B_KC, "wide steps: contraction-contiguous operands only");
   constexpr int kPitchKC = KS + 8;            // elements per row of a contraction-contiguous LDS tile (8 pad)
-  constexpr int kPitchT = 144;                // the strided form's row pitch (see bw_wgrad_kernel)
-  constexpr int kTileElems = 128 * kPitchKC;  // >= KS * kPitchT of the strided form
+  constexpr int kTileElems = 128 * kPitchKC;
   constexpr int CPR = KS / 8;                 // 16-byte chunks per tile row (contraction-contiguous form)
   constexpr int NCH = KS / 16;                // chunks per thread and operand tile
   constexpr int NBUF = KS >= 128 ? 1 : 2;
@@ -151,14 +130,10 @@ __global__ __launch_bounds__(256, DUAL ? 2 : 4) void bw_gemm_kernel(GemmArgs g) 
         const int gr = m0 + row, gk = k0 + 8 * kc;
         if (gr < g.M && gk < kend) pa[i] = *(const bf16x8*)(opA + (size_t)gr * ldA + gk);
       }
-      if (B_KC) {
+      {
         const int row = c / CPR, kc = c % CPR;
         const int gr = n0 + row, gk = k0 + 8 * kc;
         if (gr < g.N && gk < kend) pb[i] = *(const bf16x8*)(opB + (size_t)gr * ldB + gk);
-      } else {
-        const int kr = c >> 4, xc = c & 15;
-        const int gk = k0 + kr, gx = n0 + 8 * xc;
-        if (gk < kend && gx < g.N) pb[i] = *(const bf16x8*)(opB + (size_t)gk * ldB + gx);
       }
     }
   };
@@ -167,18 +142,11 @@ __global__ __launch_bounds__(256, DUAL ? 2 : 4) void bw_gemm_kernel(GemmArgs g) 
     for (int i = 0; i < NCH; ++i) {
       const int c = tid + 256 * i;
       *(bf16x8*)&sA(buf)[(c / CPR) * kPitchKC + 8 * (c % CPR)] = pa[i];
-      if (B_KC) *(bf16x8*)&sB(buf)[(c / CPR) * kPitchKC + 8 * (c % CPR)] = pb[i];
-      else      *(bf16x8*)&sB(buf)[(c >> 4) * kPitchT + 8 * (c & 15)] = pb[i];
+      *(bf16x8*)&sB(buf)[(c / CPR) * kPitchKC + 8 * (c % CPR)] = pb[i];
     }
   };
   // fragment of the 32 x 16 operand slice: lane (x = l32, hi) holds contraction slots 8 hi .. 8 hi + 7
-  const int foff = frag_t_offset<kPitchT>(lane);
   auto frag = [&](const __bf16* s, int x, int ks) -> bf16x8 { return *(const bf16x8*)&s[(x + l32) * kPitchKC + 16 * ks + 8 * hi]; };
-  auto fragB = [&](const __bf16* s, int x, int ks) -> bf16x8 {
-    if constexpr (B_KC) return frag(s, x, ks);
-    else return frag_t<kPitchT>(s + foff + 16 * ks * kPitchT + x);
-  };
-
   // Contraction steps, two LDS buffers: step's tile goes to LDS (the buffer was last read two steps ago,
   // which every thread left before the previous step's barrier), the registers are refilled with the
   // next step's tile, barrier, MFMAs.
@@ -205,7 +173,7 @@ __global__ __launch_bounds__(256, DUAL ? 2 : 4) void bw_gemm_kernel(GemmArgs g) 
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         fa[t] = frag(sA(buf), 64 * wm + 32 * t, ks);
-        fb[t] = fragB(sB(buf), 64 * wn + 32 * t, ks);
+        fb[t] = frag(sB(buf), 64 * wn + 32 * t, ks);
       }
 #pragma unroll
       for (int a = 0; a < 2; ++a)
@@ -236,16 +204,15 @@ __global__ __launch_bounds__(256, DUAL ? 2 : 4) void bw_gemm_kernel(GemmArgs g) 
   }
 #pragma unroll
   for (int a = 0; a < 2; ++a) {
-    f32x4 ld[4][2];                   // EPI_RES_F32: the chunk's residual values; EPI_DACT: its pre-activations (first 16 bytes)
-    if (g.epi == EPI_RES_F32 || g.epi == EPI_DACT) {
+    f32x4 ld[4][2];                   // EPI_RES_F32: the chunk's residual values
+    if (g.epi == EPI_RES_F32) {
 #pragma unroll
       for (int it = 0; it < 4; ++it) {
         const int m = m0 + 64 * wm + 32 * a + it * 8 + (lane >> 3);
         ld[it][0] = f32x4{0.f, 0.f, 0.f, 0.f}; ld[it][1] = ld[it][0];
         if (m >= g.M || en >= g.N) continue;
         const size_t o = (size_t)m * g.ldo + en;
-        if (g.epi == EPI_RES_F32) { ld[it][0] = *(const f32x4*)(g.res + o); ld[it][1] = *(const f32x4*)(g.res + o + 4); }
-        else ld[it][0] = *(const f32x4*)(g.pre + o);
+        ld[it][0] = *(const f32x4*)(g.res + o); ld[it][1] = *(const f32x4*)(g.res + o + 4);
       }
     }
     float v2[DUAL ? 4 : 1][8];        // two-product launch: the second product's values of this thread's chunks
@@ -292,17 +259,6 @@ __global__ __launch_bounds__(256, DUAL ? 2 : 4) void bw_gemm_kernel(GemmArgs g) 
         for (int e = 0; e < 4; ++e) { o0[e] = r0[e] + v[e]; o1[e] = r1[e] + v[4 + e]; }
         *(f32x4*)((float*)g.out + o) = o0;
         *(f32x4*)((float*)g.out + o + 4) = o1;
-      } else if (g.epi == EPI_ACT) {
-        bf16x8 oa;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) { ob[e] = (__bf16)v[e]; oa[e] = (__bf16)act_fwd(v[e], g.act); }
-        *(bf16x8*)((__bf16*)g.out + o) = ob;
-        *(bf16x8*)((__bf16*)g.out2 + o) = oa;
-      } else if (g.epi == EPI_DACT) {
-        const bf16x8 pv = __builtin_bit_cast(bf16x8, ld[it][0]);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) ob[e] = (__bf16)(v[e] * act_grad((float)pv[e], g.act));
-        *(bf16x8*)((__bf16*)g.out + o) = ob;
       } else if (DUAL && g.epi == EPI_FFN_MID) {
         bf16x8 oa;
 #pragma unroll
@@ -1478,11 +1434,11 @@ static int launched(const char* what) {
   return hipGetLastError() == hipSuccess ? 0 : api_error(LONGER_ERR_HIP, "%s launch failed", what);
 }
 
-static int gemm(hipStream_t st, bool b_kc, GemmArgs g) {
+static int gemm(hipStream_t st, GemmArgs g) {
   if (!aligned16(g.A) || !aligned16(g.B) || g.lda % 8 || g.ldb % 8) return api_error(LONGER_ERR_ARG, "backward GEMM operand misaligned");
   const int ntm = (g.M + 127) / 128, ntn = (g.N + 127) / 128;
   dim3 grid((unsigned)(((ntm + 7) / 8) * 8 * ntn));            // see the tile order in the kernel
-  if (b_kc && (g.Kc == 32 || g.Kc == 64 || g.Kc == 128) &&
+  if ((g.Kc == 32 || g.Kc == 64 || g.Kc == 128) &&
       (g.epi == EPI_FFN_MID || g.epi == EPI_BF16 || g.epi == EPI_RES_F32 || g.epi == EPI_F32)) {
     if (g.epi == EPI_FFN_MID && (!aligned16(g.A2) || !aligned16(g.B2) || g.lda2 % 8 || g.ldb2 % 8))
       return api_error(LONGER_ERR_ARG, "backward GEMM operand misaligned");
@@ -1498,25 +1454,13 @@ static int gemm(hipStream_t st, bool b_kc, GemmArgs g) {
     return launched("backward row GEMM");
   }
   if (g.epi == EPI_FFN_MID) {
-    if (!b_kc || !aligned16(g.A2) || !aligned16(g.B2) || g.lda2 % 8 || g.ldb2 % 8)
+    if (!aligned16(g.A2) || !aligned16(g.B2) || g.lda2 % 8 || g.ldb2 % 8)
       return api_error(LONGER_ERR_ARG, "backward GEMM operand misaligned");
-    bw_gemm_kernel<true, true><<<grid, 256, 0, st>>>(g);
-  } else if (b_kc) bw_gemm_kernel<true><<<grid, 256, 0, st>>>(g);
-  else bw_gemm_kernel<false><<<grid, 256, 0, st>>>(g);
+    bw_gemm_kernel<true><<<grid, 256, 0, st>>>(g);
+  } else bw_gemm_kernel<false><<<grid, 256, 0, st>>>(g);
   return launched("backward GEMM");
 }
 
-// y = x W (+ epilogue): x [ntok][kc] row-major, W [kc][.. n columns, pitch ldb] row-major; outputs,
-// residual and pre-activation [ntok][n]
-static int gemm_rows(hipStream_t st, const __bf16* x, int kc, const __bf16* W, int n, size_t ntok, int epi, int act,
-                     void* out, void* out2, const __bf16* bias, const float* res, const __bf16* pre, int ldb = 0,
-                     RowsValid rows = RowsValid{nullptr, 0}) {
-  GemmArgs g = {};
-  g.rows = rows;
-  g.A = x; g.lda = kc; g.B = W; g.ldb = ldb ? ldb : n; g.M = (int)ntok; g.N = n; g.Kc = kc;
-  g.epi = epi; g.act = act; g.out = out; g.out2 = out2; g.ldo = n; g.bias = bias; g.res = res; g.pre = pre;
-  return gemm(st, false, g);
-}
 // y = x W (+ epilogue) with W handed over transposed, wt [n][kc]: both operands contraction-contiguous
 static int gemm_rows_wt(hipStream_t st, const __bf16* x, int kc, const __bf16* wt, int n, size_t ntok, int epi,
                         void* out, const __bf16* bias, const float* res, RowsValid rows) {
@@ -1524,16 +1468,15 @@ static int gemm_rows_wt(hipStream_t st, const __bf16* x, int kc, const __bf16* w
   g.rows = rows;
   g.A = x; g.lda = kc; g.B = wt; g.ldb = kc; g.M = (int)ntok; g.N = n; g.Kc = kc;
   g.epi = epi; g.out = out; g.ldo = n; g.bias = bias; g.res = res;
-  return gemm(st, true, g);
+  return gemm(st, g);
 }
-// dx = dy W^T: dy [ntok][kc], W [n][.. kc columns, pitch ldb] row-major (the forward's [in = n][out = kc])
-static int gemm_rows_t(hipStream_t st, const __bf16* dy, int kc, const __bf16* W, int n, size_t ntok, int epi, int act,
-                       void* out, const __bf16* pre, int ldb = 0, RowsValid rows = RowsValid{nullptr, 0}) {
+// dx = dy W^T: dy [ntok][kc], W [n][kc] row-major (the forward's [in = n][out = kc])
+static int gemm_rows_t(hipStream_t st, const __bf16* dy, int kc, const __bf16* W, int n, size_t ntok, int epi, void* out, RowsValid rows) {
   GemmArgs g = {};
   g.rows = rows;
-  g.A = dy; g.lda = kc; g.B = W; g.ldb = ldb ? ldb : kc; g.M = (int)ntok; g.N = n; g.Kc = kc;
-  g.epi = epi; g.act = act; g.out = out; g.ldo = n; g.pre = pre;
-  return gemm(st, true, g);
+  g.A = dy; g.lda = kc; g.B = W; g.ldb = kc; g.M = (int)ntok; g.N = n; g.Kc = kc;
+  g.epi = epi; g.out = out; g.ldo = n;
+  return gemm(st, g);
 }
 // The middle of the FFN's backward in one launch: v = x W1 + b1 (recomputed, not stored), g = dy W2^T,
 // a_out = bf16(act(v)), dh_out = bf16(g act'(v)).  x, dy [ntok][d]; w1t = W1 transposed, [f][d]; w2 [f][d].
@@ -1544,7 +1487,7 @@ static int gemm_ffn_mid(hipStream_t st, const __bf16* x, const __bf16* dy, int d
   g.A = x; g.lda = d; g.B = w1t; g.ldb = d; g.A2 = dy; g.lda2 = d; g.B2 = w2; g.ldb2 = d;
   g.M = (int)ntok; g.N = f; g.Kc = d;
   g.epi = EPI_FFN_MID; g.act = act; g.out = dh_out; g.out2 = a_out; g.ldo = f; g.bias = b1;
-  return gemm(st, true, g);
+  return gemm(st, g);
 }
 static int transpose(hipStream_t st, const __bf16* in, __bf16* out, int rows, int cols) {
   bw_transpose_kernel<<<dim3((cols + 31) / 32, (rows + 31) / 32), 256, 0, st>>>(in, out, rows, cols);
@@ -1706,10 +1649,10 @@ static int run(const longer_config* c, const longer_block* inner, const void* H,
     // FFN: y = xmid + act(n2 W1 + b1) W2 + b2; the hidden pre-activation is formed inside the launch
     // that takes its gradient, and only the activated values and the hidden gradient reach memory
     BW_TRY(gemm_ffn_mid(st, n2, dyb, d, w1t(l), (const __bf16*)b.w2, f, (const __bf16*)b.b1, nt, c->act, dh, a, rv));
-    BW_TRY(gemm_rows_t(st, dh, f, (const __bf16*)b.w1, d, nt, EPI_BF16, 0, dn, nullptr, 0, rv));
+    BW_TRY(gemm_rows_t(st, dh, f, (const __bf16*)b.w1, d, nt, EPI_BF16, dn, rv));
     BW_TRY(ln_bwd(st, ln_grid, d, dn, xmid, (const __bf16*)b.ln2_g, dy, dxm, dxmb, lnpart[1], (int)nt, c->ln_eps, rv));
     // attention: xmid = x + att W_O + b_O
-    BW_TRY(gemm_rows_t(st, dxmb, d, (const __bf16*)b.wo, d, nt, EPI_BF16, 0, dob, nullptr, 0, rv));
+    BW_TRY(gemm_rows_t(st, dxmb, d, (const __bf16*)b.wo, d, nt, EPI_BF16, dob, rv));
     if (L % s.K == 0 && 256 % s.heads == 0 && (256 / s.heads) % s.K == 0) {     // every group inside one workgroup's rows
       group_attn(3, s.dh, s.K, ah_grid, st, qkv, dob, dqkv, stat, q, d, s.heads);
     } else {
@@ -1720,7 +1663,7 @@ static int run(const longer_config* c, const longer_block* inner, const void* H,
     // every matrix of the block at once, now that all operands are there (dyb goes to the next block's below)
     WgradBatch wg = block_wgrads(d, f, nt, rv, n1, dqkv, o, dxmb, n2, dh, a, dyb, g);
     BW_TRY(launch(wg, part, st));
-    BW_TRY(gemm_rows_t(st, dqkv, 3 * d, wcat(l), d, nt, EPI_BF16, 0, dn, nullptr, 0, rv));
+    BW_TRY(gemm_rows_t(st, dqkv, 3 * d, wcat(l), d, nt, EPI_BF16, dn, rv));
     // the gradient of this block's input is the upstream gradient of the block before it
     float* dx = l ? dy : dH;
     BW_TRY(ln_bwd(st, ln_grid, d, dn, xin(l), (const __bf16*)b.ln1_g, dxm, dx, l ? dyb : nullptr, lnpart[0],
@@ -2209,7 +2152,7 @@ int longer_input_generation_backward(const longer_config* cfg, const longer_inpu
   if ((rc = bw::launch(wg, (float*)(w8 + l.part), st))) return rc;
   rb.add(wg);
   if ((rc = bw::launch(rb, st))) return rc;
-  if ((rc = bw::gemm_rows_t(st, dh, f, (const __bf16*)w->w1, d, nt, bw::EPI_F32, 0, dx, nullptr, 0, rv))) return rc;
+  if ((rc = bw::gemm_rows_t(st, dh, f, (const __bf16*)w->w1, d, nt, bw::EPI_F32, dx, rv))) return rc;
   bw::bw_split_input_grad_kernel<<<eg, 256, 0, st>>>(dx, dE_out, dtdiff_out, q, d, d_e);
   bw::bw_pos_grad_kernel<<<bw::flat_grid((size_t)L * d_e / 4), 256, 0, st>>>(dx, grads_out + gl.pos, q, B, d, d_e);
   return bw::launched("input gradient");

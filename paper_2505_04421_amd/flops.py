@@ -74,13 +74,14 @@ def merge_backward_work(cfg, lens: Optional[Sequence[int]] = None, B: Optional[i
     product (the gradient of its input and of its weight): 2 x the InnerTrans forward count, on
     valid tokens.  ``recompute_flops``: the forward products that are computed again (the chain of
     block inputs: all blocks but the last; then every block's intermediates, without its second
-    FFN product).  ``hbm_bytes``: what the pass's kernels read and write when every tensor makes one
+    FFN product).  ``hbm_bytes``: what a pass of one kernel per operation (the form that blocks of width 256 have) reads and write when every tensor makes one
     trip per use.  Per valid token and block 38 w bytes for the recomputed intermediates (up to the
     FFN's input; the hidden pre-activation is formed again inside the launch that takes its gradient and
     never stored) and 92 w + 10 f for the gradients, 6 w for every block input that the fused forward kernel recomputes (it
     reads the raw tokens and writes fp32 rows), 12 w once for the input copy and the merge gradient.  A
     padded token is never read; it costs the zeros written for it: 16 w per block (two LayerNorm outputs,
-    two LayerNorm gradients with their bf16 copies), 4 w per recomputed block input, 10 w once."""
+    two LayerNorm gradients with their bf16 copies), 4 w per recomputed block input, 10 w once.
+    ``fused_hbm_bytes``: the same with one launch per block (blocks up to width 128)."""
     B = cfg.B if B is None else B
     L = cfg.L if L is None else L
     w = cfg.d // cfg.K if getattr(cfg, "merge", "mean") == "concat" else cfg.d
@@ -94,5 +95,11 @@ def merge_backward_work(cfg, lens: Optional[Sequence[int]] = None, B: Optional[i
     recompute = (n - 1) * per_block + n * (per_block - ffn2 * valid)
     per_token = (n - 1) * 6 * w + n * 38 * w + n * (92 * w + 10 * f) + 12 * w
     per_padded = (n - 1) * 4 * w + n * 16 * w + 10 * w
+    # one launch per block: input rows twice (bf16 raw tokens or fp32), the output gradient twice (fp32; the last block's
+    # from the merged tokens), q / k / v written and read, what the parameter gradients contract written and read,
+    # the input gradient; the chain of block inputs as above
+    last = 8 * w if getattr(cfg, "merge", "mean") == "concat" else 8 * w / cfg.K
+    fused = (n - 1) * 6 * w + 4 * w + (n - 1) * 8 * w + last + (n - 1) * 8 * w + n * (6 * w + 26 * w + 4 * f + 16 * w + 4 * f)
     return {"gradient_flops": 2 * inner, "recompute_flops": recompute,
-            "hbm_bytes": per_token * valid + per_padded * (B * L - valid)}
+            "hbm_bytes": per_token * valid + per_padded * (B * L - valid),
+            "fused_hbm_bytes": int(fused * valid) + 4 * w * (B * L - valid)}
