@@ -677,6 +677,13 @@ static int run_stack(const longer_config* c, const Shape& s, const char* packed_
   p.X_out = io.X_out; p.X_f32 = io.X_f32; p.X_ustride = io.X_ustride;
   p.logits = io.logits; p.head = io.head;
   StageScope scope(ST_ATTN, st);
+  // At most two tiles a user: eight waves for them instead of one or two waves each, as long as the users are one or two
+  // rounds of workgroups.  Whole forward pass (L = 400, K = 8, three or four layers), microseconds with it / without: width 64, m + k = 24, at
+  // 1, 128, 256, 512 users 38 / 43, 46 / 52, 60 / 66, 98 / 92; width 128, m + k = 58, at 1, 128, 512 users 100 / 123, 130 / 157, 356 / 400.
+  if (s.quad && s.D <= 128 && s.n <= 64 && B <= (s.D == 64 ? 256 : 512)) {
+    if (s.quad(MODE_STACK, 16, pair_stack(s), p, dim3(B), st)) return fail(LONGER_ERR_HIP, "stack launch failed");
+    return 0;
+  }
   if (pair_stack(s) ? s.pair(MODE_STACK, 16, p, dim3(B), st) : s.main_fn(MODE_STACK, 1, 16, p, dim3(B), st))
     return fail(LONGER_ERR_HIP, "stack launch failed");
   return 0;

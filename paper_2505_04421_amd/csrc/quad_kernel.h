@@ -2,7 +2,8 @@
 // compute unit, or eight at width 256 (bf16).
 //
 //   MODE_SCORE  candidate scoring of the KV-cache serving path (Section 3.6.3), all layers;
-//   MODE_ATTN   query side of one layer over stored K/V fragments (the cache build's sequence rows).
+//   MODE_ATTN   query side of one layer over stored K/V fragments (the cache build's sequence rows);
+//   MODE_STACK  the whole reduced stack of a user with at most two tiles (m + k <= 64) in one workgroup of eight waves.
 //
 // Why.  A request scores a hundred candidates (25 tiles), a cache build runs two tiles per user: a handful of
 // workgroups on 256 compute units, whose time is one tile's chain of dependent products.  Here feature tile t of the
@@ -18,46 +19,54 @@ namespace longer {
 
 // waves that share a tile: one feature tile each at width 128 and 256, hidden chunks dealt out among all
 constexpr int quad_waves(int d) { return d >= 256 ? 8 : 4; }
+constexpr int quad_tiles(int mode) { return mode == MODE_STACK ? 2 : 1; }      // tiles of a workgroup
 
-// segment indices inside one block's packed stream (layouts: device.h)
-enum QuadLayout { QUAD_PAIR = 0, QUAD_FUSED = 1, QUAD_SPLIT = 2 };
+// Segment indices inside one block's packed stream (layouts: device.h).  attn: the attention half of the split (or
+// pair) layout, without K and V; else the fused layouts.
+enum QuadLayout { QUAD_PLAIN = 0, QUAD_PAIR = 1 };
 template <int LAYOUT, int D>
 struct QuadSegs {
-  static constexpr int NT = D / 32;
-  int NC;
-  __device__ __forceinline__ int q(int t) const { return LAYOUT == QUAD_PAIR ? 2 + 6 * (t / 2) + (t & 1) : LAYOUT == QUAD_FUSED ? 1 + 3 * t : 1 + t; }
+  static constexpr int NT = D / 32, V0 = LAYOUT == QUAD_PAIR ? 2 : 1;       // V0: segments in front of the matrices
+  int NC; bool attn;
+  __device__ __forceinline__ int q(int t) const { return V0 + (attn ? t : LAYOUT == QUAD_PAIR ? 6 * (t / 2) + (t & 1) : 3 * t); }
   __device__ __forceinline__ int k(int t) const { return q(t) + (LAYOUT == QUAD_PAIR ? 2 : 1); }
   __device__ __forceinline__ int v(int t) const { return q(t) + (LAYOUT == QUAD_PAIR ? 4 : 2); }
-  __device__ __forceinline__ int o(int t) const { return (LAYOUT == QUAD_PAIR ? 2 + 3 * NT : LAYOUT == QUAD_FUSED ? 1 + 3 * NT : 1 + NT) + t; }
+  __device__ __forceinline__ int o(int t) const { return V0 + (attn ? NT : 3 * NT) + t; }
+  __device__ __forceinline__ int ffn() const { return V0 + (attn ? 2 * NT : 4 * NT); }
   __device__ __forceinline__ int w1(int c) const {
-    if (LAYOUT == QUAD_PAIR) return 2 + 4 * NT + 4 * (c / 2) + (c & 1);
+    if (LAYOUT == QUAD_PAIR) return ffn() + 4 * (c / 2) + (c & 1);
     return ffn() + (ffn_skewed(2, D) ? (c < 2 ? c : 2 * c) : 2 * c);
   }
   __device__ __forceinline__ int w2(int c) const {
     if (LAYOUT == QUAD_PAIR) return w1(c) + 2;
     return ffn() + (ffn_skewed(2, D) ? (c < NC - 1 ? 3 + 2 * c : 2 * NC) : 2 * c + 1);
   }
-  __device__ __forceinline__ int ffn() const { return LAYOUT == QUAD_FUSED ? 1 + 4 * NT : 1 + 2 * NT; }
-  __device__ __forceinline__ int block() const { return 2 + 4 * NT + 2 * NC; }        // a block of the fused layouts
+  __device__ __forceinline__ int block() const { return 2 + (attn ? 2 : 4) * NT + 2 * NC; }
 };
 
 template <int D, int DH, int MODE, int W, int LAYOUT, bool RELU>
-__global__ void __launch_bounds__(64 * quad_waves(D), 1) quad_kernel(const BlockParams p) {
+__global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), 1) quad_kernel(const BlockParams p) {
   using T = __bf16;
   using E = ET<T>;
   using grp = typename E::grp;
   using hgrp = typename E::hgrp;
-  constexpr int WV = quad_waves(D), kThr = 64 * WV;
+  constexpr int WV = quad_waves(D), TS = quad_tiles(MODE), kThr = 64 * WV * TS;
   constexpr int NT = D / 32, NG = D / 16, OT = (NT + WV - 1) / WV, HPT = 32 / DH, GPH = DH / 16;
-  constexpr bool SCORE = MODE == MODE_SCORE;
-  static_assert(SCORE || MODE == MODE_ATTN, "quad kernel modes");
-  __shared__ grp ops[NG][64];                        // [group][lane]: operand of the next products
-  __shared__ hgrp hid[2][WV][2][64];                  // activated hidden chunks: [parity][wave][group][lane]
-  __shared__ float2 sums[WV][64];
+  constexpr bool SCORE = MODE == MODE_SCORE, STACK = MODE == MODE_STACK;
+  static_assert(SCORE || STACK || MODE == MODE_ATTN, "quad kernel modes");
+  static_assert(!STACK || OT == 1, "the stack's K / V hand-over takes one feature tile per wave");
+  __shared__ grp ops_[TS][NG][64];                   // per tile, [group][lane]: operand of the next products
+  __shared__ hgrp hid_[TS][2][WV][2][64];            // activated hidden chunks: [parity][wave][group][lane]
+  __shared__ float2 sums_[TS][WV][64];
+  __shared__ grp kvl[STACK ? TS : 1][STACK ? NT : 1][2][2][64];      // self layers: [key tile][feature tile][K, V][group][lane]
   __shared__ f32x4 vecl[D * 4];                      // the block's fp32 vectors (at most one segment)
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 31, hi = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 31, hi = lane >> 5;
+  const int ts = TS == 1 ? 0 : wv / WV, wave = TS == 1 ? wv : wv % WV;     // tile of the workgroup, wave of the tile
+  auto& ops = ops_[ts];
+  auto& hid = hid_[ts];
+  auto& sums = sums_[ts];
   const int NC = p.FF / 32;
-  const QuadSegs<LAYOUT, D> sg = {NC};
+  QuadSegs<LAYOUT, D> sg = {NC, !SCORE};               // (the stack's first block is the cross layer's attention half)
   auto owns = [&](int i) { return NT >= WV || wave + WV * i < NT; };
 
   // ------------------------------------------------------------------ rows
@@ -65,7 +74,8 @@ __global__ void __launch_bounds__(64 * quad_waves(D), 1) quad_kernel(const Block
   int usr, Tu, tile;
   long long out_off;
   uint32_t tilebits = 0;
-  int lo1 = 0, hi1 = 0, lo2 = 0, hi2 = 0, kthi = 0;
+  int lo1 = 0, hi1 = 0, lo2 = 0, hi2 = 0, kthi = 0;    // visible key ranges of the stored keys, their tiles
+  int slo1 = 0, shi1 = 0, slo2 = 0, shi2 = 0;          // the stack's self layers
   const int widx = W == 16 ? 0 : j / (2 * W);
   uint32_t wmask[16 / W];
 #pragma unroll
@@ -95,7 +105,8 @@ __global__ void __launch_bounds__(64 * quad_waves(D), 1) quad_kernel(const Block
     const int gbase = p.m * (j / p.m);
     tilebits = ((range_bits(gbase + (p.gmask_causal ? gi : 0), gbase + p.m, 0) & vb) >> (4 * hi)) >> (2 * W * widx);
   } else {
-    usr = (int)blockIdx.x / p.tiles_per_user; tile = (int)blockIdx.x - usr * p.tiles_per_user;
+    if (STACK) { usr = (int)blockIdx.x; tile = ts; }
+    else { usr = (int)blockIdx.x / p.tiles_per_user; tile = (int)blockIdx.x - usr * p.tiles_per_user; }
     const int a = p.q0 + 32 * tile + j;
     inrange = usr < p.B && (32 * tile + j) < p.rows_per_user;
     int len = p.lens ? p.lens[usr] : p.L; len = min(max(len, 0), p.L);
@@ -117,6 +128,10 @@ __global__ void __launch_bounds__(64 * quad_waves(D), 1) quad_kernel(const Block
     }
     if (!valid) { hi1 = lo1; hi2 = lo2; }
     kthi = (p.KG + (p.key_self ? p.k : tu) + 31) / 32;
+    if (STACK && valid) {      // keys of a self-causal layer: the user's own rows, key index = row index
+      if (glob) { slo1 = p.gmask_causal ? a : 0; shi1 = p.m; slo2 = p.m + i0; shi2 = p.m + p.k; }
+      else { slo2 = p.m + i0; shi2 = p.m + i + 1; }
+    }
   }
 
   const char* wl = p.wbase;                            // the current block's stream
@@ -124,7 +139,7 @@ __global__ void __launch_bounds__(64 * quad_waves(D), 1) quad_kernel(const Block
   // workgroups of a die (every eighth) bring the whole stream in at once, each its share.
   {
     const unsigned peers = (gridDim.x + 7 - (blockIdx.x & 7)) / 8;
-    const unsigned lines = (unsigned)((SCORE ? sg.block() * p.n_layers : 2 + 2 * NT + 2 * NC) * (D / 2));
+    const unsigned lines = (unsigned)((sg.block() + (p.n_layers - 1) * (2 + 4 * NT + 2 * NC)) * (D / 2));
     unsigned keep = 0;
     for (unsigned i = (blockIdx.x >> 3) * kThr + tid; i < lines; i += peers * kThr) keep |= *reinterpret_cast<const unsigned*>(wl + (size_t)i * 128);
     asm volatile("" :: "v"(keep));
@@ -179,7 +194,8 @@ __global__ void __launch_bounds__(64 * quad_waves(D), 1) quad_kernel(const Block
     for (int g = 0; g < NG; ++g) b[g] = ops[g][lane];
   };
 
-  for (int layer = 0; layer < p.n_layers; ++layer, wl += (size_t)sg.block() * D * 64) {
+  for (int layer = 0; layer < p.n_layers; ++layer) {
+    const bool selfl = STACK && layer > 0;             // K and V made here, handed to the user's other tile through LDS
     if (layer > 0) __syncthreads();                    // nobody still reads the previous block's vectors
     for (int i = tid; i < (9 * D + p.FF) / 4; i += kThr) vecl[i] = reinterpret_cast<const f32x4*>(wl)[i];
     __syncthreads();
@@ -189,14 +205,23 @@ __global__ void __launch_bounds__(64 * quad_waves(D), 1) quad_kernel(const Block
       grp oo[OT][2];
 #pragma unroll
       for (int i = 0; i < OT; ++i) {
-        if (!owns(i)) continue;
         const int ft = wave + WV * i;
-        f32x16 aq = product(bias_tile(vec + vl.bq(), ft, hi), sg.q(ft), xn, false);
-        f32x16 ak, av;
-        if (SCORE) {
-          ak = product(splat16(0.f), sg.k(ft), xn, false);     // no b_K, no b_V: see block_kernel.h
-          av = product(splat16(0.f), sg.v(ft), xn, true);
+        f32x16 aq, ak, av;
+        if (owns(i)) {
+          aq = product(bias_tile(vec + vl.bq(), ft, hi), sg.q(ft), xn, false);
+          if (SCORE || selfl) {
+            ak = product(splat16(0.f), sg.k(ft), xn, false);     // no b_K, no b_V: see block_kernel.h
+            av = product(splat16(0.f), sg.v(ft), xn, true);
+          }
+          if (selfl) {
+            settle(ak); settle(av);
+#pragma unroll
+            for (int g = 0; g < 2; ++g) { kvl[ts][ft][0][g][lane] = E::pack(ak, g); kvl[ts][ft][1][g][lane] = E::pack(av, g); }
+          }
         }
+        if (selfl) __syncthreads();
+        if (!owns(i)) continue;
+        settle(aq);
         aq *= p.scale_l2e;
         grp qop[2];
 #pragma unroll
@@ -208,7 +233,9 @@ __global__ void __launch_bounds__(64 * quad_waves(D), 1) quad_kernel(const Block
         // stored K/V fragments (wave-uniform user, scalar loop control); two key tiles on their way
         const char* kb; const char* vb; int nkt, rlo = 0, rhi = 0;
         const int tuu = __builtin_amdgcn_readfirstlane(Tu);
-        if (!SCORE) {
+        if (selfl) {
+          kb = vb = nullptr; nkt = (p.m + p.k + 31) / 32;
+        } else if (!SCORE) {
           kb = p.kst + (size_t)usr * p.kv_ustride; vb = p.vst + (size_t)usr * p.kv_ustride;
           nkt = __builtin_amdgcn_readfirstlane(kthi);
         } else {
@@ -224,6 +251,11 @@ __global__ void __launch_bounds__(64 * quad_waves(D), 1) quad_kernel(const Block
         }
         grp kn[2][2], vn[2][2];
         auto fetch = [&](int kt, int b) {
+          if (selfl) {
+#pragma unroll
+            for (int g = 0; g < 2; ++g) { kn[b][g] = kvl[STACK ? kt : 0][STACK ? ft : 0][0][g][lane]; vn[b][g] = kvl[STACK ? kt : 0][STACK ? ft : 0][1][g][lane]; }
+            return;
+          }
           const size_t fo = ((size_t)(kt * NT + ft) * 2) * 1024 + lane * 16;
 #pragma unroll
           for (int g = 0; g < 2; ++g) {
@@ -249,7 +281,8 @@ __global__ void __launch_bounds__(64 * quad_waves(D), 1) quad_kernel(const Block
           }
         }
         auto key_tile = [&](int kt, int b) {
-          const uint32_t bits = SCORE ? range_bits(rlo, rhi, 32 * kt) : range_bits(lo1, hi1, 32 * kt) | range_bits(lo2, hi2, 32 * kt);
+          const uint32_t bits = SCORE ? range_bits(rlo, rhi, 32 * kt)
+                              : selfl ? range_bits(slo1, shi1, 32 * kt) | range_bits(slo2, shi2, 32 * kt) : range_bits(lo1, hi1, 32 * kt) | range_bits(lo2, hi2, 32 * kt);
           const uint32_t ab = (bits >> (4 * hi)) & kTileBits;
           const bool none = __builtin_amdgcn_ballot_w64(ab != 0) == 0;           // nobody sees any of these keys
           const bool full = __builtin_amdgcn_ballot_w64(ab != kTileBits) == 0;   // everybody sees all of them
@@ -337,6 +370,8 @@ __global__ void __launch_bounds__(64 * quad_waves(D), 1) quad_kernel(const Block
     }
 #pragma unroll
     for (int i = 0; i < OT; ++i) settle(x[i]);
+    wl += (size_t)sg.block() * D * 64;
+    sg.attn = false;
   }
 
   // ------------------------------------------------------------------ epilogue
@@ -345,23 +380,29 @@ __global__ void __launch_bounds__(64 * quad_waves(D), 1) quad_kernel(const Block
     const f32x16 one[1] = {x[i]};
     if (p.X_out && inrange && owns(i)) store_rows<T, 1>(one, p.X_out, p.X_f32, out_off + 32 * (wave + WV * i), valid, hi);
   }
-  if (SCORE && p.logits) {
+  if (!STACK && !SCORE) return;
+  if (p.logits) {
     // logit = <head_w, flatten(global rows)> + head_b: each wave sums over its own feature tiles
+    const int a = STACK ? 32 * ts + j : (32 * tile + j) % p.m, width = STACK ? 32 : p.m;      // row inside the head's m rows; lanes per logit
     float part = 0.f;
-    if (valid) {
+    if (valid && a < p.m) {
 #pragma unroll
       for (int i = 0; i < OT; ++i) {
         if (!owns(i)) continue;
-        const f32x16 hw = bias_tile(p.head + (size_t)((32 * tile + j) % p.m) * D, wave + WV * i, hi);
+        const f32x16 hw = bias_tile(p.head + (size_t)a * D, wave + WV * i, hi);
 #pragma unroll
         for (int r = 0; r < 16; ++r) part += x[i][r] * hw[r];
       }
     }
     part = row_sums(part, 0.f).x;
-    for (int sft = 1; sft < p.m; sft <<= 1) part += __shfl_xor(part, sft, 64);
+    for (int sft = 1; sft < width; sft <<= 1) part += __shfl_xor(part, sft, 64);
     part += p.head[(size_t)p.m * D];
-    const int cand = (32 * tile + j) / p.m;
-    if (wave == 0 && hi == 0 && (j % p.m) == 0 && cand < p.C) p.logits[(size_t)usr * p.C + cand] = part;
+    if (STACK) {
+      if (tid == 0) p.logits[usr] = part;
+    } else {
+      const int cand = (32 * tile + j) / p.m;
+      if (wave == 0 && hi == 0 && (j % p.m) == 0 && cand < p.C) p.logits[(size_t)usr * p.C + cand] = part;
+    }
   }
 }
 
@@ -371,8 +412,8 @@ int launch_quad(int mode, int win, bool pair, const BlockParams& p, dim3 grid, h
 
 #define LONGER_QUAD_LAUNCH(D, DH, MODEV, WV, LAY) \
   do {                                                                                                \
-    if (p.act == 1) hipLaunchKernelGGL((quad_kernel<D, DH, MODEV, WV, LAY, true>), grid, dim3(64 * quad_waves(D)), 0, stream, p); \
-    else hipLaunchKernelGGL((quad_kernel<D, DH, MODEV, WV, LAY, false>), grid, dim3(64 * quad_waves(D)), 0, stream, p); \
+    if (p.act == 1) hipLaunchKernelGGL((quad_kernel<D, DH, MODEV, WV, LAY, true>), grid, dim3(64 * quad_waves(D) * quad_tiles(MODEV)), 0, stream, p); \
+    else hipLaunchKernelGGL((quad_kernel<D, DH, MODEV, WV, LAY, false>), grid, dim3(64 * quad_waves(D) * quad_tiles(MODEV)), 0, stream, p); \
   } while (0)
 
 template <int D, int DH, int LAY>
@@ -382,12 +423,21 @@ static void launch_quad_score(int win, const BlockParams& p, dim3 grid, hipStrea
   else LONGER_QUAD_LAUNCH(D, DH, MODE_SCORE, 16, LAY);
 }
 
+// (width 64 streams the plain layouts, width 128 the pair layouts unless the pair kernels are switched off)
+template <int D, int DH>
+static int launch_quad_stack(bool pair, const BlockParams& p, dim3 grid, hipStream_t stream) {
+  if constexpr (D == 64) { if (!pair) { LONGER_QUAD_LAUNCH(D, DH, MODE_STACK, 16, QUAD_PLAIN); return 0; } }
+  if constexpr (D == 128) { if (pair) { LONGER_QUAD_LAUNCH(D, DH, MODE_STACK, 16, QUAD_PAIR); return 0; } }
+  return -1;
+}
+
 #define LONGER_QUAD_INSTANTIATE(D, DH)                                                                \
   template <>                                                                                         \
   int launch_quad<D, DH>(int mode, int win, bool pair, const BlockParams& p, dim3 grid, hipStream_t stream) { \
-    if (mode == MODE_ATTN) LONGER_QUAD_LAUNCH(D, DH, MODE_ATTN, 16, QUAD_SPLIT);                      \
+    if (mode == MODE_ATTN) LONGER_QUAD_LAUNCH(D, DH, MODE_ATTN, 16, QUAD_PLAIN);                      \
+    else if (mode == MODE_STACK) { if (launch_quad_stack<D, DH>(pair, p, grid, stream)) return -1; }  \
     else if (pair) { if constexpr (D >= 128) launch_quad_score<D, DH, QUAD_PAIR>(win, p, grid, stream); else return -1; } \
-    else launch_quad_score<D, DH, QUAD_FUSED>(win, p, grid, stream);                                  \
+    else launch_quad_score<D, DH, QUAD_PLAIN>(win, p, grid, stream);                                  \
     return hipGetLastError() == hipSuccess ? 0 : -3;                                                  \
   }
 

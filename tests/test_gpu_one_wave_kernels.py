@@ -71,3 +71,20 @@ def test_many_candidates_equal_the_same_candidates_in_short_lists(d, heads, m, U
         # near to zero one of them happens to come; 3e-2 of it is the parity tests' bar for a batch of logits)
         for got in (lo, lo2):
             assert np.abs(got[:, c] - lr).max() < 3e-2 * np.sqrt(np.mean(lo ** 2)), (c, got[:, c], lr)
+
+
+# The reduced stack of users with at most two tiles (m + k <= 64), bf16, d = 64 / 128: one and two tiles, rows that end inside
+# them, users without a token, every mask and query strategy; and the same model with one query more than two tiles hold
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,heads,m,k,extra", [(64, 4, 4, 32, {}), (64, 2, 1, 5, dict(gmask="causal")), (64, 4, 8, 56, {}), (64, 4, 8, 57, {}),
+                                               (128, 8, 8, 24, dict(k_uniform=10)), (128, 4, 32, 32, dict(gmask="causal")), (128, 8, 2, 31, {}),
+                                               (128, 8, 8, 57, {})])
+def test_stack_of_at_most_two_tiles(d, heads, m, k, extra):
+    import numpy as np
+    import longer_synth as synth
+    from test_gpu_parity import _entry_points, TOL
+    cfg = synth.CONFIGS["C2"].replace(B=5, L=200, d=d, heads=heads, inner_heads=heads, m=m, k_recent=k, n_self=3, ragged=True,
+                                      len_lo=0, len_hi=200, index=73, **extra)
+    case = synth.make_case(cfg)
+    case["lens"][:3] = [200, 0, 9]
+    _entry_points(case, TOL["bf16"], with_inner=False, logits_by_terms=True)
