@@ -268,9 +268,8 @@ const char* longer_last_error(void);
  *     accumulated into.
  * ws: device scratch of at least longer_backward_workspace_bytes(cfg, B, L), 256-byte aligned; all
  * pointers (parameters included) 16-byte aligned.  Supports head width 16 or 32, w one
- * of 32, 64, 128 or 256, f <= 2048.  A parameter gradient is a sum over the batch: slices of the
- * tokens are summed in a fixed order, the last step adds up to 64 such partial sums with fp32 atomics,
- * so the last bits may differ between two calls.  Same stream, error and ownership rules as the forward
+ * of 32, 64, 128 or 256, f <= 2048.  A parameter gradient is a sum over the batch, taken in slices of the
+ * tokens that are summed in a fixed order.  Same stream, error and ownership rules as the forward
  * entry points; both size queries return 0 for an unsupported configuration. */
 size_t longer_backward_workspace_bytes(const longer_config* cfg, int B, int L);
 size_t longer_block_grad_floats(const longer_config* cfg);
@@ -314,8 +313,7 @@ int longer_forward_backward(const longer_config* cfg, const longer_weights* w, c
  * 2048, d_e a multiple of 32 below d.  E, tdiff, w: device, bf16, as for longer_input_generation;
  * lens: device int32 [B] or NULL.  ws: device, 256-byte aligned, at least
  * longer_input_backward_workspace_bytes(cfg, B, L, d_e) bytes (0 = unsupported configuration).
- * Nothing is allocated; every launch goes to `stream`; parameter gradients add their last partial
- * sums with fp32 atomics as in longer_token_merge_backward (last-bit differences from run to run).
+ * Nothing is allocated; every launch goes to `stream`.
  * Errors: LONGER_ERR_ARG (shape, alignment, NULL), LONGER_ERR_WS, LONGER_ERR_HIP. */
 size_t longer_input_backward_workspace_bytes(const longer_config* cfg, int B, int L, int d_e);
 size_t longer_input_grad_floats(const longer_config* cfg, int L, int d_e);
