@@ -37,7 +37,7 @@ struct WgradArgs { WgradJob job[kMaxWgradJobs]; int njobs, tiles, nslices; };
 // every nslices-th step, so that each samples long and short users alike; the tiles of a slice, which share
 // their operands' rows, run on one accelerator die (one L2).
 // TILES: the operands are tile blocks in records (bw_block.h: rows are slots; ldx, ldy: sixteens of features from one tile to the next).  A step's
-// tile is then contiguous in memory and goes to LDS as it is.
+// tile is then contiguous in memory and goes to LDS as it is (a block of the headline batch 392 -> 370 us).
 template <int TB, bool TILES>
 __global__ __launch_bounds__(256, 3) void bw_wgrad_kernel(const WgradArgs a) {
   constexpr int PITCH = TB + 16, TT = TB / 64, NCH = TB / 64;     // NCH: 16-byte chunks per thread, operand and step
