@@ -11,7 +11,7 @@
 // the FFN's middle, three products back, attention back, two LayerNorms back) a block of the headline batch
 // (512 000 rows of width 128) moved 18.8 KB per token beside its parameter gradients in 2.1 ms; here it is 7.8-8.2 KB
 // in 0.95 ms: 4.4 TB/s, where a large copy reaches 5.0.  The matrix and vector instructions alone would take about
-// half of that (744 products and 9 000 vector instructions per tile, two waves per SIMD); the waves wait for memory.
+// half of that (808 products and 9 500 vector instructions per tile, two waves per SIMD); the waves wait for memory.
 //
 // Tile blocks.  A tensor of F features that the parameter gradients read is stored as [F / 16][1 KiB] per tile: 16
 // features of 32 tokens, 32 bytes per token, as the lanes hold them (lane half hi: features 4 hi .. + 3 and
@@ -113,6 +113,17 @@ __device__ __forceinline__ void place_window(const float (&x)[W], const uint32_t
     }
     op[g] = __builtin_bit_cast(bf16x8, v);
   }
+}
+
+// Probabilities and score gradients go into their products as two bf16 operands, the value and what its rounding left
+// (16 significant bits between them): the second pair of products costs less than the rounding did in accuracy.
+template <int W>
+__device__ __forceinline__ void place_split(const float (&x)[W], const uint32_t (&wmask)[16 / W], bf16x8 (&op)[2], bf16x8 (&rest)[2]) {
+  float lo[W];
+#pragma unroll
+  for (int c = 0; c < W; ++c) lo[c] = x[c] - (float)(__bf16)x[c];
+  place_window<W>(x, wmask, op);
+  place_window<W>(lo, wmask, rest);
 }
 
 template <int NT>
@@ -349,11 +360,15 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
         float pr[W], m, l;
         probabilities(S, pr, m, l);
         const float inv = l > 0.f ? 1.f / l : 0.f;
-        bf16x8 pop[2];
-        place_window<W>(pr, wmask, pop);
+        bf16x8 pop[2], plo[2];
+        place_split<W>(pr, wmask, pop, plo);
         f32x16 acc = splat16(0.f);
 #pragma unroll
-        for (int g = 0; g < 2; ++g) acc = E::mma(turn_out(2, g), pop[g], acc);
+        for (int g = 0; g < 2; ++g) {
+          const bf16x8 vt = turn_out(2, g);
+          acc = E::mma(vt, plo[g], acc);
+          acc = E::mma(vt, pop[g], acc);
+        }
 #pragma unroll
         for (int r = 0; r < 16 / HPT; ++r) o[16 / HPT * hh + r] = acc[16 / HPT * hh + r] * inv;
       }
@@ -491,11 +506,15 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
         }
 #pragma unroll
         for (int c = 0; c < W; ++c) pr[c] *= dp[c] - dsum;
-        bf16x8 sop[2];
-        place_window<W>(pr, wmask, sop);
+        bf16x8 sop[2], slo[2];
+        place_split<W>(pr, wmask, sop, slo);
         f32x16 acc = splat16(0.f);
 #pragma unroll
-        for (int g = 0; g < 2; ++g) acc = E::mma(turn_out(0, g), sop[g], acc);
+        for (int g = 0; g < 2; ++g) {
+          const bf16x8 kt = turn_out(0, g);
+          acc = E::mma(kt, slo[g], acc);
+          acc = E::mma(kt, sop[g], acc);
+        }
 #pragma unroll
         for (int r = 0; r < RH; ++r) dq[RH * hh + r] = acc[RH * hh + r] * scale;
       }
@@ -521,14 +540,26 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
             dp[c] = pr[c] * (dp[c] - ds[e]);
           }
         }
-        bf16x8 pop[2], sop[2];
-        place_window<W>(pr, wmask, pop);
-        place_window<W>(dp, wmask, sop);
         f32x16 accv = splat16(0.f), acck = splat16(0.f);
+        {
+          bf16x8 pop[2], plo[2];
+          place_split<W>(pr, wmask, pop, plo);
 #pragma unroll
-        for (int g = 0; g < 2; ++g) {
-          accv = E::mma(turn_out(2, g), pop[g], accv);
-          acck = E::mma(turn_out(1, g), sop[g], acck);
+          for (int g = 0; g < 2; ++g) {
+            const bf16x8 dt = turn_out(2, g);
+            accv = E::mma(dt, plo[g], accv);
+            accv = E::mma(dt, pop[g], accv);
+          }
+        }
+        {
+          bf16x8 sop[2], slo[2];
+          place_split<W>(dp, wmask, sop, slo);
+#pragma unroll
+          for (int g = 0; g < 2; ++g) {
+            const bf16x8 qt = turn_out(1, g);
+            acck = E::mma(qt, slo[g], acck);
+            acck = E::mma(qt, sop[g], acck);
+          }
         }
 #pragma unroll
         for (int r = 0; r < RH; ++r) {
