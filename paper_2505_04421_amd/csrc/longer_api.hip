@@ -617,13 +617,13 @@ struct AttnIO {
 };
 
 // Launches with few tiles: a tile's chain of products is all that counts, so four or eight waves share it (quad_kernel.h).
-// The line is where every compute unit has its workgroups (two of four waves, or one of eight at width 256) at once.
-// Four layers of scoring, microseconds with it / without: width 64 at 50, 250, 512 tiles 24 / 38, 26 / 39, 34 / 41;
-// width 128 at 25, 256, 512 tiles 53 / 107, 59 / 110, 81 / 115 (1008 tiles without it: 131); cold weights and caches, width 128,
-// 25 tiles 59 / 107.  Width 256, cold, 128 tiles: 45 less in a cache build and first list of 772.  A cache build (two layers of
-// attention), width 128 at 32, 256, 512 tiles 106 / 135, 117 / 148, 160 / 174; width 256 at 64, 256, 512 tiles 202 / 279,
-// 278 / 351, 531 / 480.
-static bool quad_pays(const Shape& s, long long tiles) { return s.quad && tiles <= (s.D >= 256 ? 256 : 512); }
+// The line is where every compute unit has its workgroups at once (two of four waves; one of eight at width 256), or another
+// round of them still costs less than the other kernels.  Four layers of scoring, microseconds with it / without: width 64 at 25,
+// 256, 512, 768 tiles 22 / 38, 24 / 38, 33 / 40, 68 / 42; width 128 at 25, 256, 512, 768, 1008 tiles 41 / 107, 47 / 110, 72 / 116, 111 / 123,
+// 138 / 132; width 256 at 25, 256, 512, 768 tiles 91 / 224, 111 / 224, 224 / 233, 325 / 253.  A cache build (two layers of
+// attention), width 64 at 16, 256 tiles 38 / 46, 59 / 67; width 128 at 64, 512, 768, 1024 tiles 95 / 137, 143 / 172, 205 / 212,
+// 252 / 242; width 256 at 32, 256, 512 tiles 170 / 279, 259 / 348, 439 / 479.
+static bool quad_pays(const Shape& s, long long tiles) { return s.quad && tiles <= (s.D == 128 ? 768 : 512); }
 
 static int run_layer(const longer_config* c, const Shape& s, const char* packed_blk, const int32_t* lens, int B, int L,
                      const AttnIO& io, bool do_attn, hipStream_t st) {
@@ -677,10 +677,11 @@ static int run_stack(const longer_config* c, const Shape& s, const char* packed_
   p.X_out = io.X_out; p.X_f32 = io.X_f32; p.X_ustride = io.X_ustride;
   p.logits = io.logits; p.head = io.head;
   StageScope scope(ST_ATTN, st);
-  // At most two tiles a user: eight waves for them instead of one or two waves each, as long as the users are one or two
-  // rounds of workgroups.  Whole forward pass (L = 400, K = 8, three or four layers), microseconds with it / without: width 64, m + k = 24, at
-  // 1, 128, 256, 512 users 38 / 43, 46 / 52, 60 / 66, 98 / 92; width 128, m + k = 58, at 1, 128, 512 users 100 / 123, 130 / 157, 356 / 400.
-  if (s.quad && s.D <= 128 && s.n <= 64 && B <= (s.D == 64 ? 256 : 512)) {
+  // At most two tiles a user: eight waves for them instead of one or two waves each; at width 64 as long as the users are
+  // one round of workgroups.  Whole forward pass (L = 400, K = 8, three or four layers), microseconds with it / without: width
+  // 64, m + k = 54, at 1, 128, 256, 384, 1024 users 39 / 46, 48 / 55, 63 / 70, 93 / 87, 185 / 173; width 128, m + k = 58, at 1, 128, 512,
+  // 1024 users 90 / 123, 124 / 157, 341 / 400, 624 / 728.
+  if (s.quad && s.D <= 128 && s.n <= 64 && (s.D == 128 || B <= 256)) {
     if (s.quad(MODE_STACK, 16, pair_stack(s), p, dim3(B), st)) return fail(LONGER_ERR_HIP, "stack launch failed");
     return 0;
   }

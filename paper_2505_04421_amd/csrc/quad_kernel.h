@@ -12,6 +12,13 @@
 // share no weights, so each fetches its fragments from L2 itself, from the same packed streams as the other kernels
 // (their segments are found by index).  With many tiles the streams' traffic and the idle matrix pipes cost more than the
 // shorter chain gains: the rule is at quad_pays in longer_api.hip.
+//
+// What bounds it: at width 128 the vector work of the attention (a third of the chain) and the two products of a hidden
+// chunk; at width 256 the weights' way into the compute unit, 64 bytes a cycle (half of a layer's time).  The waves never wait for
+// a weight fragment that they could have asked for earlier: with each product's fragments requested when it began, four
+// layers of scoring took 53 us for 25 tiles at width 128 and 255 us for 128 tiles over 20 key tiles at width 256; requested
+// behind the fragments of the product before, and four key tiles ahead, 41 and 105 us.  (Bringing a block's stream into the
+// die's L2 one block ahead, each workgroup its share, cost more than it gave: 51 and 200 us.)
 #pragma once
 #include "block_kernel.h"
 
@@ -39,35 +46,37 @@ struct QuadSegs {
   }
   __device__ __forceinline__ int w2(int c) const {
     if (LAYOUT == QUAD_PAIR) return w1(c) + 2;
-    return ffn() + (ffn_skewed(2, D) ? (c < NC - 1 ? 3 + 2 * c : 2 * NC) : 2 * c + 1);
+    return ffn() + (ffn_skewed(2, D) ? min(3 + 2 * c, 2 * NC) : 2 * c + 1);
   }
   __device__ __forceinline__ int block() const { return 2 + (attn ? 2 : 4) * NT + 2 * NC; }
 };
 
 template <int D, int DH, int MODE, int W, int LAYOUT, bool RELU>
-__global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), 1) quad_kernel(const BlockParams p) {
+__global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_waves(D) * quad_tiles(MODE) == 4 ? 2 : 1) quad_kernel(const BlockParams p) {
   using T = __bf16;
   using E = ET<T>;
   using grp = typename E::grp;
   using hgrp = typename E::hgrp;
   constexpr int WV = quad_waves(D), TS = quad_tiles(MODE), kThr = 64 * WV * TS;
-  constexpr int NT = D / 32, NG = D / 16, OT = (NT + WV - 1) / WV, HPT = 32 / DH, GPH = DH / 16;
+  constexpr int NT = D / 32, NG = D / 16, HPT = 32 / DH, GPH = DH / 16;
   constexpr bool SCORE = MODE == MODE_SCORE, STACK = MODE == MODE_STACK;
   static_assert(SCORE || STACK || MODE == MODE_ATTN, "quad kernel modes");
-  static_assert(!STACK || OT == 1, "the stack's K / V hand-over takes one feature tile per wave");
-  __shared__ grp ops_[TS][NG][64];                   // per tile, [group][lane]: operand of the next products
+  static_assert(NT <= WV, "a wave owns at most one feature tile");
+  __shared__ grp ops_[TS][2][NG][64];                // per tile, [normalised rows, attention output][group][lane]: operand of the next products
   __shared__ hgrp hid_[TS][2][WV][2][64];            // activated hidden chunks: [parity][wave][group][lane]
-  __shared__ float2 sums_[TS][WV][64];
+  __shared__ float2 sums_[TS][2][WV][64];            // row sums: [first, second LayerNorm][wave][lane]
   __shared__ grp kvl[STACK ? TS : 1][STACK ? NT : 1][2][2][64];      // self layers: [key tile][feature tile][K, V][group][lane]
   __shared__ f32x4 vecl[D * 4];                      // the block's fp32 vectors (at most one segment)
-  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 31, hi = lane >> 5;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int tid = threadIdx.x, lane = tid & 63, j = lane & 31, hi = lane >> 5;
   const int ts = TS == 1 ? 0 : wv / WV, wave = TS == 1 ? wv : wv % WV;     // tile of the workgroup, wave of the tile
   auto& ops = ops_[ts];
   auto& hid = hid_[ts];
   auto& sums = sums_[ts];
   const int NC = p.FF / 32;
   QuadSegs<LAYOUT, D> sg = {NC, !SCORE};               // (the stack's first block is the cross layer's attention half)
-  auto owns = [&](int i) { return NT >= WV || wave + WV * i < NT; };
+  const bool own = NT >= WV || wave < NT;              // the wave has a feature tile: ft
+  const int ft = NT >= WV ? wave : wave % NT;          // (width 64: waves 2 and 3 share in the hidden chunks alone; their rows go nowhere)
 
   // ------------------------------------------------------------------ rows
   bool valid, inrange;
@@ -80,14 +89,11 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), 1) quad
   uint32_t wmask[16 / W];
 #pragma unroll
   for (int w = 0; w < 16 / W; ++w) { wmask[w] = widx == w ? 0xffffffffu : 0u; asm("" : "+v"(wmask[w])); }
-  f32x16 x[OT];
+  f32x16 x;
   auto load_own = [&](const void* base, int f32, long long off) {
-#pragma unroll
-    for (int i = 0; i < OT; ++i) {
-      f32x16 one[1];
-      load_rows<T, 1>(one, base, f32, off + 32 * (wave + WV * i), valid && owns(i), hi);
-      x[i] = one[0];
-    }
+    f32x16 one[1];
+    load_rows<T, 1>(one, base, f32, off + 32 * wave, valid && own, hi);
+    x = one[0];
   };
   if (SCORE) {
     // (users are dealt to the accelerator dies like in the other kernels; a few users' tiles go to all dies)
@@ -135,92 +141,118 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), 1) quad
   }
 
   const char* wl = p.wbase;                            // the current block's stream
-  // The chain touches every weight once, and a first touch of a die's L2 takes several times as long as a hit: the
-  // workgroups of a die (every eighth) bring the whole stream in at once, each its share.
-  {
-    const unsigned peers = (gridDim.x + 7 - (blockIdx.x & 7)) / 8;
-    const unsigned lines = (unsigned)((sg.block() + (p.n_layers - 1) * (2 + 4 * NT + 2 * NC)) * (D / 2));
-    unsigned keep = 0;
-    for (unsigned i = (blockIdx.x >> 3) * kThr + tid; i < lines; i += peers * kThr) keep |= *reinterpret_cast<const unsigned*>(wl + (size_t)i * 128);
-    asm volatile("" :: "v"(keep));
-  }
-  auto frag = [&](int seg, int s) -> grp { return *reinterpret_cast<const grp*>(wl + ((size_t)(seg * NG + s) * 64 + lane) * 16); };
-  // acc + (segment seg: 32 result features) b; swapped: result with lane = feature
-  auto product = [&](f32x16 acc, int seg, const grp (&b)[NG], bool swapped) -> f32x16 {
-    grp f[NG];
-#pragma unroll
-    for (int s = 0; s < NG; ++s) f[s] = frag(seg, s);
-#pragma unroll
-    for (int s = 0; s < NG; ++s) acc = swapped ? E::mma(b[s], f[s], acc) : E::mma(f[s], b[s], acc);
-    return acc;
-  };
   const VecLayout vl{D, p.FF};
   const float* vec = reinterpret_cast<const float*>(vecl);
-  // row sums of all waves (two numbers per row); the barriers also say that everybody is done with `ops`
-  auto row_sums = [&](float a, float b) -> float2 {
-    a = sum_halves(a); b = sum_halves(b);
-    __syncthreads();
-    sums[wave][lane] = make_float2(a, b);
+  // A product's weight fragments are requested while the product ahead of it runs: each takes the registers of the fragment
+  // that was just used.  (The compiler moves no load across a barrier.)  Order of a wave's products: Q (K, V) of its feature
+  // tile, its tile of the output projection, then W1 of a hidden chunk and its tile's rows of W2 for all waves' chunks in turn.
+  constexpr int NF = NG > 2 * WV ? NG : 2 * WV;
+  constexpr bool HOLD = D <= 128;                      // (width 256: no registers for them through the attention)
+  grp fr[NF];
+  typedef __attribute__((address_space(1))) const char gchar;
+  typedef __attribute__((address_space(1))) const grp ggrp;
+  unsigned lane16 = (unsigned)lane * 16u;
+  // what is worked out from these is worked out again: kept through the layers it would cost the registers of the fragments
+  auto afresh = [&] {
+    asm volatile("" : "+v"(tid));
+    lane = tid & 63; j = lane & 31; hi = lane >> 5; lane16 = (unsigned)lane * 16u;
+  };
+  auto segment = [&](const char* w, int seg) -> gchar* {       // (wave-uniform: a scalar base, the lane's part an offset)
+    gchar* q = (gchar*)(w + (size_t)seg * (NG * 1024));
+    asm("" : "+s"(q));
+    return q;
+  };
+  auto request = [&](gchar* q) {
+#pragma unroll
+    for (int s = 0; s < NG; ++s) fr[s] = *(ggrp*)(q + (lane16 + (unsigned)s * 1024u));
+  };
+  // (products and loads stay in this order: hoisted loads would need a second set of registers)
+  auto in_order = [] { __builtin_amdgcn_sched_barrier(0x486); };
+  // acc + (a segment's 32 result features) b; swapped: result with lane = feature; the fragments of segment `next` follow
+  auto product = [&](f32x16 acc, const grp (&b)[NG], bool swapped, bool more, gchar* next) -> f32x16 {
+#pragma unroll
+    for (int s = 0; s < NG; ++s) {
+      acc = swapped ? E::mma(b[s], fr[s], acc) : E::mma(fr[s], b[s], acc);
+      if (more) fr[s] = *(ggrp*)(next + (lane16 + (unsigned)s * 1024u));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    return acc;
+  };
+  constexpr int VQ = (D * 4 + kThr - 1) / kThr;        // the block's vectors: this thread's share, on its way to LDS
+  f32x4 vq[VQ];
+  auto request_vec = [&](const char* w) {
+    const int n = (9 * D + p.FF) / 4;
+#pragma unroll
+    for (int i = 0; i < VQ; ++i) { const int c = tid + kThr * i; vq[i] = reinterpret_cast<const f32x4*>(w)[c < n ? c : 0]; }
+  };
+  request_vec(wl);
+  request(segment(wl, sg.q(ft)));
+  // row sums of all waves (two numbers per row)
+  auto row_sums = [&](int which, float a, float b) -> float2 {
+    sums[which][wave][lane] = make_float2(sum_halves(a), sum_halves(b));
     __syncthreads();
     float2 r = make_float2(0.f, 0.f);
 #pragma unroll
-    for (int w = 0; w < WV; ++w) { const float2 q = sums[w][lane]; r.x += q.x; r.y += q.y; }
+    for (int w = 0; w < WV; ++w) { const float2 q = sums[which][w][lane]; r.x += q.x; r.y += q.y; }
     return r;
   };
+  auto take = [&](int which, grp (&b)[NG]) {
+#pragma unroll
+    for (int g = 0; g < NG; ++g) b[g] = ops[which][g][lane];
+  };
   // LayerNorm of the rows as the next products' operand, in every wave
-  auto normalise = [&](int og, int ob, grp (&b)[NG]) {
+  auto normalise = [&](int which, int og, int ob, grp (&b)[NG]) {
     float s = 0.f, q = 0.f;
+    if (own) {
 #pragma unroll
-    for (int i = 0; i < OT; ++i) {
-      if (!owns(i)) continue;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) { s += x[i][r]; q = fmaf(x[i][r], x[i][r], q); }
+      for (int r = 0; r < 16; ++r) { s += x[r]; q = fmaf(x[r], x[r], q); }
     }
-    const float2 t = row_sums(s, q);
+    const float2 t = row_sums(which, s, q);
     const float mean = t.x * (1.0f / D), var = fmaxf(t.y * (1.0f / D) - mean * mean, 0.f);
     const float rstd = __builtin_amdgcn_rsqf(var + p.eps), shift = -mean * rstd;
-#pragma unroll
-    for (int i = 0; i < OT; ++i) {
-      if (!owns(i)) continue;
-      const f32x16 g = bias_tile(vec + og, wave + WV * i, hi), c = bias_tile(vec + ob, wave + WV * i, hi);
+    if (own) {
+      const f32x16 g = bias_tile(vec + og, wave, hi), c = bias_tile(vec + ob, wave, hi);
       f32x16 y;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) y[r] = fmaf(fmaf(x[i][r], rstd, shift), g[r], c[r]);
+      for (int r = 0; r < 16; ++r) y[r] = fmaf(fmaf(x[r], rstd, shift), g[r], c[r]);
 #pragma unroll
-      for (int g2 = 0; g2 < 2; ++g2) ops[2 * (wave + WV * i) + g2][lane] = E::pack(y, g2);
+      for (int g2 = 0; g2 < 2; ++g2) ops[0][2 * wave + g2][lane] = E::pack(y, g2);
     }
     __syncthreads();
-#pragma unroll
-    for (int g = 0; g < NG; ++g) b[g] = ops[g][lane];
+    take(0, b);
   };
 
+  // Areas of LDS are written once a layer and each write has a barrier of that layer between itself and the last reader:
+  // `vecl` the last hidden chunk's, `sums` and `ops` the other LayerNorm's and the attention output's.
   for (int layer = 0; layer < p.n_layers; ++layer) {
     const bool selfl = STACK && layer > 0;             // K and V made here, handed to the user's other tile through LDS
-    if (layer > 0) __syncthreads();                    // nobody still reads the previous block's vectors
-    for (int i = tid; i < (9 * D + p.FF) / 4; i += kThr) vecl[i] = reinterpret_cast<const f32x4*>(wl)[i];
-    __syncthreads();
+    const bool last = layer + 1 == p.n_layers;
+    afresh();
+    const char* wnext = wl + (size_t)sg.block() * D * 64;
+#pragma unroll
+    for (int i = 0; i < VQ; ++i) { const int c = tid + kThr * i; if (c < D * 4) vecl[c] = vq[i]; }
     {
       grp xn[NG];
-      normalise(vl.ln1_g(), vl.ln1_b(), xn);
-      grp oo[OT][2];
-#pragma unroll
-      for (int i = 0; i < OT; ++i) {
-        const int ft = wave + WV * i;
-        f32x16 aq, ak, av;
-        if (owns(i)) {
-          aq = product(bias_tile(vec + vl.bq(), ft, hi), sg.q(ft), xn, false);
-          if (SCORE || selfl) {
-            ak = product(splat16(0.f), sg.k(ft), xn, false);     // no b_K, no b_V: see block_kernel.h
-            av = product(splat16(0.f), sg.v(ft), xn, true);
-          }
-          if (selfl) {
-            settle(ak); settle(av);
-#pragma unroll
-            for (int g = 0; g < 2; ++g) { kvl[ts][ft][0][g][lane] = E::pack(ak, g); kvl[ts][ft][1][g][lane] = E::pack(av, g); }
-          }
+      normalise(0, vl.ln1_g(), vl.ln1_b(), xn);
+      grp oo[2];
+      f32x16 aq, ak, av;
+      if (own) {
+        if (SCORE || selfl) {
+          aq = product(bias_tile(vec + vl.bq(), wave, hi), xn, false, true, segment(wl, sg.k(wave)));
+          ak = product(splat16(0.f), xn, false, true, segment(wl, sg.v(wave)));   // no b_K, no b_V: see block_kernel.h
+          av = product(splat16(0.f), xn, true, HOLD, segment(wl, sg.o(wave)));
+        } else {
+          aq = product(bias_tile(vec + vl.bq(), wave, hi), xn, false, HOLD, segment(wl, sg.o(wave)));
         }
-        if (selfl) __syncthreads();
-        if (!owns(i)) continue;
+        if (selfl) {
+          settle(ak); settle(av);
+#pragma unroll
+          for (int g = 0; g < 2; ++g) { kvl[ts][wave][0][g][lane] = E::pack(ak, g); kvl[ts][wave][1][g][lane] = E::pack(av, g); }
+        }
+      }
+      if (selfl) __syncthreads();
+      if (own) {
+        __builtin_amdgcn_sched_barrier(0);
         settle(aq);
         aq *= p.scale_l2e;
         grp qop[2];
@@ -230,7 +262,8 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), 1) quad
         f32x16 acc[HPT];
 #pragma unroll
         for (int hh = 0; hh < HPT; ++hh) { mrun[hh] = kNegBig; lrun[hh] = 0.f; acc[hh] = splat16(0.f); }
-        // stored K/V fragments (wave-uniform user, scalar loop control); two key tiles on their way
+        // stored K/V fragments (wave-uniform user, scalar loop control); KD key tiles on their way
+        constexpr int KD = STACK ? 2 : 4;
         const char* kb; const char* vb; int nkt, rlo = 0, rhi = 0;
         const int tuu = __builtin_amdgcn_readfirstlane(Tu);
         if (selfl) {
@@ -249,22 +282,23 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), 1) quad
           }
           if (!valid) rhi = rlo;
         }
-        grp kn[2][2], vn[2][2];
+        if (nkt == 0) kb = vb = wl;                    // (readable: requests are made without asking, so that no value lives on through a branch)
+        grp kn[KD][2], vn[KD][2];
         auto fetch = [&](int kt, int b) {
           if (selfl) {
 #pragma unroll
-            for (int g = 0; g < 2; ++g) { kn[b][g] = kvl[STACK ? kt : 0][STACK ? ft : 0][0][g][lane]; vn[b][g] = kvl[STACK ? kt : 0][STACK ? ft : 0][1][g][lane]; }
+            for (int g = 0; g < 2; ++g) { kn[b][g] = kvl[STACK ? kt : 0][STACK ? wave : 0][0][g][lane]; vn[b][g] = kvl[STACK ? kt : 0][STACK ? wave : 0][1][g][lane]; }
             return;
           }
-          const size_t fo = ((size_t)(kt * NT + ft) * 2) * 1024 + lane * 16;
+          const size_t fo = ((size_t)(kt * NT + wave) * 2) * 1024 + lane * 16;
 #pragma unroll
           for (int g = 0; g < 2; ++g) {
             kn[b][g] = *reinterpret_cast<const grp*>(kb + fo + g * 1024);
             vn[b][g] = *reinterpret_cast<const grp*>(vb + fo + g * 1024);
           }
         };
-        if (nkt > 0) fetch(0, 0);
-        if (nkt > 1) fetch(1, 1);
+#pragma unroll
+        for (int b = 0; b < KD; ++b) fetch(min(b, max(nkt - 1, 0)), b);
         if (SCORE) {   // keys of the lane's own tile: the candidate's own globals
           grp kop[2], vop[2];
 #pragma unroll
@@ -286,26 +320,24 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), 1) quad
           const uint32_t ab = (bits >> (4 * hi)) & kTileBits;
           const bool none = __builtin_amdgcn_ballot_w64(ab != 0) == 0;           // nobody sees any of these keys
           const bool full = __builtin_amdgcn_ballot_w64(ab != kTileBits) == 0;   // everybody sees all of them
-          grp kf[2], vf[2];
-#pragma unroll
-          for (int g = 0; g < 2; ++g) { kf[g] = kn[b][g]; vf[g] = vn[b][g]; }
-          if (kt + 2 < nkt) fetch(kt + 2, b);
-          if (none) return;
+          if (none) { if (kt + KD < nkt) fetch(kt + KD, b); return; }
           const f32x16 vis = full ? splat16(0.f) : mask_tile(ab);
 #pragma unroll
           for (int hh = 0; hh < HPT; ++hh) {
             f32x16 S = vis;
 #pragma unroll
-            for (int g2 = 0; g2 < GPH; ++g2) S = E::mma(kf[hh * GPH + g2], qop[hh * GPH + g2], S);
+            for (int g2 = 0; g2 < GPH; ++g2) S = E::mma(kn[b][hh * GPH + g2], qop[hh * GPH + g2], S);
             grp pop[2];
             softmax_step<T, false>(S, 0u, mrun[hh], lrun[hh], acc[hh], pop);
 #pragma unroll
-            for (int g = 0; g < 2; ++g) acc[hh] = E::mma(vf[g], pop[g], acc[hh]);
+            for (int g = 0; g < 2; ++g) acc[hh] = E::mma(vn[b][g], pop[g], acc[hh]);
           }
+          if (kt + KD < nkt) fetch(kt + KD, b);
         };
-        for (int kt = 0; kt < nkt; kt += 2) {
-          key_tile(kt, 0);
-          if (kt + 1 < nkt) key_tile(kt + 1, 1);
+        for (int kt = 0; kt < nkt; kt += KD) {
+#pragma unroll
+          for (int b = 0; b < KD; ++b)
+            if (kt + b < nkt) key_tile(kt + b, b);
         }
         f32x16 o;
         float inv[HPT];
@@ -314,87 +346,77 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), 1) quad
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[r] = acc[HPT == 1 ? 0 : r / 8][r] * inv[HPT == 1 ? 0 : r / 8];
 #pragma unroll
-        for (int g = 0; g < 2; ++g) oo[i][g] = E::pack(o, g);
+        for (int g = 0; g < 2; ++g) ops[1][2 * wave + g][lane] = E::pack(o, g);
       }
-      // (every wave took the normalised rows out of `ops` before its attention; this barrier says so)
+      if (!HOLD || !own) request(segment(wl, sg.o(ft)));
       __syncthreads();
-#pragma unroll
-      for (int i = 0; i < OT; ++i) {
-        if (!owns(i)) continue;
-#pragma unroll
-        for (int g = 0; g < 2; ++g) ops[2 * (wave + WV * i) + g][lane] = oo[i][g];
-      }
-      __syncthreads();
-#pragma unroll
-      for (int g = 0; g < NG; ++g) xn[g] = ops[g][lane];
-#pragma unroll
-      for (int i = 0; i < OT; ++i) {
-        if (!owns(i)) continue;
-        x[i] += bias_tile(vec + vl.bo(), wave + WV * i, hi);
-        x[i] = product(x[i], sg.o(wave + WV * i), xn, false);
-        settle(x[i]);
-      }
+      take(1, xn);
+      x += bias_tile(vec + vl.bo(), ft, hi);
+      x = product(x, xn, false, true, segment(wl, sg.w1(min(wave, NC - 1))));
+      settle(x);
     }
     grp xn[NG];
-    normalise(vl.ln2_g(), vl.ln2_b(), xn);
-#pragma unroll
-    for (int i = 0; i < OT; ++i)
-      if (owns(i)) x[i] += bias_tile(vec + vl.b2(), wave + WV * i, hi);
+    afresh();
+    request_vec(last ? wl : wnext);
+    normalise(1, vl.ln2_g(), vl.ln2_b(), xn);
+    x += bias_tile(vec + vl.b2(), ft, hi);
     for (int c0 = 0, par = 0; c0 < NC; c0 += WV, par ^= 1) {
-      const int c = c0 + wave;
-      if (c < NC) {
-        f32x16 ah = product(bias_tile(vec + vl.b1(), c, hi), sg.w1(c), xn, false);
-        settle(ah);
+      const int c = min(c0 + wave, NC - 1);            // (a wave without a chunk goes through another's and hands in zeros)
+      auto request_w2 = [&](int s) {                   // fragment s % 2 of chunk c0 + s / 2 for this wave's tile
+        fr[s] = *(ggrp*)(segment(wl + 2048 * ft, sg.w2(min(c0 + s / 2, NC - 1))) + (lane16 + (unsigned)(s & 1) * 1024u));
+      };
 #pragma unroll
-        for (int g = 0; g < 2; ++g) {
-          f16x8 y;     // ah holds x / kFfnScale; to fp16 toward zero, then the packed activation
+      for (int s = NG; s < 2 * WV; ++s) request_w2(s);
+      f32x16 ah = bias_tile(vec + vl.b1(), c, hi);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const f16x2 y2 = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(ah[8 * g + 2 * e], ah[8 * g + 2 * e + 1]));
-            y[2 * e] = y2[0]; y[2 * e + 1] = y2[1];
-          }
-          hid[par][wave][g][lane] = RELU ? __builtin_elementwise_max(y, (f16x8)((_Float16)0.f)) : gelu_quarter_h8(y);
-        }
+      for (int s = 0; s < NG; ++s) {
+        ah = E::mma(fr[s], xn[s], ah);
+        request_w2(s);
+        __builtin_amdgcn_sched_barrier(0);
       }
+      settle(ah);
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        f16x8 y;     // ah holds x / kFfnScale; to fp16 toward zero, then the packed activation
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const f16x2 y2 = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(ah[8 * g + 2 * e], ah[8 * g + 2 * e + 1]));
+          y[2 * e] = y2[0]; y[2 * e + 1] = y2[1];
+        }
+        y = RELU ? __builtin_elementwise_max(y, (f16x8)((_Float16)0.f)) : gelu_quarter_h8(y);
+        if (c0 + wave >= NC) y = (f16x8)((_Float16)0.f);
+        hid[par][wave][g][lane] = y;
+      }
+      // what follows on these chunks' second product: the next hidden chunk, or the next block's first
+      gchar* next = segment(wl, sg.w1(min(c0 + WV + wave, NC - 1)));
+      if (c0 + WV >= NC && !last) next = segment(wnext, QuadSegs<LAYOUT, D>{NC, false}.q(ft));
       __syncthreads();          // (the other parity was last read ahead of the barrier before)
 #pragma unroll
-      for (int i = 0; i < OT; ++i) {
-        if (!owns(i)) continue;
-#pragma unroll
-        for (int k = 0; k < WV; ++k) {
-          if (c0 + k >= NC) break;
-#pragma unroll
-          for (int g = 0; g < 2; ++g) x[i] = E::mma_h(frag(sg.w2(c0 + k), 2 * (wave + WV * i) + g), hid[par][k][g][lane], x[i]);
-        }
+      for (int s = 0; s < 2 * WV; ++s) {
+        x = E::mma_h(fr[s], hid[par][s / 2][s & 1][lane], x);
+        if (s < NG) fr[s] = *(ggrp*)(next + (lane16 + (unsigned)s * 1024u));
+        in_order();
       }
     }
-#pragma unroll
-    for (int i = 0; i < OT; ++i) settle(x[i]);
-    wl += (size_t)sg.block() * D * 64;
+    settle(x);
+    wl = wnext;
     sg.attn = false;
   }
 
   // ------------------------------------------------------------------ epilogue
-#pragma unroll
-  for (int i = 0; i < OT; ++i) {
-    const f32x16 one[1] = {x[i]};
-    if (p.X_out && inrange && owns(i)) store_rows<T, 1>(one, p.X_out, p.X_f32, out_off + 32 * (wave + WV * i), valid, hi);
-  }
+  const f32x16 one[1] = {x};
+  if (p.X_out && inrange && own) store_rows<T, 1>(one, p.X_out, p.X_f32, out_off + 32 * wave, valid, hi);
   if (!STACK && !SCORE) return;
   if (p.logits) {
     // logit = <head_w, flatten(global rows)> + head_b: each wave sums over its own feature tiles
     const int a = STACK ? 32 * ts + j : (32 * tile + j) % p.m, width = STACK ? 32 : p.m;      // row inside the head's m rows; lanes per logit
     float part = 0.f;
-    if (valid && a < p.m) {
+    if (valid && a < p.m && own) {
+      const f32x16 hw = bias_tile(p.head + (size_t)a * D, wave, hi);
 #pragma unroll
-      for (int i = 0; i < OT; ++i) {
-        if (!owns(i)) continue;
-        const f32x16 hw = bias_tile(p.head + (size_t)a * D, wave + WV * i, hi);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) part += x[i][r] * hw[r];
-      }
+      for (int r = 0; r < 16; ++r) part += x[r] * hw[r];
     }
-    part = row_sums(part, 0.f).x;
+    part = row_sums(0, part, 0.f).x;
     for (int sft = 1; sft < width; sft <<= 1) part += __shfl_xor(part, sft, 64);
     part += p.head[(size_t)p.m * D];
     if (STACK) {

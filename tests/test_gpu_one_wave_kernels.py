@@ -26,13 +26,14 @@ def test_parity_with_the_pair_kernels_switched_off():
     assert " passed" in tail and "failed" not in tail, tail
 
 
-# Scoring more candidates than the few-tiles kernels take (512 tiles, 256 at d = 256) runs the same rows through the
+# Scoring more candidates than the few-tiles kernels take (512 tiles, 768 at d = 128) runs the same rows through the
 # two-wave (d = 128 / 256) or one-wave (d = 64) kernels: both against the oracle for the candidates at the ends of the
 # list, and against each other, a call of 40 candidates at a time, for all of them.  Users dealt to the dies (8) and not (3);
 # one row more than whole tiles, rows that end inside a tile, m = 32 (one candidate fills a tile).
 @pytest.mark.gpu
 @pytest.mark.parametrize("d,heads,m,U,C", [(64, 4, 4, 3, 1367), (64, 2, 2, 8, 1025), (128, 8, 8, 1, 2049), (128, 4, 32, 8, 65),
-                                           (256, 8, 8, 3, 343), (256, 16, 16, 8, 65)])
+                                           (256, 8, 8, 3, 343), (256, 16, 16, 8, 65), (128, 8, 8, 1, 3073), (128, 4, 32, 8, 97),
+                                           (256, 8, 8, 3, 683), (256, 16, 16, 8, 129)])
 def test_many_candidates_equal_the_same_candidates_in_short_lists(d, heads, m, U, C):
     import numpy as np
     import torch
@@ -88,3 +89,18 @@ def test_stack_of_at_most_two_tiles(d, heads, m, k, extra):
     case = synth.make_case(cfg)
     case["lens"][:3] = [200, 0, 9]
     _entry_points(case, TOL["bf16"], with_inner=False, logits_by_terms=True)
+
+
+# The few-tiles kernels where the hidden chunks do not fill the waves evenly (1 to 10 chunks for four or eight waves), and more
+# key tiles than are on their way at once (ten, and users with none, one and five): every entry point and serving
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,heads,ffn_mult", [(64, 4, 1), (64, 4, 3), (64, 2, 5), (128, 8, 1), (256, 8, 1), (256, 16, 2)])
+def test_few_tiles_with_any_number_of_hidden_chunks_and_key_tiles(d, heads, ffn_mult):
+    import longer_synth as synth
+    from test_gpu_parity import _entry_points, _serving, TOL
+    cfg = synth.CONFIGS["C2"].replace(B=4, L=1200, K=4, d=d, heads=heads, inner_heads=heads, m=4, k_recent=40, n_self=1, ffn_mult=ffn_mult,
+                                      C=11, ragged=True, len_lo=0, len_hi=1200, index=79)
+    case = synth.make_case(cfg)
+    case["lens"][:] = [1200, 0, 20, 633]
+    _entry_points(case, TOL["bf16"], with_inner=False, logits_by_terms=True)
+    _serving(case, TOL["bf16"], logits_by_terms=True)
