@@ -110,380 +110,399 @@ struct RecordOut {        // one tile's record
   __device__ __forceinline__ void put(int base, int g, bf16x8 v) const { *(bf16x8*)(p + (size_t)(base + g) * 1024 + tile_lane_offset(lane, g & 1)) = v; }
 };
 
-// Four waves share a tile: feature tile t of the rows, of every product's result and of the LayerNorms belongs to wave
-// t % 4; the hidden chunks of the FFN are dealt out the same way.  Operand groups change hands through LDS (sixteen
+// Four waves share a tile (eight at width 256): feature tile t of the rows, of every product's result and of the LayerNorms
+// belongs to wave t; the hidden chunks of the FFN are dealt out the same way (below width 128 the waves without a feature tile
+// share in those alone, going through the rest on another's).  Operand groups change hands through LDS (sixteen
 // features of 32 rows, 1 KiB), row sums as one pair of numbers per row and wave.  A wave holds few registers and fetches its
-// weight fragments from L2 itself.  (A tile per wave with the weights streamed through LDS for four tiles, as in the block
+// weight fragments from L2 itself, each a product ahead of its use into the registers of the one just used (the compiler
+// moves no load across a barrier).  (A tile per wave with the weights streamed through LDS for four tiles, as in the block
 // kernel, leaves a wave alone on its SIMD with all of the FFN's activation: 54 / 74 us forward / backward per layer at the
-// headline batch, 21 / 23 us in the small model.)
-constexpr int kStackWaves = 4;
+// headline batch, 21 / 23 us in the small model.)  A layer's launch forward / backward, with each product's fragments requested
+// when it began and now: 53 / 94 and 49 / 74 us at the headline batch (864 tiles), 34 / 33 and 19 / 23 us on 203 tiles of width 128,
+// 13 / 14 and 10 / 11 us in the small model.
+__host__ __device__ constexpr int stack_waves(int d) { return d >= 256 ? 8 : 4; }
 template <int D>
 struct StackTile {
-  static constexpr int NT = D / 32, NG = D / 16, OT = (NT + 3) / 4;      // OT: most feature tiles of a wave
+  static constexpr int NT = D / 32, NG = D / 16, WV = stack_waves(D), NF = NG > 2 * WV ? NG : 2 * WV;
+  typedef __attribute__((address_space(1))) const char gchar;
+  typedef __attribute__((address_space(1))) const bf16x8 gfrag;
   const char* w;                                                          // the launch's weights
-  int lane, hi, wave;
+  int lane, hi, wave, ft;                                                 // ft: the wave's feature tile, own: its alone
+  bool own;
   bf16x8 (*ops)[64];                                                      // [group][lane]
-  float2 (*sums)[64];                                                     // [wave][lane]
-  __device__ __forceinline__ bool owns(int i) const { return wave + 4 * i < NT; }
-  __device__ __forceinline__ bf16x8 frag(int seg, int s) const { return *(const bf16x8*)(w + ((size_t)(seg * NG + s) * 64 + lane) * 16); }
-  // acc += (segment seg: 32 result features) b
-  __device__ __forceinline__ void product(f32x16& acc, int seg, const bf16x8 (&b)[NG]) const {
-    bf16x8 f[NG];
+  float2 (*sums)[WV][64];                                                 // [use][wave][lane]
+  bf16x8 fr[NF];                                                          // weight fragments under way
+  __device__ __forceinline__ gchar* at(int seg, int s) const {            // (wave-uniform: a scalar base, the lane's part an offset)
+    gchar* q = (gchar*)(w + (size_t)(seg * NG + s) * 1024);
+    asm("" : "+s"(q));
+    return q;
+  }
+  __device__ __forceinline__ bf16x8 load(gchar* q, int s) const { return *(gfrag*)(q + ((unsigned)lane * 16u + (unsigned)s * 1024u)); }
+  __device__ __forceinline__ void request(gchar* q) {
 #pragma unroll
-    for (int s = 0; s < NG; ++s) f[s] = frag(seg, s);
+    for (int s = 0; s < NG; ++s) fr[s] = load(q, s);
+  }
+  // acc += (32 result features) b, then(s): the request that takes the registers of fragment s
+  template <typename B, typename F>
+  __device__ __forceinline__ void product(f32x16& acc, const B& b, const F& then) {
 #pragma unroll
-    for (int s = 0; s < NG; ++s) acc = ET<__bf16>::mma(f[s], b[s], acc);
+    for (int s = 0; s < NG; ++s) {
+      acc = ET<__bf16>::mma(fr[s], b(s), acc);
+      then(s);
+      __builtin_amdgcn_sched_barrier(0);                                  // (in this order: hoisted loads would need a second set of registers)
+    }
+    settle(acc);
   }
   // this wave's part of an operand to LDS, then all of it from there
-  __device__ __forceinline__ void hand_in(int t, const f32x16& y) const {
+  __device__ __forceinline__ void hand_in(const f32x16& y) const {
+    if (!own) return;
 #pragma unroll
-    for (int g = 0; g < 2; ++g) ops[2 * t + g][lane] = ET<__bf16>::pack(y, g);
+    for (int g = 0; g < 2; ++g) ops[2 * ft + g][lane] = ET<__bf16>::pack(y, g);
   }
   __device__ __forceinline__ void take(bf16x8 (&b)[NG]) const {
 #pragma unroll
     for (int g = 0; g < NG; ++g) b[g] = ops[g][lane];
   }
   // mean and 1 / standard deviation of the rows: every wave's own mean and squared deviations, combined (one barrier)
-  __device__ __forceinline__ void stats(const f32x16 (&x)[OT], float eps, float& mean, float& rstd) const {
-    float n = 0.f, m = 0.f, v = 0.f;
+  __device__ __forceinline__ void stats(int use, const f32x16& x, float eps, float& mean, float& rstd) const {
+    float m = 0.f, v = 0.f;
 #pragma unroll
-    for (int i = 0; i < OT; ++i) {
-      if (!owns(i)) continue;
+    for (int r = 0; r < 16; ++r) m += x[r];
+    m = sum_halves(m) * (1.f / 32.f);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) m += x[i][r];
-      n += 32.f;
-    }
-    m = sum_halves(m) / fmaxf(n, 1.f);
-#pragma unroll
-    for (int i = 0; i < OT; ++i) {
-      if (!owns(i)) continue;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) { const float q = x[i][r] - m; v = fmaf(q, q, v); }
-    }
-    __syncthreads();                               // (whatever was in `sums` has been read)
-    sums[wave][lane] = make_float2(m, sum_halves(v));
+    for (int r = 0; r < 16; ++r) { const float q = x[r] - m; v = fmaf(q, q, v); }
+    sums[use][wave][lane] = make_float2(m, sum_halves(v));
     __syncthreads();
     mean = 0.f;
-    float2 p[4];
+    float2 p[NT];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      p[k] = sums[k][lane];
-      mean = fmaf(p[k].x, (float)(32 * ((NT - k + 3) / 4)) * (1.f / D), mean);
+    for (int k = 0; k < NT; ++k) {
+      p[k] = sums[use][k][lane];
+      mean = fmaf(p[k].x, 32.f / D, mean);
     }
     float var = 0.f;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < NT; ++k) {
       const float q = p[k].x - mean;
-      var += p[k].y + q * q * (float)(32 * ((NT - k + 3) / 4));
+      var += p[k].y + q * q * 32.f;
     }
     rstd = 1.f / sqrtf(var * (1.f / D) + eps);
   }
-  // x <- LayerNorm backward of dn at the rows x (this wave's tiles)
-  __device__ __forceinline__ void norm_back(f32x16 (&x)[OT], f32x16 (&dn)[OT], const float* gain, float mean, float rstd) const {
+  // x <- LayerNorm backward of dn at the rows x (this wave's tile)
+  __device__ __forceinline__ void norm_back(int use, f32x16& x, f32x16& dn, const float* gain, float mean, float rstd) const {
     float c1 = 0.f, c2 = 0.f;
+    dn *= bias_tile(gain, ft, hi);
 #pragma unroll
-    for (int i = 0; i < OT; ++i) {
-      if (!owns(i)) continue;
-      dn[i] *= bias_tile(gain, wave + 4 * i, hi);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        x[i][r] = (x[i][r] - mean) * rstd;
-        c1 += dn[i][r];
-        c2 = fmaf(dn[i][r], x[i][r], c2);
-      }
+    for (int r = 0; r < 16; ++r) {
+      x[r] = (x[r] - mean) * rstd;
+      c1 += dn[r];
+      c2 = fmaf(dn[r], x[r], c2);
     }
-    __syncthreads();
-    sums[wave][lane] = make_float2(sum_halves(c1), sum_halves(c2));
+    sums[use][wave][lane] = make_float2(sum_halves(c1), sum_halves(c2));
     __syncthreads();
     c1 = 0.f; c2 = 0.f;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) { const float2 p = sums[k][lane]; c1 += p.x; c2 += p.y; }
+    for (int k = 0; k < NT; ++k) { const float2 p = sums[use][k][lane]; c1 += p.x; c2 += p.y; }
     c1 *= 1.f / D; c2 *= 1.f / D;
 #pragma unroll
-    for (int i = 0; i < OT; ++i)
+    for (int r = 0; r < 16; ++r) x[r] = rstd * (dn[r] - c1 - x[r] * c2);
+  }
+};
+
+// A launch's parameter vectors, from memory to registers (all requests at once) and on to LDS: up to N of width d and
+// the hidden bias (at most 2048 values).
+template <int D, int N>
+struct StackVectors {
+  static constexpr int THR = 64 * stack_waves(D), VD = (D + THR - 1) / THR, VF = 2048 / THR;
+  __bf16 d[N][VD], f[VF];
+  __device__ __forceinline__ void request(int i, const __bf16* v, int tid) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) x[i][r] = rstd * (dn[i][r] - c1 - x[i][r] * c2);
+    for (int k = 0; k < VD; ++k) { const int c = tid + THR * k; d[i][k] = v[c < D ? c : 0]; }
+  }
+  __device__ __forceinline__ void request_hidden(const __bf16* v, int n, int tid) {
+#pragma unroll
+    for (int k = 0; k < VF; ++k) { const int c = tid + THR * k; f[k] = v[c < n ? c : 0]; }
+  }
+  __device__ __forceinline__ void put(int i, float* to, int tid) const {
+#pragma unroll
+    for (int k = 0; k < VD; ++k) { const int c = tid + THR * k; if (c < D) to[c] = (float)d[i][k]; }
+  }
+  __device__ __forceinline__ void put_hidden(float* to, int n, int tid) const {
+#pragma unroll
+    for (int k = 0; k < VF; ++k) { const int c = tid + THR * k; if (c < n) to[c] = (float)f[k]; }
   }
 };
 
 __host__ __device__ inline int stack_vec_floats(int d, int f) { return 9 * d + f; }
 
+// What bounds the two kernels: the chain of a tile at small batches; at the headline batch (864 tiles) the exact-erf activation
+// beside the products, and 3.3 KB (forward) and 5.5 KB (backward) of memory traffic per row.
 template <int D>
-__global__ __launch_bounds__(64 * kStackWaves, 2) void bw_stack_fwd_kernel(const StackFwd p) {
+__global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stack_fwd_kernel(const StackFwd p) {
   using S = StackTile<D>;
-  constexpr int NT = S::NT, NG = S::NG, OT = S::OT;
+  constexpr int NT = S::NT, NG = S::NG, WV = S::WV;
   using E = ET<__bf16>;
   __shared__ bf16x8 ops[NG][64];
-  __shared__ bf16x8 hid[2][4][2][64];              // activated hidden chunks: [parity][wave][group][lane]
-  __shared__ float2 sums[4][64];
+  __shared__ bf16x8 hid[2][WV][2][64];             // activated hidden chunks: [parity][wave][group][lane]
+  __shared__ float2 sums[2][WV][64];
   extern __shared__ f32x4 vec4[];
   float* vec = (float*)vec4;
   const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, hi = lane >> 5, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tile = blockIdx.x, row = tile * 32 + j, NC = p.f / 32;
-  const bool in = row < p.rows;
+  const bool in = row < p.rows, own = wave < NT;
+  const int ft = wave % NT;
   const int oBo = 0, oG2 = D, oS2 = 2 * D, oB2 = 3 * D, oG1 = 4 * D, oS1 = 5 * D, oB = 6 * D, oB1 = 9 * D;
-  for (int i = tid; i < D; i += 64 * kStackWaves) {
-    if (p.o) { vec[oBo + i] = (float)p.bo[i]; vec[oG2 + i] = (float)p.ln2_g[i]; vec[oS2 + i] = (float)p.ln2_b[i]; vec[oB2 + i] = (float)p.b2[i]; }
-    if (p.out) {
-      vec[oG1 + i] = (float)p.ln1_g[i]; vec[oS1 + i] = (float)p.ln1_b[i];
-      for (int m = 0; m < p.mats; ++m) vec[oB + m * D + i] = (float)p.bias[m][i];
-    }
-  }
-  if (p.o) for (int i = tid; i < p.f; i += 64 * kStackWaves) vec[oB1 + i] = (float)p.b1[i];
-  const S s = {p.wstream, lane, hi, wave, ops, sums};
-  f32x16 x[OT];
-#pragma unroll
-  for (int i = 0; i < OT; ++i) {
+  S s = {p.wstream, lane, hi, wave, ft, own, ops, sums};
+  // everything that is read ahead of the first product is requested at once
+  f32x16 x;
+  {
     f32x16 one[1];
-    load_rows<__bf16, 1>(one, p.x, 1, (long long)row * D + 32 * (wave + 4 * i), in && s.owns(i), hi);
-    x[i] = one[0];
+    load_rows<__bf16, 1>(one, p.x, 1, (long long)row * D + 32 * ft, in, hi);
+    x = one[0];
   }
   bf16x8 nop[NG];
+  if (p.o) {
+#pragma unroll
+    for (int g = 0; g < NG; ++g) nop[g] = row_group(p.o + (size_t)row * D, g, hi, in);
+  }
+  const int head = p.o ? NT + 2 * NC : 0;          // first segment of the next layer's products
+  s.request(s.at(p.o ? ft : head + min(wave, p.mats * NT - 1), 0));
+  {
+    StackVectors<D, 9> v;
+    if (p.o) { v.request(0, p.bo, tid); v.request(1, p.ln2_g, tid); v.request(2, p.ln2_b, tid); v.request(3, p.b2, tid); v.request_hidden(p.b1, p.f, tid); }
+    if (p.out) {
+      v.request(4, p.ln1_g, tid); v.request(5, p.ln1_b, tid);
+#pragma unroll
+      for (int m = 0; m < 3; ++m) v.request(6 + m, m < p.mats ? p.bias[m] : p.bias[0], tid);
+    }
+    if (p.o) { v.put(0, vec + oBo, tid); v.put(1, vec + oG2, tid); v.put(2, vec + oS2, tid); v.put(3, vec + oB2, tid); v.put_hidden(vec + oB1, p.f, tid); }
+    if (p.out) {
+      v.put(4, vec + oG1, tid); v.put(5, vec + oS1, tid);
+#pragma unroll
+      for (int m = 0; m < 3; ++m)
+        if (m < p.mats) v.put(6 + m, vec + oB + m * D, tid);
+    }
+  }
   float mean, rstd;
-  int seg = 0;
   // rows -> normalised rows (to the records) -> operand of the next products, in every wave
-  auto normalise = [&](int og, int os, const RecordOut& rec, int at) {
-    s.stats(x, p.eps, mean, rstd);                 // (its barriers: everybody is done with `ops`, and `vec` is there)
+  auto normalise = [&](int use, int og, int os, const RecordOut& rec, int at) {
+    s.stats(use, x, p.eps, mean, rstd);            // (its barrier: everybody is done with `ops`, and `vec` is there)
+    const f32x16 g = bias_tile(vec + og, ft, hi), b = bias_tile(vec + os, ft, hi);
+    f32x16 h, y;
 #pragma unroll
-    for (int i = 0; i < OT; ++i) {
-      if (!s.owns(i)) continue;
-      const int t = wave + 4 * i;
-      const f32x16 g = bias_tile(vec + og, t, hi), b = bias_tile(vec + os, t, hi);
-      f32x16 h, y;
+    for (int r = 0; r < 16; ++r) { h[r] = (x[r] - mean) * rstd; y[r] = fmaf(h[r], g[r], b[r]); }
+    s.hand_in(y);
+    if (own) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { h[r] = (x[i][r] - mean) * rstd; y[r] = fmaf(h[r], g[r], b[r]); }
-#pragma unroll
-      for (int q = 0; q < 2; ++q) rec.put(at, 2 * t + q, E::pack(h, q));
-      s.hand_in(t, y);
+      for (int q = 0; q < 2; ++q) rec.put(at, 2 * ft + q, E::pack(h, q));
     }
     __syncthreads();
     s.take(nop);
   };
+  auto operand = [&](int k) { return nop[k]; };
   if (p.o) {
     const BlockRecord at(D, p.f);
     const RecordOut rec(p.rec, tile, at.size, lane);
-    bf16x8 oop[NG];
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      oop[g] = row_group(p.o + (size_t)row * D, g, hi, in);
-      if ((g >> 1) % 4 == wave) rec.put(at.o, g, oop[g]);
-    }
+    for (int g = 0; g < NG; ++g)
+      if ((g >> 1) % WV == wave) rec.put(at.o, g, nop[g]);
     __syncthreads();                               // `vec`
+    x += bias_tile(vec + oBo, ft, hi);
+    typename S::gchar* first = s.at(NT + 2 * min(wave, NC - 1), 0);
+    s.product(x, operand, [&](int k) { s.fr[k] = s.load(first, k); });
+    if (own) store_part<NT>(x, p.xmid, tile, ft, lane);
+    normalise(0, oG2, oS2, rec, at.xh2);
+    x += bias_tile(vec + oB2, ft, hi);
+    for (int c0 = 0, par = 0; c0 < NC; c0 += WV, par ^= 1) {
+      const int c = min(c0 + wave, NC - 1);        // (a wave without a chunk goes through another's and hands in zeros)
+      auto second = [&](int k) { s.fr[k] = s.load(s.at(NT + 2 * min(c0 + k / 2, NC - 1) + 1, 2 * ft), k & 1); };
 #pragma unroll
-    for (int i = 0; i < OT; ++i) {
-      if (!s.owns(i)) continue;
-      const int t = wave + 4 * i;
-      x[i] += bias_tile(vec + oBo, t, hi);
-      s.product(x[i], t, oop);
-      settle(x[i]);
-      store_part<NT>(x[i], p.xmid, tile, t, lane);
-    }
-    seg = NT;
-    normalise(oG2, oS2, rec, at.xh2);
+      for (int k = NG; k < 2 * WV; ++k) second(k);
+      f32x16 v = bias_tile(vec + oB1, c, hi);
+      s.product(v, operand, second);
 #pragma unroll
-    for (int i = 0; i < OT; ++i)
-      if (s.owns(i)) x[i] += bias_tile(vec + oB2, wave + 4 * i, hi);
-    for (int c0 = 0, par = 0; c0 < NC; c0 += 4, par ^= 1) {
-      const int c = c0 + wave;
-      if (c < NC) {
-        f32x16 v = bias_tile(vec + oB1, c, hi);
-        s.product(v, seg + 2 * c, nop);
-        settle(v);
+      for (int r = 0; r < 16; ++r) v[r] = c0 + wave < NC ? act_exact(v[r], p.act) : 0.f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) v[r] = act_exact(v[r], p.act);
-#pragma unroll
-        for (int g = 0; g < 2; ++g) hid[par][wave][g][lane] = E::pack(v, g);
-      }
+      for (int g = 0; g < 2; ++g) hid[par][wave][g][lane] = E::pack(v, g);
+      const bool end = c0 + WV >= NC;
+      typename S::gchar* next = s.at(end ? head + (p.out ? min(wave, p.mats * NT - 1) : -1) : NT + 2 * min(c0 + WV + wave, NC - 1), 0);
       __syncthreads();                             // (the other parity was last read ahead of the barrier before)
 #pragma unroll
-      for (int i = 0; i < OT; ++i) {
-        if (!s.owns(i)) continue;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          if (c0 + k >= NC) break;
-#pragma unroll
-          for (int g = 0; g < 2; ++g) x[i] = E::mma(s.frag(seg + 2 * (c0 + k) + 1, 2 * (wave + 4 * i) + g), hid[par][k][g][lane], x[i]);
-        }
+      for (int k = 0; k < 2 * WV; ++k) {
+        x = E::mma(s.fr[k], hid[par][k / 2][k & 1][lane], x);
+        if (k < NG) s.fr[k] = s.load(next, k);
+        __builtin_amdgcn_sched_barrier(0x486);
       }
     }
-    seg += 2 * NC;
     const bool live = in && p.desc[in ? row : 0] >= 0;
+    settle(x);
 #pragma unroll
-    for (int i = 0; i < OT; ++i) {
-      settle(x[i]);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) x[i][r] = live ? x[i][r] : 0.f;
-      const f32x16 one[1] = {x[i]};
-      if (in && s.owns(i)) store_rows<__bf16, 1>(one, p.y, 1, (long long)row * D + 32 * (wave + 4 * i), true, hi);
-    }
+    for (int r = 0; r < 16; ++r) x[r] = live ? x[r] : 0.f;
+    const f32x16 one[1] = {x};
+    if (in && own) store_rows<__bf16, 1>(one, p.y, 1, (long long)row * D + 32 * ft, true, hi);
   }
   if (p.out) {
     const RecordOut rec(p.rec1, tile, p.rec1_size, lane);
-    normalise(oG1, oS1, rec, p.rec1_xh);
-    for (int k = wave; k < p.mats * NT; k += kStackWaves) {      // segment k: matrix k % mats of feature tile k / mats
-      const int ft = k / p.mats, m = k - ft * p.mats;
-      f32x16 v = bias_tile(vec + oB + m * D, ft, hi);
-      s.product(v, seg + k, nop);
-      settle(v);
+    normalise(1, oG1, oS1, rec, p.rec1_xh);
+    for (int k = wave; k < p.mats * NT; k += WV) {      // segment k: matrix k % mats of feature tile k / mats
+      const int t = k / p.mats, m = k - t * p.mats;
+      f32x16 v = bias_tile(vec + oB + m * D, t, hi);
+      typename S::gchar* next = s.at(head + min(k + WV, p.mats * NT - 1), 0);
+      s.product(v, operand, [&](int i) { s.fr[i] = s.load(next, i); });
       if (in) {
 #pragma unroll
-        for (int g = 0; g < 2; ++g) row_put(p.out + (size_t)row * p.ldo + m * D + 32 * ft, g, hi, E::pack(v, g));
+        for (int g = 0; g < 2; ++g) row_put(p.out + (size_t)row * p.ldo + m * D + 32 * t, g, hi, E::pack(v, g));
       }
     }
   }
 }
 
 template <int D>
-__global__ __launch_bounds__(64 * kStackWaves, 2) void bw_stack_bwd_kernel(const StackBwd p) {
+__global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stack_bwd_kernel(const StackBwd p) {
   using S = StackTile<D>;
-  constexpr int NT = S::NT, NG = S::NG, OT = S::OT;
+  constexpr int NT = S::NT, NG = S::NG, WV = S::WV;
   using E = ET<__bf16>;
   __shared__ bf16x8 ops[NG][64], ops2[NG][64];
-  __shared__ bf16x8 hid[2][4][2][64];              // gradients of the hidden chunks
-  __shared__ float2 sums[4][64];
+  __shared__ bf16x8 hid[2][WV][2][64];             // gradients of the hidden chunks
+  __shared__ float2 sums[4][WV][64];
   extern __shared__ f32x4 vec4[];
   float* vec = (float*)vec4;
   const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, hi = lane >> 5, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tile = blockIdx.x, row = tile * 32 + j, NC = p.f / 32;
-  const bool in = row < p.rows;
+  const bool in = row < p.rows, own = wave < NT;
+  const int ft = wave % NT;
   const int oG1 = 0, oG2 = D, oS2 = 2 * D, oB1 = 3 * D;
-  for (int i = tid; i < D; i += 64 * kStackWaves) {
-    if (p.dqkv) vec[oG1 + i] = (float)p.ln1_g[i];
-    if (p.xmid) { vec[oG2 + i] = (float)p.ln2_g[i]; vec[oS2 + i] = (float)p.ln2_b[i]; }
-  }
-  if (p.xmid) for (int i = tid; i < p.f; i += 64 * kStackWaves) vec[oB1 + i] = (float)p.b1[i];
-  const S s = {p.wstream, lane, hi, wave, ops, sums};
-  f32x16 x[OT], dn[OT];
+  S s = {p.wstream, lane, hi, wave, ft, own, ops, sums};
+  f32x16 x, dn = splat16(0.f), xm = splat16(0.f), add = splat16(0.f);
   float mean, rstd;
-  int seg = 0;
-  const float* src = p.dqkv ? p.x : p.dy;
-#pragma unroll
-  for (int i = 0; i < OT; ++i) {
+  {
     f32x16 one[1];
-    load_rows<__bf16, 1>(one, src, 1, (long long)row * D + 32 * (wave + 4 * i), in && s.owns(i), hi);
-    x[i] = one[0];
-    dn[i] = splat16(0.f);
+    load_rows<__bf16, 1>(one, p.dqkv ? p.x : p.dy, 1, (long long)row * D + 32 * ft, in, hi);
+    x = one[0];
+  }
+  // fragment k of the products that bring dQ, dK, dV back (matrix m): 32 contracted features k / 2 of this wave's result tile
+  auto back = [&](int m, int k) { s.fr[k] = s.load(s.at((k / 2) * p.mats + m, 2 * ft), k & 1); };
+  bf16x8 bop[NG];
+  auto rows_of = [&](int m, int k) { bop[k] = row_group(p.dqkv + (size_t)row * p.ldq + m * D, k, hi, in); };
+  const int seg = p.dqkv ? NT * p.mats : 0;        // first segment of the FFN's products
+  if (p.dqkv) {
+#pragma unroll
+    for (int k = 0; k < NG; ++k) { rows_of(0, k); back(0, k); }
+    if (p.dxm_in) add = load_part<NT>(p.dxm_in, tile, ft, lane);
+  } else {
+    s.request(s.at(seg + 3 * min(wave, NC - 1), 0));
+  }
+  if (p.xmid) xm = load_part<NT>(p.xmid, tile, ft, lane);
+  {
+    StackVectors<D, 3> v;
+    if (p.dqkv) v.request(0, p.ln1_g, tid);
+    if (p.xmid) { v.request(1, p.ln2_g, tid); v.request(2, p.ln2_b, tid); v.request_hidden(p.b1, p.f, tid); }
+    if (p.dqkv) v.put(0, vec + oG1, tid);
+    if (p.xmid) { v.put(1, vec + oG2, tid); v.put(2, vec + oS2, tid); v.put_hidden(vec + oB1, p.f, tid); }
   }
   if (p.dqkv) {
     const RecordOut rec(p.rec1, tile, p.rec1_size, lane);
-    for (int ft = 0; ft < NT; ++ft)
-      for (int m = 0; m < p.mats; ++m, ++seg) {
-        bf16x8 op[2];
+    typename S::gchar* first = s.at(seg + (p.xmid ? 3 * min(wave, NC - 1) : -1), 0);
+    for (int m = 0; m < p.mats; ++m) {
+      const bool end = m + 1 == p.mats;
 #pragma unroll
-        for (int g = 0; g < 2; ++g) {
-          op[g] = row_group(p.dqkv + (size_t)row * p.ldq + m * D + 32 * ft, g, hi, in);
-          if (seg % 4 == wave) rec.put(p.rec1_dqkv + m * NG + 2 * ft, g, op[g]);
-        }
-#pragma unroll
-        for (int i = 0; i < OT; ++i) {
-          if (!s.owns(i)) continue;
-#pragma unroll
-          for (int g = 0; g < 2; ++g) dn[i] = E::mma(s.frag(seg, 2 * (wave + 4 * i) + g), op[g], dn[i]);
-        }
+      for (int k = 0; k < NG; ++k) {
+        dn = E::mma(s.fr[k], bop[k], dn);
+        if ((k >> 1) % WV == wave) rec.put(p.rec1_dqkv + m * NG, k, bop[k]);
+        rows_of(end ? m : m + 1, k);
+        s.fr[k] = s.load(end ? first + k * 1024 : s.at((k / 2) * p.mats + m + 1, 2 * ft) + (k & 1) * 1024, 0);
+        __builtin_amdgcn_sched_barrier(0);
       }
-#pragma unroll
-    for (int i = 0; i < OT; ++i) settle(dn[i]);
-    s.stats(x, p.eps, mean, rstd);
-    s.norm_back(x, dn, vec + oG1, mean, rstd);
-#pragma unroll
-    for (int i = 0; i < OT; ++i) {
-      if (!s.owns(i)) continue;
-      if (p.dxm_in) x[i] += load_part<NT>(p.dxm_in, tile, wave + 4 * i, lane);
-      const f32x16 one[1] = {x[i]};
-      if (!p.xmid && in) store_rows<__bf16, 1>(one, p.dx, 1, (long long)row * D + 32 * (wave + 4 * i), true, hi);
     }
+    settle(dn);
+    s.stats(0, x, p.eps, mean, rstd);              // (its barrier: `vec` is there)
+    s.norm_back(1, x, dn, vec + oG1, mean, rstd);
+    x += add;
+    const f32x16 one[1] = {x};
+    if (!p.xmid && in && own) store_rows<__bf16, 1>(one, p.dx, 1, (long long)row * D + 32 * ft, true, hi);
     if (!p.xmid) return;
   }
   const BlockRecord at(D, p.f);
   const RecordOut rec(p.rec, tile, at.size, lane);
   const bool live = in && p.desc[in ? row : 0] >= 0;
-  f32x16 xm[OT];
+  s.stats(2, xm, p.eps, mean, rstd);               // (its barrier: `vec` is there)
+  // (width 256: no registers for a second operand of all features, it is read from LDS)
+  constexpr bool HELD = D <= 128;
+  bf16x8 dyop[HELD ? NG : 1], nop[NG];
 #pragma unroll
-  for (int i = 0; i < OT; ++i) xm[i] = s.owns(i) ? load_part<NT>(p.xmid, tile, wave + 4 * i, lane) : splat16(0.f);
-  s.stats(xm, p.eps, mean, rstd);                  // (its barriers: `vec` is there)
-  bf16x8 dyop[NG], nop[NG];
-#pragma unroll
-  for (int i = 0; i < OT; ++i) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) x[i][r] = live ? x[i][r] : 0.f;
-    dn[i] = splat16(0.f);
-    if (!s.owns(i)) continue;
-    const int t = wave + 4 * i;
-    const f32x16 g = bias_tile(vec + oG2, t, hi), b = bias_tile(vec + oS2, t, hi);
+  for (int r = 0; r < 16; ++r) x[r] = live ? x[r] : 0.f;
+  dn = splat16(0.f);
+  {
+    const f32x16 g = bias_tile(vec + oG2, ft, hi), b = bias_tile(vec + oS2, ft, hi);
     f32x16 y;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) y[r] = fmaf((xm[i][r] - mean) * rstd, g[r], b[r]);
-    s.hand_in(t, y);
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const bf16x8 v = E::pack(x[i], q);
-      ops2[2 * t + q][lane] = v;
-      rec.put(at.dyb, 2 * t + q, v);
-    }
-  }
-  __syncthreads();
-  s.take(nop);
-#pragma unroll
-  for (int g = 0; g < NG; ++g) dyop[g] = ops2[g][lane];
-  for (int c0 = 0, par = 0; c0 < NC; c0 += 4, par ^= 1) {
-    const int c = c0 + wave;
-    if (c < NC) {
-      f32x16 v = bias_tile(vec + oB1, c, hi), g = splat16(0.f);
-      s.product(v, seg + 3 * c, nop);
-      s.product(g, seg + 3 * c + 1, dyop);
-      settle(v);
-      settle(g);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float a, da;
-        act_exact_both(v[r], p.act, &a, &da);
-        v[r] = a;
-        g[r] *= da;
-      }
+    for (int r = 0; r < 16; ++r) y[r] = fmaf((xm[r] - mean) * rstd, g[r], b[r]);
+    s.hand_in(y);
+    if (own) {
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
-        const bf16x8 h = E::pack(g, q);
-        hid[par][wave][q][lane] = h;
-        rec.put(at.dh + 2 * c, q, h);
-        rec.put(at.a + 2 * c, q, E::pack(v, q));
+        const bf16x8 v = E::pack(x, q);
+        ops2[2 * ft + q][lane] = v;
+        rec.put(at.dyb, 2 * ft + q, v);
       }
     }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < OT; ++i) {
-      if (!s.owns(i)) continue;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (c0 + k >= NC) break;
-#pragma unroll
-        for (int g = 0; g < 2; ++g) dn[i] = E::mma(s.frag(seg + 3 * (c0 + k) + 2, 2 * (wave + 4 * i) + g), hid[par][k][g][lane], dn[i]);
-      }
-    }
-  }
-  seg += 3 * NC;
-#pragma unroll
-  for (int i = 0; i < OT; ++i) settle(dn[i]);
-  s.norm_back(xm, dn, vec + oG2, mean, rstd);      // (its barriers: everybody has taken `ops`)
-#pragma unroll
-  for (int i = 0; i < OT; ++i) {
-    if (!s.owns(i)) continue;
-    const int t = wave + 4 * i;
-    x[i] += xm[i];
-    store_part<NT>(x[i], p.dxm, tile, t, lane);
-    s.hand_in(t, x[i]);
-#pragma unroll
-    for (int q = 0; q < 2; ++q) rec.put(at.dxmb, 2 * t + q, E::pack(x[i], q));
   }
   __syncthreads();
   s.take(nop);
-  for (int ft = wave; ft < NT; ft += kStackWaves) {
-    f32x16 v = splat16(0.f);
-    s.product(v, seg + ft, nop);
-    settle(v);
-    if (in) {
+  if (HELD) {
 #pragma unroll
-      for (int g = 0; g < 2; ++g) row_put(p.dob + (size_t)row * D + 32 * ft, g, hi, E::pack(v, g));
+    for (int g = 0; g < (HELD ? NG : 1); ++g) dyop[g] = ops2[g][lane];
+  }
+  auto operand = [&](int k) { return nop[k]; };
+  auto upstream = [&](int k) -> bf16x8 { return HELD ? dyop[HELD ? k : 0] : ops2[k][lane]; };
+  for (int c0 = 0, par = 0; c0 < NC; c0 += WV, par ^= 1) {
+    const int c = min(c0 + wave, NC - 1);          // (a wave without a chunk goes through another's and hands in zeros)
+    const bool there = c0 + wave < NC;
+    f32x16 v = bias_tile(vec + oB1, c, hi), g = splat16(0.f);
+    typename S::gchar* second = s.at(seg + 3 * c + 1, 0);
+    s.product(v, operand, [&](int k) { s.fr[k] = s.load(second, k); });
+    auto third = [&](int k) { s.fr[k] = s.load(s.at(seg + 3 * min(c0 + k / 2, NC - 1) + 2, 2 * ft), k & 1); };
+#pragma unroll
+    for (int k = NG; k < 2 * WV; ++k) third(k);
+    s.product(g, upstream, third);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      float a, da;
+      act_exact_both(v[r], p.act, &a, &da);
+      v[r] = a;
+      g[r] = there ? g[r] * da : 0.f;
     }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const bf16x8 h = E::pack(g, q);
+      hid[par][wave][q][lane] = h;
+      if (there) { rec.put(at.dh + 2 * c, q, h); rec.put(at.a + 2 * c, q, E::pack(v, q)); }
+    }
+    typename S::gchar* next = s.at(c0 + WV >= NC ? seg + 3 * NC + ft : seg + 3 * min(c0 + WV + wave, NC - 1), 0);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 2 * WV; ++k) {
+      dn = E::mma(s.fr[k], hid[par][k / 2][k & 1][lane], dn);
+      if (k < NG) s.fr[k] = s.load(next, k);
+      __builtin_amdgcn_sched_barrier(0x486);
+    }
+  }
+  settle(dn);
+  s.norm_back(3, xm, dn, vec + oG2, mean, rstd);   // (its barrier: everybody has taken `ops`)
+  x += xm;
+  s.hand_in(x);
+  if (own) {
+    store_part<NT>(x, p.dxm, tile, ft, lane);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) rec.put(at.dxmb, 2 * ft + q, E::pack(x, q));
+  }
+  __syncthreads();
+  s.take(nop);
+  f32x16 v = splat16(0.f);
+  s.product(v, operand, [](int) {});
+  if (in && own) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g) row_put(p.dob + (size_t)row * D + 32 * ft, g, hi, E::pack(v, g));
   }
 }
 
@@ -497,11 +516,11 @@ void bw_stack_fwd_256(const StackFwd& p, hipStream_t st);
 void bw_stack_bwd_256(const StackBwd& p, hipStream_t st);
 template <int D>
 inline void bw_stack_fwd_d(const StackFwd& p, hipStream_t st) {
-  bw_stack_fwd_kernel<D><<<(p.rows + 31) / 32, 64 * kStackWaves, (size_t)stack_vec_floats(D, p.f) * 4, st>>>(p);
+  bw_stack_fwd_kernel<D><<<(p.rows + 31) / 32, 64 * stack_waves(D), (size_t)stack_vec_floats(D, p.f) * 4, st>>>(p);
 }
 template <int D>
 inline void bw_stack_bwd_d(const StackBwd& p, hipStream_t st) {
-  bw_stack_bwd_kernel<D><<<(p.rows + 31) / 32, 64 * kStackWaves, (size_t)stack_vec_floats(D, p.f) * 4, st>>>(p);
+  bw_stack_bwd_kernel<D><<<(p.rows + 31) / 32, 64 * stack_waves(D), (size_t)stack_vec_floats(D, p.f) * 4, st>>>(p);
 }
 
 }  // namespace bw

@@ -55,3 +55,14 @@ def test_block_kernel_widest_hidden_layer():
     """One block with 2048 hidden features: its vectors and the weight ring no longer let two workgroups share a compute unit."""
     cfg = synth.CONFIGS["C2"].replace(d=128, heads=8, inner_heads=8, inner_layers=1, K=8, B=2, L=70, ffn_mult=16, index=64)
     _compare("2048 hidden features", synth.make_case(cfg), synth.draw_merge_gradient(cfg))
+
+
+# The reduced stack's tiles where the hidden chunks do not fill its four (eight) waves evenly: 2, 3, 6 and 10 chunks, 8 at width 256;
+# 33 query rows, so the second tile holds one.  (Not the draw of index 66: at width 256 its last b_2 gradient is the sum over the
+# users of (sigmoid(logit) - label) / B, 0.333 - 0.186 - 0.123 = 0.0239, times a fixed vector; the logits' error of 1.4e-2, inside
+# its bar, moves a term by up to 1.4e-2 / 4 / 3 = 1.2e-3, a twentieth of that.  With labels of one value the terms add up.)
+@pytest.mark.parametrize("d,heads,ffn", [(32, 2, 2), (32, 2, 3), (64, 4, 1), (64, 4, 3), (64, 2, 5), (256, 8, 1)])
+def test_stack_with_any_number_of_hidden_chunks(d, heads, ffn):
+    cfg = synth.CONFIGS["C2"].replace(d=d, heads=heads, inner_heads=heads, B=3, L=90, m=2, k_recent=9, n_self=2, ffn_mult=ffn, ragged=True,
+                                      len_lo=20, len_hi=90, index=67)
+    _compare_model("width %d, %d hidden features" % (d, d * ffn), synth.make_case(cfg))
