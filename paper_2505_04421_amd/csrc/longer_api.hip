@@ -2,7 +2,7 @@
 // layout, parameter packing and the launch sequence of each entry point.
 #include "../../include/longer.h"
 #include "pair_kernel.h"
-#include "quad_kernel.h"
+#include "user_kernel.h"
 
 #include <cmath>
 #include <cstdarg>
@@ -26,10 +26,10 @@ template <> int launch_block<float, 32, 16>(int, int, int, const BlockParams&, d
 template <> int launch_block<float, 64, 16>(int, int, int, const BlockParams&, dim3, hipStream_t);
 template <> int launch_block<float, 128, 16>(int, int, int, const BlockParams&, dim3, hipStream_t);
 
-template <> int launch_pair<128, 16>(int, int, const BlockParams&, dim3, hipStream_t);
-template <> int launch_pair<128, 32>(int, int, const BlockParams&, dim3, hipStream_t);
-template <> int launch_pair<256, 16>(int, int, const BlockParams&, dim3, hipStream_t);
-template <> int launch_pair<256, 32>(int, int, const BlockParams&, dim3, hipStream_t);
+template <> int launch_pair<128, 16>(int, const BlockParams&, dim3, hipStream_t);
+template <> int launch_pair<128, 32>(int, const BlockParams&, dim3, hipStream_t);
+template <> int launch_pair<256, 16>(int, const BlockParams&, dim3, hipStream_t);
+template <> int launch_pair<256, 32>(int, const BlockParams&, dim3, hipStream_t);
 
 template <> int launch_quad<64, 16>(int, int, bool, const BlockParams&, dim3, hipStream_t);
 template <> int launch_quad<64, 32>(int, int, bool, const BlockParams&, dim3, hipStream_t);
@@ -38,9 +38,15 @@ template <> int launch_quad<128, 32>(int, int, bool, const BlockParams&, dim3, h
 template <> int launch_quad<256, 16>(int, int, bool, const BlockParams&, dim3, hipStream_t);
 template <> int launch_quad<256, 32>(int, int, bool, const BlockParams&, dim3, hipStream_t);
 
+template <> int launch_user<128, 16>(int, const BlockParams&, dim3, hipStream_t);
+template <> int launch_user<128, 32>(int, const BlockParams&, dim3, hipStream_t);
+template <> int launch_user<256, 16>(int, const BlockParams&, dim3, hipStream_t);
+template <> int launch_user<256, 32>(int, const BlockParams&, dim3, hipStream_t);
+
+typedef int (*user_fn)(int, const BlockParams&, dim3, hipStream_t);
 typedef int (*quad_fn)(int, int, bool, const BlockParams&, dim3, hipStream_t);
 typedef int (*launch_fn)(int, int, int, const BlockParams&, dim3, hipStream_t);
-typedef int (*pair_fn)(int, int, const BlockParams&, dim3, hipStream_t);
+typedef int (*pair_fn)(int, const BlockParams&, dim3, hipStream_t);
 
 // The kernels that give a tile to a pair of waves (pair_kernel.h): bf16, d = 128 / 256.  The
 // environment variable LONGER_DISABLE_PAIR_KERNELS=1 (read once) keeps every launch on the
@@ -64,6 +70,14 @@ static quad_fn find_quad(int dtype, int D, int DH) {
   if (D == 64) return DH == 16 ? &launch_quad<64, 16> : DH == 32 ? &launch_quad<64, 32> : nullptr;
   if (D == 128) return DH == 16 ? &launch_quad<128, 16> : DH == 32 ? &launch_quad<128, 32> : nullptr;
   if (D == 256) return DH == 16 ? &launch_quad<256, 16> : DH == 32 ? &launch_quad<256, 32> : nullptr;
+  return nullptr;
+}
+
+// the stack kernels that give a feature tile to a wave (user_kernel.h): bf16, d = 128 / 256
+static user_fn find_user(int dtype, int D, int DH) {
+  if (one_wave_only() || dtype != LONGER_BF16) return nullptr;
+  if (D == 128) return DH == 16 ? &launch_user<128, 16> : DH == 32 ? &launch_user<128, 32> : nullptr;
+  if (D == 256) return DH == 16 ? &launch_user<256, 16> : DH == 32 ? &launch_user<256, 32> : nullptr;
   return nullptr;
 }
 
@@ -329,8 +343,9 @@ struct Shape {
   size_t pb;          // bytes reserved per packed block (either layout)
   size_t seg;         // bytes of one stream segment
   launch_fn main_fn, inner_fn;
-  pair_fn pair;       // the main stack's two-wave kernels, or NULL
+  pair_fn pair;       // the main stack's two-wave scoring kernels, or NULL
   quad_fn quad;       // its four-wave kernels, or NULL
+  user_fn user;       // its feature-tile-per-wave stack kernels, or NULL
 };
 
 static int check_cfg(const longer_config* c, Shape* s, bool need_inner, bool need_main) {
@@ -356,7 +371,7 @@ static int check_cfg(const longer_config* c, Shape* s, bool need_inner, bool nee
   s->seg = packed_seg_bytes(s->D, s->es);
   if ((size_t)(9 * s->D + s->FF) * 4 > s->seg) return fail(LONGER_ERR_ARG, "ffn_mult=%d too large for d=%d", c->ffn_mult, c->d);
   if (ffn_skewed(s->es, s->D) && s->FF < 64) return fail(LONGER_ERR_ARG, "ffn_mult * d = %d: the bf16 FFN needs a hidden width of at least 64", s->FF);
-  s->main_fn = s->inner_fn = nullptr; s->pair = nullptr; s->quad = nullptr; s->DH = s->DHi = 0;
+  s->main_fn = s->inner_fn = nullptr; s->pair = nullptr; s->quad = nullptr; s->user = nullptr; s->DH = s->DHi = 0;
   s->Di = c->d;
   if (c->merge == LONGER_MERGE_CONCAT) {
     if (c->d % c->K || (c->d / c->K) % 32)
@@ -370,6 +385,7 @@ static int check_cfg(const longer_config* c, Shape* s, bool need_inner, bool nee
     if (!s->main_fn) return fail(LONGER_ERR_ARG, "unsupported shape: dtype=%d d=%d head width=%d", c->dtype, c->d, s->DH);
     s->pair = find_pair(c->dtype, c->d, s->DH);
     s->quad = find_quad(c->dtype, c->d, s->DH);
+    s->user = find_user(c->dtype, c->d, s->DH);
   }
   if (need_inner) {
     if (c->inner_layers < 1) return fail(LONGER_ERR_ARG, "inner_layers=%d", c->inner_layers);
@@ -407,7 +423,7 @@ constexpr int kXcds = 8;
 // its workspace.
 //   merge stream   [input MLP][InnerTrans blocks, fused layout, back to back]
 //   reduced stack  [cross block, split layout]([its attention half, pair layout])[self blocks, fused layout, back to back]
-//                  (one stream: the stack kernel; the two-wave stack kernel starts at the pair copy and
+//                  (one stream: the stack kernel; at d = 128 it starts at the pair copy and
 //                  its self blocks are in the pair layout)
 //   per-layer plan [self blocks, split layout]                              (m + k > 128, cache build)
 //   scoring        [cross block, fused][self blocks, fused], back to back
@@ -419,8 +435,8 @@ struct PackedLayout {
 
 // a user's reduced rows fit one workgroup, and the stack kernel exists for the shape (block_kernel.h: kHasStackKernel)
 static bool stack_in_one_launch(const Shape& s) { return s.n <= 32 * kWaves && !(s.es == 4 && s.D >= 128); }
-// which launches run on the two-wave kernels (their parts of the packed parameters are in the pair layouts)
-static bool pair_stack(const Shape& s) { return s.pair && s.D == 128 && stack_in_one_launch(s); }   // (LDS: the K/V hand-over area fits at d = 128)
+// which launches' parts of the packed parameters are in the pair layouts
+static bool pair_stack(const Shape& s) { return s.user && s.D == 128 && stack_in_one_launch(s); }
 static bool pair_score(const Shape& s) { return s.pair != nullptr; }
 
 static PackedLayout packed_layout(const longer_config* c, const Shape& s) {
@@ -433,7 +449,7 @@ static PackedLayout packed_layout(const longer_config* c, const Shape& s) {
   o = align256(o + 4 * (s.seg > si.seg ? s.seg : si.seg));   // a stream may read whole panels past its end
   pl.score_stride = (size_t)fused_segs(s.D, s.FF) * s.seg;
   pl.cross = o; o += s.pb;                                  // the split layout fills its slot exactly:
-  // (two-wave stack kernel: a copy of the cross block's attention half in the pair layout heads the stream)
+  // (d = 128: a copy of the cross block's attention half in the pair layout heads the stack kernels' stream)
   pl.cross_pair = o; if (pair_stack(s)) o += (size_t)attn_segs(s.D, s.FF) * s.seg;
   pl.self_fused = o; o += (size_t)c->n_self * pl.score_stride;   // the stack kernel's stream runs on into these
   pl.self_split = o; o += (size_t)c->n_self * s.pb;
@@ -685,7 +701,14 @@ static int run_stack(const longer_config* c, const Shape& s, const char* packed_
     if (s.quad(MODE_STACK, 16, pair_stack(s), p, dim3(B), st)) return fail(LONGER_ERR_HIP, "stack launch failed");
     return 0;
   }
-  if (pair_stack(s) ? s.pair(MODE_STACK, 16, p, dim3(B), st) : s.main_fn(MODE_STACK, 1, 16, p, dim3(B), st))
+  // Up to four tiles, width 128 / 256: a wave per feature tile (user_kernel.h).  The stack's launch at 108 rows a user, microseconds with it /
+  // two waves a tile at width 128 (one at 256): width 128, 61 and 256 users 95 / 111, 128 / 143; 512 users of 72 rows 209 / 263;
+  // width 256, 256 users 277 / 349.
+  if (s.user) {
+    if (s.user(cdiv(s.n, 32), p, dim3(B), st)) return fail(LONGER_ERR_HIP, "stack launch failed");
+    return 0;
+  }
+  if (s.main_fn(MODE_STACK, 1, 16, p, dim3(B), st))
     return fail(LONGER_ERR_HIP, "stack launch failed");
   return 0;
 }
@@ -1099,7 +1122,7 @@ static int run_score(const longer_config* cfg, const Shape& s, const char* strea
     if (s.quad(MODE_SCORE, win, pair_score(s), p, grid, st)) return fail(LONGER_ERR_HIP, "score kernel launch failed");
     return 0;
   }
-  if (pair_score(s) ? s.pair(MODE_SCORE, win, p, grid, st) : s.main_fn(MODE_SCORE, 1, win, p, grid, st))
+  if (pair_score(s) ? s.pair(win, p, grid, st) : s.main_fn(MODE_SCORE, 1, win, p, grid, st))
     return fail(LONGER_ERR_HIP, "score kernel launch failed");
   return 0;
 }

@@ -1,10 +1,7 @@
-// The transformer-block kernel with a 32-row tile given to a PAIR of waves (bf16, d = 128 / 256):
+// The transformer-block kernel with a 32-row tile given to a PAIR of waves (bf16, d = 128 / 256): candidate scoring of
+// the KV-cache serving path (Section 3.6.3).
 //
-//   MODE_STACK  the whole reduced stack of one user in one workgroup (Eq. 10), as in block_kernel.h;
-//   MODE_SCORE  candidate scoring of the KV-cache serving path (Section 3.6.3).
-//
-// Why.  In these modes the number of tiles is fixed by the work (a user's m + k rows, or registers at
-// d = 256 allow one tile-wave per SIMD only), and a single wave per SIMD is bound by its own
+// Why.  Registers at d = 256 allow one tile-wave per SIMD only, and a single wave per SIMD is bound by its own
 // instruction issue and dependency latencies.  Here a workgroup has 8 waves, two per SIMD: waves t
 // and t + 4 share tile t.  They split every GEMM by output feature tile (wave half h owns tiles
 // 2 i + h), so neither holds fp32 partial sums of the other:
@@ -48,7 +45,7 @@ __device__ __forceinline__ void store_rows_half(const f32x16 (&x)[NTH], void* ba
   }
 }
 
-template <int D, int DH, int MODE, int W, bool RELU>
+template <int D, int DH, int W, bool RELU>
 __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams p) {
   using T = __bf16;
   using E = ET<T>;
@@ -57,8 +54,6 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
   constexpr int SEGV = NG * 64;
   constexpr int HPT = 32 / DH;        // heads per 32-feature tile
   constexpr int GPH = DH / E::GF;     // operand groups per head
-  constexpr bool STACK = MODE == MODE_STACK, SCORE = MODE == MODE_SCORE;
-  static_assert(STACK || SCORE, "pair kernel modes");
   static_assert(NT % 2 == 0 && (DH == 16 || DH == 32), "shape");
   constexpr int PSEG = 2;                           // a panel = the even and the odd tile's segment
   constexpr int NB = D >= 256 ? 2 : 3;              // ring depth in panels
@@ -66,8 +61,6 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
   __shared__ uint4 vecl[SEGV];                      // the current block's fp32 vectors
   __shared__ uint4 xch[4 * NG * 64];                // per tile: operand groups swapped inside the pair
   __shared__ float stat[4][2][2][32];               // per tile, half: LayerNorm partial sums / logit parts per row
-  // MODE_STACK: K and V fragments of the feature tile a half works on, [half][parity][key tile][K, V][group][lane]
-  __shared__ uint4 kvl[STACK ? 2 * 2 * 4 * 2 * GPT * 64 : 1];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 31, hi = lane >> 5;
   const int ts = wave & 3, h = wave >> 2;           // tile slot in the workgroup; which half of the pair
@@ -82,59 +75,20 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
   uint32_t wmask[16 / W];
 #pragma unroll
   for (int w = 0; w < 16 / W; ++w) { wmask[w] = widx == w ? 0xffffffffu : 0u; asm("" : "+v"(wmask[w])); }
-  int lo1 = 0, hi1 = 0, lo2 = 0, hi2 = 0, kthi = 0;     // cross layer: visible key ranges, key tile count
-  int slo1 = 0, shi1 = 0, slo2 = 0, shi2 = 0;           // self-causal layers of the stack
   f32x16 resid[NTH];
 
-  int wg = blockIdx.x, su = 0;
-  if (SCORE) {      // all candidate tiles of a user on one XCD (see block_kernel.h)
-    const int x = (int)blockIdx.x % p.xcds, sq = (int)blockIdx.x / p.xcds;
-    su = x + p.xcds * (sq / p.wg_per_user);
-    wg = sq % p.wg_per_user;
-    if (su >= p.B) return;
-  }
-  const int tile = wg * 4 + ts;
-  if (STACK) {
-    const int u = tile / p.tiles_per_user, qt = tile - u * p.tiles_per_user;
-    const int a = p.q0 + 32 * qt + j;
-    inrange = u < p.B && (32 * qt + j) < p.rows_per_user;
-    int len = 0;
-    if (u < p.B) { len = p.lens ? p.lens[u] : p.L; len = min(max(len, 0), p.L); }
-    const int tu = (len + p.K - 1) / p.K;
-    const bool glob = a < p.m;
-    const int i = a - p.m, i0 = first_slot(p.k, tu, p.q_learn);
-    valid = inrange && (glob || i >= i0);
-    usr = u; Tu = tu;
-    out_off = p.X_ustride * u + (long long)a * D;
-    const void* sp = glob ? p.src0.p : p.src1.p;
-    const int sf = glob ? p.src0.f32 : p.src1.f32;
-    const long long sus = glob ? p.src0.ustride : p.src1.ustride;
-    const int tok = glob ? 0 : (p.q_learn ? tu - 1 : slot_token(i, p.k, tu, p.k_uni));
-    const int row = glob ? a : (p.gather_recent ? tok : i);
-    load_rows_half<NTH>(resid, sp, sf, sus * u + (long long)row * D, valid, hi, h);
-    // visible key ranges (Eq. 8 by token type); keys of the cross layer are all T merged tokens
-    if (glob) {
-      lo1 = p.gmask_causal ? a : 0; hi1 = p.KG;
-      lo2 = p.KG; hi2 = p.KG + tu;
-    } else {
-      lo2 = p.KG; hi2 = p.KG + tok + 1;
-    }
-    if (!valid) { hi1 = lo1; hi2 = lo2; }
-    kthi = (p.KG + tu + 31) / 32;
-    if (u >= p.B) kthi = 0;
-    if (valid) {   // keys of a self-causal layer: the user's own rows, key index = row index
-      if (glob) { slo1 = p.gmask_causal ? a : 0; shi1 = p.m; slo2 = p.m + i0; shi2 = p.m + p.k; }
-      else { slo2 = p.m + i0; shi2 = p.m + i + 1; }
-    }
-  } else {  // MODE_SCORE
-    const int u = su;
+  // all candidate tiles of a user on one XCD (see block_kernel.h)
+  const int sq = (int)blockIdx.x / p.xcds, su = (int)blockIdx.x % p.xcds + p.xcds * (sq / p.wg_per_user);
+  if (su >= p.B) return;
+  const int tile = (sq % p.wg_per_user) * 4 + ts;
+  {
     const int a = 32 * tile + j;
     const int cand = a / p.m, gi = a - cand * p.m;
     inrange = cand < p.C;
     valid = inrange;
-    int len = p.lens ? p.lens[u] : p.L; len = min(max(len, 0), p.L);
-    usr = u; Tu = (len + p.K - 1) / p.K;
-    out_off = ((long long)u * p.C * p.m + a) * D;
+    int len = p.lens ? p.lens[su] : p.L; len = min(max(len, 0), p.L);
+    usr = su; Tu = (len + p.K - 1) / p.K;
+    out_off = ((long long)su * p.C * p.m + a) * D;
     load_rows_half<NTH>(resid, p.Gc, 0, out_off, valid, hi, h);
     const uint32_t vb = (uint32_t)__ballot(valid);
     const int gbase = p.m * (j / p.m);
@@ -142,8 +96,7 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
   }
 
   WStream<SEGV, PSEG, NB, false, kPairThreads> ws;
-  const int segs_fused = 2 + 4 * NT + 2 * NC, segs_attn = 2 + 2 * NT + 2 * NC;
-  ws.init(lds, p.wbase, STACK ? segs_attn + (p.n_layers - 1) * segs_fused : segs_fused * p.n_layers);
+  ws.init(lds, p.wbase, (2 + 4 * NT + 2 * NC) * p.n_layers);
 
   uint4* const xt = xch + (size_t)ts * NG * 64 + lane;      // this tile's exchange area, this lane's 16 bytes of a group
   // operand groups of own tiles go to the exchange area, the partner's come back
@@ -218,8 +171,6 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
     __syncthreads();
     ws.advance();
     ws.advance();            // [vec][unused]
-    const bool selfl = STACK && layer > 0;   // a self-causal layer of the stack: K/V made here
-    const bool own_kv = SCORE || selfl;      // K and V of this tile's rows are projected here
     layer_norm_pair(vec + vl.ln1_g(), vec + vl.ln1_b());
     grp oo[NGH], op[NGH];     // attention output of the own tiles / the partner's
 
@@ -233,35 +184,20 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
       f32x16 aq = gemm_tile(bias_tile(vec + vl.bq(), ft, hi), h, xo, xp);
       ws.advance();
       ws.advance();
-      f32x16 ak, av;
-      if (own_kv) {
-        ak = gemm_tile(splat16(0.f), h, xo, xp);   // no b_K: a per-query constant in the scores, softmax drops it
-        ws.advance();
-        ws.advance();
-        // no b_V (folded into the output bias); operands swapped: lane = feature
-        av = splat16(0.f);
+      f32x16 ak = gemm_tile(splat16(0.f), h, xo, xp);   // no b_K: a per-query constant in the scores, softmax drops it
+      ws.advance();
+      ws.advance();
+      // no b_V (folded into the output bias); operands swapped: lane = feature
+      f32x16 av = splat16(0.f);
 #pragma unroll
-        for (int i2 = 0; i2 < NTH; ++i2)
-#pragma unroll
-          for (int g = 0; g < GPT; ++g) {
-            av = E::mma(xo[i2 * GPT + g], ws.template frag_at<grp>(h, (2 * i2 + h) * GPT + g), av);
-            av = E::mma(xp[i2 * GPT + g], ws.template frag_at<grp>(h, (2 * i2 + (h ^ 1)) * GPT + g), av);
-          }
-        ws.advance();
-        ws.advance();
-      }
-      if (selfl) {
-        // this wave's rows are key tile ts of feature tile ft: hand K and V to the waves of the same half.
-        // Two buffers per half: one barrier per feature tile is enough (nobody can be two tiles ahead
-        // of a wave that still reads).
-        uint4* dstk = kvl + (size_t)((((h * 2 + (i & 1)) * 4 + ts) * 2) * GPT) * 64 + lane;
+      for (int i2 = 0; i2 < NTH; ++i2)
 #pragma unroll
         for (int g = 0; g < GPT; ++g) {
-          *reinterpret_cast<grp*>(dstk + g * 64) = E::pack(ak, g);
-          *reinterpret_cast<grp*>(dstk + (GPT + g) * 64) = E::pack(av, g);
+          av = E::mma(xo[i2 * GPT + g], ws.template frag_at<grp>(h, (2 * i2 + h) * GPT + g), av);
+          av = E::mma(xp[i2 * GPT + g], ws.template frag_at<grp>(h, (2 * i2 + (h ^ 1)) * GPT + g), av);
         }
-        __syncthreads();
-      }
+      ws.advance();
+      ws.advance();
 
       grp qop[GPT];   // Q carries log2(e) / sqrt(head width): the scores come out ready for exp2
       aq *= p.scale_l2e;
@@ -272,7 +208,7 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
 #pragma unroll
       for (int hh = 0; hh < HPT; ++hh) { mrun[hh] = kNegBig; lrun[hh] = 0.f; acc[hh] = splat16(0.f); }
 
-      if (SCORE) {   // keys of the lane's own tile: the candidate's own globals
+      {   // keys of the lane's own tile: the candidate's own globals
         grp kop[GPT], vop[GPT];
 #pragma unroll
         for (int g = 0; g < GPT; ++g) { kop[g] = E::pack(ak, g); vop[g] = E::pack(av, g); }
@@ -287,52 +223,19 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
           for (int g = 0; g < GPT; ++g) acc[hh] = E::mma(vop[g], pop[g], acc[hh]);
         }
       }
-      if (selfl) {   // K/V fragments of the user's own rows, from LDS
-        const int nkt = (p.m + p.k + 31) / 32;
-        for (int kt = 0; kt < nkt; ++kt) {
-          const uint32_t bits = range_bits(slo1, shi1, 32 * kt) | range_bits(slo2, shi2, 32 * kt);
-          const uint32_t ab = (bits >> (4 * hi)) & kTileBits;
-          if (__builtin_amdgcn_ballot_w64(ab != 0) == 0) continue;      // no query of the tile sees any of these keys
-          const bool full = __builtin_amdgcn_ballot_w64(ab != kTileBits) == 0;
-          const f32x16 vis = full ? splat16(0.f) : mask_tile(ab);
-          const uint4* srck = kvl + (size_t)((((h * 2 + (i & 1)) * 4 + kt) * 2) * GPT) * 64 + lane;
-          grp kfr[GPT], vfr[GPT];
-#pragma unroll
-          for (int g = 0; g < GPT; ++g) {
-            kfr[g] = *reinterpret_cast<const grp*>(srck + g * 64);
-            vfr[g] = *reinterpret_cast<const grp*>(srck + (GPT + g) * 64);
-          }
-#pragma unroll
-          for (int hh = 0; hh < HPT; ++hh) {
-            f32x16 S = vis;
-#pragma unroll
-            for (int g2 = 0; g2 < GPH; ++g2) S = E::mma(kfr[hh * GPH + g2], qop[hh * GPH + g2], S);
-            grp pop[GPT];
-            softmax_step<T, false>(S, 0u, mrun[hh], lrun[hh], acc[hh], pop);
-#pragma unroll
-            for (int g = 0; g < GPT; ++g) acc[hh] = E::mma(vfr[g], pop[g], acc[hh]);
-          }
-        }
-      }
-      if (SCORE || (STACK && !selfl)) {     // stored K/V fragments (wave-uniform user, scalar loop control)
+      {     // stored K/V fragments (wave-uniform user, scalar loop control)
         const int uu = __builtin_amdgcn_readfirstlane(usr);
         const int tuu = __builtin_amdgcn_readfirstlane(Tu);
         const char* kb; const char* vb; int nkt, rlo, rhi;
-        if (STACK) {
-          kb = p.kst + (size_t)uu * p.kv_ustride; vb = p.vst + (size_t)uu * p.kv_ustride;
-          nkt = __builtin_amdgcn_readfirstlane(kthi); rlo = 0; rhi = 0;
+        if (layer == 0) {
+          kb = p.cache + (size_t)uu * p.c0_ustride; vb = kb + p.c0_voff;
+          nkt = min(p.kt0, (tuu + 31) / 32); rlo = 0; rhi = tuu;
         } else {
-          const int i0 = first_slot(p.k, tuu, p.q_learn);
-          if (layer == 0) {
-            kb = p.cache + (size_t)uu * p.c0_ustride; vb = kb + p.c0_voff;
-            nkt = min(p.kt0, (tuu + 31) / 32); rlo = 0; rhi = tuu;
-          } else {
-            kb = p.cache + p.c1_off + (size_t)(layer - 1) * p.c1_lstride + (size_t)uu * p.c1_ustride;
-            vb = kb + p.c1_voff;
-            nkt = tuu > 0 ? p.kt1 : 0; rlo = i0; rhi = p.k;
-          }
-          if (!valid) rhi = rlo;
+          kb = p.cache + p.c1_off + (size_t)(layer - 1) * p.c1_lstride + (size_t)uu * p.c1_ustride;
+          vb = kb + p.c1_voff;
+          nkt = tuu > 0 ? p.kt1 : 0; rlo = first_slot(p.k, tuu, p.q_learn); rhi = p.k;
         }
+        if (!valid) rhi = rlo;
         // the fragments of key tile kt + 1 are requested before tile kt is worked on (d = 128; at
         // d = 256 the registers for that are not there, and the SIMD's other wave covers the latency)
         constexpr bool AHEAD = D < 256;
@@ -346,10 +249,7 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
           }
         }
         for (int kt = 0; kt < nkt; ++kt) {
-          uint32_t bits;
-          if (STACK) bits = range_bits(lo1, hi1, 32 * kt) | range_bits(lo2, hi2, 32 * kt);
-          else bits = range_bits(rlo, rhi, 32 * kt);
-          const uint32_t ab = (bits >> (4 * hi)) & kTileBits;
+          const uint32_t ab = (range_bits(rlo, rhi, 32 * kt) >> (4 * hi)) & kTileBits;
           const bool none = __builtin_amdgcn_ballot_w64(ab != 0) == 0;           // nobody sees any of these keys
           const bool full = __builtin_amdgcn_ballot_w64(ab != kTileBits) == 0;   // everybody sees all of them
           if (!AHEAD && none) continue;
@@ -456,16 +356,9 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
   if (p.X_out && inrange) store_rows_half<NTH>(resid, p.X_out, p.X_f32, out_off, valid, hi, h);
   if (p.logits) {
     // logit = <head_w, flatten(global rows)> + head_b: each wave sums over its own feature tiles
-    int a, width;       // row inside the head's m rows; lanes per logit
-    bool take;
-    if (STACK) {
-      const int qt = tile % p.tiles_per_user;
-      a = p.q0 + 32 * qt + j; take = valid && a < p.m; width = 32;
-    } else {
-      a = (32 * tile + j) % p.m; take = valid; width = p.m;
-    }
+    const int a = (32 * tile + j) % p.m;       // row inside the head's m rows (lanes per logit)
     float part = 0.f;
-    if (take) {
+    if (valid) {
 #pragma unroll
       for (int i = 0; i < NTH; ++i) {
         const f32x16 hw = bias_tile(p.head + (size_t)a * D, 2 * i + h, hi);
@@ -478,45 +371,29 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
     if (hi == 0) stat[ts][h][0][j] = part;
     __syncthreads();
     part = stat[ts][0][0][j] + stat[ts][1][0][j];
-    for (int sft = 1; sft < width; sft <<= 1) part += __shfl_xor(part, sft, 64);
+    for (int sft = 1; sft < p.m; sft <<= 1) part += __shfl_xor(part, sft, 64);
     part += p.head[(size_t)p.m * D];
-    if (h == 0) {
-      if (STACK) {
-        if (lane == 0 && usr < p.B && (tile % p.tiles_per_user) == 0 && p.q0 == 0) p.logits[usr] = part;
-      } else {
-        const int cand = (32 * tile + j) / p.m;
-        if (hi == 0 && (j % p.m) == 0 && cand < p.C) p.logits[(size_t)usr * p.C + cand] = part;
-      }
-    }
+    const int cand = (32 * tile + j) / p.m;
+    if (h == 0 && hi == 0 && (j % p.m) == 0 && cand < p.C) p.logits[(size_t)usr * p.C + cand] = part;
   }
 }
 
 // Host-side launcher, one definition per (D, DH) instantiation file.
 template <int D, int DH>
-int launch_pair(int mode, int win, const BlockParams& p, dim3 grid, hipStream_t stream);
+int launch_pair(int win, const BlockParams& p, dim3 grid, hipStream_t stream);
 
-#define LONGER_PAIR_LAUNCH(D, DH, MODEV, WV) \
+#define LONGER_PAIR_LAUNCH(D, DH, WV) \
   do {                                                                                                \
-    if (p.act == 1)                                                                                   \
-      hipLaunchKernelGGL((pair_kernel<D, DH, MODEV, WV, true>), grid, dim3(kPairThreads), 0, stream, p); \
-    else                                                                                              \
-      hipLaunchKernelGGL((pair_kernel<D, DH, MODEV, WV, false>), grid, dim3(kPairThreads), 0, stream, p); \
+    if (p.act == 1) hipLaunchKernelGGL((pair_kernel<D, DH, WV, true>), grid, dim3(kPairThreads), 0, stream, p); \
+    else hipLaunchKernelGGL((pair_kernel<D, DH, WV, false>), grid, dim3(kPairThreads), 0, stream, p); \
   } while (0)
 
 #define LONGER_PAIR_INSTANTIATE(D, DH)                                                                \
   template <>                                                                                         \
-  int launch_pair<D, DH>(int mode, int win, const BlockParams& p, dim3 grid, hipStream_t stream) {    \
-    switch (mode) {                                                                                   \
-      case MODE_STACK:       /* (the K/V hand-over area fits the LDS at d = 128 only) */            \
-        if constexpr (D <= 128) LONGER_PAIR_LAUNCH(D, DH, MODE_STACK, 16); else return -1;            \
-        break;                                                                                        \
-      case MODE_SCORE:                                                                                \
-        if (win == 4) LONGER_PAIR_LAUNCH(D, DH, MODE_SCORE, 4);                                       \
-        else if (win == 8) LONGER_PAIR_LAUNCH(D, DH, MODE_SCORE, 8);                                  \
-        else LONGER_PAIR_LAUNCH(D, DH, MODE_SCORE, 16);                                               \
-        break;                                                                                        \
-      default: return -1;                                                                             \
-    }                                                                                                 \
+  int launch_pair<D, DH>(int win, const BlockParams& p, dim3 grid, hipStream_t stream) {              \
+    if (win == 4) LONGER_PAIR_LAUNCH(D, DH, 4);                                                       \
+    else if (win == 8) LONGER_PAIR_LAUNCH(D, DH, 8);                                                  \
+    else LONGER_PAIR_LAUNCH(D, DH, 16);                                                               \
     return hipGetLastError() == hipSuccess ? 0 : -3;                                                  \
   }
 

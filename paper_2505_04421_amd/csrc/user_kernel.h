@@ -1,0 +1,378 @@
+// The whole reduced stack of a user (Eq. 10) with up to four tiles of 32 rows in one workgroup of eight waves (bf16, d = 128 / 256):
+// a wave owns a FEATURE tile (its part of the rows, of every product's result, its heads) for several row tiles.
+//
+// Why.  The kernels that give a row tile to one or two waves read every weight fragment once per row tile out of an LDS ring, and at
+// width 256 there is no room beside such a ring for a user's K and V: one wave per SIMD, every wait exposed.  Here a fragment
+// goes from L2 to the registers of the one wave that needs it and serves all of its row tiles (4 at width 256, 2 at width 128, where
+// two groups of waves take two row tiles each), LDS holds nothing but operands, and since a wave makes K and V of its heads
+// for its row tiles itself, at width 256 they never leave its registers.  Eight waves, two per SIMD.
+// Fragments are requested a product ahead as in quad_kernel.h.
+//
+// What bounds it: at width 256 LDS, which hands every product its row operand (1 KiB per matrix instruction and wave, the
+// 128 bytes a cycle that four SIMDs can use up), at width 128 the vector work of the attention.
+#pragma once
+#include "quad_kernel.h"
+
+namespace longer {
+
+constexpr int kUserWaves = 8;
+constexpr int user_groups(int d) { return kUserWaves / (d / 32); }     // groups of waves that share out the row tiles
+
+template <int D, int DH, int RT, int LAYOUT, bool RELU>
+__global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockParams p) {
+  using T = __bf16;
+  using E = ET<T>;
+  using grp = typename E::grp;
+  using hgrp = typename E::hgrp;
+  constexpr int NT = D / 32, NG = D / 16, WV = NT, TG = user_groups(D), TS = TG * RT, HPT = 32 / DH, GPH = DH / 16, kThr = 64 * kUserWaves;
+  constexpr bool HOLD = D <= 128;                    // (width 256: no registers for the output projection's fragments through the attention)
+  static_assert(2 * WV == NG, "as many fragments in a hidden chunk's second product as in its first");
+  __shared__ grp ops[TS][NG][64];                    // normalised rows: [row tile][group][lane]
+  __shared__ grp mid[TS][NT][2][64];                 // [row tile][wave][group][lane]: Q, then the attention output; activated hidden chunks
+  __shared__ float2 sums[TS][NT][32];                // row sums: [row tile][wave][row]
+  __shared__ grp kvl[TG > 1 ? TS : 1][TG > 1 ? NT : 1][2][2][64];      // self layers, several groups: [key tile][feature tile][K, V][group][lane]
+  __shared__ f32x4 vecl[D * 4];                      // the block's fp32 vectors (at most one segment)
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ft = wv % WV, t0 = (wv / WV) * RT;    // feature tile, first row tile
+  int tid = threadIdx.x, lane = tid & 63, j = lane & 31, hi = lane >> 5;
+  unsigned lane16 = (unsigned)lane * 16u;
+  auto afresh = [&] {                                // (see quad_kernel.h)
+    asm volatile("" : "+v"(tid));
+    lane = tid & 63; j = lane & 31; hi = lane >> 5; lane16 = (unsigned)lane * 16u;
+  };
+  const int NC = p.FF / 32, usr = (int)blockIdx.x, rows = p.rows_per_user;
+  QuadSegs<LAYOUT, D> sg = {NC, true};               // (the first block is the cross layer's attention half)
+  int len = p.lens ? p.lens[usr] : p.L; len = min(max(len, 0), p.L);
+  const int tu = (len + p.K - 1) / p.K, i0 = first_slot(p.k, tu, p.q_learn);
+
+  // ------------------------------------------------------------------ rows
+  auto row_valid = [&](int a) { return a < rows && (a < p.m || a - p.m >= i0); };
+  auto row_token = [&](int a) { return p.q_learn ? tu - 1 : slot_token(a - p.m, p.k, tu, p.k_uni); };   // newest merged token slot row a sees
+  f32x16 x[RT];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    const int a = 32 * (t0 + rt) + j;
+    const bool glob = a < p.m;
+    const int row = glob ? a : (p.gather_recent ? row_token(a) : a - p.m);
+    f32x16 one[1];
+    load_rows<T, 1>(one, glob ? p.src0.p : p.src1.p, glob ? p.src0.f32 : p.src1.f32,
+                    (glob ? p.src0.ustride : p.src1.ustride) * usr + (long long)row * D + 32 * ft, row_valid(a), hi);
+    x[rt] = one[0];
+  }
+
+  const char* wl = p.wbase;                          // the current block's stream
+  const VecLayout vl{D, p.FF};
+  const float* vec = reinterpret_cast<const float*>(vecl);
+  grp fr[NG];
+  typedef __attribute__((address_space(1))) const char gchar;
+  typedef __attribute__((address_space(1))) const grp ggrp;
+  auto segment = [&](const char* w, int seg) -> gchar* {       // (wave-uniform: a scalar base, the lane's part an offset)
+    gchar* q = (gchar*)(w + (size_t)(unsigned)__builtin_amdgcn_readfirstlane(seg * (NG * 1024)));
+    asm("" : "+s"(q));
+    return q;
+  };
+  auto load = [&](gchar* q, int s) -> grp { return *(ggrp*)(q + (lane16 + (unsigned)s * 1024u)); };
+  auto request = [&](gchar* q) {
+#pragma unroll
+    for (int s = 0; s < NG; ++s) fr[s] = load(q, s);
+  };
+  // acc[rt] += (32 result features) of row tile rt's operand groups b(rt, s), which come out of LDS a step ahead; then(s): the
+  // request that takes the registers of fragment s.  SWAP: result with lane = feature
+  auto product = [&](f32x16 (&acc)[RT], auto swap, auto b, auto mma, auto then) __attribute__((always_inline)) {
+    grp cur[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) cur[rt] = b(rt, 0);
+#pragma unroll
+    for (int s = 0; s < NG; ++s) {
+      grp nxt[RT];
+      if (s + 1 < NG) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) nxt[rt] = b(rt, s + 1);
+      }
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) acc[rt] = swap ? mma(cur[rt], fr[s], acc[rt]) : mma(fr[s], cur[rt], acc[rt]);
+      then(s);
+      __builtin_amdgcn_sched_barrier(0);
+      if (s + 1 < NG) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) cur[rt] = nxt[rt];
+      }
+    }
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) settle(acc[rt]);
+  };
+  auto mma16 = [](grp a, grp b, f32x16 c) { return E::mma(a, b, c); };
+  auto mma_h = [](grp a, grp b, f32x16 c) { return E::mma_h(a, __builtin_bit_cast(hgrp, b), c); };
+  auto normed = [&](int rt, int s) -> grp { return ops[t0 + rt][s][lane]; };
+  auto middle = [&](int rt, int s) -> grp { return mid[t0 + rt][s / 2][s & 1][lane]; };
+  constexpr std::false_type plain{};
+  constexpr std::true_type swapped{};
+
+  constexpr int VQ = (D * 4 + kThr - 1) / kThr;      // the block's vectors: this thread's share, on its way to LDS
+  f32x4 vq[VQ];
+  auto request_vec = [&](const char* w) {
+    const int n = (9 * D + p.FF) / 4;
+#pragma unroll
+    for (int i = 0; i < VQ; ++i) { const int c = tid + kThr * i; vq[i] = reinterpret_cast<const f32x4*>(w)[c < n ? c : 0]; }
+  };
+  request_vec(wl);
+  request(segment(wl, sg.q(ft)));
+  // LayerNorm of the rows: the next products' operand, in LDS
+  auto normalise = [&](int og, int ob) __attribute__((always_inline)) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      float s = 0.f, q = 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { s += x[rt][r]; q = fmaf(x[rt][r], x[rt][r], q); }
+      const float2 both = make_float2(sum_halves(s), sum_halves(q));
+      if (hi == 0) sums[t0 + rt][ft][j] = both;
+    }
+    __syncthreads();
+    const f32x16 g = bias_tile(vec + og, ft, hi), c = bias_tile(vec + ob, ft, hi);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      float2 t = make_float2(0.f, 0.f);
+#pragma unroll
+      for (int w = 0; w < NT; ++w) { const float2 q = sums[t0 + rt][w][j]; t.x += q.x; t.y += q.y; }
+      const float mean = t.x * (1.0f / D), var = fmaxf(t.y * (1.0f / D) - mean * mean, 0.f);
+      const float rstd = __builtin_amdgcn_rsqf(var + p.eps), shift = -mean * rstd;
+      f32x16 y;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) y[r] = fmaf(fmaf(x[rt][r], rstd, shift), g[r], c[r]);
+#pragma unroll
+      for (int g2 = 0; g2 < 2; ++g2) ops[t0 + rt][2 * ft + g2][lane] = E::pack(y, g2);
+    }
+    __syncthreads();
+  };
+
+  // One block; SELF: K and V of the user's own rows are made here.  Areas of LDS: `ops` is written by a LayerNorm when everybody
+  // has passed the barriers behind its last readers (Q / K / V, W1), `sums` likewise; a wave's part of `mid` is its own up to
+  // the barrier behind the attention.
+  auto block = [&](auto selfl, bool last) __attribute__((always_inline)) {
+    constexpr bool SELF = decltype(selfl)::value;
+    const char* wnext = wl + (size_t)sg.block() * D * 64;
+    afresh();
+#pragma unroll
+    for (int i = 0; i < VQ; ++i) { const int c = tid + kThr * i; if (c < D * 4) vecl[c] = vq[i]; }
+    normalise(vl.ln1_g(), vl.ln1_b());
+    grp kop[SELF && TG == 1 ? RT : 1][2], vop[SELF && TG == 1 ? RT : 1][2];
+    {
+      f32x16 a[RT];
+      const f32x16 bias = bias_tile(vec + vl.bq(), ft, hi);
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) a[rt] = bias;
+      gchar* next = segment(wl, SELF ? sg.k(ft) : sg.o(ft));
+      product(a, plain, normed, mma16, [&](int s) { if (SELF || HOLD) fr[s] = load(next, s); });
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        a[rt] *= p.scale_l2e;
+#pragma unroll
+        for (int g = 0; g < 2; ++g) mid[t0 + rt][ft][g][lane] = E::pack(a[rt], g);
+      }
+      if constexpr (SELF) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {                // K, V (no b_K, no b_V: see block_kernel.h; V with lane = feature)
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) a[rt] = splat16(0.f);
+          next = segment(wl, m == 0 ? sg.v(ft) : sg.o(ft));
+          auto then = [&](int s) { if (m == 0 || HOLD) fr[s] = load(next, s); };
+          if (m == 0) product(a, plain, normed, mma16, then); else product(a, swapped, normed, mma16, then);
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) {
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+              const grp v = E::pack(a[rt], g);
+              if constexpr (TG == 1) { if (m == 0) kop[rt][g] = v; else vop[rt][g] = v; }
+              else kvl[t0 + rt][ft][m][g][lane] = v;
+            }
+          }
+        }
+        if (TG > 1) __syncthreads();
+      }
+    }
+    // ---- attention of the wave's heads, a row tile at a time
+#pragma unroll 1
+    for (int rt = 0; rt < RT; ++rt) {
+      const int a = 32 * (t0 + rt) + j;
+      if (32 * (t0 + rt) >= rows) break;
+      const bool ok = row_valid(a), glob = a < p.m;
+      // visible key ranges (Eq. 8 by token type); a self layer's keys are the user's own rows, key index = row index
+      int lo1 = 0, hi1 = 0, lo2, hi2;
+      if (glob) { lo1 = p.gmask_causal ? a : 0; hi1 = SELF ? p.m : p.KG; }
+      if (SELF) { lo2 = p.m + i0; hi2 = glob ? p.m + p.k : a + 1; }
+      else { lo2 = p.KG; hi2 = p.KG + (glob ? tu : row_token(a) + 1); }
+      if (!ok) { hi1 = lo1; hi2 = lo2; }
+      grp qop[2];
+#pragma unroll
+      for (int g = 0; g < 2; ++g) qop[g] = mid[t0 + rt][ft][g][lane];
+      float mrun[HPT], lrun[HPT];
+      f32x16 acc[HPT];
+#pragma unroll
+      for (int hh = 0; hh < HPT; ++hh) { mrun[hh] = kNegBig; lrun[hh] = 0.f; acc[hh] = splat16(0.f); }
+      auto key_tile = [&](int kt, const grp (&k)[2], const grp (&v)[2]) __attribute__((always_inline)) {
+        const uint32_t ab = ((range_bits(lo1, hi1, 32 * kt) | range_bits(lo2, hi2, 32 * kt)) >> (4 * hi)) & kTileBits;
+        if (__builtin_amdgcn_ballot_w64(ab != 0) == 0) return;                 // nobody sees any of these keys
+        const bool full = __builtin_amdgcn_ballot_w64(ab != kTileBits) == 0;   // everybody sees all of them
+        const f32x16 vis = full ? splat16(0.f) : mask_tile(ab);
+#pragma unroll
+        for (int hh = 0; hh < HPT; ++hh) {
+          f32x16 S = vis;
+#pragma unroll
+          for (int g2 = 0; g2 < GPH; ++g2) S = E::mma(k[hh * GPH + g2], qop[hh * GPH + g2], S);
+          grp pop[2];
+          softmax_step<T, false>(S, 0u, mrun[hh], lrun[hh], acc[hh], pop);
+#pragma unroll
+          for (int g = 0; g < 2; ++g) acc[hh] = E::mma(v[g], pop[g], acc[hh]);
+        }
+      };
+      if constexpr (SELF) {
+        const int nkt = (rows + 31) / 32;
+        if constexpr (TG == 1) {
+#pragma unroll
+          for (int kt = 0; kt < RT; ++kt)
+            if (kt < nkt) key_tile(kt, kop[kt], vop[kt]);
+        } else {
+          for (int kt = 0; kt < nkt; ++kt) {
+            grp k[2], v[2];
+#pragma unroll
+            for (int g = 0; g < 2; ++g) { k[g] = kvl[kt][ft][0][g][lane]; v[g] = kvl[kt][ft][1][g][lane]; }
+            key_tile(kt, k, v);
+          }
+        }
+      } else {                                       // stored K / V fragments (scalar loop control), KD key tiles on their way
+        constexpr int KD = 4;
+        const int nkt = __builtin_amdgcn_readfirstlane((p.KG + tu + 31) / 32);
+        const char* kb = nkt > 0 ? p.kst + (size_t)usr * p.kv_ustride : wl;    // (readable in any case: requests are unconditional)
+        const char* vb = nkt > 0 ? p.vst + (size_t)usr * p.kv_ustride : wl;
+        grp kn[KD][2], vn[KD][2];
+        auto fetch = [&](int kt, int b) {
+          const size_t fo = ((size_t)(min(kt, max(nkt - 1, 0)) * NT + ft) * 2) * 1024 + lane16;
+#pragma unroll
+          for (int g = 0; g < 2; ++g) {
+            kn[b][g] = *reinterpret_cast<const grp*>(kb + fo + g * 1024);
+            vn[b][g] = *reinterpret_cast<const grp*>(vb + fo + g * 1024);
+          }
+        };
+#pragma unroll
+        for (int b = 0; b < KD; ++b) fetch(b, b);
+        for (int kt = 0; kt < nkt; kt += KD) {
+#pragma unroll
+          for (int b = 0; b < KD; ++b) {
+            if (kt + b < nkt) key_tile(kt + b, kn[b], vn[b]);
+            fetch(kt + b + KD, b);
+          }
+        }
+      }
+      f32x16 o;
+      float inv[HPT];
+#pragma unroll
+      for (int hh = 0; hh < HPT; ++hh) { settle(acc[hh]); inv[hh] = lrun[hh] > 0.f ? __builtin_amdgcn_rcpf(lrun[hh]) : 0.f; }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[r] = acc[HPT == 1 ? 0 : r / 8][r] * inv[HPT == 1 ? 0 : r / 8];
+#pragma unroll
+      for (int g = 0; g < 2; ++g) mid[t0 + rt][ft][g][lane] = E::pack(o, g);
+    }
+    if (!HOLD) request(segment(wl, sg.o(ft)));
+    __syncthreads();
+    {
+      const f32x16 bias = bias_tile(vec + vl.bo(), ft, hi);
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) x[rt] += bias;
+      gchar* next = segment(wl, sg.w1(ft));          // (at least as many hidden chunks as feature tiles: FF >= d)
+      product(x, plain, middle, mma16, [&](int s) { fr[s] = load(next, s); });
+    }
+    afresh();
+    request_vec(last ? wl : wnext);
+    normalise(vl.ln2_g(), vl.ln2_b());
+    {
+      const f32x16 bias = bias_tile(vec + vl.b2(), ft, hi);
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) x[rt] += bias;
+    }
+    for (int c0 = 0; c0 < NC; c0 += WV) {            // (FF is a multiple of d: every wave has a chunk)
+      f32x16 ah[RT];
+      const f32x16 bias = bias_tile(vec + vl.b1(), c0 + ft, hi);
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) ah[rt] = bias;
+      product(ah, plain, normed, mma16, [&](int s) { fr[s] = load(segment(wl + 2048 * ft, sg.w2(c0 + s / 2)), s & 1); });
+      if (c0 > 0) __syncthreads();                   // everybody has read the chunks before
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+          f16x8 y;     // ah holds x / kFfnScale; to fp16 toward zero, then the packed activation
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const f16x2 y2 = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(ah[rt][8 * g + 2 * e], ah[rt][8 * g + 2 * e + 1]));
+            y[2 * e] = y2[0]; y[2 * e + 1] = y2[1];
+          }
+          y = RELU ? __builtin_elementwise_max(y, (f16x8)((_Float16)0.f)) : gelu_quarter_h8(y);
+          mid[t0 + rt][ft][g][lane] = __builtin_bit_cast(grp, y);
+        }
+      }
+      // what follows on these chunks' second product: the next hidden chunk, or the next block's first
+      gchar* next = segment(wl, sg.w1(min(c0 + WV, NC - WV) + ft));
+      if (c0 + WV >= NC && !last) next = segment(wnext, QuadSegs<LAYOUT, D>{NC, false}.q(ft));
+      __syncthreads();
+      product(x, plain, middle, mma_h, [&](int s) { fr[s] = load(next, s); });
+    }
+    wl = wnext;
+    sg.attn = false;
+  };
+  block(std::false_type{}, p.n_layers == 1);
+  for (int layer = 1; layer < p.n_layers; ++layer) block(std::true_type{}, layer + 1 == p.n_layers);
+
+  // ------------------------------------------------------------------ epilogue
+  afresh();
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    const int a = 32 * (t0 + rt) + j;
+    const f32x16 one[1] = {x[rt]};
+    if (p.X_out && a < rows) store_rows<T, 1>(one, p.X_out, p.X_f32, p.X_ustride * usr + (long long)a * D + 32 * ft, row_valid(a), hi);
+  }
+  if (p.logits) {      // logit = <head_w, flatten(global rows)> + head_b: all global rows are in the first tile (m <= 32)
+    float part = 0.f;
+    if (t0 == 0 && j < p.m) {
+      const f32x16 hw = bias_tile(p.head + (size_t)j * D, ft, hi);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) part += x[0][r] * hw[r];
+    }
+    part = sum_halves(part);
+    for (int sft = 1; sft < 32; sft <<= 1) part += __shfl_xor(part, sft, 64);
+    if (t0 == 0 && lane == 0) sums[0][ft][0].x = part;      // (last read ahead of the FFN's barriers)
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      float logit = p.head[(size_t)p.m * D];
+#pragma unroll
+      for (int w = 0; w < NT; ++w) logit += sums[0][w][0].x;
+      p.logits[usr] = logit;
+    }
+  }
+}
+
+// Host-side launcher, one definition per (D, DH) instantiation file; tiles: row tiles of a user (at most four)
+template <int D, int DH>
+int launch_user(int tiles, const BlockParams& p, dim3 grid, hipStream_t stream);
+
+#define LONGER_USER_LAUNCH(D, DH, RT, LAY) \
+  do {                                                                                                \
+    if (p.act == 1) hipLaunchKernelGGL((user_kernel<D, DH, RT, LAY, true>), grid, dim3(64 * kUserWaves), 0, stream, p); \
+    else hipLaunchKernelGGL((user_kernel<D, DH, RT, LAY, false>), grid, dim3(64 * kUserWaves), 0, stream, p); \
+  } while (0)
+
+// (width 128 streams the pair layouts, width 256 the plain ones)
+#define LONGER_USER_INSTANTIATE_128(DH)                                                               \
+  template <>                                                                                         \
+  int launch_user<128, DH>(int, const BlockParams& p, dim3 grid, hipStream_t stream) {                \
+    LONGER_USER_LAUNCH(128, DH, 2, QUAD_PAIR);                                                        \
+    return hipGetLastError() == hipSuccess ? 0 : -3;                                                  \
+  }
+#define LONGER_USER_INSTANTIATE_256(DH)                                                               \
+  template <>                                                                                         \
+  int launch_user<256, DH>(int tiles, const BlockParams& p, dim3 grid, hipStream_t stream) {          \
+    if (tiles <= 2) LONGER_USER_LAUNCH(256, DH, 2, QUAD_PLAIN);                                       \
+    else if (tiles == 3) LONGER_USER_LAUNCH(256, DH, 3, QUAD_PLAIN);                                  \
+    else LONGER_USER_LAUNCH(256, DH, 4, QUAD_PLAIN);                                                  \
+    return hipGetLastError() == hipSuccess ? 0 : -3;                                                  \
+  }
+
+}  // namespace longer

@@ -104,3 +104,20 @@ def test_few_tiles_with_any_number_of_hidden_chunks_and_key_tiles(d, heads, ffn_
     case["lens"][:] = [1200, 0, 20, 633]
     _entry_points(case, TOL["bf16"], with_inner=False, logits_by_terms=True)
     _serving(case, TOL["bf16"], logits_by_terms=True)
+
+
+# The reduced stack of users with up to four tiles (m + k <= 128), bf16, d = 128 / 256: two tiles (256), three, four, rows that end
+# inside a tile, users without a token and with fewer tokens than query slots, every mask and query strategy, one hidden chunk a wave
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,heads,m,k,extra", [(128, 8, 8, 57, {}), (128, 4, 8, 88, dict(gmask="causal")), (128, 8, 32, 96, {}), (128, 8, 4, 93, dict(k_uniform=40)),
+                                               (128, 4, 2, 101, dict(q_learnable=True)), (256, 8, 1, 5, {}), (256, 16, 8, 56, dict(gmask="causal")),
+                                               (256, 8, 8, 64, dict(k_uniform=20)), (256, 16, 8, 100, {}), (256, 8, 32, 96, dict(ffn_mult=1)),
+                                               (256, 8, 8, 100, dict(q_learnable=True, gmask="causal"))])
+def test_stack_of_up_to_four_tiles(d, heads, m, k, extra):
+    import longer_synth as synth
+    from test_gpu_parity import _entry_points, TOL
+    cfg = synth.CONFIGS["C2"].replace(B=5, L=700, K=4, d=d, heads=heads, inner_heads=heads, m=m, k_recent=k, n_self=2, ragged=True,
+                                      len_lo=0, len_hi=700, index=83, **extra)
+    case = synth.make_case(cfg)
+    case["lens"][:4] = [700, 0, 9, 260]
+    _entry_points(case, TOL["bf16"], with_inner=False, logits_by_terms=True)
