@@ -226,16 +226,16 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
       {     // stored K/V fragments (wave-uniform user, scalar loop control)
         const int uu = __builtin_amdgcn_readfirstlane(usr);
         const int tuu = __builtin_amdgcn_readfirstlane(Tu);
-        const char* kb; const char* vb; int nkt, rlo, rhi;
+        const char* kb; const char* vb; int nkt; KeyRanges kr = {};
         if (layer == 0) {
           kb = p.cache + (size_t)uu * p.c0_ustride; vb = kb + p.c0_voff;
-          nkt = min(p.kt0, (tuu + 31) / 32); rlo = 0; rhi = tuu;
+          nkt = min(p.kt0, (tuu + 31) / 32); kr.hi2 = tuu;
         } else {
           kb = p.cache + p.c1_off + (size_t)(layer - 1) * p.c1_lstride + (size_t)uu * p.c1_ustride;
           vb = kb + p.c1_voff;
-          nkt = tuu > 0 ? p.kt1 : 0; rlo = first_slot(p.k, tuu, p.q_learn); rhi = p.k;
+          nkt = tuu > 0 ? p.kt1 : 0; kr.lo2 = first_slot(p.k, tuu, p.q_learn); kr.hi2 = p.k;
         }
-        if (!valid) rhi = rlo;
+        kr.settle_for(valid);
         // the fragments of key tile kt + 1 are requested before tile kt is worked on (d = 128; at
         // d = 256 the registers for that are not there, and the SIMD's other wave covers the latency)
         constexpr bool AHEAD = D < 256;
@@ -249,10 +249,6 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
           }
         }
         for (int kt = 0; kt < nkt; ++kt) {
-          const uint32_t ab = (range_bits(rlo, rhi, 32 * kt) >> (4 * hi)) & kTileBits;
-          const bool none = __builtin_amdgcn_ballot_w64(ab != 0) == 0;           // nobody sees any of these keys
-          const bool full = __builtin_amdgcn_ballot_w64(ab != kTileBits) == 0;   // everybody sees all of them
-          if (!AHEAD && none) continue;
           grp kfr[GPT], vfr[GPT];
           if (AHEAD) {
 #pragma unroll
@@ -273,18 +269,7 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
               vnx[g] = *reinterpret_cast<const grp*>(vb + fo + g * 1024);
             }
           }
-          if (none) continue;
-          const f32x16 vis = full ? splat16(0.f) : mask_tile(ab);
-#pragma unroll
-          for (int hh = 0; hh < HPT; ++hh) {
-            f32x16 S = vis;
-#pragma unroll
-            for (int g2 = 0; g2 < GPH; ++g2) S = E::mma(kfr[hh * GPH + g2], qop[hh * GPH + g2], S);
-            grp pop[GPT];
-            softmax_step<T, false>(S, 0u, mrun[hh], lrun[hh], acc[hh], pop);
-#pragma unroll
-            for (int g = 0; g < GPT; ++g) acc[hh] = E::mma(vfr[g], pop[g], acc[hh]);
-          }
+          key_tile_step<HPT, GPH>(kr, kt, kfr, vfr, qop, hi, mrun, lrun, acc);
         }
       }
       // normalise; with two heads per tile each head owns half of the accumulator rows

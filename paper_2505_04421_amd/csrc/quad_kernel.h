@@ -83,8 +83,8 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_wa
   int usr, Tu, tile;
   long long out_off;
   uint32_t tilebits = 0;
-  int lo1 = 0, hi1 = 0, lo2 = 0, hi2 = 0, kthi = 0;    // visible key ranges of the stored keys, their tiles
-  int slo1 = 0, shi1 = 0, slo2 = 0, shi2 = 0;          // the stack's self layers
+  KeyRanges kr = {}, skr = {};                         // visible keys among the stored ones; in the stack's self layers
+  int kthi = 0;                                        // tiles of the stored keys
   const int widx = W == 16 ? 0 : j / (2 * W);
   uint32_t wmask[16 / W];
 #pragma unroll
@@ -126,17 +126,15 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_wa
     const int row = glob ? a : (p.gather_recent ? tok : i);
     load_own(glob ? p.src0.p : p.src1.p, glob ? p.src0.f32 : p.src1.f32, (glob ? p.src0.ustride : p.src1.ustride) * usr + (long long)row * D);
     const int s0 = p.key_self ? i0 : 0;
-    if (glob) {
-      lo1 = p.gmask_causal ? a : 0; hi1 = p.KG;
-      lo2 = p.KG + s0; hi2 = p.KG + (p.key_self ? p.k : tu);
-    } else {
-      lo2 = p.KG + s0; hi2 = p.KG + (p.key_self ? i : tok) + 1;
-    }
-    if (!valid) { hi1 = lo1; hi2 = lo2; }
+    if (glob) { kr.lo1 = p.gmask_causal ? a : 0; kr.hi1 = p.KG; }
+    kr.lo2 = p.KG + s0;
+    kr.hi2 = p.KG + (glob ? (p.key_self ? p.k : tu) : (p.key_self ? i : tok) + 1);
+    kr.settle_for(valid);
     kthi = (p.KG + (p.key_self ? p.k : tu) + 31) / 32;
-    if (STACK && valid) {      // keys of a self-causal layer: the user's own rows, key index = row index
-      if (glob) { slo1 = p.gmask_causal ? a : 0; shi1 = p.m; slo2 = p.m + i0; shi2 = p.m + p.k; }
-      else { slo2 = p.m + i0; shi2 = p.m + i + 1; }
+    if (STACK) {      // keys of a self-causal layer: the user's own rows, key index = row index
+      if (glob) { skr.lo1 = p.gmask_causal ? a : 0; skr.hi1 = p.m; }
+      skr.lo2 = p.m + i0; skr.hi2 = p.m + (glob ? p.k : i + 1);
+      skr.settle_for(valid);
     }
   }
 
@@ -264,7 +262,7 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_wa
         for (int hh = 0; hh < HPT; ++hh) { mrun[hh] = kNegBig; lrun[hh] = 0.f; acc[hh] = splat16(0.f); }
         // stored K/V fragments (wave-uniform user, scalar loop control); KD key tiles on their way
         constexpr int KD = STACK ? 2 : 4;
-        const char* kb; const char* vb; int nkt, rlo = 0, rhi = 0;
+        const char* kb; const char* vb; int nkt;
         const int tuu = __builtin_amdgcn_readfirstlane(Tu);
         if (selfl) {
           kb = vb = nullptr; nkt = (p.m + p.k + 31) / 32;
@@ -274,13 +272,13 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_wa
         } else {
           if (layer == 0) {
             kb = p.cache + (size_t)usr * p.c0_ustride; vb = kb + p.c0_voff;
-            nkt = min(p.kt0, (tuu + 31) / 32); rhi = tuu;
+            nkt = min(p.kt0, (tuu + 31) / 32); kr = {0, 0, 0, tuu};
           } else {
             kb = p.cache + p.c1_off + (size_t)(layer - 1) * p.c1_lstride + (size_t)usr * p.c1_ustride;
             vb = kb + p.c1_voff;
-            nkt = tuu > 0 ? p.kt1 : 0; rlo = first_slot(p.k, tuu, p.q_learn); rhi = p.k;
+            nkt = tuu > 0 ? p.kt1 : 0; kr = {0, 0, first_slot(p.k, tuu, p.q_learn), p.k};
           }
-          if (!valid) rhi = rlo;
+          kr.settle_for(valid);
         }
         if (nkt == 0) kb = vb = wl;                    // (readable: requests are made without asking, so that no value lives on through a branch)
         grp kn[KD][2], vn[KD][2];
@@ -314,24 +312,8 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_wa
             for (int g = 0; g < 2; ++g) acc[hh] = E::mma(vop[g], pop[g], acc[hh]);
           }
         }
-        auto key_tile = [&](int kt, int b) {
-          const uint32_t bits = SCORE ? range_bits(rlo, rhi, 32 * kt)
-                              : selfl ? range_bits(slo1, shi1, 32 * kt) | range_bits(slo2, shi2, 32 * kt) : range_bits(lo1, hi1, 32 * kt) | range_bits(lo2, hi2, 32 * kt);
-          const uint32_t ab = (bits >> (4 * hi)) & kTileBits;
-          const bool none = __builtin_amdgcn_ballot_w64(ab != 0) == 0;           // nobody sees any of these keys
-          const bool full = __builtin_amdgcn_ballot_w64(ab != kTileBits) == 0;   // everybody sees all of them
-          if (none) { if (kt + KD < nkt) fetch(kt + KD, b); return; }
-          const f32x16 vis = full ? splat16(0.f) : mask_tile(ab);
-#pragma unroll
-          for (int hh = 0; hh < HPT; ++hh) {
-            f32x16 S = vis;
-#pragma unroll
-            for (int g2 = 0; g2 < GPH; ++g2) S = E::mma(kn[b][hh * GPH + g2], qop[hh * GPH + g2], S);
-            grp pop[2];
-            softmax_step<T, false>(S, 0u, mrun[hh], lrun[hh], acc[hh], pop);
-#pragma unroll
-            for (int g = 0; g < 2; ++g) acc[hh] = E::mma(vn[b][g], pop[g], acc[hh]);
-          }
+        auto key_tile = [&](int kt, int b) __attribute__((always_inline)) {
+          key_tile_step<HPT, GPH>(selfl ? skr : kr, kt, kn[b], vn[b], qop, hi, mrun, lrun, acc);
           if (kt + KD < nkt) fetch(kt + KD, b);
         };
         for (int kt = 0; kt < nkt; kt += KD) {

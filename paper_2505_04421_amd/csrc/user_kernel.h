@@ -196,11 +196,11 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
       if (32 * (t0 + rt) >= rows) break;
       const bool ok = row_valid(a), glob = a < p.m;
       // visible key ranges (Eq. 8 by token type); a self layer's keys are the user's own rows, key index = row index
-      int lo1 = 0, hi1 = 0, lo2, hi2;
-      if (glob) { lo1 = p.gmask_causal ? a : 0; hi1 = SELF ? p.m : p.KG; }
-      if (SELF) { lo2 = p.m + i0; hi2 = glob ? p.m + p.k : a + 1; }
-      else { lo2 = p.KG; hi2 = p.KG + (glob ? tu : row_token(a) + 1); }
-      if (!ok) { hi1 = lo1; hi2 = lo2; }
+      KeyRanges kr = {};
+      if (glob) { kr.lo1 = p.gmask_causal ? a : 0; kr.hi1 = SELF ? p.m : p.KG; }
+      if (SELF) { kr.lo2 = p.m + i0; kr.hi2 = glob ? p.m + p.k : a + 1; }
+      else { kr.lo2 = p.KG; kr.hi2 = p.KG + (glob ? tu : row_token(a) + 1); }
+      kr.settle_for(ok);
       grp qop[2];
 #pragma unroll
       for (int g = 0; g < 2; ++g) qop[g] = mid[t0 + rt][ft][g][lane];
@@ -208,22 +208,7 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
       f32x16 acc[HPT];
 #pragma unroll
       for (int hh = 0; hh < HPT; ++hh) { mrun[hh] = kNegBig; lrun[hh] = 0.f; acc[hh] = splat16(0.f); }
-      auto key_tile = [&](int kt, const grp (&k)[2], const grp (&v)[2]) __attribute__((always_inline)) {
-        const uint32_t ab = ((range_bits(lo1, hi1, 32 * kt) | range_bits(lo2, hi2, 32 * kt)) >> (4 * hi)) & kTileBits;
-        if (__builtin_amdgcn_ballot_w64(ab != 0) == 0) return;                 // nobody sees any of these keys
-        const bool full = __builtin_amdgcn_ballot_w64(ab != kTileBits) == 0;   // everybody sees all of them
-        const f32x16 vis = full ? splat16(0.f) : mask_tile(ab);
-#pragma unroll
-        for (int hh = 0; hh < HPT; ++hh) {
-          f32x16 S = vis;
-#pragma unroll
-          for (int g2 = 0; g2 < GPH; ++g2) S = E::mma(k[hh * GPH + g2], qop[hh * GPH + g2], S);
-          grp pop[2];
-          softmax_step<T, false>(S, 0u, mrun[hh], lrun[hh], acc[hh], pop);
-#pragma unroll
-          for (int g = 0; g < 2; ++g) acc[hh] = E::mma(v[g], pop[g], acc[hh]);
-        }
-      };
+      auto key_tile = [&](int kt, const grp (&k)[2], const grp (&v)[2]) __attribute__((always_inline)) { key_tile_step<HPT, GPH>(kr, kt, k, v, qop, hi, mrun, lrun, acc); };
       if constexpr (SELF) {
         const int nkt = (rows + 31) / 32;
         if constexpr (TG == 1) {
