@@ -30,6 +30,7 @@
 #include "bw_grads.h"
 #include "bw_set_attn.h"
 #include "bw_stack.h"
+#include "bw_input.h"
 
 #include <cstdio>
 
@@ -1140,17 +1141,29 @@ __global__ __launch_bounds__(256) void bw_split_input_grad_kernel(const float* _
     else *(f32x4*)(dtd + (size_t)r * (d - de) + (c - de)) = v;
   }
 }
-// dpos[p][c] = sum over the users whose sequence reaches position p of dx[u L + p][c], c < de
-__global__ __launch_bounds__(256) void bw_pos_grad_kernel(const float* __restrict__ dx, float* __restrict__ dpos, RowGeom q,
-                                                          int B, int d, int de) {
-  const size_t n = (size_t)q.L * de / 4;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-    const int p = (int)(i * 4 / de), c = (int)(i * 4 - (size_t)p * de);
-    f32x4 s = {0.f, 0.f, 0.f, 0.f};
-    for (int u = 0; u < B; ++u)
-      if (p < row_len(q, u)) s += *(const f32x4*)(dx + ((size_t)u * q.L + p) * d + c);
-    *(f32x4*)(dpos + i * 4) = s;
+// dpos[p][c] = sum over the users whose sequence reaches position p of dE[u L + p][c]: a workgroup sums 64 groups of four
+// adjacent values, each of its waves every fourth user (eight requests on their way: with one thread per sum and one request
+// at a time 90 users of 2500 positions took 33 us)
+__global__ __launch_bounds__(256) void bw_pos_grad_kernel(const float* __restrict__ dE, float* __restrict__ dpos, RowGeom q, int B, int de) {
+  __shared__ f32x4 red[4][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const size_t i = (size_t)blockIdx.x * 64 + lane, n = (size_t)q.L * de / 4;
+  const int p = i < n ? (int)(i * 4 / de) : 0x7fffffff;
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};
+  for (int u0 = w; u0 < B; u0 += 32) {
+    f32x4 v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int u = u0 + 4 * k;
+      v[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (u < B && p < row_len(q, u)) v[k] = *(const f32x4*)(dE + (size_t)u * q.L * de + i * 4);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s += v[k];
   }
+  red[w][lane] = s;
+  __syncthreads();
+  if (w == 0 && i < n) *(f32x4*)(dpos + i * 4) = red[0][lane] + red[1][lane] + red[2][lane] + red[3][lane];
 }
 
 // out[c][r] = in[r][c]  (bf16, small parameter matrices; 32 x 32 tiles through LDS)
@@ -1968,7 +1981,9 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
 
 // ------------------------------------------------------------------------------------
 // Input generation backward (longer_input_generation_backward)
-struct InputWs { size_t w1t, x, a, dyb, dh, dx, part, total; };
+// Widths 64 and 128: one launch over tiles (bw_input.h); others: kernels over row-major [token, feature] tensors.
+static bool input_tiled(int d) { return d == 64 || d == 128; }
+struct InputWs { size_t w1t, x, a, dyb, dh, dx, rec, part, total; };      // tiled: w1t holds the weight stream, rec the records
 static WgradBatch input_wgrads(int d, int f, size_t ntok, RowsValid rv, const __bf16* x, const __bf16* dh, const __bf16* a,
                                const __bf16* dyb, float* gw1, float* gw2) {
   WgradBatch w(d, ntok);
@@ -1976,17 +1991,32 @@ static WgradBatch input_wgrads(int d, int f, size_t ntok, RowsValid rv, const __
   w.add(x, d, d, dh, f, f, f, ntok, rv, gw1);
   return w;
 }
+static WgradBatch input_wgrads_tiles(int d, int f, size_t ntok, RowsValid rv, const __bf16* rec, float* gw1, float* gw2) {
+  const InputRecord r(d, f);
+  auto at = [&](int o) { return rec + (size_t)o * 512; };
+  WgradBatch w(d, ntok, true);
+  w.add(at(r.a), r.size, f, at(r.dyb), r.size, d, d, ntok, rv, gw2);
+  w.add(at(r.x), r.size, d, at(r.dh), r.size, f, f, ntok, rv, gw1);
+  return w;
+}
 static InputWs input_ws(size_t ntok, int d, int f) {
-  InputWs w;
+  InputWs w = {};
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += up256(bytes); return at; };
-  w.w1t = take((size_t)d * f * 2);
-  w.x = take(ntok * d * 2);
-  w.a = take(ntok * f * 2);
-  w.dyb = take(ntok * d * 2);
-  w.dh = take(ntok * f * 2);
-  w.dx = take(ntok * d * 4);
-  w.part = take(input_wgrads(d, f, ntok, RowsValid{}, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr).place(nullptr) * 4);
+  if (input_tiled(d)) {
+    const size_t tiles = (ntok + 32 * kBlkWaves - 1) / (32 * kBlkWaves) * kBlkWaves;      // whole workgroups
+    w.w1t = take((size_t)bw_input_segs_padded(f) * d * 64);
+    w.rec = take(tiles * InputRecord(d, f).size * 1024);
+    w.part = take(input_wgrads_tiles(d, f, ntok, RowsValid{}, nullptr, nullptr, nullptr).place(nullptr) * 4);
+  } else {
+    w.w1t = take((size_t)d * f * 2);
+    w.x = take(ntok * d * 2);
+    w.a = take(ntok * f * 2);
+    w.dyb = take(ntok * d * 2);
+    w.dh = take(ntok * f * 2);
+    w.dx = take(ntok * d * 4);
+    w.part = take(input_wgrads(d, f, ntok, RowsValid{}, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr).place(nullptr) * 4);
+  }
   w.total = o;
   return w;
 }
@@ -2136,25 +2166,44 @@ int longer_input_generation_backward(const longer_config* cfg, const longer_inpu
   const bw::InputGrads gl = bw::input_grads(L, d, f, d_e);
   hipStream_t st = (hipStream_t)stream;
   char* w8 = (char*)ws;
-  __bf16* x = (__bf16*)(w8 + l.x);   __bf16* w1t = (__bf16*)(w8 + l.w1t); __bf16* a = (__bf16*)(w8 + l.a);
-  __bf16* dyb = (__bf16*)(w8 + l.dyb); __bf16* dh = (__bf16*)(w8 + l.dh); float* dx = (float*)(w8 + l.dx);
   const bw::RowGeom q = {lens, L, 1, (int)nt};
   const bw::RowsValid rv = {lens, L};
-  const unsigned eg = bw::flat_grid(nt * d / 4);
-  bw::bw_input_rows_kernel<<<eg, 256, 0, st>>>((const __bf16*)E, (const __bf16*)w->pos, (const __bf16*)tdiff, x, q, d, d_e);
-  bw::bw_cast_rows_kernel<<<eg, 256, 0, st>>>(dH, dyb, q, d);
-  if ((rc = bw::launched("input rows"))) return rc;
-  // the hidden pre-activation is formed again inside the launch that takes its gradient (as in the merge's FFN)
-  if ((rc = bw::transpose(st, (const __bf16*)w->w1, w1t, d, f))) return rc;
-  if ((rc = bw::gemm_ffn_mid(st, x, dyb, d, w1t, (const __bf16*)w->w2, f, (const __bf16*)w->b1, nt, cfg->act, dh, a, rv))) return rc;
-  bw::WgradBatch wg = bw::input_wgrads(d, f, nt, rv, x, dh, a, dyb, grads_out + gl.w1, grads_out + gl.w2);
+  float* part = (float*)(w8 + l.part);
   bw::ReduceBatch rb;
-  if ((rc = bw::launch(wg, (float*)(w8 + l.part), st))) return rc;
-  rb.add(wg);
-  if ((rc = bw::launch(rb, st))) return rc;
-  if ((rc = bw::gemm_rows_t(st, dh, f, (const __bf16*)w->w1, d, nt, bw::EPI_F32, dx, rv))) return rc;
-  bw::bw_split_input_grad_kernel<<<eg, 256, 0, st>>>(dx, dE_out, dtdiff_out, q, d, d_e);
-  bw::bw_pos_grad_kernel<<<bw::flat_grid((size_t)L * d_e / 4), 256, 0, st>>>(dx, grads_out + gl.pos, q, B, d, d_e);
+  if (bw::input_tiled(d)) {
+    __bf16* stream_w = (__bf16*)(w8 + l.w1t);
+    __bf16* rec = (__bf16*)(w8 + l.rec);
+    bw::PackBatch pk(d, stream_w, st);
+    pk.add(w->w1, f, 1, false, f / 32, 0, 3);           // hidden values, their gradient, back through W1
+    pk.add(w->w2, 1, d, false, f / 32, 1, 3);
+    pk.add(w->w1, 1, f, true, f / 32, 2, 3);
+    if ((rc = pk.flush())) return rc;
+    const bw::InputBwParams p = {(const char*)stream_w, (const __bf16*)E, (const __bf16*)w->pos, (const __bf16*)tdiff, (const __bf16*)w->b1,
+                                 lens, B, L, d_e, f, cfg->act, dH, dE_out, dtdiff_out, rec};
+    if (d == 128) bw::bw_input_launch_128(p, st); else bw::bw_input_launch_64(p, st);
+    if ((rc = bw::launched("input gradient"))) return rc;
+    bw::WgradBatch wg = bw::input_wgrads_tiles(d, f, nt, rv, rec, grads_out + gl.w1, grads_out + gl.w2);
+    if ((rc = bw::launch(wg, part, st))) return rc;
+    rb.add(wg);
+    if ((rc = bw::launch(rb, st))) return rc;
+  } else {
+    __bf16* x = (__bf16*)(w8 + l.x);   __bf16* w1t = (__bf16*)(w8 + l.w1t); __bf16* a = (__bf16*)(w8 + l.a);
+    __bf16* dyb = (__bf16*)(w8 + l.dyb); __bf16* dh = (__bf16*)(w8 + l.dh); float* dx = (float*)(w8 + l.dx);
+    const unsigned eg = bw::flat_grid(nt * d / 4);
+    bw::bw_input_rows_kernel<<<eg, 256, 0, st>>>((const __bf16*)E, (const __bf16*)w->pos, (const __bf16*)tdiff, x, q, d, d_e);
+    bw::bw_cast_rows_kernel<<<eg, 256, 0, st>>>(dH, dyb, q, d);
+    if ((rc = bw::launched("input rows"))) return rc;
+    // the hidden pre-activation is formed again inside the launch that takes its gradient (as in the merge's FFN)
+    if ((rc = bw::transpose(st, (const __bf16*)w->w1, w1t, d, f))) return rc;
+    if ((rc = bw::gemm_ffn_mid(st, x, dyb, d, w1t, (const __bf16*)w->w2, f, (const __bf16*)w->b1, nt, cfg->act, dh, a, rv))) return rc;
+    bw::WgradBatch wg = bw::input_wgrads(d, f, nt, rv, x, dh, a, dyb, grads_out + gl.w1, grads_out + gl.w2);
+    if ((rc = bw::launch(wg, part, st))) return rc;
+    rb.add(wg);
+    if ((rc = bw::launch(rb, st))) return rc;
+    if ((rc = bw::gemm_rows_t(st, dh, f, (const __bf16*)w->w1, d, nt, bw::EPI_F32, dx, rv))) return rc;
+    bw::bw_split_input_grad_kernel<<<eg, 256, 0, st>>>(dx, dE_out, dtdiff_out, q, d, d_e);
+  }
+  bw::bw_pos_grad_kernel<<<(unsigned)(((size_t)L * d_e / 4 + 63) / 64), 256, 0, st>>>(dE_out, grads_out + gl.pos, q, B, d_e);
   return bw::launched("input gradient");
 }
 

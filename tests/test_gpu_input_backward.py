@@ -127,6 +127,16 @@ def test_input_generation_backward(d, d_e, B, L, act, ragged):
     _compare("d%d" % d, cfg, case, dH, d_e)
 
 
+# One row, a row less than a tile, a whole workgroup's tiles and one row of the next, more users than the positional sum takes at a
+# time, the narrowest and widest hidden layer (64 and 2048), and a width without a tile kernel
+@pytest.mark.parametrize("d,d_e,B,L,ffn_mult,ragged", [(64, 32, 1, 1, 4, False), (128, 32, 1, 31, 1, False), (128, 96, 41, 35, 2, True),
+                                                       (64, 32, 3, 43, 1, False), (64, 32, 1, 129, 32, False), (128, 64, 1, 128, 16, False),
+                                                       (96, 64, 3, 70, 4, True)])
+def test_input_generation_backward_tile_remainders(d, d_e, B, L, ffn_mult, ragged):
+    cfg, case, dH = _case(d, d_e, B, L, ragged=ragged, index=65, ffn_mult=ffn_mult)
+    _compare("d%d" % d, cfg, case, dH, d_e)
+
+
 def test_input_generation_backward_ignores_stale_workspace():
     """Workspace full of NaN before the call: no padded row and no stale value reaches a result."""
     cfg, case, dH = _case(128, 96, 6, 260, index=62)
