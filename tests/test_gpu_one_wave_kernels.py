@@ -121,3 +121,50 @@ def test_stack_of_up_to_four_tiles(d, heads, m, k, extra):
     case = synth.make_case(cfg)
     case["lens"][:4] = [700, 0, 9, 260]
     _entry_points(case, TOL["bf16"], with_inner=False, logits_by_terms=True)
+
+
+# Workgroups without a row to work on: key tiles past a user's last merged token are not projected (workspace and cache start as
+# NaN, 40 key tiles a user, of which users here need 40, 1, none and 2), padded raw tokens of the input generation come out as zeros
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,d,heads,k", [("f32", 32, 2, 9), ("bf16", 64, 4, 40), ("bf16", 64, 4, 90), ("bf16", 128, 8, 100), ("bf16", 256, 8, 40)])
+def test_workgroups_of_missing_rows_only(dtype, d, heads, k):
+    import numpy as np
+    import torch
+    import longer_synth as synth
+    import paper_2505_04421_amd as lg
+    from oracle import longer_oracle as orc
+    from test_gpu_parity import TOL, _check
+    cfg = synth.CONFIGS["C2"].replace(dtype=dtype, B=4, L=5000, K=4, d=d, heads=heads, inner_heads=heads, m=4, k_recent=k, n_self=1, C=6, ragged=True,
+                                      len_lo=0, len_hi=5000, index=89)
+    case = synth.make_case(cfg)
+    case["lens"][:] = [5000, 3, 0, 130]
+    model = lg.DeviceModel(cfg, case["weights"])
+    H, G, lens = model.upload(case["H"]), model.upload(case["G"]), torch.from_numpy(case["lens"].astype(np.int32)).to(model.device)
+    Gc = model.upload(case["G_cand"])
+    ws, cache = model.workspace(4, cfg.L).fill_(255), model.kv_cache(4, cfg.L).fill_(255)
+    Y, lo = model.empty(4, cfg.n, d), model.empty(4, dtype=torch.float32)
+    lg.longer_forward(model.ccfg, model.weights, H, G, lens, 4, cfg.L, Y, lo, ws)
+    ref, _ = orc.forward(cfg, case["weights"], case["H"], case["G"], case["lens"])
+    _check("longer_forward Y", Y.float().cpu().numpy().astype(np.float64), ref, TOL[dtype])
+    ws.fill_(255)
+    lg.longer_kv_cache_build(model.ccfg, model.weights, H, lens, 4, cfg.L, cache, ws)
+    Yg, ls = model.empty(4, cfg.C, 4, d), model.empty(4, cfg.C, dtype=torch.float32)
+    lg.longer_score_candidates(model.ccfg, model.weights, cache, lens, 4, cfg.L, Gc, cfg.C, Yg, ls, ws)
+    ref, _ = orc.score_candidates(cfg, case["weights"], orc.kv_cache_build(cfg, case["weights"], case["H"], case["lens"]), case["G_cand"])
+    _check("scores", Yg.float().cpu().numpy().astype(np.float64).reshape(-1, 4, d), ref.reshape(-1, 4, d), TOL[dtype])
+    if d == 64:
+        inp = synth.make_input_case(cfg, 32)
+        inp["lens"][:] = case["lens"]
+        pos = np.arange(cfg.L)[None, :, None]
+        g = np.random.default_rng(3)
+        E, td = (np.where(pos < inp["lens"][:, None, None], synth.round_bf16(g.standard_normal((4, cfg.L, 32)).astype(np.float32)), np.float32("nan"))
+                 for _ in range(2))
+        mlp = {n: model.upload(v) for n, v in inp["mlp"].items()}
+        iw = lg.CInputWeights(**{n: v.data_ptr() for n, v in mlp.items()})
+        X = model.empty(4, cfg.L, d).fill_(float("nan"))
+        lg.longer_input_generation(model.ccfg, iw, model.upload(E), model.upload(td), lens, 4, cfg.L, 32, X, ws)
+        got, ref = X.float().cpu().numpy().astype(np.float64), orc.input_generation(cfg, inp["mlp"], E, td, inp["lens"])
+        for u, n in enumerate(inp["lens"]):
+            assert not got[u, n:].any()
+            if n:
+                assert np.linalg.norm(got[u, :n] - ref[u, :n]) <= TOL[dtype] * np.linalg.norm(ref[u, :n])
