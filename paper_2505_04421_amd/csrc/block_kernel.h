@@ -62,6 +62,8 @@ struct BlockParams {
   char* kst; char* vst;
   size_t kv_ustride;
   int kt_per_user;
+  // MODE_ATTN of the few-tiles kernels: the next layer's stream (split layout) and where its K/V of the result rows go (NULL: nowhere)
+  const char* kv_w; char* kv_k; char* kv_v; size_t kv_w_ustride;
   int KG;               // number of global keys in front of the sequence keys
   int key_self;         // 1: sequence keys are the k recent slots, 0: all T merged tokens
   // MODE_ATTN / MODE_SCORE outputs; MODE_MERGE_KEEP: fp32 [block - 1][B T K][D], X_ustride floats from block to block

@@ -630,6 +630,8 @@ struct AttnIO {
   RowSrc q0src, q1src;   // query rows: globals from q0src, slots from q1src
   void* X_out; int X_f32; long long X_ustride;
   float* logits; const float* head;
+  // the next layer's packed block and where its K/V of this layer's result rows go (key i = query row i), or NULL
+  const char* next_blk; char* next_kst; char* next_vst; size_t next_ustride;
 };
 
 // Launches with few tiles: a tile's chain of products is all that counts, so four or eight waves share it (quad_kernel.h).
@@ -642,8 +644,8 @@ struct AttnIO {
 static bool quad_pays(const Shape& s, long long tiles) { return s.quad && tiles <= (s.D == 128 ? 768 : 512); }
 
 static int run_layer(const longer_config* c, const Shape& s, const char* packed_blk, const int32_t* lens, int B, int L,
-                     const AttnIO& io, bool do_attn, hipStream_t st) {
-  {
+                     const AttnIO& io, bool do_attn, hipStream_t st, bool have_kv = false) {
+  if (!have_kv) {
     BlockParams p = base_params(c, s, lens, B, L, s.DH);
     p.wbase = packed_blk;
     p.src0 = io.src0; p.src1 = io.src1; p.m0 = io.m0;
@@ -669,6 +671,7 @@ static int run_layer(const longer_config* c, const Shape& s, const char* packed_
   StageScope scope(ST_ATTN, st);
   if (quad_pays(s, tiles) && !p.logits) {
     p.n_layers = 1;
+    p.kv_w = io.next_blk; p.kv_k = io.next_kst; p.kv_v = io.next_vst; p.kv_w_ustride = io.next_ustride;
     if (s.quad(MODE_ATTN, 16, false, p, dim3((unsigned)tiles), st)) return fail(LONGER_ERR_HIP, "attention launch failed");
     return 0;
   }
@@ -1050,6 +1053,14 @@ static int cache_build_impl(const longer_config* cfg, const longer_weights* w, c
   io.q0src = io.src0; io.q1src = io.src1;
   if (cfg->q_learn) { io.q1src = RowSrc{cfg->q_learn, 0, 0}; io.gather_recent = 0; }
   io.X_out = xbuf[0]; io.X_f32 = 1; io.X_ustride = (long long)s.n * s.D;
+  // the few-tiles kernels make the next layer's K/V from a layer's result rows themselves (every layer has its own place in the cache)
+  const bool ahead = quad_pays(s, (long long)U * cdiv(cfg->k_recent, 32));
+  auto project_next = [&](AttnIO& a, int i) {
+    if (!ahead || i >= cfg->n_self) return;
+    a.next_blk = pk + pl.self_split + (size_t)i * s.pb;
+    a.next_kst = c8 + cl.c1_off + (size_t)i * cl.c1_lstride; a.next_vst = a.next_kst + cl.c1_voff; a.next_ustride = cl.c1_ustride;
+  };
+  project_next(io, 0);
   if ((rc = run_layer(cfg, s, pk + pl.cross, lens, U, L, io, cfg->n_self > 0, st))) return rc;
   for (int i = 0; i < cfg->n_self; ++i) {
     const char* xin = (const char*)xbuf[i & 1];
@@ -1063,7 +1074,8 @@ static int cache_build_impl(const longer_config* cfg, const longer_weights* w, c
     sio.q0src = sio.src0; sio.q1src = sio.src1;
     sio.X_out = xbuf[(i + 1) & 1]; sio.X_f32 = 1; sio.X_ustride = (long long)s.n * s.D;
     // the last layer's sequence rows feed nothing: only its K/V are needed
-    if ((rc = run_layer(cfg, s, pk + pl.self_split + (size_t)i * s.pb, lens, U, L, sio, i + 1 < cfg->n_self, st))) return rc;
+    project_next(sio, i + 1);
+    if ((rc = run_layer(cfg, s, pk + pl.self_split + (size_t)i * s.pb, lens, U, L, sio, i + 1 < cfg->n_self, st, ahead))) return rc;
   }
   return 0;
 }

@@ -2,7 +2,8 @@
 // compute unit, or eight at width 256 (bf16).
 //
 //   MODE_SCORE  candidate scoring of the KV-cache serving path (Section 3.6.3), all layers;
-//   MODE_ATTN   query side of one layer over stored K/V fragments (the cache build's sequence rows);
+//   MODE_ATTN   query side of one layer over stored K/V fragments (the cache build's sequence rows), and with kv_w the next
+//               layer's K and V of the result, which a launch of its own took 16 us for (two tiles a user, 16 users, width 256);
 //   MODE_STACK  the whole reduced stack of a user with at most two tiles (m + k <= 64) in one workgroup of eight waves.
 //
 // Why.  A request scores a hundred candidates (25 tiles), a cache build runs two tiles per user: a handful of
@@ -225,6 +226,7 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_wa
   for (int layer = 0; layer < p.n_layers; ++layer) {
     const bool selfl = STACK && layer > 0;             // K and V made here, handed to the user's other tile through LDS
     const bool last = layer + 1 == p.n_layers;
+    const bool project = MODE == MODE_ATTN && p.kv_w;  // (one layer)
     afresh();
     const char* wnext = wl + (size_t)sg.block() * D * 64;
 #pragma unroll
@@ -339,7 +341,7 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_wa
     }
     grp xn[NG];
     afresh();
-    request_vec(last ? wl : wnext);
+    request_vec(project ? p.kv_w : last ? wl : wnext);
     normalise(1, vl.ln2_g(), vl.ln2_b(), xn);
     x += bias_tile(vec + vl.b2(), ft, hi);
     for (int c0 = 0, par = 0; c0 < NC; c0 += WV, par ^= 1) {
@@ -372,6 +374,7 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_wa
       // what follows on these chunks' second product: the next hidden chunk, or the next block's first
       gchar* next = segment(wl, sg.w1(min(c0 + WV + wave, NC - 1)));
       if (c0 + WV >= NC && !last) next = segment(wnext, QuadSegs<LAYOUT, D>{NC, false}.q(ft));
+      if (c0 + WV >= NC && project) next = segment(p.kv_w, 1 + 2 * ft);
       __syncthreads();          // (the other parity was last read ahead of the barrier before)
 #pragma unroll
       for (int s = 0; s < 2 * WV; ++s) {
@@ -388,6 +391,26 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_wa
   // ------------------------------------------------------------------ epilogue
   const f32x16 one[1] = {x};
   if (p.X_out && inrange && own) store_rows<T, 1>(one, p.X_out, p.X_f32, out_off + 32 * wave, valid, hi);
+  if (MODE == MODE_ATTN && p.kv_w) {      // split layout: [vectors][K V of feature tile 0][K V of feature tile 1] ...
+    afresh();
+#pragma unroll
+    for (int i = 0; i < VQ; ++i) { const int c = tid + kThr * i; if (c < D * 4) vecl[c] = vq[i]; }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x[r] = valid ? x[r] : 0.f;      // (K and V of rows that do not exist: of zeros, nobody sees them)
+    grp xn[NG];
+    normalise(0, vl.ln1_g(), vl.ln1_b(), xn);
+    const f32x16 ak = product(splat16(0.f), xn, false, true, segment(p.kv_w, 2 + 2 * ft));
+    f32x16 av = product(splat16(0.f), xn, true, false, nullptr);
+    settle(av);
+    if (own) {
+      const size_t fo = (size_t)usr * p.kv_w_ustride + ((size_t)(tile * NT + wave) * 2) * 1024 + lane16;
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        *reinterpret_cast<grp*>(p.kv_k + fo + g * 1024) = E::pack(ak, g);
+        *reinterpret_cast<grp*>(p.kv_v + fo + g * 1024) = E::pack(av, g);
+      }
+    }
+  }
   if (!STACK && !SCORE) return;
   if (p.logits) {
     // logit = <head_w, flatten(global rows)> + head_b: each wave sums over its own feature tiles
