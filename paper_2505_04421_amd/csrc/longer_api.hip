@@ -3,6 +3,7 @@
 #include "../../include/longer.h"
 #include "pair_kernel.h"
 #include "user_kernel.h"
+#include "few_f32_kernel.h"
 
 #include <cmath>
 #include <cstdarg>
@@ -97,6 +98,9 @@ static launch_fn find_launch(int dtype, int D, int DH) {
   }
   return nullptr;
 }
+
+// the shapes of the small launches' kernel in full precision (few_f32_kernel.h)
+static bool few_f32_shape(launch_fn f) { return f == &launch_block<float, 32, 16> && !one_wave_only(); }
 
 static thread_local char g_err[256] = "";
 
@@ -598,6 +602,15 @@ static int check_input(const longer_config* cfg, const longer_input_weights* w, 
   return check_aligned({E, tdiff, w->pos});
 }
 
+// Full precision at width 32 (few_f32_kernel.h).  The stack of users with at most two tiles: whole forward pass (K = 4, three layers), microseconds
+// with it / without, merge as it is: 256 users of 50 raw tokens 50 / 67, 512 of 64 80 / 111, 2048 of 64 286 / 396.  It makes the
+// cross layer's K and V itself when a user's global and merged tokens fit its two tiles.
+static bool few_stack(const Shape& s) { return few_f32_shape(s.main_fn) && s.n <= 64; }
+static bool few_stack_makes_kv(const longer_config* c, const Shape& s, int L) { return few_stack(s) && c->m + cdiv(L, c->K) <= 64; }
+// The merge up to two workgroups a compute unit: beyond, the idle waves cost more than the shorter chain gains.  The same passes, with /
+// without: 8, 64, 400, 1000, 4000 tiles 40 / 48, 40 / 48, 45 / 50, 65 / 60, 128 / 94.
+constexpr int kFewMergeTiles = 512;
+
 // `packed`: the InnerTrans blocks in the fused layout; with `in`, the input MLP's segments
 // followed directly by them, and the rows come from the raw inputs instead of H
 static int run_merge(const longer_config* c, const Shape& s, const char* packed, const void* H, const int32_t* lens,
@@ -617,6 +630,10 @@ static int run_merge(const longer_config* c, const Shape& s, const char* packed,
   if (slots + 32LL * tt * kWaves >= (1LL << 31)) return fail(LONGER_ERR_ARG, "B*ceil(L/K)*K = %lld token slots: at most 2^31 per call", slots);
   const int grid = cdiv(slots, 32LL * tt * kWaves);
   StageScope scope(ST_MERGE, st);
+  if (few_f32_shape(s.inner_fn) && !in && !keep && M_out && !Z_out && slots <= 32LL * kFewMergeTiles) {
+    if (launch_few_f32(MODE_MERGE, win, p, dim3((unsigned)cdiv(slots, 32)), st)) return fail(LONGER_ERR_HIP, "merge kernel launch failed");
+    return 0;
+  }
   int rc = s.inner_fn(in ? MODE_MERGE_IN : keep ? MODE_MERGE_KEEP : MODE_MERGE, tt, win, p, dim3(grid), st);
   return rc ? fail(LONGER_ERR_HIP, "merge kernel launch failed") : 0;
 }
@@ -696,6 +713,11 @@ static int run_stack(const longer_config* c, const Shape& s, const char* packed_
   p.X_out = io.X_out; p.X_f32 = io.X_f32; p.X_ustride = io.X_ustride;
   p.logits = io.logits; p.head = io.head;
   StageScope scope(ST_ATTN, st);
+  if (few_stack(s)) {
+    if (few_stack_makes_kv(c, s, L)) { p.kst = p.vst = nullptr; p.kv_w = packed_cross; p.kv_k = (char*)io.src1.p; }
+    if (launch_few_f32(MODE_STACK, 16, p, dim3(B), st)) return fail(LONGER_ERR_HIP, "stack launch failed");
+    return 0;
+  }
   // At most two tiles a user: eight waves for them instead of one or two waves each; at width 64 as long as the users are
   // one round of workgroups.  Whole forward pass (L = 400, K = 8, three or four layers), microseconds with it / without: width
   // 64, m + k = 54, at 1, 128, 256, 384, 1024 users 39 / 46, 48 / 55, 63 / 70, 93 / 87, 185 / 173; width 128, m + k = 58, at 1, 128, 512,
@@ -979,7 +1001,7 @@ static int forward_impl(const longer_config* cfg, const longer_weights* w, const
   if (one_launch) {
     AttnIO io = cross_io(cfg, s, l, w8, G, w8 + l.M, 1, B, L, Y_out, 0);
     if (logits_out) { io.logits = logits_out; io.head = head; }
-    if ((rc = run_layer(cfg, s, pk_cross, lens, B, L, io, false, st))) return rc;
+    if (!few_stack_makes_kv(cfg, s, L) && (rc = run_layer(cfg, s, pk_cross, lens, B, L, io, false, st))) return rc;
     return run_stack(cfg, s, pk_cross, pk + pl.cross_pair, lens, B, L, io, st);
   }
   void* xbuf[2] = {w8 + l.xa, w8 + l.xb};

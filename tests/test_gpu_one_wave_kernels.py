@@ -168,3 +168,20 @@ def test_workgroups_of_missing_rows_only(dtype, d, heads, k):
             assert not got[u, n:].any()
             if n:
                 assert np.linalg.norm(got[u, :n] - ref[u, :n]) <= TOL[dtype] * np.linalg.norm(ref[u, :n])
+
+
+# Full precision at width 32 in small launches: one and two tiles of query rows, the cross layer's keys made in the stack's launch
+# (at most 64 global and merged tokens) and not, groups of every register window, hidden chunks below, at and past four, users without a
+# token; and one merge with more tiles than the small kernel takes
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,k,K,L,ffn_mult,extra", [(2, 8, 4, 64, 4, {}), (8, 24, 1, 56, 1, dict(gmask="causal")), (8, 25, 8, 457, 3, {}), (2, 62, 4, 249, 5, {}),
+                                                    (4, 9, 16, 970, 7, dict(act="relu")), (32, 32, 32, 1500, 4, dict(k_uniform=20)), (2, 20, 2, 131, 4, dict(q_learnable=True)),
+                                                    (2, 8, 4, 5000, 4, {})])
+def test_full_precision_small_launches(m, k, K, L, ffn_mult, extra):
+    import longer_synth as synth
+    from test_gpu_parity import _entry_points, TOL
+    cfg = synth.CONFIGS["C1"].replace(B=5, L=L, K=K, m=m, k_recent=k, n_self=2, inner_layers=2, ffn_mult=ffn_mult, ragged=True, len_lo=0, len_hi=L,
+                                      index=97, **extra)
+    case = synth.make_case(cfg)
+    case["lens"][:4] = [L, 0, 1, min(L, 40)]
+    _entry_points(case, TOL["f32"], with_inner=False, logits_by_terms=True)
