@@ -39,7 +39,7 @@ struct WgradArgs { WgradJob job[kMaxWgradJobs]; int njobs, tiles, nslices; };
 // TILES: the operands are tile blocks in records (bw_block.h: rows are slots; ldx, ldy: sixteens of features from one tile to the next).  A step's
 // tile is then contiguous in memory and goes to LDS as it is (a block of the headline batch 392 -> 370 us).
 template <int TB, bool TILES>
-__global__ __launch_bounds__(256, 3) void bw_wgrad_kernel(const WgradArgs a) {
+__global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const WgradArgs a) {
   constexpr int PITCH = TB + 16, TT = TB / 64, NCH = TB / 64;     // NCH: 16-byte chunks per thread, operand and step
   constexpr int CPR = TB / 8;                                     // chunks per row
   __shared__ __attribute__((aligned(16))) __bf16 sm[4 * 32 * PITCH];
@@ -80,24 +80,30 @@ __global__ __launch_bounds__(256, 3) void bw_wgrad_kernel(const WgradArgs a) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.f;
 
-  bf16x8 rx[NCH], ry[NCH];
-  auto gload = [&](int kt) {
+  // Steps on their way from memory (registers: 16 a step at TB = 128, 8 at 64).  One, three workgroups a compute unit: steps of the headline, small
+  // and raw-inputs models 4392 / 315 / 1291 us; two at the same occupancy, with spills at TB = 128: 4536 / 313 / 1317; this, two workgroups
+  // of width 128 a compute unit and as many slices: 4390 / 312 / 1275.
+  constexpr int PD = TB == 128 ? 3 : 4;
+  bf16x8 rx[PD][NCH], ry[PD][NCH];
+  auto gload = [&](int p, int kt) {
     const int k0 = (kfirst + kt * kstride) * 32;
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
       const int c = tid + 256 * i, row = k0 + c / CPR, col = 8 * (c % CPR);
-      bf16x8 z;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) z[e] = (__bf16)0.f;
-      rx[i] = z; ry[i] = z;
-      if constexpr (TILES) {
+      if constexpr (TILES) {                 // (past the last column: any other one, its results are dropped)
         const size_t tile = (size_t)(k0 >> 5);
-        const int gx = m0 / 16 + (c >> 6), gy = n0 / 16 + (c >> 6);
-        if (gx < jb.m / 16) rx[i] = *(const bf16x8*)(X + (tile * jb.ldx + gx) * 512 + 8 * (c & 63));
-        if (gy < jb.n / 16) ry[i] = *(const bf16x8*)(Y + (tile * jb.ldy + gy) * 512 + 8 * (c & 63));
-      } else if (row < jb.rows && row_valid(jb.rv, row)) {
-        if (m0 + col < jb.m) rx[i] = *(const bf16x8*)(X + (size_t)row * jb.ldx + m0 + col);
-        if (n0 + col < jb.n) ry[i] = *(const bf16x8*)(Y + (size_t)row * jb.ldy + n0 + col);
+        const int gx = min(m0 / 16 + (c >> 6), jb.m / 16 - 1), gy = min(n0 / 16 + (c >> 6), jb.n / 16 - 1);
+        rx[p][i] = *(const bf16x8*)(X + (tile * jb.ldx + gx) * 512 + 8 * (c & 63));
+        ry[p][i] = *(const bf16x8*)(Y + (tile * jb.ldy + gy) * 512 + 8 * (c & 63));
+      } else {
+        bf16x8 z;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) z[e] = (__bf16)0.f;
+        rx[p][i] = z; ry[p][i] = z;
+        if (row < jb.rows && row_valid(jb.rv, row)) {
+          if (m0 + col < jb.m) rx[p][i] = *(const bf16x8*)(X + (size_t)row * jb.ldx + m0 + col);
+          if (n0 + col < jb.n) ry[p][i] = *(const bf16x8*)(Y + (size_t)row * jb.ldy + n0 + col);
+        }
       }
     }
   };
@@ -120,39 +126,49 @@ __global__ __launch_bounds__(256, 3) void bw_wgrad_kernel(const WgradArgs a) {
       return frag_t<PITCH>(s + foff + 16 * ks * PITCH + x);
     }
   };
-  int buf = 0, kt = next_step(0);
-  if (kt < nk) gload(kt);
-  while (kt < nk) {
-    __bf16* sx = sm + buf * (2 * 32 * PITCH);
-    __bf16* sy = sx + 32 * PITCH;
+  int buf = 0, kn = next_step(0);            // kn: the next step to request
+  bool have[PD];
+  auto request = [&](int p) {
+    have[p] = kn < nk;
+    if (!have[p]) return;
+    gload(p, kn);
+    kn = next_step(kn + 1);
+  };
 #pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-      const int c = tid + 256 * i, o = TILES ? 8 * c : (c / CPR) * PITCH + 8 * (c % CPR);
-      *(bf16x8*)&sx[o] = rx[i];
-      *(bf16x8*)&sy[o] = ry[i];
-    }
-    const int kn = next_step(kt + 1);
-    if (kn < nk) gload(kn);
-    __syncthreads();       // (the other buffer was last read two steps ago, ahead of the previous barrier)
+  for (int p = 0; p < PD; ++p) request(p);
+  while (have[0]) {
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      bf16x8 fx[TT], fy[TT];
+    for (int p = 0; p < PD; ++p) {
+      if (p > 0 && !have[p]) { have[0] = false; break; }      // (requests are made in order: nothing comes after one that is missing)
+      __bf16* sx = sm + buf * (2 * 32 * PITCH);
+      __bf16* sy = sx + 32 * PITCH;
 #pragma unroll
-      for (int i = 0; i < TT; ++i) {
-        fx[i] = frag(sx, (TB / 2) * wm + 32 * i, ks);
-        fy[i] = frag(sy, (TB / 2) * wn + 32 * i, ks);
+      for (int i = 0; i < NCH; ++i) {
+        const int c = tid + 256 * i, o = TILES ? 8 * c : (c / CPR) * PITCH + 8 * (c % CPR);
+        *(bf16x8*)&sx[o] = rx[p][i];
+        *(bf16x8*)&sy[o] = ry[p][i];
       }
+      request(p);
+      __syncthreads();       // (the other buffer was last read two steps ago, ahead of the previous barrier)
 #pragma unroll
-      for (int i = 0; i < TT; ++i)
+      for (int ks = 0; ks < 2; ++ks) {
+        bf16x8 fx[TT], fy[TT];
 #pragma unroll
-        for (int j = 0; j < TT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[i], fy[j], acc[i][j], 0, 0, 0);
-      if (bias_sum) {
+        for (int i = 0; i < TT; ++i) {
+          fx[i] = frag(sx, (TB / 2) * wm + 32 * i, ks);
+          fy[i] = frag(sy, (TB / 2) * wn + 32 * i, ks);
+        }
 #pragma unroll
-        for (int j = 0; j < TT; ++j) accb[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, fy[j], accb[j], 0, 0, 0);
+        for (int i = 0; i < TT; ++i)
+#pragma unroll
+          for (int j = 0; j < TT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[i], fy[j], acc[i][j], 0, 0, 0);
+        if (bias_sum) {
+#pragma unroll
+          for (int j = 0; j < TT; ++j) accb[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, fy[j], accb[j], 0, 0, 0);
+        }
       }
+      buf ^= 1;
     }
-    buf ^= 1;
-    kt = kn;
   }
   float* out = jb.part + ((size_t)layer * kstride + kfirst) * ((size_t)jb.m * jb.n + jb.n);
 #pragma unroll
@@ -219,11 +235,11 @@ __global__ __launch_bounds__(256) void bw_reduce_jobs_kernel(const ReduceArgs a)
 }
 
 // ------------------------------------------------------------------------------------ host side
-// Slices of a launch with `tiles` output tiles over `rows` rows: enough workgroups to fill the chip three deep
-// (what fits a compute unit), but at least four row steps (128 rows) each.
+// Slices of a launch with `tiles` output tiles over `rows` rows: enough workgroups to fill the chip two deep
+// (what fits a compute unit at width 128), but at least four row steps (128 rows) each.
 static inline int wgrad_slices(int tiles, size_t rows) {
   const int steps = (int)((rows + 31) / 32);
-  int s = 3 * kComputeUnits / (tiles > 0 ? tiles : 1);
+  int s = 2 * kComputeUnits / (tiles > 0 ? tiles : 1);
   if (s > steps / 4) s = steps / 4;
   if (s > 8) s = s / 8 * 8;                 // (slices are dealt to the 8 dies)
   return s < 1 ? 1 : s;
