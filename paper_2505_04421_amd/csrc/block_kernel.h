@@ -82,27 +82,29 @@ struct BlockParams {
 };
 
 // ---------------------------------------------------------------------------- helpers
+// A lane's row (`off`: its first element), zeros where it does not exist.  All requests go out together and none of them asks
+// whether the row exists: under a condition each came to wait for the one before, sixteen trips to memory for a row of width
+// 128.  A row that does not exist reads the first one of `base`, which does.
 template <typename T, int NT>
 __device__ __forceinline__ void load_rows(f32x16 (&x)[NT], const void* base, int is_f32, long long off,
                                           bool valid, int hi) {
+  const long long o = (valid ? off : 0) + 4 * hi;
+  if (is_f32 || sizeof(T) == 4) {
+    f32x4 raw[4 * NT];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
+    for (int i = 0; i < 4 * NT; ++i) raw[i] = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(base) + o + 8 * i);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      f32x4 v = {0.f, 0.f, 0.f, 0.f};
-      if (valid) {
-        long long o = off + 32 * t + 8 * q + 4 * hi;
-        if (is_f32 || sizeof(T) == 4) {
-          v = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(base) + o);
-        } else {
-          bf16x4 b = *reinterpret_cast<const bf16x4*>(reinterpret_cast<const __bf16*>(base) + o);
+    for (int i = 0; i < 4 * NT; ++i)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = (float)b[e];
-        }
-      }
+      for (int e = 0; e < 4; ++e) { const float v = raw[i][e]; x[i / 4][4 * (i % 4) + e] = valid ? v : 0.f; }
+  } else {
+    bf16x4 raw[4 * NT];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) x[t][4 * q + e] = v[e];
-    }
+    for (int i = 0; i < 4 * NT; ++i) raw[i] = *reinterpret_cast<const bf16x4*>(reinterpret_cast<const __bf16*>(base) + o + 8 * i);
+#pragma unroll
+    for (int i = 0; i < 4 * NT; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { const float v = (float)raw[i][e]; x[i / 4][4 * (i % 4) + e] = valid ? v : 0.f; }
   }
 }
 
@@ -494,18 +496,18 @@ __device__ __forceinline__ void softmax_window(const f32x16& S, int widx, const 
 template <typename T, int NT>
 __device__ __forceinline__ void input_rows(f32x16 (&x)[NT], const BlockParams& p, long long r, int pos, bool valid, int hi) {
   const int nte = p.de / 32, dt = NT * 32 - p.de;
+  f32x16 a[NT], b[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    f32x16 a[1], b[1];
-    if (t < nte) {
-      load_rows<T, 1>(a, p.in_e, 0, r * p.de + 32 * t, valid, hi);
-      load_rows<T, 1>(b, p.in_pos, 0, (long long)pos * p.de + 32 * t, valid, hi);
-      x[t] = a[0] + b[0];
-    } else {
-      load_rows<T, 1>(a, p.in_td, 0, r * dt + 32 * (t - nte), valid, hi);
-      x[t] = a[0];
-    }
+    const bool emb = t < nte;          // (both parts are read as embeddings or time differences; the second addend of the latter is dropped)
+    f32x16 one[1];
+    load_rows<T, 1>(one, emb ? p.in_e : p.in_td, 0, emb ? r * p.de + 32 * t : r * dt + 32 * (t - nte), valid, hi);
+    a[t] = one[0];
+    load_rows<T, 1>(one, p.in_pos, 0, emb ? (long long)pos * p.de + 32 * t : 0, valid && emb, hi);
+    b[t] = one[0];
   }
+#pragma unroll
+  for (int t = 0; t < NT; ++t) x[t] = a[t] + b[t];
 }
 
 // ---------------------------------------------------------------------------- the kernel

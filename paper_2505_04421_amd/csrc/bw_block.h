@@ -390,16 +390,24 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   // ---- gradient of the block's output
   auto upstream = [&](const Token& k, int t) -> f32x16 {
     f32x16 v;
-    const float share = p.concat ? 1.f : 1.f / (float)min(p.K, k.len - k.tg * p.K);
-    const float* up = p.dM + ((size_t)k.u * p.T + k.tg) * (size_t)(p.concat ? p.K * D : D) + (p.concat ? k.jj * D : 0);
+    f32x4 w[4];
+    if (!p.dM) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      f32x4 w = {0.f, 0.f, 0.f, 0.f};
-      if (!p.dM) w = *at_dy(p.dy, 4 * t + q);
-      else if (k.valid) w = *(const f32x4*)(up + 32 * t + 8 * q + 4 * hi) * share;
+      for (int q = 0; q < 4; ++q) w[q] = *at_dy(p.dy, 4 * t + q);
+    } else {                                           // (a padded token reads the first merged token's and drops it)
+      const float share = !k.valid ? 0.f : p.concat ? 1.f : 1.f / (float)min(p.K, k.len - k.tg * p.K);
+      const float* up = p.dM + (k.valid ? ((size_t)k.u * p.T + k.tg) * (size_t)(p.concat ? p.K * D : D) + (p.concat ? k.jj * D : 0) : 0);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[4 * q + e] = w[e];
+      for (int q = 0; q < 4; ++q) w[q] = *(const f32x4*)(up + 32 * t + 8 * q + 4 * hi);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { const float one = w[q][e]; w[q][e] = k.valid ? one * share : 0.f; }
     }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[4 * q + e] = w[q][e];
     return v;
   };
   f32x16 dn[NT];

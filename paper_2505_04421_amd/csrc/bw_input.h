@@ -75,13 +75,10 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_input_kernel(const Input
   f32x16 x[NT], dy[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    f32x16 a[1], b[1] = {splat16(0.f)};
-    if (t < nte) {
-      load_rows<__bf16, 1>(a, p.E, 0, (long long)row * p.de + 32 * t, valid, hi);
-      load_rows<__bf16, 1>(b, p.pos, 0, (long long)at * p.de + 32 * t, valid, hi);
-    } else {
-      load_rows<__bf16, 1>(a, p.td, 0, (long long)row * (D - p.de) + 32 * (t - nte), valid, hi);
-    }
+    const bool emb = t < nte;                          // (no branch between the requests; a time difference has no second addend)
+    f32x16 a[1], b[1];
+    load_rows<__bf16, 1>(a, emb ? p.E : p.td, 0, emb ? (long long)row * p.de + 32 * t : (long long)row * (D - p.de) + 32 * (t - nte), valid, hi);
+    load_rows<__bf16, 1>(b, p.pos, 0, emb ? (long long)at * p.de + 32 * t : 0, valid && emb, hi);
     x[t] = a[0] + b[0];
   }
   load_rows<__bf16, NT>(dy, p.dH, 1, (long long)row * D, valid, hi);

@@ -71,11 +71,15 @@ __device__ __forceinline__ void act_exact_both(float v, int act, float* a, float
   *da = c + v * 0.39894228040143268f * e;
 }
 
-// sixteen features of a row-major row as an operand group, and back
+// sixteen features of a row-major row as an operand group, and back; zeros where it is not there (`row`: any that is; the
+// request is unconditional, see load_rows)
 __device__ __forceinline__ bf16x8 row_group(const __bf16* row, int g, int hi, bool there) {
-  bf16x4 a = {}, b = {};
-  if (there) { a = *(const bf16x4*)(row + 16 * g + 4 * hi); b = *(const bf16x4*)(row + 16 * g + 8 + 4 * hi); }
-  return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+  const bf16x4 a = *(const bf16x4*)(row + 16 * g + 4 * hi), b = *(const bf16x4*)(row + 16 * g + 8 + 4 * hi);
+  const u32x4 v = __builtin_bit_cast(u32x4, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+  u32x4 w;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) { const uint32_t one = v[e]; w[e] = there ? one : 0u; }
+  return __builtin_bit_cast(bf16x8, w);
 }
 __device__ __forceinline__ void row_put(__bf16* row, int g, int hi, bf16x8 v) {
   *(bf16x4*)(row + 16 * g + 4 * hi) = __builtin_shufflevector(v, v, 0, 1, 2, 3);
@@ -263,7 +267,7 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stac
   bf16x8 nop[NG];
   if (p.o) {
 #pragma unroll
-    for (int g = 0; g < NG; ++g) nop[g] = row_group(p.o + (size_t)row * D, g, hi, in);
+    for (int g = 0; g < NG; ++g) nop[g] = row_group(p.o + (size_t)(in ? row : 0) * D, g, hi, in);
   }
   const int head = p.o ? NT + 2 * NC : 0;          // first segment of the next layer's products
   s.request(s.at(p.o ? ft : head + min(wave, p.mats * NT - 1), 0));
@@ -383,7 +387,7 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stac
   // fragment k of the products that bring dQ, dK, dV back (matrix m): 32 contracted features k / 2 of this wave's result tile
   auto back = [&](int m, int k) { s.fr[k] = s.load(s.at((k / 2) * p.mats + m, 2 * ft), k & 1); };
   bf16x8 bop[NG];
-  auto rows_of = [&](int m, int k) { bop[k] = row_group(p.dqkv + (size_t)row * p.ldq + m * D, k, hi, in); };
+  auto rows_of = [&](int m, int k) { bop[k] = row_group(p.dqkv + (size_t)(in ? row : 0) * p.ldq + m * D, k, hi, in); };
   const int seg = p.dqkv ? NT * p.mats : 0;        // first segment of the FFN's products
   if (p.dqkv) {
 #pragma unroll
