@@ -88,11 +88,14 @@ struct BlockParams {
 template <typename T, int NT>
 __device__ __forceinline__ void load_rows(f32x16 (&x)[NT], const void* base, int is_f32, long long off,
                                           bool valid, int hi) {
+  // (global memory, said so: where the compiler cannot tell it takes flat loads, which wait for LDS as well)
+  typedef __attribute__((address_space(1))) const f32x4 gf32x4;
+  typedef __attribute__((address_space(1))) const bf16x4 gbf16x4;
   const long long o = (valid ? off : 0) + 4 * hi;
   if (is_f32 || sizeof(T) == 4) {
     f32x4 raw[4 * NT];
 #pragma unroll
-    for (int i = 0; i < 4 * NT; ++i) raw[i] = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(base) + o + 8 * i);
+    for (int i = 0; i < 4 * NT; ++i) raw[i] = *(gf32x4*)(reinterpret_cast<const float*>(base) + o + 8 * i);
 #pragma unroll
     for (int i = 0; i < 4 * NT; ++i)
 #pragma unroll
@@ -100,7 +103,7 @@ __device__ __forceinline__ void load_rows(f32x16 (&x)[NT], const void* base, int
   } else {
     bf16x4 raw[4 * NT];
 #pragma unroll
-    for (int i = 0; i < 4 * NT; ++i) raw[i] = *reinterpret_cast<const bf16x4*>(reinterpret_cast<const __bf16*>(base) + o + 8 * i);
+    for (int i = 0; i < 4 * NT; ++i) raw[i] = *(gbf16x4*)(reinterpret_cast<const __bf16*>(base) + o + 8 * i);
 #pragma unroll
     for (int i = 0; i < 4 * NT; ++i)
 #pragma unroll
