@@ -44,6 +44,9 @@ template <> int launch_user<128, 32>(int, const BlockParams&, dim3, hipStream_t)
 template <> int launch_user<256, 16>(int, const BlockParams&, dim3, hipStream_t);
 template <> int launch_user<256, 32>(int, const BlockParams&, dim3, hipStream_t);
 
+template <> int launch_user_merge<256, 16>(int, const BlockParams&, dim3, hipStream_t);
+template <> int launch_user_merge<256, 32>(int, const BlockParams&, dim3, hipStream_t);
+
 typedef int (*user_fn)(int, const BlockParams&, dim3, hipStream_t);
 typedef int (*quad_fn)(int, int, bool, const BlockParams&, dim3, hipStream_t);
 typedef int (*launch_fn)(int, int, int, const BlockParams&, dim3, hipStream_t);
@@ -80,6 +83,12 @@ static user_fn find_user(int dtype, int D, int DH) {
   if (D == 128) return DH == 16 ? &launch_user<128, 16> : DH == 32 ? &launch_user<128, 32> : nullptr;
   if (D == 256) return DH == 16 ? &launch_user<256, 16> : DH == 32 ? &launch_user<256, 32> : nullptr;
   return nullptr;
+}
+
+// and its merge: bf16, d = 256
+static user_fn find_user_merge(int dtype, int D, int DH) {
+  if (one_wave_only() || dtype != LONGER_BF16 || D != 256) return nullptr;
+  return DH == 16 ? &launch_user_merge<256, 16> : DH == 32 ? &launch_user_merge<256, 32> : nullptr;
 }
 
 static launch_fn find_launch(int dtype, int D, int DH) {
@@ -350,6 +359,7 @@ struct Shape {
   pair_fn pair;       // the main stack's two-wave scoring kernels, or NULL
   quad_fn quad;       // its four-wave kernels, or NULL
   user_fn user;       // its feature-tile-per-wave stack kernels, or NULL
+  user_fn user_merge; // the InnerTrans blocks' feature-tile-per-wave merge kernels, or NULL
 };
 
 static int check_cfg(const longer_config* c, Shape* s, bool need_inner, bool need_main) {
@@ -375,7 +385,7 @@ static int check_cfg(const longer_config* c, Shape* s, bool need_inner, bool nee
   s->seg = packed_seg_bytes(s->D, s->es);
   if ((size_t)(9 * s->D + s->FF) * 4 > s->seg) return fail(LONGER_ERR_ARG, "ffn_mult=%d too large for d=%d", c->ffn_mult, c->d);
   if (ffn_skewed(s->es, s->D) && s->FF < 64) return fail(LONGER_ERR_ARG, "ffn_mult * d = %d: the bf16 FFN needs a hidden width of at least 64", s->FF);
-  s->main_fn = s->inner_fn = nullptr; s->pair = nullptr; s->quad = nullptr; s->user = nullptr; s->DH = s->DHi = 0;
+  s->main_fn = s->inner_fn = nullptr; s->pair = nullptr; s->quad = nullptr; s->user = s->user_merge = nullptr; s->DH = s->DHi = 0;
   s->Di = c->d;
   if (c->merge == LONGER_MERGE_CONCAT) {
     if (c->d % c->K || (c->d / c->K) % 32)
@@ -396,6 +406,7 @@ static int check_cfg(const longer_config* c, Shape* s, bool need_inner, bool nee
     if (c->inner_heads <= 0 || s->Di % c->inner_heads) return fail(LONGER_ERR_ARG, "inner_heads=%d does not divide the InnerTrans width %d", c->inner_heads, s->Di);
     s->DHi = s->Di / c->inner_heads;
     s->inner_fn = find_launch(c->dtype, s->Di, s->DHi);
+    s->user_merge = find_user_merge(c->dtype, s->Di, s->DHi);
     if (!s->inner_fn) return fail(LONGER_ERR_ARG, "unsupported shape: dtype=%d InnerTrans width=%d inner head width=%d", c->dtype, s->Di, s->DHi);
     if ((size_t)(9 * s->Di + c->ffn_mult * s->Di) * 4 > packed_seg_bytes(s->Di, s->es))
       return fail(LONGER_ERR_ARG, "ffn_mult=%d too large for the InnerTrans width %d", c->ffn_mult, s->Di);
@@ -632,6 +643,10 @@ static int run_merge(const longer_config* c, const Shape& s, const char* packed,
   StageScope scope(ST_MERGE, st);
   if (few_f32_shape(s.inner_fn) && !in && !keep && M_out && !Z_out && slots <= 32LL * kFewMergeTiles) {
     if (launch_few_f32(MODE_MERGE, win, p, dim3((unsigned)cdiv(slots, 32)), st)) return fail(LONGER_ERR_HIP, "merge kernel launch failed");
+    return 0;
+  }
+  if (s.user_merge && !in && !keep) {
+    if (s.user_merge(win, p, dim3((unsigned)cdiv(slots, 32LL * kUserMergeTiles)), st)) return fail(LONGER_ERR_HIP, "merge kernel launch failed");
     return 0;
   }
   int rc = s.inner_fn(in ? MODE_MERGE_IN : keep ? MODE_MERGE_KEEP : MODE_MERGE, tt, win, p, dim3(grid), st);

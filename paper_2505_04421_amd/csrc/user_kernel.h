@@ -1,5 +1,8 @@
-// The whole reduced stack of a user (Eq. 10) with up to four tiles of 32 rows in one workgroup of eight waves (bf16, d = 128 / 256):
-// a wave owns a FEATURE tile (its part of the rows, of every product's result, its heads) for several row tiles.
+// Up to four tiles of 32 rows in one workgroup of eight waves (bf16), where a wave owns a FEATURE tile (its part of the rows, of
+// every product's result, its heads) for several row tiles:
+//
+//   MODE_STACK  the whole reduced stack of a user (Eq. 10) with at most four tiles, d = 128 / 256;
+//   MODE_MERGE  the InnerTrans blocks and the merge (Section 3.4) of four tiles of raw tokens, d = 256.
 //
 // Why.  The kernels that give a row tile to one or two waves read every weight fragment once per row tile out of an LDS ring, and at
 // width 256 there is no room beside such a ring for a user's K and V: one wave per SIMD, every wait exposed.  Here a fragment
@@ -7,6 +10,9 @@
 // two groups of waves take two row tiles each), LDS holds nothing but operands, and since a wave makes K and V of its heads
 // for its row tiles itself, at width 256 they never leave its registers.  Eight waves, two per SIMD.
 // Fragments are requested a product ahead as in quad_kernel.h.
+//
+// The merge at width 256: 160 000 raw tokens, one block, a wave a tile 335 us, this 303 us.  (At width 128 a tile's
+// wave needs half the registers, two share a SIMD, and the two mappings take the same time.)
 //
 // What bounds it: at width 256 LDS, which hands every product its row operand (1 KiB per matrix instruction and wave, the
 // 128 bytes a cycle that four SIMDs can use up), at width 128 the vector work of the attention.
@@ -18,7 +24,7 @@ namespace longer {
 constexpr int kUserWaves = 8;
 constexpr int user_groups(int d) { return kUserWaves / (d / 32); }     // groups of waves that share out the row tiles
 
-template <int D, int DH, int RT, int LAYOUT, bool RELU>
+template <int D, int DH, int RT, int LAYOUT, bool RELU, int MODE = MODE_STACK, int W = 16>
 __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockParams p) {
   using T = __bf16;
   using E = ET<T>;
@@ -26,6 +32,8 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
   using hgrp = typename E::hgrp;
   constexpr int NT = D / 32, NG = D / 16, WV = NT, TG = user_groups(D), TS = TG * RT, HPT = 32 / DH, GPH = DH / 16, kThr = 64 * kUserWaves;
   constexpr bool HOLD = D <= 128;                    // (width 256: no registers for the output projection's fragments through the attention)
+  constexpr bool MERGE = MODE == MODE_MERGE;
+  static_assert(!MERGE || TG == 1, "the merge's keys stay in their wave");
   static_assert(2 * WV == NG, "as many fragments in a hidden chunk's second product as in its first");
   __shared__ grp ops[TS][NG][64];                    // normalised rows: [row tile][group][lane]
   __shared__ grp mid[TS][NT][2][64];                 // [row tile][wave][group][lane]: Q, then the attention output; activated hidden chunks
@@ -39,10 +47,26 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
     asm volatile("" : "+v"(tid));
     lane = tid & 63; j = lane & 31; hi = lane >> 5; lane16 = (unsigned)lane * 16u;
   };
-  const int NC = p.FF / 32, usr = (int)blockIdx.x, rows = p.rows_per_user;
-  QuadSegs<LAYOUT, D> sg = {NC, true};               // (the first block is the cross layer's attention half)
-  int len = p.lens ? p.lens[usr] : p.L; len = min(max(len, 0), p.L);
+  const int NC = p.FF / 32, usr = MERGE ? 0 : (int)blockIdx.x, rows = p.rows_per_user;
+  QuadSegs<LAYOUT, D> sg = {NC, !MERGE};             // (the stack's first block is the cross layer's attention half)
+  int len = MERGE ? 0 : p.lens ? p.lens[usr] : p.L; len = min(max(len, 0), p.L);
   const int tu = (len + p.K - 1) / p.K, i0 = first_slot(p.k, tu, p.q_learn);
+  // merge: the lane's token in row tile rt of the workgroup (slots count [B][T K], a group never spans two tiles)
+  struct Token { uint32_t gidx; int jj, left; bool stored; long long row; };      // left: the group's valid tokens (at most K)
+  auto locate = [&](int rt) {
+    Token k;
+    const uint32_t slot = ((uint32_t)blockIdx.x * TS + (uint32_t)(t0 + rt)) * 32u + (uint32_t)j;
+    k.gidx = slot >> __builtin_ctz(p.K);
+    k.jj = (int)(slot & (uint32_t)(p.K - 1));
+    const int u = (int)(k.gidx / (uint32_t)p.T), t = (int)(k.gidx - (uint32_t)u * (uint32_t)p.T);
+    k.stored = u < p.B;
+    int n = 0;
+    if (k.stored) { n = p.lens ? p.lens[u] : p.L; n = min(max(n, 0), p.L); }
+    k.left = min(max(n - t * p.K, 0), p.K);
+    k.row = (long long)u * p.L + t * p.K + k.jj;
+    return k;
+  };
+  uint32_t there[RT];                                // merge: which of a row tile's tokens exist
 
   // ------------------------------------------------------------------ rows
   auto row_valid = [&](int a) { return a < rows && (a < p.m || a - p.m >= i0); };
@@ -50,6 +74,15 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
   f32x16 x[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
+    if constexpr (MERGE) {
+      const Token k = locate(rt);
+      const bool valid = k.jj < k.left;
+      there[rt] = (uint32_t)__ballot(valid);
+      f32x16 one[1];
+      load_rows<T, 1>(one, p.H, 0, k.row * D + 32 * ft, valid, hi);
+      x[rt] = one[0];
+      continue;
+    }
     const int a = 32 * (t0 + rt) + j;
     const bool glob = a < p.m;
     const int row = glob ? a : (p.gather_recent ? row_token(a) : a - p.m);
@@ -57,6 +90,37 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
     load_rows<T, 1>(one, glob ? p.src0.p : p.src1.p, glob ? p.src0.f32 : p.src1.f32,
                     (glob ? p.src0.ustride : p.src1.ustride) * usr + (long long)row * D + 32 * ft, row_valid(a), hi);
     x[rt] = one[0];
+  }
+
+  // merge: token rows and merged tokens of this wave's features, zeros where there are none
+  auto merge_out = [&](bool zeros) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      const Token k = locate(rt);
+      if (p.Z_out && k.stored) {
+        const f32x16 one[1] = {x[rt]};
+        store_rows<T, 1>(one, p.Z_out, p.Z_f32, ((long long)k.gidx * p.K + k.jj) * D + 32 * ft, !zeros && k.jj < k.left, hi);
+      }
+      if (!p.M_out) continue;
+      f32x16 sum[1] = {x[rt] * (k.jj < k.left ? 1.0f / (float)k.left : 0.f)};      // mean over the group, on K adjacent lanes (block_kernel.h)
+      if (!zeros) {
+        if (p.K >= 2) lane_sum<0xB1, 1>(sum);
+        if (p.K >= 4) lane_sum<0x4E, 1>(sum);
+        if (p.K >= 8) lane_sum<0x141, 1>(sum);
+        if (p.K >= 16) lane_sum<0x140, 1>(sum);
+        if (p.K >= 32) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sum[0][r] += __shfl_xor(sum[0][r], 16, 64);
+        }
+      }
+      if (k.stored && k.jj == 0) store_rows<T, 1>(sum, p.M_out, p.M_f32, (long long)k.gidx * D + 32 * ft, !zeros, hi);
+    }
+  };
+  if constexpr (MERGE) {
+    uint32_t any = 0;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) any |= there[rt];
+    if (any == 0) { merge_out(true); return; }       // (the same tiles in every wave: all leave)
   }
 
   const char* wl = p.wbase;                          // the current block's stream
@@ -190,8 +254,39 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
       }
     }
     // ---- attention of the wave's heads, a row tile at a time
+    if constexpr (MERGE && SELF) {                   // inside the groups: the keys are the tile's own rows
+      const int widx = W == 16 ? 0 : j / (2 * W);
+      uint32_t wmask[16 / W];
+#pragma unroll
+      for (int w = 0; w < 16 / W; ++w) wmask[w] = widx == w ? 0xffffffffu : 0u;
+      const uint32_t gb = (p.K >= 32 ? 0xffffffffu : ((1u << p.K) - 1u)) << (p.K * (j / p.K));
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const uint32_t bits = ((gb & there[rt]) >> (4 * hi)) >> (2 * W * widx);
+        grp qop[2];
+#pragma unroll
+        for (int g = 0; g < 2; ++g) qop[g] = mid[t0 + rt][ft][g][lane];
+        f32x16 o;
+#pragma unroll
+        for (int hh = 0; hh < HPT; ++hh) {
+          float mrun = kNegBig, lrun = 0.f;
+          f32x16 acc = splat16(0.f), S = splat16(0.f);
+#pragma unroll
+          for (int g2 = 0; g2 < GPH; ++g2) S = E::mma(kop[rt][hh * GPH + g2], qop[hh * GPH + g2], S);
+          grp pop[2];
+          softmax_window<T, W>(S, widx, wmask, bits, mrun, lrun, acc, pop);
+#pragma unroll
+          for (int g = 0; g < 2; ++g) acc = E::mma(vop[rt][g], pop[g], acc);
+          const float inv = lrun > 0.f ? __builtin_amdgcn_rcpf(lrun) : 0.f;
+#pragma unroll
+          for (int r = 0; r < 16 / HPT; ++r) o[16 / HPT * hh + r] = acc[16 / HPT * hh + r] * inv;
+        }
+#pragma unroll
+        for (int g = 0; g < 2; ++g) mid[t0 + rt][ft][g][lane] = E::pack(o, g);
+      }
+    }
 #pragma unroll 1
-    for (int rt = 0; rt < RT; ++rt) {
+    for (int rt = 0; !MERGE && rt < RT; ++rt) {
       const int a = 32 * (t0 + rt) + j;
       if (32 * (t0 + rt) >= rows) break;
       const bool ok = row_valid(a), glob = a < p.m;
@@ -303,11 +398,12 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
     wl = wnext;
     sg.attn = false;
   };
-  block(std::false_type{}, p.n_layers == 1);
-  for (int layer = 1; layer < p.n_layers; ++layer) block(std::true_type{}, layer + 1 == p.n_layers);
+  if constexpr (!MERGE) block(std::false_type{}, p.n_layers == 1);
+  for (int layer = MERGE ? 0 : 1; layer < p.n_layers; ++layer) block(std::true_type{}, layer + 1 == p.n_layers);
 
   // ------------------------------------------------------------------ epilogue
   afresh();
+  if constexpr (MERGE) { merge_out(false); return; }
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
     const int a = 32 * (t0 + rt) + j;
@@ -334,9 +430,12 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
   }
 }
 
-// Host-side launcher, one definition per (D, DH) instantiation file; tiles: row tiles of a user (at most four)
+// Host-side launchers, one definition per (D, DH) instantiation file; tiles: row tiles of a user (at most four); win: as in block_kernel.h
 template <int D, int DH>
 int launch_user(int tiles, const BlockParams& p, dim3 grid, hipStream_t stream);
+constexpr int kUserMergeTiles = 4;
+template <int D, int DH>
+int launch_user_merge(int win, const BlockParams& p, dim3 grid, hipStream_t stream);
 
 #define LONGER_USER_LAUNCH(D, DH, RT, LAY) \
   do {                                                                                                \
@@ -357,6 +456,19 @@ int launch_user(int tiles, const BlockParams& p, dim3 grid, hipStream_t stream);
     if (tiles <= 2) LONGER_USER_LAUNCH(256, DH, 2, QUAD_PLAIN);                                       \
     else if (tiles == 3) LONGER_USER_LAUNCH(256, DH, 3, QUAD_PLAIN);                                  \
     else LONGER_USER_LAUNCH(256, DH, 4, QUAD_PLAIN);                                                  \
+    return hipGetLastError() == hipSuccess ? 0 : -3;                                                  \
+  }
+#define LONGER_USER_MERGE_LAUNCH(DH, WV) \
+  do {                                                                                                \
+    if (p.act == 1) hipLaunchKernelGGL((user_kernel<256, DH, kUserMergeTiles, QUAD_PLAIN, true, MODE_MERGE, WV>), grid, dim3(64 * kUserWaves), 0, stream, p); \
+    else hipLaunchKernelGGL((user_kernel<256, DH, kUserMergeTiles, QUAD_PLAIN, false, MODE_MERGE, WV>), grid, dim3(64 * kUserWaves), 0, stream, p); \
+  } while (0)
+#define LONGER_USER_MERGE_INSTANTIATE_256(DH)                                                         \
+  template <>                                                                                         \
+  int launch_user_merge<256, DH>(int win, const BlockParams& p, dim3 grid, hipStream_t stream) {      \
+    if (win == 4) LONGER_USER_MERGE_LAUNCH(DH, 4);                                                    \
+    else if (win == 8) LONGER_USER_MERGE_LAUNCH(DH, 8);                                               \
+    else LONGER_USER_MERGE_LAUNCH(DH, 16);                                                            \
     return hipGetLastError() == hipSuccess ? 0 : -3;                                                  \
   }
 

@@ -185,3 +185,23 @@ def test_full_precision_small_launches(m, k, K, L, ffn_mult, extra):
     case = synth.make_case(cfg)
     case["lens"][:4] = [L, 0, 1, min(L, 40)]
     _entry_points(case, TOL["f32"], with_inner=False, logits_by_terms=True)
+
+
+# The InnerTrans blocks and both merges at width 256 (a feature tile per wave, four tiles a workgroup): groups of every register window, lengths
+# that are no multiple of K, workgroups that end inside a user, hold several or nothing but padding, one and two blocks, both head widths
+@pytest.mark.gpu
+@pytest.mark.parametrize("heads,K,B,L,layers,extra", [(8, 8, 5, 333, 1, {}), (16, 16, 3, 700, 2, {}), (8, 32, 2, 129, 1, dict(ffn_mult=1)), (16, 1, 3, 50, 1, {}),
+                                                      (8, 4, 7, 31, 2, dict(act="relu")), (16, 2, 1, 1, 1, {})])
+def test_merge_of_width_256(heads, K, B, L, layers, extra):
+    import numpy as np
+    import longer_synth as synth
+    from test_gpu_parity import _entry_points, TOL
+    cfg = synth.CONFIGS["C2"].replace(B=B, L=L, K=K, d=256, heads=8, inner_heads=heads, m=2, k_recent=5, n_self=1, inner_layers=layers, ragged=True, len_lo=0,
+                                      len_hi=L, index=101, **extra)
+    case = synth.make_case(cfg, pad_value=float("nan"))
+    case["lens"][0] = L
+    case["H"][0] = synth.round_bf16(np.random.default_rng(3).standard_normal(case["H"][0].shape).astype(np.float32))
+    if B > 2:
+        case["lens"][1] = 0
+        case["H"][1] = np.float32("nan")
+    _entry_points(case, TOL["bf16"], with_inner=True, logits_by_terms=True)
