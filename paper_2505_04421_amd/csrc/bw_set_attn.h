@@ -53,18 +53,30 @@ __device__ __forceinline__ bool attn_task(const SetAttn& a, int rounds, int* u, 
   return *u < a.B;
 }
 
+// v, or zeros.  (Requests go out unconditionally, for a row that exists, and what is not wanted is dropped afterwards: under a
+// condition each request of a workgroup's start came to wait for the one before: training step of the headline batch 4333 against
+// 4306 us, of a small one 312 against 309, both sides timed in turn.)
+__device__ __forceinline__ bf16x8 keep_if(bf16x8 v, bool wanted) {
+  const u32x4 b = __builtin_bit_cast(u32x4, v);
+  u32x4 w;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) { const uint32_t one = b[e]; w[e] = wanted ? one : 0u; }
+  return __builtin_bit_cast(bf16x8, w);
+}
 // the matrix-core operand of a row (lane = row, 8 features per lane half), straight from memory
 template <int DH>
-struct RowFrag { bf16x8 f[DH / 16]; };
+struct RowFrag {
+  bf16x8 f[DH / 16];
+  __device__ __forceinline__ void keep(bool wanted) {
+#pragma unroll
+    for (int g = 0; g < DH / 16; ++g) f[g] = keep_if(f[g], wanted);
+  }
+};
 template <int DH>
 __device__ __forceinline__ RowFrag<DH> row_frag(const __bf16* p, bool live, int hi) {
   RowFrag<DH> r;
 #pragma unroll
-  for (int g = 0; g < DH / 16; ++g) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) r.f[g][e] = (__bf16)0.f;
-    if (live) r.f[g] = *(const bf16x8*)(p + 16 * g + 8 * hi);
-  }
+  for (int g = 0; g < DH / 16; ++g) r.f[g] = keep_if(*(const bf16x8*)(p + 16 * g + 8 * hi), live);
   return r;
 }
 // rows [r0, r0 + 32) of an LDS tile (pitch DH) as the left operand, times a row operand: [rows] x [lanes]
@@ -109,19 +121,27 @@ __device__ __forceinline__ void store_row(__bf16* p, const f32x16& acc, float w,
     *(bf16x4*)(p + 8 * q + 4 * hi) = t;
   }
 }
-// n rows of a head to LDS, zeros up to the next multiple of 32
-template <int DH>
-__device__ __forceinline__ void stage_rows(__bf16* dst, const __bf16* src, size_t pitch, int n) {
-  constexpr int CP = DH / 8;
-  const int padded = (n + 31) / 32 * 32;
-  for (int c = threadIdx.x; c < padded * CP; c += 256) {
-    bf16x8 v;
+// n rows of a head on their way to LDS (at most N, n > 0), zeros up to the next multiple of 32
+template <int DH, int N>
+struct StagedRows {
+  static constexpr int CP = DH / 8, NI = (N * CP + 255) / 256;
+  bf16x8 v[NI];
+  __device__ __forceinline__ void request(const __bf16* src, size_t pitch, int n) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = (__bf16)0.f;
-    if (c / CP < n) v = *(const bf16x8*)(src + (size_t)(c / CP) * pitch + 8 * (c % CP));
-    *(bf16x8*)(dst + 8 * c) = v;
+    for (int i = 0; i < NI; ++i) {
+      const int c = threadIdx.x + 256 * i;
+      v[i] = *(const bf16x8*)(src + (size_t)min(c / CP, n - 1) * pitch + 8 * (c % CP));
+    }
   }
-}
+  __device__ __forceinline__ void put(__bf16* dst, int n) const {
+    const int padded = (n + 31) / 32 * 32;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int c = threadIdx.x + 256 * i;
+      if (c < padded * CP) *(bf16x8*)(dst + 8 * c) = keep_if(v[i], c / CP < n);
+    }
+  }
+};
 
 // Keys of a workgroup's (user, head) staged in LDS with their orders and each 32-key tile's smallest and largest order.
 template <int DH>
@@ -132,11 +152,20 @@ struct KeyTiles {
 template <int DH>
 __device__ __forceinline__ void stage_keys(KeyTiles<DH>& t, const SetAttn& a, int u, int h, int c0, int n) {
   const size_t row0 = (size_t)u * a.nk + c0;
-  stage_rows<DH>(t.k, a.k + row0 * a.kvpitch + h * DH, a.kvpitch, n);
-  stage_rows<DH>(t.v, a.v + row0 * a.kvpitch + h * DH, a.kvpitch, n);
-  const int lane = threadIdx.x & 63, l32 = lane & 31;
-  for (int kt = threadIdx.x >> 6; kt * 32 < n; kt += 4) {
-    const int j = kt * 32 + l32, ks = j < n ? key_order(a.kdesc[row0 + j]) : kNever;
+  constexpr int NT = (kAttnChunk / 32 + 3) / 4;      // key tiles of a wave
+  StagedRows<DH, kAttnChunk> k, v;
+  k.request(a.k + row0 * a.kvpitch + h * DH, a.kvpitch, n);
+  v.request(a.v + row0 * a.kvpitch + h * DH, a.kvpitch, n);
+  const int lane = threadIdx.x & 63, l32 = lane & 31, wave = threadIdx.x >> 6;
+  int desc[NT];
+#pragma unroll
+  for (int i = 0; i < NT; ++i) desc[i] = a.kdesc[row0 + min((wave + 4 * i) * 32 + l32, n - 1)];
+  k.put(t.k, n);
+  v.put(t.v, n);
+#pragma unroll
+  for (int i = 0; i < NT; ++i) {
+    const int kt = wave + 4 * i, j = kt * 32 + l32, ks = j < n ? key_order(desc[i]) : kNever;
+    if (kt * 32 >= n) continue;
     int lo = ks, up = ks;
 #pragma unroll
     for (int o = 16; o > 0; o >>= 1) { lo = min(lo, __shfl_xor(lo, o, 64)); up = max(up, __shfl_xor(up, o, 64)); }
@@ -175,11 +204,13 @@ __global__ __launch_bounds__(256) void bw_set_attn_fwd_kernel(SetAttn a, __bf16*
   const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
   const int i0 = rd * kAttnRows + 32 * (threadIdx.x >> 6), i = i0 + l32;
   const size_t row = (size_t)u * a.nq + (i < a.nq ? i : 0);
-  const int qd = i < a.nq ? a.qdesc[row] : -1;
+  int qd = a.qdesc[row];
+  RowFrag<DH> q = row_frag<DH>(a.q + row * a.qpitch + h * DH, true, hi);
+  if (i >= a.nq) qd = -1;
   const bool live = qd >= 0;
+  q.keep(live);
   const int smax = query_smax(qd), gmax = query_gmax(qd, a.gmask);
   const float c = 1.4426950408889634f * rsqrtf((float)DH);
-  const RowFrag<DH> q = row_frag<DH>(a.q + row * a.qpitch + h * DH, live, hi);
   f32x16 acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
@@ -228,13 +259,14 @@ __global__ __launch_bounds__(256) void bw_set_attn_bwd_q_kernel(SetAttn a, const
   const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
   const int i0 = rd * kAttnRows + 32 * (threadIdx.x >> 6), i = i0 + l32;
   const size_t row = (size_t)u * a.nq + (i < a.nq ? i : 0);
-  const int qd = i < a.nq ? a.qdesc[row] : -1;
-  const float lse = i < a.nq ? stat[row * a.heads + h].x : __builtin_inff();
+  int qd = a.qdesc[row];
+  float lse = stat[row * a.heads + h].x;
+  RowFrag<DH> q = row_frag<DH>(a.q + row * a.qpitch + h * DH, true, hi), g = row_frag<DH>(dob + row * d + h * DH, true, hi);
+  if (i >= a.nq) { qd = -1; lse = __builtin_inff(); }
   const bool live = qd >= 0;
+  q.keep(live); g.keep(live);
   const int smax = query_smax(qd), gmax = query_gmax(qd, a.gmask);
   const float scale = rsqrtf((float)DH), c = 1.4426950408889634f * scale;
-  const RowFrag<DH> q = row_frag<DH>(a.q + row * a.qpitch + h * DH, live, hi);
-  const RowFrag<DH> g = row_frag<DH>(dob + row * d + h * DH, live, hi);
   f32x16 acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
@@ -293,11 +325,12 @@ __global__ __launch_bounds__(256) void bw_set_attn_bwd_kv_kernel(SetAttn a, cons
   const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
   const int j0 = rd * kAttnRows + 32 * (threadIdx.x >> 6), j = j0 + l32;
   const size_t row = (size_t)u * a.nk + (j < a.nk ? j : 0);
-  const int ks = j < a.nk ? key_order(a.kdesc[row]) : kNever;
+  const int kd = a.kdesc[row];
+  RowFrag<DH> kf = row_frag<DH>(a.k + row * a.kvpitch + h * DH, true, hi), vf = row_frag<DH>(a.v + row * a.kvpitch + h * DH, true, hi);
+  const int ks = j < a.nk ? key_order(kd) : kNever;
   const bool live = ks != kNever;
+  kf.keep(live); vf.keep(live);
   const float scale = rsqrtf((float)DH), c = 1.4426950408889634f * scale;
-  const RowFrag<DH> kf = row_frag<DH>(a.k + row * a.kvpitch + h * DH, live, hi);
-  const RowFrag<DH> vf = row_frag<DH>(a.v + row * a.kvpitch + h * DH, live, hi);
   f32x16 gk, gv;
 #pragma unroll
   for (int r = 0; r < 16; ++r) { gk[r] = 0.f; gv[r] = 0.f; }
@@ -305,12 +338,19 @@ __global__ __launch_bounds__(256) void bw_set_attn_bwd_kv_kernel(SetAttn a, cons
     const int n = min(CH, a.nq - c0);
     const size_t q0 = (size_t)u * a.nq + c0;
     if (c0) __syncthreads();
-    stage_rows<DH>(t.q, a.q + q0 * a.qpitch + h * DH, a.qpitch, n);
-    stage_rows<DH>(t.g, dob + q0 * d + h * DH, d, n);
-    for (int qt = threadIdx.x >> 6; qt * 32 < n; qt += 4) {
-      const int i = qt * 32 + l32, qd = i < n ? a.qdesc[q0 + i] : -1;
+    StagedRows<DH, CH> sq, sg;
+    sq.request(a.q + q0 * a.qpitch + h * DH, a.qpitch, n);
+    sg.request(dob + q0 * d + h * DH, d, n);
+    static_assert(CH == 128, "a query tile a wave");
+    const int qt = threadIdx.x >> 6, i = qt * 32 + l32, ic = min(i, n - 1);
+    int qd = a.qdesc[q0 + ic];
+    float2 st = stat[(q0 + ic) * a.heads + h];
+    sq.put(t.q, n);
+    sg.put(t.g, n);
+    if (qt * 32 < n) {
+      if (i >= n) qd = -1;
       // a row without a query: log-sum-exp +infinity, so that its probabilities are exact zeros untested
-      const float2 st = qd >= 0 ? stat[(q0 + i) * a.heads + h] : make_float2(__builtin_inff(), 0.f);
+      if (qd < 0) st = make_float2(__builtin_inff(), 0.f);
       const int sm = query_smax(qd), gm = query_gmax(qd, a.gmask);
       int lo = qd >= 0 ? sm : kNever, up = sm, gu = gm;
 #pragma unroll
