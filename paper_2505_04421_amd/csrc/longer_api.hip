@@ -669,10 +669,10 @@ struct AttnIO {
 // Launches with few tiles: a tile's chain of products is all that counts, so four or eight waves share it (quad_kernel.h).
 // The line is where every compute unit has its workgroups at once (two of four waves; one of eight at width 256), or another
 // round of them still costs less than the other kernels.  Four layers of scoring, microseconds with it / without: width 64 at 25,
-// 256, 512, 768 tiles 22 / 38, 24 / 38, 33 / 40, 68 / 42; width 128 at 25, 256, 512, 768, 1008 tiles 41 / 107, 47 / 110, 72 / 116, 111 / 123,
-// 138 / 132; width 256 at 25, 256, 512, 768 tiles 91 / 224, 111 / 224, 224 / 233, 325 / 253.  A cache build (two layers of
-// attention), width 64 at 16, 256 tiles 38 / 46, 59 / 67; width 128 at 64, 512, 768, 1024 tiles 95 / 137, 143 / 172, 205 / 212,
-// 252 / 242; width 256 at 32, 256, 512 tiles 170 / 279, 259 / 348, 439 / 479.
+// 256, 512, 768 tiles 21 / 37, 23 / 38, 31 / 40, 68 / 42; width 128 at 25, 256, 512, 768, 1008 tiles 41 / 103, 47 / 106, 71 / 112, 111 / 117,
+// 138 / 125; width 256 at 25, 256, 512, 768 tiles 78 / 223, 96 / 222, 195 / 230, 325 / 251.  A cache build (two layers of
+// attention, each with the next one's K and V, over 50 groups of raw tokens), width 64 at 16, 256, 512 tiles 32 / 48, 51 / 68, 72 / 85; width 128 at 64,
+// 256, 512 tiles 81 / 140, 93 / 151, 135 / 177; width 256 at 32, 256, 512 tiles 131 / 274, 218 / 341, 412 / 465.
 static bool quad_pays(const Shape& s, long long tiles) { return s.quad && tiles <= (s.D == 128 ? 768 : 512); }
 
 static int run_layer(const longer_config* c, const Shape& s, const char* packed_blk, const int32_t* lens, int B, int L,

@@ -18,7 +18,7 @@
 // chunk; at width 256 the weights' way into the compute unit, 64 bytes a cycle (half of a layer's time).  The waves never wait for
 // a weight fragment that they could have asked for earlier: with each product's fragments requested when it began, four
 // layers of scoring took 53 us for 25 tiles at width 128 and 255 us for 128 tiles over 20 key tiles at width 256; requested
-// behind the fragments of the product before, and four key tiles ahead, 41 and 105 us.  (Bringing a block's stream into the
+// behind the fragments of the product before, and four key tiles ahead, 41 and 105 us (92 with the cheaper key tile step).  (Bringing a block's stream into the
 // die's L2 one block ahead, each workgroup its share, cost more than it gave: 51 and 200 us.)
 #pragma once
 #include "block_kernel.h"
