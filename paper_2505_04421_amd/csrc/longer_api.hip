@@ -5,6 +5,7 @@
 #include "user_kernel.h"
 #include "few_f32_kernel.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -479,6 +480,9 @@ static PackedLayout packed_layout(const longer_config* c, const Shape& s) {
 struct Layout {
   size_t packed, M, kst, vst, xa, xb, total;
   size_t kv_ustride;
+  // The few-tiles plan keeps one activation buffer and, in the other one's place, K and V of a layer's result rows in whole tiles
+  // (next_*); a workspace smaller than total_ahead does not hold them and takes the other plans.
+  size_t next_ustride, next_half, total_ahead;
   int ktmax;
 };
 
@@ -495,6 +499,9 @@ static Layout make_layout(const longer_config* c, const Shape& s, int B, int L) 
   l.xa = o; o += align256((size_t)B * s.n * s.D * 4);
   l.xb = o; o += align256((size_t)B * s.n * s.D * 4);
   l.total = o;
+  l.next_ustride = (size_t)cdiv(s.n, 32) * s.NT * s.GPT * 1024;
+  l.next_half = (size_t)B * l.next_ustride;
+  l.total_ahead = s.quad ? std::max(l.total, l.xb + align256(2 * l.next_half)) : l.total;
   return l;
 }
 
@@ -675,6 +682,15 @@ struct AttnIO {
 // 256, 512 tiles 81 / 140, 93 / 151, 135 / 177; width 256 at 32, 256, 512 tiles 131 / 274, 218 / 341, 412 / 465.
 static bool quad_pays(const Shape& s, long long tiles) { return s.quad && tiles <= (s.D == 128 ? 768 : 512); }
 
+// Stacks of more than two tiles a user: as long as their tiles are one round of the few-tiles kernels' workgroups (one per compute
+// unit, two at width 128), a launch per layer in which every tile has a compute unit of its own beats one workgroup per user.  Whole
+// forward pass (L = 400, K = 8, four layers), microseconds layer by layer / in one launch, at 32, 244, 384, 512 and 640 tiles of 108
+// rows a user: width 64 55 / 63, 60 / 64, 73 / 68, 75 / 68, 95 / 69; width 128 77 / 105, 89 / 108, 111 / 117, 113 / 118, 150 / 120;
+// width 256 158 / 252, 171 / 252, 310 / 303, 323 / 304, 434 / 312.  (Two tiles a user at width 256: 157 / 160 at 64 tiles, in one launch.)
+static bool layers_pay(const Shape& s, int B) {
+  return s.quad && s.n > 64 && (long long)B * cdiv(s.n, 32) <= (s.D == 128 ? 512 : 256);
+}
+
 static int run_layer(const longer_config* c, const Shape& s, const char* packed_blk, const int32_t* lens, int B, int L,
                      const AttnIO& io, bool do_attn, hipStream_t st, bool have_kv = false) {
   if (!have_kv) {
@@ -701,7 +717,7 @@ static int run_layer(const longer_config* c, const Shape& s, const char* packed_
   const long long tiles = (long long)B * p.tiles_per_user;
   const int grid = cdiv(tiles, kWaves);
   StageScope scope(ST_ATTN, st);
-  if (quad_pays(s, tiles) && !p.logits) {
+  if (quad_pays(s, tiles)) {
     p.n_layers = 1;
     p.kv_w = io.next_blk; p.kv_k = io.next_kst; p.kv_v = io.next_vst; p.kv_w_ustride = io.next_ustride;
     if (s.quad(MODE_ATTN, 16, false, p, dim3((unsigned)tiles), st)) return fail(LONGER_ERR_HIP, "attention launch failed");
@@ -842,7 +858,7 @@ size_t longer_workspace_bytes(const longer_config* cfg, int B, int L) {
   g_err[0] = 0;
   Shape s;
   if (check_cfg(cfg, &s, cfg && cfg->inner_layers > 0, true) || B <= 0 || L <= 0) return 0;
-  return make_layout(cfg, s, B, L).total;
+  return make_layout(cfg, s, B, L).total_ahead;
 }
 
 size_t longer_kv_cache_bytes(const longer_config* cfg, int U, int L) {
@@ -1002,7 +1018,8 @@ static int forward_impl(const longer_config* cfg, const longer_weights* w, const
   char* w8 = (char*)ws;
   const Shape si = inner_view(cfg, s);
   const bool concat = cfg->merge == LONGER_MERGE_CONCAT;
-  const bool one_launch = stack_in_one_launch(s);
+  const bool room = ws_bytes >= l.total_ahead;
+  const bool one_launch = stack_in_one_launch(s) && !(room && layers_pay(s, B));
   const PackedLayout pl = packed_layout(cfg, s);
   char* pk = nullptr;
   if ((rc = packed_source(cfg, s, w, in ? in->w : nullptr, w8 + l.packed,
@@ -1019,16 +1036,34 @@ static int forward_impl(const longer_config* cfg, const longer_weights* w, const
     if (!few_stack_makes_kv(cfg, s, L) && (rc = run_layer(cfg, s, pk_cross, lens, B, L, io, false, st))) return rc;
     return run_stack(cfg, s, pk_cross, pk + pl.cross_pair, lens, B, L, io, st);
   }
-  void* xbuf[2] = {w8 + l.xa, w8 + l.xb};
+  // Layer by layer.  The few-tiles kernels make the next layer's K and V of their own result rows, alternately in xb's place and in
+  // the cross layer's (no launch writes where one of its other tiles still reads), and update the rows in xa in place: a tile reads
+  // and writes its own rows only.
+  const bool ahead = room && quad_pays(s, (long long)B * cdiv(s.n, 32));
+  void* xbuf[2] = {w8 + l.xa, ahead ? w8 + l.xa : w8 + l.xb};
+  auto self_kv = [&](AttnIO& a, int i) {             // where self layer i finds its K and V
+    if (!ahead || (i & 1)) return;
+    a.kst = w8 + l.xb; a.vst = a.kst + l.next_half; a.kv_ustride = l.next_ustride;
+  };
+  auto project_next = [&](AttnIO& a, int i) {
+    if (!ahead || i >= cfg->n_self) return;
+    AttnIO next = self_io(cfg, s, l, w8, nullptr, 1, nullptr, 1);
+    self_kv(next, i);
+    a.next_blk = pk + pl.self_split + (size_t)i * s.pb;
+    a.next_kst = next.kst; a.next_vst = next.vst; a.next_ustride = next.kv_ustride;
+  };
   const bool last0 = cfg->n_self == 0;
   AttnIO io = cross_io(cfg, s, l, w8, G, w8 + l.M, 1, B, L, last0 ? Y_out : xbuf[0], last0 ? 0 : 1);
   if (last0 && logits_out) { io.logits = logits_out; io.head = head; }
+  project_next(io, 0);
   if ((rc = run_layer(cfg, s, pk_cross, lens, B, L, io, true, st))) return rc;
   for (int i = 0; i < cfg->n_self; ++i) {
     const bool last = i + 1 == cfg->n_self;
     AttnIO sio = self_io(cfg, s, l, w8, xbuf[i & 1], 1, last ? Y_out : xbuf[(i + 1) & 1], last ? 0 : 1);
     if (last && logits_out) { sio.logits = logits_out; sio.head = head; }
-    if ((rc = run_layer(cfg, s, pk + pl.self_split + (size_t)i * s.pb, lens, B, L, sio, true, st))) return rc;
+    self_kv(sio, i);
+    project_next(sio, i + 1);
+    if ((rc = run_layer(cfg, s, pk + pl.self_split + (size_t)i * s.pb, lens, B, L, sio, true, st, ahead))) return rc;
   }
   return 0;
 }

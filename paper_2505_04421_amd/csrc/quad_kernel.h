@@ -2,8 +2,9 @@
 // compute unit, or eight at width 256 (bf16).
 //
 //   MODE_SCORE  candidate scoring of the KV-cache serving path (Section 3.6.3), all layers;
-//   MODE_ATTN   query side of one layer over stored K/V fragments (the cache build's sequence rows), and with kv_w the next
-//               layer's K and V of the result, which a launch of its own took 16 us for (two tiles a user, 16 users, width 256);
+//   MODE_ATTN   query side of one layer over stored K/V fragments (the cache build's sequence rows; a small batch's reduced stack
+//               layer by layer), and with kv_w the next layer's K and V of the result, which a launch of its own took 16 us for
+//               (two tiles a user, 16 users, width 256);
 //   MODE_STACK  the whole reduced stack of a user with at most two tiles (m + k <= 64) in one workgroup of eight waves.
 //
 // Why.  A request scores a hundred candidates (25 tiles), a cache build runs two tiles per user: a handful of
@@ -411,10 +412,9 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_wa
       }
     }
   }
-  if (!STACK && !SCORE) return;
-  if (p.logits) {
+  if (p.logits && (MODE != MODE_ATTN || p.q0 + tile == 0)) {       // (the global rows, at most 32, are all in a user's first tile)
     // logit = <head_w, flatten(global rows)> + head_b: each wave sums over its own feature tiles
-    const int a = STACK ? 32 * ts + j : (32 * tile + j) % p.m, width = STACK ? 32 : p.m;      // row inside the head's m rows; lanes per logit
+    const int a = SCORE ? (32 * tile + j) % p.m : 32 * tile + j, width = SCORE ? p.m : 32;    // row inside the head's m rows; lanes per logit
     float part = 0.f;
     if (valid && a < p.m && own) {
       const f32x16 hw = bias_tile(p.head + (size_t)a * D, wave, hi);
@@ -424,7 +424,7 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_wa
     part = row_sums(0, part, 0.f).x;
     for (int sft = 1; sft < width; sft <<= 1) part += __shfl_xor(part, sft, 64);
     part += p.head[(size_t)p.m * D];
-    if (STACK) {
+    if (!SCORE) {
       if (tid == 0) p.logits[usr] = part;
     } else {
       const int cand = (32 * tile + j) / p.m;

@@ -205,3 +205,39 @@ def test_merge_of_width_256(heads, K, B, L, layers, extra):
         case["lens"][1] = 0
         case["H"][1] = np.float32("nan")
     _entry_points(case, TOL["bf16"], with_inner=True, logits_by_terms=True)
+
+
+# The reduced stack layer by layer (few tiles: the next layer's K and V alternate between two places, so both parities of n_self, and
+# none) and the same users repeated until the one-launch plan takes the call; also a workspace one byte short of the layered plan's
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,heads,m,k,n_self,extra", [(64, 4, 8, 57, 3, {}), (64, 2, 4, 120, 0, dict(gmask="causal")), (128, 8, 8, 100, 3, {}), (128, 4, 32, 33, 1, {}),
+                                                      (128, 8, 8, 88, 2, dict(k_uniform=40)), (128, 8, 8, 150, 3, {}), (256, 8, 8, 57, 3, dict(q_learnable=True)),
+                                                      (256, 16, 32, 96, 1, dict(gmask="causal"))])
+def test_stack_layer_by_layer_and_in_one_launch(d, heads, m, k, n_self, extra):
+    import numpy as np
+    import torch
+    import longer_synth as synth
+    import paper_2505_04421_amd as lg
+    from oracle import longer_oracle as orc
+    from gpu_util import GuardedModel, check_all_guards
+    from test_gpu_parity import TOL, _check
+    cfg = synth.CONFIGS["C2"].replace(B=5, L=500, K=4, d=d, heads=heads, inner_heads=heads, m=m, k_recent=k, n_self=n_self, ragged=True, len_lo=0,
+                                      len_hi=500, index=103, **extra)
+    case = synth.make_case(cfg)
+    case["lens"][:4] = [500, 0, 9, 260]
+    ref, ref_lo = orc.forward(cfg, case["weights"], case["H"], case["G"], case["lens"])
+    lo_bar = 3e-2 * np.sqrt(np.mean(ref_lo ** 2))            # (the parity tests' bar for a batch of logits)
+    model = GuardedModel(cfg, case["weights"])
+    for copies in (1, 512 // (5 * ((m + k + 31) // 32)) + 1):
+        B = 5 * copies
+        H, G = (model.upload(np.concatenate([case[n]] * copies)) for n in ("H", "G"))
+        lens = torch.from_numpy(np.concatenate([case["lens"]] * copies).astype(np.int32)).to(model.device)
+        ws = model.workspace(B, cfg.L).fill_(255)
+        for room in (ws, ws[:-1]) if (m + k) % 32 else (ws,):       # (whole tiles of rows: the smaller workspace is refused)
+            Y, lo = model.empty(B, cfg.n, d), model.empty(B, dtype=torch.float32)
+            lg.longer_forward(model.ccfg, model.weights, H, G, lens, B, cfg.L, Y, lo, room)
+            check_all_guards()
+            got, got_lo = Y.float().cpu().numpy().astype(np.float64), lo.cpu().numpy()
+            for c in range(copies):
+                _check("copy %d Y" % c, got[5 * c:5 * c + 5], ref, TOL["bf16"])
+                assert np.abs(got_lo[5 * c:5 * c + 5] - ref_lo).max() < lo_bar
