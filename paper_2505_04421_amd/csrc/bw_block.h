@@ -62,6 +62,15 @@ void bw_block_launch_128(int dh, const BlockBwParams& p, hipStream_t st);
 // the lane's 16 bytes of a sixteen whose index has parity `odd`
 __device__ __forceinline__ int tile_lane_offset(int lane, int odd) { return ((lane & 31) ^ (4 * odd)) * 32 + (lane >> 5) * 16; }
 
+// A tile's stretch of memory (wave-uniform base, `bytes` long) as a buffer: offset = the lane's part + a scalar
+struct TileBuffer {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ TileBuffer(const void* base, int bytes) : r(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00027000)) {}
+  __device__ __forceinline__ u32x4 get(unsigned lane_off, int off) const { return __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, off, 0); }
+  __device__ __forceinline__ void put(unsigned lane_off, int off, u32x4 v) const { __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)lane_off, off, 0); }
+  __device__ __forceinline__ void put_once(unsigned lane_off, int off, u32x4 v) const { __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)lane_off, off, 2); }      // (streaming: `nt`)
+};
+
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 __device__ __forceinline__ bf16x8 join_tr(s16x4 lo, s16x4 up) {
   typedef short s16x8 __attribute__((ext_vector_type(8)));
@@ -145,22 +154,24 @@ __device__ __forceinline__ void row_stats(const f32x16 (&x)[NT], float eps, floa
 template <int NT>
 __device__ __forceinline__ void norm_backward(f32x16 (&x)[NT], f32x16 (&dn)[NT], const float* gain, float mean, float rstd, int hi) {
   float c1 = 0.f, c2 = 0.f;
+  const float shift = -mean * rstd;
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     dn[t] *= bias_tile(gain, t, hi);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      x[t][r] = (x[t][r] - mean) * rstd;
+      x[t][r] = fmaf(x[t][r], rstd, shift);
       c1 += dn[t][r];
       c2 = fmaf(dn[t][r], x[t][r], c2);
     }
   }
   c1 = sum_halves(c1) * (1.f / (32 * NT));
   c2 = sum_halves(c2) * (1.f / (32 * NT));
+  c1 *= -rstd; c2 *= -rstd;
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) x[t][r] = rstd * (dn[t][r] - c1 - x[t][r] * c2);
+    for (int r = 0; r < 16; ++r) x[t][r] = fmaf(x[t][r], c2, fmaf(dn[t][r], rstd, c1));      // rstd (dn - mean(dn) - x mean(dn x))
 }
 
 // W: registers of a score tile that one group can occupy (K <= 2 W)
@@ -172,6 +183,8 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   __shared__ uint4 ring[NB * PSEG * SEGV];
   __shared__ uint4 turn[kBlkWaves][3][128];        // a wave's K, Q and dO (V on the way forward) pieces of 32 features
   __shared__ f32x4 stat[kBlkWaves][2][8];          // its queries' log-sum-exp and sum of P dP
+  __shared__ uint8_t lefts[kBlkWaves][32];         // valid tokens of its tokens' groups
+  __shared__ float2 norm1[kBlkWaves][32];          // its tokens' first LayerNorm: mean, 1 / standard deviation
   extern __shared__ f32x4 vec4[];
   float* vec = (float*)vec4;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 31, hi = lane >> 5;
@@ -182,38 +195,31 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   const int tile = blockIdx.x * kBlkWaves + wave;
   char* rec = (char*)p.rec + (size_t)tile * rc.size * 1024;       // (wave-uniform: a scalar base, the lane's part an offset)
   const unsigned lane0 = tile_lane_offset(lane, 0), lane1 = tile_lane_offset(lane, 1);
-  typedef __attribute__((address_space(1))) char gchar;
-  typedef __attribute__((address_space(1))) bf16x8 gbf16x8;
-  typedef __attribute__((address_space(1))) f32x4 gf32x4;
-  auto at_rec = [&](int base, int g) -> gbf16x8* {                    // (base is even)
-    gchar* q = (gchar*)(rec + (size_t)((base + g) * 1024));
-    asm("" : "+s"(q));
-    return (gbf16x8*)(q + (g & 1 ? lane1 : lane0));
-  };
-  auto put_rec = [&](int base, int g, bf16x8 v) { __builtin_nontemporal_store(v, at_rec(base, g)); };
-  auto get_rec = [&](int base, int g) -> bf16x8 { return *at_rec(base, g); };
-  auto at_dy = [&](const float* base, int q) -> gf32x4* {             // 1 KiB per 8 features: 4 per lane
-    gchar* b = (gchar*)(base + ((size_t)tile * (D / 8) + q) * 256);
-    asm("" : "+s"(b));
-    return (gf32x4*)(b + 16u * (unsigned)lane);
-  };
-  struct Token { uint32_t slot; int u, tg, jj, len; bool valid, stored; long long row; };
+  // records and tile blocks are addressed as buffers (a scalar base, a scalar offset and the lane's part): with 64-bit addresses
+  // every access cost the vector unit two or three instructions
+  const TileBuffer recb(rec, rc.size * 1024);
+  auto put_rec = [&](int base, int g, bf16x8 v) { recb.put_once(g & 1 ? lane1 : lane0, (base + g) * 1024, __builtin_bit_cast(u32x4, v)); };      // (base is even)
+  auto get_rec = [&](int base, int g) -> bf16x8 { return __builtin_bit_cast(bf16x8, recb.get(g & 1 ? lane1 : lane0, (base + g) * 1024)); };
+  struct Token { uint32_t slot; int u, tg, jj; bool stored; long long row; };
   auto locate = [&](uint32_t first) {
     Token k;
     k.slot = first + (uint32_t)j;
     const uint32_t gidx = k.slot >> __builtin_ctz(p.K);
     k.jj = (int)(k.slot & (uint32_t)(p.K - 1));
     k.u = (int)(gidx / (uint32_t)p.T); k.tg = (int)(gidx - (uint32_t)k.u * (uint32_t)p.T);
-    k.len = 0;
-    if (k.u < p.B) { k.len = p.lens ? p.lens[k.u] : p.L; k.len = min(max(k.len, 0), p.L); }
     const int pos = k.tg * p.K + k.jj;
-    k.valid = pos < k.len;
     k.stored = k.u < p.B && pos < p.L;             // the token has a row in the [B][L] tensors
     k.row = (long long)k.u * p.L + pos;
     return k;
   };
   const Token tk = locate((uint32_t)tile * 32u);
-  const bool valid = tk.valid;
+  int left = 0;                                    // valid tokens of the lane's group
+  if (tk.u < p.B) {
+    int len = p.lens ? p.lens[tk.u] : p.L;
+    left = min(max(min(max(len, 0), p.L) - tk.tg * p.K, 0), p.K);
+  }
+  if (hi == 0) lefts[wave][j] = (uint8_t)left;
+  const bool valid = tk.jj < left;
   if (!__syncthreads_or(valid ? 1 : 0)) {
     if (p.dx_rows && tk.stored) {
       const f32x4 z = {0.f, 0.f, 0.f, 0.f};
@@ -290,14 +296,16 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   // ---- first LayerNorm
   float mean1, rstd1;
   row_stats<NT>(x, p.eps, mean1, rstd1);
+  if (hi == 0) norm1[wave][j] = make_float2(mean1, rstd1);
   bf16x8 nop[NG];
   auto normalise = [&](float mean, float rstd, int og, int ob, int dump) {
+    const float shift = -mean * rstd;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const f32x16 g = bias_tile(vec + og, t, hi), b = bias_tile(vec + ob, t, hi);
       f32x16 h, y;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { h[r] = (x[t][r] - mean) * rstd; y[r] = fmaf(h[r], g[r], b[r]); }
+      for (int r = 0; r < 16; ++r) { h[r] = fmaf(x[t][r], rstd, shift); y[r] = fmaf(h[r], g[r], b[r]); }
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         put_rec(dump, 2 * t + q, E::pack(h, q));
@@ -324,6 +332,39 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
     for (int c = 0; c < W; ++c) { x_[c] = __builtin_amdgcn_exp2f(x_[c] - m); l += x_[c]; }
     l = sum_halves(l);
   };
+  // Gradient of the block's output: requested all at once, a product or more ahead of its use (a request waits for every store
+  // in front of it).  The tile blocks of the block after this one and the merged tokens' gradient both go on in equal steps.
+  f32x4 up[4 * NT];
+  auto request_upstream = [&](const Token& k, bool there) {
+    if (!p.dM) {
+      const TileBuffer b(p.dy + (size_t)tile * (32 * D), 128 * D);
+#pragma unroll
+      for (int i = 0; i < 4 * NT; ++i) up[i] = __builtin_bit_cast(f32x4, b.get(16u * (unsigned)lane, 1024 * i));
+    } else {                                           // (a padded token reads the first merged token's and drops it)
+      typedef __attribute__((address_space(1))) const f32x4 gcf32x4;
+      const float* base = p.dM + (there ? ((size_t)k.u * p.T + k.tg) * (size_t)(p.concat ? p.K * D : D) + (p.concat ? k.jj * D : 0) : 0) + 4 * hi;
+#pragma unroll
+      for (int i = 0; i < 4 * NT; ++i) up[i] = *(gcf32x4*)(base + 8 * i);
+    }
+  };
+  auto take_upstream = [&](int n, bool there) {
+    if (p.dM) {
+      const float share = !there ? 0.f : p.concat ? 1.f : 1.f / (float)n;
+#pragma unroll
+      for (int i = 0; i < 4 * NT; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { const float one = up[i][e]; up[i][e] = there ? one * share : 0.f; }
+    }
+  };
+  auto upstream = [&](int t) -> f32x16 {
+    f32x16 v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { const float one = up[4 * t + q][e]; v[4 * q + e] = one; }
+    return v;
+  };
+  bf16x8 dyop[NG];
   {
     bf16x8 oop[NG];
 #pragma unroll
@@ -377,52 +418,31 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
       for (int g = 0; g < 2; ++g) { oop[2 * ft + g] = E::pack(o, g); put_rec(rc.o, 2 * ft + g, oop[2 * ft + g]); }
     }
     // output projection + residual, second LayerNorm
+    request_upstream(tk, valid);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       x[t] += bias_tile(vec + oBo, t, hi);
       product(x[t], oop);
+    }
+    take_upstream(left, valid);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const f32x16 v = upstream(t);
+#pragma unroll
+      for (int g = 0; g < 2; ++g) { dyop[2 * t + g] = E::pack(v, g); put_rec(rc.dyb, 2 * t + g, dyop[2 * t + g]); }
     }
   }
   float mean2, rstd2;
   row_stats<NT>(x, p.eps, mean2, rstd2);
   normalise(mean2, rstd2, oG2, oB2n, rc.xh2);
 
-  // ---- gradient of the block's output
-  auto upstream = [&](const Token& k, int t) -> f32x16 {
-    f32x16 v;
-    f32x4 w[4];
-    if (!p.dM) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) w[q] = *at_dy(p.dy, 4 * t + q);
-    } else {                                           // (a padded token reads the first merged token's and drops it)
-      const float share = !k.valid ? 0.f : p.concat ? 1.f : 1.f / (float)min(p.K, k.len - k.tg * p.K);
-      const float* up = p.dM + (k.valid ? ((size_t)k.u * p.T + k.tg) * (size_t)(p.concat ? p.K * D : D) + (p.concat ? k.jj * D : 0) : 0);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) w[q] = *(const f32x4*)(up + 32 * t + 8 * q + 4 * hi);
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { const float one = w[q][e]; w[q][e] = k.valid ? one * share : 0.f; }
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[4 * q + e] = w[q][e];
-    return v;
-  };
   f32x16 dn[NT];
   {
     // (at width 128 the LDS pieces of the attention, idle here, hold six of the operand's eight groups)
     constexpr int PARK = NG == 8 ? 6 : 0;
-    bf16x8 dyop[NG];
     char* park = (char*)turn[wave] + lane * 16;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const f32x16 v = upstream(tk, t);
-#pragma unroll
-      for (int g = 0; g < 2; ++g) { dyop[2 * t + g] = E::pack(v, g); put_rec(rc.dyb, 2 * t + g, dyop[2 * t + g]); }
-      dn[t] = splat16(0.f);
-    }
+    for (int t = 0; t < NT; ++t) dn[t] = splat16(0.f);
 #pragma unroll
     for (int g = 0; g < PARK; ++g) *(bf16x8*)(park + g * 1024) = dyop[g];
     // FFN, 32 hidden features at a time: values and gradient formed, used and written out
@@ -453,23 +473,27 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   }
 #pragma unroll
   for (int t = 0; t < NT; ++t) settle(dn[t]);
-  norm_backward<NT>(x, dn, vec + oG2, mean2, rstd2, hi);
   // (where the lane's token sits is worked out again, so that nothing of it is kept through the FFN)
   uint32_t again = (uint32_t)tile * 32u;
   asm volatile("" : "+s"(again));
   const Token tk2 = locate(again);
-  vb = (uint32_t)__ballot(tk2.valid);
+  const int left2 = lefts[wave][j];
+  const bool valid2 = tk2.jj < left2;
+  request_upstream(tk2, valid2);
+  norm_backward<NT>(x, dn, vec + oG2, mean2, rstd2, hi);
+  vb = (uint32_t)__ballot(valid2);
   seen = ((gb & vb) >> (4 * hi)) >> (2 * W * widx);
+  take_upstream(left2, valid2);
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    x[t] += upstream(tk2, t);                          // gradient of the rows between attention and FFN
+    x[t] += upstream(t);                          // gradient of the rows between attention and FFN
 #pragma unroll
     for (int g = 0; g < 2; ++g) { nop[2 * t + g] = E::pack(x[t], g); put_rec(rc.dxmb, 2 * t + g, nop[2 * t + g]); }
     dn[t] = splat16(0.f);
   }
 
   // ---- back through the attention, 32 features (one or two heads) at a time
-  const uint32_t keyseen = tk2.valid ? seen : 0u;
+  const uint32_t keyseen = valid2 ? seen : 0u;
 #pragma unroll
   for (int ft = 0; ft < NT; ++ft) {
     bf16x8 qop[2], kop[2], vop[2], dop[2];
@@ -593,8 +617,10 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   f32x16 xin[NT];
   asm volatile("" : "+s"(again));
   const Token tk3 = locate(again);
-  load_rows<__bf16, NT>(xin, p.x, p.x_f32, (p.x_f32 ? (long long)tk3.slot : tk3.row) * D, tk3.valid, hi);
-  row_stats<NT>(xin, p.eps, mean1, rstd1);
+  const bool valid3 = tk3.jj < lefts[wave][j];
+  load_rows<__bf16, NT>(xin, p.x, p.x_f32, (p.x_f32 ? (long long)tk3.slot : tk3.row) * D, valid3, hi);
+  { const float2 st = norm1[wave][j]; mean1 = st.x; rstd1 = st.y; }
+  const TileBuffer dxb(p.dx + (p.dx_rows ? 0 : (size_t)tile * (32 * D)), p.dx_rows ? 0 : 128 * D);
 #pragma unroll
   for (int t = 0; t < NT; ++t) settle(dn[t]);
   norm_backward<NT>(xin, dn, vec + oG1, mean1, rstd1, hi);
@@ -605,8 +631,8 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
     for (int q = 0; q < 4; ++q) {
       f32x4 v;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = tk3.valid ? x[t][4 * q + e] : 0.f;
-      if (!p.dx_rows) *at_dy(p.dx, 4 * t + q) = v;
+      for (int e = 0; e < 4; ++e) v[e] = valid3 ? x[t][4 * q + e] : 0.f;
+      if (!p.dx_rows) dxb.put(16u * (unsigned)lane, 1024 * (4 * t + q), __builtin_bit_cast(u32x4, v));
       else if (tk3.stored) *(f32x4*)(p.dx + tk3.row * D + 32 * t + 8 * q + 4 * hi) = v;
     }
   }

@@ -60,9 +60,9 @@ __device__ __forceinline__ void act_both(float v, int act, float* a, float* da) 
   pl = fmaf(pl, u, -0.05893596715178192f);
   pl = fmaf(pl, u, 0.3934098519357524f);
   const float c = __builtin_amdgcn_fmed3f(fmaf(v, pl, 0.5f), 0.f, 1.f);
-  const float e = __expf(-0.5f * u);
+  const float density = __builtin_amdgcn_exp2f(fmaf(u, -0.72134752044448170f, -1.3257480647361592f));      // exp(-u / 2) / sqrt(2 pi)
   *a = v * c;
-  *da = fmaf(v * e, 0.39894228040143268f, c);
+  *da = fmaf(v, density, c);
 }
 // the activation, and a gradient g times its derivative
 __device__ __forceinline__ void act_both(float v, int act, float* a, float* dg, float g) {

@@ -63,13 +63,8 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_input_kernel(const Input
   char* rec = (char*)p.rec + (size_t)tile * InputRecord(D, p.f).size * 1024;
   const InputRecord rc(D, p.f);
   const unsigned lane0 = tile_lane_offset(lane, 0), lane1 = tile_lane_offset(lane, 1);
-  typedef __attribute__((address_space(1))) char gchar;
-  typedef __attribute__((address_space(1))) bf16x8 gbf16x8;
-  auto put_rec = [&](int base, int g, bf16x8 v) {                     // (base is even)
-    gchar* q = (gchar*)(rec + (size_t)((base + g) * 1024));
-    asm("" : "+s"(q));
-    __builtin_nontemporal_store(v, (gbf16x8*)(q + (g & 1 ? lane1 : lane0)));
-  };
+  const TileBuffer recb(rec, rc.size * 1024);
+  auto put_rec = [&](int base, int g, bf16x8 v) { recb.put_once(g & 1 ? lane1 : lane0, (base + g) * 1024, __builtin_bit_cast(u32x4, v)); };      // (base is even)
 
   // everything that is read ahead of the first product is requested at once
   f32x16 x[NT], dy[NT];
