@@ -62,13 +62,16 @@ void bw_block_launch_128(int dh, const BlockBwParams& p, hipStream_t st);
 // the lane's 16 bytes of a sixteen whose index has parity `odd`
 __device__ __forceinline__ int tile_lane_offset(int lane, int odd) { return ((lane & 31) ^ (4 * odd)) * 32 + (lane >> 5) * 16; }
 
-// A tile's stretch of memory (wave-uniform base, `bytes` long) as a buffer: offset = the lane's part + a scalar
+// A tile's stretch of memory (wave-uniform base, `bytes` long) as a buffer: offset = the lane's part + a uniform one.  Loads take
+// the uniform part from a scalar register, stores do not: a store reads its data for two more cycles after its issue, and the
+// compiler keeps the registers for that long unless the store has a scalar offset.  With one, the vector instruction
+// right behind a store replaced its data now and then (one 1 KiB piece of a few tiles in a pass of 16 000).
 struct TileBuffer {
   __amdgpu_buffer_rsrc_t r;
   __device__ __forceinline__ TileBuffer(const void* base, int bytes) : r(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00027000)) {}
   __device__ __forceinline__ u32x4 get(unsigned lane_off, int off) const { return __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, off, 0); }
-  __device__ __forceinline__ void put(unsigned lane_off, int off, u32x4 v) const { __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)lane_off, off, 0); }
-  __device__ __forceinline__ void put_once(unsigned lane_off, int off, u32x4 v) const { __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)lane_off, off, 2); }      // (streaming: `nt`)
+  __device__ __forceinline__ void put(unsigned lane_off, int off, u32x4 v) const { __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)lane_off + off, 0, 0); }
+  __device__ __forceinline__ void put_once(unsigned lane_off, int off, u32x4 v) const { __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)lane_off + off, 0, 2); }      // (streaming: `nt`)
 };
 
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
@@ -195,8 +198,7 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   const int tile = blockIdx.x * kBlkWaves + wave;
   char* rec = (char*)p.rec + (size_t)tile * rc.size * 1024;       // (wave-uniform: a scalar base, the lane's part an offset)
   const unsigned lane0 = tile_lane_offset(lane, 0), lane1 = tile_lane_offset(lane, 1);
-  // records and tile blocks are addressed as buffers (a scalar base, a scalar offset and the lane's part): with 64-bit addresses
-  // every access cost the vector unit two or three instructions
+  // records and tile blocks are addressed as buffers: with 64-bit addresses every access cost the vector unit two or three instructions
   const TileBuffer recb(rec, rc.size * 1024);
   auto put_rec = [&](int base, int g, bf16x8 v) { recb.put_once(g & 1 ? lane1 : lane0, (base + g) * 1024, __builtin_bit_cast(u32x4, v)); };      // (base is even)
   auto get_rec = [&](int base, int g) -> bf16x8 { return __builtin_bit_cast(bf16x8, recb.get(g & 1 ? lane1 : lane0, (base + g) * 1024)); };

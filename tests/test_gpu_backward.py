@@ -397,3 +397,25 @@ def test_random_configurations_backward(seed):
     _say("random configuration %d: %s" % (seed, cfg))
     _compare("random %d (token merge)" % seed, case, synth.draw_merge_gradient(cfg))
     _compare_model("random %d (whole model)" % seed, case)
+
+
+# Two InnerTrans blocks hand the gradient of the rows between them over through memory.  What the merge's gradients and dH are made of has
+# no atomic sums: every pass over the same inputs gives the same bits, also when the chip is full (16 tiles per compute unit)
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,heads,K,B,L", [(128, 8, 8, 64, 2000), (64, 4, 16, 61, 2000)])
+def test_repeated_passes_give_the_same_gradients(d, heads, K, B, L):
+    import paper_2505_04421_amd as lg
+    cfg = synth.CONFIGS["C2"].replace(B=B, L=L, K=K, d=d, heads=heads, inner_heads=heads, m=4, k_recent=20, n_self=1, inner_layers=2, index=107)
+    g = torch.Generator(device="cuda:0").manual_seed(3)
+    model = lg.DeviceModel(cfg, synth.make_case(cfg.replace(B=1, L=16))["weights"])
+    H, G = (torch.randn(*shape, generator=g, device="cuda:0").to(model.tdtype) for shape in ((B, L, d), (B, 4, d)))
+    labels = (torch.rand(B, generator=g, device="cuda:0") < 0.5).float()
+    ws = torch.empty(lg.longer_forward_backward_workspace_bytes(model.ccfg, B, L), dtype=torch.uint8, device="cuda:0")
+    grads = torch.empty(lg.longer_model_grad_floats(model.ccfg), device="cuda:0")
+    first = None
+    for _ in range(6):
+        loss, dH, dG = torch.empty(4, device="cuda:0"), torch.empty(B, L, d, device="cuda:0"), torch.empty(B, 4, d, device="cuda:0")
+        lg.longer_forward_backward(model.ccfg, model.weights, H, G, None, B, L, labels, loss, None, dH, dG, grads, ws)
+        if first is None:
+            first = dH, dG
+        assert torch.equal(dH, first[0]) and torch.equal(dG, first[1])
