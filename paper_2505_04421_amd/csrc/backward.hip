@@ -37,6 +37,7 @@
 namespace longer {
 
 int api_error(int code, const char* fmt, ...);   // longer_api.hip
+size_t least_workspace_bytes(const longer_config* cfg, int B, int L);
 int inner_chain_f32(const longer_config* cfg, const longer_block* inner, int layers, const void* H, const int32_t* lens,
                     int B, int L, float* Z_out, void* ws, size_t ws_bytes, void* stream);   // longer_api.hip
 int merge_keep_f32(const longer_config* cfg, const longer_block* inner, const void* H, const int32_t* lens, int B, int L, void* M_out,
@@ -941,10 +942,6 @@ __global__ __launch_bounds__(256) void bw_take_rows_kernel(const float* __restri
   }
 }
 
-__global__ __launch_bounds__(256) void bw_zero_kernel(float* p, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = 0.f;
-}
-
 
 // ------------------------------------------------------------------------------------
 // The reduced stack (Section 3.5): cross-causal layer over R = [G; M] with the query set O of Eq. 5,
@@ -967,27 +964,24 @@ __device__ __forceinline__ int merged_len(const StackGeom& g, int u) {
   return (l + g.K - 1) / g.K;
 }
 
-// descriptors of the query rows [B][m + k] and of the cross layer's key rows [B][m + T]
-__global__ __launch_bounds__(256) void bw_desc_kernel(StackGeom g, int* qdesc, int* kdesc) {
+// entry i of the descriptors of the query rows [B][m + k] and, behind them, of the cross layer's key rows [B][m + T]
+__device__ __forceinline__ void write_descriptor(const StackGeom& g, int i, int* qdesc, int* kdesc) {
   const int n = g.m + g.k, nk = g.m + g.T;
-  const int total = g.B * (n + nk);
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
-    if (i < g.B * n) {
-      const int u = i / n, r = i - u * n;
-      int dsc = r;
-      if (r >= g.m) {
-        const int tu = merged_len(g, u);
-        // a learnable query token stands after the user's newest token, in slot order (it sees every valid
-        // merged token in the cross layer and the slots up to itself in the self layers); no token, no slot
-        const int t = g.learn ? (tu > 0 ? tu + (r - g.m) : -1) : slot_merged_index(r - g.m, g.k, tu, g.k_uniform);
-        dsc = t >= 0 ? kSeq + t : -1;
-      }
-      qdesc[i] = dsc;
-    } else {
-      const int j = i - g.B * n;
-      const int u = j / nk, r = j - u * nk;
-      kdesc[j] = r < g.m ? r : (r - g.m < merged_len(g, u) ? kSeq + (r - g.m) : -1);
+  if (i < g.B * n) {
+    const int u = i / n, r = i - u * n;
+    int dsc = r;
+    if (r >= g.m) {
+      const int tu = merged_len(g, u);
+      // a learnable query token stands after the user's newest token, in slot order (it sees every valid
+      // merged token in the cross layer and the slots up to itself in the self layers); no token, no slot
+      const int t = g.learn ? (tu > 0 ? tu + (r - g.m) : -1) : slot_merged_index(r - g.m, g.k, tu, g.k_uniform);
+      dsc = t >= 0 ? kSeq + t : -1;
     }
+    qdesc[i] = dsc;
+  } else {
+    const int j = i - g.B * n;
+    const int u = j / nk, r = j - u * nk;
+    kdesc[j] = r < g.m ? r : (r - g.m < merged_len(g, u) ? kSeq + (r - g.m) : -1);
   }
 }
 
@@ -1054,7 +1048,8 @@ __global__ __launch_bounds__(256) void bw_head_kernel(const float* __restrict__ 
   }
 }
 
-// dG = the global rows of dO + the global rows of dR; dM[u][t] = dR's row of merged token t (zeros past T_u)
+// dG = the global rows of dO + the global rows of dR; dM[u][t] = dR's row of merged token t (zeros past T_u), plus dO's row of the
+// slot that holds it (of other than the most recent tokens and learnable ones: bw_slot_grad_kernel)
 __global__ __launch_bounds__(256) void bw_split_grad_kernel(StackGeom g, int d, const float* __restrict__ dO,
                                                             const float* __restrict__ dR, float* __restrict__ dG,
                                                             float* __restrict__ dM) {
@@ -1069,8 +1064,13 @@ __global__ __launch_bounds__(256) void bw_split_grad_kernel(StackGeom g, int d, 
       *(f32x4*)(dG + ((size_t)u * g.m + r) * d + c) = v + *(const f32x4*)(dO + ((size_t)u * n + r) * d + c);
     } else {
       const int t = r - g.m;
-      f32x4 z = {0.f, 0.f, 0.f, 0.f};
-      *(f32x4*)(dM + ((size_t)u * g.T + t) * d + c) = t < merged_len(g, u) ? v : z;
+      const int tu = merged_len(g, u), slot = t - tu + g.k;           // (the most recent k tokens fill the slots in order)
+      f32x4 w = {0.f, 0.f, 0.f, 0.f};
+      if (t < tu) {
+        w = v;
+        if (!g.k_uniform && !g.learn && slot >= 0) w += *(const f32x4*)(dO + ((size_t)u * n + g.m + slot) * d + c);
+      }
+      *(f32x4*)(dM + ((size_t)u * g.T + t) * d + c) = w;
     }
   }
 }
@@ -1182,15 +1182,30 @@ __global__ __launch_bounds__(256) void bw_transpose_kernel(const __bf16* __restr
 // fragments of 64 lanes x 16 bytes.  Fragment = 32 rows of the product's result (lane % 32) x 16 contracted features in
 // the order the lanes hold them (element e of lane half hi: 8 (e / 4) + 4 hi + e % 4).  A segment is either 32 result
 // features over the whole width, or (spread) all result features over 32 contracted ones.
+//
+// A training step's launch also writes what else it needs ahead of everything: the rows' descriptors and the zeros that
+// are added to with atomics (kPrepareRows rows of workgroups behind the jobs').  As launches of their own (two fills, descriptors,
+// the stack's and the InnerTrans blocks' weights) they took 28 of the 316 us of the small model's step.
 struct PackJob {
-  const __bf16* w; int sk, sm;            // element (contracted k, result m) at w[k sk + m sm]
-  int spread, n, pos, stride;             // n segments, the i-th at place pos + i stride of the stream
+  const __bf16* w; __bf16* out; int sk, sm;        // element (contracted k, result m) at w[k sk + m sm]
+  int d, spread, n, pos, stride;                   // n segments, the i-th at place pos + i stride of the stream `out`
 };
-constexpr int kPackJobs = 64;
-struct PackJobs { PackJob job[kPackJobs]; __bf16* out; };
-__global__ __launch_bounds__(256) void bw_pack_kernel(const PackJobs a, int d) {
+constexpr int kPackJobs = 72, kPrepareRows = 8;
+struct PackJobs { PackJob job[kPackJobs]; int n; };
+struct Prepare { StackGeom geo; int *qdesc, *kdesc; float* zeros; size_t nzeros; float* loss; };
+__global__ __launch_bounds__(256) void bw_pack_kernel(const PackJobs a, const Prepare q) {
+  if ((int)blockIdx.y >= a.n) {
+    const size_t rows = (size_t)q.geo.B * (2 * q.geo.m + q.geo.k + q.geo.T), total = rows + q.nzeros;
+    const size_t first = ((size_t)(blockIdx.y - a.n) * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
+    if (first == 0) *q.loss = 0.f;
+    for (size_t i = first; i < total; i += (size_t)kPrepareRows * gridDim.x * 256) {
+      if (i < rows) write_descriptor(q.geo, (int)i, q.qdesc, q.kdesc);
+      else q.zeros[i - rows] = 0.f;
+    }
+    return;
+  }
   const PackJob& b = a.job[blockIdx.y];
-  const int NG = d / 16, total = b.n * NG * 64;
+  const int NG = b.d / 16, total = b.n * NG * 64;
   for (int i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
     const int lane = i & 63, s = (i >> 6) % NG, seg = (i >> 6) / NG, m = lane & 31, hi = lane >> 5;
     const __bf16* src = b.w + (b.spread ? (size_t)(32 * seg + 16 * (s % 2)) * b.sk + (size_t)(32 * (s / 2) + m) * b.sm
@@ -1198,7 +1213,7 @@ __global__ __launch_bounds__(256) void bw_pack_kernel(const PackJobs a, int d) {
     bf16x8 v;
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = src[(size_t)(8 * (e / 4) + 4 * hi + e % 4) * b.sk];
-    *(bf16x8*)(a.out + (((size_t)(b.pos + seg * b.stride) * NG + s) * 64 + lane) * 8) = v;
+    *(bf16x8*)(b.out + (((size_t)(b.pos + seg * b.stride) * NG + s) * 64 + lane) * 8) = v;
   }
 }
 
@@ -1206,11 +1221,12 @@ __global__ __launch_bounds__(256) void bw_pack_kernel(const PackJobs a, int d) {
 // of the products W): with X = xh^T dY and c = column sums of dY (bias gradients) both summed by now,
 //   dW = diag(g) X + s c^T,   dg[e] = sum_c W[e][c] X[e][c],   ds[e] = sum_c W[e][c] c[c],
 // so the LayerNorm gradients need no pass over the tokens.  One workgroup per row e and LayerNorm.
-constexpr int kNormBlocks = 8;            // blocks per launch
-struct NormGrads { struct { const __bf16 *w[3], *gain, *shift; float *dw, *dgain; } n[2 * kNormBlocks]; };
-__global__ __launch_bounds__(256) void bw_norm_grads_kernel(const NormGrads a, int d, int f) {
-  const int which = blockIdx.y & 1, e = blockIdx.x, n = which ? f : d, mats = which ? 1 : 3;     // ln1: Q, K, V; ln2: W1
+constexpr int kNormBlocks = 16;           // blocks per launch
+struct NormGrads { struct { const __bf16 *w[3], *gain, *shift; float *dw, *dgain; int d, f; } n[2 * kNormBlocks]; };
+__global__ __launch_bounds__(256) void bw_norm_grads_kernel(const NormGrads a) {
   const auto& q = a.n[blockIdx.y];
+  const int which = blockIdx.y & 1, e = blockIdx.x, d = q.d, n = which ? q.f : d, mats = which ? 1 : 3;     // ln1: Q, K, V; ln2: W1
+  if (e >= d) return;
   const float gain = (float)q.gain[e], shift = (float)q.shift[e];
   float sg = 0.f, ss = 0.f;
   for (int i = threadIdx.x; i < mats * n; i += 256) {
@@ -1308,38 +1324,53 @@ static int launch(const ReduceBatch& r, hipStream_t st) {
 // Weights of one or several streams, packed in as few launches as their number allows
 struct PackBatch {
   PackJobs a = {};
-  int n = 0, d; hipStream_t st; int rc = 0;
-  PackBatch(int d_, __bf16* out, hipStream_t st_) : d(d_), st(st_) { a.out = out; }
+  int d; __bf16* out; hipStream_t st; int rc = 0;
+  PackBatch(int d_, __bf16* out_, hipStream_t st_) : d(d_), out(out_), st(st_) {}
+  void into(int d_, __bf16* out_) { d = d_; out = out_; }      // the following jobs' width and stream
   void add(const void* w, int sk, int sm, bool spread, int segs, int pos, int stride) {
-    if (n == kPackJobs) flush();
-    a.job[n++] = PackJob{(const __bf16*)w, sk, sm, spread, segs, pos, stride};
+    if (a.n == kPackJobs) flush();
+    a.job[a.n++] = PackJob{(const __bf16*)w, out, sk, sm, d, spread, segs, pos, stride};
   }
-  int flush() {
-    if (n && !rc) {
-      bw_pack_kernel<<<dim3(64, n), 256, 0, st>>>(a, d);
+  int flush(const Prepare* prepare = nullptr) {
+    if ((a.n || prepare) && !rc) {
+      bw_pack_kernel<<<dim3(64, a.n + (prepare ? kPrepareRows : 0)), 256, 0, st>>>(a, prepare ? *prepare : Prepare{});
       if (hipGetLastError() != hipSuccess) rc = api_error(LONGER_ERR_HIP, "weight packing launch failed");
     }
-    n = 0;
+    a.n = 0;
     return rc;
   }
 };
-// LayerNorm gradients and dW = diag(g) X + s c^T of whole blocks (bw_norm_grads_kernel); grads of block i at g0 + i stride
-static int norm_grads(int d, int f, const longer_block* blocks, int count, float* g0, size_t stride, hipStream_t st) {
-  const GradLayout gl = grad_layout(d, f);
-  for (int l0 = 0; l0 < count; l0 += kNormBlocks) {
-    NormGrads ng = {};
-    const int n = count - l0 < kNormBlocks ? count - l0 : kNormBlocks;
-    for (int i = 0; i < n; ++i) {
-      const longer_block& b = blocks[l0 + i];
-      float* g = g0 + (size_t)(l0 + i) * stride;
-      ng.n[2 * i] = {{(const __bf16*)b.wq, (const __bf16*)b.wk, (const __bf16*)b.wv}, (const __bf16*)b.ln1_g, (const __bf16*)b.ln1_b, g + gl.wq, g + gl.ln1_g};
-      ng.n[2 * i + 1] = {{(const __bf16*)b.w1, nullptr, nullptr}, (const __bf16*)b.ln2_g, (const __bf16*)b.ln2_b, g + gl.w1, g + gl.ln2_g};
+// LayerNorm gradients and dW = diag(g) X + s c^T of whole blocks (bw_norm_grads_kernel), of one or several widths
+struct NormBatch {
+  NormGrads a = {};
+  int n = 0, width = 0, rc = 0; hipStream_t st;
+  NormBatch(hipStream_t st_) : st(st_) {}
+  void add(int d, int f, const longer_block* blocks, int count, float* g0, size_t stride) {      // grads of block i at g0 + i stride
+    const GradLayout gl = grad_layout(d, f);
+    for (int i = 0; i < count; ++i) {
+      if (n == kNormBlocks) flush();
+      const longer_block& b = blocks[i];
+      float* g = g0 + (size_t)i * stride;
+      a.n[2 * n] = {{(const __bf16*)b.wq, (const __bf16*)b.wk, (const __bf16*)b.wv}, (const __bf16*)b.ln1_g, (const __bf16*)b.ln1_b, g + gl.wq, g + gl.ln1_g, d, f};
+      a.n[2 * n + 1] = {{(const __bf16*)b.w1, nullptr, nullptr}, (const __bf16*)b.ln2_g, (const __bf16*)b.ln2_b, g + gl.w1, g + gl.ln2_g, d, f};
+      ++n;
+      width = d > width ? d : width;
     }
-    bw_norm_grads_kernel<<<dim3(d, 2 * n), 256, 0, st>>>(ng, d, f);
-    if (hipGetLastError() != hipSuccess) return api_error(LONGER_ERR_HIP, "LayerNorm gradient launch failed");
   }
-  return 0;
-}
+  int flush() {
+    if (n && !rc) {
+      bw_norm_grads_kernel<<<dim3(width, 2 * n), 256, 0, st>>>(a);
+      if (hipGetLastError() != hipSuccess) rc = api_error(LONGER_ERR_HIP, "LayerNorm gradient launch failed");
+    }
+    n = width = 0;
+    return rc;
+  }
+};
+// Sums and LayerNorm gradients that wait for the next such launch (their partial results keep a place of their own)
+struct GradTail {
+  ReduceBatch sums; NormBatch norms;
+  GradTail(hipStream_t st) : norms(st) {}
+};
 
 static Workspace workspace(int layers, size_t ntok, int d, int f, int heads, size_t fwd_bytes, size_t ztmp_bytes) {
   Workspace w;
@@ -1400,9 +1431,9 @@ static Workspace tiled_workspace(const Dims& s, size_t fwd_bytes) {
 // then sit at [B, T K] instead of [B, L])
 static Workspace merge_workspace(const longer_config* c, const Dims& s, int B, int L) {
   size_t fwd = 0, zt = 0;
-  if (s.tiled) return tiled_workspace(s, s.layers > 1 ? longer_workspace_bytes(c, B, L) : 0);
+  if (s.tiled) return tiled_workspace(s, s.layers > 1 ? least_workspace_bytes(c, B, L) : 0);
   if (s.layers > 1) {
-    fwd = longer_workspace_bytes(c, B, L);
+    fwd = least_workspace_bytes(c, B, L);
     if (L % s.K) zt = (size_t)B * s.T * s.K * s.d * 4;
   }
   return workspace(s.layers, s.ntok, s.d, s.f, s.heads, fwd, zt);
@@ -1534,15 +1565,9 @@ static unsigned flat_grid(size_t n) {
 
 #define BW_TRY(x) do { int rc_ = (x); if (rc_) return rc_; } while (0)
 
-static int run_tiled(const longer_config* c, const longer_block* inner, const void* H, const int32_t* lens, int B, int L,
-                     const float* dM, float* dH, float* grads, char* ws, hipStream_t st, const Dims& s, bool inputs_kept) {
+// the block kernel's weights, all blocks' streams one after the other
+static void pack_tiled(PackBatch& pk, const longer_block* inner, const Dims& s) {
   const int d = s.d, f = s.f;
-  const Workspace w = merge_workspace(c, s, B, L);
-  const GradLayout gl = grad_layout(d, f);
-  const RowsValid rv = {lens, s.T * s.K};
-  const size_t stream_elems = (size_t)bw_block_segs_padded(d, f) * packed_seg_bytes(d, 2) / 2;
-  auto at = [&](size_t o) { return (__bf16*)(ws + o); };
-  PackBatch pk(d, at(w.stream), st);
   for (int l = 0; l < s.layers; ++l) {
     const longer_block& b = inner[l];
     const int NT = d / 32, NC = f / 32, o = l * bw_block_segs_padded(d, f), c = o + 4 * NT, k = c + 3 * NC;
@@ -1555,7 +1580,23 @@ static int run_tiled(const longer_config* c, const longer_block* inner, const vo
     pk.add(b.wo, 1, d, false, NT, k, 4);              // back through W_O and, 32 features at a time, W_Q, W_K, W_V
     for (int i = 0; i < 3; ++i) pk.add(qkv[i], 1, d, true, NT, k + 1 + i, 4);
   }
-  BW_TRY(pk.flush());
+}
+
+static int run_tiled(const longer_config* c, const longer_block* inner, const void* H, const int32_t* lens, int B, int L,
+                     const float* dM, float* dH, float* grads, char* ws, hipStream_t st, const Dims& s, bool inputs_kept, GradTail* tail) {
+  const int d = s.d, f = s.f;
+  const Workspace w = merge_workspace(c, s, B, L);
+  const GradLayout gl = grad_layout(d, f);
+  const RowsValid rv = {lens, s.T * s.K};
+  const size_t stream_elems = (size_t)bw_block_segs_padded(d, f) * packed_seg_bytes(d, 2) / 2;
+  auto at = [&](size_t o) { return (__bf16*)(ws + o); };
+  if (!tail) {                                         // (a whole training step has packed them already)
+    PackBatch pk(d, at(w.stream), st);
+    pack_tiled(pk, inner, s);
+    BW_TRY(pk.flush());
+  }
+  GradTail own(st);
+  GradTail& t = tail ? *tail : own;
   // block inputs, by the fused forward kernel (its fp32 residual stream after l blocks is block l's input)
   auto xin = [&](int l) { return (float*)(ws + w.xin) + (size_t)(l - 1) * s.padded * d; };
   // unless the forward merge of the same call left them there
@@ -1580,17 +1621,22 @@ static int run_tiled(const longer_config* c, const longer_block* inner, const vo
     BW_TRY(launched("block backward"));
     WgradBatch wg = block_wgrads_tiles(d, f, s.slots, rv, p.rec, g);
     BW_TRY(launch(wg, (float*)(ws + w.part), st));
-    ReduceBatch rb;
-    rb.add(wg);
-    BW_TRY(launch(rb, st));
+    t.sums.add(wg);
+    BW_TRY(launch(t.sums, st));
+    t.sums = ReduceBatch{};
   }
-  BW_TRY(norm_grads(d, f, inner, s.layers, grads, gl.total, st));
-  return 0;
+  t.norms.add(d, f, inner, s.layers, grads, gl.total);
+  return t.norms.flush();
 }
 
 static int run(const longer_config* c, const longer_block* inner, const void* H, const int32_t* lens, int B, int L,
-               const float* dM, float* dH, float* grads, char* ws, hipStream_t st, const Dims& s, bool inputs_kept = false) {
-  if (s.tiled) return run_tiled(c, inner, H, lens, B, L, dM, dH, grads, ws, st, s, inputs_kept);
+               const float* dM, float* dH, float* grads, char* ws, hipStream_t st, const Dims& s, bool inputs_kept = false,
+               GradTail* tail = nullptr) {
+  if (s.tiled) return run_tiled(c, inner, H, lens, B, L, dM, dH, grads, ws, st, s, inputs_kept, tail);
+  if (tail) {
+    BW_TRY(launch(tail->sums, st));
+    BW_TRY(tail->norms.flush());
+  }
   const int d = s.d, f = s.f;
   const size_t nt = s.ntok;
   const Workspace w = merge_workspace(c, s, B, L);
@@ -1818,7 +1864,8 @@ static ModelGrads model_grads(const Dims& mi, const StackDims& s, bool learn) {
 
 static int run_model(const longer_config* c, const longer_weights* wts, const void* H, const void* G, const int32_t* lens,
                      int B, int L, const float* labels, float* loss, float* logits, float* dH, float* dG, float* grads,
-                     char* ws, size_t fwd_bytes, hipStream_t st, const Dims& mi, const StackDims& s, float* block_inputs) {
+                     char* ws, size_t fwd_bytes, hipStream_t st, const Dims& mi, const StackDims& s, float* block_inputs,
+                     __bf16* block_stream, GradTail& tail) {
   const int d = s.d, f = s.f;
   const size_t rq = s.rq, rk = s.rk;
   const StackWs w = stack_ws(s, fwd_bytes);
@@ -1839,19 +1886,7 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
   const int NT = d / 32, NC = f / 32, last = s.layers - 1;
   auto stream_at = [&](int seg) { return ws + w.stream + (size_t)seg * packed_seg_bytes(d, 2); };
 
-  // what is added to with atomics: the head's gradients, the learnable query tokens', the loss
-  bw_zero_kernel<<<flat_grid(mg.total - mg.head_w), 256, 0, st>>>(grads + mg.head_w, mg.total - mg.head_w);
-  bw_zero_kernel<<<1, 256, 0, st>>>(loss, 1);
-  BW_TRY(launched("zero fill"));
-
-  // ---- forward from the inputs: merged tokens (the fused forward kernel; the merge's intermediates are
-  // recomputed later by its own backward pass), then the stack, keeping every layer's intermediates
-  int rc = block_inputs ? merge_keep_f32(c, wts->inner, H, lens, B, L, Mb, block_inputs, mi.padded * mi.d, ws + w.fwd_ws, fwd_bytes, st)
-                        : longer_token_merge(c, wts->inner, H, lens, B, L, Mb, ws + w.fwd_ws, fwd_bytes, st);
-  if (rc) return rc;
-  bw_desc_kernel<<<flat_grid(rq + rk), 256, 0, st>>>(geo, qdesc, kdesc);
-  bw_build_rows_kernel<<<flat_grid((rq + rk) * d / 4), 256, 0, st>>>(geo, d, (const __bf16*)G, Mb, (const __bf16*)c->q_learn, qdesc, kdesc, xs(0), Rx);
-  BW_TRY(launched("row build"));
+  // ---- weights in the launches' order, row descriptors, zeros
   PackBatch pk(d, (__bf16*)(ws + w.stream), st);
   for (int l = 0; l < s.layers; ++l) {
     const longer_block& b = blk(l);
@@ -1873,8 +1908,21 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
     pk.add(b.w1, 1, f, true, NC, h + 2, 3);
     pk.add(b.wo, 1, d, false, NT, h + 3 * NC, 1);
   }
-  BW_TRY(pk.flush());
+  if (block_stream) {
+    pk.into(mi.d, block_stream);
+    pack_tiled(pk, wts->inner, mi);
+  }
+  // (added to with atomics: the head's gradients, the learnable query tokens', the loss)
+  const Prepare prepare = {geo, qdesc, kdesc, grads + mg.head_w, mg.total - mg.head_w, loss};
+  BW_TRY(pk.flush(&prepare));
 
+  // ---- forward from the inputs: merged tokens (the fused forward kernel; the merge's intermediates are
+  // recomputed later by its own backward pass), then the stack, keeping every layer's intermediates
+  int rc = block_inputs ? merge_keep_f32(c, wts->inner, H, lens, B, L, Mb, block_inputs, mi.padded * mi.d, ws + w.fwd_ws, fwd_bytes, st)
+                        : longer_token_merge(c, wts->inner, H, lens, B, L, Mb, ws + w.fwd_ws, fwd_bytes, st);
+  if (rc) return rc;
+  bw_build_rows_kernel<<<flat_grid((rq + rk) * d / 4), 256, 0, st>>>(geo, d, (const __bf16*)G, Mb, (const __bf16*)c->q_learn, qdesc, kdesc, xs(0), Rx);
+  BW_TRY(launched("row build"));
   auto attn = [&](int l) {
     SetAttn t;
     const __bf16* qkv = (const __bf16*)of(w.qkv, l);
@@ -1889,14 +1937,14 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
     else set_attn_launch<32>(st, which, attn(l), dob, d, out, pitch, dk, dv, stat);
     return launched(which ? "attention backward" : "attention");
   };
-  auto fwd = [&](const StackFwd& p) -> int {
-    if (d == 32) bw_stack_fwd_32(p, st); else if (d == 64) bw_stack_fwd_64(p, st);
-    else if (d == 128) bw_stack_fwd_128(p, st); else bw_stack_fwd_256(p, st);
+  auto fwd = [&](const StackFwd& p, const StackFwd& k) -> int {
+    if (d == 32) bw_stack_fwd_32(p, k, st); else if (d == 64) bw_stack_fwd_64(p, k, st);
+    else if (d == 128) bw_stack_fwd_128(p, k, st); else bw_stack_fwd_256(p, k, st);
     return launched("stack forward");
   };
-  auto bwd = [&](const StackBwd& p) -> int {
-    if (d == 32) bw_stack_bwd_32(p, st); else if (d == 64) bw_stack_bwd_64(p, st);
-    else if (d == 128) bw_stack_bwd_128(p, st); else bw_stack_bwd_256(p, st);
+  auto bwd = [&](const StackBwd& p, const StackBwd& k) -> int {
+    if (d == 32) bw_stack_bwd_32(p, k, st); else if (d == 64) bw_stack_bwd_64(p, k, st);
+    else if (d == 128) bw_stack_bwd_128(p, k, st); else bw_stack_bwd_256(p, k, st);
     return launched("stack backward");
   };
   // forward: [head of 0 (and its keys)], attention, [tail of l, head of l + 1], ...
@@ -1918,15 +1966,14 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
       p.ln1_g = bf(b.ln1_g); p.ln1_b = bf(b.ln1_b); p.bias[0] = bf(b.bq); p.bias[1] = bf(b.bk); p.bias[2] = bf(b.bv);
       p.out = (__bf16*)of(w.qkv, l + 1); p.ldo = p.mats * d; p.rec1 = (__bf16*)of(w.rec, l + 1); p.rec1_size = r.size; p.rec1_xh = r.xh1;
     }
-    BW_TRY(fwd(p));
+    StackFwd k = {};
     if (l < 0) {
       const longer_block& b = blk(0);
-      StackFwd k = {};
       k.rows = (int)rk; k.f = f; k.eps = c->ln_eps; k.wstream = stream_at(sg.kv_f); k.x = Rx;
       k.ln1_g = bf(b.ln1_g); k.ln1_b = bf(b.ln1_b); k.bias[0] = bf(b.bk); k.bias[1] = bf(b.bv);
       k.mats = 2; k.out = kv; k.ldo = 2 * d; k.rec1 = krec; k.rec1_size = key_record(d); k.rec1_xh = 0;
-      BW_TRY(fwd(k));
     }
+    BW_TRY(fwd(p, k));
   }
 
   // ---- head and loss (Eq. 1-2), and the gradient of the stack's output
@@ -1953,27 +2000,25 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
       p.desc = qdesc; p.xmid = (const float*)of(w.xmid, l - 1); p.ln2_g = bf(b.ln2_g); p.ln2_b = bf(b.ln2_b); p.b1 = bf(b.b1);
       p.dxm = dxm; p.dob = dob; p.rec = (__bf16*)of(w.rec, l - 1);
     }
-    BW_TRY(bwd(p));
+    StackBwd k = {};
     if (l == 0) {
-      StackBwd k = {};
       k.rows = (int)rk; k.f = f; k.eps = c->ln_eps; k.wstream = stream_at(sg.kv_b); k.mats = 2;
       k.dqkv = dkv; k.ldq = 2 * d; k.x = Rx; k.ln1_g = bf(blk(0).ln1_g); k.rec1 = krec; k.rec1_size = key_record(d);
       k.rec1_dqkv = d / 16; k.dx = dR;
-      BW_TRY(bwd(k));
     }
+    BW_TRY(bwd(p, k));
   }
-  // ---- parameter gradients of all layers: one launch, one for the sums of its partial results, the LayerNorms' from those
+  // ---- parameter gradients of all layers: one launch; the sums of its partial results and the LayerNorms' from those go with the merge's
   WgradBatch wg = stack_wgrads(s, w, ws, grads, mg.cross, mg.self0, mg.per_main);
   BW_TRY(launch(wg, (float*)(ws + w.part), st));
-  ReduceBatch rb;
-  rb.add(wg);
-  BW_TRY(launch(rb, st));
-  BW_TRY(norm_grads(d, f, wts->cross, 1, grads + mg.cross, mg.per_main, st));
-  if (s.layers > 1) BW_TRY(norm_grads(d, f, wts->self, s.layers - 1, grads + mg.self0, mg.per_main, st));
+  tail.sums.add(wg);
+  tail.norms.add(d, f, wts->cross, 1, grads + mg.cross, mg.per_main);
+  if (s.layers > 1) tail.norms.add(d, f, wts->self, s.layers - 1, grads + mg.self0, mg.per_main);
   // ---- gradients of the stack's inputs: global tokens (query rows and key rows), merged tokens (key
   // rows, plus the query slots that hold them)
   bw_split_grad_kernel<<<flat_grid(rk * d / 4), 256, 0, st>>>(geo, d, dy, dR, dG, dM);
-  bw_slot_grad_kernel<<<flat_grid((size_t)B * s.k * d / 4), 256, 0, st>>>(geo, d, dy, qdesc, dM, grads + mg.q_learn);
+  if (geo.k_uniform || geo.learn)
+    bw_slot_grad_kernel<<<flat_grid((size_t)B * s.k * d / 4), 256, 0, st>>>(geo, d, dy, qdesc, dM, grads + mg.q_learn);
   BW_TRY(launched("gradient routing"));
   return 0;
 }
@@ -2091,7 +2136,7 @@ size_t longer_forward_backward_workspace_bytes(const longer_config* cfg, int B, 
   bw::Dims mi;
   bw::StackDims s;
   if (bw::check(cfg, B, L, &mi) || bw::check_stack(cfg, B, L, &s)) return 0;
-  const size_t fwd = longer_workspace_bytes(cfg, B, L);
+  const size_t fwd = least_workspace_bytes(cfg, B, L);
   if (fwd == 0) return 0;
   return bw::stack_ws(s, fwd).total + bw::merge_workspace(cfg, mi, B, L).total;
 }
@@ -2119,7 +2164,7 @@ int longer_forward_backward(const longer_config* cfg, const longer_weights* w, c
     for (int i = 0; i < 16; ++i)
       if (!p[i] || !bw::aligned16(p[i])) return api_error(LONGER_ERR_ARG, "block %d: parameter %d is NULL or not 16-byte aligned", l, i);
   }
-  const size_t fwd = longer_workspace_bytes(cfg, B, L);
+  const size_t fwd = least_workspace_bytes(cfg, B, L);
   if (fwd == 0) return LONGER_ERR_ARG;
   const size_t stack_bytes = bw::stack_ws(s, fwd).total;
   const size_t need = stack_bytes + bw::merge_workspace(cfg, mi, B, L).total;
@@ -2128,11 +2173,14 @@ int longer_forward_backward(const longer_config* cfg, const longer_weights* w, c
   // with several blocks the forward merge writes the later ones' input rows where the merge's backward pass expects them
   const bool keep = mi.tiled && mi.layers > 1;
   float* block_inputs = keep ? (float*)((char*)ws + stack_bytes + bw::merge_workspace(cfg, mi, B, L).xin) : nullptr;
-  rc = bw::run_model(cfg, w, H, G, lens, B, L, labels, loss_out, logits_out, dH_out, dG_out, grads_out, (char*)ws, fwd, st, mi, s, block_inputs);
+  bw::GradTail tail(st);
+  __bf16* block_stream = mi.tiled ? (__bf16*)((char*)ws + stack_bytes + bw::merge_workspace(cfg, mi, B, L).stream) : nullptr;
+  rc = bw::run_model(cfg, w, H, G, lens, B, L, labels, loss_out, logits_out, dH_out, dG_out, grads_out, (char*)ws, fwd, st, mi, s, block_inputs,
+                     block_stream, tail);
   if (rc) return rc;
   // the merge's gradients: dM was left in the stack's workspace; the InnerTrans blocks come first in grads_out
   const float* dM = (const float*)((char*)ws + bw::stack_ws(s, fwd).dM);
-  return bw::run(cfg, w->inner, H, lens, B, L, dM, dH_out, grads_out, (char*)ws + stack_bytes, st, mi, keep);
+  return bw::run(cfg, w->inner, H, lens, B, L, dM, dH_out, grads_out, (char*)ws + stack_bytes, st, mi, keep, &tail);
 }
 
 size_t longer_input_backward_workspace_bytes(const longer_config* cfg, int B, int L, int d_e) {

@@ -242,7 +242,7 @@ __host__ __device__ inline int stack_vec_floats(int d, int f) { return 9 * d + f
 // What bounds the two kernels: the chain of a tile at small batches; at the headline batch (864 tiles) the exact-erf activation
 // beside the products, and 3.3 KB (forward) and 5.5 KB (backward) of memory traffic per row.
 template <int D>
-__global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stack_fwd_kernel(const StackFwd p) {
+__global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stack_fwd_kernel(const StackFwd p0, const StackFwd p1, int tiles0) {
   using S = StackTile<D>;
   constexpr int NT = S::NT, NG = S::NG, WV = S::WV;
   using E = ET<__bf16>;
@@ -252,7 +252,9 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stac
   extern __shared__ f32x4 vec4[];
   float* vec = (float*)vec4;
   const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, hi = lane >> 5, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int tile = blockIdx.x, row = tile * 32 + j, NC = p.f / 32;
+  StackFwd p = p0;
+  if ((int)blockIdx.x >= tiles0) p = p1;
+  const int tile = (int)blockIdx.x - ((int)blockIdx.x >= tiles0 ? tiles0 : 0), row = tile * 32 + j, NC = p.f / 32;
   const bool in = row < p.rows, own = wave < NT;
   const int ft = wave % NT;
   const int oBo = 0, oG2 = D, oS2 = 2 * D, oB2 = 3 * D, oG1 = 4 * D, oS1 = 5 * D, oB = 6 * D, oB1 = 9 * D;
@@ -362,7 +364,7 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stac
 }
 
 template <int D>
-__global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stack_bwd_kernel(const StackBwd p) {
+__global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stack_bwd_kernel(const StackBwd p0, const StackBwd p1, int tiles0) {
   using S = StackTile<D>;
   constexpr int NT = S::NT, NG = S::NG, WV = S::WV;
   using E = ET<__bf16>;
@@ -372,7 +374,9 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stac
   extern __shared__ f32x4 vec4[];
   float* vec = (float*)vec4;
   const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, hi = lane >> 5, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int tile = blockIdx.x, row = tile * 32 + j, NC = p.f / 32;
+  StackBwd p = p0;
+  if ((int)blockIdx.x >= tiles0) p = p1;
+  const int tile = (int)blockIdx.x - ((int)blockIdx.x >= tiles0 ? tiles0 : 0), row = tile * 32 + j, NC = p.f / 32;
   const bool in = row < p.rows, own = wave < NT;
   const int ft = wave % NT;
   const int oG1 = 0, oG2 = D, oS2 = 2 * D, oB1 = 3 * D;
@@ -510,21 +514,25 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stac
   }
 }
 
-void bw_stack_fwd_32(const StackFwd& p, hipStream_t st);
-void bw_stack_bwd_32(const StackBwd& p, hipStream_t st);
-void bw_stack_fwd_64(const StackFwd& p, hipStream_t st);
-void bw_stack_bwd_64(const StackBwd& p, hipStream_t st);
-void bw_stack_fwd_128(const StackFwd& p, hipStream_t st);
-void bw_stack_bwd_128(const StackBwd& p, hipStream_t st);
-void bw_stack_fwd_256(const StackFwd& p, hipStream_t st);
-void bw_stack_bwd_256(const StackBwd& p, hipStream_t st);
+void bw_stack_fwd_32(const StackFwd& p, const StackFwd& k, hipStream_t st);
+void bw_stack_bwd_32(const StackBwd& p, const StackBwd& k, hipStream_t st);
+void bw_stack_fwd_64(const StackFwd& p, const StackFwd& k, hipStream_t st);
+void bw_stack_bwd_64(const StackBwd& p, const StackBwd& k, hipStream_t st);
+void bw_stack_fwd_128(const StackFwd& p, const StackFwd& k, hipStream_t st);
+void bw_stack_bwd_128(const StackBwd& p, const StackBwd& k, hipStream_t st);
+void bw_stack_fwd_256(const StackFwd& p, const StackFwd& k, hipStream_t st);
+void bw_stack_bwd_256(const StackBwd& p, const StackBwd& k, hipStream_t st);
+// k: the cross layer's key rows, beside its query rows in one launch (no rows: none).  Two launches of their own in either direction
+// were each the chain of a tile on a part of the chip.
 template <int D>
-inline void bw_stack_fwd_d(const StackFwd& p, hipStream_t st) {
-  bw_stack_fwd_kernel<D><<<(p.rows + 31) / 32, 64 * stack_waves(D), (size_t)stack_vec_floats(D, p.f) * 4, st>>>(p);
+inline void bw_stack_fwd_d(const StackFwd& p, const StackFwd& k, hipStream_t st) {
+  const int t0 = (p.rows + 31) / 32, t1 = (k.rows + 31) / 32;
+  bw_stack_fwd_kernel<D><<<t0 + t1, 64 * stack_waves(D), (size_t)stack_vec_floats(D, p.f) * 4, st>>>(p, k, t0);
 }
 template <int D>
-inline void bw_stack_bwd_d(const StackBwd& p, hipStream_t st) {
-  bw_stack_bwd_kernel<D><<<(p.rows + 31) / 32, 64 * stack_waves(D), (size_t)stack_vec_floats(D, p.f) * 4, st>>>(p);
+inline void bw_stack_bwd_d(const StackBwd& p, const StackBwd& k, hipStream_t st) {
+  const int t0 = (p.rows + 31) / 32, t1 = (k.rows + 31) / 32;
+  bw_stack_bwd_kernel<D><<<t0 + t1, 64 * stack_waves(D), (size_t)stack_vec_floats(D, p.f) * 4, st>>>(p, k, t0);
 }
 
 }  // namespace bw

@@ -1,6 +1,6 @@
 // instantiations of the reduced stack's training kernels at width 256
 #include "bw_stack.h"
 namespace longer { namespace bw {
-void bw_stack_fwd_256(const StackFwd& p, hipStream_t st) { bw_stack_fwd_d<256>(p, st); }
-void bw_stack_bwd_256(const StackBwd& p, hipStream_t st) { bw_stack_bwd_d<256>(p, st); }
+void bw_stack_fwd_256(const StackFwd& p, const StackFwd& k, hipStream_t st) { bw_stack_fwd_d<256>(p, k, st); }
+void bw_stack_bwd_256(const StackBwd& p, const StackBwd& k, hipStream_t st) { bw_stack_bwd_d<256>(p, k, st); }
 } }

@@ -1314,6 +1314,13 @@ int longer_probe_mfma_layout(int32_t* out, void* stream) {
 }  // extern "C"
 
 namespace longer {
+// the workspace a forward pass cannot do without (longer_workspace_bytes: with room for its few-tiles plan)
+__attribute__((visibility("hidden"))) size_t least_workspace_bytes(const longer_config* cfg, int B, int L) {
+  Shape s;
+  if (check_cfg(cfg, &s, cfg && cfg->inner_layers > 0, true) || B <= 0 || L <= 0) return 0;
+  return make_layout(cfg, s, B, L).total;
+}
+
 // For the backward pass (backward.hip): the output rows of the first `layers` InnerTrans blocks as fp32,
 // Z [B, T, K, w] (the fp32 residual stream of the fused kernel, zeros for padded tokens): the input rows
 // of block `layers`, recomputed by the forward kernel.
