@@ -11,12 +11,14 @@
 // What bounds it: the exponentials and the score arithmetic around them (about 60 vector instructions per
 // 32 x 32 scores against 4-6 matrix instructions, half empty at head width 16).  Row-per-thread loops over LDS rows, the
 // kernels before these, were chains of dependent LDS reads: forward / query side / key side at the headline batch
-// (256 users, 108 queries, 258 keys in the cross layer and 108 in three self layers) 276 / 322 / 336 us, now 89 / 166 / 121.
+// (256 users, 108 queries, 258 keys in the cross layer and 108 in three self layers) 276 / 322 / 336 us, now 94 / 138 / 122.
 #pragma once
 #include "bw_common.h"
 
 namespace longer {
 namespace bw {
+
+using longer::settle;
 
 // Every row carries a descriptor of its token: -1 invalid, a for global token a, kSeq + t for the sequence token
 // with merged index t (a learnable query token stands after the newest one).
@@ -31,15 +33,17 @@ struct SetAttn {
   int nq, nk, B, heads, gmask;
 };
 
-// Eq. 8 on descriptors, as one comparison: a key with order `ks` is visible to a query with limits (smax, gmax) iff
-// ks <= (ks > 0 ? smax : gmax).  Sequence keys have their descriptor as order (> 0), global key a has -a,
-// an invalid key stands above every limit.  A sequence query sees the sequence keys up to its own token and no
-// global; a global query sees every sequence key and the globals of its set (causal: those with index >= its own).
-constexpr int kNever = 0x7fffffff, kNothing = -0x7fffffff;
-__device__ __forceinline__ int key_order(int kd) { return kd >= kSeq ? kd : (kd >= 0 ? -kd : kNever); }
-__device__ __forceinline__ int query_smax(int qd) { return qd >= kSeq ? qd : (qd >= 0 ? kNever - 1 : kNothing); }
-__device__ __forceinline__ int query_gmax(int qd, int gmask) {
-  return (qd < 0 || qd >= kSeq) ? kNothing : (gmask == LONGER_GMASK_FULL ? 0 : -qd);
+// Eq. 8 on descriptors: a key stands at a position (global token a at a - kSeq, sequence token t at t, an invalid one behind
+// everything) and a query sees one interval of them, so that a key is tested by a subtraction and an unsigned comparison, and by the
+// comparison alone where no global query is about (its interval starts at 0).  A sequence query sees the sequence keys up to its own
+// token and no global; a global query sees every sequence key and the globals of its set (causal: those with index >= its own).
+constexpr int kNone = 0x7fffffff - kSeq;
+__device__ __forceinline__ int key_position(int kd) { return kd >= 0 ? kd - kSeq : kNone; }
+struct Seen { int lo, end; };              // positions lo .. end - 1 (no query: none)
+__device__ __forceinline__ Seen query_sees(int qd, int gmask) {
+  if (qd < 0) return {0, 0};
+  if (qd >= kSeq) return {0, qd - kSeq + 1};
+  return {gmask == LONGER_GMASK_FULL ? -kSeq : qd - kSeq, kNone};
 }
 
 // Workgroup -> (user, head, 128 rows).  Workgroups go to the 8 accelerator dies round-robin, each with its own L2; a head's
@@ -52,6 +56,8 @@ __device__ __forceinline__ bool attn_task(const SetAttn& a, int rounds, int* u, 
   *h = in / rounds; *rd = in - *h * rounds;
   return *u < a.B;
 }
+
+__device__ __forceinline__ void settle(f32x16& a, f32x16& b) { asm volatile("s_nop 10" : "+v"(a), "+v"(b)); }      // (device.h, for two)
 
 // v, or zeros.  (Requests go out unconditionally, for a row that exists, and what is not wanted is dropped afterwards: under a
 // condition each request of a workgroup's start came to wait for the one before: training step of the headline batch 4333 against
@@ -143,11 +149,11 @@ struct StagedRows {
   }
 };
 
-// Keys of a workgroup's (user, head) staged in LDS with their orders and each 32-key tile's smallest and largest order.
+// Keys of a workgroup's (user, head) staged in LDS with their positions and each 32-key tile's smallest and largest one.
 template <int DH>
 struct KeyTiles {
   __bf16 k[kAttnChunk * DH], v[kAttnChunk * DH];
-  int order[kAttnChunk], least[kAttnChunk / 32], most[kAttnChunk / 32];
+  int pos[kAttnChunk], least[kAttnChunk / 32], most[kAttnChunk / 32];
 };
 template <int DH>
 __device__ __forceinline__ void stage_keys(KeyTiles<DH>& t, const SetAttn& a, int u, int h, int c0, int n) {
@@ -164,32 +170,38 @@ __device__ __forceinline__ void stage_keys(KeyTiles<DH>& t, const SetAttn& a, in
   v.put(t.v, n);
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
-    const int kt = wave + 4 * i, j = kt * 32 + l32, ks = j < n ? key_order(desc[i]) : kNever;
+    const int kt = wave + 4 * i, j = kt * 32 + l32, ks = j < n ? key_position(desc[i]) : kNone;
     if (kt * 32 >= n) continue;
     int lo = ks, up = ks;
 #pragma unroll
     for (int o = 16; o > 0; o >>= 1) { lo = min(lo, __shfl_xor(lo, o, 64)); up = max(up, __shfl_xor(up, o, 64)); }
-    if (lane < 32) t.order[j] = ks;
+    if (lane < 32) t.pos[j] = ks;
     if (lane == 0) { t.least[kt] = lo; t.most[kt] = up; }
   }
 }
 // Does any lane's query see a key of tile kt (`none` otherwise), and must single keys be tested?  (A lane without a
 // query sees nothing and wants nothing tested: what it computes is dropped.)
 template <int DH>
-__device__ __forceinline__ void tile_visibility(const KeyTiles<DH>& t, int kt, bool live, int smax, bool* none, bool* test) {
+__device__ __forceinline__ void tile_visibility(const KeyTiles<DH>& t, int kt, bool live, const Seen& see, bool* none, bool* test) {
   const int lo = t.least[kt], up = t.most[kt];
-  *none = lo > 0 && __builtin_amdgcn_ballot_w64(live && lo <= smax) == 0;
-  *test = lo <= 0 || __builtin_amdgcn_ballot_w64(live && up > smax) != 0;
+  *none = __builtin_amdgcn_ballot_w64(live && lo < see.end && up >= see.lo) == 0;
+  *test = __builtin_amdgcn_ballot_w64(live && (lo < see.lo || up >= see.end)) != 0;
 }
-// scores of keys the lane's query does not see become -infinity
+// scores of keys the lane's query does not see become -infinity; plain: no lane's interval starts elsewhere than at 0
 template <int DH>
-__device__ __forceinline__ void mask_scores(f32x16& s, const KeyTiles<DH>& t, int kt, int smax, int gmax, int hi) {
+__device__ __forceinline__ void mask_scores(f32x16& s, const KeyTiles<DH>& t, int kt, const Seen& see, bool plain, int hi) {
   typedef int i32x4 __attribute__((ext_vector_type(4)));
+  const unsigned width = (unsigned)(see.end - see.lo);
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const i32x4 ks = *(const i32x4*)(t.order + 32 * kt + 8 * q + 4 * hi);
+    const i32x4 ks = *(const i32x4*)(t.pos + 32 * kt + 8 * q + 4 * hi);
+    if (plain) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) s[4 * q + e] = ks[e] <= (ks[e] > 0 ? smax : gmax) ? s[4 * q + e] : -__builtin_inff();
+      for (int e = 0; e < 4; ++e) s[4 * q + e] = (unsigned)ks[e] < width ? s[4 * q + e] : -__builtin_inff();
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[4 * q + e] = (unsigned)(ks[e] - see.lo) < width ? s[4 * q + e] : -__builtin_inff();
+    }
   }
 }
 
@@ -209,7 +221,8 @@ __global__ __launch_bounds__(256) void bw_set_attn_fwd_kernel(SetAttn a, __bf16*
   if (i >= a.nq) qd = -1;
   const bool live = qd >= 0;
   q.keep(live);
-  const int smax = query_smax(qd), gmax = query_gmax(qd, a.gmask);
+  const Seen see = query_sees(qd, a.gmask);
+  const bool plain = __builtin_amdgcn_ballot_w64(see.lo != 0) == 0;
   const float c = 1.4426950408889634f * rsqrtf((float)DH);
   f32x16 acc;
 #pragma unroll
@@ -223,10 +236,11 @@ __global__ __launch_bounds__(256) void bw_set_attn_fwd_kernel(SetAttn a, __bf16*
     if (i0 >= a.nq) continue;
     for (int kt = 0; kt * 32 < n; ++kt) {
       bool none, test;
-      tile_visibility<DH>(t, kt, live, smax, &none, &test);
+      tile_visibility<DH>(t, kt, live, see, &none, &test);
       if (none) continue;
       f32x16 s = rows_times<DH>(t.k, 32 * kt, q, l32, hi);
-      if (test) mask_scores<DH>(s, t, kt, smax, gmax, hi);
+      settle(s);                                       // (a branch follows: device.h)
+      if (test) mask_scores<DH>(s, t, kt, see, plain, hi);
       float mt = s[0];
 #pragma unroll
       for (int r = 1; r < 16; ++r) mt = fmaxf(mt, s[r]);
@@ -241,6 +255,7 @@ __global__ __launch_bounds__(256) void bw_set_attn_fwd_kernel(SetAttn a, __bf16*
     }
   }
   l = sum_halves(l);
+  settle(acc);
   if (i >= a.nq) return;
   const bool any = live && l > 0.f;
   store_row<DH>(o + row * d + h * DH, acc, any ? 1.f / l : 0.f, hi);
@@ -248,9 +263,13 @@ __global__ __launch_bounds__(256) void bw_set_attn_fwd_kernel(SetAttn a, __bf16*
 }
 
 // Query side of the gradient: P_ij = exp2(c s_ij - lse_i), dP_ij = do_i . v_j, D_i = sum_j P_ij dP_ij (to stat[].y),
-// dq_i = sum_j P_ij (dP_ij - D_i) k_j / sqrt(DH).  Two passes over the keys: D first.
-template <int DH>
-__global__ __launch_bounds__(256) void bw_set_attn_bwd_q_kernel(SetAttn a, const __bf16* __restrict__ dob, int d,
+// dq_i = sum_j P_ij (dP_ij - D_i) k_j / sqrt(DH).  Two passes over the keys: D first.  HELD: at most kHeldTiles key tiles (a
+// self layer's), whose P and dP stay in registers for the second pass, 128 of them beside the 38 that the rest takes, so that two or
+// three waves still share a SIMD: all query sides of the headline, small and raw-inputs models' steps 229 us with scores and
+// exponentials formed twice, 193 so.
+constexpr int kHeldTiles = 4;
+template <int DH, bool HELD>
+__global__ __launch_bounds__(256, HELD ? 2 : 1) void bw_set_attn_bwd_q_kernel(SetAttn a, const __bf16* __restrict__ dob, int d,
                                                                 __bf16* __restrict__ dq, int dqpitch, float2* __restrict__ stat) {
   __shared__ __attribute__((aligned(16))) KeyTiles<DH> t;
   const int rounds = (a.nq + kAttnRows - 1) / kAttnRows;
@@ -265,13 +284,44 @@ __global__ __launch_bounds__(256) void bw_set_attn_bwd_q_kernel(SetAttn a, const
   if (i >= a.nq) { qd = -1; lse = __builtin_inff(); }
   const bool live = qd >= 0;
   q.keep(live); g.keep(live);
-  const int smax = query_smax(qd), gmax = query_gmax(qd, a.gmask);
+  const Seen see = query_sees(qd, a.gmask);
+  const bool plain = __builtin_amdgcn_ballot_w64(see.lo != 0) == 0;
   const float scale = rsqrtf((float)DH), c = 1.4426950408889634f * scale;
   f32x16 acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
   float D = 0.f;
-  for (int pass = 0; pass < 2; ++pass) {
+  if constexpr (HELD) {
+    stage_keys<DH>(t, a, u, h, 0, a.nk);
+    __syncthreads();
+    if (i0 >= a.nq) return;
+    f32x16 P[kHeldTiles], dP[kHeldTiles];
+    bool skip[kHeldTiles];
+#pragma unroll
+    for (int kt = 0; kt < kHeldTiles; ++kt) {
+      skip[kt] = true;
+      if (kt * 32 >= a.nk) continue;
+      bool none, test;
+      tile_visibility<DH>(t, kt, live, see, &none, &test);
+      if (none) continue;
+      skip[kt] = false;
+      P[kt] = rows_times<DH>(t.k, 32 * kt, q, l32, hi);
+      dP[kt] = rows_times<DH>(t.v, 32 * kt, g, l32, hi);
+      settle(P[kt], dP[kt]);
+      if (test) mask_scores<DH>(P[kt], t, kt, see, plain, hi);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { P[kt][r] = __builtin_amdgcn_exp2f(fmaf(P[kt][r], c, -lse)); D = fmaf(P[kt][r], dP[kt][r], D); }
+    }
+    D = sum_halves(D);
+#pragma unroll
+    for (int kt = 0; kt < kHeldTiles; ++kt) {
+      if (skip[kt]) continue;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) P[kt][r] *= dP[kt][r] - D;
+      add_transposed<DH>(acc, t.k, 32 * kt, P[kt], lane);
+    }
+  }
+  for (int pass = HELD ? 2 : 0; pass < 2; ++pass) {
     for (int c0 = 0; c0 < a.nk; c0 += kAttnChunk) {
       const int n = min(kAttnChunk, a.nk - c0);
       if (pass == 0 || a.nk > kAttnChunk) {       // (a single chunk stays for the second pass)
@@ -282,11 +332,12 @@ __global__ __launch_bounds__(256) void bw_set_attn_bwd_q_kernel(SetAttn a, const
       if (i0 >= a.nq) continue;
       for (int kt = 0; kt * 32 < n; ++kt) {
         bool none, test;
-        tile_visibility<DH>(t, kt, live, smax, &none, &test);
+        tile_visibility<DH>(t, kt, live, see, &none, &test);
         if (none) continue;
         f32x16 s = rows_times<DH>(t.k, 32 * kt, q, l32, hi);
-        const f32x16 dp = rows_times<DH>(t.v, 32 * kt, g, l32, hi);
-        if (test) mask_scores<DH>(s, t, kt, smax, gmax, hi);
+        f32x16 dp = rows_times<DH>(t.v, 32 * kt, g, l32, hi);
+        settle(s, dp);
+        if (test) mask_scores<DH>(s, t, kt, see, plain, hi);
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c, -lse));
         if (pass == 0) {
@@ -301,6 +352,7 @@ __global__ __launch_bounds__(256) void bw_set_attn_bwd_q_kernel(SetAttn a, const
     }
     if (pass == 0) D = sum_halves(D);
   }
+  settle(acc);
   if (i >= a.nq) return;
   store_row<DH>(dq + row * dqpitch + h * DH, acc, live ? scale : 0.f, hi);
   if (hi == 0) stat[row * a.heads + h].y = live ? D : 0.f;
@@ -315,8 +367,8 @@ __global__ __launch_bounds__(256) void bw_set_attn_bwd_kv_kernel(SetAttn a, cons
   __shared__ __attribute__((aligned(16))) struct {
     __bf16 q[CH * DH], g[CH * DH];
     float lse[CH], D[CH];
-    int smax[CH], gmax[CH];
-    int least[CH / 32], most[CH / 32], gmost[CH / 32];      // per 32-row tile: limits of its queries
+    int lo[CH], width[CH];
+    int least[CH / 32], most[CH / 32], start[CH / 32], end[CH / 32];      // per 32-row tile: positions that some query sees, that all see
   } t;
   typedef int i32x4 __attribute__((ext_vector_type(4)));
   const int rounds = (a.nk + kAttnRows - 1) / kAttnRows;
@@ -327,8 +379,8 @@ __global__ __launch_bounds__(256) void bw_set_attn_bwd_kv_kernel(SetAttn a, cons
   const size_t row = (size_t)u * a.nk + (j < a.nk ? j : 0);
   const int kd = a.kdesc[row];
   RowFrag<DH> kf = row_frag<DH>(a.k + row * a.kvpitch + h * DH, true, hi), vf = row_frag<DH>(a.v + row * a.kvpitch + h * DH, true, hi);
-  const int ks = j < a.nk ? key_order(kd) : kNever;
-  const bool live = ks != kNever;
+  const int ks = j < a.nk ? key_position(kd) : kNone;
+  const bool live = ks != kNone;
   kf.keep(live); vf.keep(live);
   const float scale = rsqrtf((float)DH), c = 1.4426950408889634f * scale;
   f32x16 gk, gv;
@@ -351,30 +403,46 @@ __global__ __launch_bounds__(256) void bw_set_attn_bwd_kv_kernel(SetAttn a, cons
       if (i >= n) qd = -1;
       // a row without a query: log-sum-exp +infinity, so that its probabilities are exact zeros untested
       if (qd < 0) st = make_float2(__builtin_inff(), 0.f);
-      const int sm = query_smax(qd), gm = query_gmax(qd, a.gmask);
-      int lo = qd >= 0 ? sm : kNever, up = sm, gu = gm;
+      const Seen see = query_sees(qd, a.gmask);
+      const bool is = qd >= 0;
+      int lo = is ? see.lo : kNone, up = is ? see.end : -kSeq, from = is ? see.lo : -kSeq, to = is ? see.end : kNone;
 #pragma unroll
       for (int o = 16; o > 0; o >>= 1) {
-        lo = min(lo, __shfl_xor(lo, o, 64)); up = max(up, __shfl_xor(up, o, 64)); gu = max(gu, __shfl_xor(gu, o, 64));
+        lo = min(lo, __shfl_xor(lo, o, 64)); up = max(up, __shfl_xor(up, o, 64));
+        from = max(from, __shfl_xor(from, o, 64)); to = min(to, __shfl_xor(to, o, 64));
       }
-      if (lane < 32) { t.lse[i] = st.x; t.D[i] = st.y; t.smax[i] = sm; t.gmax[i] = gm; }
-      if (lane == 0) { t.least[qt] = lo; t.most[qt] = up; t.gmost[qt] = gu; }
+      if (lane < 32) { t.lse[i] = st.x; t.D[i] = st.y; t.lo[i] = see.lo; t.width[i] = see.end - see.lo; }
+      if (lane == 0) { t.least[qt] = lo; t.most[qt] = up; t.start[qt] = from; t.end[qt] = to; }
     }
     __syncthreads();
     if (j0 >= a.nk) continue;
     for (int qt = 0; qt * 32 < n; ++qt) {
-      if (__builtin_amdgcn_ballot_w64(live && ks <= (ks > 0 ? t.most[qt] : t.gmost[qt])) == 0) continue;     // seen by no query
-      const bool test = __builtin_amdgcn_ballot_w64(live && (ks <= 0 || ks > t.least[qt])) != 0;
+      const int first = __builtin_amdgcn_readfirstlane(t.least[qt]);
+      if (__builtin_amdgcn_ballot_w64(live && ks >= first && ks < t.most[qt]) == 0) continue;     // seen by no query
+      const bool test = __builtin_amdgcn_ballot_w64(live && (ks < t.start[qt] || ks >= t.end[qt])) != 0;
       f32x16 p = rows_times<DH>(t.q, 32 * qt, kf, l32, hi);
       f32x16 ds = rows_times<DH>(t.g, 32 * qt, vf, l32, hi);
+      settle(p, ds);
+      if (test) {
+        if (first >= 0) {                            // (every interval starts at 0)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4) {
+            const i32x4 width = *(const i32x4*)(t.width + 32 * qt + 8 * q4 + 4 * hi);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[4 * q4 + e] = (unsigned)ks < (unsigned)width[e] ? p[4 * q4 + e] : -__builtin_inff();
+          }
+        } else {
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4) {
+            const i32x4 width = *(const i32x4*)(t.width + 32 * qt + 8 * q4 + 4 * hi), lo = *(const i32x4*)(t.lo + 32 * qt + 8 * q4 + 4 * hi);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[4 * q4 + e] = (unsigned)(ks - lo[e]) < (unsigned)width[e] ? p[4 * q4 + e] : -__builtin_inff();
+          }
+        }
+      }
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
         const f32x4 lse = *(const f32x4*)(t.lse + 32 * qt + 8 * q4 + 4 * hi), D = *(const f32x4*)(t.D + 32 * qt + 8 * q4 + 4 * hi);
-        if (test) {
-          const i32x4 sm = *(const i32x4*)(t.smax + 32 * qt + 8 * q4 + 4 * hi), gm = *(const i32x4*)(t.gmax + 32 * qt + 8 * q4 + 4 * hi);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) p[4 * q4 + e] = ks <= (ks > 0 ? sm[e] : gm[e]) ? p[4 * q4 + e] : -__builtin_inff();
-        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           p[4 * q4 + e] = __builtin_amdgcn_exp2f(fmaf(p[4 * q4 + e], c, -lse[e]));
@@ -385,6 +453,7 @@ __global__ __launch_bounds__(256) void bw_set_attn_bwd_kv_kernel(SetAttn a, cons
       add_transposed<DH>(gk, t.q, 32 * qt, ds, lane);
     }
   }
+  settle(gk, gv);
   if (j >= a.nk) return;
   store_row<DH>(dk + row * dkvpitch + h * DH, gk, live ? scale : 0.f, hi);
   store_row<DH>(dv + row * dkvpitch + h * DH, gv, live ? 1.f : 0.f, hi);
@@ -397,7 +466,10 @@ static void set_attn_launch(hipStream_t st, int which, const SetAttn& a, const _
   const unsigned uh = (unsigned)((a.B + 7) / 8 * 8 * a.heads);      // (see attn_task)
   const unsigned gq = uh * ((a.nq + kAttnRows - 1) / kAttnRows), gk = uh * ((a.nk + kAttnRows - 1) / kAttnRows);
   if (which == 0) bw_set_attn_fwd_kernel<DH><<<gq, 256, 0, st>>>(a, o_or_dq, d, stat);
-  else if (which == 1) bw_set_attn_bwd_q_kernel<DH><<<gq, 256, 0, st>>>(a, dob, d, o_or_dq, pitch, stat);
+  else if (which == 1) {
+    if (a.nk <= 32 * kHeldTiles) bw_set_attn_bwd_q_kernel<DH, true><<<gq, 256, 0, st>>>(a, dob, d, o_or_dq, pitch, stat);
+    else bw_set_attn_bwd_q_kernel<DH, false><<<gq, 256, 0, st>>>(a, dob, d, o_or_dq, pitch, stat);
+  }
   else bw_set_attn_bwd_kv_kernel<DH><<<gk, 256, 0, st>>>(a, dob, d, dk, dv, pitch, stat);
 }
 

@@ -66,3 +66,16 @@ def test_stack_with_any_number_of_hidden_chunks(d, heads, ffn):
     cfg = synth.CONFIGS["C2"].replace(d=d, heads=heads, inner_heads=heads, B=3, L=90, m=2, k_recent=9, n_self=2, ffn_mult=ffn, ragged=True,
                                       len_lo=20, len_hi=90, index=67)
     _compare_model("width %d, %d hidden features" % (d, d * ffn), synth.make_case(cfg))
+
+
+# The stack's attention where a self layer's keys stay in registers and where they do not (four key tiles and one key more), with one to
+# four key tiles, rows of the last one missing; every mask: global rows alone in a tile, beside sequence rows, causal ones; users without
+# a token; sampled and learnable slots
+@pytest.mark.parametrize("d,heads,m,k,extra", [(64, 4, 8, 120, {}), (64, 4, 8, 121, dict(gmask="causal")), (128, 4, 32, 33, dict(gmask="causal")),
+                                               (64, 2, 4, 28, dict(k_uniform=9)), (32, 2, 16, 70, dict(q_learnable=True, gmask="causal"))])
+def test_set_attention_key_tiles_and_masks(d, heads, m, k, extra):
+    cfg = synth.CONFIGS["C2"].replace(d=d, heads=heads, inner_heads=heads, B=4, L=700, K=4, m=m, k_recent=k, n_self=2, ragged=True, len_lo=0, len_hi=700,
+                                      index=109, **extra)
+    case = synth.make_case(cfg)
+    case["lens"][:3] = [700, 0, 50]
+    _compare_model("width %d, %d + %d rows" % (d, m, k), case)
