@@ -4,6 +4,7 @@
 #include "pair_kernel.h"
 #include "user_kernel.h"
 #include "few_f32_kernel.h"
+#include "kv_kernel.h"
 
 #include <algorithm>
 #include <cmath>
@@ -702,7 +703,9 @@ static int run_layer(const longer_config* c, const Shape& s, const char* packed_
     p.key_self = io.key_self;
     const int grid = cdiv((long long)B * p.tiles_per_user, kWaves);
     StageScope scope(ST_KVPROJ, st);
-    if (s.main_fn(MODE_KVPROJ, 1, 16, p, dim3(grid), st)) return fail(LONGER_ERR_HIP, "kv projection launch failed");
+    if (s.user && (long long)B * p.tiles_per_user < (1LL << 30)) {
+      if (launch_kv(s.D, p, B * p.tiles_per_user, st)) return fail(LONGER_ERR_HIP, "kv projection launch failed");
+    } else if (s.main_fn(MODE_KVPROJ, 1, 16, p, dim3(grid), st)) return fail(LONGER_ERR_HIP, "kv projection launch failed");
   }
   if (!do_attn) return 0;
   BlockParams p = base_params(c, s, lens, B, L, s.DH);

@@ -241,3 +241,31 @@ def test_stack_layer_by_layer_and_in_one_launch(d, heads, m, k, n_self, extra):
             for c in range(copies):
                 _check("copy %d Y" % c, got[5 * c:5 * c + 5], ref, TOL["bf16"])
                 assert np.abs(got_lo[5 * c:5 * c + 5] - ref_lo).max() < lo_bar
+
+
+# K and V of one attention layer where a workgroup goes through several tiles (more than 512 of them at width 128, 256 at width 256): users whose
+# key tiles are all needed, one, and none, the last tile with rows missing, tiles with and without global rows; rows in bf16 as this entry
+# point takes them, and (the forward pass) in fp32
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,heads,m,B,T", [(128, 8, 8, 75, 250), (128, 4, 32, 130, 97), (256, 8, 8, 40, 250), (256, 16, 1, 90, 95)])
+def test_key_value_projection_of_many_tiles(d, heads, m, B, T):
+    import numpy as np
+    import longer_synth as synth
+    from oracle import longer_oracle as orc
+    from gpu_util import Runner
+    from test_gpu_parity import TOL, _check
+    cfg = synth.CONFIGS["C2"].replace(B=5, L=4 * T - 3, K=4, d=d, heads=heads, inner_heads=heads, m=m, k_recent=3, n_self=0, ragged=True, len_lo=0,
+                                      len_hi=4 * T - 3, index=113)
+    case = synth.make_case(cfg)
+    case["lens"][:4] = [4 * T - 3, 0, 9, 2 * T]
+    ref, _ = orc.forward(cfg, case["weights"], case["H"], case["G"], case["lens"])
+    big = cfg.replace(B=B)
+    many = dict(case, cfg=big, **{n: np.concatenate([case[n]] * (B // 5)) for n in ("H", "G", "lens")})
+    Y, _ = Runner(many).forward()
+    for c in range(B // 5):
+        _check("copy %d" % c, Y[5 * c:5 * c + 5], ref, TOL["bf16"])
+    M = synth.round_bf16(np.random.default_rng(7).standard_normal((5, T, d)).astype(np.float32))
+    ref = orc.hybrid_cross_attn(cfg, case["weights"]["cross"], case["G"], M, case["lens"], L=cfg.L)
+    X = Runner(many).cross(np.concatenate([case["G"]] * (B // 5)), np.concatenate([M] * (B // 5)))
+    for c in range(B // 5):
+        _check("copy %d, bf16 rows" % c, X[5 * c:5 * c + 5], ref, TOL["bf16"])
