@@ -1222,7 +1222,8 @@ __global__ __launch_bounds__(256) void bw_pack_kernel(const PackJobs a, const Pr
 //   dW = diag(g) X + s c^T,   dg[e] = sum_c W[e][c] X[e][c],   ds[e] = sum_c W[e][c] c[c],
 // so the LayerNorm gradients need no pass over the tokens.  One workgroup per row e and LayerNorm.
 constexpr int kNormBlocks = 16;           // blocks per launch
-struct NormGrads { struct { const __bf16 *w[3], *gain, *shift; float *dw, *dgain; int d, f; } n[2 * kNormBlocks]; };
+struct NormJob { const __bf16 *w[3], *gain, *shift; float *dw, *dgain; int d, f; };
+struct NormGrads { NormJob n[2 * kNormBlocks]; };
 __global__ __launch_bounds__(256) void bw_norm_grads_kernel(const NormGrads a) {
   const auto& q = a.n[blockIdx.y];
   const int which = blockIdx.y & 1, e = blockIdx.x, d = q.d, n = which ? q.f : d, mats = which ? 1 : 3;     // ln1: Q, K, V; ln2: W1
@@ -1340,36 +1341,46 @@ struct PackBatch {
     return rc;
   }
 };
-// LayerNorm gradients and dW = diag(g) X + s c^T of whole blocks (bw_norm_grads_kernel), of one or several widths
-struct NormBatch {
-  NormGrads a = {};
-  int n = 0, width = 0, rc = 0; hipStream_t st;
-  NormBatch(hipStream_t st_) : st(st_) {}
-  void add(int d, int f, const longer_block* blocks, int count, float* g0, size_t stride) {      // grads of block i at g0 + i stride
+// Sums over partial results that wait for the next such launch (the results keep a place of their own), and the blocks whose LayerNorm
+// gradients and dW = diag(g) X + s c^T (bw_norm_grads_kernel; blocks of one or several widths) are made of sums.  Nothing of the second
+// part is launched but by finish(), behind all sums: with launches as they filled up, a model of sixteen self layers had
+// its LayerNorm gradients taken ahead of the sums.
+constexpr int kMaxBlocks = 64;            // (at most 32 InnerTrans blocks, 31 of the stack)
+struct GradTail {
+  ReduceBatch sums;
+  NormJob norm[2 * kMaxBlocks];
+  int blocks = 0; hipStream_t st;
+  GradTail(hipStream_t st_) : st(st_) {}
+  int add(int d, int f, const longer_block* blk, int count, float* g0, size_t stride) {      // grads of block i at g0 + i stride
     const GradLayout gl = grad_layout(d, f);
-    for (int i = 0; i < count; ++i) {
-      if (n == kNormBlocks) flush();
-      const longer_block& b = blocks[i];
+    if (blocks + count > kMaxBlocks) return api_error(LONGER_ERR_ARG, "more than %d blocks", kMaxBlocks);
+    for (int i = 0; i < count; ++i, ++blocks) {
+      const longer_block& b = blk[i];
       float* g = g0 + (size_t)i * stride;
-      a.n[2 * n] = {{(const __bf16*)b.wq, (const __bf16*)b.wk, (const __bf16*)b.wv}, (const __bf16*)b.ln1_g, (const __bf16*)b.ln1_b, g + gl.wq, g + gl.ln1_g, d, f};
-      a.n[2 * n + 1] = {{(const __bf16*)b.w1, nullptr, nullptr}, (const __bf16*)b.ln2_g, (const __bf16*)b.ln2_b, g + gl.w1, g + gl.ln2_g, d, f};
-      ++n;
-      width = d > width ? d : width;
+      norm[2 * blocks] = {{(const __bf16*)b.wq, (const __bf16*)b.wk, (const __bf16*)b.wv}, (const __bf16*)b.ln1_g, (const __bf16*)b.ln1_b, g + gl.wq, g + gl.ln1_g, d, f};
+      norm[2 * blocks + 1] = {{(const __bf16*)b.w1, nullptr, nullptr}, (const __bf16*)b.ln2_g, (const __bf16*)b.ln2_b, g + gl.w1, g + gl.ln2_g, d, f};
     }
+    return 0;
   }
-  int flush() {
-    if (n && !rc) {
+  int sum() {
+    if (!sums.a.njobs) return 0;
+    const int rc = launch(sums, st);
+    sums = ReduceBatch{};
+    return rc;
+  }
+  int finish() {
+    int rc = sum();
+    for (int first = 0; first < blocks && !rc; first += kNormBlocks) {
+      NormGrads a = {};
+      const int n = blocks - first < kNormBlocks ? blocks - first : kNormBlocks;
+      int width = 0;
+      for (int i = 0; i < 2 * n; ++i) { a.n[i] = norm[2 * first + i]; width = a.n[i].d > width ? a.n[i].d : width; }
       bw_norm_grads_kernel<<<dim3(width, 2 * n), 256, 0, st>>>(a);
       if (hipGetLastError() != hipSuccess) rc = api_error(LONGER_ERR_HIP, "LayerNorm gradient launch failed");
     }
-    n = width = 0;
+    blocks = 0;
     return rc;
   }
-};
-// Sums and LayerNorm gradients that wait for the next such launch (their partial results keep a place of their own)
-struct GradTail {
-  ReduceBatch sums; NormBatch norms;
-  GradTail(hipStream_t st) : norms(st) {}
 };
 
 static Workspace workspace(int layers, size_t ntok, int d, int f, int heads, size_t fwd_bytes, size_t ztmp_bytes) {
@@ -1622,21 +1633,17 @@ static int run_tiled(const longer_config* c, const longer_block* inner, const vo
     WgradBatch wg = block_wgrads_tiles(d, f, s.slots, rv, p.rec, g);
     BW_TRY(launch(wg, (float*)(ws + w.part), st));
     t.sums.add(wg);
-    BW_TRY(launch(t.sums, st));
-    t.sums = ReduceBatch{};
+    BW_TRY(t.sum());
   }
-  t.norms.add(d, f, inner, s.layers, grads, gl.total);
-  return t.norms.flush();
+  BW_TRY(t.add(d, f, inner, s.layers, grads, gl.total));
+  return t.finish();
 }
 
 static int run(const longer_config* c, const longer_block* inner, const void* H, const int32_t* lens, int B, int L,
                const float* dM, float* dH, float* grads, char* ws, hipStream_t st, const Dims& s, bool inputs_kept = false,
                GradTail* tail = nullptr) {
   if (s.tiled) return run_tiled(c, inner, H, lens, B, L, dM, dH, grads, ws, st, s, inputs_kept, tail);
-  if (tail) {
-    BW_TRY(launch(tail->sums, st));
-    BW_TRY(tail->norms.flush());
-  }
+  if (tail) BW_TRY(tail->finish());
   const int d = s.d, f = s.f;
   const size_t nt = s.ntok;
   const Workspace w = merge_workspace(c, s, B, L);
@@ -2012,8 +2019,8 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
   WgradBatch wg = stack_wgrads(s, w, ws, grads, mg.cross, mg.self0, mg.per_main);
   BW_TRY(launch(wg, (float*)(ws + w.part), st));
   tail.sums.add(wg);
-  tail.norms.add(d, f, wts->cross, 1, grads + mg.cross, mg.per_main);
-  if (s.layers > 1) tail.norms.add(d, f, wts->self, s.layers - 1, grads + mg.self0, mg.per_main);
+  BW_TRY(tail.add(d, f, wts->cross, 1, grads + mg.cross, mg.per_main));
+  if (s.layers > 1) BW_TRY(tail.add(d, f, wts->self, s.layers - 1, grads + mg.self0, mg.per_main));
   // ---- gradients of the stack's inputs: global tokens (query rows and key rows), merged tokens (key
   // rows, plus the query slots that hold them)
   bw_split_grad_kernel<<<flat_grid(rk * d / 4), 256, 0, st>>>(geo, d, dy, dR, dG, dM);

@@ -79,3 +79,12 @@ def test_set_attention_key_tiles_and_masks(d, heads, m, k, extra):
     case = synth.make_case(cfg)
     case["lens"][:3] = [700, 0, 50]
     _compare_model("width %d, %d + %d rows" % (d, m, k), case)
+
+
+# More blocks than one launch of the LayerNorm gradients takes (16): their gradients are made of the stack's sums over its rows, which a whole
+# step forms together with the merge's.  With a merge in tiles and one without (width 256)
+@pytest.mark.parametrize("d,heads,n_self,inner", [(64, 4, 15, 1), (64, 4, 16, 2), (32, 2, 30, 1), (256, 8, 16, 1), (64, 4, 14, 17)])
+def test_gradients_of_deep_models(d, heads, n_self, inner):
+    cfg = synth.CONFIGS["C2"].replace(d=d, heads=heads, inner_heads=heads, B=4, L=90, m=4, k_recent=9, n_self=n_self, inner_layers=inner,
+                                      ragged=True, len_lo=20, len_hi=90, index=127)
+    _compare_model("width %d, %d self layers, %d InnerTrans blocks" % (d, n_self, inner), synth.make_case(cfg))
