@@ -692,6 +692,16 @@ static bool layers_pay(const Shape& s, int B) {
   return s.quad && s.n > 64 && (long long)B * cdiv(s.n, 32) <= (s.D == 128 ? 512 : 256);
 }
 
+// K and V with the weights in registers (kv_kernel.h: its figures).  At width 128, ragged users of at most two key tiles in more than one round
+// of workgroups stay with the block kernel, whose workgroups the hardware deals out as they come: 512, 1500 and 5000 users of one key tile 6.6 /
+// 11.2 (one round), 14.3 / 14.4, 34.5 / 32.9 us with it / with the block kernel, of two 11.9 / 11.0, 22.7 / 22.4, 67.7 / 62.6; of three 14.0 / 14.1,
+// 27.1 / 30.1, 82.6 / 92.3.  (Width 256, one key tile: 12.9 / 17.9 for 512 users, 84 / 94 for 5000; two 21.8 / 20.8, 125 / 171.)
+static bool kv_in_registers(const Shape& s, const BlockParams& p) {
+  const long long tiles = (long long)p.B * p.tiles_per_user;
+  if (!s.user || tiles >= (1LL << 30)) return false;
+  return !(s.D == 128 && p.lens && !p.key_self && p.tiles_per_user <= 2 && tiles > kv_workgroups(s.D));
+}
+
 static int run_layer(const longer_config* c, const Shape& s, const char* packed_blk, const int32_t* lens, int B, int L,
                      const AttnIO& io, bool do_attn, hipStream_t st, bool have_kv = false) {
   if (!have_kv) {
@@ -703,8 +713,8 @@ static int run_layer(const longer_config* c, const Shape& s, const char* packed_
     p.key_self = io.key_self;
     const int grid = cdiv((long long)B * p.tiles_per_user, kWaves);
     StageScope scope(ST_KVPROJ, st);
-    if (s.user && (long long)B * p.tiles_per_user < (1LL << 30)) {
-      if (launch_kv(s.D, p, B * p.tiles_per_user, st)) return fail(LONGER_ERR_HIP, "kv projection launch failed");
+    if (kv_in_registers(s, p)) {
+      if (launch_kv(s.D, p, st)) return fail(LONGER_ERR_HIP, "kv projection launch failed");
     } else if (s.main_fn(MODE_KVPROJ, 1, 16, p, dim3(grid), st)) return fail(LONGER_ERR_HIP, "kv projection launch failed");
   }
   if (!do_attn) return 0;

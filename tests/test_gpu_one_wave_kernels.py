@@ -269,3 +269,54 @@ def test_key_value_projection_of_many_tiles(d, heads, m, B, T):
     X = Runner(many).cross(np.concatenate([case["G"]] * (B // 5)), np.concatenate([M] * (B // 5)))
     for c in range(B // 5):
         _check("copy %d, bf16 rows" % c, X[5 * c:5 * c + 5], ref, TOL["bf16"])
+
+
+# Users of different length, many tiles: which tiles are needed is dealt out evenly, whatever key tiles a user has (4, 7 and 16; dividing the
+# workgroups or not), with users of no token at the front, between others and at the end; more users than a workgroup has threads
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,heads,m,B,T", [(128, 8, 8, 600, 120), (128, 8, 1, 85, 223), (256, 8, 8, 40, 504), (256, 16, 32, 550, 40)])
+def test_key_value_projection_of_ragged_users(d, heads, m, B, T):
+    import numpy as np
+    import longer_synth as synth
+    from oracle import longer_oracle as orc
+    from gpu_util import Runner
+    from test_gpu_parity import TOL, _check
+    n = 10
+    cfg = synth.CONFIGS["C2"].replace(B=n, L=T, K=1, d=d, heads=heads, inner_heads=heads, m=m, k_recent=3, n_self=0, ragged=True, len_lo=0, len_hi=T, index=131)
+    case = synth.make_case(cfg)
+    case["lens"][:] = [0, 0, T, 1, T // 2, 32 - m % 32, 0, 33, T - 1, 0]
+    ref, _ = orc.forward(cfg, case["weights"], case["H"], case["G"], case["lens"])
+    pick = np.concatenate([np.arange(n), np.random.default_rng(3).integers(0, n, size=B - 2 * n), np.arange(n)])
+    many = dict(case, cfg=cfg.replace(B=B), **{k: case[k][pick] for k in ("H", "G", "lens")})
+    Y, _ = Runner(many).forward()
+    _check("all users", Y, ref[pick], TOL["bf16"])
+
+
+# ... and evenly enough: with half of the tiles needed the launch takes clearly less than with all of them (0.52 and 0.58 times as long at widths
+# 128 and 256; 0.71 and 0.92 where a workgroup met the same key tile of every user)
+@pytest.mark.gpu
+@pytest.mark.parametrize("d", [128, 256])
+def test_key_value_projection_of_ragged_users_is_balanced(d):
+    import numpy as np
+    import torch
+    import longer_synth as synth
+    import paper_2505_04421_amd as lg
+    B, T = 512, 504
+    cfg = synth.CONFIGS["C2"].replace(B=B, L=T, K=1, d=d, heads=8, inner_heads=8, m=8, k_recent=8, n_self=0, index=137)
+    model = lg.DeviceModel(cfg, synth.make_case(cfg.replace(B=1, L=4))["weights"])
+    weights = model.pack()
+    H, G = (torch.randn(*shape, device=model.device).to(model.tdtype) for shape in ((B, T, d), (B, 8, d)))
+    lens = np.random.default_rng(5).permutation(np.linspace(T // 50, T, B)).astype(np.int32)
+    ws, Y, logits = model.workspace(B, T), model.empty(B, 16, d), model.empty(B, dtype=torch.float32)
+    ms = {}
+    for name, n in (("all", np.full(B, T, np.int32)), ("half", lens)):
+        n = torch.from_numpy(n).to(model.device)
+        times = []
+        for _ in range(15):
+            lg.longer_stage_timing(True, stages=["kvproj"])
+            lg.longer_forward(model.ccfg, weights, H, G, n, B, T, Y, logits, ws)
+            times.append(lg.longer_stage_timing_read()["kvproj"][0])
+            lg.longer_stage_timing(False)
+        ms[name] = sorted(times)[7]
+    print("K / V of %d users, width %d: %.1f us, half of the tiles %.1f us" % (B, d, 1e3 * ms["all"], 1e3 * ms["half"]), flush=True)
+    assert ms["half"] < 0.66 * ms["all"]
