@@ -11,7 +11,7 @@
 // What bounds it: the exponentials and the score arithmetic around them (about 60 vector instructions per
 // 32 x 32 scores against 4-6 matrix instructions, half empty at head width 16).  Row-per-thread loops over LDS rows, the
 // kernels before these, were chains of dependent LDS reads: forward / query side / key side at the headline batch
-// (256 users, 108 queries, 258 keys in the cross layer and 108 in three self layers) 276 / 322 / 336 us, now 94 / 138 / 122.
+// (256 users, 108 queries, 258 keys in the cross layer and 108 in three self layers) 276 / 322 / 336 us, now 86 / 125 / 111.
 #pragma once
 #include "bw_common.h"
 
@@ -34,8 +34,8 @@ struct SetAttn {
 };
 
 // Eq. 8 on descriptors: a key stands at a position (global token a at a - kSeq, sequence token t at t, an invalid one behind
-// everything) and a query sees one interval of them, so that a key is tested by a subtraction and an unsigned comparison, and by the
-// comparison alone where no global query is about (its interval starts at 0).  A sequence query sees the sequence keys up to its own
+// everything) and a query sees one interval of them, so that a key is tested by a subtraction and an unsigned comparison.  (A second form without the
+// subtraction, for tiles without a global query, cost the forward and query sides 5 to 10 % where it was not taken, and gave nothing where it was.)  A sequence query sees the sequence keys up to its own
 // token and no global; a global query sees every sequence key and the globals of its set (causal: those with index >= its own).
 constexpr int kNone = 0x7fffffff - kSeq;
 __device__ __forceinline__ int key_position(int kd) { return kd >= 0 ? kd - kSeq : kNone; }
@@ -187,21 +187,16 @@ __device__ __forceinline__ void tile_visibility(const KeyTiles<DH>& t, int kt, b
   *none = __builtin_amdgcn_ballot_w64(live && lo < see.end && up >= see.lo) == 0;
   *test = __builtin_amdgcn_ballot_w64(live && (lo < see.lo || up >= see.end)) != 0;
 }
-// scores of keys the lane's query does not see become -infinity; plain: no lane's interval starts elsewhere than at 0
+// scores of keys the lane's query does not see become -infinity
 template <int DH>
-__device__ __forceinline__ void mask_scores(f32x16& s, const KeyTiles<DH>& t, int kt, const Seen& see, bool plain, int hi) {
+__device__ __forceinline__ void mask_scores(f32x16& s, const KeyTiles<DH>& t, int kt, const Seen& see, int hi) {
   typedef int i32x4 __attribute__((ext_vector_type(4)));
   const unsigned width = (unsigned)(see.end - see.lo);
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const i32x4 ks = *(const i32x4*)(t.pos + 32 * kt + 8 * q + 4 * hi);
-    if (plain) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) s[4 * q + e] = (unsigned)ks[e] < width ? s[4 * q + e] : -__builtin_inff();
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) s[4 * q + e] = (unsigned)(ks[e] - see.lo) < width ? s[4 * q + e] : -__builtin_inff();
-    }
+    for (int e = 0; e < 4; ++e) s[4 * q + e] = (unsigned)(ks[e] - see.lo) < width ? s[4 * q + e] : -__builtin_inff();
   }
 }
 
@@ -222,7 +217,6 @@ __global__ __launch_bounds__(256) void bw_set_attn_fwd_kernel(SetAttn a, __bf16*
   const bool live = qd >= 0;
   q.keep(live);
   const Seen see = query_sees(qd, a.gmask);
-  const bool plain = __builtin_amdgcn_ballot_w64(see.lo != 0) == 0;
   const float c = 1.4426950408889634f * rsqrtf((float)DH);
   f32x16 acc;
 #pragma unroll
@@ -240,7 +234,7 @@ __global__ __launch_bounds__(256) void bw_set_attn_fwd_kernel(SetAttn a, __bf16*
       if (none) continue;
       f32x16 s = rows_times<DH>(t.k, 32 * kt, q, l32, hi);
       settle(s);                                       // (a branch follows: device.h)
-      if (test) mask_scores<DH>(s, t, kt, see, plain, hi);
+      if (test) mask_scores<DH>(s, t, kt, see, hi);
       float mt = s[0];
 #pragma unroll
       for (int r = 1; r < 16; ++r) mt = fmaxf(mt, s[r]);
@@ -265,8 +259,8 @@ __global__ __launch_bounds__(256) void bw_set_attn_fwd_kernel(SetAttn a, __bf16*
 // Query side of the gradient: P_ij = exp2(c s_ij - lse_i), dP_ij = do_i . v_j, D_i = sum_j P_ij dP_ij (to stat[].y),
 // dq_i = sum_j P_ij (dP_ij - D_i) k_j / sqrt(DH).  Two passes over the keys: D first.  HELD: at most kHeldTiles key tiles (a
 // self layer's), whose P and dP stay in registers for the second pass, 128 of them beside the 38 that the rest takes, so that two or
-// three waves still share a SIMD: all query sides of the headline, small and raw-inputs models' steps 229 us with scores and
-// exponentials formed twice, 193 so.
+// three waves still share a SIMD: all query sides of the headline, small and raw-inputs models' steps 224 us with scores and
+// exponentials formed twice, 175 so.
 constexpr int kHeldTiles = 4;
 template <int DH, bool HELD>
 __global__ __launch_bounds__(256, HELD ? 2 : 1) void bw_set_attn_bwd_q_kernel(SetAttn a, const __bf16* __restrict__ dob, int d,
@@ -285,7 +279,6 @@ __global__ __launch_bounds__(256, HELD ? 2 : 1) void bw_set_attn_bwd_q_kernel(Se
   const bool live = qd >= 0;
   q.keep(live); g.keep(live);
   const Seen see = query_sees(qd, a.gmask);
-  const bool plain = __builtin_amdgcn_ballot_w64(see.lo != 0) == 0;
   const float scale = rsqrtf((float)DH), c = 1.4426950408889634f * scale;
   f32x16 acc;
 #pragma unroll
@@ -308,7 +301,7 @@ __global__ __launch_bounds__(256, HELD ? 2 : 1) void bw_set_attn_bwd_q_kernel(Se
       P[kt] = rows_times<DH>(t.k, 32 * kt, q, l32, hi);
       dP[kt] = rows_times<DH>(t.v, 32 * kt, g, l32, hi);
       settle(P[kt], dP[kt]);
-      if (test) mask_scores<DH>(P[kt], t, kt, see, plain, hi);
+      if (test) mask_scores<DH>(P[kt], t, kt, see, hi);
 #pragma unroll
       for (int r = 0; r < 16; ++r) { P[kt][r] = __builtin_amdgcn_exp2f(fmaf(P[kt][r], c, -lse)); D = fmaf(P[kt][r], dP[kt][r], D); }
     }
@@ -337,7 +330,7 @@ __global__ __launch_bounds__(256, HELD ? 2 : 1) void bw_set_attn_bwd_q_kernel(Se
         f32x16 s = rows_times<DH>(t.k, 32 * kt, q, l32, hi);
         f32x16 dp = rows_times<DH>(t.v, 32 * kt, g, l32, hi);
         settle(s, dp);
-        if (test) mask_scores<DH>(s, t, kt, see, plain, hi);
+        if (test) mask_scores<DH>(s, t, kt, see, hi);
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c, -lse));
         if (pass == 0) {
@@ -417,27 +410,17 @@ __global__ __launch_bounds__(256) void bw_set_attn_bwd_kv_kernel(SetAttn a, cons
     __syncthreads();
     if (j0 >= a.nk) continue;
     for (int qt = 0; qt * 32 < n; ++qt) {
-      const int first = __builtin_amdgcn_readfirstlane(t.least[qt]);
-      if (__builtin_amdgcn_ballot_w64(live && ks >= first && ks < t.most[qt]) == 0) continue;     // seen by no query
+      if (__builtin_amdgcn_ballot_w64(live && ks >= t.least[qt] && ks < t.most[qt]) == 0) continue;     // seen by no query
       const bool test = __builtin_amdgcn_ballot_w64(live && (ks < t.start[qt] || ks >= t.end[qt])) != 0;
       f32x16 p = rows_times<DH>(t.q, 32 * qt, kf, l32, hi);
       f32x16 ds = rows_times<DH>(t.g, 32 * qt, vf, l32, hi);
       settle(p, ds);
       if (test) {
-        if (first >= 0) {                            // (every interval starts at 0)
 #pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4) {
-            const i32x4 width = *(const i32x4*)(t.width + 32 * qt + 8 * q4 + 4 * hi);
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const i32x4 width = *(const i32x4*)(t.width + 32 * qt + 8 * q4 + 4 * hi), lo = *(const i32x4*)(t.lo + 32 * qt + 8 * q4 + 4 * hi);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) p[4 * q4 + e] = (unsigned)ks < (unsigned)width[e] ? p[4 * q4 + e] : -__builtin_inff();
-          }
-        } else {
-#pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4) {
-            const i32x4 width = *(const i32x4*)(t.width + 32 * qt + 8 * q4 + 4 * hi), lo = *(const i32x4*)(t.lo + 32 * qt + 8 * q4 + 4 * hi);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) p[4 * q4 + e] = (unsigned)(ks - lo[e]) < (unsigned)width[e] ? p[4 * q4 + e] : -__builtin_inff();
-          }
+          for (int e = 0; e < 4; ++e) p[4 * q4 + e] = (unsigned)(ks - lo[e]) < (unsigned)width[e] ? p[4 * q4 + e] : -__builtin_inff();
         }
       }
 #pragma unroll
