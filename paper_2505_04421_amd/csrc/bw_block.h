@@ -138,8 +138,9 @@ __device__ __forceinline__ void place_split(const float (&x)[W], const uint32_t 
   place_window<W>(lo, wmask, rest);
 }
 
-template <int NT>
-__device__ __forceinline__ void row_stats(const f32x16 (&x)[NT], float eps, float& mean, float& rstd) {
+// CENTRE: the mean is taken from the rows as well
+template <int NT, bool CENTRE = false>
+__device__ __forceinline__ void row_stats(f32x16 (&x)[NT], float eps, float& mean, float& rstd) {
   float s = 0.f, v = 0.f;
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -149,21 +150,22 @@ __device__ __forceinline__ void row_stats(const f32x16 (&x)[NT], float eps, floa
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { const float q = x[t][r] - mean; v = fmaf(q, q, v); }
+    for (int r = 0; r < 16; ++r) { const float q = x[t][r] - mean; v = fmaf(q, q, v); if (CENTRE) x[t][r] = q; }
   rstd = 1.f / sqrtf(sum_halves(v) * (1.f / (32 * NT)) + eps);
 }
 
-// dx = res + LayerNorm backward of dn at the rows x; result in x
+// dx = res + LayerNorm backward of dn at the rows x; result in x.  (Normalised rows are formed by subtraction, here and on the way forward: in
+// x rstd - mean rstd, one instruction, the second product is rounded ahead of the difference, and rows whose mean is large
+// against their deviation lose digits: rows of equal features 1000 came out as up to 0.016 instead of 0.)
 template <int NT>
 __device__ __forceinline__ void norm_backward(f32x16 (&x)[NT], f32x16 (&dn)[NT], const float* gain, float mean, float rstd, int hi) {
   float c1 = 0.f, c2 = 0.f;
-  const float shift = -mean * rstd;
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     dn[t] *= bias_tile(gain, t, hi);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      x[t][r] = fmaf(x[t][r], rstd, shift);
+      x[t][r] = (x[t][r] - mean) * rstd;
       c1 += dn[t][r];
       c2 = fmaf(dn[t][r], x[t][r], c2);
     }
@@ -301,13 +303,12 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   if (hi == 0) norm1[wave][j] = make_float2(mean1, rstd1);
   bf16x8 nop[NG];
   auto normalise = [&](float mean, float rstd, int og, int ob, int dump) {
-    const float shift = -mean * rstd;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const f32x16 g = bias_tile(vec + og, t, hi), b = bias_tile(vec + ob, t, hi);
       f32x16 h, y;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { h[r] = fmaf(x[t][r], rstd, shift); y[r] = fmaf(h[r], g[r], b[r]); }
+      for (int r = 0; r < 16; ++r) { h[r] = (x[t][r] - mean) * rstd; y[r] = fmaf(h[r], g[r], b[r]); }
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         put_rec(dump, 2 * t + q, E::pack(h, q));
@@ -435,8 +436,8 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
     }
   }
   float mean2, rstd2;
-  row_stats<NT>(x, p.eps, mean2, rstd2);
-  normalise(mean2, rstd2, oG2, oB2n, rc.xh2);
+  row_stats<NT, true>(x, p.eps, mean2, rstd2);       // (the rows themselves are not needed any more)
+  normalise(0.f, rstd2, oG2, oB2n, rc.xh2);
 
   f32x16 dn[NT];
   {
@@ -482,7 +483,7 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   const int left2 = lefts[wave][j];
   const bool valid2 = tk2.jj < left2;
   request_upstream(tk2, valid2);
-  norm_backward<NT>(x, dn, vec + oG2, mean2, rstd2, hi);
+  norm_backward<NT>(x, dn, vec + oG2, 0.f, rstd2, hi);
   vb = (uint32_t)__ballot(valid2);
   seen = ((gb & vb) >> (4 * hi)) >> (2 * W * widx);
   take_upstream(left2, valid2);

@@ -88,3 +88,26 @@ def test_gradients_of_deep_models(d, heads, n_self, inner):
     cfg = synth.CONFIGS["C2"].replace(d=d, heads=heads, inner_heads=heads, B=4, L=90, m=4, k_recent=9, n_self=n_self, inner_layers=inner,
                                       ragged=True, len_lo=20, len_hi=90, index=127)
     _compare_model("width %d, %d self layers, %d InnerTrans blocks" % (d, n_self, inner), synth.make_case(cfg))
+
+
+# Rows whose features are all alike and far from zero: their normalised rows are exact zeros, and with them the gradient of the first
+# LayerNorm's gain.  (A normalised row of x / s - mean / s, the quotients rounded on their own, came out as up to 0.016 here, and the gain's gradient
+# as 2e-3 of the shift's.  The gradients of W_Q and W_K are zero as well, all keys being alike, so they are not compared.)
+@pytest.mark.parametrize("d,heads,K", [(128, 8, 8), (64, 4, 16), (32, 2, 4)])
+def test_rows_without_spread(d, heads, K):
+    import numpy as np
+    from oracle import longer_oracle_grad as org
+    from test_gpu_backward import TOL, _rel, _run_gpu
+    cfg = synth.CONFIGS["C2"].replace(d=d, heads=heads, inner_heads=heads, B=4, L=150, K=K, m=2, k_recent=4, n_self=1, inner_layers=1, index=139)
+    case = synth.make_case(cfg)
+    value = synth.round_bf16(np.random.default_rng(11).uniform(300.0, 1000.0, size=case["H"].shape[:2] + (1,)).astype(np.float32))
+    case["H"] = np.broadcast_to(value, case["H"].shape).astype(np.float32)
+    dM = synth.draw_merge_gradient(cfg)
+    dH, grads = _run_gpu(case, dM)
+    gain, shift = (float(np.linalg.norm(grads[0][k])) for k in ("ln1_g", "ln1_b"))
+    _say("rows without spread, width %d: gradient of the first LayerNorm's gain %.3e, shift %.3e" % (d, gain, shift))
+    assert shift > 0 and gain <= 1e-6 * shift
+    dH_ref, g_ref = org.token_merge_backward(cfg, case["weights"]["inner"], case["H"], None, dM, keep="input_only")
+    assert _rel(dH, dH_ref) <= TOL
+    for name in ("ln1_b", "wv", "wo", "ln2_g", "w1", "w2"):
+        assert _rel(grads[0][name], g_ref[0][name]) <= TOL, name
