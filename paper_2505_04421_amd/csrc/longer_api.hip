@@ -688,8 +688,15 @@ static bool quad_pays(const Shape& s, long long tiles) { return s.quad && tiles 
 // forward pass (L = 400, K = 8, four layers), microseconds layer by layer / in one launch, at 32, 244, 384, 512 and 640 tiles of 108
 // rows a user: width 64 55 / 63, 60 / 64, 73 / 68, 75 / 68, 95 / 69; width 128 77 / 105, 89 / 108, 111 / 117, 113 / 118, 150 / 120;
 // width 256 158 / 252, 171 / 252, 310 / 303, 323 / 304, 434 / 312.  (Two tiles a user at width 256: 157 / 160 at 64 tiles, in one launch.)
-static bool layers_pay(const Shape& s, int B) {
-  return s.quad && s.n > 64 && (long long)B * cdiv(s.n, 32) <= (s.D == 128 ? 512 : 256);
+// With two workgroups on a compute unit, or nearly all of them busy at width 64, only the cross layer gains and each layer behind it costs:
+// width 128, 102 users of 68 rows (306 tiles), five, seven, eleven and 21 layers 122 / 126, 158 / 159, 231 / 225, 412 / 390, at 510 tiles
+// 145 / 144, 182 / 177, 256 / 241, 439 / 405 (four layers 125 / 129); width 64 at 255 tiles 73 / 74, 95 / 95, 139 / 137, 249 / 242, at 177 tiles
+// 235 / 238 for 21.  With heads of 32 features the lines come sooner: four layers, width 128 103 / 105 at 435 tiles, 123 / 121 at 510;
+// width 64 54 / 55 at 192, 58.3 / 57.7 at 255.
+static bool layers_pay(const longer_config* c, const Shape& s, int B) {
+  if (!s.quad || s.n <= 64) return false;
+  const int most = s.D == 256 ? 256 : s.D == 128 ? (c->n_self > 3 ? 256 : s.DH == 32 ? 448 : 512) : (c->n_self > 6 || s.DH == 32 ? 192 : 256);
+  return (long long)B * cdiv(s.n, 32) <= most;
 }
 
 // K and V with the weights in registers (kv_kernel.h: its figures).  At width 128, ragged users of at most two key tiles in more than one round
@@ -1032,7 +1039,7 @@ static int forward_impl(const longer_config* cfg, const longer_weights* w, const
   const Shape si = inner_view(cfg, s);
   const bool concat = cfg->merge == LONGER_MERGE_CONCAT;
   const bool room = ws_bytes >= l.total_ahead;
-  const bool one_launch = stack_in_one_launch(s) && !(room && layers_pay(s, B));
+  const bool one_launch = stack_in_one_launch(s) && !(room && layers_pay(cfg, s, B));
   const PackedLayout pl = packed_layout(cfg, s);
   char* pk = nullptr;
   if ((rc = packed_source(cfg, s, w, in ? in->w : nullptr, w8 + l.packed,
