@@ -320,3 +320,26 @@ def test_key_value_projection_of_ragged_users_is_balanced(d):
         ms[name] = sorted(times)[7]
     print("K / V of %d users, width %d: %.1f us, half of the tiles %.1f us" % (B, d, 1e3 * ms["all"], 1e3 * ms["half"]), flush=True)
     assert ms["half"] < 0.66 * ms["all"]
+
+
+# Query sets of more than four tiles in more tiles than the few-tiles plan takes: every layer's K and V in a launch of their own, the self layers' from
+# fp32 rows (width 256: in registers, several tiles a workgroup; width 128: the block kernel), all their tiles needed whatever the lengths
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,heads,m,k,B,extra", [(256, 8, 8, 150, 110, {}), (256, 16, 32, 101, 105, dict(gmask="causal")), (128, 8, 8, 150, 160, {}),
+                                                 (256, 8, 8, 150, 105, dict(q_learnable=True)), (128, 4, 8, 129, 155, dict(k_uniform=60))])
+def test_wide_query_sets_in_many_tiles(d, heads, m, k, B, extra):
+    import numpy as np
+    import longer_synth as synth
+    from oracle import longer_oracle as orc
+    from gpu_util import Runner
+    from test_gpu_parity import TOL, _check
+    n = 5
+    cfg = synth.CONFIGS["C2"].replace(B=n, L=800, K=4, d=d, heads=heads, inner_heads=heads, m=m, k_recent=k, n_self=2, ragged=True, len_lo=0, len_hi=800,
+                                      index=149, **extra)
+    case = synth.make_case(cfg)
+    case["lens"][:4] = [800, 0, 9, 500]
+    ref, _ = orc.forward(cfg, case["weights"], case["H"], case["G"], case["lens"])
+    pick = np.concatenate([np.arange(n), np.random.default_rng(7).integers(0, n, size=B - n)])
+    many = dict(case, cfg=cfg.replace(B=B), **{name: case[name][pick] for name in ("H", "G", "lens")})
+    Y, _ = Runner(many).forward()
+    _check("all users", Y, ref[pick], TOL["bf16"])
