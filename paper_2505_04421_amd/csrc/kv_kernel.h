@@ -7,7 +7,7 @@
 // the next tile's rows on their way; LayerNorm sums and the normalised rows change hands through LDS (two barriers a tile).
 //
 // Users of different length need different numbers of key tiles, and as many workgroups as run at once have no successor that could take a
-// share of the longer ones' work: the needed tiles are counted and dealt out evenly (dealt by a fixed stride, with key tiles a user
+// share of the longer ones' work: there the needed tiles are counted and dealt out evenly (dealt by a fixed stride, with key tiles a user
 // that divide the number of workgroups, a workgroup met the same key tile of every user; 512 users of 2 to 100 % of 16 key tiles took
 // 63 us at width 128 and 148 at 256, as long as with all tiles needed).
 //
@@ -57,14 +57,22 @@ __global__ void __launch_bounds__(2 * D, D >= 256 ? 1 : 2) kv_kernel(const Block
     if (!p.key_self) t.need = min(t.need, (p.m0 + t.tu + 31) / 32);
     return t;
   };
-  auto step = [&](Tile t) {                          // the next needed tile (the caller knows that there is one)
+  int du = 0, dk = 0;                                // tiles dealt out by a stride: users and key tiles in it
+  auto step = [&](Tile t) {                          // the workgroup's next tile (the caller knows that there is one)
+    if (du + dk > 0) {
+      const int kt = t.kt + dk, over = kt >= p.tiles_per_user;
+      t = user(t.u + du + over);
+      t.kt = kt - (over ? p.tiles_per_user : 0);
+      return t;
+    }
     if (++t.kt < t.need) return t;
     do t = user(t.u + 1); while (t.need == 0);
     return t;
   };
-  // One round of workgroups: a tile each.  More tiles: every workgroup takes as many needed tiles as the others, one after the other, `left`
-  // in all from the needed tile number `first` on; with users of one length a division finds it, else each thread counts the tiles
-  // of its share of the users.
+  // One round of workgroups: a tile each.  More tiles: every workgroup takes as many needed tiles as the others, `left` in all.  With all of
+  // them needed, by a stride: what runs at once then writes one stretch of memory (256 users of nine tiles, width 256, buffers not
+  // in the caches: 40.3 us, in runs of consecutive tiles 45.2), and the workgroups that meet one key tile of every user have no less to do than
+  // the others.  Else in runs: each thread counts the tiles of its share of the users to find the first.
   int left;
   Tile t;
   {
@@ -72,10 +80,10 @@ __global__ void __launch_bounds__(2 * D, D >= 256 ? 1 : 2) kv_kernel(const Block
     const long long all = (long long)p.B * per;
     const bool round = all <= MOST;
     if (round || !p.lens || p.key_self || (per == 1 && p.m0 > 0)) {      // (a user's first tile has its global rows)
-      const int first = round ? b : (int)(b * all / MOST);
-      t = user(first / per);
-      t.kt = first - t.u * per;
-      left = round ? (t.kt < t.need ? 1 : 0) : (int)((b + 1) * all / MOST) - first;
+      t = user(b / per);
+      t.kt = b - t.u * per;
+      left = round ? (t.kt < t.need ? 1 : 0) : (int)((all - b + MOST - 1) / MOST);
+      du = MOST / per; dk = MOST - du * per;
     } else {
       __shared__ int count[NT];
       __shared__ Tile start;

@@ -292,6 +292,26 @@ def test_key_value_projection_of_ragged_users(d, heads, m, B, T):
     _check("all users", Y, ref[pick], TOL["bf16"])
 
 
+# Users of one length, more tiles than workgroups: dealt out by a stride, of 7, 16 and 5 key tiles (dividing the workgroups or not, a last round
+# that is nearly empty or full)
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,heads,m,B,T", [(128, 8, 8, 80, 216), (128, 8, 4, 33, 500), (256, 8, 8, 40, 210), (256, 16, 2, 103, 158)])
+def test_key_value_projection_of_many_users_of_one_length(d, heads, m, B, T):
+    import numpy as np
+    import longer_synth as synth
+    from oracle import longer_oracle as orc
+    from gpu_util import Runner
+    from test_gpu_parity import TOL, _check
+    n = 3
+    cfg = synth.CONFIGS["C2"].replace(B=n, L=T, K=1, d=d, heads=heads, inner_heads=heads, m=m, k_recent=3, n_self=0, ragged=False, index=151)
+    case = synth.make_case(cfg)
+    ref, _ = orc.forward(cfg, case["weights"], case["H"], case["G"], case["lens"])
+    pick = np.random.default_rng(9).integers(0, n, size=B)
+    many = dict(case, cfg=cfg.replace(B=B), lens=None, **{k: case[k][pick] for k in ("H", "G")})
+    Y, _ = Runner(many).forward()
+    _check("all users", Y, ref[pick], TOL["bf16"])
+
+
 # ... and evenly enough: with half of the tiles needed the launch takes clearly less than with all of them (0.52 and 0.58 times as long at widths
 # 128 and 256; 0.71 and 0.92 where a workgroup met the same key tile of every user)
 @pytest.mark.gpu
