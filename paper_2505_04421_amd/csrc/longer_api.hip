@@ -699,16 +699,14 @@ static bool layers_pay(const longer_config* c, const Shape& s, int B) {
   return (long long)B * cdiv(s.n, 32) <= most;
 }
 
-// K and V with the weights in registers (kv_kernel.h: its figures).  At width 128 and beyond one round of workgroups two kinds stay with the
-// block kernel.  Self layers: its workgroups take the tiles that the attention launch before and behind has on the same die (138 users of
-// 208 rows 12.1 / 10.5 us a layer with it / with the block kernel, 182 14.3 / 13.0, 400 19.3 / 18.5, 1000 of 158 28.4 / 28.6; width 256 19.3 / 18.4,
-// 21.8 / 29.6, 38.4 / 46.8, 71.5 / 79.8).  Ragged users of at most two key tiles, where the hardware deals its workgroups out as they come: 512, 1500
-// and 5000 users of one key tile 6.6 / 11.2 (one round), 14.3 / 14.4, 34.5 / 32.9 us, of two 11.9 / 11.0, 22.7 / 22.4, 67.7 / 62.6; of
-// three 14.0 / 14.1, 27.1 / 30.1, 82.6 / 92.3.  (Width 256, one key tile: 12.9 / 17.9 for 512 users, 84 / 94 for 5000; two 21.8 / 20.8, 125 / 171.)
+// K and V with the weights in registers (kv_kernel.h: its figures).  At width 128, ragged users of at most two key tiles in more than one round
+// of workgroups stay with the block kernel, whose workgroups the hardware deals out as they come: 512, 1500 and 5000 users of one key tile 6.6 /
+// 11.2 (one round), 14.3 / 14.4, 34.5 / 32.9 us with it / with the block kernel, of two 11.9 / 11.0, 22.7 / 22.4, 67.7 / 62.6; of three 14.0 / 14.1,
+// 27.1 / 30.1, 82.6 / 92.3.  (Width 256, one key tile: 12.9 / 17.9 for 512 users, 84 / 94 for 5000; two 21.8 / 20.8, 125 / 171.)
 static bool kv_in_registers(const Shape& s, const BlockParams& p) {
   const long long tiles = (long long)p.B * p.tiles_per_user;
   if (!s.user || tiles >= (1LL << 30)) return false;
-  return !(s.D == 128 && tiles > kv_workgroups(s.D) && (p.key_self || (p.lens && p.tiles_per_user <= 2)));
+  return !(s.D == 128 && p.lens && !p.key_self && p.tiles_per_user <= 2 && tiles > kv_workgroups(s.D));
 }
 
 static int run_layer(const longer_config* c, const Shape& s, const char* packed_blk, const int32_t* lens, int B, int L,

@@ -343,7 +343,7 @@ def test_key_value_projection_of_ragged_users_is_balanced(d):
 
 
 # Query sets of more than four tiles in more tiles than the few-tiles plan takes: every layer's K and V in a launch of their own, the self layers' from
-# fp32 rows (width 256: in registers, several tiles a workgroup; width 128: the block kernel), all their tiles needed whatever the lengths
+# fp32 rows, several tiles a workgroup, all of them needed whatever the lengths
 @pytest.mark.gpu
 @pytest.mark.parametrize("d,heads,m,k,B,extra", [(256, 8, 8, 150, 110, {}), (256, 16, 32, 101, 105, dict(gmask="causal")), (128, 8, 8, 150, 160, {}),
                                                  (256, 8, 8, 150, 105, dict(q_learnable=True)), (128, 4, 8, 129, 155, dict(k_uniform=60))])
