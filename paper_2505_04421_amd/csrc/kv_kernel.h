@@ -143,11 +143,17 @@ __global__ void __launch_bounds__(2 * D, D >= 256 ? 1 : 2) kv_kernel(const Block
     const bool valid = exists(t);
     f32x16 x;
     if (ahead) {
-      const bool global = !p.src0.f32 && 32 * t.kt + j < p.m0;
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { const float one = raw[q][e], two = (float)front[q][e]; x[4 * q + e] = !valid ? 0.f : global ? two : one; }
+        for (int e = 0; e < 4; ++e) { const float one = raw[q][e]; x[4 * q + e] = valid ? one : 0.f; }
+      if (!p.src0.f32 && 32 * t.kt < p.m0) {
+        const bool global = valid && 32 * t.kt + j < p.m0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[4 * q + e] = global ? (float)front[q][e] : x[4 * q + e];
+      }
     } else {
       const int c = 32 * t.kt + j;
       const bool first = c < p.m0;
