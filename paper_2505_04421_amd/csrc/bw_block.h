@@ -10,8 +10,8 @@
 // What bounds it: as thirteen launches over [token, feature] tensors (two LayerNorms, three products, attention,
 // the FFN's middle, three products back, attention back, two LayerNorms back) a block of the headline batch
 // (512 000 rows of width 128) moved 18.8 KB per token beside its parameter gradients in 2.1 ms; here it is 7.8-8.2 KB
-// in 0.84 ms: 4.9 TB/s, where a large copy reaches 5.0.  Memory and the vector unit add up: with a third of its stores left out
-// it took 0.80 instead of 0.90 ms, and with 9 650 instead of 10 800 vector instructions per tile (beside 808 products) 0.84.
+// in 0.85 ms (0.84 to 0.87 by box): 4.8 TB/s, where a large copy reaches 5.0.  Memory and the vector unit add up: with a third of its stores
+// left out it took 0.80 instead of 0.90 ms, and with 9 650 instead of 10 800 vector instructions per tile (beside 808 products) 0.84.
 //
 // Tile blocks.  A tensor of F features that the parameter gradients read is stored as [F / 16][1 KiB] per tile: 16
 // features of 32 tokens, 32 bytes per token, as the lanes hold them (lane half hi: features 4 hi .. + 3 and
