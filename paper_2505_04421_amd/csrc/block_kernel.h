@@ -111,25 +111,28 @@ __device__ __forceinline__ void load_rows(f32x16 (&x)[NT], const void* base, int
   }
 }
 
+// (which of the two types is asked once, not at every piece)
 template <typename T, int NT>
 __device__ __forceinline__ void store_rows(const f32x16 (&x)[NT], void* base, int is_f32, long long off,
                                            bool nonzero, int hi) {
+  typedef __attribute__((address_space(1))) f32x4 gf32x4;
+  typedef __attribute__((address_space(1))) bf16x4 gbf16x4;
+  const long long o = off + 4 * hi;
+  if (is_f32 || sizeof(T) == 4) {
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int i = 0; i < 4 * NT; ++i) {
       f32x4 v;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = nonzero ? x[t][4 * q + e] : 0.f;
-      long long o = off + 32 * t + 8 * q + 4 * hi;
-      if (is_f32 || sizeof(T) == 4) {
-        *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(base) + o) = v;
-      } else {
-        bf16x4 b;
+      for (int e = 0; e < 4; ++e) v[e] = nonzero ? x[i / 4][4 * (i % 4) + e] : 0.f;
+      *(gf32x4*)(reinterpret_cast<float*>(base) + o + 8 * i) = v;
+    }
+  } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) b[e] = (__bf16)v[e];
-        *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(base) + o) = b;
-      }
+    for (int i = 0; i < 4 * NT; ++i) {
+      bf16x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = (__bf16)(nonzero ? x[i / 4][4 * (i % 4) + e] : 0.f);
+      *(gbf16x4*)(reinterpret_cast<__bf16*>(base) + o + 8 * i) = v;
     }
   }
 }
@@ -1339,16 +1342,29 @@ static int launch_stack_mode(const BlockParams& p, dim3 grid, hipStream_t stream
   }
 }
 
-// (training: bf16 up to width 128, what the block kernel of the backward pass covers)
+// bf16, d = 128: the merge and input generation modes have a kernel of their own (merge_kernel.h)
+template <int D, int DH>
+int launch_merge(int mode, int win, const BlockParams& p, dim3 grid, hipStream_t stream);
+
 template <typename T, int D, int DH>
-static int launch_merge_keep(int win, const BlockParams& p, dim3 grid, hipStream_t stream) {
-  if constexpr (sizeof(T) == 2 && D <= 128) {
-    if (win == 4) LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE_KEEP, 4);
-    else if (win == 8) LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE_KEEP, 8);
-    else LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE_KEEP, 16);
+static int launch_rows_mode(int mode, int win, const BlockParams& p, dim3 grid, hipStream_t stream) {
+  if constexpr (sizeof(T) == 2 && D == 128) return launch_merge<D, DH>(mode, win, p, grid, stream);
+  else {
+    if (mode == MODE_INPUT) LONGER_LAUNCH(T, D, DH, 1, MODE_INPUT, 16);
+    else if (mode == MODE_MERGE) {
+      if (win == 4) LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE, 4);
+      else if (win == 8) LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE, 8);
+      else LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE, 16);
+    } else if (mode == MODE_MERGE_IN) {
+      if (win == 4) LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE_IN, 4);
+      else if (win == 8) LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE_IN, 8);
+      else LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE_IN, 16);
+    } else if constexpr (sizeof(T) == 2 && D < 128) {      // MODE_MERGE_KEEP (training): what the block kernel of the backward pass covers
+      if (win == 4) LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE_KEEP, 4);
+      else if (win == 8) LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE_KEEP, 8);
+      else LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE_KEEP, 16);
+    } else return -1;
     return 0;
-  } else {
-    return -1;
   }
 }
 
@@ -1357,26 +1373,17 @@ static int launch_merge_keep(int win, const BlockParams& p, dim3 grid, hipStream
   int launch_block<T, D, DH>(int mode, int tt, int win, const BlockParams& p, dim3 grid, hipStream_t stream) { \
     if (tt != 1) return -1;                                                                           \
     switch (mode) {                                                                                   \
-      case MODE_MERGE:                                                                                \
-        if (win == 4) LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE, 4);                                      \
-        else if (win == 8) LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE, 8);                                 \
-        else LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE, 16);                                              \
+      case MODE_MERGE: case MODE_MERGE_IN: case MODE_MERGE_KEEP: case MODE_INPUT:                     \
+        if (launch_rows_mode<T, D, DH>(mode, win, p, grid, stream)) return -1;                        \
         break;                                                                                        \
       case MODE_KVPROJ: LONGER_LAUNCH(T, D, DH, 1, MODE_KVPROJ, 16); break;                           \
       case MODE_ATTN: LONGER_LAUNCH(T, D, DH, 1, MODE_ATTN, 16); break;                               \
       case MODE_STACK: if (launch_stack_mode<T, D, DH>(p, grid, stream)) return -1; break;           \
-      case MODE_INPUT: LONGER_LAUNCH(T, D, DH, 1, MODE_INPUT, 16); break;                             \
-      case MODE_MERGE_IN:                                                                             \
-        if (win == 4) LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE_IN, 4);                                   \
-        else if (win == 8) LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE_IN, 8);                              \
-        else LONGER_LAUNCH(T, D, DH, 1, MODE_MERGE_IN, 16);                                           \
-        break;                                                                                        \
       case MODE_SCORE:                                                                                \
         if (win == 4) LONGER_LAUNCH(T, D, DH, 1, MODE_SCORE, 4);                                      \
         else if (win == 8) LONGER_LAUNCH(T, D, DH, 1, MODE_SCORE, 8);                                 \
         else LONGER_LAUNCH(T, D, DH, 1, MODE_SCORE, 16);                                              \
         break;                                                                                        \
-      case MODE_MERGE_KEEP: if (launch_merge_keep<T, D, DH>(win, p, grid, stream)) return -1; break;  \
       default: return -1;                                                                             \
     }                                                                                                 \
     return hipGetLastError() == hipSuccess ? 0 : -3;                                                  \
