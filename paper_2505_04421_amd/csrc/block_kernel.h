@@ -437,7 +437,7 @@ __device__ __forceinline__ void key_tile_step(const KeyRanges& r, int kt, const 
       const bool fresh = sum_halves(sum[hh]) == 0.f;
       const bool move = (m > ref[hh] + kScoreSpan) | (fresh & (m < ref[hh] - kScoreSpan) & (m > kNegBig));
       if (__builtin_amdgcn_ballot_w64(move) != 0) {
-        const float alpha = move & !fresh ? __builtin_amdgcn_exp2f(ref[hh] - m) : 1.f;
+        const float alpha = (move & !fresh) ? __builtin_amdgcn_exp2f(ref[hh] - m) : 1.f;
         ref[hh] = move ? m : ref[hh];
         sum[hh] *= alpha;
         settle(acc[hh]);

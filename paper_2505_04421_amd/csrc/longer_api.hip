@@ -3,6 +3,7 @@
 #include "../../include/longer.h"
 #include "pair_kernel.h"
 #include "user_kernel.h"
+#include "chain_kernel.h"
 #include "few_f32_kernel.h"
 #include "kv_kernel.h"
 
@@ -34,7 +35,8 @@ template <> int launch_pair<128, 32>(int, const BlockParams&, dim3, hipStream_t)
 template <> int launch_pair<256, 16>(int, const BlockParams&, dim3, hipStream_t);
 template <> int launch_pair<256, 32>(int, const BlockParams&, dim3, hipStream_t);
 
-template <> int launch_quad<64, 16>(int, int, bool, const BlockParams&, dim3, hipStream_t);
+template <> int launch_chain<64>(int, int, bool, const BlockParams&, dim3, hipStream_t);
+template <> int launch_chain<128>(int, int, bool, const BlockParams&, dim3, hipStream_t);
 template <> int launch_quad<64, 32>(int, int, bool, const BlockParams&, dim3, hipStream_t);
 template <> int launch_quad<128, 16>(int, int, bool, const BlockParams&, dim3, hipStream_t);
 template <> int launch_quad<128, 32>(int, int, bool, const BlockParams&, dim3, hipStream_t);
@@ -73,7 +75,7 @@ static pair_fn find_pair(int dtype, int D, int DH) {
 // the kernels that give a tile to four waves (quad_kernel.h), for launches with few tiles: bf16, d = 64 / 128 / 256
 static quad_fn find_quad(int dtype, int D, int DH) {
   if (one_wave_only() || dtype != LONGER_BF16) return nullptr;
-  if (D == 64) return DH == 16 ? &launch_quad<64, 16> : DH == 32 ? &launch_quad<64, 32> : nullptr;
+  if (D == 64) return DH == 16 ? &launch_chain<64> : DH == 32 ? &launch_quad<64, 32> : nullptr;
   if (D == 128) return DH == 16 ? &launch_quad<128, 16> : DH == 32 ? &launch_quad<128, 32> : nullptr;
   if (D == 256) return DH == 16 ? &launch_quad<256, 16> : DH == 32 ? &launch_quad<256, 32> : nullptr;
   return nullptr;
@@ -682,6 +684,12 @@ struct AttnIO {
 // attention, each with the next one's K and V, over 50 groups of raw tokens), width 64 at 16, 256, 512 tiles 32 / 48, 51 / 68, 72 / 85; width 128 at 64,
 // 256, 512 tiles 81 / 140, 93 / 151, 135 / 177; width 256 at 32, 256, 512 tiles 131 / 274, 218 / 341, 412 / 465.
 static bool quad_pays(const Shape& s, long long tiles) { return s.quad && tiles <= (s.D == 128 ? 768 : 512); }
+// At width 128 and heads of 16 features a wave per head (chain_kernel.h) as long as every tile has a compute unit of its own: 256 / 257, 320, 512 tiles
+// of candidates, wave per head / two heads a wave, 43 / 47, 76 / 56, 78 / 59, 80 / 65 us.
+static int launch_few(const Shape& s, int mode, int win, bool pair, long long tiles, const BlockParams& p, hipStream_t st) {
+  const bool chain = s.D == 128 && s.DH == 16 && tiles <= 256;
+  return (chain ? &launch_chain<128> : s.quad)(mode, win, pair, p, dim3((unsigned)tiles), st);
+}
 
 // Stacks of more than two tiles a user: as long as their tiles are one round of the few-tiles kernels' workgroups (one per compute
 // unit, two at width 128), a launch per layer in which every tile has a compute unit of its own beats one workgroup per user.  Whole
@@ -740,7 +748,7 @@ static int run_layer(const longer_config* c, const Shape& s, const char* packed_
   if (quad_pays(s, tiles)) {
     p.n_layers = 1;
     p.kv_w = io.next_blk; p.kv_k = io.next_kst; p.kv_v = io.next_vst; p.kv_w_ustride = io.next_ustride;
-    if (s.quad(MODE_ATTN, 16, false, p, dim3((unsigned)tiles), st)) return fail(LONGER_ERR_HIP, "attention launch failed");
+    if (launch_few(s, MODE_ATTN, 16, false, tiles, p, st)) return fail(LONGER_ERR_HIP, "attention launch failed");
     return 0;
   }
   if (s.main_fn(MODE_ATTN, 1, 16, p, dim3(grid), st)) return fail(LONGER_ERR_HIP, "attention launch failed");
@@ -1222,8 +1230,7 @@ static int run_score(const longer_config* cfg, const Shape& s, const char* strea
   const int win = cfg->m <= 8 ? 4 : (cfg->m <= 16 ? 8 : 16);
   if (quad_pays(s, (long long)U * tiles)) {
     p.wg_per_user = tiles;
-    grid = dim3((unsigned)((long long)U * tiles));
-    if (s.quad(MODE_SCORE, win, pair_score(s), p, grid, st)) return fail(LONGER_ERR_HIP, "score kernel launch failed");
+    if (launch_few(s, MODE_SCORE, win, pair_score(s), (long long)U * tiles, p, st)) return fail(LONGER_ERR_HIP, "score kernel launch failed");
     return 0;
   }
   if (pair_score(s) ? s.pair(win, p, grid, st) : s.main_fn(MODE_SCORE, 1, win, p, grid, st))
