@@ -240,9 +240,10 @@ struct StackVectors {
 __host__ __device__ inline int stack_vec_floats(int d, int f) { return 9 * d + f; }
 
 // What bounds the two kernels: the chain of a tile at small batches; at the headline batch (864 tiles) the exact-erf activation
-// beside the products, and 3.3 KB (forward) and 5.5 KB (backward) of memory traffic per row.
-template <int D>
-__global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stack_fwd_kernel(const StackFwd p0, const StackFwd p1, int tiles0) {
+// beside the products, and 3.3 KB (forward) and 5.5 KB (backward) of memory traffic per row: 46 and 71 us a launch with four and three
+// workgroups a compute unit, 50 and 73 with three and two.  MANY: see kStackManyTiles.
+template <int D, bool MANY>
+__global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : MANY ? 4 : 2) void bw_stack_fwd_kernel(const StackFwd p0, const StackFwd p1, int tiles0) {
   using S = StackTile<D>;
   constexpr int NT = S::NT, NG = S::NG, WV = S::WV;
   using E = ET<__bf16>;
@@ -303,9 +304,9 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stac
       for (int q = 0; q < 2; ++q) rec.put(at, 2 * ft + q, E::pack(h, q));
     }
     __syncthreads();
-    s.take(nop);
+    if (!MANY) s.take(nop);
   };
-  auto operand = [&](int k) { return nop[k]; };
+  auto operand = [&](int k) -> bf16x8 { return MANY ? ops[k][lane] : nop[k]; };
   if (p.o) {
     const BlockRecord at(D, p.f);
     const RecordOut rec(p.rec, tile, at.size, lane);
@@ -315,7 +316,7 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stac
     __syncthreads();                               // `vec`
     x += bias_tile(vec + oBo, ft, hi);
     typename S::gchar* first = s.at(NT + 2 * min(wave, NC - 1), 0);
-    s.product(x, operand, [&](int k) { s.fr[k] = s.load(first, k); });
+    s.product(x, [&](int k) { return nop[k]; }, [&](int k) { s.fr[k] = s.load(first, k); });
     if (own) store_part<NT>(x, p.xmid, tile, ft, lane);
     normalise(0, oG2, oS2, rec, at.xh2);
     x += bias_tile(vec + oB2, ft, hi);
@@ -363,8 +364,8 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stac
   }
 }
 
-template <int D>
-__global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stack_bwd_kernel(const StackBwd p0, const StackBwd p1, int tiles0) {
+template <int D, bool MANY>
+__global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : MANY ? 3 : 2) void bw_stack_bwd_kernel(const StackBwd p0, const StackBwd p1, int tiles0) {
   using S = StackTile<D>;
   constexpr int NT = S::NT, NG = S::NG, WV = S::WV;
   using E = ET<__bf16>;
@@ -435,8 +436,8 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stac
   const bool live = in && p.desc[in ? row : 0] >= 0;
   s.stats(2, xm, p.eps, mean, rstd);               // (its barrier: `vec` is there)
   // (width 256: no registers for a second operand of all features, it is read from LDS)
-  constexpr bool HELD = D <= 128;
-  bf16x8 dyop[HELD ? NG : 1], nop[NG];
+  constexpr bool HELD = D <= 128 && !MANY;
+  bf16x8 dyop[HELD ? NG : 1], nop[MANY ? 1 : NG];
 #pragma unroll
   for (int r = 0; r < 16; ++r) x[r] = live ? x[r] : 0.f;
   dn = splat16(0.f);
@@ -456,12 +457,12 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stac
     }
   }
   __syncthreads();
-  s.take(nop);
+  if constexpr (!MANY) s.take(nop);
   if (HELD) {
 #pragma unroll
     for (int g = 0; g < (HELD ? NG : 1); ++g) dyop[g] = ops2[g][lane];
   }
-  auto operand = [&](int k) { return nop[k]; };
+  auto operand = [&](int k) -> bf16x8 { return MANY ? ops[k][lane] : nop[MANY ? 0 : k]; };
   auto upstream = [&](int k) -> bf16x8 { return HELD ? dyop[HELD ? k : 0] : ops2[k][lane]; };
   for (int c0 = 0, par = 0; c0 < NC; c0 += WV, par ^= 1) {
     const int c = min(c0 + wave, NC - 1);          // (a wave without a chunk goes through another's and hands in zeros)
@@ -505,7 +506,7 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : 2) void bw_stac
     for (int q = 0; q < 2; ++q) rec.put(at.dxmb, 2 * ft + q, E::pack(x, q));
   }
   __syncthreads();
-  s.take(nop);
+  if constexpr (!MANY) s.take(nop);
   f32x16 v = splat16(0.f);
   s.product(v, operand, [](int) {});
   if (in && own) {
@@ -522,17 +523,28 @@ void bw_stack_fwd_128(const StackFwd& p, const StackFwd& k, hipStream_t st);
 void bw_stack_bwd_128(const StackBwd& p, const StackBwd& k, hipStream_t st);
 void bw_stack_fwd_256(const StackFwd& p, const StackFwd& k, hipStream_t st);
 void bw_stack_bwd_256(const StackBwd& p, const StackBwd& k, hipStream_t st);
+// Beyond one round of two workgroups a compute unit the operands of the products stay in LDS (MANY) instead of a wave's registers: four
+// workgroups fit forward (119 registers instead of 150) and three backward (160 instead of 224).  A training step of width 128 and 108 rows a user, 439,
+// 513, 642, 864, 1728 tiles, without / with it 643 / 646, 765 / 734, 842 / 818, 1037 / 1020, 1748 / 1721 us; width 64 and 104 rows, 520, 650,
+// 1664 tiles 353 / 334, 381 / 366, 732 / 716.
+constexpr int kStackManyTiles = 512;
 // k: the cross layer's key rows, beside its query rows in one launch (no rows: none).  Two launches of their own in either direction
 // were each the chain of a tile on a part of the chip.
 template <int D>
 inline void bw_stack_fwd_d(const StackFwd& p, const StackFwd& k, hipStream_t st) {
   const int t0 = (p.rows + 31) / 32, t1 = (k.rows + 31) / 32;
-  bw_stack_fwd_kernel<D><<<t0 + t1, 64 * stack_waves(D), (size_t)stack_vec_floats(D, p.f) * 4, st>>>(p, k, t0);
+  const dim3 grid(t0 + t1), block(64 * stack_waves(D));
+  const size_t lds = (size_t)stack_vec_floats(D, p.f) * 4;
+  if constexpr (D == 128 || D == 64) { if (t0 + t1 > kStackManyTiles) { bw_stack_fwd_kernel<D, true><<<grid, block, lds, st>>>(p, k, t0); return; } }
+  bw_stack_fwd_kernel<D, false><<<grid, block, lds, st>>>(p, k, t0);
 }
 template <int D>
 inline void bw_stack_bwd_d(const StackBwd& p, const StackBwd& k, hipStream_t st) {
   const int t0 = (p.rows + 31) / 32, t1 = (k.rows + 31) / 32;
-  bw_stack_bwd_kernel<D><<<t0 + t1, 64 * stack_waves(D), (size_t)stack_vec_floats(D, p.f) * 4, st>>>(p, k, t0);
+  const dim3 grid(t0 + t1), block(64 * stack_waves(D));
+  const size_t lds = (size_t)stack_vec_floats(D, p.f) * 4;
+  if constexpr (D == 128 || D == 64) { if (t0 + t1 > kStackManyTiles) { bw_stack_bwd_kernel<D, true><<<grid, block, lds, st>>>(p, k, t0); return; } }
+  bw_stack_bwd_kernel<D, false><<<grid, block, lds, st>>>(p, k, t0);
 }
 
 }  // namespace bw
