@@ -11,7 +11,9 @@
 // the FFN's middle, three products back, attention back, two LayerNorms back) a block of the headline batch
 // (512 000 rows of width 128) moved 18.8 KB per token beside its parameter gradients in 2.1 ms; here it is 7.8-8.2 KB
 // in 0.85 ms (0.84 to 0.87 by box): 4.8 TB/s, where a large copy reaches 5.0.  Memory and the vector unit add up: with a third of its stores
-// left out it took 0.80 instead of 0.90 ms, and with 9 650 instead of 10 800 vector instructions per tile (beside 808 products) 0.84.
+// left out it took 0.80 instead of 0.90 ms, and with 9 650 instead of 10 800 vector instructions per tile (beside 808 products) 0.84.  The stream's waits
+// waited for the records' stores with it (step of the headline model 4169 -> 4100 us without that), a segment's fragments came out of LDS two at a time
+// (four: 4079), and q, k, v, which the tile reads again, passed by the caches (now not: 0.2 % there, 1 % of a step of 128 short users).
 //
 // Tile blocks.  A tensor of F features that the parameter gradients read is stored as [F / 16][1 KiB] per tile: 16
 // features of 32 tokens, 32 bytes per token, as the lanes hold them (lane half hi: features 4 hi .. + 3 and
@@ -179,6 +181,23 @@ __device__ __forceinline__ void norm_backward(f32x16 (&x)[NT], f32x16 (&dn)[NT],
     for (int r = 0; r < 16; ++r) x[t][r] = fmaf(x[t][r], c2, fmaf(dn[t][r], rstd, c1));      // rstd (dn - mean(dn) - x mean(dn x))
 }
 
+// use(s, fragment s) for the stream's current segment, four fragments on their way out of LDS (the compiler keeps two, and each pair of
+// products waited out the latency)
+template <int NG, typename WS, typename F>
+__device__ __forceinline__ void segment_fragments(const WS& ws, const F& use) {
+  constexpr int AH = NG < 4 ? NG : 4;
+  bf16x8 fr[AH];
+#pragma unroll
+  for (int s = 0; s < AH; ++s) fr[s] = ws.template frag<bf16x8>(s);
+#pragma unroll
+  for (int s = 0; s < NG; ++s) {
+    __builtin_amdgcn_sched_barrier(0x6);
+    use(s, fr[s % AH]);
+    if (s + AH < NG) fr[s % AH] = ws.template frag<bf16x8>(s + AH);
+  }
+  __builtin_amdgcn_sched_barrier(0x6);
+}
+
 // W: registers of a score tile that one group can occupy (K <= 2 W)
 template <int D, int DH, int W>
 __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const BlockBwParams p) {
@@ -203,6 +222,8 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   // records and tile blocks are addressed as buffers: with 64-bit addresses every access cost the vector unit two or three instructions
   const TileBuffer recb(rec, rc.size * 1024);
   auto put_rec = [&](int base, int g, bf16x8 v) { recb.put_once(g & 1 ? lane1 : lane0, (base + g) * 1024, __builtin_bit_cast(u32x4, v)); };      // (base is even)
+  // (q, k and v are read again by this tile; everything else by a later launch only)
+  auto keep_rec = [&](int base, int g, bf16x8 v) { recb.put(g & 1 ? lane1 : lane0, (base + g) * 1024, __builtin_bit_cast(u32x4, v)); };
   auto get_rec = [&](int base, int g) -> bf16x8 { return __builtin_bit_cast(bf16x8, recb.get(g & 1 ? lane1 : lane0, (base + g) * 1024)); };
   struct Token { uint32_t slot; int u, tg, jj; bool stored; long long row; };
   auto locate = [&](uint32_t first) {
@@ -271,18 +292,22 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
     if (c < p.f) vec[oBf + c] = (float)vf[k];
   }
   __syncthreads();
-  auto product = [&](f32x16& acc, const bf16x8 (&b)[NG]) {      // acc += (this segment's 32 output features) b
-#pragma unroll
-    for (int s = 0; s < NG; ++s) acc = E::mma(ws.template frag<bf16x8>(s), b[s], acc);
-    ws.advance();
+  // The stream's waits leave the records' stores alone: of those issued since the panel due was requested, two panels ago, at least
+  // these many may still be on their way (in the order of the stream: Q, K, V of a feature tile with two stores behind each and two
+  // of o; the output projection, the last of which has four stores in two panels of two segments; a hidden chunk's four; two in front of
+  // each product that takes dq, dk, dv back).  Waiting for them as well, a chunk could not end before its stores had.
+  typedef std::integral_constant<int, 8> Attn;
+  typedef std::integral_constant<int, PSEG == 2 ? 4 : D == 64 ? 8 : 0> Hidden;
+  typedef std::integral_constant<int, 6> Back;
+  auto fragments = [&](auto&& use) { segment_fragments<NG>(ws, use); };
+  auto product = [&](f32x16& acc, const bf16x8 (&b)[NG], auto younger) {      // acc += (this segment's 32 output features) b
+    fragments([&](int s, const bf16x8 w) { acc = E::mma(w, b[s], acc); });
+    ws.template advance<D >= 64 ? decltype(younger)::value : 0>();
     settle(acc);
   };
-  auto spread = [&](f32x16 (&acc)[NT], const bf16x8 (&b)[2]) {  // acc += (all output features of 32 contracted ones) b
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-      for (int g = 0; g < 2; ++g) acc[t] = E::mma(ws.template frag<bf16x8>(2 * t + g), b[g], acc[t]);
-    ws.advance();
+  auto spread = [&](f32x16 (&acc)[NT], const bf16x8 (&b)[2], auto younger) {  // acc += (all output features of 32 contracted ones) b
+    fragments([&](int s, const bf16x8 w) { acc[s / 2] = E::mma(w, b[s & 1], acc[s / 2]); });
+    ws.template advance<D >= 64 ? decltype(younger)::value : 0>();
   };
   // pieces of 32 features through LDS: in as the lanes hold them, out with lane = feature (tokens 16 g ..)
   const int put = j * 32 + hi * 16, put1 = 1024 + (j ^ 4) * 32 + hi * 16, get = tile_tr_offset(lane, 4 * hi);
@@ -375,23 +400,23 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
       bf16x8 qop[2], kop[2];
       {
         f32x16 q = bias_tile(vec + oBq, ft, hi);
-        product(q, nop);
+        product(q, nop, Attn{});
         q *= qscale;
 #pragma unroll
-        for (int g = 0; g < 2; ++g) { qop[g] = E::pack(q, g); put_rec(rc.qkv, 2 * ft + g, qop[g]); }
+        for (int g = 0; g < 2; ++g) { qop[g] = E::pack(q, g); keep_rec(rc.qkv, 2 * ft + g, qop[g]); }
       }
       {
         f32x16 k = splat16(0.f);
-        product(k, nop);
+        product(k, nop, Attn{});
 #pragma unroll
-        for (int g = 0; g < 2; ++g) { kop[g] = E::pack(k, g); put_rec(rc.qkv, NG + 2 * ft + g, kop[g]); }
+        for (int g = 0; g < 2; ++g) { kop[g] = E::pack(k, g); keep_rec(rc.qkv, NG + 2 * ft + g, kop[g]); }
       }
       {
         f32x16 v = bias_tile(vec + oBv, ft, hi);
-        product(v, nop);
+        product(v, nop, Attn{});
         bf16x8 vop[2];
 #pragma unroll
-        for (int g = 0; g < 2; ++g) { vop[g] = E::pack(v, g); put_rec(rc.qkv, 2 * NG + 2 * ft + g, vop[g]); }
+        for (int g = 0; g < 2; ++g) { vop[g] = E::pack(v, g); keep_rec(rc.qkv, 2 * NG + 2 * ft + g, vop[g]); }
         turn_in(2, vop);
       }
       __builtin_amdgcn_wave_barrier();
@@ -425,7 +450,7 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       x[t] += bias_tile(vec + oBo, t, hi);
-      product(x[t], oop);
+      if (t + 1 < NT) product(x[t], oop, Attn{}); else product(x[t], oop, Hidden{});
     }
     take_upstream(left, valid);
 #pragma unroll
@@ -451,11 +476,9 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
     // FFN, 32 hidden features at a time: values and gradient formed, used and written out
     for (int c = 0; c < NC; ++c) {
       f32x16 v = bias_tile(vec + oBf, c, hi), g = splat16(0.f);
-      product(v, nop);
-#pragma unroll
-      for (int s = 0; s < NG; ++s)
-        g = E::mma(ws.template frag<bf16x8>(s), s < PARK ? *(const bf16x8*)(park + s * 1024) : dyop[s], g);
-      ws.advance();
+      product(v, nop, Hidden{});
+      fragments([&](int s, const bf16x8 w) { g = E::mma(w, s < PARK ? *(const bf16x8*)(park + s * 1024) : dyop[s], g); });
+      ws.template advance<Hidden::value>();
       settle(g);
       if (p.act == LONGER_ACT_RELU) {
 #pragma unroll
@@ -471,7 +494,7 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
         put_rec(rc.dh, 2 * c + q, hop[q]);
         put_rec(rc.a, 2 * c + q, E::pack(v, q));
       }
-      spread(dn, hop);
+      spread(dn, hop, Hidden{});
     }
   }
 #pragma unroll
@@ -508,7 +531,7 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
     }
     {
       f32x16 d = splat16(0.f);
-      product(d, nop);
+      product(d, nop, Back{});
 #pragma unroll
       for (int g = 0; g < 2; ++g) dop[g] = E::pack(d, g);
     }
@@ -612,7 +635,7 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
         op[g] = E::pack(m == 0 ? dq : m == 1 ? dk : dv, g);
         put_rec(rc.qkv, m * NG + 2 * ft + g, op[g]);
       }
-      spread(dn, op);
+      spread(dn, op, Back{});
     }
   }
 

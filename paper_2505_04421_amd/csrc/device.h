@@ -234,17 +234,16 @@ __device__ __forceinline__ void wait_vmcnt() {
 //
 // Ordering invariant behind the hand-counted waits.  The stream's loads are inline assembly, so
 // the compiler's own wait-count bookkeeping does not see them; this struct counts them itself.
-// Vector-memory LOADS of a wave return in issue order, and the counter a wait tests (vmcnt) counts
-// the wave's outstanding loads, the compiler's ordinary global loads included.  "At most N
-// outstanding" therefore proves that everything issued before the last N loads has landed.  An
-// ordinary load that the compiler issues between two panels only makes the count larger than the
-// stream assumes, so a wait for N can only wait longer than needed, never too little; and the
-// compiler's own waits for its loads (which it believes are the only ones) are waits for a count
-// that the stream's younger loads can only push up, so they too err on the strict side.  What
-// breaks the argument is a global STORE inside the loop: stores also count in vmcnt on this
-// target but may retire out of order with respect to loads.  A mode that stores inside its loop
-// (the K/V projection) sets DRAIN and always waits for zero.  Every other mode stores only after
-// its last advance() and a wait for zero.
+// Vector-memory operations of a wave, stores included, are reported complete in the order of issue (flat
+// operations excepted; none is used here), and the counter a wait tests (vmcnt) counts the wave's outstanding
+// ones, the compiler's ordinary loads and stores among them.  "At most N outstanding" therefore proves
+// that everything issued before the last N operations has landed.  An ordinary operation that the
+// compiler issues between two panels only makes the count larger than the stream assumes, so a wait
+// for N can only wait longer than needed, never too little; and the compiler's own waits for its loads
+// (which it believes are the only ones) are waits for a count that the stream's younger loads can only
+// push up, so they too err on the strict side.  A loop that stores in every step thus waits for those
+// stores with each panel: advance<YOUNGER>() counts them in where their number is known.  The K/V
+// projection, whose stores depend on the row, sets DRAIN and always waits for zero.
 template <int SEGV, int PSEG, int NB, bool DRAIN, int NTHR = kThreads>
 struct WStream {
   static constexpr int PANV = SEGV * PSEG;              // 16-byte vectors per panel
@@ -273,8 +272,8 @@ struct WStream {
       slot_issue = slot_issue + 1 == NB ? 0 : slot_issue + 1;
     }
   }
-  // DRAIN: a mode that stores to global memory inside its loop (loads and stores may
-  // retire out of order with respect to each other) always waits for everything.
+  // DRAIN: a mode that stores to global memory inside its loop, a number of times that
+  // depends on the row: it always waits for everything.
   __device__ __forceinline__ void init(uint4* lds_, const void* gbase, int total_segments) {
     lds = lds_; total = (total_segments + PSEG - 1) / PSEG; step = 0; sub = 0; issued = 0; slot_issue = 0; slot_cur = 0;
     const int tid = threadIdx.x;
@@ -289,14 +288,17 @@ struct WStream {
     else wait_vmcnt<0>();
     __syncthreads();
   }
-  // the current segment has been consumed by this wave: move to the next one
+  // The current segment has been consumed by this wave: move to the next one.  YOUNGER: vector-memory operations other than the stream's that
+  // this wave has issued for certain since the panel now due was requested (NPRE panels ago).  Completion is reported in
+  // the order of issue, stores included, so that many more may be outstanding.
+  template <int YOUNGER = 0>
   __device__ __forceinline__ void advance() {
     if (PSEG > 1 && ++sub < PSEG) return;      // still inside the panel: nothing to wait for
     sub = 0;
     ++step;
     slot_cur = slot_cur + 1 == NB ? 0 : slot_cur + 1;
     // panels step .. step+NPRE-1 are in flight (when that many remain): the oldest must have landed
-    if (!DRAIN && step + NPRE <= total) wait_vmcnt<(NPRE - 1) * NSTAGE>();
+    if (!DRAIN && step + NPRE <= total) wait_vmcnt<(NPRE - 1) * NSTAGE + YOUNGER>();
     else wait_vmcnt<0>();
     __syncthreads();               // everyone sees panel `step`; everyone is done with `step - 1`
     issue();                       // into the buffer that held panel step - 1
