@@ -1938,11 +1938,16 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
     else { t.q = qkv; t.qpitch = 3 * d; t.k = qkv + d; t.v = qkv + 2 * d; t.kvpitch = 3 * d; t.kdesc = qdesc; t.nk = s.n; }
     return t;
   };
-  auto set_attn = [&](int which, int l, __bf16* out, int pitch, __bf16* dk, __bf16* dv) -> int {
+  auto attn_forward = [&](int l) -> int {
     float2* stat = (float2*)of(w.stat, l);
-    if (s.dh == 16) set_attn_launch<16>(st, which, attn(l), dob, d, out, pitch, dk, dv, stat);
-    else set_attn_launch<32>(st, which, attn(l), dob, d, out, pitch, dk, dv, stat);
-    return launched(which ? "attention backward" : "attention");
+    if (s.dh == 16) set_attn_forward<16>(st, attn(l), o, d, stat); else set_attn_forward<32>(st, attn(l), o, d, stat);
+    return launched("attention");
+  };
+  auto attn_backward = [&](int l, int dqpitch, __bf16* dk, __bf16* dv, int dkvpitch) -> int {
+    float2* stat = (float2*)of(w.stat, l);
+    if (s.dh == 16) set_attn_backward<16>(st, attn(l), dob, d, dqkv, dqpitch, dk, dv, dkvpitch, stat);
+    else set_attn_backward<32>(st, attn(l), dob, d, dqkv, dqpitch, dk, dv, dkvpitch, stat);
+    return launched("attention backward");
   };
   auto fwd = [&](const StackFwd& p, const StackFwd& k) -> int {
     if (d == 32) bw_stack_fwd_32(p, k, st); else if (d == 64) bw_stack_fwd_64(p, k, st);
@@ -1960,7 +1965,7 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
     p.rows = (int)rq; p.f = f; p.act = c->act; p.eps = c->ln_eps;
     if (l >= 0) {
       const longer_block& b = blk(l);
-      BW_TRY(set_attn(0, l, o, 0, nullptr, nullptr));
+      BW_TRY(attn_forward(l));
       p.wstream = stream_at(sg.fwd_tail(l));
       p.x = xs(l); p.o = o; p.bo = bf(b.bo); p.ln2_g = bf(b.ln2_g); p.ln2_b = bf(b.ln2_b); p.b1 = bf(b.b1); p.b2 = bf(b.b2);
       p.desc = qdesc; p.xmid = (float*)of(w.xmid, l); p.y = xs(l + 1); p.rec = (__bf16*)of(w.rec, l);
@@ -1994,8 +1999,7 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
     p.rows = (int)rq; p.f = f; p.act = c->act; p.eps = c->ln_eps;
     if (l <= last) {
       // (the cross layer's keys are rows of their own; a self layer's dq, dk, dv lie side by side)
-      BW_TRY(set_attn(1, l, dqkv, l ? 3 * d : d, nullptr, nullptr));
-      BW_TRY(l ? set_attn(2, l, nullptr, 3 * d, dqkv + d, dqkv + 2 * d) : set_attn(2, l, nullptr, 2 * d, dkv, dkv + d));
+      BW_TRY(l ? attn_backward(l, 3 * d, dqkv + d, dqkv + 2 * d, 3 * d) : attn_backward(l, d, dkv, dkv + d, 2 * d));
       p.mats = l ? 3 : 1; p.wstream = stream_at(sg.bwd_tail(l));
       p.dqkv = dqkv; p.ldq = p.mats * d; p.x = xs(l); p.ln1_g = bf(blk(l).ln1_g); p.dxm_in = dxm;
       p.rec1 = (__bf16*)of(w.rec, l); p.rec1_size = r.size; p.rec1_dqkv = r.qkv; p.dx = dy;

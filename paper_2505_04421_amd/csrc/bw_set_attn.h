@@ -9,9 +9,12 @@
 // row-major LDS tiles by the transposing LDS read.
 //
 // What bounds it: the exponentials and the score arithmetic around them (about 60 vector instructions per
-// 32 x 32 scores against 4-6 matrix instructions, half empty at head width 16).  Row-per-thread loops over LDS rows, the
+// 32 x 32 scores against 4-6 matrix instructions, half empty at head width 16), and, with two to nine of these squares a wave, what a workgroup does
+// before its first: requests, addresses, the tiles' ranges.  Row-per-thread loops over LDS rows, the
 // kernels before these, were chains of dependent LDS reads: forward / query side / key side at the headline batch
-// (256 users, 108 queries, 258 keys in the cross layer and 108 in three self layers) 276 / 322 / 336 us, now 86 / 125 / 111.
+// (256 users, 108 queries, 258 keys in the cross layer and 108 in three self layers) 276 / 322 / 336 us, these 86 / 125 / 111 as kernels of their
+// own; both sides in one 195, with their start made cheaper (ranges without LDS, all requests ahead of the first use, 32-bit addresses, no zeros behind the last row)
+// and a self layer's probabilities alone held, 167 and the forward 80.
 #pragma once
 #include "bw_common.h"
 
@@ -127,69 +130,98 @@ __device__ __forceinline__ void store_row(__bf16* p, const f32x16& acc, float w,
     *(bf16x4*)(p + 8 * q + 4 * hi) = t;
   }
 }
-// n rows of a head on their way to LDS (at most N, n > 0), zeros up to the next multiple of 32
+// n rows of a head on their way to LDS (at most N, n > 0); behind them the last one again, whose weights there are exact zeros
 template <int DH, int N>
 struct StagedRows {
   static constexpr int CP = DH / 8, NI = (N * CP + 255) / 256;
   bf16x8 v[NI];
-  __device__ __forceinline__ void request(const __bf16* src, size_t pitch, int n) {
+  __device__ __forceinline__ void request(const __bf16* src, int pitch, int n) {
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int c = threadIdx.x + 256 * i;
-      v[i] = *(const bf16x8*)(src + (size_t)min(c / CP, n - 1) * pitch + 8 * (c % CP));
+      v[i] = *(const bf16x8*)((const char*)src + (uint32_t)(2 * (min(c / CP, n - 1) * pitch + 8 * (c % CP))));
     }
   }
-  __device__ __forceinline__ void put(__bf16* dst, int n) const {
-    const int padded = (n + 31) / 32 * 32;
+  __device__ __forceinline__ void put(__bf16* dst) const {
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int c = threadIdx.x + 256 * i;
-      if (c < padded * CP) *(bf16x8*)(dst + 8 * c) = keep_if(v[i], c / CP < n);
+      if (256 * (i + 1) <= N * CP || c < N * CP) *(bf16x8*)(dst + 8 * c) = v[i];
     }
   }
 };
 
-// Keys of a workgroup's (user, head) staged in LDS with their positions and each 32-key tile's smallest and largest one.
-template <int DH>
-struct KeyTiles {
-  __bf16 k[kAttnChunk * DH], v[kAttnChunk * DH];
-  int pos[kAttnChunk], least[kAttnChunk / 32], most[kAttnChunk / 32];
-};
-template <int DH>
-__device__ __forceinline__ void stage_keys(KeyTiles<DH>& t, const SetAttn& a, int u, int h, int c0, int n) {
-  const size_t row0 = (size_t)u * a.nk + c0;
-  constexpr int NT = (kAttnChunk / 32 + 3) / 4;      // key tiles of a wave
-  StagedRows<DH, kAttnChunk> k, v;
-  k.request(a.k + row0 * a.kvpitch + h * DH, a.kvpitch, n);
-  v.request(a.v + row0 * a.kvpitch + h * DH, a.kvpitch, n);
-  const int lane = threadIdx.x & 63, l32 = lane & 31, wave = threadIdx.x >> 6;
-  int desc[NT];
-#pragma unroll
-  for (int i = 0; i < NT; ++i) desc[i] = a.kdesc[row0 + min((wave + 4 * i) * 32 + l32, n - 1)];
-  k.put(t.k, n);
-  v.put(t.v, n);
-#pragma unroll
-  for (int i = 0; i < NT; ++i) {
-    const int kt = wave + 4 * i, j = kt * 32 + l32, ks = j < n ? key_position(desc[i]) : kNone;
-    if (kt * 32 >= n) continue;
-    int lo = ks, up = ks;
-#pragma unroll
-    for (int o = 16; o > 0; o >>= 1) { lo = min(lo, __shfl_xor(lo, o, 64)); up = max(up, __shfl_xor(up, o, 64)); }
-    if (lane < 32) t.pos[j] = ks;
-    if (lane == 0) { t.least[kt] = lo; t.most[kt] = up; }
-  }
+// The smallest a and the largest b of 32 lanes (both lane halves hold the same): the lower half looks for the one and the upper for the
+// smallest ~b, within rows of 16 lanes by data-parallel moves, and a lane of each row is read out.  (Shuffles go through LDS: ten in a row,
+// a tenth of a workgroup's life.)
+struct Range { int least, most; };
+template <int CTRL> __device__ __forceinline__ int min_with(int v) { return min(v, __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false)); }
+__device__ __forceinline__ Range range_of(int a, int b) {
+  int v = threadIdx.x & 32 ? ~b : a;
+  v = min_with<0x140>(min_with<0x141>(min_with<0x4e>(min_with<0xb1>(v))));      // lane ^ 1, ^ 2, mirrored in 8, in 16
+  return {min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)), ~min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48))};
 }
-// Does any lane's query see a key of tile kt (`none` otherwise), and must single keys be tested?  (A lane without a
-// query sees nothing and wants nothing tested: what it computes is dropped.)
-template <int DH>
-__device__ __forceinline__ void tile_visibility(const KeyTiles<DH>& t, int kt, bool live, const Seen& see, bool* none, bool* test) {
-  const int lo = t.least[kt], up = t.most[kt];
-  *none = __builtin_amdgcn_ballot_w64(live && lo < see.end && up >= see.lo) == 0;
-  *test = __builtin_amdgcn_ballot_w64(live && (lo < see.lo || up >= see.end)) != 0;
+// all that was requested is on its way before any of it is used (what is used under a condition came to be requested under it)
+__device__ __forceinline__ void all_requested() { asm volatile("" ::: "memory"); }
+
+// Keys of a workgroup's (user, head) staged in LDS with their positions and each 32-key tile's smallest and largest one.
+template <int DH, int N>
+struct KeyTiles {
+  __bf16 k[N * DH], v[N * DH];
+  int pos[N], least[N / 32], most[N / 32];
+};
+// n of them (at most N) on their way there
+template <int DH, int N>
+struct StagedKeys {
+  static constexpr int NT = (N / 32 + 3) / 4;      // key tiles of a wave
+  StagedRows<DH, N> k, v;
+  int desc[NT];
+  __device__ __forceinline__ void request(const SetAttn& a, int u, int h, int c0, int n) {
+    const size_t row0 = (size_t)u * a.nk + c0;
+    k.request(a.k + row0 * a.kvpitch + h * DH, a.kvpitch, n);
+    v.request(a.v + row0 * a.kvpitch + h * DH, a.kvpitch, n);
+#pragma unroll
+    for (int i = 0; i < NT; ++i) desc[i] = a.kdesc[row0 + min(((int)(threadIdx.x >> 6) + 4 * i) * 32 + (int)(threadIdx.x & 31), n - 1)];
+  }
+  __device__ __forceinline__ void put(KeyTiles<DH, N>& t, int n) const {
+    const int lane = threadIdx.x & 63, l32 = lane & 31, wave = threadIdx.x >> 6;
+    k.put(t.k);
+    v.put(t.v);
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      const int kt = wave + 4 * i, j = kt * 32 + l32, ks = j < n ? key_position(desc[i]) : kNone;
+      if (kt * 32 >= n) continue;
+      const Range range = range_of(ks, ks);
+      if (lane < 32) t.pos[j] = ks;
+      if (lane == 0) { t.least[kt] = range.least; t.most[kt] = range.most; }
+    }
+  }
+};
+template <int DH, int N>
+__device__ __forceinline__ void stage_keys(KeyTiles<DH, N>& t, const SetAttn& a, int u, int h, int c0, int n) {
+  StagedKeys<DH, N> s;
+  s.request(a, u, h, c0, n);
+  all_requested();
+  s.put(t, n);
+}
+// What the 32 queries of a tile see: the positions that some of them sees (least .. most - 1), and those that all see (start .. end - 1).  A lane
+// without a query sees nothing and wants nothing tested: what it computes is dropped.
+struct Span { int least, most, start, end; };
+__device__ __forceinline__ Span span_of(bool live, const Seen& see) {
+  const Range some = range_of(live ? see.lo : kNone, live ? see.end : -kSeq), all = range_of(live ? see.end : kNone, live ? see.lo : -kSeq);
+  return {some.least, some.most, all.most, all.least};
+}
+// bit kt of `some`: a key of tile kt may be seen; of `test`: single keys must be tested
+struct Tiles { uint32_t some, test; };
+template <int DH, int N>
+__device__ __forceinline__ Tiles key_tiles(const KeyTiles<DH, N>& t, int n, const Span& q) {
+  const int lane = threadIdx.x & 63, kt = min(lane, N / 32 - 1), lo = t.least[kt], up = t.most[kt];
+  const bool in = lane * 32 < n;
+  return {(uint32_t)__builtin_amdgcn_ballot_w64(in && lo < q.most && up >= q.least), (uint32_t)__builtin_amdgcn_ballot_w64(in && (lo < q.start || up >= q.end))};
 }
 // scores of keys the lane's query does not see become -infinity
-template <int DH>
-__device__ __forceinline__ void mask_scores(f32x16& s, const KeyTiles<DH>& t, int kt, const Seen& see, int hi) {
+template <int DH, int N>
+__device__ __forceinline__ void mask_scores(f32x16& s, const KeyTiles<DH, N>& t, int kt, const Seen& see, int hi) {
   typedef int i32x4 __attribute__((ext_vector_type(4)));
   const unsigned width = (unsigned)(see.end - see.lo);
 #pragma unroll
@@ -204,7 +236,7 @@ __device__ __forceinline__ void mask_scores(f32x16& s, const KeyTiles<DH>& t, in
 // log-sum-exp of its scores in units of log 2 (+infinity without a key: every probability taken from it is zero).
 template <int DH>
 __global__ __launch_bounds__(256) void bw_set_attn_fwd_kernel(SetAttn a, __bf16* __restrict__ o, int d, float2* __restrict__ stat) {
-  __shared__ __attribute__((aligned(16))) KeyTiles<DH> t;
+  __shared__ __attribute__((aligned(16))) KeyTiles<DH, kAttnChunk> t;
   const int rounds = (a.nq + kAttnRows - 1) / kAttnRows;
   int u, h, rd;
   if (!attn_task(a, rounds, &u, &h, &rd)) return;
@@ -217,6 +249,7 @@ __global__ __launch_bounds__(256) void bw_set_attn_fwd_kernel(SetAttn a, __bf16*
   const bool live = qd >= 0;
   q.keep(live);
   const Seen see = query_sees(qd, a.gmask);
+  const Span span = span_of(live, see);
   const float c = 1.4426950408889634f * rsqrtf((float)DH);
   f32x16 acc;
 #pragma unroll
@@ -225,16 +258,15 @@ __global__ __launch_bounds__(256) void bw_set_attn_fwd_kernel(SetAttn a, __bf16*
   for (int c0 = 0; c0 < a.nk; c0 += kAttnChunk) {
     const int n = min(kAttnChunk, a.nk - c0);
     if (c0) __syncthreads();
-    stage_keys<DH>(t, a, u, h, c0, n);
+    stage_keys(t, a, u, h, c0, n);
     __syncthreads();
     if (i0 >= a.nq) continue;
-    for (int kt = 0; kt * 32 < n; ++kt) {
-      bool none, test;
-      tile_visibility<DH>(t, kt, live, see, &none, &test);
-      if (none) continue;
+    const Tiles tiles = key_tiles(t, n, span);
+    for (uint32_t left = tiles.some; left; left &= left - 1) {
+      const int kt = __builtin_ctz(left);
       f32x16 s = rows_times<DH>(t.k, 32 * kt, q, l32, hi);
       settle(s);                                       // (a branch follows: device.h)
-      if (test) mask_scores<DH>(s, t, kt, see, hi);
+      if (tiles.test >> kt & 1) mask_scores(s, t, kt, see, hi);
       float mt = s[0];
 #pragma unroll
       for (int r = 1; r < 16; ++r) mt = fmaxf(mt, s[r]);
@@ -256,16 +288,200 @@ __global__ __launch_bounds__(256) void bw_set_attn_fwd_kernel(SetAttn a, __bf16*
   if (hi == 0) stat[row * a.heads + h] = make_float2(any ? m + __builtin_amdgcn_logf(l) : __builtin_inff(), 0.f);
 }
 
-// Query side of the gradient: P_ij = exp2(c s_ij - lse_i), dP_ij = do_i . v_j, D_i = sum_j P_ij dP_ij (to stat[].y),
-// dq_i = sum_j P_ij (dP_ij - D_i) k_j / sqrt(DH).  Two passes over the keys: D first.  HELD: at most kHeldTiles key tiles (a
-// self layer's), whose P and dP stay in registers for the second pass, 128 of them beside the 38 that the rest takes, so that two or
-// three waves still share a SIMD: all query sides of the headline, small and raw-inputs models' steps 224 us with scores and
-// exponentials formed twice, 175 so.
+// Query side of the gradient: P_ij = exp2(c s_ij - lse_i), dP_ij = do_i . v_j, D_i = sum_j P_ij dP_ij,
+// dq_i = sum_j P_ij (dP_ij - D_i) k_j / sqrt(DH).  Two passes over the keys: D first.
+// At most kHeldTiles key tiles (a self layer's): their P stay in registers for the second pass, 64 of them, so that four waves still share a
+// SIMD; dP is formed again, a matrix product of a few cycles.  (With dP held as well, three waves a SIMD: three self layers of the headline batch 116 us, so 96.
+// Beyond four tiles, the first four held and the others formed again: ten registers spilled, and no faster.)
 constexpr int kHeldTiles = 4;
+template <int DH, int N>
+__device__ __forceinline__ void query_side_held(const KeyTiles<DH, N>& t, int nk, const RowFrag<DH>& q, const RowFrag<DH>& g, const Span& span, const Seen& see,
+                                                float lse, float c, float& D, f32x16& acc, int lane) {
+  const int l32 = lane & 31, hi = lane >> 5;
+  f32x16 P[kHeldTiles];
+  const Tiles tiles = key_tiles(t, nk, span);
+#pragma unroll
+  for (int kt = 0; kt < kHeldTiles; ++kt) {
+    if (!(tiles.some >> kt & 1)) continue;
+    P[kt] = rows_times<DH>(t.k, 32 * kt, q, l32, hi);
+    f32x16 dp = rows_times<DH>(t.v, 32 * kt, g, l32, hi);
+    settle(P[kt], dp);
+    if (tiles.test >> kt & 1) mask_scores(P[kt], t, kt, see, hi);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { P[kt][r] = __builtin_amdgcn_exp2f(fmaf(P[kt][r], c, -lse)); D = fmaf(P[kt][r], dp[r], D); }
+  }
+  D = sum_halves(D);
+#pragma unroll
+  for (int kt = 0; kt < kHeldTiles; ++kt) {
+    if (!(tiles.some >> kt & 1)) continue;
+    f32x16 dp = rows_times<DH>(t.v, 32 * kt, g, l32, hi);
+    settle(dp);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) P[kt][r] *= dp[r] - D;
+    add_transposed<DH>(acc, t.k, 32 * kt, P[kt], lane);
+  }
+}
+// one pass over n staged keys: D (SECOND: dq, D known)
+template <bool SECOND, int DH, int N>
+__device__ __forceinline__ void query_side_pass(const KeyTiles<DH, N>& t, int n, const RowFrag<DH>& q, const RowFrag<DH>& g, const Span& span, const Seen& see,
+                                                float lse, float c, float& D, f32x16& acc, int lane) {
+  const int l32 = lane & 31, hi = lane >> 5;
+  const Tiles tiles = key_tiles(t, n, span);
+  for (uint32_t left = tiles.some; left; left &= left - 1) {
+    const int kt = __builtin_ctz(left);
+    f32x16 s = rows_times<DH>(t.k, 32 * kt, q, l32, hi);
+    f32x16 dp = rows_times<DH>(t.v, 32 * kt, g, l32, hi);
+    settle(s, dp);
+    if (tiles.test >> kt & 1) mask_scores(s, t, kt, see, hi);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c, -lse));
+    if constexpr (!SECOND) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) D = fmaf(s[r], dp[r], D);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] *= dp[r] - D;
+      add_transposed<DH>(acc, t.k, 32 * kt, s, lane);
+    }
+  }
+}
+
+// Query rows of a workgroup's (user, head) staged in LDS, a tile a wave, with the upstream gradient of their output, their
+// statistics and what they see.
+constexpr int kQueryRows = 128;
+template <int DH>
+struct QueryTiles {
+  __bf16 q[kQueryRows * DH], g[kQueryRows * DH];
+  float lse[kQueryRows], D[kQueryRows];
+  int lo[kQueryRows], width[kQueryRows];
+  Span span[kQueryRows / 32];
+};
+template <int DH>
+struct StagedQueries {
+  StagedRows<DH, kQueryRows> q, g;
+  int qd;
+  float2 st;
+  __device__ __forceinline__ void request(const SetAttn& a, const __bf16* dob, int d, const float2* stat, int u, int h, int c0, int n) {
+    const size_t q0 = (size_t)u * a.nq + c0;
+    q.request(a.q + q0 * a.qpitch + h * DH, a.qpitch, n);
+    g.request(dob + q0 * d + h * DH, d, n);
+    const int ic = min((int)(threadIdx.x >> 6) * 32 + (int)(threadIdx.x & 31), n - 1);
+    qd = a.qdesc[q0 + ic];
+    st = stat[(q0 + ic) * a.heads + h];
+  }
+  __device__ __forceinline__ void put(QueryTiles<DH>& t, int gmask, int n) {
+    const int lane = threadIdx.x & 63, qt = threadIdx.x >> 6, i = qt * 32 + (lane & 31);
+    q.put(t.q);
+    g.put(t.g);
+    if (qt * 32 >= n) return;
+    if (i >= n) qd = -1;
+    // a row without a query: log-sum-exp +infinity, so that its probabilities are exact zeros untested
+    if (qd < 0) st = make_float2(__builtin_inff(), 0.f);
+    const Seen see = query_sees(qd, gmask);
+    const Span span = span_of(qd >= 0, see);
+    if (lane < 32) { t.lse[i] = st.x; t.D[i] = st.y; t.lo[i] = see.lo; t.width[i] = see.end - see.lo; }
+    if (lane == 0) t.span[qt] = span;
+  }
+};
+// Key side: dv_j = sum_i P_ij do_i, dk_j = sum_i P_ij (dP_ij - D_i) q_i / sqrt(DH), over n staged query rows; the lane's key stands at ks.
+template <int DH>
+__device__ __forceinline__ void key_side(const QueryTiles<DH>& t, int n, const RowFrag<DH>& kf, const RowFrag<DH>& vf, int ks, float c,
+                                         f32x16& gk, f32x16& gv, int lane) {
+  typedef int i32x4 __attribute__((ext_vector_type(4)));
+  const int l32 = lane & 31, hi = lane >> 5;
+  const Range keys = range_of(ks, ks != kNone ? ks : -kSeq - 1);
+  const Span span = t.span[min(lane, kQueryRows / 32 - 1)];
+  const uint32_t some = (uint32_t)__builtin_amdgcn_ballot_w64(lane * 32 < n && keys.least < span.most && keys.most >= span.least);      // (bit qt: may be seen by a query of the tile)
+  const uint32_t tested = (uint32_t)__builtin_amdgcn_ballot_w64(lane * 32 < n && (keys.least < span.start || keys.most >= span.end));
+  for (uint32_t left = some; left; left &= left - 1) {
+    const int qt = __builtin_ctz(left);
+    f32x16 p = rows_times<DH>(t.q, 32 * qt, kf, l32, hi);
+    f32x16 ds = rows_times<DH>(t.g, 32 * qt, vf, l32, hi);
+    settle(p, ds);
+    if (tested >> qt & 1) {
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const i32x4 width = *(const i32x4*)(t.width + 32 * qt + 8 * q4 + 4 * hi), lo = *(const i32x4*)(t.lo + 32 * qt + 8 * q4 + 4 * hi);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[4 * q4 + e] = (unsigned)(ks - lo[e]) < (unsigned)width[e] ? p[4 * q4 + e] : -__builtin_inff();
+      }
+    }
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const f32x4 lse = *(const f32x4*)(t.lse + 32 * qt + 8 * q4 + 4 * hi), D = *(const f32x4*)(t.D + 32 * qt + 8 * q4 + 4 * hi);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        p[4 * q4 + e] = __builtin_amdgcn_exp2f(fmaf(p[4 * q4 + e], c, -lse[e]));
+        ds[4 * q4 + e] = p[4 * q4 + e] * (ds[4 * q4 + e] - D[e]);
+      }
+    }
+    add_transposed<DH>(gv, t.g, 32 * qt, p, lane);
+    add_transposed<DH>(gk, t.q, 32 * qt, ds, lane);
+  }
+}
+
+// Both sides of a (user, head) whose queries fit one workgroup and whose keys fit LDS: every row is fetched once and D stays here.  (A launch a side,
+// as beyond these sizes: three self layers and the cross layer of the headline batch 137 + 99 us, so 96 + 71.)
+template <int DH, bool HELD>
+__global__ __launch_bounds__(256, 4) void bw_set_attn_bwd_kernel(SetAttn a, const __bf16* __restrict__ dob, int d, __bf16* __restrict__ dq, int dqpitch,
+                                                                            __bf16* __restrict__ dk, __bf16* __restrict__ dv, int dkvpitch,
+                                                                            const float2* stat) {
+  constexpr int N = HELD ? 32 * kHeldTiles : kAttnChunk;
+  __shared__ __attribute__((aligned(16))) KeyTiles<DH, N> t;
+  __shared__ __attribute__((aligned(16))) QueryTiles<DH> s;
+  int u, h, rd;
+  if (!attn_task(a, 1, &u, &h, &rd)) return;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5, wave = threadIdx.x >> 6;
+  {
+    StagedKeys<DH, N> keys;
+    StagedQueries<DH> queries;
+    queries.request(a, dob, d, stat, u, h, 0, a.nq);
+    keys.request(a, u, h, 0, a.nk);
+    all_requested();
+    queries.put(s, a.gmask, a.nq);
+    keys.put(t, a.nk);
+  }
+  __syncthreads();
+  const float scale = rsqrtf((float)DH), c = 1.4426950408889634f * scale;
+  if (32 * wave < a.nq) {
+    const int i = 32 * wave + l32, lo = s.lo[i], width = s.width[i];
+    const bool live = width != 0;      // (a query sees an interval of some length, no query one of none)
+    const Seen see = {lo, lo + width};
+    const Span span = s.span[wave];
+    RowFrag<DH> q = row_frag<DH>(s.q + i * DH, live, hi), g = row_frag<DH>(s.g + i * DH, live, hi);
+    const float lse = s.lse[i];
+    f32x16 acc = splat16(0.f);
+    float D = 0.f;
+    if constexpr (HELD) query_side_held(t, a.nk, q, g, span, see, lse, c, D, acc, lane);
+    else {
+      query_side_pass<false>(t, a.nk, q, g, span, see, lse, c, D, acc, lane);
+      D = sum_halves(D);
+      query_side_pass<true>(t, a.nk, q, g, span, see, lse, c, D, acc, lane);
+    }
+    settle(acc);
+    if (hi == 0) s.D[i] = live ? D : 0.f;
+    if (i < a.nq) store_row<DH>(dq + ((size_t)u * a.nq + i) * dqpitch + h * DH, acc, live ? scale : 0.f, hi);
+  }
+  __syncthreads();
+  for (int kt = wave; kt * 32 < a.nk; kt += 4) {
+    const int j = 32 * kt + l32, ks = t.pos[j];
+    const bool live = ks != kNone;
+    const RowFrag<DH> kf = row_frag<DH>(t.k + j * DH, live, hi), vf = row_frag<DH>(t.v + j * DH, live, hi);
+    f32x16 gk = splat16(0.f), gv = splat16(0.f);
+    key_side(s, a.nq, kf, vf, ks, c, gk, gv, lane);
+    settle(gk, gv);
+    if (j >= a.nk) continue;
+    const size_t row = (size_t)u * a.nk + j;
+    store_row<DH>(dk + row * dkvpitch + h * DH, gk, live ? scale : 0.f, hi);
+    store_row<DH>(dv + row * dkvpitch + h * DH, gv, live ? 1.f : 0.f, hi);
+  }
+}
+
+// The query side alone (D to stat[].y).
 template <int DH, bool HELD>
 __global__ __launch_bounds__(256, HELD ? 2 : 1) void bw_set_attn_bwd_q_kernel(SetAttn a, const __bf16* __restrict__ dob, int d,
                                                                 __bf16* __restrict__ dq, int dqpitch, float2* __restrict__ stat) {
-  __shared__ __attribute__((aligned(16))) KeyTiles<DH> t;
+  __shared__ __attribute__((aligned(16))) KeyTiles<DH, kAttnChunk> t;
   const int rounds = (a.nq + kAttnRows - 1) / kAttnRows;
   int u, h, rd;
   if (!attn_task(a, rounds, &u, &h, &rd)) return;
@@ -279,69 +495,29 @@ __global__ __launch_bounds__(256, HELD ? 2 : 1) void bw_set_attn_bwd_q_kernel(Se
   const bool live = qd >= 0;
   q.keep(live); g.keep(live);
   const Seen see = query_sees(qd, a.gmask);
+  const Span span = span_of(live, see);
   const float scale = rsqrtf((float)DH), c = 1.4426950408889634f * scale;
   f32x16 acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
   float D = 0.f;
   if constexpr (HELD) {
-    stage_keys<DH>(t, a, u, h, 0, a.nk);
+    stage_keys(t, a, u, h, 0, a.nk);
     __syncthreads();
     if (i0 >= a.nq) return;
-    f32x16 P[kHeldTiles], dP[kHeldTiles];
-    bool skip[kHeldTiles];
-#pragma unroll
-    for (int kt = 0; kt < kHeldTiles; ++kt) {
-      skip[kt] = true;
-      if (kt * 32 >= a.nk) continue;
-      bool none, test;
-      tile_visibility<DH>(t, kt, live, see, &none, &test);
-      if (none) continue;
-      skip[kt] = false;
-      P[kt] = rows_times<DH>(t.k, 32 * kt, q, l32, hi);
-      dP[kt] = rows_times<DH>(t.v, 32 * kt, g, l32, hi);
-      settle(P[kt], dP[kt]);
-      if (test) mask_scores<DH>(P[kt], t, kt, see, hi);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) { P[kt][r] = __builtin_amdgcn_exp2f(fmaf(P[kt][r], c, -lse)); D = fmaf(P[kt][r], dP[kt][r], D); }
-    }
-    D = sum_halves(D);
-#pragma unroll
-    for (int kt = 0; kt < kHeldTiles; ++kt) {
-      if (skip[kt]) continue;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) P[kt][r] *= dP[kt][r] - D;
-      add_transposed<DH>(acc, t.k, 32 * kt, P[kt], lane);
-    }
+    query_side_held(t, a.nk, q, g, span, see, lse, c, D, acc, lane);
   }
   for (int pass = HELD ? 2 : 0; pass < 2; ++pass) {
     for (int c0 = 0; c0 < a.nk; c0 += kAttnChunk) {
       const int n = min(kAttnChunk, a.nk - c0);
       if (pass == 0 || a.nk > kAttnChunk) {       // (a single chunk stays for the second pass)
         if (pass || c0) __syncthreads();
-        stage_keys<DH>(t, a, u, h, c0, n);
+        stage_keys(t, a, u, h, c0, n);
         __syncthreads();
       }
       if (i0 >= a.nq) continue;
-      for (int kt = 0; kt * 32 < n; ++kt) {
-        bool none, test;
-        tile_visibility<DH>(t, kt, live, see, &none, &test);
-        if (none) continue;
-        f32x16 s = rows_times<DH>(t.k, 32 * kt, q, l32, hi);
-        f32x16 dp = rows_times<DH>(t.v, 32 * kt, g, l32, hi);
-        settle(s, dp);
-        if (test) mask_scores<DH>(s, t, kt, see, hi);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c, -lse));
-        if (pass == 0) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) D = fmaf(s[r], dp[r], D);
-        } else {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) s[r] *= dp[r] - D;
-          add_transposed<DH>(acc, t.k, 32 * kt, s, lane);
-        }
-      }
+      if (pass == 0) query_side_pass<false>(t, n, q, g, span, see, lse, c, D, acc, lane);
+      else query_side_pass<true>(t, n, q, g, span, see, lse, c, D, acc, lane);
     }
     if (pass == 0) D = sum_halves(D);
   }
@@ -351,19 +527,12 @@ __global__ __launch_bounds__(256, HELD ? 2 : 1) void bw_set_attn_bwd_q_kernel(Se
   if (hi == 0) stat[row * a.heads + h].y = live ? D : 0.f;
 }
 
-// Key side: dv_j = sum_i P_ij do_i, dk_j = sum_i P_ij (dP_ij - D_i) q_i / sqrt(DH), over the user's query rows.
+// The key side alone, over the user's query rows (D from stat[].y).
 template <int DH>
 __global__ __launch_bounds__(256) void bw_set_attn_bwd_kv_kernel(SetAttn a, const __bf16* __restrict__ dob, int d,
                                                                  __bf16* __restrict__ dk, __bf16* __restrict__ dv, int dkvpitch,
-                                                                 const float2* __restrict__ stat) {
-  constexpr int CH = 128;       // staged query rows
-  __shared__ __attribute__((aligned(16))) struct {
-    __bf16 q[CH * DH], g[CH * DH];
-    float lse[CH], D[CH];
-    int lo[CH], width[CH];
-    int least[CH / 32], most[CH / 32], start[CH / 32], end[CH / 32];      // per 32-row tile: positions that some query sees, that all see
-  } t;
-  typedef int i32x4 __attribute__((ext_vector_type(4)));
+                                                                 const float2* stat) {
+  __shared__ __attribute__((aligned(16))) QueryTiles<DH> t;
   const int rounds = (a.nk + kAttnRows - 1) / kAttnRows;
   int u, h, rd;
   if (!attn_task(a, rounds, &u, &h, &rd)) return;
@@ -379,62 +548,15 @@ __global__ __launch_bounds__(256) void bw_set_attn_bwd_kv_kernel(SetAttn a, cons
   f32x16 gk, gv;
 #pragma unroll
   for (int r = 0; r < 16; ++r) { gk[r] = 0.f; gv[r] = 0.f; }
-  for (int c0 = 0; c0 < a.nq; c0 += CH) {
-    const int n = min(CH, a.nq - c0);
-    const size_t q0 = (size_t)u * a.nq + c0;
+  for (int c0 = 0; c0 < a.nq; c0 += kQueryRows) {
+    const int n = min(kQueryRows, a.nq - c0);
     if (c0) __syncthreads();
-    StagedRows<DH, CH> sq, sg;
-    sq.request(a.q + q0 * a.qpitch + h * DH, a.qpitch, n);
-    sg.request(dob + q0 * d + h * DH, d, n);
-    static_assert(CH == 128, "a query tile a wave");
-    const int qt = threadIdx.x >> 6, i = qt * 32 + l32, ic = min(i, n - 1);
-    int qd = a.qdesc[q0 + ic];
-    float2 st = stat[(q0 + ic) * a.heads + h];
-    sq.put(t.q, n);
-    sg.put(t.g, n);
-    if (qt * 32 < n) {
-      if (i >= n) qd = -1;
-      // a row without a query: log-sum-exp +infinity, so that its probabilities are exact zeros untested
-      if (qd < 0) st = make_float2(__builtin_inff(), 0.f);
-      const Seen see = query_sees(qd, a.gmask);
-      const bool is = qd >= 0;
-      int lo = is ? see.lo : kNone, up = is ? see.end : -kSeq, from = is ? see.lo : -kSeq, to = is ? see.end : kNone;
-#pragma unroll
-      for (int o = 16; o > 0; o >>= 1) {
-        lo = min(lo, __shfl_xor(lo, o, 64)); up = max(up, __shfl_xor(up, o, 64));
-        from = max(from, __shfl_xor(from, o, 64)); to = min(to, __shfl_xor(to, o, 64));
-      }
-      if (lane < 32) { t.lse[i] = st.x; t.D[i] = st.y; t.lo[i] = see.lo; t.width[i] = see.end - see.lo; }
-      if (lane == 0) { t.least[qt] = lo; t.most[qt] = up; t.start[qt] = from; t.end[qt] = to; }
-    }
+    StagedQueries<DH> s;
+    s.request(a, dob, d, stat, u, h, c0, n);
+    all_requested();
+    s.put(t, a.gmask, n);
     __syncthreads();
-    if (j0 >= a.nk) continue;
-    for (int qt = 0; qt * 32 < n; ++qt) {
-      if (__builtin_amdgcn_ballot_w64(live && ks >= t.least[qt] && ks < t.most[qt]) == 0) continue;     // seen by no query
-      const bool test = __builtin_amdgcn_ballot_w64(live && (ks < t.start[qt] || ks >= t.end[qt])) != 0;
-      f32x16 p = rows_times<DH>(t.q, 32 * qt, kf, l32, hi);
-      f32x16 ds = rows_times<DH>(t.g, 32 * qt, vf, l32, hi);
-      settle(p, ds);
-      if (test) {
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const i32x4 width = *(const i32x4*)(t.width + 32 * qt + 8 * q4 + 4 * hi), lo = *(const i32x4*)(t.lo + 32 * qt + 8 * q4 + 4 * hi);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) p[4 * q4 + e] = (unsigned)(ks - lo[e]) < (unsigned)width[e] ? p[4 * q4 + e] : -__builtin_inff();
-        }
-      }
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const f32x4 lse = *(const f32x4*)(t.lse + 32 * qt + 8 * q4 + 4 * hi), D = *(const f32x4*)(t.D + 32 * qt + 8 * q4 + 4 * hi);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          p[4 * q4 + e] = __builtin_amdgcn_exp2f(fmaf(p[4 * q4 + e], c, -lse[e]));
-          ds[4 * q4 + e] = p[4 * q4 + e] * (ds[4 * q4 + e] - D[e]);
-        }
-      }
-      add_transposed<DH>(gv, t.g, 32 * qt, p, lane);
-      add_transposed<DH>(gk, t.q, 32 * qt, ds, lane);
-    }
+    if (j0 < a.nk) key_side(t, n, kf, vf, ks, c, gk, gv, lane);
   }
   settle(gk, gv);
   if (j >= a.nk) return;
@@ -442,18 +564,24 @@ __global__ __launch_bounds__(256) void bw_set_attn_bwd_kv_kernel(SetAttn a, cons
   store_row<DH>(dv + row * dkvpitch + h * DH, gv, live ? 1.f : 0.f, hi);
 }
 
-// which: 0 forward (o), 1 query side (dq), 2 key side (dk, dv)
 template <int DH>
-static void set_attn_launch(hipStream_t st, int which, const SetAttn& a, const __bf16* dob, int d, __bf16* o_or_dq, int pitch,
-                            __bf16* dk, __bf16* dv, float2* stat) {
+static void set_attn_forward(hipStream_t st, const SetAttn& a, __bf16* o, int d, float2* stat) {
   const unsigned uh = (unsigned)((a.B + 7) / 8 * 8 * a.heads);      // (see attn_task)
-  const unsigned gq = uh * ((a.nq + kAttnRows - 1) / kAttnRows), gk = uh * ((a.nk + kAttnRows - 1) / kAttnRows);
-  if (which == 0) bw_set_attn_fwd_kernel<DH><<<gq, 256, 0, st>>>(a, o_or_dq, d, stat);
-  else if (which == 1) {
-    if (a.nk <= 32 * kHeldTiles) bw_set_attn_bwd_q_kernel<DH, true><<<gq, 256, 0, st>>>(a, dob, d, o_or_dq, pitch, stat);
-    else bw_set_attn_bwd_q_kernel<DH, false><<<gq, 256, 0, st>>>(a, dob, d, o_or_dq, pitch, stat);
+  bw_set_attn_fwd_kernel<DH><<<uh * ((a.nq + kAttnRows - 1) / kAttnRows), 256, 0, st>>>(a, o, d, stat);
+}
+template <int DH>
+static void set_attn_backward(hipStream_t st, const SetAttn& a, const __bf16* dob, int d, __bf16* dq, int dqpitch, __bf16* dk, __bf16* dv,
+                              int dkvpitch, float2* stat) {
+  const unsigned uh = (unsigned)((a.B + 7) / 8 * 8 * a.heads);
+  if (a.nq <= kQueryRows && a.nk <= kAttnChunk) {
+    if (a.nk <= 32 * kHeldTiles) bw_set_attn_bwd_kernel<DH, true><<<uh, 256, 0, st>>>(a, dob, d, dq, dqpitch, dk, dv, dkvpitch, stat);
+    else bw_set_attn_bwd_kernel<DH, false><<<uh, 256, 0, st>>>(a, dob, d, dq, dqpitch, dk, dv, dkvpitch, stat);
+    return;
   }
-  else bw_set_attn_bwd_kv_kernel<DH><<<gk, 256, 0, st>>>(a, dob, d, dk, dv, pitch, stat);
+  const unsigned gq = uh * ((a.nq + kAttnRows - 1) / kAttnRows), gk = uh * ((a.nk + kAttnRows - 1) / kAttnRows);
+  if (a.nk <= 32 * kHeldTiles) bw_set_attn_bwd_q_kernel<DH, true><<<gq, 256, 0, st>>>(a, dob, d, dq, dqpitch, stat);
+  else bw_set_attn_bwd_q_kernel<DH, false><<<gq, 256, 0, st>>>(a, dob, d, dq, dqpitch, stat);
+  bw_set_attn_bwd_kv_kernel<DH><<<gk, 256, 0, st>>>(a, dob, d, dk, dv, dkvpitch, stat);
 }
 
 }  // namespace bw
