@@ -7,7 +7,9 @@
 // cycles each), exact activations and waits for the weight ring.  Here Q, K and V are made by three waves at once, the
 // two heads by two, the hidden chunks by four (their contributions summed through LDS, in chunk order); every wave keeps the rows
 // themselves, so LayerNorm and the output projection need no exchange and a layer has four barriers.  Weight fragments come from
-// L2 into registers a layer ahead.  Forward pass of four users of 64 raw tokens (two layers): 50.6 -> 30.9 us.
+// L2 into registers a layer ahead.  Forward pass of four users of 64 raw tokens (two layers): 50.6 -> 30.9 us; with the waves of a second tile that has
+// no rows gone (they shared the first's matrix pipes) 25.8, of the stack's 15.7 us (37 000 cycles) two layers of five products 16, attention 6.5, the erf 4.6,
+// start and first weights 5 thousand.
 #pragma once
 #include "block_kernel.h"
 
@@ -30,60 +32,17 @@ __global__ void __launch_bounds__(64 * kFewWaves * few_tiles(MODE), 1) few_f32_k
   const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, hi = lane >> 5, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ts = wv / kFewWaves, wave = wv % kFewWaves, NC = p.FF / 32;
 
-  // ------------------------------------------------------------------ rows
-  f32x16 x[1][1], key[1][1];                         // key: the cross layer's key rows (their K and V made here)
+  // the user and its length: requested first, the weights behind it, and only then waited for
   const bool inline_kv = STACK && p.kst == nullptr;
-  bool valid, inrange;
-  int usr = 0, tu = 0, nkt0 = 0;
-  long long out_off = 0;
-  uint32_t slot = 0, tilebits = 0;
-  KeyRanges kr = {}, skr = {};
-  const int widx = W == 16 ? 0 : j / (2 * W);
-  uint32_t wmask[16 / W];
-#pragma unroll
-  for (int w = 0; w < 16 / W; ++w) wmask[w] = widx == w ? 0xffffffffu : 0u;
-  if (STACK) {
-    usr = (int)blockIdx.x;
-    const int a = 32 * ts + j;
-    inrange = a < p.rows_per_user;
-    int len = p.lens ? p.lens[usr] : p.L; len = min(max(len, 0), p.L);
-    tu = (len + p.K - 1) / p.K;
-    const bool glob = a < p.m;
-    const int i = a - p.m, i0 = first_slot(p.k, tu, p.q_learn);
-    valid = inrange && (glob || i >= i0);
-    out_off = p.X_ustride * usr + (long long)a * D;
-    const int tok = glob ? 0 : (p.q_learn ? tu - 1 : slot_token(i, p.k, tu, p.k_uni));
-    const int row = glob ? a : (p.gather_recent ? tok : i);
-    load_rows<float, 1>(x[0], glob ? p.src0.p : p.src1.p, 1, (glob ? p.src0.ustride : p.src1.ustride) * usr + (long long)row * D, valid, hi);
-    key[0][0] = splat16(0.f);
-    if (inline_kv) {
-      const bool there = glob || i < tu;             // key a: global token, then merged token
-      load_rows<float, 1>(key[0], glob ? p.src0.p : p.kv_k, 1, (glob ? p.src0.ustride : (long long)p.T * D) * usr + (long long)(glob ? a : i) * D, there, hi);
-    }
-    if (glob) { kr.lo1 = skr.lo1 = p.gmask_causal ? a : 0; kr.hi1 = p.KG; skr.hi1 = p.m; }
-    kr.lo2 = p.KG; kr.hi2 = p.KG + (glob ? tu : tok + 1);
-    skr.lo2 = p.m + i0; skr.hi2 = p.m + (glob ? p.k : i + 1);
-    kr.settle_for(valid); skr.settle_for(valid);
-    nkt0 = __builtin_amdgcn_readfirstlane((p.KG + tu + 31) / 32);
-  } else {
+  int usr = (int)blockIdx.x;
+  uint32_t slot = 0;
+  bool inrange = true;
+  if (!STACK) {
     slot = (uint32_t)blockIdx.x * 32u + (uint32_t)j;
-    const uint32_t gidx = slot >> __builtin_ctz(p.K);
-    usr = (int)(gidx / (uint32_t)p.T);
-    const int pos = (int)(gidx - (uint32_t)usr * (uint32_t)p.T) * p.K + (int)(slot & (uint32_t)(p.K - 1));
+    usr = (int)((slot >> __builtin_ctz(p.K)) / (uint32_t)p.T);
     inrange = usr < p.B;
-    int len = 0;
-    if (inrange) { len = p.lens ? p.lens[usr] : p.L; len = min(max(len, 0), p.L); }
-    tu = len;                                        // (the raw length here)
-    valid = inrange && pos < len;
-    load_rows<float, 1>(x[0], p.H, 1, ((long long)usr * p.L + pos) * D, valid, hi);
-    const uint32_t vb = (uint32_t)__ballot(valid);
-    const uint32_t gb = (p.K >= 32 ? 0xffffffffu : ((1u << p.K) - 1u)) << (p.K * (j / p.K));
-    tilebits = ((gb & vb) >> (4 * hi)) >> (2 * W * widx);
-    if (vb == 0) {                                   // nothing but padding
-      if (wave == 0 && inrange && (slot & (uint32_t)(p.K - 1)) == 0) store_rows<float, 1>(x[0], p.M_out, 1, (long long)gidx * D, false, hi);
-      return;
-    }
   }
+  int len = p.lens ? p.lens[inrange ? usr : 0] : p.L;
 
   // ------------------------------------------------------------------ weights: segments of four fragments (layouts: device.h)
   const char* wl = p.wbase;                          // the current block's stream
@@ -109,6 +68,58 @@ __global__ void __launch_bounds__(64 * kFewWaves * few_tiles(MODE), 1) few_f32_k
   const float* vec = reinterpret_cast<const float*>(vecl);
   const int nv = (9 * D + p.FF) / 4;
   f32x4 vq = reinterpret_cast<const f32x4*>(wl)[tid < nv ? tid : 0];
+
+  asm volatile("" ::: "memory");
+
+  // ------------------------------------------------------------------ rows
+  len = inrange ? min(max(len, 0), p.L) : 0;
+  f32x16 x[1][1], key[1][1];                         // key: the cross layer's key rows (their K and V made here)
+  bool valid;
+  int tu = 0, nk0 = 0;                               // nk0: keys of the cross layer
+  long long out_off = 0;
+  uint32_t tilebits = 0;
+  KeyRanges kr = {}, skr = {};
+  const int widx = W == 16 ? 0 : j / (2 * W);
+  uint32_t wmask[16 / W];
+#pragma unroll
+  for (int w = 0; w < 16 / W; ++w) wmask[w] = widx == w ? 0xffffffffu : 0u;
+  if (STACK) {
+    const int a = 32 * ts + j;
+    inrange = a < p.rows_per_user;
+    tu = (len + p.K - 1) / p.K;
+    const bool glob = a < p.m;
+    const int i = a - p.m, i0 = first_slot(p.k, tu, p.q_learn);
+    valid = inrange && (glob || i >= i0);
+    out_off = p.X_ustride * usr + (long long)a * D;
+    const int tok = glob ? 0 : (p.q_learn ? tu - 1 : slot_token(i, p.k, tu, p.k_uni));
+    const int row = glob ? a : (p.gather_recent ? tok : i);
+    load_rows<float, 1>(x[0], glob ? p.src0.p : p.src1.p, 1, (glob ? p.src0.ustride : p.src1.ustride) * usr + (long long)row * D, valid, hi);
+    key[0][0] = splat16(0.f);
+    if (inline_kv) {
+      const bool there = glob || i < tu;             // key a: global token, then merged token
+      load_rows<float, 1>(key[0], glob ? p.src0.p : p.kv_k, 1, (glob ? p.src0.ustride : (long long)p.T * D) * usr + (long long)(glob ? a : i) * D, there, hi);
+    }
+    if (glob) { kr.lo1 = skr.lo1 = p.gmask_causal ? a : 0; kr.hi1 = p.KG; skr.hi1 = p.m; }
+    kr.lo2 = p.KG; kr.hi2 = p.KG + (glob ? tu : tok + 1);
+    skr.lo2 = p.m + i0; skr.hi2 = p.m + (glob ? p.k : i + 1);
+    kr.settle_for(valid); skr.settle_for(valid);
+    nk0 = __builtin_amdgcn_readfirstlane(p.KG + tu);
+    // a second tile without rows or keys: its waves leave the matrix pipes to the first's (a barrier waits for those still there only)
+    if (ts > 0 && p.rows_per_user <= 32 && !(inline_kv && nk0 > 32)) return;
+  } else {
+    const uint32_t gidx = slot >> __builtin_ctz(p.K);
+    const int pos = (int)(gidx - (uint32_t)usr * (uint32_t)p.T) * p.K + (int)(slot & (uint32_t)(p.K - 1));
+    tu = len;                                        // (the raw length here)
+    valid = inrange && pos < len;
+    load_rows<float, 1>(x[0], p.H, 1, ((long long)usr * p.L + pos) * D, valid, hi);
+    const uint32_t vb = (uint32_t)__ballot(valid);
+    const uint32_t gb = (p.K >= 32 ? 0xffffffffu : ((1u << p.K) - 1u)) << (p.K * (j / p.K));
+    tilebits = ((gb & vb) >> (4 * hi)) >> (2 * W * widx);
+    if (vb == 0) {                                   // nothing but padding
+      if (wave == 0 && inrange && (slot & (uint32_t)(p.K - 1)) == 0) store_rows<float, 1>(x[0], p.M_out, 1, (long long)gidx * D, false, hi);
+      return;
+    }
+  }
 
   for (int layer = 0; layer < p.n_layers; ++layer) {
     const bool selfl = STACK && layer > 0, last = layer + 1 == p.n_layers;
@@ -136,6 +147,7 @@ __global__ void __launch_bounds__(64 * kFewWaves * few_tiles(MODE), 1) few_f32_k
       request(wr, wnext, 1 + role);                  // (every block after the first is in the fused layout)
     }
     __syncthreads();
+    if (STACK && ts > 0 && p.rows_per_user <= 32) return;      // (it had keys only)
     if (wave < 2) {                                  // a head each
       const int h = wave;
       const grp q[2] = {qkv[ts][0][2 * h][lane], qkv[ts][0][2 * h + 1][lane]};
@@ -146,16 +158,17 @@ __global__ void __launch_bounds__(64 * kFewWaves * few_tiles(MODE), 1) few_f32_k
         for (int g = 0; g < 2; ++g) S = E::mma(k[g], q[g], S);
         return S;
       };
-      auto values = [&](const grp (&v)[4], const grp (&pop)[4]) {
+      auto values = [&](const grp (&v)[4], const grp (&pop)[4], int n) {      // (the first n keys: the others' weights are zeros)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) acc = E::mma(v[g], pop[g], acc);
+        for (int g = 0; g < 4; ++g)
+          if (g == 0 || 8 * g < n) acc = E::mma(v[g], pop[g], acc);
       };
-      auto tile_of = [&](const KeyRanges& r, int kt, const grp (&k)[2], const grp (&v)[4]) {
+      auto tile_of = [&](const KeyRanges& r, int n, int kt, const grp (&k)[2], const grp (&v)[4]) {
         const uint32_t ab = ((range_bits(r.lo1, r.hi1, 32 * kt) | range_bits(r.lo2, r.hi2, 32 * kt)) >> (4 * hi)) & kTileBits;
         f32x16 S = keys(mask_tile(ab), k);
         grp pop[4];
         softmax_step<float, false>(S, 0u, mrun, lrun, acc, pop);
-        values(v, pop);
+        values(v, pop, n - 32 * kt);
       };
       if (!STACK) {
         const grp k[2] = {qkv[ts][1][2 * h][lane], qkv[ts][1][2 * h + 1][lane]};
@@ -163,13 +176,13 @@ __global__ void __launch_bounds__(64 * kFewWaves * few_tiles(MODE), 1) few_f32_k
         const f32x16 S = keys(splat16(0.f), k);
         grp pop[4];
         softmax_window<float, W>(S, widx, wmask, tilebits, mrun, lrun, acc, pop);
-        values(v, pop);
+        values(v, pop, 32);
       } else if (selfl || inline_kv) {
-        const int nkt = selfl ? (p.rows_per_user + 31) / 32 : nkt0;
-        for (int kt = 0; kt < nkt; ++kt) {
+        const int n = selfl ? p.rows_per_user : nk0;
+        for (int kt = 0; 32 * kt < n; ++kt) {
           const grp k[2] = {qkv[kt][1][2 * h][lane], qkv[kt][1][2 * h + 1][lane]};
           const grp v[4] = {qkv[kt][2][0][lane], qkv[kt][2][1][lane], qkv[kt][2][2][lane], qkv[kt][2][3][lane]};
-          tile_of(selfl ? skr : kr, kt, k, v);
+          tile_of(selfl ? skr : kr, n, kt, k, v);
         }
       } else {                                       // stored K / V fragments, the next tile's on their way
         const char* kb = p.kst + (size_t)usr * p.kv_ustride;
@@ -182,11 +195,11 @@ __global__ void __launch_bounds__(64 * kFewWaves * few_tiles(MODE), 1) few_f32_k
 #pragma unroll
           for (int g = 0; g < 4; ++g) vn[g] = *reinterpret_cast<const grp*>(vb + fo + g * 1024);
         };
-        if (nkt0 > 0) fetch(0);
-        for (int kt = 0; kt < nkt0; ++kt) {
+        if (nk0 > 0) fetch(0);
+        for (int kt = 0; 32 * kt < nk0; ++kt) {
           const grp k[2] = {kn[0], kn[1]}, v[4] = {vn[0], vn[1], vn[2], vn[3]};
-          if (kt + 1 < nkt0) fetch(kt + 1);
-          tile_of(kr, kt, k, v);
+          if (32 * (kt + 1) < nk0) fetch(kt + 1);
+          tile_of(kr, nk0, kt, k, v);
         }
       }
       settle(acc);

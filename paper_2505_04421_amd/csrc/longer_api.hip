@@ -624,7 +624,7 @@ static int check_input(const longer_config* cfg, const longer_input_weights* w, 
 }
 
 // Full precision at width 32 (few_f32_kernel.h).  The stack of users with at most two tiles: whole forward pass (K = 4, three layers), microseconds
-// with it / without, merge as it is: 256 users of 50 raw tokens 50 / 67, 512 of 64 80 / 111, 2048 of 64 286 / 396.  It makes the
+// with it / without, merge as it is: 256 users of 50 raw tokens 37 / 67, 512 of 64 62 / 111, 2048 of 64 219 / 396; with two tiles of rows (k = 40) 2048 of 64 318.  It makes the
 // cross layer's K and V itself when a user's global and merged tokens fit its two tiles.
 static bool few_stack(const Shape& s) { return few_f32_shape(s.main_fn) && s.n <= 64; }
 static bool few_stack_makes_kv(const longer_config* c, const Shape& s, int L) { return few_stack(s) && c->m + cdiv(L, c->K) <= 64; }
