@@ -71,19 +71,27 @@ __device__ __forceinline__ void act_exact_both(float v, int act, float* a, float
   *da = c + v * 0.39894228040143268f * e;
 }
 
-// sixteen features of a row-major row as an operand group, and back; zeros where it is not there (`row`: any that is; the
-// request is unconditional, see load_rows)
-__device__ __forceinline__ bf16x8 row_group(const __bf16* row, int g, int hi, bool there) {
-  const bf16x4 a = *(const bf16x4*)(row + 16 * g + 4 * hi), b = *(const bf16x4*)(row + 16 * g + 8 + 4 * hi);
-  const u32x4 v = __builtin_bit_cast(u32x4, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
-  u32x4 w;
+// Sixteen features of a row-major row as an operand group, and back; zeros where it is not there (`row`: any that is; the
+// request is unconditional, see load_rows).  A lane reads or writes sixteen bytes: its half's eight features, of which the lane halves
+// exchange four (pieces of eight bytes, 768 apart from lane to lane, cost the address unit twice as much).
+__device__ __forceinline__ u32x4 exchange_halves(u32x4 v) {
 #pragma unroll
-  for (int e = 0; e < 4; ++e) { const uint32_t one = v[e]; w[e] = there ? one : 0u; }
-  return __builtin_bit_cast(bf16x8, w);
+  for (int e = 0; e < 2; ++e) {
+    const uint32_t a = v[e], b = v[e + 2];
+    const auto x = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    v[e] = x[0]; v[e + 2] = x[1];
+  }
+  return v;
+}
+__device__ __forceinline__ bf16x8 row_request(const __bf16* row, int g, int hi) { return *(const bf16x8*)(row + 16 * g + 8 * hi); }
+__device__ __forceinline__ bf16x8 row_group(bf16x8 requested, bool there) {
+  u32x4 v = exchange_halves(__builtin_bit_cast(u32x4, requested));
+#pragma unroll
+  for (int e = 0; e < 4; ++e) { const uint32_t one = v[e]; v[e] = there ? one : 0u; }
+  return __builtin_bit_cast(bf16x8, v);
 }
 __device__ __forceinline__ void row_put(__bf16* row, int g, int hi, bf16x8 v) {
-  *(bf16x4*)(row + 16 * g + 4 * hi) = __builtin_shufflevector(v, v, 0, 1, 2, 3);
-  *(bf16x4*)(row + 16 * g + 8 + 4 * hi) = __builtin_shufflevector(v, v, 4, 5, 6, 7);
+  *(u32x4*)(row + 16 * g + 8 * hi) = exchange_halves(__builtin_bit_cast(u32x4, v));
 }
 // fp32 tile blocks: [tile][D / 8][64 lanes][4]
 // one feature tile of fp32 tile blocks: [tile][D / 8][64 lanes][4]
@@ -123,7 +131,10 @@ struct RecordOut {        // one tile's record
 // kernel, leaves a wave alone on its SIMD with all of the FFN's activation: 54 / 74 us forward / backward per layer at the
 // headline batch, 21 / 23 us in the small model.)  A layer's launch forward / backward, with each product's fragments requested
 // when it began and now: 53 / 94 and 49 / 74 us at the headline batch (864 tiles), 34 / 33 and 19 / 23 us on 203 tiles of width 128,
-// 13 / 14 and 10 / 11 us in the small model.
+// 13 / 14 and 10 / 11 us in the small model.  Rows of attention outputs and of dQ, dK, dV come and go sixteen bytes a lane, each from memory in one
+// wave and through LDS to the others: with every wave fetching all of them in pieces of eight bytes the address unit took 11 600 of a
+// backward workgroup's 47 900 cycles for them on 203 tiles of width 128, and a step of that model 1140 us instead of 1111, of the headline batch 3976 instead of
+// 3871, of the small model 278 instead of 268.
 __host__ __device__ constexpr int stack_waves(int d) { return d >= 256 ? 8 : 4; }
 template <int D>
 struct StackTile {
@@ -240,8 +251,8 @@ struct StackVectors {
 __host__ __device__ inline int stack_vec_floats(int d, int f) { return 9 * d + f; }
 
 // What bounds the two kernels: the chain of a tile at small batches; at the headline batch (864 tiles) the exact-erf activation
-// beside the products, and 3.3 KB (forward) and 5.5 KB (backward) of memory traffic per row: 46 and 71 us a launch with four and three
-// workgroups a compute unit, 50 and 73 with three and two.  MANY: see kStackManyTiles.
+// beside the products, and 3.3 KB (forward) and 5.5 KB (backward) of memory traffic per row: 37 and 56 us a launch (mean of five) with four and three
+// workgroups a compute unit.  MANY: see kStackManyTiles.
 template <int D, bool MANY>
 __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : MANY ? 4 : 2) void bw_stack_fwd_kernel(const StackFwd p0, const StackFwd p1, int tiles0) {
   using S = StackTile<D>;
@@ -267,10 +278,12 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : MANY ? 4 : 2) v
     load_rows<__bf16, 1>(one, p.x, 1, (long long)row * D + 32 * ft, in, hi);
     x = one[0];
   }
-  bf16x8 nop[NG];
+  bf16x8 nop[MANY ? 1 : NG], mine[2];                // (mine: this wave's part of the attention output)
+  int desc = 0;
   if (p.o) {
 #pragma unroll
-    for (int g = 0; g < NG; ++g) nop[g] = row_group(p.o + (size_t)(in ? row : 0) * D, g, hi, in);
+    for (int q = 0; q < 2; ++q) mine[q] = row_request(p.o + (size_t)(in ? row : 0) * D, 2 * ft + q, hi);
+    desc = p.desc[in ? row : 0];
   }
   const int head = p.o ? NT + 2 * NC : 0;          // first segment of the next layer's products
   s.request(s.at(p.o ? ft : head + min(wave, p.mats * NT - 1), 0));
@@ -304,19 +317,25 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : MANY ? 4 : 2) v
       for (int q = 0; q < 2; ++q) rec.put(at, 2 * ft + q, E::pack(h, q));
     }
     __syncthreads();
-    if (!MANY) s.take(nop);
+    if constexpr (!MANY) s.take(nop);
   };
-  auto operand = [&](int k) -> bf16x8 { return MANY ? ops[k][lane] : nop[k]; };
+  auto operand = [&](int k) -> bf16x8 { return MANY ? ops[k][lane] : nop[MANY ? 0 : k]; };
   if (p.o) {
     const BlockRecord at(D, p.f);
     const RecordOut rec(p.rec, tile, at.size, lane);
+    if (own) {
 #pragma unroll
-    for (int g = 0; g < NG; ++g)
-      if ((g >> 1) % WV == wave) rec.put(at.o, g, nop[g]);
-    __syncthreads();                               // `vec`
+      for (int q = 0; q < 2; ++q) {
+        const bf16x8 v = row_group(mine[q], in);
+        ops[2 * ft + q][lane] = v;
+        rec.put(at.o, 2 * ft + q, v);
+      }
+    }
+    __syncthreads();                               // `vec`, `ops`
+    if constexpr (!MANY) s.take(nop);
     x += bias_tile(vec + oBo, ft, hi);
     typename S::gchar* first = s.at(NT + 2 * min(wave, NC - 1), 0);
-    s.product(x, [&](int k) { return nop[k]; }, [&](int k) { s.fr[k] = s.load(first, k); });
+    s.product(x, operand, [&](int k) { s.fr[k] = s.load(first, k); });
     if (own) store_part<NT>(x, p.xmid, tile, ft, lane);
     normalise(0, oG2, oS2, rec, at.xh2);
     x += bias_tile(vec + oB2, ft, hi);
@@ -341,7 +360,7 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : MANY ? 4 : 2) v
         __builtin_amdgcn_sched_barrier(0x486);
       }
     }
-    const bool live = in && p.desc[in ? row : 0] >= 0;
+    const bool live = in && desc >= 0;
     settle(x);
 #pragma unroll
     for (int r = 0; r < 16; ++r) x[r] = live ? x[r] : 0.f;
@@ -391,17 +410,21 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : MANY ? 3 : 2) v
   }
   // fragment k of the products that bring dQ, dK, dV back (matrix m): 32 contracted features k / 2 of this wave's result tile
   auto back = [&](int m, int k) { s.fr[k] = s.load(s.at((k / 2) * p.mats + m, 2 * ft), k & 1); };
-  bf16x8 bop[NG];
-  auto rows_of = [&](int m, int k) { bop[k] = row_group(p.dqkv + (size_t)(in ? row : 0) * p.ldq + m * D, k, hi, in); };
+  bf16x8 mine[3][2];                               // this wave's part of dQ, dK, dV
   const int seg = p.dqkv ? NT * p.mats : 0;        // first segment of the FFN's products
   if (p.dqkv) {
 #pragma unroll
-    for (int k = 0; k < NG; ++k) { rows_of(0, k); back(0, k); }
+    for (int m = 0; m < 3; ++m)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) mine[m][q] = row_request(p.dqkv + (size_t)(in ? row : 0) * p.ldq + min(m, p.mats - 1) * D, 2 * ft + q, hi);
+#pragma unroll
+    for (int k = 0; k < NG; ++k) back(0, k);
     if (p.dxm_in) add = load_part<NT>(p.dxm_in, tile, ft, lane);
   } else {
     s.request(s.at(seg + 3 * min(wave, NC - 1), 0));
   }
-  if (p.xmid) xm = load_part<NT>(p.xmid, tile, ft, lane);
+  int desc = 0;
+  if (p.xmid) { xm = load_part<NT>(p.xmid, tile, ft, lane); desc = p.desc[in ? row : 0]; }
   {
     StackVectors<D, 3> v;
     if (p.dqkv) v.request(0, p.ln1_g, tid);
@@ -412,19 +435,34 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : MANY ? 3 : 2) v
   if (p.dqkv) {
     const RecordOut rec(p.rec1, tile, p.rec1_size, lane);
     typename S::gchar* first = s.at(seg + (p.xmid ? 3 * min(wave, NC - 1) : -1), 0);
+    // (through the buffers of what comes later: free until the barriers behind this)
+    static_assert(NG <= 4 * WV, "dV in the hidden chunks' place");
+    if (own) {
+#pragma unroll
+      for (int m = 0; m < 3; ++m)
+        if (m < p.mats) {
+          bf16x8 (*to)[64] = m == 0 ? ops : m == 1 ? ops2 : &hid[0][0][0];
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const bf16x8 v = row_group(mine[m][q], in);
+            to[2 * ft + q][lane] = v;
+            rec.put(p.rec1_dqkv + m * NG, 2 * ft + q, v);
+          }
+        }
+    }
+    __syncthreads();                               // (and `vec` is there)
     for (int m = 0; m < p.mats; ++m) {
       const bool end = m + 1 == p.mats;
+      bf16x8 (*from)[64] = m == 0 ? ops : m == 1 ? ops2 : &hid[0][0][0];
 #pragma unroll
       for (int k = 0; k < NG; ++k) {
-        dn = E::mma(s.fr[k], bop[k], dn);
-        if ((k >> 1) % WV == wave) rec.put(p.rec1_dqkv + m * NG, k, bop[k]);
-        rows_of(end ? m : m + 1, k);
+        dn = E::mma(s.fr[k], from[k][lane], dn);
         s.fr[k] = s.load(end ? first + k * 1024 : s.at((k / 2) * p.mats + m + 1, 2 * ft) + (k & 1) * 1024, 0);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
     settle(dn);
-    s.stats(0, x, p.eps, mean, rstd);              // (its barrier: `vec` is there)
+    s.stats(0, x, p.eps, mean, rstd);              // (its barrier: everybody is done with the buffers)
     s.norm_back(1, x, dn, vec + oG1, mean, rstd);
     x += add;
     const f32x16 one[1] = {x};
@@ -433,7 +471,7 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : MANY ? 3 : 2) v
   }
   const BlockRecord at(D, p.f);
   const RecordOut rec(p.rec, tile, at.size, lane);
-  const bool live = in && p.desc[in ? row : 0] >= 0;
+  const bool live = in && desc >= 0;
   s.stats(2, xm, p.eps, mean, rstd);               // (its barrier: `vec` is there)
   // (width 256: no registers for a second operand of all features, it is read from LDS)
   constexpr bool HELD = D <= 128 && !MANY;
@@ -524,9 +562,9 @@ void bw_stack_bwd_128(const StackBwd& p, const StackBwd& k, hipStream_t st);
 void bw_stack_fwd_256(const StackFwd& p, const StackFwd& k, hipStream_t st);
 void bw_stack_bwd_256(const StackBwd& p, const StackBwd& k, hipStream_t st);
 // Beyond one round of two workgroups a compute unit the operands of the products stay in LDS (MANY) instead of a wave's registers: four
-// workgroups fit forward (119 registers instead of 150) and three backward (160 instead of 224).  A training step of width 128 and 108 rows a user, 439,
-// 513, 642, 864, 1728 tiles, without / with it 643 / 646, 765 / 734, 842 / 818, 1037 / 1020, 1748 / 1721 us; width 64 and 104 rows, 520, 650,
-// 1664 tiles 353 / 334, 381 / 366, 732 / 716.
+// workgroups fit forward (118 registers instead of 149) and three backward (160 instead of 224).  A training step of width 128 and 108 rows a user, 257, 439,
+// 513, 642, 864, 1728 tiles, without / with it 660 / 662, 860 / 860, 1001 / 961, 1213 / 1185, 1509 / 1500, 2553 / 2524 us; width 64 and 104 rows, 260, 520, 650,
+// 1664 tiles 233 / 236, 320 / 301, 344 / 325, 658 / 636.
 constexpr int kStackManyTiles = 512;
 // k: the cross layer's key rows, beside its query rows in one launch (no rows: none).  Two launches of their own in either direction
 // were each the chain of a tile on a part of the chip.
