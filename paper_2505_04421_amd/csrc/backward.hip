@@ -263,13 +263,16 @@ __global__ __launch_bounds__(256, DUAL ? 2 : 4) void bw_gemm_kernel(GemmArgs g) 
         *(f32x4*)((float*)g.out + o + 4) = o1;
       } else if (DUAL && g.epi == EPI_FFN_MID) {
         bf16x8 oa;
+        auto both = [&](int act) {                    // (which activation: asked once, not between the chains of eight values)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          float av, dv;
-          act_both(v[e], g.act, &av, &dv);
-          oa[e] = (__bf16)av;
-          ob[e] = (__bf16)(v2[DUAL ? it : 0][e] * dv);
-        }
+          for (int e = 0; e < 8; ++e) {
+            float av, dv;
+            act_both(v[e], act, &av, &dv);
+            oa[e] = (__bf16)av;
+            ob[e] = (__bf16)(v2[DUAL ? it : 0][e] * dv);
+          }
+        };
+        if (g.act == LONGER_ACT_RELU) both(LONGER_ACT_RELU); else both(LONGER_ACT_GELU_ERF);
         *(bf16x8*)((__bf16*)g.out + o) = ob;
         *(bf16x8*)((__bf16*)g.out2 + o) = oa;
       } else {
@@ -433,13 +436,16 @@ __global__ __launch_bounds__(512, 1) void bw_rowgemm_kernel(GemmArgs g, int P) {
       bf16x8 ob;
       if (DUAL) {
         bf16x8 oa;
+        auto both = [&](int act) {                    // (which activation: asked once, not between the chains of eight values)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          float av, dv;
-          act_both(v[e], g.act, &av, &dv);
-          oa[e] = (__bf16)av;
-          ob[e] = (__bf16)(v2[DUAL ? it : 0][e] * dv);
-        }
+          for (int e = 0; e < 8; ++e) {
+            float av, dv;
+            act_both(v[e], act, &av, &dv);
+            oa[e] = (__bf16)av;
+            ob[e] = (__bf16)(v2[DUAL ? it : 0][e] * dv);
+          }
+        };
+        if (g.act == LONGER_ACT_RELU) both(LONGER_ACT_RELU); else both(LONGER_ACT_GELU_ERF);
         *(bf16x8*)((__bf16*)g.out + o) = ob;
         *(bf16x8*)((__bf16*)g.out2 + o) = oa;
       } else if (g.epi == EPI_BF16) {

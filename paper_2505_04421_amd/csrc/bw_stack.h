@@ -56,19 +56,38 @@ struct StackBwd {
   float* dxm; __bf16* dob; __bf16* rec;     // dxm: tile blocks; dob: [rows][D], gradient of the attention output
 };
 
-// activation and derivative in the exact-erf form (gauss_cdf: 1.5e-7)
-__device__ __forceinline__ float act_exact(float v, int act) {
-  if (act == LONGER_ACT_RELU) return v > 0.f ? v : 0.f;
-  float c, e;
-  gauss_cdf(v, &c, &e);
-  return v * c;
+// activation and derivative in the exact-erf form (gauss_cdf: 1.5e-7).  (Which one, and whether the wave has a chunk at all, is asked once for sixteen
+// values: asked for each, every value's chain of twenty instructions stood between two branches of its own, a third of a tile's time: step of the
+// small model 268 us instead of 257, with inputs 1111 instead of 1091.)
+__device__ __forceinline__ void act_exact(f32x16& v, int act, bool there) {
+  if (!there) v = splat16(0.f);
+  else if (act == LONGER_ACT_RELU) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] = v[r] > 0.f ? v[r] : 0.f;
+  } else {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      float c, e;
+      gauss_cdf(v[r], &c, &e);
+      v[r] *= c;
+    }
+  }
 }
-__device__ __forceinline__ void act_exact_both(float v, int act, float* a, float* da) {
-  if (act == LONGER_ACT_RELU) { *a = v > 0.f ? v : 0.f; *da = v > 0.f ? 1.f : 0.f; return; }
-  float c, e;
-  gauss_cdf(v, &c, &e);
-  *a = v * c;
-  *da = c + v * 0.39894228040143268f * e;
+// v <- the activation, g <- g times its derivative (of no use without a chunk but for g, zeros)
+__device__ __forceinline__ void act_exact_both(f32x16& v, f32x16& g, int act, bool there) {
+  if (!there) g = splat16(0.f);
+  else if (act == LONGER_ACT_RELU) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { g[r] *= v[r] > 0.f ? 1.f : 0.f; v[r] = v[r] > 0.f ? v[r] : 0.f; }
+  } else {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      float c, e;
+      gauss_cdf(v[r], &c, &e);
+      g[r] *= c + v[r] * 0.39894228040143268f * e;
+      v[r] *= c;
+    }
+  }
 }
 
 // Sixteen features of a row-major row as an operand group, and back; zeros where it is not there (`row`: any that is; the
@@ -346,8 +365,7 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : MANY ? 4 : 2) v
       for (int k = NG; k < 2 * WV; ++k) second(k);
       f32x16 v = bias_tile(vec + oB1, c, hi);
       s.product(v, operand, second);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) v[r] = c0 + wave < NC ? act_exact(v[r], p.act) : 0.f;
+      act_exact(v, p.act, c0 + wave < NC);
 #pragma unroll
       for (int g = 0; g < 2; ++g) hid[par][wave][g][lane] = E::pack(v, g);
       const bool end = c0 + WV >= NC;
@@ -512,13 +530,7 @@ __global__ __launch_bounds__(64 * stack_waves(D), D >= 256 ? 1 : MANY ? 3 : 2) v
 #pragma unroll
     for (int k = NG; k < 2 * WV; ++k) third(k);
     s.product(g, upstream, third);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float a, da;
-      act_exact_both(v[r], p.act, &a, &da);
-      v[r] = a;
-      g[r] = there ? g[r] * da : 0.f;
-    }
+    act_exact_both(v, g, p.act, there);
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const bf16x8 h = E::pack(g, q);
