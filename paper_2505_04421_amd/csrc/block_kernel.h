@@ -1383,13 +1383,13 @@ static int launch_stack_mode(const BlockParams& p, dim3 grid, hipStream_t stream
   }
 }
 
-// bf16, d = 128: the merge and input generation modes have a kernel of their own (merge_kernel.h)
+// bf16, d = 64 and 128: the merge and input generation modes have a kernel of their own (merge_kernel.h)
 template <int D, int DH>
 int launch_merge(int mode, int win, const BlockParams& p, dim3 grid, hipStream_t stream);
 
 template <typename T, int D, int DH>
 static int launch_rows_mode(int mode, int win, const BlockParams& p, dim3 grid, hipStream_t stream) {
-  if constexpr (sizeof(T) == 2 && D == 128) return launch_merge<D, DH>(mode, win, p, grid, stream);
+  if constexpr (sizeof(T) == 2 && (D == 128 || D == 64)) return launch_merge<D, DH>(mode, win, p, grid, stream);
   else {
     if (mode == MODE_INPUT) LONGER_LAUNCH(T, D, DH, 1, MODE_INPUT, 16);
     else if (mode == MODE_MERGE) {

@@ -1,4 +1,4 @@
-// Token merge and input generation, bf16, d = 128 (the block kernel's modes of the same names, same packed streams, same results):
+// Token merge and input generation, bf16, d = 64 and 128 (the block kernel's modes of the same names, same packed streams, same results):
 //
 //   MODE_MERGE       K-groups of raw tokens through the InnerTrans blocks, mean of each group (Section 3.4);
 //   MODE_MERGE_KEEP  the same, every later block's input rows written as well (a training step's merge);
@@ -7,12 +7,13 @@
 //
 // A wave owns 32 tokens in registers and streams the weights through LDS (device.h).  What bounds it is the issue of matrix and
 // vector instructions under the chip's power limit (the shader clock is 1.7 to 1.9 GHz here), so the wave must not wait as well: one that had
-// the SIMD to itself took 74 cycles per MFMA of the FFN (32 are the pipe's); of those the fragment reads behind each barrier, the
+// the SIMD to itself took (d = 128) 74 cycles per MFMA of the FFN (32 are the pipe's); of those the fragment reads behind each barrier, the
 // barriers and the burst of eight load-to-LDS instructions per panel were 36.  Here a panel is one step of the FFN (two segments, 16 KiB) in a ring of four; a
 // panel is known to have landed one barrier before its use, so that a segment's first fragments are read under the last products of the
 // one before, and the loads of the panel three ahead go out one by one behind products.  FFN loop alone, two workgroups a compute unit: 702 ->
 // 633 ns per pair of segments; a wave's life in the merge of two blocks 100.8k -> 93.4k cycles (alone on its SIMD 80.6k -> 73.6k).  Whole passes: 256 users of 2000
-// tokens, two blocks 559 -> 543 us, 512 of at most 5000, one block 858 -> 831, 61 of 1501 from the raw inputs 183 -> 176.
+// tokens, two blocks 559 -> 543 us, 512 of at most 5000, one block 858 -> 831, 61 of 1501 from the raw inputs 183 -> 176.  Width 64 (three workgroups a
+// compute unit): 128 users of 512 tokens 43.4 -> 42.6, 512 of 4000, two blocks 687 -> 681.
 #pragma once
 #include "block_kernel.h"
 
@@ -64,7 +65,7 @@ struct FlowStream {
 };
 
 template <int D, int DH, int MODE, int W, bool RELU>
-__global__ void __launch_bounds__(256, 2) merge_kernel(const BlockParams p) {
+__global__ void __launch_bounds__(256, D == 64 ? 3 : 2) merge_kernel(const BlockParams p) {
   typedef __bf16 T;
   using E = ET<T>;
   using grp = E::grp;
@@ -306,7 +307,7 @@ __global__ void __launch_bounds__(256, 2) merge_kernel(const BlockParams p) {
         if ((q & 1) && q / 2 < 2 * FlowStream<SEGV>::kPieces) ws.piece();
 #pragma unroll
         for (int pc = q * NP / NM; pc < (q + 1) * NP / NM; ++pc) act_stage(ah[PA], pc / NS, pc % NS, hop[PA][pc / NS]);
-        if (q == NM - 4) ah[PA] = bias_tile(vec + vl.b1(), min(i + 2, NC - 1), hi);      // chunk i + 2 starts from its bias
+        if (q == NM - (NG > 4 ? 4 : 2)) ah[PA] = bias_tile(vec + vl.b1(), min(i + 2, NC - 1), hi);      // chunk i + 2 starts from its bias (chunk i's values are taken)
       }
       ws.next_panel();
     };
