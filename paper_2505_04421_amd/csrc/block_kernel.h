@@ -313,10 +313,7 @@ __device__ __forceinline__ f32x16 mask_tile(uint32_t ab) {
 // key gets the score -infinity (below the running maximum's start value, so its probability
 // is an exact zero without a second test).  Updates the running maximum m and sum l,
 // rescales the accumulator and writes the probabilities as B-operand groups.
-// the reference of a running softmax (key_tile_step) whose first keys' largest score is mt
-__device__ __forceinline__ float first_reference(float mt) { return fabsf(mt) <= 64.f || mt <= kNegBig ? 0.f : mt; }
-
-template <typename T, bool MASKED, bool RUNNING = false>
+template <typename T, bool MASKED>
 __device__ __forceinline__ void softmax_step(const f32x16& S, uint32_t ab, float& m, float& l, f32x16& acc,
                                              typename ET<T>::grp (&pop)[ET<T>::GPT]) {
   float sc[16];
@@ -328,8 +325,8 @@ __device__ __forceinline__ void softmax_step(const f32x16& S, uint32_t ab, float
     mt = fmaxf(mt, sc[r]);
   }
   mt = max_halves(mt);
-  const float mnew = RUNNING ? first_reference(mt) : fmaxf(m, mt);
-  const float alpha = RUNNING ? 1.f : __builtin_amdgcn_exp2f(m - mnew);
+  const float mnew = fmaxf(m, mt);
+  const float alpha = __builtin_amdgcn_exp2f(m - mnew);
   m = mnew;
   acc *= alpha;
   f32x16 pv;
@@ -339,7 +336,7 @@ __device__ __forceinline__ void softmax_step(const f32x16& S, uint32_t ab, float
     pv[r] = __builtin_amdgcn_exp2f(sc[r] - mnew);
     lt += pv[r];
   }
-  if (!RUNNING) l = fmaf(l, alpha, sum_halves(lt));
+  l = fmaf(l, alpha, sum_halves(lt));
 #pragma unroll
   for (int g = 0; g < ET<T>::GPT; ++g) pop[g] = ET<T>::pack(pv, g);
 }
@@ -356,41 +353,19 @@ struct KeyRanges {
   }
 };
 
-// Running softmax of a feature tile's heads over stored keys (bf16): weights exp2(score - ref), their sum over this lane half's keys, the
-// weighted values.  A softmax does not depend on what is subtracted; fp32 and bf16 hold 2^+-64 and sums of such weights as exactly as
-// weights up to 1, so as long as a query's scores lie within +-64 (log2 units) nothing is.  ref moves when a tile's maximum is more than 64 above
-// it, or more than 64 below for a query that has seen no key yet; sums and values are rescaled then.  shifted: some lane's ref is not 0.
-// A kernel starts with ref = sum = 0 and shifted = false, or a softmax_window that ran on them, and multiplies by weight_inverse(sum) in the end.
-__device__ __forceinline__ float weight_inverse(float sum) {      // 0 for a query without a key
-  const float l = sum_halves(sum);
-  return l > 0.f ? __builtin_amdgcn_rcpf(l) : 0.f;
-}
-template <int HPT>
-__device__ __forceinline__ bool any_shifted(const float (&ref)[HPT]) {
-  bool any = false;
-#pragma unroll
-  for (int hh = 0; hh < HPT; ++hh) any |= ref[hh] != 0.f;
-  return __builtin_amdgcn_ballot_w64(any) != 0;
-}
-constexpr float kScoreSpan = 64.f;
-// c + the weights of an operand group, as they are multiplied (rounded to bf16): a query that picks one key gets that key's value exactly
-__device__ __forceinline__ float add_weights(const bf16x8& w, float c) {
-  const bf16x2 one = {(__bf16)1.f, (__bf16)1.f};
-#pragma unroll
-  for (int e = 0; e < 4; ++e) { const bf16x2 pair = {w[2 * e], w[2 * e + 1]}; c = __builtin_amdgcn_fdot2_f32_bf16(pair, one, c, false); }
-  return c;
-}
-
-// One 32-key tile, keys from registers: scores, softmax, weighted values.  Vector work bounds it, so that is kept small: a tile that
-// every query sees whole is recognised by two compares and starts its scores from zero; the mask of another is built with two
-// instructions a score; nothing is subtracted from scores within their span, lane halves are added once, at the end, and the sum
-// takes the weights in pairs (83 -> 48 vector instructions a head and full tile; scoring 16 000 candidates 1063 -> 1046 us, 99 of them
-// 41.8 -> 40.4, 128 users of width 64 49.3 -> 47.4, with 256 users of width 128 and 512 ragged ones 1 to 1.5 % of the pass).
-// (Two key tiles at a time for heads of width 32, twice the independent work, spilled registers: 361
-// instead of 350 us for a forward pass of width 256.)
-template <int HPT, int GPH>
+// One 32-key tile in the attention of a feature tile's heads (bf16), keys from registers: scores, running softmax, weighted
+// values.  Vector work bounds it, so that is kept small: a tile that every query sees whole is recognised by two compares
+// and starts its scores from zero; the mask of another is built with two instructions a score; the accumulators are rescaled only when a
+// query's maximum has grown by more than 8 (log2 units) since the last time: until then weights and their sum carry a common
+// factor of at most 2^8, which fp32 sums and bf16 weights hold without loss.  Four layers of scoring at width 256, 20 key tiles in the
+// first: 4000 tiles 1074 -> 1040 us, 128 tiles 105 -> 92 us.  (Two key tiles at a time for heads of width 32, twice the
+// independent work, spilled registers: 361 instead of 350 us for a forward pass of width 256.  A reference that stays 0 while scores lie within
+// +-64 units, and a sum of the weights as they are multiplied, save 35 of 83 instructions a head and full tile, 1 to 4 % of a pass; but a query's
+// largest weights, 1 here, are then rounded to bf16 like any other: outputs 2e-3 of their size apart where a constant is added to all scores.)
+// EACH: every head by itself (one that grows does not take the other along), as a wave does that has one of them: quad_kernel.h's rows are chain_kernel.h's.
+template <int HPT, int GPH, bool EACH = false>
 __device__ __forceinline__ void key_tile_step(const KeyRanges& r, int kt, const bf16x8 (&k)[2], const bf16x8 (&v)[2], const bf16x8 (&q)[2], int hi,
-                                              float (&ref)[HPT], float (&sum)[HPT], f32x16 (&acc)[HPT], bool& shifted) {
+                                              float (&mrun)[HPT], float (&lrun)[HPT], f32x16 (&acc)[HPT]) {
   using E = ET<__bf16>;
   const int base = 32 * kt;
   const bool full = __builtin_amdgcn_ballot_w64(base < r.from || base + 32 > r.to) == 0;      // everybody sees all of them
@@ -422,45 +397,39 @@ __device__ __forceinline__ void key_tile_step(const KeyRanges& r, int kt, const 
 #pragma unroll
   for (int hh = 0; hh < HPT; ++hh) settle(S[hh]);
   float mt[HPT];
-  bool out = false;                                  // a maximum outside the span around its reference
+  bool grow[HPT], grown = false;
 #pragma unroll
   for (int hh = 0; hh < HPT; ++hh) {
     mt[hh] = S[hh][0];
 #pragma unroll
     for (int e = 1; e < 16; ++e) mt[hh] = fmaxf(mt[hh], S[hh][e]);
-    out |= (fabsf(mt[hh] - ref[hh]) > kScoreSpan) & (mt[hh] > kNegBig);      // (lane halves that see no key are common)
+    mt[hh] = max_halves(mt[hh]);
+    grow[hh] = mt[hh] > mrun[hh] + 8.f;
+    grown |= grow[hh];
   }
-  if (__builtin_amdgcn_ballot_w64(out) != 0) {
+  if (__builtin_amdgcn_ballot_w64(grown) != 0) {
 #pragma unroll
     for (int hh = 0; hh < HPT; ++hh) {
-      const float m = max_halves(mt[hh]);
-      const bool fresh = sum_halves(sum[hh]) == 0.f;
-      const bool move = (m > ref[hh] + kScoreSpan) | (fresh & (m < ref[hh] - kScoreSpan) & (m > kNegBig));
-      if (__builtin_amdgcn_ballot_w64(move) != 0) {
-        const float alpha = (move & !fresh) ? __builtin_amdgcn_exp2f(ref[hh] - m) : 1.f;
-        ref[hh] = move ? m : ref[hh];
-        sum[hh] *= alpha;
-        settle(acc[hh]);
-        acc[hh] *= alpha;
-        shifted = true;
-      }
+      if (EACH && HPT > 1 && __builtin_amdgcn_ballot_w64(grow[hh]) == 0) continue;
+      const float mnew = fmaxf(mrun[hh], mt[hh]), alpha = __builtin_amdgcn_exp2f(mrun[hh] - mnew);
+      mrun[hh] = mnew;
+      lrun[hh] *= alpha;
+      settle(acc[hh]);
+      acc[hh] *= alpha;
     }
-  }
-  if (shifted) {
-#pragma unroll
-    for (int hh = 0; hh < HPT; ++hh) S[hh] -= ref[hh];
   }
 #pragma unroll
   for (int hh = 0; hh < HPT; ++hh) {
     f32x16 pv;
+    float lt = 0.f;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) pv[e] = __builtin_amdgcn_exp2f(S[hh][e]);
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      const bf16x8 w = E::pack(pv, g);
-      sum[hh] = add_weights(w, sum[hh]);
-      acc[hh] = E::mma(v[g], w, acc[hh]);
+    for (int e = 0; e < 16; ++e) {
+      pv[e] = __builtin_amdgcn_exp2f(S[hh][e] - mrun[hh]);
+      lt += pv[e];
     }
+    lrun[hh] += sum_halves(lt);
+#pragma unroll
+    for (int g = 0; g < 2; ++g) acc[hh] = E::mma(v[g], E::pack(pv, g), acc[hh]);
   }
 }
 
@@ -469,13 +438,11 @@ __device__ __forceinline__ void key_tile_step(const KeyRanges& r, int kt, const 
 // [W widx, W widx + W) with widx = (lane % 32) / (2 W)).  `wb` holds the visibility bits of
 // the window (bit 8 (c/4) + c%4 for window register c).  It is the first step of a query's
 // softmax (m, l, acc at their start values); with W = 16 it is softmax_step.
-// RUNNING: the start of what key_tile_step goes on with (m its reference, l the sum over this lane half's keys).
-template <typename T, int W, bool RUNNING = false>
+template <typename T, int W>
 __device__ __forceinline__ void softmax_window(const f32x16& S, int widx, const uint32_t (&wmask)[16 / W], uint32_t wb,
                                                float& m, float& l, f32x16& acc,
                                                typename ET<T>::grp (&pop)[ET<T>::GPT]) {
-  auto own_sum = [&] { if constexpr (RUNNING) l = add_weights(pop[1], add_weights(pop[0], 0.f)); };
-  if (W == 16) { softmax_step<T, true, RUNNING>(S, wb, m, l, acc, pop); own_sum(); return; }
+  if (W == 16) { softmax_step<T, true>(S, wb, m, l, acc, pop); return; }
   float x[W];
   const bool b0 = widx & 1, b1 = widx & 2;
   // each score goes through an opaque register copy so that the choice below stays a
@@ -502,15 +469,16 @@ __device__ __forceinline__ void softmax_window(const f32x16& S, int widx, const 
     mt = fmaxf(mt, x[c]);
   }
   mt = max_halves(mt);
-  const float mnew = RUNNING ? first_reference(mt) : fmaxf(m, mt);
-  const float alpha = RUNNING ? 1.f : __builtin_amdgcn_exp2f(m - mnew);
+  const float mnew = fmaxf(m, mt);
+  const float alpha = __builtin_amdgcn_exp2f(m - mnew);
   float lt = 0.f;
 #pragma unroll
   for (int c = 0; c < W; ++c) {
     x[c] = __builtin_amdgcn_exp2f(x[c] - mnew);
     lt += x[c];
   }
-  if (!RUNNING) l = l * alpha + sum_halves(lt);
+  lt = sum_halves(lt);
+  l = l * alpha + lt;
   m = mnew;
   if (sizeof(T) == 2) {
     // pairs of probabilities -> packed bf16, dropped into the window's slots of the 8 pair slots
@@ -528,7 +496,6 @@ __device__ __forceinline__ void softmax_window(const f32x16& S, int widx, const 
       const u32x4 v = {slot[4 * g], slot[4 * g + 1], slot[4 * g + 2], slot[4 * g + 3]};
       pop[g] = __builtin_bit_cast(typename ET<T>::grp, v);
     }
-    own_sum();
   } else {
     f32x16 pv;
 #pragma unroll

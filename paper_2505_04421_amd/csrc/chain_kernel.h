@@ -268,11 +268,9 @@ __global__ void __launch_bounds__(64 * chain_waves(D) * quad_tiles(MODE), chain_
         for (int g = 0; g < 2; ++g) { kvl[ts][ft][0][g][lane] = E::pack(ak, g); kvl[ts][ft][1][g][lane] = E::pack(av, g); }
       }
     }
-    float ref[1], sum[1];                                  // this wave's head owns half of the accumulator's rows
+    float mrun[1] = {kNegBig}, lrun[1] = {0.f};            // this wave's head owns half of the accumulator's rows
     f32x16 acc[1];
-    bool shifted = false;
-#pragma unroll
-    for (int hh = 0; hh < 1; ++hh) { ref[hh] = 0.f; sum[hh] = 0.f; acc[hh] = splat16(0.f); }
+    acc[0] = splat16(0.f);
     {
       __syncthreads();                                 // Q (K, V) of every feature tile
       if (selfl) {
@@ -292,13 +290,12 @@ __global__ void __launch_bounds__(64 * chain_waves(D) * quad_tiles(MODE), chain_
         uint32_t wmask[16 / W];
 #pragma unroll
         for (int w = 0; w < 16 / W; ++w) { wmask[w] = widx == w ? 0xffffffffu : 0u; asm("" : "+v"(wmask[w])); }
-        softmax_window<T, W, true>(S, widx, wmask, tilebits, ref[0], sum[0], acc[0], pop);
+        softmax_window<T, W>(S, widx, wmask, tilebits, mrun[0], lrun[0], acc[0], pop);
 #pragma unroll
         for (int g = 0; g < 2; ++g) acc[0] = E::mma(vop[g], pop[g], acc[0]);
-        shifted = any_shifted(ref);
       }
       auto key_tile = [&](int kt, int b) __attribute__((always_inline)) {
-        key_tile_step<1, 1>(selfl ? skr : kr, kt, kn[b], vn[b], qop, hi, ref, sum, acc, shifted);
+        key_tile_step<1, 1>(selfl ? skr : kr, kt, kn[b], vn[b], qop, hi, mrun, lrun, acc);
         if (kt + KD < nkt) fetch(kt + KD, b);
       };
       for (int kt = 0; kt < nkt; kt += KD) {
@@ -315,7 +312,7 @@ __global__ void __launch_bounds__(64 * chain_waves(D) * quad_tiles(MODE), chain_
     request_vec(project ? p.kv_w : last ? wl : wnext);
     {
       settle(acc[0]);
-      const float inv = weight_inverse(sum[0]);
+      const float inv = lrun[0] > 0.f ? __builtin_amdgcn_rcpf(lrun[0]) : 0.f;
       f32x16 o;
 #pragma unroll
       for (int r = 0; r < 8; ++r) { const float lo = acc[0][r], up = acc[0][8 + r]; o[r] = (head ? up : lo) * inv; }

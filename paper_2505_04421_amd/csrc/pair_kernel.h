@@ -203,11 +203,10 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
       aq *= p.scale_l2e;
 #pragma unroll
       for (int g = 0; g < GPT; ++g) qop[g] = E::pack(aq, g);
-      float ref[HPT], sum[HPT];
+      float mrun[HPT], lrun[HPT];
       f32x16 acc[HPT];
-      bool shifted = false;
 #pragma unroll
-      for (int hh = 0; hh < HPT; ++hh) { ref[hh] = 0.f; sum[hh] = 0.f; acc[hh] = splat16(0.f); }
+      for (int hh = 0; hh < HPT; ++hh) { mrun[hh] = kNegBig; lrun[hh] = 0.f; acc[hh] = splat16(0.f); }
 
       {   // keys of the lane's own tile: the candidate's own globals
         grp kop[GPT], vop[GPT];
@@ -219,11 +218,10 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
 #pragma unroll
           for (int g2 = 0; g2 < GPH; ++g2) S = E::mma(kop[hh * GPH + g2], qop[hh * GPH + g2], S);
           grp pop[GPT];
-          softmax_window<T, W, true>(S, widx, wmask, tilebits, ref[hh], sum[hh], acc[hh], pop);
+          softmax_window<T, W>(S, widx, wmask, tilebits, mrun[hh], lrun[hh], acc[hh], pop);
 #pragma unroll
           for (int g = 0; g < GPT; ++g) acc[hh] = E::mma(vop[g], pop[g], acc[hh]);
         }
-        shifted = any_shifted(ref);
       }
       {     // stored K/V fragments (wave-uniform user, scalar loop control)
         const int uu = __builtin_amdgcn_readfirstlane(usr);
@@ -271,14 +269,14 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
               vnx[g] = *reinterpret_cast<const grp*>(vb + fo + g * 1024);
             }
           }
-          key_tile_step<HPT, GPH>(kr, kt, kfr, vfr, qop, hi, ref, sum, acc, shifted);
+          key_tile_step<HPT, GPH>(kr, kt, kfr, vfr, qop, hi, mrun, lrun, acc);
         }
       }
       // normalise; with two heads per tile each head owns half of the accumulator rows
       f32x16 o;
       float inv[HPT];
 #pragma unroll
-      for (int hh = 0; hh < HPT; ++hh) inv[hh] = weight_inverse(sum[hh]);
+      for (int hh = 0; hh < HPT; ++hh) inv[hh] = lrun[hh] > 0.f ? __builtin_amdgcn_rcpf(lrun[hh]) : 0.f;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int hh = HPT == 1 ? 0 : r / 8;

@@ -87,6 +87,10 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_wa
   uint32_t tilebits = 0;
   KeyRanges kr = {}, skr = {};                         // visible keys among the stored ones; in the stack's self layers
   int kthi = 0;                                        // tiles of the stored keys
+  const int widx = W == 16 ? 0 : j / (2 * W);
+  uint32_t wmask[16 / W];
+#pragma unroll
+  for (int w = 0; w < 16 / W; ++w) { wmask[w] = widx == w ? 0xffffffffu : 0u; asm("" : "+v"(wmask[w])); }
   f32x16 x;
   auto load_own = [&](const void* base, int f32, long long off) {
     f32x16 one[1];
@@ -107,7 +111,7 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_wa
     load_own(p.Gc, 0, out_off);
     const uint32_t vb = (uint32_t)__ballot(valid);
     const int gbase = p.m * (j / p.m);
-    tilebits = ((range_bits(gbase + (p.gmask_causal ? gi : 0), gbase + p.m, 0) & vb) >> (4 * hi)) >> (W == 16 ? 0 : 2 * W * (j / (2 * W)));
+    tilebits = ((range_bits(gbase + (p.gmask_causal ? gi : 0), gbase + p.m, 0) & vb) >> (4 * hi)) >> (2 * W * widx);
   } else {
     if (STACK) { usr = (int)blockIdx.x; tile = ts; }
     else { usr = (int)blockIdx.x / p.tiles_per_user; tile = (int)blockIdx.x - usr * p.tiles_per_user; }
@@ -255,11 +259,10 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_wa
         grp qop[2];
 #pragma unroll
         for (int g = 0; g < 2; ++g) qop[g] = E::pack(aq, g);
-        float ref[HPT], sum[HPT];
+        float mrun[HPT], lrun[HPT];
         f32x16 acc[HPT];
-        bool shifted = false;
 #pragma unroll
-        for (int hh = 0; hh < HPT; ++hh) { ref[hh] = 0.f; sum[hh] = 0.f; acc[hh] = splat16(0.f); }
+        for (int hh = 0; hh < HPT; ++hh) { mrun[hh] = kNegBig; lrun[hh] = 0.f; acc[hh] = splat16(0.f); }
         // stored K/V fragments (wave-uniform user, scalar loop control); KD key tiles on their way
         constexpr int KD = STACK ? 2 : 4;
         const char* kb; const char* vb; int nkt;
@@ -298,10 +301,6 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_wa
 #pragma unroll
         for (int b = 0; b < KD; ++b) fetch(min(b, max(nkt - 1, 0)), b);
         if (SCORE) {   // keys of the lane's own tile: the candidate's own globals
-          const int widx = W == 16 ? 0 : j / (2 * W);
-          uint32_t wmask[16 / W];
-#pragma unroll
-          for (int w = 0; w < 16 / W; ++w) { wmask[w] = widx == w ? 0xffffffffu : 0u; asm("" : "+v"(wmask[w])); }
           grp kop[2], vop[2];
 #pragma unroll
           for (int g = 0; g < 2; ++g) { kop[g] = E::pack(ak, g); vop[g] = E::pack(av, g); }
@@ -311,14 +310,13 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_wa
 #pragma unroll
             for (int g2 = 0; g2 < GPH; ++g2) S = E::mma(kop[hh * GPH + g2], qop[hh * GPH + g2], S);
             grp pop[2];
-            softmax_window<T, W, true>(S, widx, wmask, tilebits, ref[hh], sum[hh], acc[hh], pop);
+            softmax_window<T, W>(S, widx, wmask, tilebits, mrun[hh], lrun[hh], acc[hh], pop);
 #pragma unroll
             for (int g = 0; g < 2; ++g) acc[hh] = E::mma(vop[g], pop[g], acc[hh]);
           }
-          shifted = any_shifted(ref);
         }
         auto key_tile = [&](int kt, int b) __attribute__((always_inline)) {
-          key_tile_step<HPT, GPH>(selfl ? skr : kr, kt, kn[b], vn[b], qop, hi, ref, sum, acc, shifted);
+          key_tile_step<HPT, GPH, true>(selfl ? skr : kr, kt, kn[b], vn[b], qop, hi, mrun, lrun, acc);
           if (kt + KD < nkt) fetch(kt + KD, b);
         };
         for (int kt = 0; kt < nkt; kt += KD) {
@@ -329,7 +327,7 @@ __global__ void __launch_bounds__(64 * quad_waves(D) * quad_tiles(MODE), quad_wa
         f32x16 o;
         float inv[HPT];
 #pragma unroll
-        for (int hh = 0; hh < HPT; ++hh) { settle(acc[hh]); inv[hh] = weight_inverse(sum[hh]); }
+        for (int hh = 0; hh < HPT; ++hh) { settle(acc[hh]); inv[hh] = lrun[hh] > 0.f ? __builtin_amdgcn_rcpf(lrun[hh]) : 0.f; }
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[r] = acc[HPT == 1 ? 0 : r / 8][r] * inv[HPT == 1 ? 0 : r / 8];
 #pragma unroll

@@ -299,12 +299,11 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
       grp qop[2];
 #pragma unroll
       for (int g = 0; g < 2; ++g) qop[g] = mid[t0 + rt][ft][g][lane];
-      float ref[HPT], sum[HPT];
+      float mrun[HPT], lrun[HPT];
       f32x16 acc[HPT];
-      bool shifted = false;
 #pragma unroll
-      for (int hh = 0; hh < HPT; ++hh) { ref[hh] = 0.f; sum[hh] = 0.f; acc[hh] = splat16(0.f); }
-      auto key_tile = [&](int kt, const grp (&k)[2], const grp (&v)[2]) __attribute__((always_inline)) { key_tile_step<HPT, GPH>(kr, kt, k, v, qop, hi, ref, sum, acc, shifted); };
+      for (int hh = 0; hh < HPT; ++hh) { mrun[hh] = kNegBig; lrun[hh] = 0.f; acc[hh] = splat16(0.f); }
+      auto key_tile = [&](int kt, const grp (&k)[2], const grp (&v)[2]) __attribute__((always_inline)) { key_tile_step<HPT, GPH>(kr, kt, k, v, qop, hi, mrun, lrun, acc); };
       if constexpr (SELF) {
         const int nkt = (rows + 31) / 32;
         if constexpr (TG == 1) {
@@ -346,7 +345,7 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
       f32x16 o;
       float inv[HPT];
 #pragma unroll
-      for (int hh = 0; hh < HPT; ++hh) { settle(acc[hh]); inv[hh] = weight_inverse(sum[hh]); }
+      for (int hh = 0; hh < HPT; ++hh) { settle(acc[hh]); inv[hh] = lrun[hh] > 0.f ? __builtin_amdgcn_rcpf(lrun[hh]) : 0.f; }
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[r] = acc[HPT == 1 ? 0 : r / 8][r] * inv[HPT == 1 ? 0 : r / 8];
 #pragma unroll

@@ -184,3 +184,19 @@ def assert_zero_where_ref_zero_rows(got, ref):
     """Rows that the oracle reports as invalid (all-zero) must be exact zeros."""
     zr = (ref == 0).all(axis=-1)
     assert (got[zr] == 0).all()
+
+
+def add_to_scores(block, heads, units):
+    """Block parameters that add `units` (of log 2) to every attention score: feature 0 of the block's normalised rows is 1 whatever the row is,
+    feature 0 of each head's keys is that feature, and of each head's queries the constant.  No softmax sees such a constant."""
+    from longer_synth import round_bf16
+    d = block["wq"].shape[0]
+    cols = np.arange(heads) * (d // heads)
+    b = {k: v.copy() for k, v in block.items()}
+    b["ln1_g"][0], b["ln1_b"][0] = 0, 1
+    b["wq"][:, cols] = 0
+    b["wk"][:, cols] = 0
+    b["wk"][0, cols] = 1
+    b["bk"][cols] = 0
+    b["bq"][cols] = round_bf16(np.full(heads, units * np.sqrt(d / heads) / np.log2(np.e), dtype=np.float32))
+    return b
