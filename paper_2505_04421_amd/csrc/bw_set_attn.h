@@ -119,14 +119,15 @@ __device__ __forceinline__ void add_transposed(f32x16& acc, const __bf16* s, int
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), b, acc, 0, 0, 0);
   }
 }
-// acc holds [features] x [rows = lanes]: the lane's row, scaled
+// acc holds [features] x [rows = lanes]: the lane's row, scaled; w = 0: zeros, whatever the lane holds (a key row without a token has infinite
+// probabilities where a query's log-sum-exp lies below -128)
 template <int DH>
 __device__ __forceinline__ void store_row(__bf16* p, const f32x16& acc, float w, int hi) {
 #pragma unroll
   for (int q = 0; q < DH / 8; ++q) {
     bf16x4 t;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) t[e] = (__bf16)(acc[4 * q + e] * w);
+    for (int e = 0; e < 4; ++e) t[e] = (__bf16)(w != 0.f ? acc[4 * q + e] * w : 0.f);
     *(bf16x4*)(p + 8 * q + 4 * hi) = t;
   }
 }
