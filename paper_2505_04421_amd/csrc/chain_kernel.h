@@ -228,6 +228,8 @@ __global__ void __launch_bounds__(64 * chain_waves(D) * quad_tiles(MODE), chain_
     }
     if (nkt == 0) kb = vb = wl;                      // (readable: requests are made without asking, so that no value lives on through a branch)
     grp kn[KD][2], vn[KD][2];                        // (kn[..][1] stays unused: a head of 16 features is one operand group)
+#pragma unroll
+    for (int b = 0; b < KD; ++b) vn[b][0] = vn[b][1] = grp{};        // (the lanes of the other head's features are never loaded)
     auto fetch = [&](int kt, int b) {
       if (selfl) {
         kn[b][0] = kvl[STACK ? kt : 0][ft][0][head][lane];
@@ -239,7 +241,7 @@ __global__ void __launch_bounds__(64 * chain_waves(D) * quad_tiles(MODE), chain_
       gchar *kq = (gchar*)(kb + fo + head * 1024), *vq2 = (gchar*)(vb + fo);
       asm("" : "+s"(kq), "+s"(vq2));
       kn[b][0] = *(ggrp*)(kq + lane16);
-      // (V's other features belong to the other head: their lanes ask for nothing, what they hold goes nowhere)
+      // (V's other features belong to the other head: their lanes ask for nothing, their zeros go nowhere)
       if (((lane >> 4) & 1) == head) {
 #pragma unroll
         for (int g = 0; g < 2; ++g) vn[b][g] = *(ggrp*)(vq2 + (lane16 + (unsigned)g * 1024u));
