@@ -442,8 +442,8 @@ static int launch_chain_other(int mode, const BlockParams& p, dim3 grid, hipStre
   template <>                                                                                                                            \
   int launch_chain<D>(int mode, int win, bool pair, const BlockParams& p, dim3 grid, hipStream_t stream) {                               \
     if (mode != MODE_SCORE) { if (pair || launch_chain_other<D>(mode, p, grid, stream)) return -1; }                                     \
-    else if (!pair) launch_chain_score<D, QUAD_PLAIN>(win, p, grid, stream);                                                             \
-    else { if constexpr (D == 128) launch_chain_score<D, QUAD_PAIR>(win, p, grid, stream); else return -1; }                             \
+    else if (pair != (D == 128)) return -1;                                                                                              \
+    else launch_chain_score<D, D == 128 ? QUAD_PAIR : QUAD_PLAIN>(win, p, grid, stream);                                                 \
     return hipGetLastError() == hipSuccess ? 0 : -3;                                                                                     \
   }
 

@@ -450,7 +450,7 @@ static void launch_quad_score(int win, const BlockParams& p, dim3 grid, hipStrea
   else LONGER_QUAD_LAUNCH(D, DH, MODE_SCORE, 16, LAY);
 }
 
-// (width 64 streams the plain layouts, width 128 the pair layouts unless the pair kernels are switched off)
+// (width 64 streams the plain layouts, widths 128 and, in scoring, 256 the pair layouts)
 template <int D, int DH>
 static int launch_quad_stack(bool pair, const BlockParams& p, dim3 grid, hipStream_t stream) {
   if constexpr (D == 64) { if (!pair) { LONGER_QUAD_LAUNCH(D, DH, MODE_STACK, 16, QUAD_PLAIN); return 0; } }
@@ -463,8 +463,8 @@ static int launch_quad_stack(bool pair, const BlockParams& p, dim3 grid, hipStre
   int launch_quad<D, DH>(int mode, int win, bool pair, const BlockParams& p, dim3 grid, hipStream_t stream) { \
     if (mode == MODE_ATTN) LONGER_QUAD_LAUNCH(D, DH, MODE_ATTN, 16, QUAD_PLAIN);                      \
     else if (mode == MODE_STACK) { if (launch_quad_stack<D, DH>(pair, p, grid, stream)) return -1; }  \
-    else if (pair) { if constexpr (D >= 128) launch_quad_score<D, DH, QUAD_PAIR>(win, p, grid, stream); else return -1; } \
-    else launch_quad_score<D, DH, QUAD_PLAIN>(win, p, grid, stream);                                  \
+    else if (pair != (D >= 128)) return -1;                                                           \
+    else launch_quad_score<D, DH, D >= 128 ? QUAD_PAIR : QUAD_PLAIN>(win, p, grid, stream);           \
     return hipGetLastError() == hipSuccess ? 0 : -3;                                                  \
   }
 
