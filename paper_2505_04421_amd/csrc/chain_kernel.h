@@ -12,9 +12,9 @@
 // feature tile t of the rows: the first keeps the rows (fp32) and makes Q, the output projection and the second FFN product, the
 // second makes K and V; each takes one head, and both a hidden chunk of a round.  The FFN's weights are on their way during the output
 // projection and LayerNorm, the next layer's first ones during the FFN, the first key tiles during LayerNorm.  Two heads a wave (quad_kernel.h) /
-// a wave per head, microseconds: 1, 25, 128, 256 tiles of candidates at width 128 (four layers) 39.7 / 35.9, 40.5 / 37.1, 42.2 / 39.1, 46.6 /
-// 43.4, at width 64 (three layers) 1, 256, 512 tiles 20.5 / 17.1, 22.6 / 19.1, 28.6 / 24.0; passes of 1, 128, 256 users of width 64 and
-// 36 rows 38.6 / 34.4, 47.9 / 43.2, 57.6 / 52.9, of 61 users of width 128 and 108 rows 85.6 / 80.6.
+// a wave per head, microseconds: 1, 25, 128, 256 tiles of candidates at width 128 (four layers) 41.6 / 37.5, 41.9 / 37.9, 43.3 / 39.5, 46.6 /
+// 42.8, at width 64 (three layers) 1, 256, 512 tiles 20.8 / 17.2, 22.5 / 18.6, 29.1 / 23.6; passes of 1, 128, 256 users of width 64 and
+// 36 rows 39.6 / 34.6, 48.1 / 42.5, 59.6 / 53.9, of 61 users of width 128 and 108 rows 84.2 / 81.4.
 #pragma once
 #include "quad_kernel.h"
 

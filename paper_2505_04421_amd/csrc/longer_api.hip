@@ -72,7 +72,8 @@ static pair_fn find_pair(int dtype, int D, int DH) {
   return nullptr;
 }
 
-// the kernels that give a tile to four waves (quad_kernel.h), for launches with few tiles: bf16, d = 64 / 128 / 256
+// the kernels for launches with few tiles, bf16, d = 64 / 128 / 256: a tile given to four or eight waves (quad_kernel.h), at width 64 with heads of 16
+// features a wave per head (chain_kernel.h; at width 128 launch_few chooses)
 static quad_fn find_quad(int dtype, int D, int DH) {
   if (one_wave_only() || dtype != LONGER_BF16) return nullptr;
   if (D == 64) return DH == 16 ? &launch_chain<64> : DH == 32 ? &launch_quad<64, 32> : nullptr;
@@ -676,16 +677,18 @@ struct AttnIO {
   const char* next_blk; char* next_kst; char* next_vst; size_t next_ustride;
 };
 
-// Launches with few tiles: a tile's chain of products is all that counts, so four or eight waves share it (quad_kernel.h).
+// Launches with few tiles: a tile's chain of products is all that counts, so four or eight waves share it (quad_kernel.h, chain_kernel.h).
 // The line is where every compute unit has its workgroups at once (two of four waves; one of eight at width 256), or another
-// round of them still costs less than the other kernels.  Four layers of scoring, microseconds with it / without: width 64 at 25,
-// 256, 512, 768 tiles 21 / 37, 23 / 38, 31 / 40, 68 / 42; width 128 at 25, 256, 512, 768, 1008 tiles 41 / 103, 47 / 106, 71 / 112, 111 / 117,
-// 138 / 125; width 256 at 25, 256, 512, 768 tiles 78 / 223, 96 / 222, 195 / 230, 325 / 251.  A cache build (two layers of
-// attention, each with the next one's K and V, over 50 groups of raw tokens), width 64 at 16, 256, 512 tiles 32 / 48, 51 / 68, 72 / 85; width 128 at 64,
-// 256, 512 tiles 81 / 140, 93 / 151, 135 / 177; width 256 at 32, 256, 512 tiles 131 / 274, 218 / 341, 412 / 465.
+// round of them still costs less than the other kernels.  Four layers of scoring, microseconds with it / without, heads of 16 features (of 32 at width 256) at 25, 256,
+// 512, 640, 768, 1008 tiles: width 64 25 / 55, 26 / 56, 34 / 57, 42 / 58, 43 / 60, 59 / 60; width 128 38 / 101, 43 / 102, 67 / 107, 97 / 106,
+// 102 / 109, 124 / 112; width 256 83 / 242, 95 / 240, 186 / 245, 252 / 239, 269 / 250, 340 / 257.  Heads of 32: width 64 26 / 46, 28 / 47, 35 / 48,
+// 55 / 48, 56 / 48, 65 / 50 (the line of width 64 is theirs); width 128 37 / 87, 42 / 88, 59 / 91, 87 / 92, 91 / 94, 113 / 99.  A cache build and one candidate (three
+// layers of attention, each with the next one's K and V, over 50 groups of raw tokens) at 16, 256, 512, 768, 1024 tiles: width 64 60 / 85, 66 / 93,
+// 84 / 106, 99 / 117, 123 / 130 (heads of 32 63 / 84, 72 / 94, 89 / 107, 116 / 117, 133 / 131); width 128 94 / 147, 109 / 159, 156 / 195, 218 / 237, 277 / 289;
+// width 256 201 / 333, 267 / 392, 501 / 561, 705 / 707, 897 / 851.
 static bool quad_pays(const Shape& s, long long tiles) { return s.quad && tiles <= (s.D == 128 ? 768 : 512); }
 // At width 128 and heads of 16 features a wave per head (chain_kernel.h) as long as every tile has a compute unit of its own: 256 / 257, 320, 512 tiles
-// of candidates, wave per head / two heads a wave, 43 / 47, 76 / 56, 78 / 59, 80 / 65 us.
+// of candidates, wave per head / two heads a wave, 43 / 47, 77 / 57, 78 / 59, 85 / 66 us.
 static int launch_few(const Shape& s, int mode, int win, bool pair, long long tiles, const BlockParams& p, hipStream_t st) {
   const bool chain = s.D == 128 && s.DH == 16 && tiles <= 256;
   return (chain ? &launch_chain<128> : s.quad)(mode, win, pair, p, dim3((unsigned)tiles), st);
@@ -694,13 +697,13 @@ static int launch_few(const Shape& s, int mode, int win, bool pair, long long ti
 // Stacks of more than two tiles a user: as long as their tiles are one round of the few-tiles kernels' workgroups (one per compute
 // unit, two at width 128), a launch per layer in which every tile has a compute unit of its own beats one workgroup per user.  Whole
 // forward pass (L = 400, K = 8, four layers), microseconds layer by layer / in one launch, at 32, 244, 384, 512 and 640 tiles of 108
-// rows a user: width 64 55 / 63, 60 / 64, 73 / 68, 75 / 68, 95 / 69; width 128 77 / 105, 89 / 108, 111 / 117, 113 / 118, 150 / 120;
-// width 256 158 / 252, 171 / 252, 310 / 303, 323 / 304, 434 / 312.  (Two tiles a user at width 256: 157 / 160 at 64 tiles, in one launch.)
-// With two workgroups on a compute unit, or nearly all of them busy at width 64, only the cross layer gains and each layer behind it costs:
-// width 128, 102 users of 68 rows (306 tiles), five, seven, eleven and 21 layers 122 / 126, 158 / 159, 231 / 225, 412 / 390, at 510 tiles
-// 145 / 144, 182 / 177, 256 / 241, 439 / 405 (four layers 125 / 129); width 64 at 255 tiles 73 / 74, 95 / 95, 139 / 137, 249 / 242, at 177 tiles
-// 235 / 238 for 21.  With heads of 32 features the lines come sooner: four layers, width 128 103 / 105 at 435 tiles, 123 / 121 at 510;
-// width 64 54 / 55 at 192, 58.3 / 57.7 at 255.
+// rows a user: width 64 51 / 62, 55 / 63, 64 / 68, 66 / 68, 94 / 68 (heads of 32 features 51 / 56, 57 / 58, 68 / 62, 71 / 63, 89 / 62); width 128 74 / 101,
+// 83 / 104, 111 / 113, 117 / 116, 151 / 118 (heads of 32 72 / 93, 82 / 95, 105 / 104, 113 / 108, 145 / 110); width 256 149 / 241, 170 / 242, 317 / 305, 326 / 297,
+// 430 / 311.  (Two tiles a user at width 256: 146 / 149 at 64 tiles, in one launch.)
+// With two workgroups on a compute unit, or nearly all of them busy at width 64 with heads of 32, only the cross layer gains and each layer behind it costs:
+// width 128, 102 users of 68 rows (306 tiles), four, five, seven, eleven and 21 layers 103 / 103, 121 / 119, 158 / 151, 229 / 215, 411 / 376, at 510 tiles
+// 127 / 126, 148 / 143, 186 / 176, 260 / 238, 451 / 404; width 64, heads of 32, at 192 tiles 54 / 55, 64 / 64, 84 / 82, 123 / 119, 221 / 210, at 255 59 / 59, 69 / 68,
+// 89 / 85, 131 / 122, 234 / 213.  (Heads of 16, a wave each, gain at any depth at width 64: 212 / 238 for 21 layers at 192 tiles, 222 / 240 at 255.)
 static bool layers_pay(const longer_config* c, const Shape& s, int B) {
   if (!s.quad || s.n <= 64) return false;
   const int most = s.D == 256 ? 256 : s.D == 128 ? (c->n_self > 3 ? 256 : s.DH == 32 ? 448 : 512) : (c->n_self > 6 || s.DH == 32 ? 192 : 256);
@@ -778,9 +781,9 @@ static int run_stack(const longer_config* c, const Shape& s, const char* packed_
     return 0;
   }
   // At most two tiles a user: eight waves for them instead of one or two waves each; at width 64 as long as the users are
-  // one round of workgroups.  Whole forward pass (L = 400, K = 8, three or four layers), microseconds with it / without: width
-  // 64, m + k = 54, at 1, 128, 256, 384, 1024 users 39 / 46, 48 / 55, 63 / 70, 93 / 87, 185 / 173; width 128, m + k = 58, at 1, 128, 512,
-  // 1024 users 90 / 123, 124 / 157, 341 / 400, 624 / 728.
+  // one round of workgroups.  Whole forward pass (L = 400, K = 8, four layers, m + k = 54), microseconds with it / without, at 1, 128, 256, 300, 512, 1024
+  // users: width 64 39 / 53, 47 / 61, 56 / 71, 80 / 83, 95 / 101, 174 / 180, with heads of 32 features, whose line it is, 42 / 50, 50 / 57, 60 / 67, 86 / 77,
+  // 102 / 94, 187 / 169; width 128 73 / 90, 87 / 105, 119 / 140, 163 / 204, 214 / 256, 411 / 489.
   if (s.quad && s.D <= 128 && s.n <= 64 && (s.D == 128 || B <= 256)) {
     if (s.quad(MODE_STACK, 16, pair_stack(s), p, dim3(B), st)) return fail(LONGER_ERR_HIP, "stack launch failed");
     return 0;
