@@ -41,3 +41,30 @@ def test_stack_of_width_64(m, k, n_self, ffn_mult):
     case = synth.make_case(cfg)
     case["lens"][:] = [300, 0, 7, 131]
     _entry_points(case, TOL["bf16"], with_inner=False, logits_by_terms=True)
+
+
+# Users in multiples of eight are dealt to the accelerator dies, others in a row: every user's candidates score as the user's alone do, bit for bit
+@pytest.mark.parametrize("d,heads,U,C,m", [(64, 4, 8, 11, 4), (64, 4, 16, 40, 8), (128, 8, 8, 11, 4), (128, 8, 16, 40, 8), (128, 8, 7, 11, 4)])
+def test_users_dealt_to_the_dies(d, heads, U, C, m):
+    import paper_2505_04421_amd as lg
+    cfg = synth.CONFIGS["C2"].replace(B=U, L=300, K=4, d=d, heads=heads, inner_heads=heads, m=m, k_recent=20, n_self=1, index=93)
+    case = synth.make_case(cfg)
+    model = lg.DeviceModel(cfg, case["weights"])
+    n = np.random.default_rng(8).integers(0, 301, size=U).astype(np.int32)
+    n[:2] = [0, 300]
+    H, lens = model.upload(case["H"]), torch.from_numpy(n).to(model.device)
+    G = model.upload(np.random.default_rng(9).standard_normal((U, C, m, d)).astype(np.float32))
+    ws = model.workspace(U, 300)
+
+    def score(H, lens, G):
+        u = H.shape[0]
+        cache, Y, lo = model.kv_cache(u, 300), model.empty(u, C, m, d), model.empty(u, C, dtype=torch.float32)
+        lg.longer_kv_cache_build(model.ccfg, model.weights, H, lens, u, 300, cache, ws)
+        lg.longer_score_candidates(model.ccfg, model.weights, cache, lens, u, 300, G, C, Y, lo, ws)
+        return Y.float().cpu().numpy(), lo.cpu().numpy()
+
+    Y, lo = score(H, lens, G)
+    assert np.isfinite(Y).all() and (np.abs(Y).max((1, 2, 3)) > 0).all()
+    for u in range(U):
+        Y1, lo1 = score(H[u:u + 1].contiguous(), lens[u:u + 1].contiguous(), G[u:u + 1].contiguous())
+        assert np.array_equal(Y[u], Y1[0]) and np.array_equal(lo[u], lo1[0]), u

@@ -1,5 +1,6 @@
-"""Gradients of the stack's attention (csrc/bw_set_attn.h) where its dispatch draws its lines: 128 query rows and one more, 128 keys (a query's
-probabilities stay in registers) and one more, 288 keys (all of a head's in LDS at once) and one more; rows missing in the last tile on both sides,
+"""Gradients of the stack's attention (csrc/bw_set_attn.h) where its dispatch draws its lines: 128 query rows and one more (also over few keys: a launch a
+side, the query side with its probabilities in registers), 128 keys (a query's probabilities stay in registers) and one more, 288 keys (all of a head's in LDS
+at once) and one more; rows missing in the last tile on both sides,
 users without a token.  Oracle, tolerances and their derivation as in test_gpu_backward."""
 import numpy as np
 import pytest
@@ -14,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("d,heads,k,keys,extra", [(64, 4, 120, 128, {}), (64, 4, 120, 129, dict(gmask="causal")), (128, 4, 120, 288, {}),
                                                   (64, 4, 121, 288, {}), (64, 2, 119, 289, dict(gmask="causal")), (64, 4, 25, 288, dict(k_uniform=7)),
-                                                  (32, 2, 40, 127, dict(q_learnable=True))])
+                                                  (32, 2, 40, 127, dict(q_learnable=True)), (64, 4, 121, 127, {}), (64, 2, 130, 96, dict(gmask="causal"))])
 def test_query_and_key_sides_at_the_lines(d, heads, k, keys, extra):
     m = 8
     L = 4 * (keys - m)
