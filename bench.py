@@ -320,12 +320,14 @@ def run_forward(lg, torch, synth, cfg, args, steps, warmup, want_graph=True):
     valid_tokens = float(B * L if lens_np is None else lens_np.sum())
     merged_tokens = float(B * cfg.T if lens_np is None else np.ceil(lens_np / cfg.K).sum())
     merge_bytes = valid_tokens * cfg.d_in * es + merged_tokens * cfg.d * 4
-    roof_kernel = "block_kernel<MODE_MERGE> (fused gather + InnerTrans + pooling)"
+    bf16 = cfg.dtype == "bf16"
+    merge_kernel = "merge_kernel" if bf16 and cfg.d_in in (64, 128) else "user_kernel" if bf16 and cfg.d_in == 256 and not from_inputs else "block_kernel"
+    roof_kernel = "%s<%s> (fused gather + InnerTrans + pooling)" % (merge_kernel, "MODE_MERGE_IN" if from_inputs else "MODE_MERGE")
     roof_ms, roof_flop = merge_avg_ms, fl["inner"]
     if dom == "attn":
         # the reduced stack dominates (wide main stack over a narrow InnerTrans): price that launch instead.
         # Its work is everything but the InnerTrans and the cross layer's K/V projections (a launch of their own)
-        roof_kernel = "block_kernel<MODE_STACK> (query side of the cross layer + all self layers)"
+        roof_kernel = "reduced stack (query side of the cross layer + all self layers)"
         roof_ms, roof_flop = dom_ms / max(dom_n, 1), fl["total"] - fl["inner"] - fl["kv_cross"]
     achieved = roof_flop / (roof_ms * 1e-3) / 1e12
     total_tflops = fl["total"] / (ms_per_step * 1e-3) / 1e12
