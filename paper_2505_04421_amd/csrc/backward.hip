@@ -1020,7 +1020,7 @@ __global__ __launch_bounds__(256) void bw_build_rows_kernel(StackGeom g, int d, 
 
 // Head and loss (Eq. 1-2) for one user per block: logit = <head_w, the m global rows of Y> + head_b,
 // loss += (softplus form of the cross-entropy) / B, dlogit = (sigmoid(logit) - label) / B, and the
-// gradients that follow: dY (global rows dlogit head_w, the other rows zero), head_w, head_b.
+// gradients that follow: dY (global rows dlogit head_w; the other rows have none and are not written), head_w, head_b.
 __global__ __launch_bounds__(256) void bw_head_kernel(const float* __restrict__ Y, const __bf16* __restrict__ hw,
                                                       const __bf16* __restrict__ hb, const float* __restrict__ labels,
                                                       int B, int n, int m, int d, float* __restrict__ logits,
@@ -1047,10 +1047,9 @@ __global__ __launch_bounds__(256) void bw_head_kernel(const float* __restrict__ 
   }
   __syncthreads();
   const float dl = dl_s;
-  for (int j = threadIdx.x; j < n * d; j += 256) {
-    const float g = j < m * d ? dl * (float)hw[j] : 0.f;
-    dY[(size_t)u * n * d + j] = g;
-    if (j < m * d) unsafeAtomicAdd(dhw + j, dl * y[j]);
+  for (int j = threadIdx.x; j < m * d; j += 256) {
+    dY[(size_t)u * n * d + j] = dl * (float)hw[j];
+    unsafeAtomicAdd(dhw + j, dl * y[j]);
   }
 }
 
@@ -1789,18 +1788,21 @@ static WgradBatch stack_wgrads(const StackDims& s, const StackWs& w, const char*
   WgradBatch b(d, s.rq, true);
   const long long ls = (long long)(w.per_layer / 2), os = (long long)per_main;
   auto at = [&](int o, int l) { return (const __bf16*)(ws + w.rec + (size_t)l * w.per_layer) + (size_t)o * 512; };
-  auto side = [&](int l, int n, float* g) {
-    b.add(at(r.a, l), r.size, f, at(r.dyb, l), r.size, d, d, s.rq, all, g + gl.w2, n, ls, ls, os);
-    b.add(at(r.xh2, l), r.size, d, at(r.dh, l), r.size, f, f, s.rq, all, g + gl.w1, n, ls, ls, os);
-    b.add(at(r.o, l), r.size, d, at(r.dxmb, l), r.size, d, d, s.rq, all, g + gl.wo, n, ls, ls, os);
+  auto side = [&](int l, int n, float* g, size_t rows) {
+    b.add(at(r.a, l), r.size, f, at(r.dyb, l), r.size, d, d, rows, all, g + gl.w2, n, ls, ls, os);
+    b.add(at(r.xh2, l), r.size, d, at(r.dh, l), r.size, f, f, rows, all, g + gl.w1, n, ls, ls, os);
+    b.add(at(r.o, l), r.size, d, at(r.dxmb, l), r.size, d, d, rows, all, g + gl.wo, n, ls, ls, os);
   };
+  const int last = s.layers - 1;          // (its records hold the global rows alone, but for those of Q, K and V)
+  const size_t rg = (size_t)s.B * s.m;
   if (s.layers > 1) {
     float* g = grads + self0;
-    side(1, s.layers - 1, g);
+    if (last > 1) side(1, last - 1, g, s.rq);
+    side(last, 1, g + (size_t)(last - 1) * os, rg);
     b.add(at(r.xh1, 1), r.size, d, at(r.qkv, 1), r.size, 3 * d, d, s.rq, all, g + gl.wq, s.layers - 1, ls, ls, os);
   }
   float* g = grads + cross;
-  side(0, 1, g);
+  side(0, 1, g, last ? s.rq : rg);
   b.add(at(r.xh1, 0), r.size, d, at(r.qkv, 0), r.size, d, d, s.rq, all, g + gl.wq);
   const __bf16* kr = (const __bf16*)(ws + w.krec);
   b.add(kr, key_record(d), d, kr + (size_t)(d / 16) * 512, key_record(d), 2 * d, d, s.rk, all, g + gl.wk);
@@ -1939,7 +1941,7 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
   auto attn = [&](int l) {
     SetAttn t;
     const __bf16* qkv = (const __bf16*)of(w.qkv, l);
-    t.qdesc = qdesc; t.nq = s.n; t.B = B; t.heads = s.heads; t.gmask = c->gmask;
+    t.qdesc = qdesc; t.nq = l == last ? s.m : s.n; t.qrows = s.n; t.B = B; t.heads = s.heads; t.gmask = c->gmask;
     if (l == 0) { t.q = qkv; t.qpitch = d; t.k = kv; t.v = kv + d; t.kvpitch = 2 * d; t.kdesc = kdesc; t.nk = s.m + s.T; }
     else { t.q = qkv; t.qpitch = 3 * d; t.k = qkv + d; t.v = qkv + 2 * d; t.kvpitch = 3 * d; t.kdesc = qdesc; t.nk = s.n; }
     return t;
@@ -1965,6 +1967,7 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
     else if (d == 128) bw_stack_bwd_128(p, k, st); else bw_stack_bwd_256(p, k, st);
     return launched("stack backward");
   };
+  const StackRows globals = {s.m, s.n};
   // forward: [head of 0 (and its keys)], attention, [tail of l, head of l + 1], ...
   for (int l = -1; l <= last; ++l) {
     StackFwd p = {};
@@ -1975,6 +1978,7 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
       p.wstream = stream_at(sg.fwd_tail(l));
       p.x = xs(l); p.o = o; p.bo = bf(b.bo); p.ln2_g = bf(b.ln2_g); p.ln2_b = bf(b.ln2_b); p.b1 = bf(b.b1); p.b2 = bf(b.b2);
       p.desc = qdesc; p.xmid = (float*)of(w.xmid, l); p.y = xs(l + 1); p.rec = (__bf16*)of(w.rec, l);
+      if (l == last) { p.only = globals; p.rows = (int)((size_t)B * s.m); }
     } else {
       p.wstream = stream_at(sg.fwd_head(0)); p.x = xs(0);
     }
@@ -2007,15 +2011,17 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
       // (the cross layer's keys are rows of their own; a self layer's dq, dk, dv lie side by side)
       BW_TRY(l ? attn_backward(l, 3 * d, dqkv + d, dqkv + 2 * d, 3 * d) : attn_backward(l, d, dkv, dkv + d, 2 * d));
       p.mats = l ? 3 : 1; p.wstream = stream_at(sg.bwd_tail(l));
-      p.dqkv = dqkv; p.ldq = p.mats * d; p.x = xs(l); p.ln1_g = bf(blk(l).ln1_g); p.dxm_in = dxm;
+      p.dqkv = dqkv; p.ldq = p.mats * d; p.x = xs(l); p.ln1_g = bf(blk(l).ln1_g); p.dxm_in = l == last ? (const float*)of(w.xmid, last) : dxm;
       p.rec1 = (__bf16*)of(w.rec, l); p.rec1_size = r.size; p.rec1_dqkv = r.qkv; p.dx = dy;
+      if (l == last) p.head = globals;
     } else {
-      p.wstream = stream_at(sg.bwd_head(last)); p.dy = dy;
+      p.wstream = stream_at(sg.bwd_head(last)); p.dy = dy; p.only = globals; p.rows = (int)((size_t)B * s.m);
     }
     if (l > 0) {
       const longer_block& b = blk(l - 1);
       p.desc = qdesc; p.xmid = (const float*)of(w.xmid, l - 1); p.ln2_g = bf(b.ln2_g); p.ln2_b = bf(b.ln2_b); p.b1 = bf(b.b1);
-      p.dxm = dxm; p.dob = dob; p.rec = (__bf16*)of(w.rec, l - 1);
+      // (the last layer's takes the place of its rows, tile by tile: the launch that reads it writes dxm in tiles of all rows)
+      p.dxm = l > last ? (float*)of(w.xmid, last) : dxm; p.dob = dob; p.rec = (__bf16*)of(w.rec, l - 1);
     }
     StackBwd k = {};
     if (l == 0) {

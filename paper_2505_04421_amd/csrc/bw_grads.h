@@ -23,7 +23,7 @@ struct WgradJob {
   int nsub;                           // slices of this job per slice of the launch (a job with more rows than the others)
   int first;                          // its first tile inside a slice's tiles
 };
-constexpr int kMaxWgradJobs = 10;
+constexpr int kMaxWgradJobs = 12;
 struct WgradArgs { WgradJob job[kMaxWgradJobs]; int njobs, tiles, nslices; };
 
 // TB: output tile TB x TB, four waves in 2 x 2.  Both operands are stored with the contraction (token) index
@@ -199,7 +199,7 @@ struct ReduceJob {
   long long sstride, plstride, olstride;    // floats from slice to slice, from layer to layer (partial, output)
   int nslices, m, n, nb, layers, cxlog, blocks, first;   // blocks: workgroups per layer; first: its first workgroup
 };
-constexpr int kMaxReduceJobs = 16;
+constexpr int kMaxReduceJobs = 18;
 struct ReduceArgs { ReduceJob job[kMaxReduceJobs]; int njobs; };
 
 __global__ __launch_bounds__(256) void bw_reduce_jobs_kernel(const ReduceArgs a) {

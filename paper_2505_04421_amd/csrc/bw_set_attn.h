@@ -30,10 +30,11 @@ constexpr int kAttnRows = 128;      // rows of a workgroup
 constexpr int kAttnChunk = 288;     // staged rows of the other side: m + T = 258 at the headline batch in one go
 
 struct SetAttn {
-  const __bf16* q; int qpitch;          // [B nq][..]
+  const __bf16* q; int qpitch;          // [B qrows][..]
   const __bf16* k; const __bf16* v; int kvpitch;   // [B nk][..]
   const int* qdesc; const int* kdesc;
   int nq, nk, B, heads, gmask;
+  int qrows;                            // a user's rows in q, qdesc and what goes with them (outputs, statistics, gradients): the first nq are queries
 };
 
 // Eq. 8 on descriptors: a key stands at a position (global token a at a - kSeq, sequence token t at t, an invalid one behind
@@ -243,7 +244,7 @@ __global__ __launch_bounds__(256) void bw_set_attn_fwd_kernel(SetAttn a, __bf16*
   if (!attn_task(a, rounds, &u, &h, &rd)) return;
   const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
   const int i0 = rd * kAttnRows + 32 * (threadIdx.x >> 6), i = i0 + l32;
-  const size_t row = (size_t)u * a.nq + (i < a.nq ? i : 0);
+  const size_t row = (size_t)u * a.qrows + (i < a.nq ? i : 0);
   int qd = a.qdesc[row];
   RowFrag<DH> q = row_frag<DH>(a.q + row * a.qpitch + h * DH, true, hi);
   if (i >= a.nq) qd = -1;
@@ -363,7 +364,7 @@ struct StagedQueries {
   int qd;
   float2 st;
   __device__ __forceinline__ void request(const SetAttn& a, const __bf16* dob, int d, const float2* stat, int u, int h, int c0, int n) {
-    const size_t q0 = (size_t)u * a.nq + c0;
+    const size_t q0 = (size_t)u * a.qrows + c0;
     q.request(a.q + q0 * a.qpitch + h * DH, a.qpitch, n);
     g.request(dob + q0 * d + h * DH, d, n);
     const int ic = min((int)(threadIdx.x >> 6) * 32 + (int)(threadIdx.x & 31), n - 1);
@@ -461,7 +462,7 @@ __global__ __launch_bounds__(256, 4) void bw_set_attn_bwd_kernel(SetAttn a, cons
     }
     settle(acc);
     if (hi == 0) s.D[i] = live ? D : 0.f;
-    if (i < a.nq) store_row<DH>(dq + ((size_t)u * a.nq + i) * dqpitch + h * DH, acc, live ? scale : 0.f, hi);
+    if (i < a.nq) store_row<DH>(dq + ((size_t)u * a.qrows + i) * dqpitch + h * DH, acc, live ? scale : 0.f, hi);
   }
   __syncthreads();
   for (int kt = wave; kt * 32 < a.nk; kt += 4) {
@@ -488,7 +489,7 @@ __global__ __launch_bounds__(256, HELD ? 2 : 1) void bw_set_attn_bwd_q_kernel(Se
   if (!attn_task(a, rounds, &u, &h, &rd)) return;
   const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
   const int i0 = rd * kAttnRows + 32 * (threadIdx.x >> 6), i = i0 + l32;
-  const size_t row = (size_t)u * a.nq + (i < a.nq ? i : 0);
+  const size_t row = (size_t)u * a.qrows + (i < a.nq ? i : 0);
   int qd = a.qdesc[row];
   float lse = stat[row * a.heads + h].x;
   RowFrag<DH> q = row_frag<DH>(a.q + row * a.qpitch + h * DH, true, hi), g = row_frag<DH>(dob + row * d + h * DH, true, hi);
