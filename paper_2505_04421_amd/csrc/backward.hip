@@ -1301,12 +1301,15 @@ static WgradBatch block_wgrads(int d, int f, size_t ntok, RowsValid rv, const __
   return w;
 }
 // the same from the block kernel's tile records
-static WgradBatch block_wgrads_tiles(int d, int f, size_t slots, RowsValid rv, const __bf16* rec, float* g) {
+// (the last block's W2 from its groups' operands, where they are kept: `groups` of K tokens)
+struct GroupOperands { const __bf16 *x, *y; int groups, K; };
+static WgradBatch block_wgrads_tiles(int d, int f, size_t slots, RowsValid rv, const __bf16* rec, float* g, const GroupOperands* go = nullptr) {
   const GradLayout gl = grad_layout(d, f);
-  const BlockRecord r(d, f);
+  const BlockRecord r(d, f, go != nullptr);
   auto at = [&](int o) { return rec + (size_t)o * 512; };
-  WgradBatch w(d, slots, true);
-  w.add(at(r.a), r.size, f, at(r.dyb), r.size, d, d, slots, rv, g + gl.w2);
+  WgradBatch w(d, slots < 64 ? 64 : slots, true);      // (the groups' job has no more rows than that)
+  if (go) w.add(go->x, f / 16, f, go->y, d / 16, d, d, 64 * group_tiles(slots, go->K), RowsValid{rv.lens, rv.L / go->K, go->K}, g + gl.w2, 1, 0, 0, 0, go->groups);
+  else w.add(at(r.a), r.size, f, at(r.dyb), r.size, d, d, slots, rv, g + gl.w2);
   w.add(at(r.xh2), r.size, d, at(r.dh), r.size, f, f, slots, rv, g + gl.w1);
   w.add(at(r.o), r.size, d, at(r.dxmb), r.size, d, d, slots, rv, g + gl.wo);
   w.add(at(r.xh1), r.size, d, at(r.qkv), r.size, 3 * d, d, slots, rv, g + gl.wq);
@@ -1631,11 +1634,19 @@ static int run_tiled(const longer_config* c, const longer_block* inner, const vo
     p.dy = (const float*)(ws + w.dy);
     p.rec = at(w.rec);
     p.dx = l ? (float*)(ws + w.dy) : dH; p.dx_rows = l == 0;      // (dy in place: a tile's values are read before they are replaced)
+    // (the groups' operands behind the records, which are smaller by more than that)
+    const bool grouped = l == s.layers - 1 && !p.concat && group_operands(s.K);
+    GroupOperands go = {};
+    if (grouped) {
+      p.gx = p.rec + s.padded / 32 * BlockRecord(d, f, true).size * 512;
+      p.gy = p.gx + group_tiles(s.padded, s.K) * (2 * f / 16) * 512;
+      go = GroupOperands{p.gx, p.gy, B * s.T, s.K};
+    }
     if (d == 32) bw_block_launch_32(s.dh, p, st);
     else if (d == 64) bw_block_launch_64(s.dh, p, st);
     else bw_block_launch_128(s.dh, p, st);
     BW_TRY(launched("block backward"));
-    WgradBatch wg = block_wgrads_tiles(d, f, s.slots, rv, p.rec, g);
+    WgradBatch wg = block_wgrads_tiles(d, f, s.slots, rv, p.rec, g, grouped ? &go : nullptr);
     BW_TRY(launch(wg, (float*)(ws + w.part), st));
     t.sums.add(wg);
     BW_TRY(t.sum());

@@ -10,7 +10,7 @@
 // What bounds it: as thirteen launches over [token, feature] tensors (two LayerNorms, three products, attention,
 // the FFN's middle, three products back, attention back, two LayerNorms back) a block of the headline batch
 // (512 000 rows of width 128) moved 18.8 KB per token beside its parameter gradients in 2.1 ms; here it is 7.8-8.2 KB
-// in 0.85 ms (0.84 to 0.87 by box): 4.8 TB/s, where a large copy reaches 5.0.  Memory and the vector unit add up: with a third of its stores
+// in 0.80 ms (0.79 to 0.83 by box), the last block 6.7-7.1 in 0.79: 5 TB/s, what a large copy reaches.  Memory and the vector unit add up: with a third of its stores
 // left out it took 0.80 instead of 0.90 ms, and with 9 650 instead of 10 800 vector instructions per tile (beside 808 products) 0.84.  The stream's waits
 // waited for the records' stores with it (step of the headline model 4169 -> 4100 us without that), a segment's fragments came out of LDS two at a time
 // (four: 4079), and q, k, v, which the tile reads again, passed by the caches (now not: 0.2 % there, 1 % of a step of 128 short users).
@@ -39,14 +39,25 @@ struct BlockBwParams {
   const float* dy;                          // or (dM NULL) the fp32 tile blocks the block after this one wrote
   __bf16* rec;                              // tile records (BlockRecord)
   float* dx; int dx_rows;                   // gradient of the input: fp32 tile blocks, or [B][L][D] (zeros for padded tokens)
+  __bf16* gx; __bf16* gy;                   // NULL, or where the operands of W2's gradient go group by group (GroupOperands)
 };
+
+// The last block's output gradient is the same for all tokens of a group (the merge takes their mean), so W2's gradient contracts over groups: the
+// mean of a group's activated hidden values, in two bf16 parts (the value and what its rounding left), times the merged token's gradient.  At K = 8
+// these are 288 instead of 1280 bytes a token, written here and read by the gradients: step of the headline model 3725 -> 3610 us (the block 826 -> 788, its
+// gradients 388 -> 348), from the raw inputs 1108 -> 1073, of the small model 249 -> 244; W2's gradient comes out 2 to 4 % closer to double precision.  Tile blocks of 32 groups: x [2 t + part][f / 16], y [t][d / 16].
+// For K = 8 and 16: below, two parts of few tokens save little; at 32 a group is a whole tile.
+__host__ __device__ inline bool group_operands(int K) { return K == 8 || K == 16; }
+__host__ __device__ inline size_t group_tiles(size_t slots, int K) { return (slots / K + 31) / 32; }
 
 // A tile's record: all of its tile blocks side by side (xh: normalised rows before gain and shift; the gradients of q, k,
 // v take the place of q, k, v).  Offsets and size in sixteens of features (1 KiB).
 struct BlockRecord {
   int qkv, xh1, o, xh2, dyb, dxmb, a, dh, size;
-  __host__ __device__ BlockRecord(int d, int f)
-      : qkv(0), xh1(3 * d / 16), o(4 * d / 16), xh2(5 * d / 16), dyb(6 * d / 16), dxmb(7 * d / 16), a(8 * d / 16), dh(a + f / 16), size(dh + f / 16) {}
+  // grouped: dyb and a are not there (GroupOperands take their place)
+  __host__ __device__ BlockRecord(int d, int f, bool grouped = false)
+      : qkv(0), xh1(3 * d / 16), o(4 * d / 16), xh2(5 * d / 16), dyb(6 * d / 16), dxmb(grouped ? dyb : 7 * d / 16), a(dxmb + d / 16),
+        dh(grouped ? a : a + f / 16), size(dh + f / 16) {}
 };
 
 constexpr int kBlkWaves = 4;
@@ -67,13 +78,18 @@ __device__ __forceinline__ int tile_lane_offset(int lane, int odd) { return ((la
 // A tile's stretch of memory (wave-uniform base, `bytes` long) as a buffer: offset = the lane's part + a uniform one.  Loads take
 // the uniform part from a scalar register, stores do not: a store reads its data for two more cycles after its issue, and the
 // compiler keeps the registers for that long unless the store has a scalar offset.  With one, the vector instruction
-// right behind a store replaced its data now and then (one 1 KiB piece of a few tiles in a pass of 16 000).
+// right behind a store replaced its data now and then (one 1 KiB piece of a few tiles in a pass of 16 000).  Their uniform part goes into the
+// buffer's base instead: as part of the lane's offset each was a vector addition, whose results the compiler kept, and spilled, from one place to another.
 struct TileBuffer {
   __amdgpu_buffer_rsrc_t r;
-  __device__ __forceinline__ TileBuffer(const void* base, int bytes) : r(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00027000)) {}
+  char* b; int n;
+  __device__ __forceinline__ TileBuffer(const void* base, int bytes) : r(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00027000)), b((char*)base), n(bytes) {}
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t at(int off) const { return __builtin_amdgcn_make_buffer_rsrc(b + (off & ~4095), 0, n - (off & ~4095), 0x00027000); }
   __device__ __forceinline__ u32x4 get(unsigned lane_off, int off) const { return __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, off, 0); }
-  __device__ __forceinline__ void put(unsigned lane_off, int off, u32x4 v) const { __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)lane_off + off, 0, 0); }
-  __device__ __forceinline__ void put_once(unsigned lane_off, int off, u32x4 v) const { __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)lane_off + off, 0, 2); }      // (streaming: `nt`)
+  __device__ __forceinline__ void put(unsigned lane_off, int off, u32x4 v) const { __builtin_amdgcn_raw_buffer_store_b128(v, at(off), (int)lane_off + (off & 4095), 0, 0); }
+  __device__ __forceinline__ void put4(unsigned lane_off, int off, uint32_t v) const { __builtin_amdgcn_raw_buffer_store_b32(v, at(off), (int)lane_off + (off & 4095), 0, 2); }
+  __device__ __forceinline__ void put2(unsigned lane_off, int off, uint16_t v) const { __builtin_amdgcn_raw_buffer_store_b16(v, at(off), (int)lane_off + (off & 4095), 0, 2); }
+  __device__ __forceinline__ void put_once(unsigned lane_off, int off, u32x4 v) const { __builtin_amdgcn_raw_buffer_store_b128(v, at(off), (int)lane_off + (off & 4095), 0, 2); }      // (streaming: `nt`)
 };
 
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
@@ -199,7 +215,8 @@ __device__ __forceinline__ void segment_fragments(const WS& ws, const F& use) {
 }
 
 // W: registers of a score tile that one group can occupy (K <= 2 W)
-template <int D, int DH, int W>
+// GROUPED: W2's operands are kept group by group
+template <int D, int DH, int W, bool GROUPED>
 __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const BlockBwParams p) {
   constexpr int NT = D / 32, NG = D / 16, SEGV = NG * 64, HPT = 32 / DH, GPH = DH / 16;
   constexpr int PSEG = D >= 128 ? kBlkPanel : 4, NB = 3;
@@ -213,7 +230,7 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
   float* vec = (float*)vec4;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 31, hi = lane >> 5;
   const int NC = p.f / 32;
-  const BlockRecord rc(D, p.f);
+  const BlockRecord rc(D, p.f, GROUPED);
 
   // ---- the lane's token
   const int tile = blockIdx.x * kBlkWaves + wave;
@@ -256,6 +273,8 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
     return;
   }
   const int widx = W == 16 ? 0 : j / (2 * W);
+  constexpr int KG = 2 * W;                        // tokens of a group where its operands are kept group by group
+  const int gfirst = tile * (32 / KG);             // and the tile's first group
   uint32_t wmask[16 / W];
 #pragma unroll
   for (int w = 0; w < 16 / W; ++w) { wmask[w] = widx == w ? 0xffffffffu : 0u; asm("" : "+v"(wmask[w])); }
@@ -452,12 +471,29 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
       x[t] += bias_tile(vec + oBo, t, hi);
       if (t + 1 < NT) product(x[t], oop, Attn{}); else product(x[t], oop, Hidden{});
     }
+    if constexpr (GROUPED) {   // the merged token's gradient, from the lanes of its group's first token (of an empty group: any, the reader drops it)
+      const TileBuffer yb(p.gy + (size_t)(gfirst / 32) * (NG * 512), NG * 1024);
+      const int q = gfirst % 32 + j / KG;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const f32x16 v = upstream(t);
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+          const bf16x8 b = E::pack(v, g);
+          if (j % KG == 0) yb.put_once((q ^ (4 * g)) * 32 + hi * 16, (2 * t + g) * 1024, __builtin_bit_cast(u32x4, b));
+        }
+      }
+      if (hi == 0) ((float*)stat[wave][0])[j] = left > 0 ? 1.f / (float)left : 0.f;
+    }
     take_upstream(left, valid);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const f32x16 v = upstream(t);
 #pragma unroll
-      for (int g = 0; g < 2; ++g) { dyop[2 * t + g] = E::pack(v, g); put_rec(rc.dyb, 2 * t + g, dyop[2 * t + g]); }
+      for (int g = 0; g < 2; ++g) {
+        dyop[2 * t + g] = E::pack(v, g);
+        if (!GROUPED) put_rec(rc.dyb, 2 * t + g, dyop[2 * t + g]);
+      }
     }
   }
   float mean2, rstd2;
@@ -473,6 +509,53 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
     for (int t = 0; t < NT; ++t) dn[t] = splat16(0.f);
 #pragma unroll
     for (int g = 0; g < PARK; ++g) *(bf16x8*)(park + g * 1024) = dyop[g];
+    // (K = 8: the lane ends with registers 8 b2 + 4 b0 + 2 b1, + 1 of its group's mean, one 4-byte piece of a row; K = 16: with 8 b3 + 4 b2 + 2 b0 + b1,
+    // two bytes, where b0 .. b3 are the bits of its token)
+    const int b0 = j & 1, b1 = (j >> 1) & 1, b2 = (j >> 2) & 1, b3 = (j >> 3) & 1;
+    const int gg = KG == 8 ? b2 : b3, ge = KG == 8 ? 4 * b0 + 2 * b1 : 4 * b2 + 2 * b0 + b1;
+    const unsigned goff = gg * 1024 + (((gfirst % 32 + j / KG) ^ (4 * gg)) * 32) + hi * 16 + 2 * ge;
+    const TileBuffer xb(p.gx + (size_t)(gfirst / 32) * (2 * p.f * 32), 2 * p.f * 64);
+    const bool some_padding = (uint32_t)__ballot(valid) != 0xffffffffu;
+    auto put_group = [&](int c, f32x16& v) {
+      if (some_padding) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r] = valid ? v[r] : 0.f;
+      }
+      const float share = ((const float*)stat[wave][0])[j];
+      // sums over a group's lanes, halving the registers a lane is left with at each step
+      float a[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) a[r] = v[r];
+      auto both = [](float x, auto ctrl) {
+        return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xF, 0xF, true));
+      };
+      auto step = [&](auto n, auto ctrl, int bit) {
+        constexpr int N = decltype(n)::value;
+#pragma unroll
+        for (int i = 0; i < N; ++i) a[i] = both(a[i], ctrl);
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) a[i] = bit ? a[i + N / 2] : a[i];
+      };
+      using std::integral_constant;
+      typedef integral_constant<int, 0x140> Mirror16; typedef integral_constant<int, 0x141> Mirror8;
+      typedef integral_constant<int, 0xB1> Swap1; typedef integral_constant<int, 0x4E> Swap2;
+      if constexpr (KG == 8) {
+        step(integral_constant<int, 16>{}, Mirror8{}, b2); step(integral_constant<int, 8>{}, Swap1{}, b0); step(integral_constant<int, 4>{}, Swap2{}, b1);
+      } else {
+        step(integral_constant<int, 16>{}, Mirror16{}, b3); step(integral_constant<int, 8>{}, Mirror8{}, b2);
+        step(integral_constant<int, 4>{}, Swap1{}, b0); step(integral_constant<int, 2>{}, Swap2{}, b1);
+      }
+      const float m0 = a[0] * share, m1 = a[1] * share;
+      if constexpr (KG == 8) {
+        const longer::bf16x2 up2 = {(__bf16)m0, (__bf16)m1}, lo2 = {(__bf16)(m0 - (float)up2[0]), (__bf16)(m1 - (float)up2[1])};
+        xb.put4(goff, c * 2048, __builtin_bit_cast(uint32_t, up2));
+        xb.put4(goff, c * 2048 + p.f * 64, __builtin_bit_cast(uint32_t, lo2));
+      } else {
+        const __bf16 up1 = (__bf16)m0;
+        xb.put2(goff, c * 2048, __builtin_bit_cast(uint16_t, up1));
+        xb.put2(goff, c * 2048 + p.f * 64, __builtin_bit_cast(uint16_t, (__bf16)(m0 - (float)up1)));
+      }
+    };
     // FFN, 32 hidden features at a time: values and gradient formed, used and written out
     for (int c = 0; c < NC; ++c) {
       f32x16 v = bias_tile(vec + oBf, c, hi), g = splat16(0.f);
@@ -492,8 +575,9 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
       for (int q = 0; q < 2; ++q) {
         hop[q] = E::pack(g, q);
         put_rec(rc.dh, 2 * c + q, hop[q]);
-        put_rec(rc.a, 2 * c + q, E::pack(v, q));
+        if (!GROUPED) put_rec(rc.a, 2 * c + q, E::pack(v, q));
       }
+      if constexpr (GROUPED) put_group(c, v);
       spread(dn, hop, Hidden{});
     }
   }
@@ -669,7 +753,11 @@ inline void bw_block_launch_d(int dh, const BlockBwParams& p, hipStream_t st) {
   const size_t tiles = ((size_t)p.B * p.T * p.K + 31) / 32;
   const unsigned grid = (unsigned)((tiles + kBlkWaves - 1) / kBlkWaves);
   const size_t lds = (size_t)bw_block_vec_floats(D, p.f) * 4;
-#define LONGER_BW_BLOCK(DH, W) bw_block_kernel<D, DH, W><<<grid, 64 * kBlkWaves, lds, st>>>(p)
+#define LONGER_BW_BLOCK(DH, W)                                                                                    \
+  do {                                                                                                            \
+    if constexpr (W < 16) { if (p.gx) { bw_block_kernel<D, DH, W, true><<<grid, 64 * kBlkWaves, lds, st>>>(p); break; } } \
+    bw_block_kernel<D, DH, W, false><<<grid, 64 * kBlkWaves, lds, st>>>(p);                                       \
+  } while (0)
   if (dh == 16) { if (p.K <= 8) LONGER_BW_BLOCK(16, 4); else if (p.K == 16) LONGER_BW_BLOCK(16, 8); else LONGER_BW_BLOCK(16, 16); }
   else { if (p.K <= 8) LONGER_BW_BLOCK(32, 4); else if (p.K == 16) LONGER_BW_BLOCK(32, 8); else LONGER_BW_BLOCK(32, 16); }
 #undef LONGER_BW_BLOCK

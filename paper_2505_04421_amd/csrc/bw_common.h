@@ -11,21 +11,32 @@ constexpr int kComputeUnits = 256;
 // Padded token rows (row r = u L + pos with pos >= the user's length) carry no gradient.  With the
 // batch's geometry at hand a kernel leaves them out: row GEMMs skip tiles without a valid row, the
 // gradient GEMMs read them as zeros and pass over steps that hold nothing else, the LayerNorm kernels
-// write zeros for them.  L = 0: every row counts (the reduced stack's rows).
-struct RowsValid { const int32_t* lens; int L; };
+// write zeros for them.  L = 0: every row counts (the reduced stack's rows).  A row stands for `unit` tokens (a group's sums: K).
+struct RowsValid { const int32_t* lens; int L; int unit = 1; };
 __device__ __forceinline__ bool row_valid(const RowsValid& v, int r) {
   if (v.L == 0 || v.lens == nullptr) return true;
   const int u = r / v.L;
-  return r - u * v.L < v.lens[u];
+  return (r - u * v.L) * v.unit < v.lens[u];
 }
 // any valid row in [r0, r1)?
 __device__ __forceinline__ bool rows_any_valid(const RowsValid& v, int r0, int r1) {
   if (v.L == 0 || v.lens == nullptr) return true;
   for (int u = r0 / v.L; u * v.L < r1; ++u) {
     const int first = max(r0, u * v.L) - u * v.L;
-    if (first < v.lens[u]) return true;
+    if (first * v.unit < v.lens[u]) return true;
   }
   return false;
+}
+
+// v, or zeros.  (Requests go out unconditionally, for a row that exists, and what is not wanted is dropped afterwards: under a
+// condition each request of a workgroup's start came to wait for the one before: training step of the headline batch 4333 against
+// 4306 us, of a small one 312 against 309, both sides timed in turn.)
+__device__ __forceinline__ bf16x8 keep_if(bf16x8 v, bool wanted) {
+  const u32x4 b = __builtin_bit_cast(u32x4, v);
+  u32x4 w;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) { const uint32_t one = b[e]; w[e] = wanted ? one : 0u; }
+  return __builtin_bit_cast(bf16x8, w);
 }
 
 // Phi(v) = (1 + erf(v / sqrt 2)) / 2 and exp(-v^2 / 2) from one exponential: for z >= 0,

@@ -22,6 +22,8 @@ struct WgradJob {
   int tiles_m, tiles_n, layers;
   int nsub;                           // slices of this job per slice of the launch (a job with more rows than the others)
   int first;                          // its first tile inside a slice's tiles
+  int groups;                         // 0, or the operands are of that many groups (bw_block.h, GroupOperands): X's tile 2 t + part goes with Y's tile t, rows
+                                      // without a token, which nobody wrote, count as zeros, and db, twice what it should be, is halved
 };
 constexpr int kMaxWgradJobs = 12;
 struct WgradArgs { WgradJob job[kMaxWgradJobs]; int njobs, tiles, nslices; };
@@ -78,13 +80,15 @@ __global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const 
   const bool bias_sum = tm == 0 && wm == 0;
   bf16x8 ones;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.f;
+  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)(TILES && jb.groups ? 0.5f : 1.f);
 
   // Steps on their way from memory (registers: 16 a step at TB = 128, 8 at 64).  One, three workgroups a compute unit: steps of the headline, small
   // and raw-inputs models 4392 / 315 / 1291 us; two at the same occupancy, with spills at TB = 128: 4536 / 313 / 1317; this, two workgroups
   // of width 128 a compute unit and as many slices: 4390 / 312 / 1275.
   constexpr int PD = TB == 128 ? 3 : 4;
   bf16x8 rx[PD][NCH], ry[PD][NCH];
+  bool there[PD][NCH];                       // (groups)
+  auto first_row = [&](int kt) { const int k0 = (kfirst + kt * kstride) * 32; return TILES && jb.groups ? (k0 >> 6) << 5 : k0; };
   auto gload = [&](int p, int kt) {
     const int k0 = (kfirst + kt * kstride) * 32;
 #pragma unroll
@@ -94,7 +98,11 @@ __global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const 
         const size_t tile = (size_t)(k0 >> 5);
         const int gx = min(m0 / 16 + (c >> 6), jb.m / 16 - 1), gy = min(n0 / 16 + (c >> 6), jb.n / 16 - 1);
         rx[p][i] = *(const bf16x8*)(X + (tile * jb.ldx + gx) * 512 + 8 * (c & 63));
-        ry[p][i] = *(const bf16x8*)(Y + (tile * jb.ldy + gy) * 512 + 8 * (c & 63));
+        ry[p][i] = *(const bf16x8*)(Y + ((jb.groups ? tile >> 1 : tile) * jb.ldy + gy) * 512 + 8 * (c & 63));
+        if (jb.groups) {
+          const int r = first_row(kt) + (((c & 63) >> 1) ^ (4 * ((c >> 6) & 1)));
+          there[p][i] = r < jb.groups && row_valid(jb.rv, r);
+        }
       } else {
         bf16x8 z;
 #pragma unroll
@@ -109,8 +117,8 @@ __global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const 
   };
   auto next_step = [&](int kt) {
     while (kt < nk) {
-      const int k0 = (kfirst + kt * kstride) * 32;
-      if (rows_any_valid(jb.rv, k0, min(jb.rows, k0 + 32))) break;
+      const int k0 = first_row(kt);
+      if (rows_any_valid(jb.rv, k0, min(TILES && jb.groups ? jb.groups : jb.rows, k0 + 32))) break;
       ++kt;
     }
     return kt;
@@ -145,6 +153,7 @@ __global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const 
 #pragma unroll
       for (int i = 0; i < NCH; ++i) {
         const int c = tid + 256 * i, o = TILES ? 8 * c : (c / CPR) * PITCH + 8 * (c % CPR);
+        if (TILES && jb.groups) { rx[p][i] = keep_if(rx[p][i], there[p][i]); ry[p][i] = keep_if(ry[p][i], there[p][i]); }
         *(bf16x8*)&sx[o] = rx[p][i];
         *(bf16x8*)&sy[o] = ry[p][i];
       }
@@ -255,8 +264,9 @@ struct WgradBatch {
   struct Out { float* out; long long olstride; int nb; } outs[kMaxWgradJobs];
   WgradBatch(int d, size_t rows_, bool tiled_ = false) : tiled(tiled_), tb(wgrad_tile(d)), rows(rows_) {}
   void add(const __bf16* X, int ldx, int m, const __bf16* Y, int ldy, int n, int nb, size_t nrows, RowsValid rv, float* out,
-           int layers = 1, long long xstride = 0, long long ystride = 0, long long olstride = 0) {
+           int layers = 1, long long xstride = 0, long long ystride = 0, long long olstride = 0, int groups = 0) {
     WgradJob& j = a.job[a.njobs];
+    j.groups = groups;
     j.X = X; j.Y = Y; j.ldx = ldx; j.ldy = ldy; j.m = m; j.n = n; j.rows = (int)nrows; j.rv = rv;
     j.tiles_m = (m + tb - 1) / tb; j.tiles_n = (n + tb - 1) / tb; j.layers = layers;
     j.nsub = nrows > rows ? (int)((nrows + rows - 1) / rows) : 1;

@@ -63,16 +63,6 @@ __device__ __forceinline__ bool attn_task(const SetAttn& a, int rounds, int* u, 
 
 __device__ __forceinline__ void settle(f32x16& a, f32x16& b) { asm volatile("s_nop 10" : "+v"(a), "+v"(b)); }      // (device.h, for two)
 
-// v, or zeros.  (Requests go out unconditionally, for a row that exists, and what is not wanted is dropped afterwards: under a
-// condition each request of a workgroup's start came to wait for the one before: training step of the headline batch 4333 against
-// 4306 us, of a small one 312 against 309, both sides timed in turn.)
-__device__ __forceinline__ bf16x8 keep_if(bf16x8 v, bool wanted) {
-  const u32x4 b = __builtin_bit_cast(u32x4, v);
-  u32x4 w;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) { const uint32_t one = b[e]; w[e] = wanted ? one : 0u; }
-  return __builtin_bit_cast(bf16x8, w);
-}
 // the matrix-core operand of a row (lane = row, 8 features per lane half), straight from memory
 template <int DH>
 struct RowFrag {
