@@ -201,8 +201,9 @@ __global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const 
 // Sums of partial results: out = sum over the slices of part[slice][m n + n], for every job (and layer) of a
 // launch.  Columns come in blocks of nb (the three matrices of [W_Q | W_K | W_V] are one job): column block j, its
 // m rows and then its n-vector, goes to out + j (m nb + nb).  m = 0: a plain vector of n (the LayerNorms' [gain | shift]).
-// A workgroup sums 4 CX adjacent outputs, its 256 / CX rows of threads each every (256 / CX)-th slice: CX = 16 for the
-// matrices (tens of slices), 4 for the vectors (hundreds).  Every sum is taken in a fixed order.
+// A workgroup sums 4 CX adjacent outputs, its 256 / CX rows of threads each every (256 / CX)-th slice: CX = 64 or 128 for the
+// matrices (a thread has about ten slices to ask for at once; with 16 it was one or two, and 15 000 workgroups came and went: 28.8 -> 16.8 us for the 56 MB of a
+// step of the headline model), 4 for the vectors (hundreds of slices).  Every sum is taken in a fixed order.
 struct ReduceJob {
   const float* part; float* out;
   long long sstride, plstride, olstride;    // floats from slice to slice, from layer to layer (partial, output)
@@ -295,7 +296,7 @@ struct ReduceBatch {
            long long olstride) {
     ReduceJob& j = a.job[a.njobs++];
     j.part = part; j.out = out; j.sstride = sstride; j.nslices = nslices; j.m = m; j.n = n; j.nb = nb; j.layers = layers;
-    j.plstride = plstride; j.olstride = olstride; j.cxlog = m ? 4 : 2;
+    j.plstride = plstride; j.olstride = olstride; j.cxlog = !m ? 2 : nslices > 16 ? 6 : 7;
     const long long groups = ((long long)m * n + n) / 4;
     j.blocks = (int)((groups + (1 << j.cxlog) - 1) >> j.cxlog);
     j.first = blocks;
