@@ -50,6 +50,7 @@ struct BlockParams {
   const void* H;
   void* M_out; int M_f32;
   void* Z_out; int Z_f32;
+  int pool;             // user_kernel.h, merge: the last block's second FFN product on the groups' sums
   // MODE_KVPROJ / MODE_ATTN rows: rows [0, m0) of a user come from src0, the rest from src1
   RowSrc src0, src1;
   int m0;
@@ -188,7 +189,7 @@ __device__ __forceinline__ uint32_t range_bits(int lo, int hi, int base) {
 // overflows gives an infinite polynomial of the right sign, which the clamp turns into 0 or 1.
 // A whole operand group (8 elements, 4 register pairs) goes through each step together, so that
 // an instruction never uses the result of the one right before it (which costs a wait state).
-__device__ __forceinline__ f16x8 gelu_quarter_h8(f16x8 y) {
+__device__ __forceinline__ f16x8 gelu_quarter_phi_h8(f16x8 y) {      // its second factor
   const f16x8 v = y * y;
   f16x8 pl = (f16x8)((_Float16)2.4554419175668456f);
   pl = __builtin_elementwise_fma(pl, v, (f16x8)((_Float16)-6.304095499217479f));
@@ -197,8 +198,9 @@ __device__ __forceinline__ f16x8 gelu_quarter_h8(f16x8 y) {
   pl = __builtin_elementwise_fma(pl, v, (f16x8)((_Float16)1.5736394077430096f));
   f16x8 phi = __builtin_elementwise_fma(y, pl, (f16x8)((_Float16)0.5f));
   phi = __builtin_elementwise_min(__builtin_elementwise_max(phi, (f16x8)((_Float16)0.f)), (f16x8)((_Float16)1.f));
-  return y * phi;
+  return phi;
 }
+__device__ __forceinline__ f16x8 gelu_quarter_h8(f16x8 y) { return y * gelu_quarter_phi_h8(y); }
 
 template <bool EXACT>
 __device__ __forceinline__ float gelu_fn(float x) {

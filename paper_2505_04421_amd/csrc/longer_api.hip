@@ -646,6 +646,7 @@ static int run_merge(const longer_config* c, const Shape& s, const char* packed,
     p.in_e = in->E; p.in_pos = in->w->pos; p.in_td = in->tdiff; p.de = in->d_e;
     p.n_layers = c->inner_layers + 1;
   }
+  p.pool = M_out && !Z_out && c->K >= 8 && c->inner_layers > 0;
   const int tt = 1;
   const int win = c->K <= 8 ? 4 : (c->K <= 16 ? 8 : 16);
   const long long slots = (long long)B * p.T * c->K;

@@ -24,7 +24,7 @@ namespace longer {
 constexpr int kUserWaves = 8;
 constexpr int user_groups(int d) { return kUserWaves / (d / 32); }     // groups of waves that share out the row tiles
 
-template <int D, int DH, int RT, int LAYOUT, bool RELU, int MODE = MODE_STACK, int W = 16>
+template <int D, int DH, int RT, int LAYOUT, bool RELU, int MODE = MODE_STACK, int W = 16, bool POOL = false>
 __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockParams p) {
   using T = __bf16;
   using E = ET<T>;
@@ -92,6 +92,13 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
     x[rt] = one[0];
   }
 
+  // The last block's second FFN product where only the groups' means leave (p.pool): it is linear, so it takes the sums of the activated values, a column
+  // a group instead of a column a token: one tile of columns instead of four, in the products and in what they read from LDS.  The first
+  // product runs with its operands exchanged (lane = hidden value, registers = tokens), so that the sums are in-lane: the activation's last
+  // product and the sum are one dot instruction, in fp32.  A sum goes on as two fp16 values, what the first leaves over sixteen columns
+  // further.  A padded token starts from a value whose activation is zero.  K = 8, 16, 32 (below, the columns are more than a tile).
+  // 160 000 tokens of width 256, K = 16: FILLP.
+  constexpr int KK = W == 4 ? 8 : 2 * W, GPW = 32 / KK;      // tokens of a group, groups of a row tile
   // merge: token rows and merged tokens of this wave's features, zeros where there are none
   auto merge_out = [&](bool zeros) {
 #pragma unroll
@@ -211,8 +218,8 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
   // One block; SELF: K and V of the user's own rows are made here.  Areas of LDS: `ops` is written by a LayerNorm when everybody
   // has passed the barriers behind its last readers (Q / K / V, W1), `sums` likewise; a wave's part of `mid` is its own up to
   // the barrier behind the attention.
-  auto block = [&](auto selfl, bool last) __attribute__((always_inline)) {
-    constexpr bool SELF = decltype(selfl)::value;
+  auto block = [&](auto selfl, bool last, auto pooledl) __attribute__((always_inline)) {
+    constexpr bool SELF = decltype(selfl)::value, POOLED = decltype(pooledl)::value;      // POOLED: the merge's last block, see above
     const char* wnext = wl + (size_t)sg.block() * D * 64;
     afresh();
 #pragma unroll
@@ -363,6 +370,127 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
     afresh();
     request_vec(last ? wl : wnext);
     normalise(vl.ln2_g(), vl.ln2_b());
+    if constexpr (POOLED) {
+      {
+        // the rows' own sums, a column a group as well, are what the product starts from (and no row is held through it)
+        f32x16 ffn;
+        {
+          float* area = (float*)&mid[0][0][0][0] + ft * (16 * 36);
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) {
+            f32x16 sum[1] = {x[rt] * ((there[rt] >> j) & 1u ? 1.f / KK : 0.f)};
+            lane_sum<0xB1, 1>(sum); lane_sum<0x4E, 1>(sum); lane_sum<0x141, 1>(sum);
+            if (KK >= 16) lane_sum<0x140, 1>(sum);
+            if (KK >= 32) {
+#pragma unroll
+              for (int r = 0; r < 16; ++r) sum[0][r] += __shfl_xor(sum[0][r], 16, 64);
+            }
+            if (j % KK == 0) {
+#pragma unroll
+              for (int q = 0; q < 4; ++q) *(f32x4*)(area + (rt * GPW + j / KK) * 36 + 8 * q + 4 * hi) = f32x4{sum[0][4 * q], sum[0][4 * q + 1], sum[0][4 * q + 2], sum[0][4 * q + 3]};
+            }
+          }
+          __builtin_amdgcn_wave_barrier();
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x4 v = *(const f32x4*)(area + (j & 15) * 36 + 8 * q + 4 * hi);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { const float one = v[e]; ffn[4 * q + e] = j < RT * GPW ? one : 0.f; }
+          }
+          __syncthreads();                           // (hidden chunks take the place)
+        }
+        // the lane's hidden value as an element of the operand groups: piece (operand group, lane half) of its column
+        char* put = (char*)&mid[0][ft][(lane >> 4) & 1][32 * ((lane >> 2) & 1)] + 8 * ((lane >> 3) & 1) + 2 * (lane & 3);
+        for (int c0 = 0; c0 < NC; c0 += WV) {
+          f32x16 ah[RT];
+          const float bias = vec[vl.b1() + 32 * (c0 + ft) + j];
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) {
+            ah[rt] = splat16(bias);
+            if (there[rt] != 0xffffffffu) {
+              uint32_t mine = there[rt] >> (4 * hi);
+              asm volatile("" : "+v"(mine));             // (asked again each time: 64 answers held would be 128 registers)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) ah[rt][r] = (mine >> (8 * (r / 4) + r % 4)) & 1u ? bias : -1e38f;
+            }
+          }
+          product(ah, swapped, normed, mma16, [&](int s) { fr[s] = load(segment(wl + 2048 * ft, sg.w2(c0 + s / 2)), s & 1); });
+          if (c0 > 0) __syncthreads();               // everybody has read the chunks before
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) {
+            float sum[GPW];
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+              f16x8 y, f;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const f16x2 y2 = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(ah[rt][8 * g + 2 * e], ah[rt][8 * g + 2 * e + 1]));
+                y[2 * e] = y2[0]; y[2 * e + 1] = y2[1];
+              }
+              if (RELU) { y = __builtin_elementwise_max(y, (f16x8)((_Float16)0.f)); f = (f16x8)((_Float16)1.f); }
+              else f = gelu_quarter_phi_h8(y);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {          // pair e: registers 8 g + 2 e, + 1; quad 2 g + e / 2
+                const int at = (2 * g + e / 2) / (KK / 8), first = KK == 8 ? e % 2 == 0 : KK == 16 ? e == 0 : g == 0 && e == 0;
+                const f16x2 y2 = {y[2 * e], y[2 * e + 1]}, f2 = {f[2 * e], f[2 * e + 1]};
+                sum[at] = __builtin_amdgcn_fdot2(y2, f2, first ? 0.f : sum[at], false);
+              }
+            }
+            auto halves = [](float a, float b) {     // lanes below 32: a's sum over the lane halves, the others: b's
+              const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+              const unsigned r0 = r[0], r1 = r[1];
+              return (__builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1)) * (1.f / KK);
+            };
+            const float v0 = halves(sum[0], sum[GPW > 1 ? 1 : 0]), v1 = GPW == 4 ? halves(sum[GPW == 4 ? 2 : 0], sum[GPW == 4 ? 3 : 0]) : 0.f;
+            const f16x2 h = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(v0, v1));
+            const f16x2 l = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(v0 - (float)h[0], v1 - (float)h[1]));
+            char* at = put + 16 * (rt * GPW + (GPW > 1 ? hi : 0));
+            *(_Float16*)at = h[0];
+            *(_Float16*)(at + 256) = l[0];
+            if (GPW == 4) { *(_Float16*)(at + 32) = h[1]; *(_Float16*)(at + 32 + 256) = l[1]; }
+          }
+          gchar* next = segment(wl, sg.w1(min(c0 + WV, NC - WV) + ft));
+          __syncthreads();
+          grp cur = middle(0, 0);
+#pragma unroll
+          for (int s = 0; s < NG; ++s) {
+            grp nxt = cur;
+            if (s + 1 < NG) nxt = middle(0, s + 1);
+            ffn = mma_h(fr[s], cur, ffn);
+            fr[s] = load(next, s);
+            __builtin_amdgcn_sched_barrier(0);
+            cur = nxt;
+          }
+        }
+        settle(ffn);
+        // a value and its rest: lanes below 16 of a lane half take the first eight registers of a column, the others the last eight
+        const int c = lane & 15, half = (lane >> 4) & 1;
+        const uint32_t gidx = (uint32_t)blockIdx.x * (RT * GPW) + (uint32_t)c;
+        const int u = (int)(gidx / (uint32_t)p.T), t = (int)(gidx - (uint32_t)u * (uint32_t)p.T);
+        const bool stored = c < RT * GPW && u < p.B;
+        int n = 0;
+        if (stored) { n = p.lens ? p.lens[u] : p.L; n = min(max(n, 0), p.L); }
+        const int left = min(max(n - t * p.K, 0), p.K);
+        const float share = left > 0 ? (float)KK / (float)left : 0.f;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int f0 = 32 * ft + 16 * half + 8 * q + 4 * hi;
+          const f32x4 bias = *(const f32x4*)(vec + vl.b2() + f0);
+          f32x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float a = ffn[4 * q + e], b = ffn[8 + 4 * q + e];
+            const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+            const unsigned r0 = r[0], r1 = r[1];
+            v[e] = left > 0 ? fmaf(__builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1), share, bias[e]) : 0.f;
+          }
+          if (!stored) continue;
+          if (p.M_f32) *(f32x4*)(reinterpret_cast<float*>(p.M_out) + (size_t)gidx * D + f0) = v;
+          else *(bf16x4*)(reinterpret_cast<__bf16*>(p.M_out) + (size_t)gidx * D + f0) = bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
+        }
+      }
+    }
+    if constexpr (!POOLED) {
     {
       const f32x16 bias = bias_tile(vec + vl.b2(), ft, hi);
 #pragma unroll
@@ -395,15 +523,17 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
       __syncthreads();
       product(x, plain, middle, mma_h, [&](int s) { fr[s] = load(next, s); });
     }
+    }
     wl = wnext;
     sg.attn = false;
   };
-  if constexpr (!MERGE) block(std::false_type{}, p.n_layers == 1);
-  for (int layer = MERGE ? 0 : 1; layer < p.n_layers; ++layer) block(std::true_type{}, layer + 1 == p.n_layers);
+  if constexpr (!MERGE) block(std::false_type{}, p.n_layers == 1, std::false_type{});
+  for (int layer = MERGE ? 0 : 1; layer < p.n_layers - POOL; ++layer) block(std::true_type{}, layer + 1 == p.n_layers, std::false_type{});
+  if constexpr (POOL) block(std::true_type{}, true, std::true_type{});
 
   // ------------------------------------------------------------------ epilogue
   afresh();
-  if constexpr (MERGE) { merge_out(false); return; }
+  if constexpr (MERGE) { if (!POOL) merge_out(false); return; }
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
     const int a = 32 * (t0 + rt) + j;
@@ -458,11 +588,13 @@ int launch_user_merge(int win, const BlockParams& p, dim3 grid, hipStream_t stre
     else LONGER_USER_LAUNCH(256, DH, 4, QUAD_PLAIN);                                                  \
     return hipGetLastError() == hipSuccess ? 0 : -3;                                                  \
   }
-#define LONGER_USER_MERGE_LAUNCH(DH, WV) \
+#define LONGER_USER_MERGE_LAUNCH2(DH, WV, POOL) \
   do {                                                                                                \
-    if (p.act == 1) hipLaunchKernelGGL((user_kernel<256, DH, kUserMergeTiles, QUAD_PLAIN, true, MODE_MERGE, WV>), grid, dim3(64 * kUserWaves), 0, stream, p); \
-    else hipLaunchKernelGGL((user_kernel<256, DH, kUserMergeTiles, QUAD_PLAIN, false, MODE_MERGE, WV>), grid, dim3(64 * kUserWaves), 0, stream, p); \
+    if (p.act == 1) hipLaunchKernelGGL((user_kernel<256, DH, kUserMergeTiles, QUAD_PLAIN, true, MODE_MERGE, WV, POOL>), grid, dim3(64 * kUserWaves), 0, stream, p); \
+    else hipLaunchKernelGGL((user_kernel<256, DH, kUserMergeTiles, QUAD_PLAIN, false, MODE_MERGE, WV, POOL>), grid, dim3(64 * kUserWaves), 0, stream, p); \
   } while (0)
+#define LONGER_USER_MERGE_LAUNCH(DH, WV) \
+  do { if (p.pool) LONGER_USER_MERGE_LAUNCH2(DH, WV, true); else LONGER_USER_MERGE_LAUNCH2(DH, WV, false); } while (0)
 #define LONGER_USER_MERGE_INSTANTIATE_256(DH)                                                         \
   template <>                                                                                         \
   int launch_user_merge<256, DH>(int win, const BlockParams& p, dim3 grid, hipStream_t stream) {      \
