@@ -48,6 +48,8 @@ template <> int launch_user<128, 32>(int, const BlockParams&, dim3, hipStream_t)
 template <> int launch_user<256, 16>(int, const BlockParams&, dim3, hipStream_t);
 template <> int launch_user<256, 32>(int, const BlockParams&, dim3, hipStream_t);
 
+template <> int launch_user_merge<128, 16>(int, const BlockParams&, dim3, hipStream_t);
+template <> int launch_user_merge<128, 32>(int, const BlockParams&, dim3, hipStream_t);
 template <> int launch_user_merge<256, 16>(int, const BlockParams&, dim3, hipStream_t);
 template <> int launch_user_merge<256, 32>(int, const BlockParams&, dim3, hipStream_t);
 
@@ -90,9 +92,10 @@ static user_fn find_user(int dtype, int D, int DH) {
   return nullptr;
 }
 
-// and its merge: bf16, d = 256
+// and its merge: bf16, d = 256, and d = 128 where only the groups' means leave
 static user_fn find_user_merge(int dtype, int D, int DH) {
-  if (one_wave_only() || dtype != LONGER_BF16 || D != 256) return nullptr;
+  if (one_wave_only() || dtype != LONGER_BF16 || (D != 128 && D != 256)) return nullptr;
+  if (D == 128) return DH == 16 ? &launch_user_merge<128, 16> : DH == 32 ? &launch_user_merge<128, 32> : nullptr;
   return DH == 16 ? &launch_user_merge<256, 16> : DH == 32 ? &launch_user_merge<256, 32> : nullptr;
 }
 
@@ -657,7 +660,9 @@ static int run_merge(const longer_config* c, const Shape& s, const char* packed,
     if (launch_few_f32(MODE_MERGE, win, p, dim3((unsigned)cdiv(slots, 32)), st)) return fail(LONGER_ERR_HIP, "merge kernel launch failed");
     return 0;
   }
-  if (s.user_merge && !in && !keep) {
+  // Width 128, feature-tile-per-wave against merge_kernel.h, 512 000 tokens: one block, K = 8 235 / 236 us, K = 16 228 / 240, 512 users of 100 to 5000 tokens
+  // 645 / 663; two blocks, K = 8 432 / 427 (the one that hands on every token takes 210 there and 197 here).
+  if (s.user_merge && !in && !keep && (s.Di == 256 || (p.pool && c->inner_layers == 1))) {
     if (s.user_merge(win, p, dim3((unsigned)cdiv(slots, 32LL * kUserMergeTiles)), st)) return fail(LONGER_ERR_HIP, "merge kernel launch failed");
     return 0;
   }

@@ -2,7 +2,8 @@
 // every product's result, its heads) for several row tiles:
 //
 //   MODE_STACK  the whole reduced stack of a user (Eq. 10) with at most four tiles, d = 128 / 256;
-//   MODE_MERGE  the InnerTrans blocks and the merge (Section 3.4) of four tiles of raw tokens, d = 256.
+//   MODE_MERGE  the InnerTrans blocks and the merge (Section 3.4) of four tiles of raw tokens, d = 256, and d = 128 with four waves where only the
+//               groups' means leave and there is one block.
 //
 // Why.  The kernels that give a row tile to one or two waves read every weight fragment once per row tile out of an LDS ring, and at
 // width 256 there is no room beside such a ring for a user's K and V: one wave per SIMD, every wait exposed.  Here a fragment
@@ -11,8 +12,8 @@
 // for its row tiles itself, at width 256 they never leave its registers.  Eight waves, two per SIMD.
 // Fragments are requested a product ahead as in quad_kernel.h.
 //
-// The merge at width 256: 160 000 raw tokens, one block, a wave a tile 335 us, this 303 us.  (At width 128 a tile's
-// wave needs half the registers, two share a SIMD, and the two mappings take the same time.)
+// The merge at width 256: 160 000 raw tokens, one block, a wave a tile 335 us, this 303 us, with the last FFN product on
+// group sums 237.  (At width 128 a tile's wave needs half the registers and two share a SIMD: without those sums the two mappings take the same time.)
 //
 // What bounds it: at width 256 LDS, which hands every product its row operand (1 KiB per matrix instruction and wave, the
 // 128 bytes a cycle that four SIMDs can use up), at width 128 the vector work of the attention.
@@ -21,16 +22,54 @@
 
 namespace longer {
 
-constexpr int kUserWaves = 8;
-constexpr int user_groups(int d) { return kUserWaves / (d / 32); }     // groups of waves that share out the row tiles
+constexpr int user_waves(int d, int mode) { return mode == MODE_MERGE && d == 128 ? 4 : 8; }
+constexpr int user_groups(int d, int mode) { return user_waves(d, mode) / (d / 32); }     // groups of waves that share out the row tiles
+
+// The packed activation of a hidden tile (gelu_quarter_h8) in stages of four packed instructions, one behind a matrix instruction each: sixteen a tile
+// (kStages per operand group).  Every stage's first operand passes through an empty asm statement, or the compiler gathers them in front of the products.
+template <bool RELU>
+struct HiddenStages {
+  static constexpr int kStages = RELU ? 2 : 8;
+  f16x8 y, v, p;
+  static __device__ __forceinline__ void pin(f16x8& x) {
+    u32x4 t = __builtin_bit_cast(u32x4, x);
+    asm volatile("" : "+v"(t));
+    x = __builtin_bit_cast(f16x8, t);
+  }
+  // stage st of operand group gg of the tile a; the last one gives the group
+  __device__ __forceinline__ f16x8 run(const f32x16& a, int gg, int st) {
+    if (st == 0) {          // pairs of elements to fp16 (toward zero: never to infinity)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float lo = a[8 * gg + 2 * e], up = a[8 * gg + 2 * e + 1];
+        asm volatile("" : "+v"(lo), "+v"(up));
+        const f16x2 y2 = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(lo, up));
+        y[2 * e] = y2[0]; y[2 * e + 1] = y2[1];
+      }
+      return y;
+    }
+    if (st == 1 || RELU) pin(y); else if (st == 2) pin(v); else pin(p);
+    if (RELU) return __builtin_elementwise_max(y, (f16x8)((_Float16)0.f));
+    if (st == 1) v = y * y;
+    else if (st == 2) p = __builtin_elementwise_fma((f16x8)((_Float16)2.4554419175668456f), v, (f16x8)((_Float16)-6.304095499217479f));
+    else if (st == 3) p = __builtin_elementwise_fma(p, v, (f16x8)((_Float16)6.604333663059149f));
+    else if (st == 4) p = __builtin_elementwise_fma(p, v, (f16x8)((_Float16)-3.771901897714043f));
+    else if (st == 5) p = __builtin_elementwise_fma(p, v, (f16x8)((_Float16)1.5736394077430096f));
+    else if (st == 6) {
+      p = __builtin_elementwise_fma(y, p, (f16x8)((_Float16)0.5f));
+      p = __builtin_elementwise_min(__builtin_elementwise_max(p, (f16x8)((_Float16)0.f)), (f16x8)((_Float16)1.f));
+    }
+    return y * p;
+  }
+};
 
 template <int D, int DH, int RT, int LAYOUT, bool RELU, int MODE = MODE_STACK, int W = 16, bool POOL = false>
-__global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockParams p) {
+__global__ void __launch_bounds__(64 * user_waves(D, MODE), MODE == MODE_MERGE && D == 128 ? 2 : 1) user_kernel(const BlockParams p) {
   using T = __bf16;
   using E = ET<T>;
   using grp = typename E::grp;
   using hgrp = typename E::hgrp;
-  constexpr int NT = D / 32, NG = D / 16, WV = NT, TG = user_groups(D), TS = TG * RT, HPT = 32 / DH, GPH = DH / 16, kThr = 64 * kUserWaves;
+  constexpr int NT = D / 32, NG = D / 16, WV = NT, TG = user_groups(D, MODE), TS = TG * RT, HPT = 32 / DH, GPH = DH / 16, kThr = 64 * user_waves(D, MODE);
   constexpr bool HOLD = D <= 128;                    // (width 256: no registers for the output projection's fragments through the attention)
   constexpr bool MERGE = MODE == MODE_MERGE;
   static_assert(!MERGE || TG == 1, "the merge's keys stay in their wave");
@@ -72,12 +111,34 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
   auto row_valid = [&](int a) { return a < rows && (a < p.m || a - p.m >= i0); };
   auto row_token = [&](int a) { return p.q_learn ? tu - 1 : slot_token(a - p.m, p.k, tu, p.k_uni); };   // newest merged token slot row a sees
   f32x16 x[RT];
+  Token at[RT];
+  if constexpr (MERGE) {
+    uint32_t any = 0;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      at[rt] = locate(rt);
+      there[rt] = (uint32_t)__ballot(at[rt].jj < at[rt].left);
+      any |= there[rt];
+    }
+    // Nothing but padding (the same tiles in every wave: all leave), before any row is asked for: half of the workgroups of 512 users of 100 to 5000
+    // tokens, whose merge took 666 instead of 645 us when they asked first.
+    if (POOL && any == 0) {
+      const uint32_t groups = RT * (32u >> __builtin_ctz(p.K)), g0 = (uint32_t)blockIdx.x * groups;
+      for (uint32_t i = threadIdx.x; i < groups * (D / 4); i += kThr) {
+        const uint32_t g = g0 + i / (D / 4);
+        if (g >= (uint32_t)p.B * (uint32_t)p.T) break;
+        const size_t o = (size_t)g * D + 4 * (i % (D / 4));
+        if (p.M_f32) *(f32x4*)(reinterpret_cast<float*>(p.M_out) + o) = f32x4{0.f, 0.f, 0.f, 0.f};
+        else *(uint2*)(reinterpret_cast<__bf16*>(p.M_out) + o) = make_uint2(0u, 0u);
+      }
+      return;
+    }
+  }
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
     if constexpr (MERGE) {
-      const Token k = locate(rt);
+      const Token& k = at[rt];
       const bool valid = k.jj < k.left;
-      there[rt] = (uint32_t)__ballot(valid);
       f32x16 one[1];
       load_rows<T, 1>(one, p.H, 0, k.row * D + 32 * ft, valid, hi);
       x[rt] = one[0];
@@ -97,7 +158,8 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
   // product runs with its operands exchanged (lane = hidden value, registers = tokens), so that the sums are in-lane: the activation's last
   // product and the sum are one dot instruction, in fp32.  A sum goes on as two fp16 values, what the first leaves over sixteen columns
   // further.  A padded token starts from a value whose activation is zero.  K = 8, 16, 32 (below, the columns are more than a tile).
-  // 160 000 tokens of width 256, K = 16: FILLP.
+  // 160 000 tokens of width 256, K = 16, one block: 291 -> 246 us, 237 with the activation of either
+  // half of the row tiles behind the other one's products; as a run-time branch in the layer loop 200 registers spilled and it took 295.
   constexpr int KK = W == 4 ? 8 : 2 * W, GPW = 32 / KK;      // tokens of a group, groups of a row tile
   // merge: token rows and merged tokens of this wave's features, zeros where there are none
   auto merge_out = [&](bool zeros) {
@@ -123,11 +185,11 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
       if (k.stored && k.jj == 0) store_rows<T, 1>(sum, p.M_out, p.M_f32, (long long)k.gidx * D + 32 * ft, !zeros, hi);
     }
   };
-  if constexpr (MERGE) {
+  if constexpr (MERGE && !POOL) {
     uint32_t any = 0;
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) any |= there[rt];
-    if (any == 0) { merge_out(true); return; }       // (the same tiles in every wave: all leave)
+    if (any == 0) { merge_out(true); return; }
   }
 
   const char* wl = p.wbase;                          // the current block's stream
@@ -170,6 +232,34 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
     }
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) settle(acc[rt]);
+  };
+  // the same for row tiles T0 .. T1 - 1 alone, behind(n) after the n-th matrix instruction
+  auto part = [&](f32x16 (&acc)[RT], auto t0_, auto t1_, auto b, auto mma, auto then, auto behind) __attribute__((always_inline)) {
+    constexpr int T0 = decltype(t0_)::value, T1 = decltype(t1_)::value, N = T1 - T0;
+    grp cur[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) cur[i] = b(T0 + i, 0);
+#pragma unroll
+    for (int s = 0; s < NG; ++s) {
+      grp nxt[N];
+      if (s + 1 < NG) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) nxt[i] = b(T0 + i, s + 1);
+      }
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        acc[T0 + i] = mma(fr[s], cur[i], acc[T0 + i]);
+        if (i + 1 == N) then(s);
+        behind(s * N + i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (s + 1 < NG) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) cur[i] = nxt[i];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) settle(acc[T0 + i]);
   };
   auto mma16 = [](grp a, grp b, f32x16 c) { return E::mma(a, b, c); };
   auto mma_h = [](grp a, grp b, f32x16 c) { return E::mma_h(a, __builtin_bit_cast(hgrp, b), c); };
@@ -401,11 +491,13 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
         }
         // the lane's hidden value as an element of the operand groups: piece (operand group, lane half) of its column
         char* put = (char*)&mid[0][ft][(lane >> 4) & 1][32 * ((lane >> 2) & 1)] + 8 * ((lane >> 3) & 1) + 2 * (lane & 3);
-        for (int c0 = 0; c0 < NC; c0 += WV) {
-          f32x16 ah[RT];
+        typedef std::integral_constant<int, 0> T0; typedef std::integral_constant<int, (RT + 1) / 2> TH; typedef std::integral_constant<int, RT> T1;
+        constexpr int H = TH::value, NS = HiddenStages<RELU>::kStages;
+        f32x16 ah[RT];
+        auto start = [&](int c0, int first, int count) __attribute__((always_inline)) {
           const float bias = vec[vl.b1() + 32 * (c0 + ft) + j];
 #pragma unroll
-          for (int rt = 0; rt < RT; ++rt) {
+          for (int rt = first; rt < first + count; ++rt) {
             ah[rt] = splat16(bias);
             if (there[rt] != 0xffffffffu) {
               uint32_t mine = there[rt] >> (4 * hi);
@@ -414,53 +506,83 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
               for (int r = 0; r < 16; ++r) ah[rt][r] = (mine >> (8 * (r / 4) + r % 4)) & 1u ? bias : -1e38f;
             }
           }
-          product(ah, swapped, normed, mma16, [&](int s) { fr[s] = load(segment(wl + 2048 * ft, sg.w2(c0 + s / 2)), s & 1); });
-          if (c0 > 0) __syncthreads();               // everybody has read the chunks before
+        };
+        HiddenStages<RELU> act;
+        float sum[GPW];
+        // a row tile's sums, as operands, to buffer `par` of the hidden chunks
+        auto finish = [&](int rt, int par) __attribute__((always_inline)) {
+          auto halves = [](float a, float b) {       // lanes below 32: a's sum over the lane halves, the others: b's
+            const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+            const unsigned r0 = r[0], r1 = r[1];
+            return (__builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1)) * (1.f / KK);
+          };
+          const float v0 = halves(sum[0], sum[GPW > 1 ? 1 : 0]), v1 = GPW == 4 ? halves(sum[GPW == 4 ? 2 : 0], sum[GPW == 4 ? 3 : 0]) : 0.f;
+          const f16x2 h = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(v0, v1));
+          const f16x2 l = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(v0 - (float)h[0], v1 - (float)h[1]));
+          char* at = put + par * (int)sizeof(mid[0]) + 16 * (rt * GPW + (GPW > 1 ? hi : 0));
+          *(_Float16*)at = h[0];
+          *(_Float16*)(at + 256) = l[0];
+          if (GPW == 4) { *(_Float16*)(at + 32) = h[1]; *(_Float16*)(at + 32 + 256) = l[1]; }
+        };
+        // stages of row tiles first .. first + count - 1 behind the n-th of `of` matrix instructions
+        auto stages = [&](int first, int count, int n, int of, int par) __attribute__((always_inline)) {
+          const int all = count * 2 * NS;
 #pragma unroll
-          for (int rt = 0; rt < RT; ++rt) {
-            float sum[GPW];
+          for (int i = 0; i < (all + of - 1) / of; ++i) {
+            const int k = n * all / of + i;
+            if (k >= (n + 1) * all / of) continue;
+            const int rt = first + k / (2 * NS), g = k / NS % 2, st = k % NS;
+            if (st < NS - 1) { act.run(ah[rt], g, st); continue; }
+            f16x8 f;
+            if (RELU) { f = (f16x8)((_Float16)1.f); HiddenStages<RELU>::pin(act.y); act.y = __builtin_elementwise_max(act.y, (f16x8)((_Float16)0.f)); }
+            else { HiddenStages<RELU>::pin(act.p); f = act.p; }
 #pragma unroll
-            for (int g = 0; g < 2; ++g) {
-              f16x8 y, f;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const f16x2 y2 = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(ah[rt][8 * g + 2 * e], ah[rt][8 * g + 2 * e + 1]));
-                y[2 * e] = y2[0]; y[2 * e + 1] = y2[1];
-              }
-              if (RELU) { y = __builtin_elementwise_max(y, (f16x8)((_Float16)0.f)); f = (f16x8)((_Float16)1.f); }
-              else f = gelu_quarter_phi_h8(y);
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {          // pair e: registers 8 g + 2 e, + 1; quad 2 g + e / 2
-                const int at = (2 * g + e / 2) / (KK / 8), first = KK == 8 ? e % 2 == 0 : KK == 16 ? e == 0 : g == 0 && e == 0;
-                const f16x2 y2 = {y[2 * e], y[2 * e + 1]}, f2 = {f[2 * e], f[2 * e + 1]};
-                sum[at] = __builtin_amdgcn_fdot2(y2, f2, first ? 0.f : sum[at], false);
-              }
+            for (int e = 0; e < 4; ++e) {            // pair e: registers 8 g + 2 e, + 1; quad 2 g + e / 2
+              const int at = (2 * g + e / 2) / (KK / 8), fresh = KK == 8 ? e % 2 == 0 : KK == 16 ? e == 0 : g == 0 && e == 0;
+              const f16x2 y2 = {act.y[2 * e], act.y[2 * e + 1]}, f2 = {f[2 * e], f[2 * e + 1]};
+              sum[at] = __builtin_amdgcn_fdot2(y2, f2, fresh ? 0.f : sum[at], false);
             }
-            auto halves = [](float a, float b) {     // lanes below 32: a's sum over the lane halves, the others: b's
-              const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
-              const unsigned r0 = r[0], r1 = r[1];
-              return (__builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1)) * (1.f / KK);
-            };
-            const float v0 = halves(sum[0], sum[GPW > 1 ? 1 : 0]), v1 = GPW == 4 ? halves(sum[GPW == 4 ? 2 : 0], sum[GPW == 4 ? 3 : 0]) : 0.f;
-            const f16x2 h = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(v0, v1));
-            const f16x2 l = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(v0 - (float)h[0], v1 - (float)h[1]));
-            char* at = put + 16 * (rt * GPW + (GPW > 1 ? hi : 0));
-            *(_Float16*)at = h[0];
-            *(_Float16*)(at + 256) = l[0];
-            if (GPW == 4) { *(_Float16*)(at + 32) = h[1]; *(_Float16*)(at + 32 + 256) = l[1]; }
+            if (g == 1) finish(rt, par);
           }
-          gchar* next = segment(wl, sg.w1(min(c0 + WV, NC - WV) + ft));
-          __syncthreads();
-          grp cur = middle(0, 0);
+        };
+        auto nothing = [](int) {};
+        auto mma_swapped = [](grp a, grp b, f32x16 c) { return E::mma(b, a, c); };
+        grp fr2[NG];                                 // W2's fragments
+        auto second = [&](int par) __attribute__((always_inline)) {
+          grp cur = mid[par][0][0][lane];
 #pragma unroll
           for (int s = 0; s < NG; ++s) {
             grp nxt = cur;
-            if (s + 1 < NG) nxt = middle(0, s + 1);
-            ffn = mma_h(fr[s], cur, ffn);
-            fr[s] = load(next, s);
+            if (s + 1 < NG) nxt = mid[par][(s + 1) / 2][(s + 1) & 1][lane];
+            ffn = mma_h(fr2[s], cur, ffn);
             __builtin_amdgcn_sched_barrier(0);
             cur = nxt;
           }
+        };
+        auto w2_at = [&](int c0, int s) { return load(segment(wl + 2048 * ft, sg.w2(c0 + s / 2)), s & 1); };
+        // Chunks c0: either half of the row tiles is activated under the other half's products, the second one's under the next chunks'; the second
+        // product follows two barriers of the chunks behind (its operand is in one of two buffers)
+        start(0, 0, H);
+        part(ah, T0{}, TH{}, normed, mma_swapped, nothing, nothing);
+        start(0, H, RT - H);
+        for (int c0 = 0, par = 0;; par ^= 1) {
+          gchar* next = segment(wl, sg.w1(min(c0 + WV, NC - WV) + ft));
+          part(ah, TH{}, T1{}, normed, mma_swapped, [&](int s) { fr[s] = load(next, s); }, [&](int n) __attribute__((always_inline)) { stages(0, H, n, NG * (RT - H), par); });
+          if (c0 > 0) second(par ^ 1);
+          if (c0 + WV >= NC) {
+#pragma unroll
+            for (int s = 0; s < NG; ++s) fr2[s] = w2_at(c0, s);
+#pragma unroll
+            for (int n = 0; n < NG; ++n) stages(H, RT - H, n, NG, par);
+            __syncthreads();
+            second(par);
+            break;
+          }
+          start(c0 + WV, 0, H);
+          part(ah, T0{}, TH{}, normed, mma_swapped, [&](int s) { fr2[s] = w2_at(c0, s); }, [&](int n) __attribute__((always_inline)) { stages(H, RT - H, n, NG * H, par); });
+          c0 += WV;
+          start(c0, H, RT - H);
+          __syncthreads();
         }
         settle(ffn);
         // a value and its rest: lanes below 16 of a lane half take the first eight registers of a column, the others the last eight
@@ -496,32 +618,41 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) x[rt] += bias;
     }
+    // A wave's row tiles in two halves, so that either half's activation goes behind the matrix instructions of the other one's products, first or
+    // second (the two waves of a SIMD meet at every barrier and had nothing but the activation to do at the same time): 256 users of 108 rows at
+    // width 256, concat merge, 340 -> 330 us a pass, the stack of 512 users of 72 rows at width 128 168 -> 161.
+    typedef std::integral_constant<int, 0> T0; typedef std::integral_constant<int, (RT + 1) / 2> TH; typedef std::integral_constant<int, RT> T1;
+    constexpr int H = TH::value;
     for (int c0 = 0; c0 < NC; c0 += WV) {            // (FF is a multiple of d: every wave has a chunk)
       f32x16 ah[RT];
       const f32x16 bias = bias_tile(vec + vl.b1(), c0 + ft, hi);
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) ah[rt] = bias;
-      product(ah, plain, normed, mma16, [&](int s) { fr[s] = load(segment(wl + 2048 * ft, sg.w2(c0 + s / 2)), s & 1); });
-      if (c0 > 0) __syncthreads();                   // everybody has read the chunks before
+      HiddenStages<RELU> act;
+      constexpr int NS = HiddenStages<RELU>::kStages;
+      // stages of row tiles first .. first + count - 1 behind the n-th of `of` matrix instructions; a finished group goes to LDS
+      auto stages = [&](int first, int count, int n, int of) __attribute__((always_inline)) {
+        const int all = count * 2 * NS;
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-#pragma unroll
-        for (int g = 0; g < 2; ++g) {
-          f16x8 y;     // ah holds x / kFfnScale; to fp16 toward zero, then the packed activation
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const f16x2 y2 = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(ah[rt][8 * g + 2 * e], ah[rt][8 * g + 2 * e + 1]));
-            y[2 * e] = y2[0]; y[2 * e + 1] = y2[1];
-          }
-          y = RELU ? __builtin_elementwise_max(y, (f16x8)((_Float16)0.f)) : gelu_quarter_h8(y);
-          mid[t0 + rt][ft][g][lane] = __builtin_bit_cast(grp, y);
+        for (int i = 0; i < (all + of - 1) / of; ++i) {
+          const int k = n * all / of + i;
+          if (k >= (n + 1) * all / of) continue;
+          const int rt = first + k / (2 * NS), g = k / NS % 2, st = k % NS;
+          const f16x8 y = act.run(ah[rt], g, st);
+          if (st == NS - 1) mid[t0 + rt][ft][g][lane] = __builtin_bit_cast(grp, y);
         }
-      }
+      };
+      auto nothing = [](int) {};
+      part(ah, T0{}, TH{}, normed, mma16, nothing, nothing);
+      part(ah, TH{}, T1{}, normed, mma16, [&](int s) { fr[s] = load(segment(wl + 2048 * ft, sg.w2(c0 + s / 2)), s & 1); },
+           [&](int n) __attribute__((always_inline)) { stages(0, H, n, NG * (RT - H)); });
+      __syncthreads();
+      part(x, T0{}, TH{}, middle, mma_h, nothing, [&](int n) __attribute__((always_inline)) { stages(H, RT - H, n, NG * H); });
       // what follows on these chunks' second product: the next hidden chunk, or the next block's first
       gchar* next = segment(wl, sg.w1(min(c0 + WV, NC - WV) + ft));
       if (c0 + WV >= NC && !last) next = segment(wnext, QuadSegs<LAYOUT, D>{NC, false}.q(ft));
       __syncthreads();
-      product(x, plain, middle, mma_h, [&](int s) { fr[s] = load(next, s); });
+      part(x, TH{}, T1{}, middle, mma_h, [&](int s) { fr[s] = load(next, s); }, nothing);
     }
     }
     wl = wnext;
@@ -569,8 +700,8 @@ int launch_user_merge(int win, const BlockParams& p, dim3 grid, hipStream_t stre
 
 #define LONGER_USER_LAUNCH(D, DH, RT, LAY) \
   do {                                                                                                \
-    if (p.act == 1) hipLaunchKernelGGL((user_kernel<D, DH, RT, LAY, true>), grid, dim3(64 * kUserWaves), 0, stream, p); \
-    else hipLaunchKernelGGL((user_kernel<D, DH, RT, LAY, false>), grid, dim3(64 * kUserWaves), 0, stream, p); \
+    if (p.act == 1) hipLaunchKernelGGL((user_kernel<D, DH, RT, LAY, true>), grid, dim3(64 * user_waves(D, MODE_STACK)), 0, stream, p); \
+    else hipLaunchKernelGGL((user_kernel<D, DH, RT, LAY, false>), grid, dim3(64 * user_waves(D, MODE_STACK)), 0, stream, p); \
   } while (0)
 
 // (width 128 streams the pair layouts, width 256 the plain ones)
@@ -588,19 +719,29 @@ int launch_user_merge(int win, const BlockParams& p, dim3 grid, hipStream_t stre
     else LONGER_USER_LAUNCH(256, DH, 4, QUAD_PLAIN);                                                  \
     return hipGetLastError() == hipSuccess ? 0 : -3;                                                  \
   }
-#define LONGER_USER_MERGE_LAUNCH2(DH, WV, POOL) \
+#define LONGER_USER_MERGE_LAUNCH(D, DH, WV, POOL) \
   do {                                                                                                \
-    if (p.act == 1) hipLaunchKernelGGL((user_kernel<256, DH, kUserMergeTiles, QUAD_PLAIN, true, MODE_MERGE, WV, POOL>), grid, dim3(64 * kUserWaves), 0, stream, p); \
-    else hipLaunchKernelGGL((user_kernel<256, DH, kUserMergeTiles, QUAD_PLAIN, false, MODE_MERGE, WV, POOL>), grid, dim3(64 * kUserWaves), 0, stream, p); \
+    const dim3 threads(64 * user_waves(D, MODE_MERGE));                                               \
+    if (p.act == 1) hipLaunchKernelGGL((user_kernel<D, DH, kUserMergeTiles, QUAD_PLAIN, true, MODE_MERGE, WV, POOL>), grid, threads, 0, stream, p); \
+    else hipLaunchKernelGGL((user_kernel<D, DH, kUserMergeTiles, QUAD_PLAIN, false, MODE_MERGE, WV, POOL>), grid, threads, 0, stream, p); \
   } while (0)
-#define LONGER_USER_MERGE_LAUNCH(DH, WV) \
-  do { if (p.pool) LONGER_USER_MERGE_LAUNCH2(DH, WV, true); else LONGER_USER_MERGE_LAUNCH2(DH, WV, false); } while (0)
+#define LONGER_USER_MERGE_WIN(D, DH, POOL) \
+  do {                                                                                                \
+    if (win == 4) LONGER_USER_MERGE_LAUNCH(D, DH, 4, POOL);                                           \
+    else if (win == 8) LONGER_USER_MERGE_LAUNCH(D, DH, 8, POOL);                                      \
+    else LONGER_USER_MERGE_LAUNCH(D, DH, 16, POOL);                                                   \
+  } while (0)
 #define LONGER_USER_MERGE_INSTANTIATE_256(DH)                                                         \
   template <>                                                                                         \
   int launch_user_merge<256, DH>(int win, const BlockParams& p, dim3 grid, hipStream_t stream) {      \
-    if (win == 4) LONGER_USER_MERGE_LAUNCH(DH, 4);                                                    \
-    else if (win == 8) LONGER_USER_MERGE_LAUNCH(DH, 8);                                               \
-    else LONGER_USER_MERGE_LAUNCH(DH, 16);                                                            \
+    if (p.pool) LONGER_USER_MERGE_WIN(256, DH, true); else LONGER_USER_MERGE_WIN(256, DH, false);     \
+    return hipGetLastError() == hipSuccess ? 0 : -3;                                                  \
+  }
+#define LONGER_USER_MERGE_INSTANTIATE_128(DH)                                                         \
+  template <>                                                                                         \
+  int launch_user_merge<128, DH>(int win, const BlockParams& p, dim3 grid, hipStream_t stream) {      \
+    if (!p.pool) return -3;                                                                           \
+    LONGER_USER_MERGE_WIN(128, DH, true);                                                             \
     return hipGetLastError() == hipSuccess ? 0 : -3;                                                  \
   }
 

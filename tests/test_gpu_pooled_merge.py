@@ -1,0 +1,33 @@
+"""The merge's last FFN product on the groups' sums (csrc/user_kernel.h: widths 128 and 256, bf16, K = 8, 16 and 32, mean merge).  Where that can go wrong: every
+K against every register window, K = 4 (stays token by token), groups with fewer tokens than K (masked start values, the divisor), users without a token, a
+workgroup with nothing but padding beside one that has some, one slot, a last workgroup that is partly empty, one hidden chunk a wave and several, both
+activations, one block and several in front of it, fp32 and bf16 merged tokens (stand-alone and inside longer_forward).  Against the fp64 oracle at the bf16 bar."""
+import numpy as np
+import pytest
+import torch
+
+import longer_synth as synth
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="needs the GPU")]
+
+
+@pytest.mark.parametrize("d,inner_heads,K,ffn_mult,layers,B,L,act", [
+    (128, 8, 8, 4, 1, 1, 1, "gelu_erf"), (128, 4, 16, 1, 1, 3, 203, "relu"), (128, 8, 32, 2, 1, 5, 97, "gelu_erf"), (128, 8, 8, 3, 1, 6, 643, "gelu_erf"),
+    (128, 8, 4, 4, 1, 3, 61, "gelu_erf"), (256, 8, 8, 1, 2, 3, 83, "gelu_erf"), (256, 16, 16, 4, 1, 6, 401, "gelu_erf"), (256, 8, 32, 2, 1, 3, 100, "relu"),
+    (256, 16, 8, 2, 1, 1, 3, "relu")])
+def test_group_sums(d, inner_heads, K, ffn_mult, layers, B, L, act):
+    from test_gpu_parity import _check, _runner, TOL
+    from oracle import longer_oracle as orc
+    cfg = synth.CONFIGS["C2"].replace(B=B, L=L, K=K, d=d, heads=8, inner_heads=inner_heads, ffn_mult=ffn_mult, inner_layers=layers, act=act,
+                                      k_recent=3, n_self=1, ragged=True, len_lo=0, len_hi=L, index=91)
+    case = synth.make_case(cfg)
+    case["lens"][0] = L
+    if B > 3:
+        case["lens"][1:4] = [0, min(L, 5), 0]
+    case["H"][0] = synth.round_bf16(np.random.default_rng(14).standard_normal(case["H"][0].shape).astype(np.float32))
+    r = _runner(case)
+    _check("longer_token_merge", r.token_merge(), orc.token_merge(cfg, case["weights"]["inner"], case["H"], case["lens"]), TOL["bf16"])
+    _check("longer_inner_transformer", r.inner_transformer(), orc.inner_transformer(cfg, case["weights"]["inner"], case["H"], case["lens"]), TOL["bf16"])
+    Y, logits = r.forward()[:2]
+    Yr, lr = orc.forward(cfg, case["weights"], case["H"], case["G"], case["lens"])
+    _check("longer_forward", Y, Yr, TOL["bf16"])
