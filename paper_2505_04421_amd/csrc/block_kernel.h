@@ -202,6 +202,44 @@ __device__ __forceinline__ f16x8 gelu_quarter_phi_h8(f16x8 y) {      // its seco
 }
 __device__ __forceinline__ f16x8 gelu_quarter_h8(f16x8 y) { return y * gelu_quarter_phi_h8(y); }
 
+// The packed activation of a hidden tile (gelu_quarter_h8) in stages of four packed instructions, one behind a matrix instruction each: sixteen a tile
+// (kStages per operand group).  Every stage's first operand passes through an empty asm statement, or the compiler gathers them in front of the products.
+template <bool RELU>
+struct HiddenStages {
+  static constexpr int kStages = RELU ? 2 : 8;
+  f16x8 y, v, p;
+  static __device__ __forceinline__ void pin(f16x8& x) {
+    u32x4 t = __builtin_bit_cast(u32x4, x);
+    asm volatile("" : "+v"(t));
+    x = __builtin_bit_cast(f16x8, t);
+  }
+  // stage st of operand group gg of the tile a; the last one gives the group
+  __device__ __forceinline__ f16x8 run(const f32x16& a, int gg, int st) {
+    if (st == 0) {          // pairs of elements to fp16 (toward zero: never to infinity)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float lo = a[8 * gg + 2 * e], up = a[8 * gg + 2 * e + 1];
+        asm volatile("" : "+v"(lo), "+v"(up));
+        const f16x2 y2 = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(lo, up));
+        y[2 * e] = y2[0]; y[2 * e + 1] = y2[1];
+      }
+      return y;
+    }
+    if (st == 1 || RELU) pin(y); else if (st == 2) pin(v); else pin(p);
+    if (RELU) return __builtin_elementwise_max(y, (f16x8)((_Float16)0.f));
+    if (st == 1) v = y * y;
+    else if (st == 2) p = __builtin_elementwise_fma((f16x8)((_Float16)2.4554419175668456f), v, (f16x8)((_Float16)-6.304095499217479f));
+    else if (st == 3) p = __builtin_elementwise_fma(p, v, (f16x8)((_Float16)6.604333663059149f));
+    else if (st == 4) p = __builtin_elementwise_fma(p, v, (f16x8)((_Float16)-3.771901897714043f));
+    else if (st == 5) p = __builtin_elementwise_fma(p, v, (f16x8)((_Float16)1.5736394077430096f));
+    else if (st == 6) {
+      p = __builtin_elementwise_fma(y, p, (f16x8)((_Float16)0.5f));
+      p = __builtin_elementwise_min(__builtin_elementwise_max(p, (f16x8)((_Float16)0.f)), (f16x8)((_Float16)1.f));
+    }
+    return y * p;
+  }
+};
+
 template <bool EXACT>
 __device__ __forceinline__ float gelu_fn(float x) {
   if (EXACT) return 0.5f * x * (1.0f + erff(x * 0.70710678118654752440f));

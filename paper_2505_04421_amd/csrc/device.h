@@ -22,6 +22,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace longer {
 
@@ -244,7 +245,9 @@ __device__ __forceinline__ void wait_vmcnt() {
 // push up, so they too err on the strict side.  A loop that stores in every step thus waits for those
 // stores with each panel: advance<YOUNGER>() counts them in where their number is known.  The K/V
 // projection, whose stores depend on the row, sets DRAIN and always waits for zero.
-template <int SEGV, int PSEG, int NB, bool DRAIN, int NTHR = kThreads>
+// Panels in the order they lie in.  (Another order: at(n), the place of the n-th panel, asked once each and in turn.)
+struct InOrder {};
+template <int SEGV, int PSEG, int NB, bool DRAIN, int NTHR = kThreads, typename ORDER = InOrder>
 struct WStream {
   static constexpr int PANV = SEGV * PSEG;              // 16-byte vectors per panel
   static constexpr int NSTAGE = PANV / NTHR;
@@ -255,9 +258,12 @@ struct WStream {
   unsigned lane_off;
   unsigned lds_wave;     // LDS byte address of this wave's first 16-byte slot in ring buffer 0
   int total, step, sub, issued, slot_issue, slot_cur, lane;   // total / step / issued count panels
+  ORDER order;
+  const char* g0;
 
   __device__ __forceinline__ void issue() {
     if (issued < total) {
+      if constexpr (!std::is_same<ORDER, InOrder>::value) gnext = g0 + (size_t)(unsigned)order.at(issued) * (PANV * 16);
       const unsigned dst = lds_wave + (unsigned)slot_issue * (PANV * 16);
 #pragma unroll
       for (int i = 0; i < NSTAGE; ++i) {
@@ -278,7 +284,7 @@ struct WStream {
     lds = lds_; total = (total_segments + PSEG - 1) / PSEG; step = 0; sub = 0; issued = 0; slot_issue = 0; slot_cur = 0;
     const int tid = threadIdx.x;
     lane = tid & 63;
-    gnext = reinterpret_cast<const char*>(gbase);
+    gnext = g0 = reinterpret_cast<const char*>(gbase);
     lane_off = (unsigned)tid * 16u;
     lds_wave = __builtin_amdgcn_readfirstlane((unsigned)(unsigned long long)lds_ + (unsigned)(tid >> 6) * 1024u);
 #pragma unroll
