@@ -157,9 +157,6 @@ __global__ void __launch_bounds__(64 * chain_waves(D) * quad_tiles(MODE), chain_
 #pragma unroll
     for (int i = 0; i < VQ; ++i) { const int c = tid + kThr * i; if (c < D * 4) vecl[c] = vq[i]; }
   };
-  request_vec(wl);
-  // the wave's first product of a block: Q, or (the second wave of a pair, where K and V are made here) K
-  request(fr, segment(wl, keeper || !SCORE ? sg.q(ft) : sg.k(ft)));
   // row sums of the whole tile (two numbers per row) for the waves that hold rows; every wave is behind a barrier afterwards
   auto row_sums = [&](int which, float a, float b) -> float2 {
     if (keeper) sums[which][ft][lane] = make_float2(sum_halves(a), sum_halves(b));
@@ -196,6 +193,43 @@ __global__ void __launch_bounds__(64 * chain_waves(D) * quad_tiles(MODE), chain_
     __syncthreads();
     take(0, b);
   };
+
+  request_vec(STACK && p.kv_w ? p.kv_w : wl);
+  // the wave's first product of a block: Q, or (the second wave of a pair, where K and V are made here) K
+  request(fr, segment(wl, keeper || !SCORE ? sg.q(ft) : sg.k(ft)));
+  // The stack's cross layer finds its K and V in memory.  A short user's (kv_w: the cross block's K / V stream, kv_k: the merged tokens) are made here, two
+  // key tiles at a time, a wave of a pair each; they go the same way, but no further than the workgroup that wrote them.
+  if (STACK && p.kv_w) {
+    const f32x16 queries = x;
+    request(f1, segment(p.kv_w, keeper ? 1 + 2 * ft : 2 + 2 * ft));
+    auto key_rows = [&](int kt) {
+      const int a = 32 * kt + j;
+      const bool glob = a < p.m, ok = glob || a - p.m < Tu;
+      f32x16 one[1];
+      load_rows<T, 1>(one, glob ? p.src0.p : (const void*)p.kv_k, glob ? p.src0.f32 : 1,
+                      (glob ? p.src0.ustride * usr + (long long)a * D : (long long)p.kv_w_ustride * usr + (long long)(a - p.m) * D) + 32 * ft, ok, hi);
+      return one[0];
+    };
+    f32x16 ahead = key_rows(ts);
+    for (int k0 = 0; k0 < kthi; k0 += TS) {            // (the same number of times for either tile: barriers)
+      const int kt = k0 + ts;
+      x = ahead;
+      ahead = key_rows(min(kt + TS, kthi - 1));
+      if (k0 == 0) { store_vec(); request_vec(wl); }
+      grp xn[NG];
+      normalise(0, vl.ln1_g(), vl.ln1_b(), xn);
+      f32x16 o = keeper ? product(splat16(0.f), f1, xn, false, false, nullptr) : product(splat16(0.f), f1, xn, true, false, nullptr);
+      settle(o);
+      if (kt < kthi) {
+        char* dst = (keeper ? p.kst : p.vst) + (size_t)usr * p.kv_ustride + ((size_t)(kt * NT + ft) * 2) * 1024 + lane16;
+#pragma unroll
+        for (int g = 0; g < 2; ++g) *reinterpret_cast<grp*>(dst + g * 1024) = E::pack(o, g);
+      }
+    }
+    x = queries;
+    wait_vmcnt<0>();                                   // (written, for the workgroup's other waves)
+    __syncthreads();
+  }
 
   // Areas of LDS are written once a layer (hid: once in two rounds) and each write has a barrier between itself and the last
   // reader: `vecl` the last round's, `sums` and `ops` the other LayerNorm's and the attention output's, `qx` and `kvl` the output

@@ -764,6 +764,15 @@ static int run_layer(const longer_config* c, const Shape& s, const char* packed_
   return 0;
 }
 
+// Width 64, heads of 16, at most two tiles of rows a user and one round of users (chain_kernel.h): the stack's launch makes the cross layer's K and V of up to
+// three key tiles itself.  Whole forward pass (three layers, m + k = 36), microseconds with it / with a launch of their own, 128 users of 32, 72, 96, 128, 158, 198 keys
+// 33.2 / 36.0, 39.3 / 42.0, 44.0 / 45.9, 50.6 / 51.0, 56.6 / 57.2, 64.8 / 63.4; 256 users of 72, 96, 128, 198 50.0 / 53.1, 58.8 / 60.4, 69.2 / 70.4, 93.6 / 93.9;
+// 16 users of 254 41.7 / 39.6, one of 16 30.0 / 31.6.
+constexpr int kChainKeyRows = 96;
+static bool chain_makes_kv(const longer_config* c, const Shape& s, int B, int L) {
+  return s.quad && s.es == 2 && s.D == 64 && s.DH == 16 && s.n <= 64 && B <= 256 && c->m + cdiv(L, c->K) <= kChainKeyRows;
+}
+
 // The reduced stack of every user in one launch (one workgroup per user): the query side of
 // the cross layer over the K/V fragments that run_layer(.., do_attn = false) stored, then
 // all self layers.  `packed_cross` holds the cross block in the split layout, followed directly
@@ -791,6 +800,7 @@ static int run_stack(const longer_config* c, const Shape& s, const char* packed_
   // users: width 64 39 / 53, 47 / 61, 56 / 71, 80 / 83, 95 / 101, 174 / 180, with heads of 32 features, whose line it is, 42 / 50, 50 / 57, 60 / 67, 86 / 77,
   // 102 / 94, 187 / 169; width 128 73 / 90, 87 / 105, 119 / 140, 163 / 204, 214 / 256, 411 / 489.
   if (s.quad && s.D <= 128 && s.n <= 64 && (s.D == 128 || B <= 256)) {
+    if (chain_makes_kv(c, s, B, L)) { p.kv_w = packed_cross; p.kv_k = (char*)io.src1.p; p.kv_w_ustride = (size_t)io.src1.ustride; }
     if (s.quad(MODE_STACK, 16, pair_stack(s), p, dim3(B), st)) return fail(LONGER_ERR_HIP, "stack launch failed");
     return 0;
   }
@@ -1070,7 +1080,7 @@ static int forward_impl(const longer_config* cfg, const longer_weights* w, const
   if (one_launch) {
     AttnIO io = cross_io(cfg, s, l, w8, G, w8 + l.M, 1, B, L, Y_out, 0);
     if (logits_out) { io.logits = logits_out; io.head = head; }
-    if (!few_stack_makes_kv(cfg, s, L) && (rc = run_layer(cfg, s, pk_cross, lens, B, L, io, false, st))) return rc;
+    if (!few_stack_makes_kv(cfg, s, L) && !chain_makes_kv(cfg, s, B, L) && (rc = run_layer(cfg, s, pk_cross, lens, B, L, io, false, st))) return rc;
     return run_stack(cfg, s, pk_cross, pk + pl.cross_pair, lens, B, L, io, st);
   }
   // Layer by layer.  The few-tiles kernels make the next layer's K and V of their own result rows, alternately in xb's place and in
