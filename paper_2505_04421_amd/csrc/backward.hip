@@ -991,33 +991,6 @@ __device__ __forceinline__ void write_descriptor(const StackGeom& g, int i, int*
   }
 }
 
-// R = [G; M] (merged tokens past T_u as zeros) and O = [G; the slots' merged tokens] as fp32 rows
-__global__ __launch_bounds__(256) void bw_build_rows_kernel(StackGeom g, int d, const __bf16* __restrict__ G,
-                                                            const __bf16* __restrict__ M, const __bf16* __restrict__ qlearn,
-                                                            const int* __restrict__ qdesc,
-                                                            const int* __restrict__ kdesc, float* __restrict__ Ox,
-                                                            float* __restrict__ Rx) {
-  const int n = g.m + g.k, nk = g.m + g.T, d4 = d / 4;
-  const size_t total = (size_t)g.B * (n + nk) * d4;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
-    const int c = (int)(i % d4) * 4;
-    size_t row = i / d4;
-    const bool isq = row < (size_t)g.B * n;
-    if (!isq) row -= (size_t)g.B * n;
-    const int per = isq ? n : nk;
-    const int u = (int)(row / per), r = (int)(row - (size_t)u * per);
-    const int dsc = isq ? qdesc[row] : kdesc[row];
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (dsc >= 0) {
-      const __bf16* src = dsc < kSeq ? G + ((size_t)u * g.m + dsc) * d
-                        : (isq && g.learn) ? qlearn + (size_t)(r - g.m) * d       // slot i: row i of the parameter
-                                           : M + ((size_t)u * g.T + (dsc - kSeq)) * d;
-      v = load_bf16x4(src + c);
-    }
-    *(f32x4*)((isq ? Ox : Rx) + row * d + c) = v;
-  }
-}
-
 // Head and loss (Eq. 1-2) for one user per block: logit = <head_w, the m global rows of Y> + head_b,
 // loss += (softplus form of the cross-entropy) / B, dlogit = (sigmoid(logit) - label) / B, and the
 // gradients that follow: dY (global rows dlogit head_w; the other rows have none and are not written), head_w, head_b.
@@ -1767,7 +1740,7 @@ struct StackDims { int d, f, heads, dh, m, k, n, T, B, layers; size_t rq, rk; };
 struct StackWs {
   size_t fwd_ws, Mb, dM;                  // forward token merge: its scratch, M (bf16), and the gradient handed to the merge
   size_t qdesc, kdesc, stream;
-  size_t Rx, xs;                          // cross-layer key rows; the layers' input rows ([layers + 1][rq][d], [0] = O)
+  size_t xs;                              // the input rows of layers 1 .. and the last one's output ([layers][rq][d])
   size_t qkv, stat, xmid, rec, per_layer; // every layer's intermediates are kept (per_layer bytes apart): the reduced stack is
                                           // small, only the merge is recomputed
   size_t kv, krec, o, dy, dxm, dob, dqkv, dkv, dR, part;
@@ -1832,8 +1805,7 @@ static StackWs stack_ws(const StackDims& s, size_t fwd_bytes) {
   w.qdesc = take(rq * 4);
   w.kdesc = take(rk * 4);
   w.stream = take((size_t)StackStreams(s.d, s.f, s.layers).total * packed_seg_bytes(s.d, 2));
-  w.Rx = take(rk * d * 4);
-  w.xs = take((size_t)(s.layers + 1) * rq * d * 4);
+  w.xs = take((size_t)s.layers * rq * d * 4);
   const size_t layer0 = o;
   w.qkv = take(rq * 3 * d * 2);
   w.stat = take(rq * s.heads * 8);
@@ -1899,8 +1871,8 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
   const GradLayout gl = grad_layout(d, f);
   const StackGeom geo = {lens, L, c->K, s.T, s.m, s.k, c->k_uniform, B, c->q_learn != nullptr};
   int* qdesc = (int*)(ws + w.qdesc);   int* kdesc = (int*)(ws + w.kdesc);
-  __bf16* Mb = (__bf16*)(ws + w.Mb);   float* dM = (float*)(ws + w.dM);     float* Rx = (float*)(ws + w.Rx);
-  auto xs = [&](int l) { return (float*)(ws + w.xs) + (size_t)l * rq * d; };
+  __bf16* Mb = (__bf16*)(ws + w.Mb);   float* dM = (float*)(ws + w.dM);
+  auto xs = [&](int l) { return (float*)(ws + w.xs) + (size_t)(l - 1) * rq * d; };
   auto blk = [&](int l) -> const longer_block& { return l == 0 ? wts->cross[0] : wts->self[l - 1]; };
   auto of = [&](size_t o, int l) { return ws + o + (size_t)l * w.per_layer; };      // a layer's own buffers
   auto bf = [](const void* q) { return (const __bf16*)q; };
@@ -1947,8 +1919,9 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
   int rc = block_inputs ? merge_keep_f32(c, wts->inner, H, lens, B, L, Mb, block_inputs, mi.padded * mi.d, ws + w.fwd_ws, fwd_bytes, st)
                         : longer_token_merge(c, wts->inner, H, lens, B, L, Mb, ws + w.fwd_ws, fwd_bytes, st);
   if (rc) return rc;
-  bw_build_rows_kernel<<<flat_grid((rq + rk) * d / 4), 256, 0, st>>>(geo, d, (const __bf16*)G, Mb, (const __bf16*)c->q_learn, qdesc, kdesc, xs(0), Rx);
-  BW_TRY(launched("row build"));
+  // the cross layer's rows: R = [G; M] (merged tokens past T_u are zeros) and O = [G; the slots' merged tokens]
+  const StackSource key_rows = {(const __bf16*)G, Mb, nullptr, nullptr, s.m + s.T, s.m, s.T};
+  const StackSource query_rows = {(const __bf16*)G, Mb, (const __bf16*)c->q_learn, qdesc, s.n, s.m, s.T};
   auto attn = [&](int l) {
     SetAttn t;
     const __bf16* qkv = (const __bf16*)of(w.qkv, l);
@@ -1987,11 +1960,12 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
       const longer_block& b = blk(l);
       BW_TRY(attn_forward(l));
       p.wstream = stream_at(sg.fwd_tail(l));
-      p.x = xs(l); p.o = o; p.bo = bf(b.bo); p.ln2_g = bf(b.ln2_g); p.ln2_b = bf(b.ln2_b); p.b1 = bf(b.b1); p.b2 = bf(b.b2);
+      if (l) p.x = xs(l); else p.from = query_rows;
+      p.o = o; p.bo = bf(b.bo); p.ln2_g = bf(b.ln2_g); p.ln2_b = bf(b.ln2_b); p.b1 = bf(b.b1); p.b2 = bf(b.b2);
       p.desc = qdesc; p.xmid = (float*)of(w.xmid, l); p.y = xs(l + 1); p.rec = (__bf16*)of(w.rec, l);
       if (l == last) { p.only = globals; p.rows = (int)((size_t)B * s.m); }
     } else {
-      p.wstream = stream_at(sg.fwd_head(0)); p.x = xs(0);
+      p.wstream = stream_at(sg.fwd_head(0)); p.from = query_rows;
     }
     if (l < last) {
       const longer_block& b = blk(l + 1);
@@ -2002,7 +1976,7 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
     StackFwd k = {};
     if (l < 0) {
       const longer_block& b = blk(0);
-      k.rows = (int)rk; k.f = f; k.eps = c->ln_eps; k.wstream = stream_at(sg.kv_f); k.x = Rx;
+      k.rows = (int)rk; k.f = f; k.eps = c->ln_eps; k.wstream = stream_at(sg.kv_f); k.from = key_rows;
       k.ln1_g = bf(b.ln1_g); k.ln1_b = bf(b.ln1_b); k.bias[0] = bf(b.bk); k.bias[1] = bf(b.bv);
       k.mats = 2; k.out = kv; k.ldo = 2 * d; k.rec1 = krec; k.rec1_size = key_record(d); k.rec1_xh = 0;
     }
@@ -2022,7 +1996,8 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
       // (the cross layer's keys are rows of their own; a self layer's dq, dk, dv lie side by side)
       BW_TRY(l ? attn_backward(l, 3 * d, dqkv + d, dqkv + 2 * d, 3 * d) : attn_backward(l, d, dkv, dkv + d, 2 * d));
       p.mats = l ? 3 : 1; p.wstream = stream_at(sg.bwd_tail(l));
-      p.dqkv = dqkv; p.ldq = p.mats * d; p.x = xs(l); p.ln1_g = bf(blk(l).ln1_g); p.dxm_in = l == last ? (const float*)of(w.xmid, last) : dxm;
+      if (l) p.x = xs(l); else p.from = query_rows;
+      p.dqkv = dqkv; p.ldq = p.mats * d; p.ln1_g = bf(blk(l).ln1_g); p.dxm_in = l == last ? (const float*)of(w.xmid, last) : dxm;
       p.rec1 = (__bf16*)of(w.rec, l); p.rec1_size = r.size; p.rec1_dqkv = r.qkv; p.dx = dy;
       if (l == last) p.head = globals;
     } else {
@@ -2037,7 +2012,7 @@ static int run_model(const longer_config* c, const longer_weights* wts, const vo
     StackBwd k = {};
     if (l == 0) {
       k.rows = (int)rk; k.f = f; k.eps = c->ln_eps; k.wstream = stream_at(sg.kv_b); k.mats = 2;
-      k.dqkv = dkv; k.ldq = 2 * d; k.x = Rx; k.ln1_g = bf(blk(0).ln1_g); k.rec1 = krec; k.rec1_size = key_record(d);
+      k.dqkv = dkv; k.ldq = 2 * d; k.from = key_rows; k.ln1_g = bf(blk(0).ln1_g); k.rec1 = krec; k.rec1_size = key_record(d);
       k.rec1_dqkv = d / 16; k.dx = dR;
     }
     BW_TRY(bwd(p, k));

@@ -8,6 +8,10 @@ namespace bw {
 
 constexpr int kComputeUnits = 256;
 
+// Every row carries a descriptor of its token: -1 invalid, a for global token a, kSeq + t for the sequence token
+// with merged index t (a learnable query token stands after the newest one).
+constexpr int kSeq = 1 << 24;
+
 // Padded token rows (row r = u L + pos with pos >= the user's length) carry no gradient.  With the
 // batch's geometry at hand a kernel leaves them out: row GEMMs skip tiles without a valid row, the
 // gradient GEMMs read them as zeros and pass over steps that hold nothing else, the LayerNorm kernels

@@ -23,9 +23,6 @@ namespace bw {
 
 using longer::settle;
 
-// Every row carries a descriptor of its token: -1 invalid, a for global token a, kSeq + t for the sequence token
-// with merged index t (a learnable query token stands after the newest one).
-constexpr int kSeq = 1 << 24;
 constexpr int kAttnRows = 128;      // rows of a workgroup
 constexpr int kAttnChunk = 288;     // staged rows of the other side: m + T = 258 at the headline batch in one go
 
