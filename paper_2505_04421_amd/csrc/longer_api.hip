@@ -660,9 +660,12 @@ static int run_merge(const longer_config* c, const Shape& s, const char* packed,
     if (launch_few_f32(MODE_MERGE, win, p, dim3((unsigned)cdiv(slots, 32)), st)) return fail(LONGER_ERR_HIP, "merge kernel launch failed");
     return 0;
   }
-  // Width 128, feature-tile-per-wave against merge_kernel.h, 512 000 tokens: one block, K = 8 235 / 236 us, K = 16 228 / 240, 512 users of 100 to 5000 tokens
-  // 645 / 663; two blocks, K = 8 432 / 427 (the one that hands on every token takes 210 there and 197 here).
-  if (s.user_merge && !in && !keep && (s.Di == 256 || (p.pool && c->inner_layers == 1))) {
+  // Width 128, feature-tile-per-wave against merge_kernel.h, 512 000 tokens: one block, K = 8 235 / 236 us, K = 16 235 / 238, 512 users of 100 to 5000 tokens
+  // 645 / 663; two blocks, K = 8 432 / 427 (the one that hands on every token takes 210 there and 197 here).  Its workgroups, each four tiles from the
+  // first weight to the last, pay only where many follow one another on a compute unit: one block of 32 000 tokens 29.4 / 27.5, 192 000 104 / 104,
+  // 320 000 159 / 157, 384 000 185 / 183.5.
+  const bool many = slots > 3584 * 32LL * kUserMergeTiles;      // seven rounds of two workgroups a compute unit
+  if (s.user_merge && !in && !keep && (s.Di == 256 || (p.pool && c->inner_layers == 1 && many))) {
     if (s.user_merge(win, p, dim3((unsigned)cdiv(slots, 32LL * kUserMergeTiles)), st)) return fail(LONGER_ERR_HIP, "merge kernel launch failed");
     return 0;
   }

@@ -31,3 +31,25 @@ def test_group_sums(d, inner_heads, K, ffn_mult, layers, B, L, act):
     Y, logits = r.forward()[:2]
     Yr, lr = orc.forward(cfg, case["weights"], case["H"], case["G"], case["lens"])
     _check("longer_forward", Y, Yr, TOL["bf16"])
+
+
+@pytest.mark.parametrize("inner_heads,K,L,act", [(8, 8, 643, "gelu_erf"), (4, 16, 401, "relu"), (8, 32, 97, "gelu_erf")])
+def test_group_sums_of_many_users(inner_heads, K, L, act):
+    """Width 128 takes this kernel beyond 3584 workgroups of 128 slots: the case's users again and again, the last workgroup partly empty, and each copy
+    against the oracle's one result (a user's groups lie anywhere in a workgroup)."""
+    from test_gpu_parity import _check, _runner, TOL
+    from oracle import longer_oracle as orc
+    cfg = synth.CONFIGS["C2"].replace(B=6, L=L, K=K, d=128, heads=8, inner_heads=inner_heads, ffn_mult=2, inner_layers=1, act=act, k_recent=3, n_self=1,
+                                      ragged=True, len_lo=0, len_hi=L, index=91)
+    case = synth.make_case(cfg)
+    case["lens"][0] = L
+    case["lens"][1:4] = [0, min(L, 5), 0]
+    ref = orc.token_merge(cfg, case["weights"]["inner"], case["H"], case["lens"])
+    copies = 3584 * 128 // (6 * -(-L // K) * K) + 1
+    case["cfg"] = cfg.replace(B=6 * copies)
+    case["H"] = np.tile(case["H"], (copies, 1, 1))
+    case["lens"] = np.tile(case["lens"], copies)
+    case["G"] = np.tile(case["G"], (copies, 1, 1))
+    M = _runner(case).token_merge()
+    for i in (0, 1, copies // 2, copies - 1):
+        _check("copy %d" % i, M[6 * i:6 * i + 6], ref, TOL["bf16"])
