@@ -583,6 +583,8 @@ __global__ void __launch_bounds__(64 * user_waves(D, MODE), MODE == MODE_MERGE &
     // A wave's row tiles in two halves, so that either half's activation goes behind the matrix instructions of the other one's products, first or
     // second (the two waves of a SIMD meet at every barrier and had nothing but the activation to do at the same time): 256 users of 108 rows at
     // width 256, concat merge, 340 -> 330 us a pass, the stack of 512 users of 72 rows at width 128 168 -> 161.
+    // Two row tiles at width 256 (one wave a SIMD) stay together: 256 users of 64 rows there 69.4 us, in halves 71.1.
+    constexpr bool SPLIT = RT > 2 || D == 128;
     typedef std::integral_constant<int, 0> T0; typedef std::integral_constant<int, (RT + 1) / 2> TH; typedef std::integral_constant<int, RT> T1;
     constexpr int H = TH::value;
     for (int c0 = 0; c0 < NC; c0 += WV) {            // (FF is a multiple of d: every wave has a chunk)
@@ -605,14 +607,38 @@ __global__ void __launch_bounds__(64 * user_waves(D, MODE), MODE == MODE_MERGE &
         }
       };
       auto nothing = [](int) {};
+      // what follows on these chunks' second product: the next hidden chunk, or the next block's first
+      auto following = [&]() __attribute__((always_inline)) -> gchar* {
+        return c0 + WV >= NC && !last ? segment(wnext, QuadSegs<LAYOUT, D>{NC, false}.q(ft)) : segment(wl, sg.w1(min(c0 + WV, NC - WV) + ft));
+      };
+      if constexpr (!SPLIT) {
+        product(ah, plain, normed, mma16, [&](int s) { fr[s] = load(segment(wl + 2048 * ft, sg.w2(c0 + s / 2)), s & 1); });
+        if (c0 > 0) __syncthreads();                 // everybody has read the chunks before
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+#pragma unroll
+          for (int g = 0; g < 2; ++g) {
+            f16x8 y;     // ah holds x / kFfnScale; to fp16 toward zero, then the packed activation
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const f16x2 y2 = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(ah[rt][8 * g + 2 * e], ah[rt][8 * g + 2 * e + 1]));
+              y[2 * e] = y2[0]; y[2 * e + 1] = y2[1];
+            }
+            y = RELU ? __builtin_elementwise_max(y, (f16x8)((_Float16)0.f)) : gelu_quarter_h8(y);
+            mid[t0 + rt][ft][g][lane] = __builtin_bit_cast(grp, y);
+          }
+        }
+        gchar* next = following();
+        __syncthreads();
+        product(x, plain, middle, mma_h, [&](int s) { fr[s] = load(next, s); });
+        continue;
+      }
       part(ah, T0{}, TH{}, normed, mma16, nothing, nothing);
       part(ah, TH{}, T1{}, normed, mma16, [&](int s) { fr[s] = load(segment(wl + 2048 * ft, sg.w2(c0 + s / 2)), s & 1); },
            [&](int n) __attribute__((always_inline)) { stages(0, H, n, NG * (RT - H)); });
       __syncthreads();
       part(x, T0{}, TH{}, middle, mma_h, nothing, [&](int n) __attribute__((always_inline)) { stages(H, RT - H, n, NG * H); });
-      // what follows on these chunks' second product: the next hidden chunk, or the next block's first
-      gchar* next = segment(wl, sg.w1(min(c0 + WV, NC - WV) + ft));
-      if (c0 + WV >= NC && !last) next = segment(wnext, QuadSegs<LAYOUT, D>{NC, false}.q(ft));
+      gchar* next = following();
       __syncthreads();
       part(x, TH{}, T1{}, middle, mma_h, [&](int s) { fr[s] = load(next, s); }, nothing);
     }
