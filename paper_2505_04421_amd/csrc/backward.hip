@@ -1292,7 +1292,10 @@ static int launch(WgradBatch& w, float* part, hipStream_t st) {
   w.place(part);
   const unsigned grid = (unsigned)((w.a.nslices + 7) / 8 * 8 * w.a.tiles);
   if (w.tiled) {
-    if (w.tb == 128) bw_wgrad_kernel<128, true><<<grid, 256, 0, st>>>(w.a);
+    if (w.a.job[0].groups) {             // (a job of groups is the first one)
+      if (w.tb == 128) bw_wgrad_kernel<128, true, true><<<grid, 256, 0, st>>>(w.a);
+      else bw_wgrad_kernel<64, true, true><<<grid, 256, 0, st>>>(w.a);
+    } else if (w.tb == 128) bw_wgrad_kernel<128, true><<<grid, 256, 0, st>>>(w.a);
     else bw_wgrad_kernel<64, true><<<grid, 256, 0, st>>>(w.a);
   } else if (w.tb == 128) bw_wgrad_kernel<128, false><<<grid, 256, 0, st>>>(w.a);
   else bw_wgrad_kernel<64, false><<<grid, 256, 0, st>>>(w.a);
@@ -1608,7 +1611,7 @@ static int run_tiled(const longer_config* c, const longer_block* inner, const vo
     p.rec = at(w.rec);
     p.dx = l ? (float*)(ws + w.dy) : dH; p.dx_rows = l == 0;      // (dy in place: a tile's values are read before they are replaced)
     // (the groups' operands behind the records, which are smaller by more than that)
-    const bool grouped = l == s.layers - 1 && !p.concat && group_operands(s.K);
+    const bool grouped = l == s.layers - 1 && !p.concat && group_operands(d, s.K);
     GroupOperands go = {};
     if (grouped) {
       p.gx = p.rec + s.padded / 32 * BlockRecord(d, f, true).size * 512;

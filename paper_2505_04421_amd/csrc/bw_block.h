@@ -46,8 +46,9 @@ struct BlockBwParams {
 // mean of a group's activated hidden values, in two bf16 parts (the value and what its rounding left), times the merged token's gradient.  At K = 8
 // these are 288 instead of 1280 bytes a token, written here and read by the gradients: step of the headline model 3725 -> 3610 us (the block 826 -> 788, its
 // gradients 388 -> 348), from the raw inputs 1108 -> 1073, of the small model 249 -> 244; W2's gradient comes out 2 to 4 % closer to double precision.  Tile blocks of 32 groups: x [2 t + part][f / 16], y [t][d / 16].
-// For K = 8 and 16: below, two parts of few tokens save little; at 32 a group is a whole tile.
-__host__ __device__ inline bool group_operands(int K) { return K == 8 || K == 16; }
+// For K = 8, and 16 at width 128: below, two parts of few tokens save little; at 32 a group is a whole tile; below width 128 a token's W2 operands are a smaller
+// share of its record, and at K = 16 the readers' masks cost as much (65 536 tokens of width 64: K = 8 241 / 246 us a step, K = 16 294 / 291).
+__host__ __device__ constexpr bool group_operands(int d, int K) { return K == 8 || (K == 16 && d >= 128); }
 __host__ __device__ inline size_t group_tiles(size_t slots, int K) { return (slots / K + 31) / 32; }
 
 // A tile's record: all of its tile blocks side by side (xh: normalised rows before gain and shift; the gradients of q, k,
@@ -755,7 +756,7 @@ inline void bw_block_launch_d(int dh, const BlockBwParams& p, hipStream_t st) {
   const size_t lds = (size_t)bw_block_vec_floats(D, p.f) * 4;
 #define LONGER_BW_BLOCK(DH, W)                                                                                    \
   do {                                                                                                            \
-    if constexpr (W < 16) { if (p.gx) { bw_block_kernel<D, DH, W, true><<<grid, 64 * kBlkWaves, lds, st>>>(p); break; } } \
+    if constexpr (group_operands(D, 2 * W)) { if (p.gx) { bw_block_kernel<D, DH, W, true><<<grid, 64 * kBlkWaves, lds, st>>>(p); break; } } \
     bw_block_kernel<D, DH, W, false><<<grid, 64 * kBlkWaves, lds, st>>>(p);                                       \
   } while (0)
   if (dh == 16) { if (p.K <= 8) LONGER_BW_BLOCK(16, 4); else if (p.K == 16) LONGER_BW_BLOCK(16, 8); else LONGER_BW_BLOCK(16, 16); }

@@ -40,7 +40,9 @@ struct WgradArgs { WgradJob job[kMaxWgradJobs]; int njobs, tiles, nslices; };
 // their operands' rows, run on one accelerator die (one L2).
 // TILES: the operands are tile blocks in records (bw_block.h: rows are slots; ldx, ldy: sixteens of features from one tile to the next).  A step's
 // tile is then contiguous in memory and goes to LDS as it is (a block of the headline batch 392 -> 370 us).
-template <int TB, bool TILES>
+// GROUPED: a job may be of groups (with that read from the job in every launch's steps, those without one were slower too: 110 -> 115 us and 70 -> 75 us at
+// width 64, 187 000 rows; both kinds' loops in one kernel 188 and 118)
+template <int TB, bool TILES, bool GROUPED = false>
 __global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const WgradArgs a) {
   constexpr int PITCH = TB + 16, TT = TB / 64, NCH = TB / 64;     // NCH: 16-byte chunks per thread, operand and step
   constexpr int CPR = TB / 8;                                     // chunks per row
@@ -80,7 +82,7 @@ __global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const 
   const bool bias_sum = tm == 0 && wm == 0;
   bf16x8 ones;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)(TILES && jb.groups ? 0.5f : 1.f);
+  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)(GROUPED && jb.groups ? 0.5f : 1.f);
 
   // Steps on their way from memory (registers: 16 a step at TB = 128, 8 at 64).  One, three workgroups a compute unit: steps of the headline, small
   // and raw-inputs models 4392 / 315 / 1291 us; two at the same occupancy, with spills at TB = 128: 4536 / 313 / 1317; this, two workgroups
@@ -88,7 +90,7 @@ __global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const 
   constexpr int PD = TB == 128 ? 3 : 4;
   bf16x8 rx[PD][NCH], ry[PD][NCH];
   bool there[PD][NCH];                       // (groups)
-  auto first_row = [&](int kt) { const int k0 = (kfirst + kt * kstride) * 32; return TILES && jb.groups ? (k0 >> 6) << 5 : k0; };
+  auto first_row = [&](int kt) { const int k0 = (kfirst + kt * kstride) * 32; return GROUPED && jb.groups ? (k0 >> 6) << 5 : k0; };
   auto gload = [&](int p, int kt) {
     const int k0 = (kfirst + kt * kstride) * 32;
 #pragma unroll
@@ -98,8 +100,8 @@ __global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const 
         const size_t tile = (size_t)(k0 >> 5);
         const int gx = min(m0 / 16 + (c >> 6), jb.m / 16 - 1), gy = min(n0 / 16 + (c >> 6), jb.n / 16 - 1);
         rx[p][i] = *(const bf16x8*)(X + (tile * jb.ldx + gx) * 512 + 8 * (c & 63));
-        ry[p][i] = *(const bf16x8*)(Y + ((jb.groups ? tile >> 1 : tile) * jb.ldy + gy) * 512 + 8 * (c & 63));
-        if (jb.groups) {
+        ry[p][i] = *(const bf16x8*)(Y + ((GROUPED && jb.groups ? tile >> 1 : tile) * jb.ldy + gy) * 512 + 8 * (c & 63));
+        if (GROUPED && jb.groups) {
           const int r = first_row(kt) + (((c & 63) >> 1) ^ (4 * ((c >> 6) & 1)));
           there[p][i] = r < jb.groups && row_valid(jb.rv, r);
         }
@@ -118,7 +120,7 @@ __global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const 
   auto next_step = [&](int kt) {
     while (kt < nk) {
       const int k0 = first_row(kt);
-      if (rows_any_valid(jb.rv, k0, min(TILES && jb.groups ? jb.groups : jb.rows, k0 + 32))) break;
+      if (rows_any_valid(jb.rv, k0, min(GROUPED && jb.groups ? jb.groups : jb.rows, k0 + 32))) break;
       ++kt;
     }
     return kt;
@@ -153,7 +155,7 @@ __global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const 
 #pragma unroll
       for (int i = 0; i < NCH; ++i) {
         const int c = tid + 256 * i, o = TILES ? 8 * c : (c / CPR) * PITCH + 8 * (c % CPR);
-        if (TILES && jb.groups) { rx[p][i] = keep_if(rx[p][i], there[p][i]); ry[p][i] = keep_if(ry[p][i], there[p][i]); }
+        if (GROUPED && jb.groups) { rx[p][i] = keep_if(rx[p][i], there[p][i]); ry[p][i] = keep_if(ry[p][i], there[p][i]); }
         *(bf16x8*)&sx[o] = rx[p][i];
         *(bf16x8*)&sy[o] = ry[p][i];
       }
@@ -203,7 +205,8 @@ __global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const 
 // m rows and then its n-vector, goes to out + j (m nb + nb).  m = 0: a plain vector of n (the LayerNorms' [gain | shift]).
 // A workgroup sums 4 CX adjacent outputs, its 256 / CX rows of threads each every (256 / CX)-th slice: CX = 64 or 128 for the
 // matrices (a thread has about ten slices to ask for at once; with 16 it was one or two, and 15 000 workgroups came and went: 28.8 -> 16.8 us for the 56 MB of a
-// step of the headline model), 4 for the vectors (hundreds of slices).  Every sum is taken in a fixed order.
+// step of the headline model), 16 for small ones of many slices (64 x 256 of 40 slices, where 64 left too few workgroups: 14.0 -> 10.6 us), 4 for the
+// vectors (hundreds of slices).  Every sum is taken in a fixed order.
 struct ReduceJob {
   const float* part; float* out;
   long long sstride, plstride, olstride;    // floats from slice to slice, from layer to layer (partial, output)
@@ -296,7 +299,7 @@ struct ReduceBatch {
            long long olstride) {
     ReduceJob& j = a.job[a.njobs++];
     j.part = part; j.out = out; j.sstride = sstride; j.nslices = nslices; j.m = m; j.n = n; j.nb = nb; j.layers = layers;
-    j.plstride = plstride; j.olstride = olstride; j.cxlog = !m ? 2 : nslices > 16 ? 6 : 7;
+    j.plstride = plstride; j.olstride = olstride; j.cxlog = !m ? 2 : nslices > 16 ? (m * n <= 16384 ? 4 : 6) : 7;
     const long long groups = ((long long)m * n + n) / 4;
     j.blocks = (int)((groups + (1 << j.cxlog) - 1) >> j.cxlog);
     j.first = blocks;
