@@ -189,7 +189,7 @@ __device__ __forceinline__ uint32_t range_bits(int lo, int hi, int base) {
 // overflows gives an infinite polynomial of the right sign, which the clamp turns into 0 or 1.
 // A whole operand group (8 elements, 4 register pairs) goes through each step together, so that
 // an instruction never uses the result of the one right before it (which costs a wait state).
-__device__ __forceinline__ f16x8 gelu_quarter_phi_h8(f16x8 y) {      // its second factor
+__device__ __forceinline__ f16x8 gelu_quarter_h8(f16x8 y) {
   const f16x8 v = y * y;
   f16x8 pl = (f16x8)((_Float16)2.4554419175668456f);
   pl = __builtin_elementwise_fma(pl, v, (f16x8)((_Float16)-6.304095499217479f));
@@ -198,9 +198,8 @@ __device__ __forceinline__ f16x8 gelu_quarter_phi_h8(f16x8 y) {      // its seco
   pl = __builtin_elementwise_fma(pl, v, (f16x8)((_Float16)1.5736394077430096f));
   f16x8 phi = __builtin_elementwise_fma(y, pl, (f16x8)((_Float16)0.5f));
   phi = __builtin_elementwise_min(__builtin_elementwise_max(phi, (f16x8)((_Float16)0.f)), (f16x8)((_Float16)1.f));
-  return phi;
+  return y * phi;
 }
-__device__ __forceinline__ f16x8 gelu_quarter_h8(f16x8 y) { return y * gelu_quarter_phi_h8(y); }
 
 // The packed activation of a hidden tile (gelu_quarter_h8) in stages of four packed instructions, one behind a matrix instruction each: sixteen a tile
 // (kStages per operand group).  Every stage's first operand passes through an empty asm statement, or the compiler gathers them in front of the products.
