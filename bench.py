@@ -142,7 +142,7 @@ def run_merge_backward(lg, torch, cfg, case, steps):
             "roofline": {"bound": "hbm", "achieved": nbytes / (ms * 1e-3) / 1e9, "peak": 8000.0, "unit": "GB/s",
                          "frac": nbytes / (ms * 1e-3) / 1e9 / 8000.0,
                          "bytes_per_step": nbytes,
-                         "traffic": 13.1e9 if cfg.name == "C3" else None,
+                         "traffic": 11.9e9 if cfg.name == "C3" else None,
                          "traffic_source": "profiles/merge_backward_c3_hbm_traffic.md" if cfg.name == "C3" else None,
                          "note": "one launch per block, one for its parameter gradients: what these contract makes one trip through memory each "
                                  "way (tally in paper_2505_04421_amd/flops.py)"},
