@@ -92,7 +92,7 @@ static user_fn find_user(int dtype, int D, int DH) {
   return nullptr;
 }
 
-// and its merge: bf16, d = 256, and d = 128 where only the groups' means leave
+// and its merge: bf16, d = 256, and d = 128 where only the groups' means leave of many tokens
 static user_fn find_user_merge(int dtype, int D, int DH) {
   if (one_wave_only() || dtype != LONGER_BF16 || (D != 128 && D != 256)) return nullptr;
   if (D == 128) return DH == 16 ? &launch_user_merge<128, 16> : DH == 32 ? &launch_user_merge<128, 32> : nullptr;

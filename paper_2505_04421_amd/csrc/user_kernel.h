@@ -3,7 +3,7 @@
 //
 //   MODE_STACK  the whole reduced stack of a user (Eq. 10) with at most four tiles, d = 128 / 256;
 //   MODE_MERGE  the InnerTrans blocks and the merge (Section 3.4) of four tiles of raw tokens, d = 256, and d = 128 with four waves where only the
-//               groups' means leave and there is one block.
+//               groups' means leave, there is one block and many workgroups follow one another.
 //
 // Why.  The kernels that give a row tile to one or two waves read every weight fragment once per row tile out of an LDS ring, and at
 // width 256 there is no room beside such a ring for a user's K and V: one wave per SIMD, every wait exposed.  Here a fragment
