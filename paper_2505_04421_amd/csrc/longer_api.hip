@@ -48,8 +48,6 @@ template <> int launch_user<128, 32>(int, const BlockParams&, dim3, hipStream_t)
 template <> int launch_user<256, 16>(int, const BlockParams&, dim3, hipStream_t);
 template <> int launch_user<256, 32>(int, const BlockParams&, dim3, hipStream_t);
 
-template <> int launch_user_merge<128, 16>(int, const BlockParams&, dim3, hipStream_t);
-template <> int launch_user_merge<128, 32>(int, const BlockParams&, dim3, hipStream_t);
 template <> int launch_user_merge<256, 16>(int, const BlockParams&, dim3, hipStream_t);
 template <> int launch_user_merge<256, 32>(int, const BlockParams&, dim3, hipStream_t);
 
@@ -92,10 +90,9 @@ static user_fn find_user(int dtype, int D, int DH) {
   return nullptr;
 }
 
-// and its merge: bf16, d = 256, and d = 128 where only the groups' means leave of many tokens
+// and its merge: bf16, d = 256
 static user_fn find_user_merge(int dtype, int D, int DH) {
-  if (one_wave_only() || dtype != LONGER_BF16 || (D != 128 && D != 256)) return nullptr;
-  if (D == 128) return DH == 16 ? &launch_user_merge<128, 16> : DH == 32 ? &launch_user_merge<128, 32> : nullptr;
+  if (one_wave_only() || dtype != LONGER_BF16 || D != 256) return nullptr;
   return DH == 16 ? &launch_user_merge<256, 16> : DH == 32 ? &launch_user_merge<256, 32> : nullptr;
 }
 
@@ -660,12 +657,7 @@ static int run_merge(const longer_config* c, const Shape& s, const char* packed,
     if (launch_few_f32(MODE_MERGE, win, p, dim3((unsigned)cdiv(slots, 32)), st)) return fail(LONGER_ERR_HIP, "merge kernel launch failed");
     return 0;
   }
-  // Width 128, feature-tile-per-wave against merge_kernel.h, 512 000 tokens: one block, K = 8 235 / 236 us, K = 16 235 / 238, 512 users of 100 to 5000 tokens
-  // 645 / 663; two blocks, K = 8 432 / 427 (the one that hands on every token takes 210 there and 197 here).  Its workgroups, each four tiles from the
-  // first weight to the last, pay only where many follow one another on a compute unit: one block of 32 000 tokens 29.4 / 27.5, 192 000 104 / 104,
-  // 320 000 159 / 157, 384 000 185 / 183.5.
-  const bool many = slots > 3584 * 32LL * kUserMergeTiles;      // seven rounds of two workgroups a compute unit
-  if (s.user_merge && !in && !keep && (s.Di == 256 || (p.pool && c->inner_layers == 1 && many))) {
+  if (s.user_merge && !in && !keep) {
     if (s.user_merge(win, p, dim3((unsigned)cdiv(slots, 32LL * kUserMergeTiles)), st)) return fail(LONGER_ERR_HIP, "merge kernel launch failed");
     return 0;
   }

@@ -2,8 +2,7 @@
 // every product's result, its heads) for several row tiles:
 //
 //   MODE_STACK  the whole reduced stack of a user (Eq. 10) with at most four tiles, d = 128 / 256;
-//   MODE_MERGE  the InnerTrans blocks and the merge (Section 3.4) of four tiles of raw tokens, d = 256, and d = 128 with four waves where only the
-//               groups' means leave, there is one block and many workgroups follow one another.
+//   MODE_MERGE  the InnerTrans blocks and the merge (Section 3.4) of four tiles of raw tokens, d = 256.
 //
 // Why.  The kernels that give a row tile to one or two waves read every weight fragment once per row tile out of an LDS ring, and at
 // width 256 there is no room beside such a ring for a user's K and V: one wave per SIMD, every wait exposed.  Here a fragment
@@ -13,7 +12,7 @@
 // Fragments are requested a product ahead as in quad_kernel.h.
 //
 // The merge at width 256: 160 000 raw tokens, one block, a wave a tile 335 us, this 303 us, with the last FFN product on
-// group sums 237.  (At width 128 a tile's wave needs half the registers and two share a SIMD: without those sums the two mappings take the same time.)
+// group sums 237.  (At width 128 a tile's wave needs half the registers and two share a SIMD: the two mappings take the same time.)
 //
 // What bounds it: at width 256 LDS, which hands every product its row operand (1 KiB per matrix instruction and wave, the
 // 128 bytes a cycle that four SIMDs can use up), at width 128 the vector work of the attention.
@@ -22,16 +21,16 @@
 
 namespace longer {
 
-constexpr int user_waves(int d, int mode) { return mode == MODE_MERGE && d == 128 ? 4 : 8; }
-constexpr int user_groups(int d, int mode) { return user_waves(d, mode) / (d / 32); }     // groups of waves that share out the row tiles
+constexpr int kUserWaves = 8;
+constexpr int user_groups(int d) { return kUserWaves / (d / 32); }     // groups of waves that share out the row tiles
 
 template <int D, int DH, int RT, int LAYOUT, bool RELU, int MODE = MODE_STACK, int W = 16, bool POOL = false>
-__global__ void __launch_bounds__(64 * user_waves(D, MODE), MODE == MODE_MERGE && D == 128 ? 2 : 1) user_kernel(const BlockParams p) {
+__global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockParams p) {
   using T = __bf16;
   using E = ET<T>;
   using grp = typename E::grp;
   using hgrp = typename E::hgrp;
-  constexpr int NT = D / 32, NG = D / 16, WV = NT, TG = user_groups(D, MODE), TS = TG * RT, HPT = 32 / DH, GPH = DH / 16, kThr = 64 * user_waves(D, MODE);
+  constexpr int NT = D / 32, NG = D / 16, WV = NT, TG = user_groups(D), TS = TG * RT, HPT = 32 / DH, GPH = DH / 16, kThr = 64 * kUserWaves;
   constexpr bool HOLD = D <= 128;                    // (width 256: no registers for the output projection's fragments through the attention)
   constexpr bool MERGE = MODE == MODE_MERGE;
   static_assert(!MERGE || TG == 1, "the merge's keys stay in their wave");
@@ -82,8 +81,8 @@ __global__ void __launch_bounds__(64 * user_waves(D, MODE), MODE == MODE_MERGE &
       there[rt] = (uint32_t)__ballot(at[rt].jj < at[rt].left);
       any |= there[rt];
     }
-    // Nothing but padding (the same tiles in every wave: all leave), before any row is asked for: half of the workgroups of 512 users of 100 to 5000
-    // tokens, whose merge took 666 instead of 645 us when they asked first.
+    // Nothing but padding (the same tiles in every wave: all leave).  Zeros by all threads, a row from 64 of them, rather than by the lanes that hold a group's first
+    // token, behind the row requests: 512 users of 100 to 2000 tokens, K = 8 995 / 1015 us, 128 of at most 5000, K = 16 522 / 527.
     if (POOL && any == 0) {
       const uint32_t groups = RT * (32u >> __builtin_ctz(p.K)), g0 = (uint32_t)blockIdx.x * groups;
       for (uint32_t i = threadIdx.x; i < groups * (D / 4); i += kThr) {
@@ -688,8 +687,8 @@ int launch_user_merge(int win, const BlockParams& p, dim3 grid, hipStream_t stre
 
 #define LONGER_USER_LAUNCH(D, DH, RT, LAY) \
   do {                                                                                                \
-    if (p.act == 1) hipLaunchKernelGGL((user_kernel<D, DH, RT, LAY, true>), grid, dim3(64 * user_waves(D, MODE_STACK)), 0, stream, p); \
-    else hipLaunchKernelGGL((user_kernel<D, DH, RT, LAY, false>), grid, dim3(64 * user_waves(D, MODE_STACK)), 0, stream, p); \
+    if (p.act == 1) hipLaunchKernelGGL((user_kernel<D, DH, RT, LAY, true>), grid, dim3(64 * kUserWaves), 0, stream, p); \
+    else hipLaunchKernelGGL((user_kernel<D, DH, RT, LAY, false>), grid, dim3(64 * kUserWaves), 0, stream, p); \
   } while (0)
 
 // (width 128 streams the pair layouts, width 256 the plain ones)
@@ -709,9 +708,8 @@ int launch_user_merge(int win, const BlockParams& p, dim3 grid, hipStream_t stre
   }
 #define LONGER_USER_MERGE_LAUNCH(D, DH, WV, POOL) \
   do {                                                                                                \
-    const dim3 threads(64 * user_waves(D, MODE_MERGE));                                               \
-    if (p.act == 1) hipLaunchKernelGGL((user_kernel<D, DH, kUserMergeTiles, QUAD_PLAIN, true, MODE_MERGE, WV, POOL>), grid, threads, 0, stream, p); \
-    else hipLaunchKernelGGL((user_kernel<D, DH, kUserMergeTiles, QUAD_PLAIN, false, MODE_MERGE, WV, POOL>), grid, threads, 0, stream, p); \
+    if (p.act == 1) hipLaunchKernelGGL((user_kernel<D, DH, kUserMergeTiles, QUAD_PLAIN, true, MODE_MERGE, WV, POOL>), grid, dim3(64 * kUserWaves), 0, stream, p); \
+    else hipLaunchKernelGGL((user_kernel<D, DH, kUserMergeTiles, QUAD_PLAIN, false, MODE_MERGE, WV, POOL>), grid, dim3(64 * kUserWaves), 0, stream, p); \
   } while (0)
 #define LONGER_USER_MERGE_WIN(D, DH, POOL) \
   do {                                                                                                \
@@ -723,13 +721,6 @@ int launch_user_merge(int win, const BlockParams& p, dim3 grid, hipStream_t stre
   template <>                                                                                         \
   int launch_user_merge<256, DH>(int win, const BlockParams& p, dim3 grid, hipStream_t stream) {      \
     if (p.pool) LONGER_USER_MERGE_WIN(256, DH, true); else LONGER_USER_MERGE_WIN(256, DH, false);     \
-    return hipGetLastError() == hipSuccess ? 0 : -3;                                                  \
-  }
-#define LONGER_USER_MERGE_INSTANTIATE_128(DH)                                                         \
-  template <>                                                                                         \
-  int launch_user_merge<128, DH>(int win, const BlockParams& p, dim3 grid, hipStream_t stream) {      \
-    if (!p.pool) return -3;                                                                           \
-    LONGER_USER_MERGE_WIN(128, DH, true);                                                             \
     return hipGetLastError() == hipSuccess ? 0 : -3;                                                  \
   }
 

@@ -1,7 +1,8 @@
-"""The merge's last FFN product on the groups' sums (csrc/user_kernel.h: widths 128 and 256, bf16, K = 8, 16 and 32, mean merge).  Where that can go wrong: every
+"""The merge's last FFN product on the groups' sums (csrc/user_kernel.h: width 256, bf16, K = 8, 16 and 32, mean merge).  Where that can go wrong: every
 K against every register window, K = 4 (stays token by token), groups with fewer tokens than K (masked start values, the divisor), users without a token, a
 workgroup with nothing but padding beside one that has some, one slot, a last workgroup that is partly empty, one hidden chunk a wave and several, both
-activations, one block and several in front of it, fp32 and bf16 merged tokens (stand-alone and inside longer_forward).  Against the fp64 oracle at the bf16 bar."""
+activations, one block and several in front of it, fp32 and bf16 merged tokens (stand-alone and inside longer_forward).  The same at width 128, where every token goes through
+that product (csrc/merge_kernel.h).  Against the fp64 oracle at the bf16 bar."""
 import numpy as np
 import pytest
 import torch
@@ -35,8 +36,8 @@ def test_group_sums(d, inner_heads, K, ffn_mult, layers, B, L, act):
 
 @pytest.mark.parametrize("inner_heads,K,L,act", [(8, 8, 643, "gelu_erf"), (4, 16, 401, "relu"), (8, 32, 97, "gelu_erf")])
 def test_group_sums_of_many_users(inner_heads, K, L, act):
-    """Width 128 takes this kernel beyond 3584 workgroups of 128 slots: the case's users again and again, the last workgroup partly empty, and each copy
-    against the oracle's one result (a user's groups lie anywhere in a workgroup)."""
+    """Many rounds of workgroups, several of them with nothing but padding between others: the case's users again and again, the last workgroup partly empty, and
+    each copy against the oracle's one result (a user's groups lie anywhere in a workgroup)."""
     from test_gpu_parity import _check, _runner, TOL
     from oracle import longer_oracle as orc
     cfg = synth.CONFIGS["C2"].replace(B=6, L=L, K=K, d=128, heads=8, inner_heads=inner_heads, ffn_mult=2, inner_layers=1, act=act, k_recent=3, n_self=1,
