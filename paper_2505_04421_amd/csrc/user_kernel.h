@@ -479,7 +479,8 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
           };
           const float v0 = halves(sum[0], sum[GPW > 1 ? 1 : 0]), v1 = GPW == 4 ? halves(sum[GPW == 4 ? 2 : 0], sum[GPW == 4 ? 3 : 0]) : 0.f;
           const f16x2 h = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(v0, v1));
-          const f16x2 l = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(v0 - (float)h[0], v1 - (float)h[1]));
+          // (the rest of an infinite sum, a NaN, becomes the lowest finite number, which the infinity outweighs)
+          const f16x2 l = __builtin_elementwise_max(__builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(v0 - (float)h[0], v1 - (float)h[1])), (f16x2)((_Float16)-65504.f));
           char* at = put + par * (int)sizeof(mid[0]) + 16 * (rt * GPW + (GPW > 1 ? hi : 0));
           *(_Float16*)at = h[0];
           *(_Float16*)(at + 256) = l[0];

@@ -54,3 +54,23 @@ def test_group_sums_of_many_users(inner_heads, K, L, act):
     M = _runner(case).token_merge()
     for i in (0, 1, copies // 2, copies - 1):
         _check("copy %d" % i, M[6 * i:6 * i + 6], ref, TOL["bf16"])
+
+
+@pytest.mark.parametrize("K,L,act", [(8, 83, "gelu_erf"), (16, 83, "relu"), (32, 100, "gelu_erf")])
+def test_a_hidden_value_of_infinity(K, L, act):
+    """A hidden unit whose bias is +infinity (each of its activations is infinite, W2 gives the sign): every feature of every group with a token is an infinity of
+    that sign, not the NaN of infinity less infinity in the sum's rounding rest.  A group without a token stays zero."""
+    from test_gpu_parity import _runner
+    cfg = synth.CONFIGS["C2"].replace(B=3, L=L, K=K, d=256, heads=8, inner_heads=8, inner_layers=1, act=act, k_recent=3, n_self=1, ragged=True, len_lo=0, len_hi=L,
+                                      index=91)
+    case = synth.make_case(cfg)
+    case["lens"][:] = [L, 0, K + 3]
+    block = case["weights"]["inner"][0]
+    sign = np.where(np.random.default_rng(15).random(256) < 0.5, -1.0, 1.0).astype(np.float32)
+    block["b1"][5] = np.inf
+    block["w2"][5] = 0.5 * sign
+    M = _runner(case).token_merge()
+    for u, n in enumerate(case["lens"]):
+        groups = -(-int(n) // K)
+        assert np.array_equal(M[u, :groups], np.broadcast_to(np.inf * sign, (groups, 256))), u
+        assert not M[u, groups:].any(), u
