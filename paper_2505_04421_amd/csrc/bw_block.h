@@ -547,14 +547,16 @@ __global__ __launch_bounds__(64 * kBlkWaves, 2) void bw_block_kernel(const Block
         step(integral_constant<int, 4>{}, Swap1{}, b0); step(integral_constant<int, 2>{}, Swap2{}, b1);
       }
       const float m0 = a[0] * share, m1 = a[1] * share;
+      // what the rounding to u left, below 2^119; where u is infinite (a NaN, or an infinity, is left) a finite number, which the infinity outweighs
+      auto rest = [](float m, __bf16 u) { return fmaxf(m - (float)u, -0x1p120f); };
       if constexpr (KG == 8) {
-        const longer::bf16x2 up2 = {(__bf16)m0, (__bf16)m1}, lo2 = {(__bf16)(m0 - (float)up2[0]), (__bf16)(m1 - (float)up2[1])};
+        const longer::bf16x2 up2 = {(__bf16)m0, (__bf16)m1}, lo2 = {(__bf16)rest(m0, up2[0]), (__bf16)rest(m1, up2[1])};
         xb.put4(goff, c * 2048, __builtin_bit_cast(uint32_t, up2));
         xb.put4(goff, c * 2048 + p.f * 64, __builtin_bit_cast(uint32_t, lo2));
       } else {
         const __bf16 up1 = (__bf16)m0;
         xb.put2(goff, c * 2048, __builtin_bit_cast(uint16_t, up1));
-        xb.put2(goff, c * 2048 + p.f * 64, __builtin_bit_cast(uint16_t, (__bf16)(m0 - (float)up1)));
+        xb.put2(goff, c * 2048 + p.f * 64, __builtin_bit_cast(uint16_t, (__bf16)rest(m0, up1)));
       }
     };
     // FFN, 32 hidden features at a time: values and gradient formed, used and written out

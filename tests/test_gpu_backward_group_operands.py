@@ -2,10 +2,11 @@
 slots than a tile of 32 groups, one tile and one group more, a tile half of which no workgroup wrote (all of its tokens are padding), groups with fewer tokens
 than K (their mean's divisor), empty users, two blocks (the first one's operands stay token by token, in records of another size), concatenation (no group
 operands), every width.  The workspace starts as NaN: what nobody wrote must not count.  Oracle and bars as in test_gpu_backward."""
+import numpy as np
 import pytest
 
 import longer_synth as synth
-from test_gpu_backward import _compare
+from test_gpu_backward import _compare, _run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -27,3 +28,16 @@ def test_w2_from_group_operands(d, K, B, L, layers, merge):
         if B > 5:
             case["lens"][2:5] = [3, 0, 0]        # (L = 700: whole workgroups of padding inside a tile of 32 groups)
     _compare("d = %d, K = %d, %d x %d, %d blocks, %s" % (d, K, B, L, layers, merge), case, synth.draw_merge_gradient(cfg), ws_fill=0xFF)
+
+
+@pytest.mark.parametrize("d,K", [(128, 8), (128, 16), (64, 8)])
+def test_w2_gradient_of_an_infinite_hidden_value(d, K):
+    """A hidden unit whose bias is +infinity, upstream gradients above zero, no padding: its row of W2's gradient is +infinity (the rounding rest of an infinite mean
+    is not infinity less infinity), and every other row is finite."""
+    cfg = synth.CONFIGS["C2"].replace(d=d, heads=d // 16, inner_heads=d // 16, K=K, B=2, L=64, k_recent=5, n_self=1, inner_layers=1, act="relu", index=97)
+    case = synth.make_case(cfg)
+    case["weights"]["inner"][0]["b1"][5] = np.inf
+    _, grads = _run_gpu(case, np.abs(synth.draw_merge_gradient(cfg)) + 0.5)
+    w2 = grads[0]["w2"]
+    assert (w2[5] == np.inf).all()
+    assert np.isfinite(np.delete(w2, 5, axis=0)).all()
