@@ -64,3 +64,17 @@ def test_fp16_gelu_error_against_the_erf_form():
     with np.errstate(over="ignore", invalid="ignore"):
         assert np.all(np.abs(_emulate(big, k16) - big) <= big * 2.0 ** -10)
         assert np.all(_emulate(-big, k16) == 0.0)
+
+
+def test_every_form_of_the_polynomial_is_the_same():
+    """The packed polynomial stands in four places: whole (gelu_quarter_h8), in stages for any kernel (HiddenStages), and in stages inside the one-wave kernels' and the
+    merge kernel's loops.  Which one runs depends on a launch's size, so all have the same coefficients, 1/2 and clamp, in the same order."""
+    whole = [str(c) for c in _coefficients()[0]] + ["0.5", "0.0", "1.0"]
+    forms = []
+    for name in ("block_kernel.h", "merge_kernel.h"):
+        text = open(os.path.join(os.path.dirname(KERNEL), name)).read()
+        found = [str(float(x)) for x in re.findall(r"\(_Float16\)(-?[0-9]+\.[0-9]*)f\)", text)]
+        starts = [i for i, c in enumerate(found) if c == whole[0]]
+        forms += [found[i:i + len(whole)] for i in starts]
+        assert len(starts) == text.count(whole[0])
+    assert len(forms) == 4 and all(f == whole for f in forms), forms
