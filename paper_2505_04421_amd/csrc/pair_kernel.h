@@ -55,7 +55,8 @@ struct SkewedFfn {
   }
 };
 
-template <int D, int DH, int W, bool RELU>
+// SKEW: the activation of a pair of hidden chunks behind the second products of the pair before (where: pair_start)
+template <int D, int DH, int W, bool RELU, bool SKEW>
 __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams p) {
   using T = __bf16;
   using E = ET<T>;
@@ -105,8 +106,8 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
     tilebits = ((range_bits(gbase + (p.gmask_causal ? gi : 0), gbase + p.m, 0) & vb) >> (4 * hi)) >> (2 * W * widx);
   }
 
-  WStream<SEGV, PSEG, NB, false, kPairThreads, SkewedFfn> ws;
-  ws.order = SkewedFfn{1 + 2 * NT, 1 + 2 * NT + NC, 0};
+  WStream<SEGV, PSEG, NB, false, kPairThreads, std::conditional_t<SKEW, SkewedFfn, InOrder>> ws;
+  if constexpr (SKEW) ws.order = SkewedFfn{1 + 2 * NT, 1 + 2 * NT + NC, 0};
   ws.init(lds, p.wbase, (2 + 4 * NT + 2 * NC) * p.n_layers);
 
   uint4* const xt = xch + (size_t)ts * NG * 64 + lane;      // this tile's exchange area, this lane's 16 bytes of a group
@@ -314,70 +315,103 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
     __syncthreads();          // everybody has its copy: the exchange area is free for the activated chunks
 #pragma unroll
     for (int i = 0; i < NTH; ++i) resid[i] += bias_tile(vec + vl.b2(), 2 * i + h, hi);
-    // The activation of a chunk goes behind the second products of the pair of chunks before it (both waves of a SIMD are at the same place
-    // of the loop: with a chunk's activation between its own products the matrix pipe stood still for it: 16 x 1000 candidates at width 256, 1089 -> 1074 us).
-    HiddenStages<RELU> act;
-    constexpr int NS = HiddenStages<RELU>::kStages, NP = GPT * NS, NM = 2 * GPT * NTH;
-    typename E::hgrp hown[GPT], hoth[GPT], hnew[GPT];
-    // chunk pairs alternate between two places of the exchange area
-    auto hand = [&](int par) {
-#pragma unroll
-      for (int g = 0; g < GPT; ++g) *reinterpret_cast<typename E::hgrp*>(xt + (par * 2 * GPT + h * GPT + g) * 64) = hown[g];
-    };
-    auto take = [&](int par) {
-#pragma unroll
-      for (int g = 0; g < GPT; ++g) hoth[g] = *reinterpret_cast<const typename E::hgrp*>(xt + (par * 2 * GPT + (h ^ 1) * GPT + g) * 64);
-    };
-    // second GEMM of a pair of chunks for the own output tiles, then(n) behind the n-th product
-    auto second = [&](auto then) __attribute__((always_inline)) {
-      constexpr int AH = 4;
-      auto frag = [&](int q) { return ws.template frag_at<grp>(q & 1 ? h ^ 1 : h, (2 * (q / 2 % NTH) + h) * GPT + q / 2 / NTH); };
-      grp fr[AH];
-#pragma unroll
-      for (int q = 0; q < AH; ++q) fr[q] = frag(q);
-#pragma unroll
-      for (int q = 0; q < NM; ++q) {
-        __builtin_amdgcn_sched_barrier(0);
-        const int i = q / 2 % NTH, g = q / 2 / NTH;
-        resid[i] = E::mma_h(fr[q % AH], q & 1 ? hoth[g] : hown[g], resid[i]);
-        if (q + AH < NM) fr[q % AH] = frag(q + AH);
-        then(q);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    auto first = [&](int c) { return gemm_tile(bias_tile(vec + vl.b1(), 2 * c + h, hi), h, xo, xp); };
-    f32x16 ah = first(0);
-    ws.advance();
-    ws.advance();
-#pragma unroll
-    for (int k = 0; k < NP; ++k) { const f16x8 y = act.run(ah, k / NS, k % NS); if (k % NS == NS - 1) hown[k / NS] = y; }
-    hand(0);
+    if constexpr (!SKEW) {
 #pragma unroll 1
-    for (int c = 0; c + 1 < NC / 2; ++c) {
-      ah = first(c + 1);
-      ws.advance();
-      ws.advance();          // (the panel switch's barrier also orders the exchange: written above, read below)
-      take(c & 1);
-      second([&](int q) __attribute__((always_inline)) {
+      for (int c2 = 0; c2 < NC / 2; ++c2) {
+        // panel [w1(2 c2) w1(2 c2 + 1)]: first GEMM + activation of the own chunk
+        f32x16 ah = gemm_tile(bias_tile(vec + vl.b1(), 2 * c2 + h, hi), h, xo, xp);
+        typename E::hgrp hown[GPT], hoth[GPT];
 #pragma unroll
-        for (int k = 0; k < (NP + NM - 1) / NM; ++k) {
-          const int at = q * NP / NM + k;
-          if (at >= (q + 1) * NP / NM) continue;
-          const f16x8 y = act.run(ah, at / NS, at % NS);
-          if (at % NS == NS - 1) hnew[at / NS] = y;
+        for (int g = 0; g < GPT; ++g) {
+          f16x8 y;     // ah holds x / kFfnScale; to fp16 toward zero, then the packed activation
+#pragma unroll
+          for (int e = 0; e < E::EPL / 2; ++e) {
+            const f16x2 y2 = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(ah[E::EPL * g + 2 * e], ah[E::EPL * g + 2 * e + 1]));
+            y[2 * e] = y2[0]; y[2 * e + 1] = y2[1];
+          }
+          hown[g] = RELU ? __builtin_elementwise_max(y, (f16x8)((_Float16)0.f)) : gelu_quarter_h8(y);
+          *reinterpret_cast<typename E::hgrp*>(xt + (h * GPT + g) * 64) = hown[g];
         }
-      });
+        ws.advance();
+        ws.advance();          // (the panel switch's barrier also orders the exchange: written above, read below)
 #pragma unroll
-      for (int g = 0; g < GPT; ++g) hown[g] = hnew[g];
-      hand((c & 1) ^ 1);
+        for (int g = 0; g < GPT; ++g) hoth[g] = *reinterpret_cast<const typename E::hgrp*>(xt + ((h ^ 1) * GPT + g) * 64);
+        // panel [w2(2 c2) w2(2 c2 + 1)]: second GEMM of both chunks for the own output tiles
+#pragma unroll
+        for (int g = 0; g < GPT; ++g)
+#pragma unroll
+          for (int i = 0; i < NTH; ++i) {
+            resid[i] = E::mma_h(ws.template frag_at<grp>(h, (2 * i + h) * GPT + g), hown[g], resid[i]);
+            resid[i] = E::mma_h(ws.template frag_at<grp>(h ^ 1, (2 * i + h) * GPT + g), hoth[g], resid[i]);
+          }
+        ws.advance();
+        ws.advance();          // (its barrier: the partner has read this chunk pair before the next one is written)
+      }
+    } else {
+      // The activation of a chunk goes behind the second products of the pair of chunks before it (both waves of a SIMD are at the same place
+      // of the loop: with a chunk's activation between its own products the matrix pipe stood still for it).
+      HiddenStages<RELU> act;
+      constexpr int NS = HiddenStages<RELU>::kStages, NP = GPT * NS, NM = 2 * GPT * NTH;
+      typename E::hgrp hown[GPT], hoth[GPT], hnew[GPT];
+      // chunk pairs alternate between two places of the exchange area
+      auto hand = [&](int par) {
+#pragma unroll
+        for (int g = 0; g < GPT; ++g) *reinterpret_cast<typename E::hgrp*>(xt + (par * 2 * GPT + h * GPT + g) * 64) = hown[g];
+      };
+      auto take = [&](int par) {
+#pragma unroll
+        for (int g = 0; g < GPT; ++g) hoth[g] = *reinterpret_cast<const typename E::hgrp*>(xt + (par * 2 * GPT + (h ^ 1) * GPT + g) * 64);
+      };
+      // second GEMM of a pair of chunks for the own output tiles, then(n) behind the n-th product
+      auto second = [&](auto then) __attribute__((always_inline)) {
+        constexpr int AH = 4;
+        auto frag = [&](int q) { return ws.template frag_at<grp>(q & 1 ? h ^ 1 : h, (2 * (q / 2 % NTH) + h) * GPT + q / 2 / NTH); };
+        grp fr[AH];
+#pragma unroll
+        for (int q = 0; q < AH; ++q) fr[q] = frag(q);
+#pragma unroll
+        for (int q = 0; q < NM; ++q) {
+          __builtin_amdgcn_sched_barrier(0);
+          const int i = q / 2 % NTH, g = q / 2 / NTH;
+          resid[i] = E::mma_h(fr[q % AH], q & 1 ? hoth[g] : hown[g], resid[i]);
+          if (q + AH < NM) fr[q % AH] = frag(q + AH);
+          then(q);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      auto first = [&](int c) { return gemm_tile(bias_tile(vec + vl.b1(), 2 * c + h, hi), h, xo, xp); };
+      f32x16 ah = first(0);
+      ws.advance();
+      ws.advance();
+#pragma unroll
+      for (int k = 0; k < NP; ++k) { const f16x8 y = act.run(ah, k / NS, k % NS); if (k % NS == NS - 1) hown[k / NS] = y; }
+      hand(0);
+#pragma unroll 1
+      for (int c = 0; c + 1 < NC / 2; ++c) {
+        ah = first(c + 1);
+        ws.advance();
+        ws.advance();          // (the panel switch's barrier also orders the exchange: written above, read below)
+        take(c & 1);
+        second([&](int q) __attribute__((always_inline)) {
+#pragma unroll
+          for (int k = 0; k < (NP + NM - 1) / NM; ++k) {
+            const int at = q * NP / NM + k;
+            if (at >= (q + 1) * NP / NM) continue;
+            const f16x8 y = act.run(ah, at / NS, at % NS);
+            if (at % NS == NS - 1) hnew[at / NS] = y;
+          }
+        });
+#pragma unroll
+        for (int g = 0; g < GPT; ++g) hown[g] = hnew[g];
+        hand((c & 1) ^ 1);
+        ws.advance();
+        ws.advance();
+      }
+      take((NC / 2 - 1) & 1);          // (at least two pairs: FF is a multiple of D; the loop's barriers lie between)
+      second([](int) {});
       ws.advance();
       ws.advance();
     }
-    if (NC == 2) __syncthreads();
-    take((NC / 2 - 1) & 1);
-    second([](int) {});
-    ws.advance();
-    ws.advance();
   }
 
   wait_vmcnt<0>();   // nothing of the weight stream may still be in flight when the wave ends
@@ -411,10 +445,21 @@ __global__ void __launch_bounds__(kPairThreads, 1) pair_kernel(const BlockParams
 template <int D, int DH>
 int launch_pair(int win, const BlockParams& p, dim3 grid, hipStream_t stream);
 
+// The skewed FFN (plain order / skewed, microseconds, FFN of one, two, four times the width): width 256, heads of 32, 16 x 300 candidates over 125 groups, GELU 263 / 265,
+// 322 / 317, 438 / 422, ReLU 260 / 261, 315 / 313, 425 / 415; heads of 16, two, three, four times, ReLU 347 / 343, 402 / 393, 458 / 445, but GELU 356 / 358, 414 / 418,
+// 474 / 478.  Width 128, 16 x 500 candidates, GELU 158 / 161, 175 / 179, 211 / 218, ReLU 156 / 160, 172 / 176, 202 / 211: a panel is half as long there, and finding its place
+// in the skewed order and the order held between products cost more than the hidden activation.
+template <int D, int DH, int W, bool RELU>
+void pair_start(const BlockParams& p, dim3 grid, hipStream_t stream) {
+  if constexpr (D == 256 && (DH == 32 || RELU)) {
+    if (p.FF > D) { hipLaunchKernelGGL((pair_kernel<D, DH, W, RELU, true>), grid, dim3(kPairThreads), 0, stream, p); return; }
+  }
+  hipLaunchKernelGGL((pair_kernel<D, DH, W, RELU, false>), grid, dim3(kPairThreads), 0, stream, p);
+}
+
 #define LONGER_PAIR_LAUNCH(D, DH, WV) \
   do {                                                                                                \
-    if (p.act == 1) hipLaunchKernelGGL((pair_kernel<D, DH, WV, true>), grid, dim3(kPairThreads), 0, stream, p); \
-    else hipLaunchKernelGGL((pair_kernel<D, DH, WV, false>), grid, dim3(kPairThreads), 0, stream, p); \
+    if (p.act == 1) pair_start<D, DH, WV, true>(p, grid, stream); else pair_start<D, DH, WV, false>(p, grid, stream); \
   } while (0)
 
 #define LONGER_PAIR_INSTANTIATE(D, DH)                                                                \
