@@ -582,9 +582,10 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
     }
     // A wave's row tiles in two halves, so that either half's activation goes behind the matrix instructions of the other one's products, first or
     // second (the two waves of a SIMD meet at every barrier and had nothing but the activation to do at the same time): 256 users of 108 rows at
-    // width 256, concat merge, 340 -> 330 us a pass, the stack of 512 users of 72 rows at width 128 168 -> 161.
-    // Two row tiles at width 256 (one wave a SIMD) stay together: 256 users of 64 rows there 69.4 us, in halves 71.1.
-    constexpr bool SPLIT = RT > 2 || D == 128;
+    // width 256, concat merge, 340 -> 330 us a pass, with ReLU and an FFN as wide as the rows 233 -> 226.
+    // Two row tiles stay together: width 256 (one wave a SIMD), 256 users of 64 rows, 69.4 us, in halves 71.1; width 128, 180 and 512 users of 72 rows 78.3 / 79.0 and
+    // 172 / 175, 1000 of 108 409 / 406, with an FFN as wide as the rows 256 of 72 60.1 / 61.0, 512 of 108 149 / 150.
+    constexpr bool SPLIT = RT > 2;
     typedef std::integral_constant<int, 0> T0; typedef std::integral_constant<int, (RT + 1) / 2> TH; typedef std::integral_constant<int, RT> T1;
     constexpr int H = TH::value;
     for (int c0 = 0; c0 < NC; c0 += WV) {            // (FF is a multiple of d: every wave has a chunk)

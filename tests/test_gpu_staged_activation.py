@@ -1,6 +1,7 @@
 """The FFN loops whose activation goes behind other chunks' or other row tiles' products, with either activation and hidden widths of one to three times the
 rows' (the loops' entry and exit meet, an odd number of turns).  Two waves a tile (csrc/pair_kernel.h): scoring beyond 768 tiles at width 128 and 512 at 256; at 256 the
-weight panels come in another order than they lie, but for the smallest hidden width and for GELU with heads of 16.  Against the fp64 oracle at the bf16 bar; every row of
+weight panels come in another order than they lie, but for the smallest hidden width and for GELU with heads of 16.  The stack's row tiles in halves (csrc/user_kernel.h):
+three and four tiles of rows a user at width 256, more users than the launch-a-layer plan takes; together at width 128.  Against the fp64 oracle at the bf16 bar; every row of
 a long list also against the same rows in short lists (other kernels)."""
 import numpy as np
 import pytest
@@ -44,3 +45,23 @@ def test_scoring_in_two_waves(d, heads, m, U, C, ffn_mult, act):
     ref, lref = orc.score_candidates(cfg, case["weights"], orc.kv_cache_build(cfg, case["weights"], case["H"], case["lens"]), G[:, some].float().cpu().numpy())
     _check("rows", Y[:, some].reshape(-1, m, d), ref.reshape(-1, m, d), TOL["bf16"])
     assert np.abs(lo[:, some] - lref).max() < 3e-2 * np.sqrt(np.mean(lo ** 2))
+
+
+@pytest.mark.parametrize("d,heads,m,k,B,ffn_mult,act", [(128, 8, 8, 57, 173, 1, "relu"), (128, 4, 4, 124, 131, 3, "gelu_erf"), (128, 8, 16, 93, 133, 3, "relu"),
+                                                        (256, 8, 8, 64, 87, 3, "relu"), (256, 16, 8, 88, 86, 1, "gelu_erf"), (256, 8, 2, 99, 66, 1, "relu"),
+                                                        (256, 16, 32, 96, 65, 3, "gelu_erf")])
+def test_stack_of_row_tiles_in_halves(d, heads, m, k, B, ffn_mult, act):
+    from test_gpu_parity import _check, _runner, TOL
+    from oracle import longer_oracle as orc
+    tiles = -(-(m + k) // 32)
+    assert 64 < m + k <= 128 and B * tiles > (512 if d == 128 else 256)      # one launch for the stack
+    cfg = synth.CONFIGS["C2"].replace(B=B, L=300, K=4, d=d, heads=heads, inner_heads=heads, m=m, k_recent=k, n_self=2, inner_layers=1, ffn_mult=ffn_mult, act=act,
+                                      ragged=True, len_lo=0, len_hi=300, index=94)
+    case = synth.make_case(cfg)
+    case["lens"][:4] = [300, 0, 1, 131]
+    Y, logits = _runner(case).forward()
+    assert np.isfinite(Y).all() and np.isfinite(logits).all()
+    some = np.array([0, 1, 2, 3, B // 2, B - 1])
+    ref, lref = orc.forward(cfg, case["weights"], case["H"][some], case["G"][some], case["lens"][some])
+    _check("rows", Y[some], ref, TOL["bf16"])
+    assert np.abs(logits[some] - lref).max() < 3e-2 * np.sqrt(np.mean(logits ** 2))
