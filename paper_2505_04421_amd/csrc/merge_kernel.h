@@ -94,10 +94,12 @@ __global__ void __launch_bounds__(256, D == 64 ? 3 : 2) merge_kernel(const Block
   if (inrange) { len = p.lens ? p.lens[u] : p.L; len = min(max(len, 0), p.L); }
   const bool valid = inrange && pos < len;
 
-  // A workgroup whose tokens are all padding writes zeros and leaves, before any row is asked for (half of the workgroups of users of 100 to 5000 tokens; asked
-  // behind the row requests, and with a group's zeros from one lane a row: 512 such users, one block 659 / 645 us, two blocks 1145 / 1130, 128 of them
-  // 171 / 165, 2000 users of at most 600 tokens 376 / 371, width 64 314 / 310; users of full length take the same time).
-  if (!__syncthreads_or(valid ? 1 : 0)) {
+  // A workgroup whose tokens are all padding writes zeros and leaves.  Without `lens` there is none.  Raw tokens: before any row is asked for (half of the workgroups of
+  // users of 100 to 5000 tokens; asked behind the row requests, and with a group's zeros from one lane a row: 512 such users, one block 659 / 645 us, two blocks
+  // 1145 / 1130, 128 of them 171 / 165, 2000 users of at most 600 tokens 376 / 371, width 64 314 / 310).  From the inputs: behind the requests, whose
+  // address arithmetic it waits for (100 users of 2000 tokens, width 64: 54.8 / 54.3 us).
+  auto all_padding = [&]() {
+    if (__syncthreads_or(valid ? 1 : 0)) return false;
     const uint32_t slot0 = (uint32_t)blockIdx.x * 128u;
     auto zeros = [&](void* out, int is_f32, uint32_t row0, uint32_t rows, long long all) {       // rows row0 .. row0 + rows - 1 of `all`
       const long long end = min((long long)row0 + rows, all) * D;
@@ -113,8 +115,9 @@ __global__ void __launch_bounds__(256, D == 64 ? 3 : 2) merge_kernel(const Block
       if (p.Z_out) zeros(p.Z_out, p.Z_f32, slot0, 128u, groups << kl);
       if (p.M_out) zeros(p.M_out, p.M_f32, slot0 >> kl, 128u >> kl, groups);
     }
-    return;
-  }
+    return true;
+  };
+  if (!FROM_IN && p.lens && all_padding()) return;
 
   const int widx = W == 16 ? 0 : j / (2 * W);
   uint32_t wmask[16 / W];
@@ -130,6 +133,8 @@ __global__ void __launch_bounds__(256, D == 64 ? 3 : 2) merge_kernel(const Block
     const uint32_t gb = (p.K >= 32 ? 0xffffffffu : ((1u << p.K) - 1u)) << (p.K * (j / p.K));
     tilebits = ((gb & vb) >> (4 * hi)) >> (2 * W * widx);
   }
+
+  if (FROM_IN && p.lens && all_padding()) return;
 
   const int block_segs = 2 + 4 * NT + 2 * NC, mlp_segments = 2 + 2 * NC;
   FlowStream<SEGV> ws;
