@@ -47,7 +47,8 @@ struct BlockBwParams {
 // these are 288 instead of 1280 bytes a token, written here and read by the gradients: step of the headline model 3725 -> 3610 us (the block 826 -> 788, its
 // gradients 388 -> 348), from the raw inputs 1108 -> 1073, of the small model 249 -> 244; W2's gradient comes out 2 to 4 % closer to double precision.  Tile blocks of 32 groups: x [2 t + part][f / 16], y [t][d / 16].
 // For K = 8, and 16 at width 128: below, two parts of few tokens save little; at 32 a group is a whole tile; below width 128 a token's W2 operands are a smaller
-// share of its record, and at K = 16 the readers' masks cost as much (65 536 tokens of width 64: K = 8 241 / 246 us a step, K = 16 294 / 291).
+// share of its record, and at K = 16 the readers' masks cost as much (a step with them / without, 65 536 tokens of width 64: K = 8 241 / 246 us, K = 16 294 / 291; width 32,
+// steps of 16 x 200, 128 x 2000 and 400 x 3000 tokens: K = 8 110 / 109, 272 / 273, 853 / 876, K = 16 111 / 110, 250 / 259, 808 / 827: there only large ones gain).
 __host__ __device__ constexpr bool group_operands(int d, int K) { return K == 8 || (K == 16 && d >= 128); }
 __host__ __device__ inline size_t group_tiles(size_t slots, int K) { return (slots / K + 31) / 32; }
 

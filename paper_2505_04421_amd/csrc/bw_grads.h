@@ -203,9 +203,11 @@ __global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const 
 // Sums of partial results: out = sum over the slices of part[slice][m n + n], for every job (and layer) of a
 // launch.  Columns come in blocks of nb (the three matrices of [W_Q | W_K | W_V] are one job): column block j, its
 // m rows and then its n-vector, goes to out + j (m nb + nb).  m = 0: a plain vector of n (the LayerNorms' [gain | shift]).
-// A workgroup sums 4 CX adjacent outputs, its 256 / CX rows of threads each every (256 / CX)-th slice: CX = 64 or 128 for the
-// matrices (a thread has about ten slices to ask for at once; with 16 it was one or two, and 15 000 workgroups came and went: 28.8 -> 16.8 us for the 56 MB of a
-// step of the headline model), 16 for small ones of many slices (64 x 256 of 40 slices, where 64 left too few workgroups: 14.0 -> 10.6 us), 4 for the
+// A workgroup sums 4 CX adjacent outputs, its 256 / CX rows of threads each every (256 / CX)-th slice.  CX = 64 for the matrices, 128 up to 16 slices: a thread
+// has about ten slices to ask for at once (with 16 it was one or two, and 15 000 workgroups came and went: 28.8 -> 16.8 us for the 56 MB of a step of the headline
+// model; steps of 8 x 100 and 32 x 400 tokens of width 128, which have few slices, 392 and 460 us, with 64 throughout 393 and 462, with 16 409 and 473).  16 for matrices of at most
+// 16 384 elements and more slices than that, where 64 leaves too few workgroups (64 x 256 of 40 slices 14.0 -> 10.6 us; a step of 128 x 2000 tokens of
+// width 32 267 us, with 64 throughout 271, with 128 278; of 64 x 3000 tokens of width 64 425, 427, 430).  4 for the
 // vectors (hundreds of slices).  Every sum is taken in a fixed order.
 struct ReduceJob {
   const float* part; float* out;
@@ -249,7 +251,8 @@ __global__ __launch_bounds__(256) void bw_reduce_jobs_kernel(const ReduceArgs a)
 
 // ------------------------------------------------------------------------------------ host side
 // Slices of a launch with `tiles` output tiles over `rows` rows: enough workgroups to fill the chip two deep
-// (what fits a compute unit at width 128), but at least four row steps (128 rows) each.
+// (what fits a compute unit at width 128), but at least four row steps (128 rows) each.  A job with fewer rows than the launch's (groups, the last
+// layer's global rows) has as many slices, shorter ones; those beyond its last step are zeros in its sum.
 static inline int wgrad_slices(int tiles, size_t rows) {
   const int steps = (int)((rows + 31) / 32);
   int s = 2 * kComputeUnits / (tiles > 0 ? tiles : 1);
