@@ -584,8 +584,10 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
     // second (the two waves of a SIMD meet at every barrier and had nothing but the activation to do at the same time): 256 users of 108 rows at
     // width 256, concat merge, 340 -> 330 us a pass, with ReLU and an FFN as wide as the rows 233 -> 226.
     // Two row tiles stay together: width 256 (one wave a SIMD), 256 users of 64 rows, 69.4 us, in halves 71.1; width 128, 180 and 512 users of 72 rows 78.3 / 79.0 and
-    // 172 / 175, 1000 of 108 409 / 406, with an FFN as wide as the rows 256 of 72 60.1 / 61.0, 512 of 108 149 / 150.
-    constexpr bool SPLIT = RT > 2;
+    // 172 / 175, 1000 of 108 409 / 406, with an FFN as wide as the rows 256 of 72 60.1 / 61.0, 512 of 108 149 / 150.  So do a stack's four with ReLU, two stages only, and heads of 16
+    // (256 users of 108 rows, FFN of one, two, four times the width 227.9 / 232.9, 257.3 / 262.4, 320.8 / 323.2; three tiles of such rows 252.8 -> 252.0 in halves, a
+    // merge's four 102.2 -> 99.5, 148.8 -> 144.6).
+    constexpr bool SPLIT = RT > 2 && !(!MERGE && RT == 4 && DH == 16 && RELU);
     typedef std::integral_constant<int, 0> T0; typedef std::integral_constant<int, (RT + 1) / 2> TH; typedef std::integral_constant<int, RT> T1;
     constexpr int H = TH::value;
     for (int c0 = 0; c0 < NC; c0 += WV) {            // (FF is a multiple of d: every wave has a chunk)
@@ -608,9 +610,12 @@ __global__ void __launch_bounds__(64 * kUserWaves, 1) user_kernel(const BlockPar
         }
       };
       auto nothing = [](int) {};
-      // what follows on these chunks' second product: the next hidden chunk, or the next block's first
+      // what follows on these chunks' second product: the next hidden chunk, or the next block's first (chosen by a conditional expression, both places are
+      // held through the product: four tiles with heads of 16, 84 instead of 64 registers spilled together, 62 instead of 51 in halves)
       auto following = [&]() __attribute__((always_inline)) -> gchar* {
-        return c0 + WV >= NC && !last ? segment(wnext, QuadSegs<LAYOUT, D>{NC, false}.q(ft)) : segment(wl, sg.w1(min(c0 + WV, NC - WV) + ft));
+        gchar* next = segment(wl, sg.w1(min(c0 + WV, NC - WV) + ft));
+        if (c0 + WV >= NC && !last) next = segment(wnext, QuadSegs<LAYOUT, D>{NC, false}.q(ft));
+        return next;
       };
       if constexpr (!SPLIT) {
         product(ah, plain, normed, mma16, [&](int s) { fr[s] = load(segment(wl + 2048 * ft, sg.w2(c0 + s / 2)), s & 1); });

@@ -1,8 +1,8 @@
 """The FFN loops whose activation goes behind other chunks' or other row tiles' products, with either activation and hidden widths of one to three times the
 rows' (the loops' entry and exit meet, an odd number of turns).  Two waves a tile (csrc/pair_kernel.h): scoring beyond 768 tiles at width 128 and 512 at 256; at 256 the
 weight panels come in another order than they lie, but for the smallest hidden width and for GELU with heads of 16.  The stack's row tiles in halves (csrc/user_kernel.h):
-three and four tiles of rows a user at width 256, more users than the launch-a-layer plan takes; together at width 128.  Against the fp64 oracle at the bf16 bar; every row of
-a long list also against the same rows in short lists (other kernels)."""
+three and four tiles of rows a user at width 256 (four with ReLU and heads of 16 together), more users than the launch-a-layer
+plan takes; together at width 128.  Against the fp64 oracle at the bf16 bar; every row of a long list also against the same rows in short lists (other kernels)."""
 import numpy as np
 import pytest
 import torch
@@ -49,7 +49,7 @@ def test_scoring_in_two_waves(d, heads, m, U, C, ffn_mult, act):
 
 @pytest.mark.parametrize("d,heads,m,k,B,ffn_mult,act", [(128, 8, 8, 57, 173, 1, "relu"), (128, 4, 4, 124, 131, 3, "gelu_erf"), (128, 8, 16, 93, 133, 3, "relu"),
                                                         (256, 8, 8, 64, 87, 3, "relu"), (256, 16, 8, 88, 86, 1, "gelu_erf"), (256, 8, 2, 99, 66, 1, "relu"),
-                                                        (256, 16, 32, 96, 65, 3, "gelu_erf")])
+                                                        (256, 16, 2, 103, 66, 3, "relu"), (256, 16, 32, 96, 65, 3, "gelu_erf")])
 def test_stack_of_row_tiles_in_halves(d, heads, m, k, B, ffn_mult, act):
     from test_gpu_parity import _check, _runner, TOL
     from oracle import longer_oracle as orc
