@@ -1281,7 +1281,7 @@ static WgradBatch block_wgrads_tiles(int d, int f, size_t slots, RowsValid rv, c
   const BlockRecord r(d, f, go != nullptr);
   auto at = [&](int o) { return rec + (size_t)o * 512; };
   WgradBatch w(d, slots < 64 ? 64 : slots, true);      // (the groups' job has no more rows than that)
-  if (go) w.add(go->x, f / 16, f, go->y, d / 16, d, d, 64 * group_tiles(slots, go->K), RowsValid{rv.lens, rv.L / go->K, go->K}, g + gl.w2, 1, 0, 0, 0, go->groups);
+  if (go) w.add(go->x, f / 16, f, go->y, d / 16, d, d, 64 * group_tiles(slots, go->K), RowsValid{rv.lens, rv.L / go->K}, g + gl.w2, 1, 0, 0, 0, go->groups, go->K);
   else w.add(at(r.a), r.size, f, at(r.dyb), r.size, d, d, slots, rv, g + gl.w2);
   w.add(at(r.xh2), r.size, d, at(r.dh), r.size, f, f, slots, rv, g + gl.w1);
   w.add(at(r.o), r.size, d, at(r.dxmb), r.size, d, d, slots, rv, g + gl.wo);

@@ -16,18 +16,18 @@ constexpr int kSeq = 1 << 24;
 // batch's geometry at hand a kernel leaves them out: row GEMMs skip tiles without a valid row, the
 // gradient GEMMs read them as zeros and pass over steps that hold nothing else, the LayerNorm kernels
 // write zeros for them.  L = 0: every row counts (the reduced stack's rows).  A row stands for `unit` tokens (a group's sums: K).
-struct RowsValid { const int32_t* lens; int L; int unit = 1; };
-__device__ __forceinline__ bool row_valid(const RowsValid& v, int r) {
+struct RowsValid { const int32_t* lens; int L; };
+__device__ __forceinline__ bool row_valid(const RowsValid& v, int r, int unit = 1) {
   if (v.L == 0 || v.lens == nullptr) return true;
   const int u = r / v.L;
-  return (r - u * v.L) * v.unit < v.lens[u];
+  return (r - u * v.L) * unit < v.lens[u];
 }
 // any valid row in [r0, r1)?
-__device__ __forceinline__ bool rows_any_valid(const RowsValid& v, int r0, int r1) {
+__device__ __forceinline__ bool rows_any_valid(const RowsValid& v, int r0, int r1, int unit = 1) {
   if (v.L == 0 || v.lens == nullptr) return true;
   for (int u = r0 / v.L; u * v.L < r1; ++u) {
     const int first = max(r0, u * v.L) - u * v.L;
-    if (first * v.unit < v.lens[u]) return true;
+    if (first * unit < v.lens[u]) return true;
   }
   return false;
 }

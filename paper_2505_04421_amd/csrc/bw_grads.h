@@ -22,8 +22,8 @@ struct WgradJob {
   int tiles_m, tiles_n, layers;
   int nsub;                           // slices of this job per slice of the launch (a job with more rows than the others)
   int first;                          // its first tile inside a slice's tiles
-  int groups;                         // 0, or the operands are of that many groups (bw_block.h, GroupOperands): X's tile 2 t + part goes with Y's tile t, rows
-                                      // without a token, which nobody wrote, count as zeros, and db, twice what it should be, is halved
+  int groups, unit;                   // 0, or the operands are of that many groups of `unit` tokens (bw_block.h, GroupOperands): X's tile 2 t + part goes with Y's tile t,
+                                      // rows without a token, which nobody wrote, count as zeros, and db, twice what it should be, is halved
 };
 constexpr int kMaxWgradJobs = 12;
 struct WgradArgs { WgradJob job[kMaxWgradJobs]; int njobs, tiles, nslices; };
@@ -90,7 +90,8 @@ __global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const 
   constexpr int PD = TB == 128 ? 3 : 4;
   bf16x8 rx[PD][NCH], ry[PD][NCH];
   bool there[PD][NCH];                       // (groups)
-  auto first_row = [&](int kt) { const int k0 = (kfirst + kt * kstride) * 32; return GROUPED && jb.groups ? (k0 >> 6) << 5 : k0; };
+  const int two = GROUPED && jb.groups ? 1 : 0, row_end = two ? jb.groups : jb.rows, unit = GROUPED ? jb.unit : 1;
+  auto first_row = [&](int kt) { return (kfirst + kt * kstride) >> two << 5; };
   auto gload = [&](int p, int kt) {
     const int k0 = (kfirst + kt * kstride) * 32;
 #pragma unroll
@@ -100,10 +101,10 @@ __global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const 
         const size_t tile = (size_t)(k0 >> 5);
         const int gx = min(m0 / 16 + (c >> 6), jb.m / 16 - 1), gy = min(n0 / 16 + (c >> 6), jb.n / 16 - 1);
         rx[p][i] = *(const bf16x8*)(X + (tile * jb.ldx + gx) * 512 + 8 * (c & 63));
-        ry[p][i] = *(const bf16x8*)(Y + ((GROUPED && jb.groups ? tile >> 1 : tile) * jb.ldy + gy) * 512 + 8 * (c & 63));
-        if (GROUPED && jb.groups) {
+        ry[p][i] = *(const bf16x8*)(Y + ((tile >> two) * jb.ldy + gy) * 512 + 8 * (c & 63));
+        if (GROUPED && two) {
           const int r = first_row(kt) + (((c & 63) >> 1) ^ (4 * ((c >> 6) & 1)));
-          there[p][i] = r < jb.groups && row_valid(jb.rv, r);
+          there[p][i] = r < row_end && row_valid(jb.rv, r, unit);
         }
       } else {
         bf16x8 z;
@@ -120,7 +121,7 @@ __global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const 
   auto next_step = [&](int kt) {
     while (kt < nk) {
       const int k0 = first_row(kt);
-      if (rows_any_valid(jb.rv, k0, min(GROUPED && jb.groups ? jb.groups : jb.rows, k0 + 32))) break;
+      if (rows_any_valid(jb.rv, k0, min(row_end, k0 + 32), unit)) break;
       ++kt;
     }
     return kt;
@@ -155,7 +156,7 @@ __global__ __launch_bounds__(256, TB == 128 ? 2 : 3) void bw_wgrad_kernel(const 
 #pragma unroll
       for (int i = 0; i < NCH; ++i) {
         const int c = tid + 256 * i, o = TILES ? 8 * c : (c / CPR) * PITCH + 8 * (c % CPR);
-        if (GROUPED && jb.groups) { rx[p][i] = keep_if(rx[p][i], there[p][i]); ry[p][i] = keep_if(ry[p][i], there[p][i]); }
+        if (GROUPED && two) { rx[p][i] = keep_if(rx[p][i], there[p][i]); ry[p][i] = keep_if(ry[p][i], there[p][i]); }
         *(bf16x8*)&sx[o] = rx[p][i];
         *(bf16x8*)&sy[o] = ry[p][i];
       }
@@ -271,9 +272,9 @@ struct WgradBatch {
   struct Out { float* out; long long olstride; int nb; } outs[kMaxWgradJobs];
   WgradBatch(int d, size_t rows_, bool tiled_ = false) : tiled(tiled_), tb(wgrad_tile(d)), rows(rows_) {}
   void add(const __bf16* X, int ldx, int m, const __bf16* Y, int ldy, int n, int nb, size_t nrows, RowsValid rv, float* out,
-           int layers = 1, long long xstride = 0, long long ystride = 0, long long olstride = 0, int groups = 0) {
+           int layers = 1, long long xstride = 0, long long ystride = 0, long long olstride = 0, int groups = 0, int unit = 1) {
     WgradJob& j = a.job[a.njobs];
-    j.groups = groups;
+    j.groups = groups; j.unit = unit;
     j.X = X; j.Y = Y; j.ldx = ldx; j.ldy = ldy; j.m = m; j.n = n; j.rows = (int)nrows; j.rv = rv;
     j.tiles_m = (m + tb - 1) / tb; j.tiles_n = (n + tb - 1) / tb; j.layers = layers;
     j.nsub = nrows > rows ? (int)((nrows + rows - 1) / rows) : 1;
