@@ -1611,7 +1611,7 @@ static int run_tiled(const longer_config* c, const longer_block* inner, const vo
     p.rec = at(w.rec);
     p.dx = l ? (float*)(ws + w.dy) : dH; p.dx_rows = l == 0;      // (dy in place: a tile's values are read before they are replaced)
     // (the groups' operands behind the records, which are smaller by more than that)
-    const bool grouped = l == s.layers - 1 && !p.concat && group_operands(d, s.K);
+    const bool grouped = l == s.layers - 1 && !p.concat && group_operands(d, s.K, lens != nullptr);
     GroupOperands go = {};
     if (grouped) {
       p.gx = p.rec + s.padded / 32 * BlockRecord(d, f, true).size * 512;

@@ -48,8 +48,12 @@ struct BlockBwParams {
 // gradients 388 -> 348), from the raw inputs 1108 -> 1073, of the small model 249 -> 244; W2's gradient comes out 2 to 4 % closer to double precision.  Tile blocks of 32 groups: x [2 t + part][f / 16], y [t][d / 16].
 // For K = 8, and 16 at width 128: below, two parts of few tokens save little; at 32 a group is a whole tile; below width 128 a token's W2 operands are a smaller
 // share of its record, and at K = 16 the readers' masks cost as much (a step with them / without, 65 536 tokens of width 64: K = 8 241 / 246 us, K = 16 294 / 291; width 32,
-// steps of 16 x 200, 128 x 2000 and 400 x 3000 tokens: K = 8 110 / 109, 272 / 273, 853 / 876, K = 16 111 / 110, 250 / 259, 808 / 827: there only large ones gain).
+// steps of 16 x 200, 128 x 2000 and 400 x 3000 tokens: K = 8 110 / 109, 272 / 273, 853 / 876, K = 16 111 / 110, 250 / 259, 808 / 827: there only large ones gain).  Nor below
+// width 128 for users of different length: the readers look for tokens row by row, with a loop that knows groups for the other matrices too, and what either block
+// writes finds fewer lines of the other one's records in the last-level cache (width 64, 256 users of at most 512 tokens, two blocks 457 / 444 us, 128 of them, one block 243 / 241,
+// 60 of at most 4000 390 / 385; width 32, 500 of at most 1000 358 / 352).
 __host__ __device__ constexpr bool group_operands(int d, int K) { return K == 8 || (K == 16 && d >= 128); }
+inline bool group_operands(int d, int K, bool ragged) { return group_operands(d, K) && (d >= 128 || !ragged); }
 __host__ __device__ inline size_t group_tiles(size_t slots, int K) { return (slots / K + 31) / 32; }
 
 // A tile's record: all of its tile blocks side by side (xh: normalised rows before gain and shift; the gradients of q, k,

@@ -100,8 +100,8 @@ def merge_backward_work(cfg, lens: Optional[Sequence[int]] = None, B: Optional[i
     # the input gradient; the chain of block inputs as above
     last = 8 * w if getattr(cfg, "merge", "mean") == "concat" else 8 * w / cfg.K
     fused = (n - 1) * 6 * w + 4 * w + (n - 1) * 8 * w + last + (n - 1) * 8 * w + n * (6 * w + 26 * w + 4 * f + 16 * w + 4 * f)
-    # the last block's W2 operands group by group, two bf16 parts of the hidden values (mean merge, K = 8, and 16 at width 128)
-    if getattr(cfg, "merge", "mean") != "concat" and (cfg.K == 8 or (cfg.K == 16 and w >= 128)):
+    # the last block's W2 operands group by group, two bf16 parts of the hidden values (mean merge; width 128: K = 8 and 16, below: K = 8, users of one length)
+    if getattr(cfg, "merge", "mean") != "concat" and (cfg.K in (8, 16) if w >= 128 else cfg.K == 8 and lens is None):
         fused += (8 * f + 4 * w) / cfg.K - (4 * f + 4 * w)
     return {"gradient_flops": 2 * inner, "recompute_flops": recompute,
             "hbm_bytes": per_token * valid + per_padded * (B * L - valid),

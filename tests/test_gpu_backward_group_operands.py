@@ -1,7 +1,7 @@
 """The last block's W2 gradient from operands kept group by group (csrc/bw_block.h: groups of 8 and 16 tokens, mean merge).  Where that can go wrong: fewer
 slots than a tile of 32 groups, one tile and one group more, a tile half of which no workgroup wrote (all of its tokens are padding), groups with fewer tokens
 than K (their mean's divisor), empty users, two blocks (the first one's operands stay token by token, in records of another size), concatenation (no group
-operands), every width.  The workspace starts as NaN: what nobody wrote must not count.  Oracle and bars as in test_gpu_backward."""
+operands).  Below width 128 users of different length keep theirs token by token, users of one length (the last group filled up) by groups.  The workspace starts as NaN: what nobody wrote must not count.  Oracle and bars as in test_gpu_backward."""
 import numpy as np
 import pytest
 
@@ -28,6 +28,12 @@ def test_w2_from_group_operands(d, K, B, L, layers, merge):
         if B > 5:
             case["lens"][2:5] = [3, 0, 0]        # (L = 700: whole workgroups of padding inside a tile of 32 groups)
     _compare("d = %d, K = %d, %d x %d, %d blocks, %s" % (d, K, B, L, layers, merge), case, synth.draw_merge_gradient(cfg), ws_fill=0xFF)
+
+
+@pytest.mark.parametrize("d,B,L,layers", [(64, 9, 257, 2), (64, 1, 3, 1), (64, 3, 83, 1), (32, 4, 131, 1), (32, 5, 264, 2), (128, 3, 260, 1)])
+def test_w2_from_group_operands_of_users_of_one_length(d, B, L, layers):
+    cfg = synth.CONFIGS["C2"].replace(d=d, heads=d // 16, inner_heads=d // 16, K=8, B=B, L=L, k_recent=5, n_self=1, inner_layers=layers, index=97)
+    _compare("d = %d, %d x %d, %d blocks, one length" % (d, B, L, layers), synth.make_case(cfg), synth.draw_merge_gradient(cfg), ws_fill=0xFF)
 
 
 @pytest.mark.parametrize("d,K", [(128, 8), (128, 16), (64, 8)])
