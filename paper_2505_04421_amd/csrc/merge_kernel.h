@@ -94,10 +94,12 @@ __global__ void __launch_bounds__(256, D == 64 ? 3 : 2) merge_kernel(const Block
   if (inrange) { len = p.lens ? p.lens[u] : p.L; len = min(max(len, 0), p.L); }
   const bool valid = inrange && pos < len;
 
-  // A workgroup whose tokens are all padding writes zeros and leaves.  Without `lens` there is none.  Raw tokens: before any row is asked for (half of the workgroups of
-  // users of 100 to 5000 tokens; asked behind the row requests, and with a group's zeros from one lane a row: 512 such users, one block 659 / 645 us, two blocks
-  // 1145 / 1130, 128 of them 171 / 165, 2000 users of at most 600 tokens 376 / 371, width 64 314 / 310).  From the inputs: behind the requests, whose
-  // address arithmetic it waits for (100 users of 2000 tokens, width 64: 54.8 / 54.3 us).
+  // A workgroup whose tokens are all padding writes zeros and leaves.  Without `lens` there is none.  Raw tokens, workgroups that follow one another: before any row is asked
+  // for (half of the workgroups of users of 100 to 5000 tokens; asked behind the row requests, and with a group's zeros from one lane a row: 512 such users, one block
+  // 659 / 645 us, two blocks 1145 / 1130, 128 of them 171 / 165, 2000 users of at most 600 tokens 376 / 371, width 64 314 / 310).  Where all workgroups start at once the barrier
+  // ahead of the requests is time lost (59 users of at most 218 tokens 59.4 / 59.8 us a pass), and so from the inputs, whose requests have arithmetic in front of
+  // them (100 users of 2000 tokens, width 64: 54.3 / 54.8).
+  const bool ask_first = !FROM_IN && gridDim.x > (D == 64 ? 768u : 512u);
   auto all_padding = [&]() {
     if (__syncthreads_or(valid ? 1 : 0)) return false;
     const uint32_t slot0 = (uint32_t)blockIdx.x * 128u;
@@ -117,7 +119,7 @@ __global__ void __launch_bounds__(256, D == 64 ? 3 : 2) merge_kernel(const Block
     }
     return true;
   };
-  if (!FROM_IN && p.lens && all_padding()) return;
+  if (ask_first && p.lens && all_padding()) return;
 
   const int widx = W == 16 ? 0 : j / (2 * W);
   uint32_t wmask[16 / W];
@@ -134,7 +136,7 @@ __global__ void __launch_bounds__(256, D == 64 ? 3 : 2) merge_kernel(const Block
     tilebits = ((gb & vb) >> (4 * hi)) >> (2 * W * widx);
   }
 
-  if (FROM_IN && p.lens && all_padding()) return;
+  if (!ask_first && p.lens && all_padding()) return;
 
   const int block_segs = 2 + 4 * NT + 2 * NC, mlp_segments = 2 + 2 * NC;
   FlowStream<SEGV> ws;
