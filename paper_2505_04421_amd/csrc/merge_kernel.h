@@ -110,16 +110,13 @@ __global__ void __launch_bounds__(256, D == 64 ? 3 : 2) merge_kernel(const Block
         else *(uint2*)(reinterpret_cast<__bf16*>(out) + i) = make_uint2(0u, 0u);
       }
     };
-    if (MODE == MODE_INPUT) zeros(p.X_out, 0, slot0, 128u, (long long)p.B * p.L);
-    else {
-      const int kl = __builtin_ctz(p.K);
-      const long long groups = (long long)p.B * p.T;
-      if (p.Z_out) zeros(p.Z_out, p.Z_f32, slot0, 128u, groups << kl);
-      if (p.M_out) zeros(p.M_out, p.M_f32, slot0 >> kl, 128u >> kl, groups);
-    }
+    const int kl = __builtin_ctz(p.K);
+    const long long groups = (long long)p.B * p.T;
+    if (p.Z_out) zeros(p.Z_out, p.Z_f32, slot0, 128u, groups << kl);
+    if (p.M_out) zeros(p.M_out, p.M_f32, slot0 >> kl, 128u >> kl, groups);
     return true;
   };
-  if (ask_first && p.lens && all_padding()) return;
+  if constexpr (!FROM_IN) { if (ask_first && p.lens && all_padding()) return; }
 
   const int widx = W == 16 ? 0 : j / (2 * W);
   uint32_t wmask[16 / W];
@@ -136,7 +133,17 @@ __global__ void __launch_bounds__(256, D == 64 ? 3 : 2) merge_kernel(const Block
     tilebits = ((gb & vb) >> (4 * hi)) >> (2 * W * widx);
   }
 
-  if (!ask_first && p.lens && all_padding()) return;
+  if (!ask_first && p.lens && !__syncthreads_or(valid ? 1 : 0)) {      // (zeros from the lanes that have the rows: shorter, and one round does not wait for them)
+    if (inrange) {
+      if (MODE == MODE_INPUT) store_rows<T, NT>(resid, p.X_out, 0, (long long)slot * D, false, hi);
+      else {
+        if (p.Z_out) store_rows<T, NT>(resid, p.Z_out, p.Z_f32, (long long)slot * D, false, hi);
+        if (p.M_out && (slot & (uint32_t)(p.K - 1)) == 0)
+          store_rows<T, NT>(resid, p.M_out, p.M_f32, (long long)(slot >> __builtin_ctz(p.K)) * D, false, hi);
+      }
+    }
+    return;
+  }
 
   const int block_segs = 2 + 4 * NT + 2 * NC, mlp_segments = 2 + 2 * NC;
   FlowStream<SEGV> ws;
