@@ -10,7 +10,7 @@
 // What bounds it: as thirteen launches over [token, feature] tensors (two LayerNorms, three products, attention,
 // the FFN's middle, three products back, attention back, two LayerNorms back) a block of the headline batch
 // (512 000 rows of width 128) moved 18.8 KB per token beside its parameter gradients in 2.1 ms; here it is 8.0 KB (4.1 GB)
-// in 0.80 ms (to 0.84 by box): 5 TB/s, what a large copy reaches; the last block 6.7 KB (3.4 GB) in 0.79 (to 0.82), 4.3 TB/s, the groups' sums beside it.  Memory and the vector unit add up: with a third of its stores
+// in 0.80 ms (to 0.84 by card): 5 TB/s, what a large copy reaches; the last block 6.7 KB (3.4 GB) in 0.79 (to 0.82), 4.3 TB/s, the groups' sums beside it.  Memory and the vector unit add up: with a third of its stores
 // left out it took 0.80 instead of 0.90 ms, and with 9 650 instead of 10 800 vector instructions per tile (beside 808 products) 0.84.  The stream's waits
 // waited for the records' stores with it (step of the headline model 4169 -> 4100 us without that), a segment's fragments came out of LDS two at a time
 // (four: 4079), and q, k, v, which the tile reads again, passed by the caches (now not: 0.2 % there, 1 % of a step of 128 short users).
